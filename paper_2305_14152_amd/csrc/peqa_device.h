@@ -41,39 +41,18 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
 }
 
 // A pair of bf16 (16 + code), scaled and shifted in fp32 and rounded once (to nearest even) back to a
-// bf16 pair:  lo -> s_lo * lo + b_lo,  hi -> s_hi * hi + b_hi.
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+// bf16 pair:  lo -> s_lo * lo + b_lo,  hi -> s_hi * hi + b_hi.  The conversion is volatile assembly so that it stays where
+// the caller put it among its matrix instructions: those are assembly too, and the wait states that the hardware wants
+// between a vector write and a matrix read of the same register are the distance the caller keeps (the compiler, free to
+// move the conversion, put it right before its use, and the matrix instruction read the old value).
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t scale_pair(uint32_t pair, float s_lo, float b_lo, float s_hi, float b_hi)
 {
-    f32x2 v;
-    v[0] = __builtin_fmaf(__uint_as_float(pair << 16), s_lo, b_lo);
-    v[1] = __builtin_fmaf(__uint_as_float(pair & 0xFFFF0000u), s_hi, b_hi);
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-}
-
-// A pair of bf16 times a pair of fp32 factors, rounded once (to nearest even) back to a bf16 pair.
-__device__ __forceinline__ uint32_t mul_pair(uint32_t pair, float s_lo, float s_hi)
-{
-    f32x2 v;
-    v[0] = __uint_as_float(pair << 16) * s_lo;
-    v[1] = __uint_as_float(pair & 0xFFFF0000u) * s_hi;
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-}
-
-// Two fp32 rounded (to nearest even) to a bf16 pair: one conversion instruction.
-__device__ __forceinline__ uint32_t cvt_pair(float lo, float hi)
-{
-    f32x2 v;
-    v[0] = lo;
-    v[1] = hi;
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-}
-
-// c + a.lo * b.lo + a.hi * b.hi of two bf16 pairs, in fp32 (v_dot2c_f32_bf16).
-__device__ __forceinline__ float dot2_bf16(uint32_t a, uint32_t b, float c)
-{
-    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a), __builtin_bit_cast(bf16x2, b), c, false);
+    const float lo = __builtin_fmaf(__uint_as_float(pair << 16), s_lo, b_lo);
+    const float hi = __builtin_fmaf(__uint_as_float(pair & 0xFFFF0000u), s_hi, b_hi);
+    uint32_t d;
+    asm volatile("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(d) : "v"(lo), "v"(hi));
+    return d;
 }
 
 // ((x shifted) & mask) | magic in two VALU ops (one when no shift is needed).  mask rides the
@@ -187,6 +166,51 @@ struct BlockUnpacker {
         return f;
     }
 };
+
+// ---------------------------------------------------------------------------------
+// Half of an 8x8 block -> four operand fragments: the two lanes c = 2b, 2b + 1 of a 64-column wave share block b.
+//   along features, 4 bits: the lane has channels 4h .. 4h + 3 (h = c % 2): words 4h .. 4h + 3 of the block
+//   along features, 3 bits: channels p, 2 + p, 4 + p, 6 + p (p = c % 2), which are exactly words p, 2 + p, 4 + p
+//   along channels:         features p, 2 + p, 4 + p, 6 + p: the low (p = 0) or high half-words of all words, partner
+//                           channels merged by one byte permute per word pair
+// so that every lane runs the same shifts and masks.  Column of fragment I within the wave's 64: see half_col.
+// ---------------------------------------------------------------------------------
+template <int BITS, bool ALONG_CH>
+struct HalfBlockUnpacker {
+    static constexpr int WORDS = ALONG_CH ? 2 * BITS : BITS;      // words a lane reads
+    static constexpr bool BY_PARITY = ALONG_CH || BITS == 3;
+    uint32_t w[BITS];
+
+    // sel: along channels, the byte permute of this lane's half-words (0x05040100 for p = 0, 0x07060302 for p = 1)
+    __device__ __forceinline__ void prepare(const uint32_t *words, uint32_t sel)
+    {
+#pragma unroll
+        for (int m = 0; m < BITS; ++m) {
+            if constexpr (ALONG_CH) w[m] = __builtin_amdgcn_perm(words[2 * m + 1], words[2 * m], sel);
+            else w[m] = words[m];
+        }
+    }
+
+    // register J (elements 2J, 2J + 1 of the contraction) of fragment I (0..3)
+    template <int I, int J>
+    __device__ __forceinline__ uint32_t frag_reg(uint32_t magic) const
+    {
+        if constexpr (BITS == 4) {
+            if constexpr (ALONG_CH) return field_pair<4, I>(w[J], magic);
+            else return field_pair<4, J>(w[I], magic);
+        } else {
+            constexpr int u = ALONG_CH ? 4 * J + I : 4 * I + J;
+            if constexpr (u < 15) return field_pair<3, u % 5>(w[u / 5], magic);
+            else return spare_pair3(w[0], w[1], w[2], magic);
+        }
+    }
+};
+
+// The neighbouring lane's value (lanes 2i and 2i + 1 swap).
+__device__ __forceinline__ float swap_pair_lane(float v)
+{
+    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), 0xB1, 0xF, 0xF, true));
+}
 
 // Per-channel backward, the part of dY the dX contraction reads:  dYs[t,i] = bf16(dY[t,i] (s0 + ds)[i])  and
 // crow[t] = sum_i dYs[t,i] (16 + z0[i] + dz[i])  (from the rounded dYs, so that it cancels the code offset of the
