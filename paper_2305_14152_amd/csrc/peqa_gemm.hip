@@ -182,6 +182,9 @@ static int halves_per_workgroup(int tiles, bool paired)
     return tiles > cus ? 1 : 2;
 }
 
+// Workgroups that the tiles of a contraction take in a launch: their number rounded up to a multiple of 8.
+int gemm_multi_wgs(int tiles_t, int tiles_c) { return (tiles_t * tiles_c + 7) / 8 * 8; }
+
 bool gemm_four_waves(int tiles) { return halves_per_workgroup(tiles, false) == 1; }
 
 template <int BITS, int MODE, bool GROUPED, int KW>
@@ -199,9 +202,7 @@ static hipError_t launch_one(const GemmArgs &a, hipStream_t stream)
         if (e != hipSuccess) return e;
         attr_bytes[dev] = lds_bytes;
     }
-    const int pt = a.patch_t, pc = 32 / pt;
-    const int patches = ((a.tiles_t + pt - 1) / pt) * ((a.tiles_c + pc - 1) / pc);
-    const int grid = ((patches + 7) / 8) * 8 * 32;
+    const int grid = gemm_multi_wgs(a.tiles_t, a.tiles_c);
     // grouped scale gradient: one pair of scale groups per workgroup along y
     const int gy = GROUPED && MODE == MODE_DDS ? (a.G + 1) / 2 : 1;
     // spare workgroups (see the kernel) exist in one instantiation only
@@ -243,7 +244,7 @@ static hipError_t dispatch(int bits, int mode, const GemmArgs &a, hipStream_t st
 hipError_t launch_gemm(int bits, int mode, const GemmArgs &a_in, hipStream_t stream)
 {
     GemmArgs a = a_in;
-    a.patch_t = a.tiles_t >= 4 ? 4 : (a.tiles_t >= 2 ? 2 : 1);
+    a.patch_t = a.tiles_t < 4 ? a.tiles_t : 4;
     const int kid = mode == MODE_Y ? KID_GEMM_Y : (mode == MODE_DDS ? KID_GEMM_DDS : KID_GEMM_DX);
     trace_before(kid, stream);
     const hipError_t e = dispatch(bits, mode, a, stream);
@@ -265,24 +266,13 @@ static hipError_t launch_pair(const GemmArgs &a_dds, const GemmArgs &a_dx, hipSt
         if (e != hipSuccess) return e;
         attr_bytes[dev] = lds_bytes;
     }
-    auto grid_of = [](const GemmArgs &a) {
-        const int pt = a.patch_t, pc = 32 / pt;
-        const int patches = ((a.tiles_t + pt - 1) / pt) * ((a.tiles_c + pc - 1) / pc);
-        return ((patches + 7) / 8) * 8 * 32;               // a multiple of 8: both parts keep workgroup id % 8 = XCD
-    };
+    auto grid_of = [](const GemmArgs &a) { return gemm_multi_wgs(a.tiles_t, a.tiles_c); };   // multiples of 8: both parts keep workgroup id % 8 = XCD
     // the tiles that take longer go first: the short ones fill the last round better
     const int dx_first = a_dx.KC >= a_dds.KC;
     const int n_first = grid_of(dx_first ? a_dx : a_dds), n_second = grid_of(dx_first ? a_dds : a_dx);
     hipLaunchKernelGGL((gemm_bwd_pair_kernel<BITS>), dim3(n_first + n_second), dim3(256), lds_bytes, stream, a_dds, a_dx,
                        n_first, dx_first);
     return hipGetLastError();
-}
-
-int gemm_multi_wgs(int tiles_t, int tiles_c)
-{
-    const int pt = tiles_t >= 4 ? 4 : (tiles_t >= 2 ? 2 : 1), pc = 32 / pt;
-    const int patches = ((tiles_t + pt - 1) / pt) * ((tiles_c + pc - 1) / pc);
-    return ((patches + 7) / 8) * 8 * 32;
 }
 
 template <int BITS, int GMODE>
@@ -313,7 +303,7 @@ hipError_t launch_gemm_multi(int bits, bool grouped, MultiArgs &m, hipStream_t s
             GemmArgs &a = m.job[j].a;
             if ((a.gsz > 0) != grouped || a.tp_blocks) return hipErrorInvalidValue;
             if (grouped && m.job[j].mode == MODE_DDS) return hipErrorInvalidValue;
-            a.patch_t = a.tiles_t >= 4 ? 4 : (a.tiles_t >= 2 ? 2 : 1);
+            a.patch_t = a.tiles_t < 4 ? a.tiles_t : 4;
             total += gemm_multi_wgs(a.tiles_t, a.tiles_c);
         } else {
             m.job[j] = m.job[m.n_jobs > 0 ? m.n_jobs - 1 : 0];
@@ -344,7 +334,7 @@ hipError_t launch_gemm_bwd_pair(int bits, const GemmArgs &dds_in, const GemmArgs
     GemmArgs a_dds = dds_in, a_dx = dx_in;
     if (a_dds.gsz > 0 || a_dx.gsz > 0 || a_dds.tp_blocks || a_dx.tp_blocks || a_dds.tiles_t != a_dx.tiles_t)
         return hipErrorInvalidValue;
-    a_dds.patch_t = a_dx.patch_t = a_dds.tiles_t >= 4 ? 4 : (a_dds.tiles_t >= 2 ? 2 : 1);
+    a_dds.patch_t = a_dx.patch_t = a_dds.tiles_t < 4 ? a_dds.tiles_t : 4;
     trace_before(KID_GEMM_BWD, stream);
     const hipError_t e = bits == 4 ? launch_pair<4>(a_dds, a_dx, stream) : launch_pair<3>(a_dds, a_dx, stream);
     trace_after(KID_GEMM_BWD, stream);

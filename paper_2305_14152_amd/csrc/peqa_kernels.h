@@ -26,7 +26,7 @@ struct GemmArgs {
     int C;                    // output columns:     N (MODE_Y/DDS) or K (MODE_DX)
     int K;                    // input features of the layer (fixes the block stride of `packed`)
     int tiles_c, tiles_t;     // ceil(C/256), ceil(T/128)
-    int patch_t;              // token tiles per L2 patch (1, 2 or 4; set by launch_gemm)
+    int patch_t;              // token tiles per L2 patch (at most 4; set by the launches)
     const float *s0;          // [N]            (MODE_Y)
     const float *ds;          // [N] or NULL    (MODE_Y)
     const uint8_t *z0;        // [N]            (MODE_Y, MODE_DDS)
@@ -106,7 +106,7 @@ struct MultiArgs {
 // Per-channel jobs (any mode), or, with `grouped`, group-wise MODE_Y / MODE_DX jobs (their tables in a.sb).
 static_assert(sizeof(MultiArgs) <= 4096, "kernel argument block");
 hipError_t launch_gemm_multi(int bits, bool grouped, MultiArgs &m, hipStream_t stream);
-// workgroups a contraction's tiles take in such a launch (a multiple of 8: whole XCD patches)
+// workgroups a contraction's tiles take in a launch (a multiple of 8)
 int gemm_multi_wgs(int tiles_t, int tiles_c);
 
 // Arguments of the token contraction dW = dY^T X with the codes applied in its epilogue (peqa_dw.hip):
