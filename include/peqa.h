@@ -43,7 +43,13 @@
  * gradient of the shared input (the sum of the members' dX) from a single contraction.
  * Results per member are those of running it alone -- bit for bit when both runs take the same
  * form of the contraction kernel (see Options; the forms add the same products in a different
- * order), else to the last bf16 bit; only dX, a sum, is new.
+ * order) and the same number of pieces (see Workspaces), else to the last bf16 bit; only dX, a sum, is new.
+ *
+ * Workspaces.  Where a launch's tiles would leave the machine idle (T > 16, but few tokens or a few tiles of a long
+ * contraction), contractions are split along their length into pieces whose fp32 sums meet in the workspace.  The size
+ * queries include that room.  A workspace that has room for everything but the pieces (what the queries return while
+ * PEQA_OPT_GEMM_WAVES or PEQA_OPT_BWD_PAIR forces a form) is served too, with whole contractions: the same products
+ * in another order.  For a given shape, T and workspace size results are always the same bits.
  */
 #ifndef PEQA_H
 #define PEQA_H
@@ -87,7 +93,7 @@ typedef enum {
 peqa_status peqa_check_layout(const peqa_layout *L);
 size_t peqa_packed_words(const peqa_layout *L);   /* N*K*bits/32 uint32 words; 0 if invalid */
 size_t peqa_num_scales(const peqa_layout *L);     /* N*G; 0 if invalid                      */
-/* Bytes of scratch the given call needs for T tokens (0 if invalid). */
+/* Bytes of scratch the given call asks for with T tokens (0 if invalid; see Workspaces). */
 size_t peqa_workspace_bytes(const peqa_layout *L, int32_t T, int32_t op);
 const char *peqa_status_string(int32_t status);
 

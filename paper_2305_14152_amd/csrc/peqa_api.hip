@@ -7,6 +7,8 @@
 #include <math.h>
 #include <string.h>
 
+#include <atomic>
+
 #include "peqa_host.h"
 
 using namespace peqa::host;
@@ -17,14 +19,20 @@ constexpr int PEQA_GEMV_MAX_T = GEMV_MAX_T;
 
 struct Workspace {
     size_t rs, dys, crow, partial, table, rsz, zpartial, xt, dyt, pc, total;
+    // Pieces of the contractions (1 = whole) and the regions of their partial results.  `total` includes these regions; a
+    // workspace of at least `min_total` but less than `total` bytes is served too, with whole contractions.
+    size_t min_total;
+    int split_y, split_dx, split_dds;      // split_dx, split_dds: of the backward that computes both gradients
+    int split_dx_alone;
+    size_t acc, acc_dds;
 };
 
-Workspace carve(const peqa_layout *L, int32_t T, int32_t op)
+Workspace carve_whole(const peqa_layout *L, int32_t T, int32_t op)
 {
-    if (op == PEQA_OP_FWD_Z && T > PEQA_GEMV_MAX_T) return carve(L, T, PEQA_OP_FWD);
+    if (op == PEQA_OP_FWD_Z && T > PEQA_GEMV_MAX_T) return carve_whole(L, T, PEQA_OP_FWD);
     if (op == PEQA_OP_BWD_Z) {
         // the plain backward's needs, then the group sums of X and the partials of the zero-point gradient
-        Workspace w = carve(L, T, PEQA_OP_BWD);
+        Workspace w = carve_whole(L, T, PEQA_OP_BWD);
         const size_t slices = ((size_t)T + peqa::KEPT_ROWS - 1) / peqa::KEPT_ROWS;
         const size_t NG = (size_t)L->n_out * (size_t)groups(L);
         w.rsz = w.total;      w.total += round256((size_t)T * groups(L) * sizeof(float));
@@ -82,9 +90,69 @@ Workspace carve(const peqa_layout *L, int32_t T, int32_t op)
     return w;
 }
 
+// The regions of carve_whole, then those of the split contractions.
+Workspace carve(const peqa_layout *L, int32_t T, int32_t op)
+{
+    Workspace w = carve_whole(L, T, op);
+    w.min_total = w.total;
+    w.split_y = w.split_dx = w.split_dds = w.split_dx_alone = 1;
+    const bool fwd = op == PEQA_OP_FWD || op == PEQA_OP_FWD_Z || op == PEQA_OP_FWD_KEEP;
+    if (fwd && op != PEQA_OP_FWD_KEEP && T <= PEQA_GEMV_MAX_T) return w;
+    const int N = L->n_out, K = L->k_in, tiles_t = (T + 127) / 128;
+    const size_t y_bytes = (size_t)T * N * sizeof(float), dx_bytes = (size_t)T * K * sizeof(float);
+    const peqa::SplitJob y{tiles_t * ((N + 255) / 256), K, y_bytes, 1}, dx{tiles_t * ((K + 255) / 256), N, dx_bytes, 1};
+    if (fwd) {
+        // a forward that fits peqa_linear_fwd_static's scratch whole is split within it: both calls run the same contraction
+        size_t most = ~(size_t)0;
+        if (w.total <= (size_t)PEQA_STATIC_SCRATCH_BYTES) most = (size_t)PEQA_STATIC_SCRATCH_BYTES - w.total;
+        peqa::SplitJob j = y;
+        peqa::gemm_plan_splits(1, &j, grouped(L), true, most);
+        w.split_y = j.split;
+        w.acc = w.total;
+        if (j.split > 1) w.total += round256((size_t)j.split * y_bytes);
+        return w;
+    }
+    peqa::SplitJob alone = dx;
+    peqa::gemm_plan_splits(1, &alone, grouped(L), true, ~(size_t)0);
+    w.split_dx = w.split_dx_alone = alone.split;
+    if (!grouped(L) && op != PEQA_OP_BWD_KEPT) {
+        peqa::SplitJob both[2] = {y, dx};
+        both[0].out_bytes = 0;
+        peqa::gemm_plan_splits(2, both, false, false, ~(size_t)0);
+        w.split_dds = both[0].split;
+        w.split_dx = both[1].split;
+    }
+    const int most_dx = w.split_dx > w.split_dx_alone ? w.split_dx : w.split_dx_alone;
+    w.acc = w.total;
+    if (most_dx > 1) w.total += round256((size_t)most_dx * dx_bytes);
+    w.acc_dds = w.total;
+    if (w.split_dds > 1) w.total += round256((size_t)w.split_dds * tiles_t * N * sizeof(float));
+    return w;
+}
+
+// Takes the splits back where the caller's workspace only holds the whole contractions' needs.
+void fit_workspace(Workspace &w, size_t bytes)
+{
+    if (bytes < w.total) w.split_y = w.split_dx = w.split_dds = w.split_dx_alone = 1;
+}
+
+// One contraction with `split` pieces: the launch, and the sum of its pieces.
+peqa_status run_contraction(int bits, int mode, peqa::GemmArgs &a, int split, float *acc, hipStream_t s)
+{
+    a.split = split;
+    a.acc_part = acc;
+    if (peqa::launch_gemm(bits, mode, a, s) != hipSuccess) return PEQA_ERR_DEVICE;
+    if (split < 2) return PEQA_OK;
+    peqa::FinishMulti f{};
+    f.job[0].a = a;
+    f.job[0].mode = mode;
+    f.n = 1;
+    return dev_status(peqa::launch_split_finish(f, s));
+}
+
 peqa_status fwd_per_channel(const peqa_layout *L, const uint32_t *packed, const float *s0, const float *ds,
                             const uint8_t *z0, const float *dz, const uint16_t *X, int32_t T, uint16_t *Y, float *P,
-                            const float *rs, hipStream_t s);
+                            const float *rs, int split, float *acc, hipStream_t s);
 
 // Scale gradient of group-wise layers: by the contraction over tokens (default), or, with the option
 // grouped_dds = 1, by the contraction over features, one pair of scale groups per workgroup: the older,
@@ -225,8 +293,9 @@ static peqa_status fwd_impl(const peqa_layout *L, const uint32_t *packed, const 
     if (!aligned16(packed) || !aligned16(s0) || !aligned16(z0) || !aligned16(X) || !aligned16(Y) ||
         (ds && !aligned16(ds)) || (dz && !aligned16(dz)))
         return PEQA_ERR_ALIGN;
-    const Workspace w = carve(L, T, dz ? PEQA_OP_FWD_Z : PEQA_OP_FWD);
-    if (!workspace || workspace_bytes < w.total) return PEQA_ERR_WORKSPACE;
+    Workspace w = carve(L, T, dz ? PEQA_OP_FWD_Z : PEQA_OP_FWD);
+    if (!workspace || workspace_bytes < w.min_total) return PEQA_ERR_WORKSPACE;
+    fit_workspace(w, workspace_bytes);
     if (!aligned16(workspace)) return PEQA_ERR_ALIGN;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -243,11 +312,11 @@ static peqa_status fwd_impl(const peqa_layout *L, const uint32_t *packed, const 
         a.packed = packed; a.A = X; a.T = T; a.KC = K; a.C = N; a.K = K;
         a.tiles_c = (N + 255) / 256; a.tiles_t = (T + 127) / 128;
         a.N = N; a.gsz = L->group_size; a.G = groups(L); a.sb = sb; a.out = Y;
-        return dev_status(peqa::launch_gemm(L->bits, peqa::MODE_Y, a, s));
+        return run_contraction(L->bits, peqa::MODE_Y, a, w.split_y, reinterpret_cast<float *>(ws + w.acc), s);
     }
     float *rs = reinterpret_cast<float *>(ws + w.rs);
     if (peqa::launch_rowsum(X, T, K, ksplit, rs, s) != hipSuccess) return PEQA_ERR_DEVICE;
-    return fwd_per_channel(L, packed, s0, ds, z0, dz, X, T, Y, nullptr, rs, s);
+    return fwd_per_channel(L, packed, s0, ds, z0, dz, X, T, Y, nullptr, rs, w.split_y, reinterpret_cast<float *>(ws + w.acc), s);
 }
 
 peqa_status peqa_quantize_search(const peqa_layout *L, const float *W0, int32_t n_ratios, float min_ratio,
@@ -306,7 +375,7 @@ peqa_status peqa_linear_fwd_static(const peqa_layout *L, const uint32_t *packed,
     peqa_status st = peqa_check_layout(L);
     if (st != PEQA_OK) return st;
     if (T < 1 || T > (1 << 24)) return PEQA_ERR_SHAPE;
-    if (carve(L, T, PEQA_OP_FWD).total > (size_t)PEQA_STATIC_SCRATCH_BYTES) return PEQA_ERR_WORKSPACE;
+    if (carve(L, T, PEQA_OP_FWD).min_total > (size_t)PEQA_STATIC_SCRATCH_BYTES) return PEQA_ERR_WORKSPACE;
     if (!packed || !s0 || !z0 || !X || !Y) return PEQA_ERR_NULL;    // before the device is touched
     void *ws = nullptr;
     st = static_scratch(&ws);
@@ -333,13 +402,15 @@ peqa_status peqa_linear_fwd_keep(const peqa_layout *L, const uint32_t *packed, c
     if (!aligned16(packed) || !aligned16(s0) || !aligned16(z0) || !aligned16(X) || !aligned16(Y) || !aligned16(P) ||
         (ds && !aligned16(ds)))
         return PEQA_ERR_ALIGN;
-    const Workspace w = carve(L, T, PEQA_OP_FWD_KEEP);
-    if (!workspace || workspace_bytes < w.total) return PEQA_ERR_WORKSPACE;
+    Workspace w = carve(L, T, PEQA_OP_FWD_KEEP);
+    if (!workspace || workspace_bytes < w.min_total) return PEQA_ERR_WORKSPACE;
+    fit_workspace(w, workspace_bytes);
     if (!aligned16(workspace)) return PEQA_ERR_ALIGN;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    float *rs = reinterpret_cast<float *>(static_cast<uint8_t *>(workspace) + w.rs);
+    uint8_t *ws = static_cast<uint8_t *>(workspace);
+    float *rs = reinterpret_cast<float *>(ws + w.rs);
     if (peqa::launch_rowsum(X, T, L->k_in, split_point(L->k_in), rs, s) != hipSuccess) return PEQA_ERR_DEVICE;
-    return fwd_per_channel(L, packed, s0, ds, z0, nullptr, X, T, Y, P, rs, s);
+    return fwd_per_channel(L, packed, s0, ds, z0, nullptr, X, T, Y, P, rs, w.split_y, reinterpret_cast<float *>(ws + w.acc), s);
 }
 
 }  // extern "C"
@@ -348,14 +419,14 @@ namespace {
 // Per-channel forward contraction for T > 16, the row sums of X already in `rs`.
 peqa_status fwd_per_channel(const peqa_layout *L, const uint32_t *packed, const float *s0, const float *ds,
                             const uint8_t *z0, const float *dz, const uint16_t *X, int32_t T, uint16_t *Y, float *P,
-                            const float *rs, hipStream_t s)
+                            const float *rs, int split, float *acc, hipStream_t s)
 {
     const int N = L->n_out, K = L->k_in;
     peqa::GemmArgs a{};
     a.packed = packed; a.A = X; a.T = T; a.KC = K; a.C = N; a.K = K;
     a.tiles_c = (N + 255) / 256; a.tiles_t = (T + 127) / 128;
     a.s0 = s0; a.ds = ds; a.z0 = z0; a.dz = dz; a.rs = rs; a.out = Y; a.P = P;
-    return dev_status(peqa::launch_gemm(L->bits, peqa::MODE_Y, a, s));
+    return run_contraction(L->bits, peqa::MODE_Y, a, split, acc, s);
 }
 }  // namespace
 
@@ -409,7 +480,15 @@ static peqa_status fwd_fused_impl(int32_t n, const peqa_fwd_item *items, const u
             return PEQA_ERR_ALIGN;
     }
     if (!aligned16(X)) return PEQA_ERR_ALIGN;
-    const size_t need = peqa_workspace_bytes_fused(n, items, T);
+    size_t need = 0;                                       // what whole contractions need at least
+    if (T <= PEQA_GEMV_MAX_T) {
+        need = peqa_workspace_bytes_fused(n, items, T);
+    } else {
+        for (int j = 0; j < n; ++j) {
+            const size_t b = carve(&items[j].layout, T, PEQA_OP_FWD).min_total;
+            need = b > need ? b : need;
+        }
+    }
     if (!workspace || workspace_bytes < need) return PEQA_ERR_WORKSPACE;
     if (!aligned16(workspace)) return PEQA_ERR_ALIGN;
     if (T <= PEQA_GEMV_MAX_T) {
@@ -430,7 +509,10 @@ static peqa_status fwd_fused_impl(int32_t n, const peqa_fwd_item *items, const u
         }
         for (int j = 0; j < n; ++j) {
             const peqa_fwd_item &it = items[j];
-            st = fwd_per_channel(&it.layout, it.packed, it.s0, it.ds, it.z0, nullptr, X, T, it.Y, nullptr, rs, s);
+            Workspace w = carve(&it.layout, T, PEQA_OP_FWD);
+            fit_workspace(w, workspace_bytes);
+            st = fwd_per_channel(&it.layout, it.packed, it.s0, it.ds, it.z0, nullptr, X, T, it.Y, nullptr, rs, w.split_y,
+                                 reinterpret_cast<float *>(static_cast<uint8_t *>(workspace) + w.acc), s);
             if (st != PEQA_OK) return st;
         }
         return PEQA_OK;
@@ -471,8 +553,9 @@ static peqa_status bwd_impl(const peqa_layout *L, const uint32_t *packed, const 
         (ds && !aligned16(ds)) || (dX && !aligned16(dX)) || (d_ds && !aligned16(d_ds)) || (dz && !aligned16(dz)) ||
         (d_dz && !aligned16(d_dz)))
         return PEQA_ERR_ALIGN;
-    const Workspace w = carve(L, T, op);
-    if (!workspace || workspace_bytes < w.total) return PEQA_ERR_WORKSPACE;
+    Workspace w = carve(L, T, op);
+    if (!workspace || workspace_bytes < w.min_total) return PEQA_ERR_WORKSPACE;
+    fit_workspace(w, workspace_bytes);
     if (!aligned16(workspace)) return PEQA_ERR_ALIGN;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -497,7 +580,7 @@ static peqa_status bwd_impl(const peqa_layout *L, const uint32_t *packed, const 
         uint16_t *xt = reinterpret_cast<uint16_t *>(ws + w.xt), *dyt = reinterpret_cast<uint16_t *>(ws + w.dyt);
         // When dX is wanted too and its contraction runs two workgroups per compute unit, it goes first and spare
         // workgroups of its launch write the transposed copies that the token contraction needs.
-        const bool tp_in_dx = d_ds && by_tokens && dX && peqa::gemm_four_waves(tiles_t * ((K + 255) / 256));
+        const bool tp_in_dx = d_ds && by_tokens && dX && peqa::gemm_four_waves(tiles_t * ((K + 255) / 256) * w.split_dx);
         auto run_dx = [&](bool with_transposes) -> peqa_status {
             float *sb = reinterpret_cast<float *>(ws + w.table);
             if (peqa::launch_group_table(s0, ds, z0, dz, N, G, sb, s) != hipSuccess) return PEQA_ERR_DEVICE;
@@ -508,7 +591,7 @@ static peqa_status bwd_impl(const peqa_layout *L, const uint32_t *packed, const 
             if (with_transposes) {
                 a.tp_blocks = (Tp / 64) * (K / 64 + N / 64); a.tp_Tp = Tp; a.tp_X = X; a.tp_Xt = xt; a.tp_dYt = dyt;
             }
-            return peqa::launch_gemm(L->bits, peqa::MODE_DX, a, s) == hipSuccess ? PEQA_OK : PEQA_ERR_DEVICE;
+            return run_contraction(L->bits, peqa::MODE_DX, a, w.split_dx, reinterpret_cast<float *>(ws + w.acc), s);
         };
         if (tp_in_dx) {
             const peqa_status st = run_dx(true);
@@ -557,6 +640,10 @@ static peqa_status bwd_impl(const peqa_layout *L, const uint32_t *packed, const 
     bool pair = d_ds && dX && peqa::gemm_four_waves(1 << 30);
     if (peqa::options().bwd_pair >= 0) pair = d_ds && dX && peqa::options().bwd_pair == 1;
     peqa::GemmArgs a_dds{}, a_dx{};
+    // a split scale gradient leaves one row of partials per token tile and piece
+    float *partial = reinterpret_cast<float *>(ws + (w.split_dds > 1 ? w.acc_dds : w.partial));
+    const int partial_rows = tiles_t * w.split_dds;
+    float *acc = reinterpret_cast<float *>(ws + w.acc);
     if (d_ds) {
         // row sums of X over the two contraction halves: the caller's (peqa_row_sums), or taken here
         const float *rs = row_sums;
@@ -568,7 +655,8 @@ static peqa_status bwd_impl(const peqa_layout *L, const uint32_t *packed, const 
         peqa::GemmArgs &a = a_dds;
         a.packed = packed; a.A = X; a.T = T; a.KC = K; a.C = N; a.K = K;
         a.tiles_c = (N + 255) / 256; a.tiles_t = tiles_t;
-        a.z0 = z0; a.dz = dz; a.rs = rs; a.dY = dY; a.partial = reinterpret_cast<float *>(ws + w.partial);
+        a.z0 = z0; a.dz = dz; a.rs = rs; a.dY = dY; a.partial = partial;
+        a.split = w.split_dds;
     }
     if (dX) {
         peqa::GemmArgs &a = a_dx;
@@ -576,27 +664,36 @@ static peqa_status bwd_impl(const peqa_layout *L, const uint32_t *packed, const 
         a.tiles_c = (K + 255) / 256; a.tiles_t = tiles_t;
         a.crow = reinterpret_cast<float *>(ws + w.crow); a.out = dX;
     }
-    float *partial = reinterpret_cast<float *>(ws + w.partial);
     uint16_t *dys = reinterpret_cast<uint16_t *>(ws + w.dys);
     float *crow = reinterpret_cast<float *>(ws + w.crow);
     if (pair) {
         if (peqa::launch_scale_dy(dY, s0, ds, z0, dz, T, N, dys, crow, nullptr, 0, 0, nullptr, s) != hipSuccess)
             return PEQA_ERR_DEVICE;
+        a_dx.split = w.split_dx;
+        a_dx.acc_part = acc;
         if (peqa::launch_gemm_bwd_pair(L->bits, a_dds, a_dx, s) != hipSuccess) return PEQA_ERR_DEVICE;
-        if (peqa::launch_reduce_partials(partial, tiles_t, (size_t)N, d_ds, s) != hipSuccess) return PEQA_ERR_DEVICE;
+        if (w.split_dx > 1) {
+            peqa::FinishMulti f{};
+            f.job[0].a = a_dx;
+            f.job[0].mode = peqa::MODE_DX;
+            f.n = 1;
+            if (peqa::launch_split_finish(f, s) != hipSuccess) return PEQA_ERR_DEVICE;
+        }
+        if (peqa::launch_reduce_partials(partial, partial_rows, (size_t)N, d_ds, s) != hipSuccess) return PEQA_ERR_DEVICE;
     } else {
         // one after the other; when dX follows the scale gradient, the sum of its partials rides in the launch
         // that scales dY
         if (d_ds) {
             if (peqa::launch_gemm(L->bits, peqa::MODE_DDS, a_dds, s) != hipSuccess) return PEQA_ERR_DEVICE;
-            if (!dX && peqa::launch_reduce_partials(partial, tiles_t, (size_t)N, d_ds, s) != hipSuccess)
+            if (!dX && peqa::launch_reduce_partials(partial, partial_rows, (size_t)N, d_ds, s) != hipSuccess)
                 return PEQA_ERR_DEVICE;
         }
         if (dX) {
-            if (peqa::launch_scale_dy(dY, s0, ds, z0, dz, T, N, dys, crow, partial, tiles_t, d_ds ? (size_t)N : 0, d_ds,
+            if (peqa::launch_scale_dy(dY, s0, ds, z0, dz, T, N, dys, crow, partial, partial_rows, d_ds ? (size_t)N : 0, d_ds,
                                       s) != hipSuccess)
                 return PEQA_ERR_DEVICE;
-            if (peqa::launch_gemm(L->bits, peqa::MODE_DX, a_dx, s) != hipSuccess) return PEQA_ERR_DEVICE;
+            const peqa_status st = run_contraction(L->bits, peqa::MODE_DX, a_dx, w.split_dx_alone, acc, s);
+            if (st != PEQA_OK) return st;
         }
     }
     if (d_dz) {
@@ -657,8 +754,9 @@ peqa_status peqa_linear_bwd_kept(const peqa_layout *L, const uint32_t *packed, c
     if (!aligned16(packed) || !aligned16(s0) || !aligned16(z0) || !aligned16(dY) || (P && !aligned16(P)) ||
         (ds && !aligned16(ds)) || (dX && !aligned16(dX)) || (d_ds && !aligned16(d_ds)))
         return PEQA_ERR_ALIGN;
-    const Workspace w = carve(L, T, PEQA_OP_BWD_KEPT);
-    if (!workspace || workspace_bytes < w.total) return PEQA_ERR_WORKSPACE;
+    Workspace w = carve(L, T, PEQA_OP_BWD_KEPT);
+    if (!workspace || workspace_bytes < w.min_total) return PEQA_ERR_WORKSPACE;
+    fit_workspace(w, workspace_bytes);
     if (!aligned16(workspace)) return PEQA_ERR_ALIGN;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -681,7 +779,7 @@ peqa_status peqa_linear_bwd_kept(const peqa_layout *L, const uint32_t *packed, c
         a.packed = packed; a.A = dys; a.T = T; a.KC = N; a.C = K; a.K = K;
         a.tiles_c = (K + 255) / 256; a.tiles_t = (T + 127) / 128;
         a.crow = crow; a.out = dX;
-        if (peqa::launch_gemm(L->bits, peqa::MODE_DX, a, s) != hipSuccess) return PEQA_ERR_DEVICE;
+        return run_contraction(L->bits, peqa::MODE_DX, a, w.split_dx_alone, reinterpret_cast<float *>(ws + w.acc), s);
     }
     return PEQA_OK;
 }
@@ -821,6 +919,18 @@ Options &options()
     static Options o;
     return o;
 }
+
+int compute_units()
+{
+    static std::atomic<int> known[64];
+    int dev = -1, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+    cus = known[dev].load(std::memory_order_relaxed);
+    if (cus > 0) return cus;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) return 256;
+    known[dev].store(cus, std::memory_order_relaxed);
+    return cus;
+}
 }  // namespace peqa
 
 namespace {
@@ -835,7 +945,7 @@ char g_trace_prefix[32] = "";     // only kernels whose name starts with this ar
 
 const char *const kKernelNames[peqa::KID_COUNT] = {
     "quantize", "rowsum", "gemm_y", "gemm_dds", "gemm_dx", "scale_dy", "reduce_partials", "adamw", "gemv",
-    "gemv_finish", "group_table", "dds_kept", "dz_partial", "dz_finish", "transpose_pad", "gemm_dw", "gemm_bwd", "gemm_multi_y", "gemm_multi_dds", "gemm_multi_dx"};
+    "gemv_finish", "group_table", "dds_kept", "dz_partial", "dz_finish", "transpose_pad", "gemm_dw", "gemm_bwd", "gemm_multi_y", "gemm_multi_dds", "gemm_multi_dx", "gemm_finish"};
 
 }  // namespace
 namespace {

@@ -6,7 +6,7 @@ using namespace peqa::host;
 
 // every table of a launch holds an entry per item of a call
 static_assert(peqa::MULTI_MAX_JOBS >= PEQA_MAX_BLOCK && peqa::DW_MAX_JOBS >= PEQA_MAX_BLOCK && peqa::GT_MAX >= PEQA_MAX_BLOCK &&
-                  peqa::ROWSUM_MAX >= PEQA_MAX_BLOCK && peqa::GEMV_MAX_LAYERS >= PEQA_MAX_BLOCK,
+                  peqa::ROWSUM_MAX >= PEQA_MAX_BLOCK && peqa::FINISH_MAX >= PEQA_MAX_BLOCK && peqa::GEMV_MAX_LAYERS >= PEQA_MAX_BLOCK,
               "launch tables against PEQA_MAX_BLOCK");
 
 namespace {
@@ -53,6 +53,11 @@ struct BlockSpace {
     size_t dyt[PEQA_MAX_BLOCK];      //   the same of its dY [N, T']
     size_t pc[PEQA_MAX_BLOCK];       //   scale gradient per 64-feature chunk [N, K / 64]
     size_t total;
+    // Pieces of the contractions (1 = whole) and the regions of their partial results, behind the others: `total` includes
+    // them, and a workspace of at least `min_total` bytes is served with whole contractions.
+    size_t min_total;
+    int split_y[PEQA_MAX_BLOCK], split_dx[PEQA_MAX_BLOCK], split_dds[PEQA_MAX_BLOCK];
+    size_t acc[PEQA_MAX_BLOCK], acc_dds[PEQA_MAX_BLOCK];
 };
 
 BlockSpace carve_block(int32_t n, const peqa_block_item *items, int32_t T, int32_t op)
@@ -79,15 +84,72 @@ BlockSpace carve_block(int32_t n, const peqa_block_item *items, int32_t T, int32
             w.partial[j] = off; off += round256(tiles_t * N * sizeof(float));
         }
     }
-    w.total = off ? off : 256;
+    w.total = w.min_total = off ? off : 256;
+    // splits, planned per launch: the per-channel items' forward, scale-gradient and dX launches, the group-wise items'
+    // forward and dX launches (as if every gradient of every item were asked for)
+    for (int j = 0; j < n; ++j) w.split_y[j] = w.split_dx[j] = w.split_dds[j] = 1;
+    auto plan = [&](bool gw, int mode, int *split) {
+        peqa::SplitJob job[PEQA_MAX_BLOCK];
+        int of[PEQA_MAX_BLOCK], m = 0;
+        for (int j = 0; j < n; ++j) {
+            const peqa_layout *L = &items[j].layout;
+            if (grouped(L) != gw) continue;
+            const int C = mode == peqa::MODE_DX ? L->k_in : L->n_out, KC = mode == peqa::MODE_DX ? L->n_out : L->k_in;
+            of[m] = j;
+            job[m++] = peqa::SplitJob{(int)tiles_t * ((C + 255) / 256), KC, mode == peqa::MODE_DDS ? 0 : (size_t)T * C * sizeof(float), 1};
+        }
+        if (m == 0) return;
+        peqa::gemm_plan_splits(m, job, gw, false, ~(size_t)0);
+        for (int i = 0; i < m; ++i) split[of[i]] = job[i].split;
+    };
+    if (op == PEQA_OP_FWD) {
+        plan(false, peqa::MODE_Y, w.split_y);
+        plan(true, peqa::MODE_Y, w.split_y);
+    } else {
+        plan(false, peqa::MODE_DDS, w.split_dds);
+        plan(false, peqa::MODE_DX, w.split_dx);
+        plan(true, peqa::MODE_DX, w.split_dx);
+    }
+    for (int j = 0; j < n; ++j) {
+        const size_t N = (size_t)items[j].layout.n_out, K = (size_t)items[j].layout.k_in;
+        w.acc[j] = w.total;
+        if (w.split_y[j] > 1) w.total += round256((size_t)w.split_y[j] * T * N * sizeof(float));
+        if (w.split_dx[j] > 1) w.total += round256((size_t)w.split_dx[j] * T * K * sizeof(float));
+        w.acc_dds[j] = w.total;
+        if (w.split_dds[j] > 1) w.total += round256((size_t)w.split_dds[j] * tiles_t * N * sizeof(float));
+    }
     return w;
 }
 
-// Jobs of a multi-contraction launch in order of falling contraction length.
+// The regions for a workspace of `bytes`: whole contractions where it is too small for the split ones.
+bool fit_block(BlockSpace &w, int32_t n, const void *workspace, size_t bytes)
+{
+    if (!workspace || bytes < w.min_total) return false;
+    if (bytes < w.total)
+        for (int j = 0; j < n; ++j) w.split_y[j] = w.split_dx[j] = w.split_dds[j] = 1;
+    return true;
+}
+
+// A multi-contraction launch, and the sums of its split contractions.
+peqa_status launch_multi(int bits, bool gw, peqa::MultiArgs &m, hipStream_t s)
+{
+    if (peqa::launch_gemm_multi(bits, gw, m, s) != hipSuccess) return PEQA_ERR_DEVICE;
+    peqa::FinishMulti f{};
+    for (int j = 0; j < m.n_jobs; ++j) {
+        if (m.job[j].a.split < 2 || m.job[j].mode == peqa::MODE_DDS) continue;
+        f.job[f.n].a = m.job[j].a;
+        f.job[f.n++].mode = m.job[j].mode;
+    }
+    return f.n > 0 ? dev_status(peqa::launch_split_finish(f, s)) : PEQA_OK;
+}
+
+int piece_length(const peqa::MultiJob &j) { return j.a.KC / (j.a.split > 1 ? j.a.split : 1); }
+
+// Jobs of a multi-contraction launch in order of falling contraction length (of a piece).
 void sort_jobs(peqa::MultiArgs &m)
 {
     for (int i = 1; i < m.n_jobs; ++i)
-        for (int k = i; k > 0 && m.job[k].a.KC > m.job[k - 1].a.KC; --k) {
+        for (int k = i; k > 0 && piece_length(m.job[k]) > piece_length(m.job[k - 1]); --k) {
             const peqa::MultiJob t = m.job[k];
             m.job[k] = m.job[k - 1];
             m.job[k - 1] = t;
@@ -99,9 +161,8 @@ void sort_jobs(peqa::MultiArgs &m)
 void place_aux(peqa::MultiArgs &m, int aux_wgs)
 {
     int total = 0;
-    for (int j = 0; j < m.n_jobs; ++j) total += peqa::gemm_multi_wgs(m.job[j].a.tiles_t, m.job[j].a.tiles_c);
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    for (int j = 0; j < m.n_jobs; ++j) total += peqa::gemm_multi_wgs(m.job[j].a);
+    const int cus = peqa::compute_units();
     const int first_round = 2 * cus / 8 * 8;
     m.aux_begin = total < first_round ? total : first_round;
     if (total == 0) aux_wgs = 4 * cus / 8 * 8;
@@ -157,13 +218,13 @@ peqa_status peqa_block_fwd(int32_t n, const peqa_block_item *items, int32_t T, v
             (it.ds && !aligned16(it.ds)) || (it.row_sums && !aligned16(it.row_sums)))
             return PEQA_ERR_ALIGN;
     }
-    const size_t need = peqa_block_workspace_bytes(n, items, T, PEQA_OP_FWD);
-    if (!workspace || workspace_bytes < need) return PEQA_ERR_WORKSPACE;
-    if (!aligned16(workspace)) return PEQA_ERR_ALIGN;
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint8_t *ws = static_cast<uint8_t *>(workspace);
 
     if (T <= GEMV_MAX_T) {
+        const size_t need = peqa_block_workspace_bytes(n, items, T, PEQA_OP_FWD);
+        if (!workspace || workspace_bytes < need) return PEQA_ERR_WORKSPACE;
+        if (!aligned16(workspace)) return PEQA_ERR_ALIGN;
         GemvItem gi[PEQA_MAX_BLOCK];
         for (int j = 0; j < n; ++j)
             gi[j] = GemvItem{&items[j].layout, items[j].packed, items[j].s0, items[j].ds, items[j].z0, nullptr,
@@ -171,7 +232,9 @@ peqa_status peqa_block_fwd(int32_t n, const peqa_block_item *items, int32_t T, v
         return gemv_forward(n, gi, T, true, reinterpret_cast<float *>(ws), s);
     }
 
-    const BlockSpace w = carve_block(n, items, T, PEQA_OP_FWD);
+    BlockSpace w = carve_block(n, items, T, PEQA_OP_FWD);
+    if (!fit_block(w, n, workspace, workspace_bytes)) return PEQA_ERR_WORKSPACE;
+    if (!aligned16(workspace)) return PEQA_ERR_ALIGN;
     int xi[PEQA_MAX_BLOCK], ks[PEQA_MAX_BLOCK];
     const uint16_t *xs[PEQA_MAX_BLOCK];
     const int nx = distinct_inputs(n, items, xi, xs, ks);
@@ -214,6 +277,7 @@ peqa_status peqa_block_fwd(int32_t n, const peqa_block_item *items, int32_t T, v
         a.packed = it.packed; a.A = it.X; a.T = T; a.KC = K; a.C = N; a.K = K;
         a.tiles_c = (N + 255) / 256; a.tiles_t = (T + 127) / 128;
         a.out = it.Y;
+        a.split = w.split_y[j]; a.acc_part = reinterpret_cast<float *>(ws + w.acc[j]);
         if (gw) {
             a.N = N; a.gsz = it.layout.group_size; a.G = groups(&it.layout);
             a.sb = reinterpret_cast<const float *>(ws + w.table[j]);
@@ -224,12 +288,14 @@ peqa_status peqa_block_fwd(int32_t n, const peqa_block_item *items, int32_t T, v
     if (m.n_jobs > 0) {
         sort_jobs(m);
         place_aux(m, 0);
-        if (peqa::launch_gemm_multi(bits, false, m, s) != hipSuccess) return PEQA_ERR_DEVICE;
+        st = launch_multi(bits, false, m, s);
+        if (st != PEQA_OK) return st;
     }
     if (mg.n_jobs > 0) {
         sort_jobs(mg);
         place_aux(mg, 0);
-        if (peqa::launch_gemm_multi(bits, true, mg, s) != hipSuccess) return PEQA_ERR_DEVICE;
+        st = launch_multi(bits, true, mg, s);
+        if (st != PEQA_OK) return st;
     }
     return PEQA_OK;
 }
@@ -248,12 +314,11 @@ peqa_status peqa_block_bwd(int32_t n, const peqa_block_item *items, int32_t T, v
             (it.d_ds && !aligned16(it.d_ds)) || (it.row_sums && !aligned16(it.row_sums)))
             return PEQA_ERR_ALIGN;
     }
-    const size_t need = peqa_block_workspace_bytes(n, items, T, PEQA_OP_BWD);
-    if (!workspace || workspace_bytes < need) return PEQA_ERR_WORKSPACE;
+    BlockSpace w = carve_block(n, items, T, PEQA_OP_BWD);
+    if (!fit_block(w, n, workspace, workspace_bytes)) return PEQA_ERR_WORKSPACE;
     if (!aligned16(workspace)) return PEQA_ERR_ALIGN;
     uint8_t *ws = static_cast<uint8_t *>(workspace);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const BlockSpace w = carve_block(n, items, T, PEQA_OP_BWD);
     int xi[PEQA_MAX_BLOCK], ks[PEQA_MAX_BLOCK];
     const uint16_t *xs[PEQA_MAX_BLOCK];
     const int nx = distinct_inputs(n, items, xi, xs, ks);
@@ -297,7 +362,7 @@ peqa_status peqa_block_bwd(int32_t n, const peqa_block_item *items, int32_t T, v
         const int N = it.layout.n_out, K = it.layout.k_in;
         uint16_t *dys = reinterpret_cast<uint16_t *>(ws + w.dys[j]);
         float *crow = reinterpret_cast<float *>(ws + w.crow[j]);
-        float *partial = reinterpret_cast<float *>(ws + w.partial[j]);
+        float *partial = reinterpret_cast<float *>(ws + (w.split_dds[j] > 1 ? w.acc_dds[j] : w.partial[j]));
         if (it.d_ds) {
             peqa::MultiJob &job = ma.job[ma.n_jobs++];
             job.mode = peqa::MODE_DDS;
@@ -305,8 +370,9 @@ peqa_status peqa_block_bwd(int32_t n, const peqa_block_item *items, int32_t T, v
             a.packed = it.packed; a.A = it.X; a.T = T; a.KC = K; a.C = N; a.K = K;
             a.tiles_c = (N + 255) / 256; a.tiles_t = tiles_t;
             a.z0 = it.z0; a.rs = rs[xi[j]]; a.dY = it.dY; a.partial = partial;
+            a.split = w.split_dds[j];
             peqa::ReduceJob &r = mb.red[mb.n_red++];
-            r.partial = partial; r.out = it.d_ds; r.ntiles = tiles_t; r.n = N;
+            r.partial = partial; r.out = it.d_ds; r.ntiles = tiles_t * w.split_dds[j]; r.n = N;
             red_chunks += (N + 255) / 256;
             r.chunk_end = red_chunks;
         }
@@ -321,17 +387,20 @@ peqa_status peqa_block_bwd(int32_t n, const peqa_block_item *items, int32_t T, v
             a.packed = it.packed; a.A = dys; a.T = T; a.KC = N; a.C = K; a.K = K;
             a.tiles_c = (K + 255) / 256; a.tiles_t = tiles_t;
             a.crow = crow; a.out = it.dX;
+            a.split = w.split_dx[j]; a.acc_part = reinterpret_cast<float *>(ws + w.acc[j]);
         }
     }
     if (ma.n_jobs > 0 || ma.n_sdy > 0) {
         sort_jobs(ma);
         place_aux(ma, 128);
-        if (peqa::launch_gemm_multi(bits, false, ma, s) != hipSuccess) return PEQA_ERR_DEVICE;
+        st = launch_multi(bits, false, ma, s);
+        if (st != PEQA_OK) return st;
     }
     if (mb.n_jobs > 0 || mb.n_red > 0) {
         sort_jobs(mb);
         place_aux(mb, 64);
-        if (peqa::launch_gemm_multi(bits, false, mb, s) != hipSuccess) return PEQA_ERR_DEVICE;
+        st = launch_multi(bits, false, mb, s);
+        if (st != PEQA_OK) return st;
     }
 
     // ---- group-wise items.  Their (s, b) tables in one launch; every dX contraction in one launch, whose auxiliary
@@ -355,6 +424,7 @@ peqa_status peqa_block_bwd(int32_t n, const peqa_block_item *items, int32_t T, v
             a.tiles_c = (K + 255) / 256; a.tiles_t = tiles_t;
             a.N = N; a.gsz = it.layout.group_size; a.G = G;
             a.sb = reinterpret_cast<const float *>(ws + w.table[j]); a.out = it.dX;
+            a.split = w.split_dx[j]; a.acc_part = reinterpret_cast<float *>(ws + w.acc[j]);
         }
         if (it.d_ds) {
             if (!xt_of[xi[j]]) {
@@ -381,7 +451,8 @@ peqa_status peqa_block_bwd(int32_t n, const peqa_block_item *items, int32_t T, v
     if (mg.n_jobs > 0 || mg.n_tp > 0) {
         sort_jobs(mg);
         place_aux(mg, 128);
-        if (peqa::launch_gemm_multi(bits, true, mg, s) != hipSuccess) return PEQA_ERR_DEVICE;
+        st = launch_multi(bits, true, mg, s);
+        if (st != PEQA_OK) return st;
     }
     if (dw.n_jobs > 0) {
         if (peqa::launch_dw_multi(bits, dw, s) != hipSuccess) return PEQA_ERR_DEVICE;

@@ -164,7 +164,68 @@ __global__ __launch_bounds__(256, 2) void gemm_multi_kernel(MultiArgs m)
     }
 }
 
+// One 256-thread workgroup per 1024 elements of a split contraction's result, four neighbouring columns per thread:
+// HBM-bound, split x 4 + 2 bytes per element.
+__global__ __launch_bounds__(256) void split_finish_kernel(FinishMulti f)
+{
+    const FinishJob J = kernarg_load<FinishJob>((uint32_t)(blockIdx.y * sizeof(FinishJob)));
+    const GemmArgs &a = J.a;
+    if (a.split < 2) return;
+    const uint32_t c4 = (uint32_t)a.C >> 2;
+    const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (e >= (size_t)a.T * c4) return;
+    const size_t t = e / c4;
+    const int col = (int)(e - t * c4) * 4;
+    const f32x4 *p = reinterpret_cast<const f32x4 *>(a.acc_part) + e;
+    const size_t stride = (size_t)a.T * c4;
+    f32x4 v = p[0];
+    int i = 1;
+    for (; i + 4 <= a.split; i += 4) {                         // four loads in flight, added in order
+        f32x4 w[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) w[u] = p[(size_t)(i + u) * stride];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v += w[u];
+    }
+    for (; i < a.split; ++i) v += p[(size_t)i * stride];
+    if (a.gsz == 0) {
+        if (J.mode == MODE_Y) {
+            const float r = a.rs[2 * t] + a.rs[2 * t + 1];
+            const uint32_t zz = *reinterpret_cast<const uint32_t *>(a.z0 + col);
+            f32x4 zoff;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) zoff[u] = kCodeOffset + (float)((zz >> (8 * u)) & 0xFFu);
+            if (a.dz) zoff += *reinterpret_cast<const f32x4 *>(a.dz + col);
+            f32x4 sc = *reinterpret_cast<const f32x4 *>(a.s0 + col);
+            if (a.ds) sc += *reinterpret_cast<const f32x4 *>(a.ds + col);
+            v -= zoff * r;
+            if (a.P) *reinterpret_cast<f32x4 *>(a.P + t * a.C + col) = v;
+            v *= sc;
+        } else {
+            v -= a.crow[t];
+        }
+    }
+    u32x2 o;
+    o[0] = pack_bf16x2(v[0], v[1]);
+    o[1] = pack_bf16x2(v[2], v[3]);
+    *reinterpret_cast<u32x2 *>(a.out + t * a.C + col) = o;
+}
+
 }  // namespace
+
+hipError_t launch_split_finish(const FinishMulti &f, hipStream_t stream)
+{
+    size_t most = 0;
+    for (int j = 0; j < f.n; ++j) {
+        const GemmArgs &a = f.job[j].a;
+        if (a.split > 1 && (size_t)a.T * a.C > most) most = (size_t)a.T * a.C;
+    }
+    if (most == 0) return hipSuccess;
+    trace_before(KID_GEMM_FINISH, stream);
+    hipLaunchKernelGGL(split_finish_kernel, dim3((unsigned)((most + 1023) / 1024), f.n), dim3(256), 0, stream, f);
+    trace_after(KID_GEMM_FINISH, stream);
+    return hipGetLastError();
+}
 
 // Contraction halves per workgroup.  Eight waves with two halves, one workgroup per compute unit, when a launch
 // has at most one tile per compute unit (a lone four-wave workgroup leaves every SIMD a single wave, which
@@ -177,13 +238,72 @@ static int halves_per_workgroup(int tiles, bool paired)
     if (paired) return 2;
     if (options().gemm_waves == 4) return 1;
     if (options().gemm_waves == 8) return 2;
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    const int cus = compute_units();
     return tiles > cus ? 1 : 2;
 }
 
+static int pieces(const GemmArgs &a) { return a.split > 1 ? a.split : 1; }
+
 // Workgroups that the tiles of a contraction take in a launch: their number rounded up to a multiple of 8.
-int gemm_multi_wgs(int tiles_t, int tiles_c) { return (tiles_t * tiles_c + 7) / 8 * 8; }
+int gemm_multi_wgs(const GemmArgs &a) { return (a.tiles_t * a.tiles_c * pieces(a) + 7) / 8 * 8; }
+
+// A launch lasts as long as its longest workgroup (a step of 32 takes 0.40 us with one workgroup on the compute unit, 0.66
+// with two; 8 us to fill the ring, drain and store) or as the work that two workgroups per unit get through, plus about a
+// third of a workgroup for the last round (per-channel figures; the vector instructions of group-wise scaling make a step
+// 1.6 times as long).  Pieces of Y and dX cost a second launch and fp32 sums written and read again (3.5 TB/s).  Among
+// splits into pieces of equal length over the launch the one with the least estimate is taken, if that is 13 % below the
+// unsplit one: the estimate is no better than that, and splits with less to gain measured between 5 % faster and 7 %
+// slower (4096 x 11008 backward at T = 800 and 1200).  Measured, whole -> split, us per call:
+//                                     T = 17          T = 128         T = 500
+//   7B block 4-bit, forward           124 ->  56      131 ->  71      whole
+//                   backward          392 -> 108      397 -> 140      480 -> 367
+//   13B block 3-bit g128, forward     239 ->  93      240 -> 113      whole
+//                         backward    708 -> 310      749 -> 393      953 -> 853
+//   4096 x 11008 4-bit alone, forward 103 ->  28      107 ->  37      112 ->  72
+void gemm_plan_splits(int n, SplitJob *jobs, bool grouped, bool single, size_t max_bytes)
+{
+    const int cus = compute_units();
+    int longest = 0;
+    for (int j = 0; j < n; ++j) {
+        jobs[j].split = 1;
+        longest = jobs[j].KC > longest ? jobs[j].KC : longest;
+    }
+    if (options().gemm_waves != 0 || options().bwd_pair >= 0) return;   // forced forms are whole contractions
+    constexpr int kMinPiece = 512;                             // shorter pieces are mostly fill and drain
+    const double f = grouped ? 1.6 : 1.0;
+    double best = 0.0;
+    for (int d = 1; d <= 48; d += d < 6 ? 1 : (d < 12 ? 2 : 4)) {
+        const int target = (longest + d - 1) / d;              // features (or channels) per piece
+        if (d > 1 && target < kMinPiece) break;
+        int s[FINISH_MAX], wgs = 0, piece = 0;
+        double steps = 0.0;
+        size_t bytes = 0;
+        for (int j = 0; j < n; ++j) {
+            s[j] = (jobs[j].KC + target - 1) / target;
+            s[j] = s[j] < jobs[j].KC / kMinPiece ? s[j] : (jobs[j].KC < kMinPiece ? 1 : jobs[j].KC / kMinPiece);
+            wgs += jobs[j].tiles * s[j];
+            const int len = (jobs[j].KC / 128 + s[j] - 1) / s[j] * 4;
+            piece = len > piece ? len : piece;
+            steps += (double)jobs[j].tiles * jobs[j].KC / 32;
+            if (s[j] > 1) bytes += s[j] * jobs[j].out_bytes;
+        }
+        if (d > 1 && bytes > max_bytes) continue;
+        double us;
+        if (single && wgs <= cus) {
+            us = 0.33 * f * piece + 11.0;                      // the eight-wave form
+        } else {
+            const double chain = 0.40 * f * piece + 8.0, work = (0.66 * f * steps + 8.0 * wgs) / (2.0 * cus) + 0.3 * chain;
+            us = chain > work ? chain : work;
+        }
+        if (bytes > 0) us += 4.0 + (double)bytes * 2.0 / 3.5e6;
+        if (d == 1) {
+            best = 0.87 * us;
+        } else if (us < best) {
+            best = us;
+            for (int j = 0; j < n; ++j) jobs[j].split = s[j];
+        }
+    }
+}
 
 bool gemm_four_waves(int tiles) { return halves_per_workgroup(tiles, false) == 1; }
 
@@ -202,7 +322,7 @@ static hipError_t launch_one(const GemmArgs &a, hipStream_t stream)
         if (e != hipSuccess) return e;
         attr_bytes[dev] = lds_bytes;
     }
-    const int grid = gemm_multi_wgs(a.tiles_t, a.tiles_c);
+    const int grid = gemm_multi_wgs(a);
     // grouped scale gradient: one pair of scale groups per workgroup along y
     const int gy = GROUPED && MODE == MODE_DDS ? (a.G + 1) / 2 : 1;
     // spare workgroups (see the kernel) exist in one instantiation only
@@ -219,7 +339,7 @@ static hipError_t launch_halves(const GemmArgs &a, hipStream_t stream)
 {
     constexpr bool PAIRED = GROUPED && MODE == MODE_DDS;
     if constexpr (!PAIRED) {
-        if (halves_per_workgroup(a.tiles_t * a.tiles_c, false) == 1) return launch_one<BITS, MODE, GROUPED, 1>(a, stream);
+        if (halves_per_workgroup(a.tiles_t * a.tiles_c * pieces(a), false) == 1) return launch_one<BITS, MODE, GROUPED, 1>(a, stream);
     }
     return launch_one<BITS, MODE, GROUPED, 2>(a, stream);
 }
@@ -266,10 +386,10 @@ static hipError_t launch_pair(const GemmArgs &a_dds, const GemmArgs &a_dx, hipSt
         if (e != hipSuccess) return e;
         attr_bytes[dev] = lds_bytes;
     }
-    auto grid_of = [](const GemmArgs &a) { return gemm_multi_wgs(a.tiles_t, a.tiles_c); };   // multiples of 8: both parts keep workgroup id % 8 = XCD
-    // the tiles that take longer go first: the short ones fill the last round better
-    const int dx_first = a_dx.KC >= a_dds.KC;
-    const int n_first = grid_of(dx_first ? a_dx : a_dds), n_second = grid_of(dx_first ? a_dds : a_dx);
+        // the tiles that take longer go first: the short ones fill the last round better
+    // (the numbers of workgroups are multiples of 8: both parts keep workgroup id % 8 = XCD)
+    const int dx_first = a_dx.KC / pieces(a_dx) >= a_dds.KC / pieces(a_dds);
+    const int n_first = gemm_multi_wgs(dx_first ? a_dx : a_dds), n_second = gemm_multi_wgs(dx_first ? a_dds : a_dx);
     hipLaunchKernelGGL((gemm_bwd_pair_kernel<BITS>), dim3(n_first + n_second), dim3(256), lds_bytes, stream, a_dds, a_dx,
                        n_first, dx_first);
     return hipGetLastError();
@@ -304,7 +424,7 @@ hipError_t launch_gemm_multi(int bits, bool grouped, MultiArgs &m, hipStream_t s
             if ((a.gsz > 0) != grouped || a.tp_blocks) return hipErrorInvalidValue;
             if (grouped && m.job[j].mode == MODE_DDS) return hipErrorInvalidValue;
             a.patch_t = a.tiles_t < 4 ? a.tiles_t : 4;
-            total += gemm_multi_wgs(a.tiles_t, a.tiles_c);
+            total += gemm_multi_wgs(a);
         } else {
             m.job[j] = m.job[m.n_jobs > 0 ? m.n_jobs - 1 : 0];
         }

@@ -413,8 +413,7 @@ void gemv_plan(int n, const int *N, const int *K, const int *chunk, int bits, in
     // of a 4096-feature layer is two thirds of a compute unit's share of a LLaMA-7B block, so whole tiles load
     // the units 2 : 1; halves deal out evenly, and at such T their partial sums are a few per cent of the bytes
     // (measured on that block: 7 % less time at T = 1, 2 % more at T = 16).
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    const int cus = compute_units();
     double total = 0.0;
     bool per_channel_all = true;
     for (int j = 0; j < n; ++j) {
@@ -442,11 +441,7 @@ hipError_t launch_gemv(int bits, const GemvArgs &a_in, hipStream_t stream)
 {
     const int wgs = a_in.layer[a_in.n_layers - 1].wg_end;
     GemvArgs a = a_in;
-    {
-        int d = 0, cus = 256;
-        if (hipGetDevice(&d) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, d);
-        a.second_from = cus;
-    }
+    a.second_from = compute_units();
     bool per_channel_all = true, sliced = false;
     unsigned max_tn = 0;
     for (int j = 0; j < a.n_layers; ++j) {

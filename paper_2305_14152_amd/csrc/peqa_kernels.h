@@ -42,6 +42,10 @@ struct GemmArgs {
     const uint16_t *tp_X;
     uint16_t *tp_Xt, *tp_dYt;
     uint16_t *out;            // [T, C] bf16    (MODE_Y: Y, MODE_DX: dX)
+    // pieces of the contraction per tile (0 or 1: whole).  MODE_Y, MODE_DX: piece p leaves its sums in acc_part [split, T, C]
+    // fp32 for launch_split_finish; MODE_DDS: its column sums in row p tiles_t + tile_t of `partial`.
+    int split;
+    float *acc_part;
     float *P;                 // [T, N] fp32 or NULL (MODE_Y, per-channel): sum_k X[t,k] (Q[i,k] - z0[i]), kept
     // group-wise layers (gsz > 0; a multiple of 64):
     int N;                    // output channels of the layer
@@ -52,6 +56,30 @@ struct GemmArgs {
 };
 
 hipError_t launch_gemm(int bits, int mode, const GemmArgs &a, hipStream_t stream);
+
+// Contractions of a launch whose tiles leave the machine idle (few tokens, or a few tiles of a long contraction) are split
+// along the contraction: GemmArgs::split pieces per tile.  gemm_plan_splits fills `split` of every job of one launch.
+struct SplitJob {
+    int tiles;                // of 128 x 256
+    int KC;                   // contraction length
+    size_t out_bytes;         // fp32 bytes of one piece's partial result (T C 4); 0 for MODE_DDS, whose pieces add partial rows
+    int split;                // out
+};
+// single: the jobs are one contraction that runs by itself (launch_gemm), which may take the eight-wave form.
+// max_bytes: the most the partial results may take.
+void gemm_plan_splits(int n, SplitJob *jobs, bool grouped, bool single, size_t max_bytes);
+// Epilogue of the split MODE_Y / MODE_DX contractions of a launch: adds the pieces in order, then does what the tile's own
+// epilogue would have done.  Jobs with split 1 are skipped.
+constexpr int FINISH_MAX = 8;
+struct FinishJob {
+    GemmArgs a;
+    int mode;
+};
+struct FinishMulti {
+    FinishJob job[FINISH_MAX];             // must stay the first member: indexed in the argument block
+    int n;
+};
+hipError_t launch_split_finish(const FinishMulti &f, hipStream_t stream);
 // whether a per-channel launch of that many 128 x 256 tiles takes the four-wave form (two workgroups per compute unit);
 // for a huge count: whether the four-wave form is allowed at all (the option gemm_waves = 8 forbids it)
 bool gemm_four_waves(int tiles);
@@ -106,8 +134,8 @@ struct MultiArgs {
 // Per-channel jobs (any mode), or, with `grouped`, group-wise MODE_Y / MODE_DX jobs (their tables in a.sb).
 static_assert(sizeof(MultiArgs) <= 4096, "kernel argument block");
 hipError_t launch_gemm_multi(int bits, bool grouped, MultiArgs &m, hipStream_t stream);
-// workgroups a contraction's tiles take in a launch (a multiple of 8)
-int gemm_multi_wgs(int tiles_t, int tiles_c);
+// workgroups a contraction's tiles (and pieces of tiles) take in a launch (a multiple of 8)
+int gemm_multi_wgs(const GemmArgs &a);
 
 // Arguments of the token contraction dW = dY^T X with the codes applied in its epilogue (peqa_dw.hip):
 // the scale gradient of group-wise layers.
@@ -237,13 +265,16 @@ bool quantize_resident_fits(int K, int G, bool search);
 hipError_t launch_quantize_search(const float *W0, int N, int K, int bits, int group, int n_ratios, float step,
                                   uint32_t *packed, float *s0, uint8_t *z0, hipStream_t stream);
 
+// Compute units of the current device (looked up once per device; 256, an MI355X's, where there is none).
+int compute_units();
+
 // Tracing hook: every launch goes through these so that peqa_trace_* can time it.
 void trace_before(int kernel_id, hipStream_t stream);
 void trace_after(int kernel_id, hipStream_t stream);
 
 enum {
     KID_QUANTIZE = 0, KID_ROWSUM, KID_GEMM_Y, KID_GEMM_DDS, KID_GEMM_DX, KID_SCALE_DY,
-    KID_REDUCE, KID_ADAMW, KID_GEMV, KID_GEMV_FINISH, KID_GROUP_TABLE, KID_DDS_KEPT, KID_DZ_PARTIAL, KID_DZ_FINISH, KID_TRANSPOSE, KID_GEMM_DW, KID_GEMM_BWD, KID_GEMM_MULTI_Y, KID_GEMM_MULTI_DDS, KID_GEMM_MULTI_DX, KID_COUNT
+    KID_REDUCE, KID_ADAMW, KID_GEMV, KID_GEMV_FINISH, KID_GROUP_TABLE, KID_DDS_KEPT, KID_DZ_PARTIAL, KID_DZ_FINISH, KID_TRANSPOSE, KID_GEMM_DW, KID_GEMM_BWD, KID_GEMM_MULTI_Y, KID_GEMM_MULTI_DDS, KID_GEMM_MULTI_DX, KID_GEMM_FINISH, KID_COUNT
 };
 
 }  // namespace peqa

@@ -67,11 +67,17 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
     // shares activation rows and weight columns through its L2, and every XCD has the same number of tiles whatever their
     // count.  (Patches dealt to the XCDs as wholes left six of them without work where a contraction has 48 tiles: forward
     // of a LLaMA-7B block, 3 bits, T = 333: 328 -> 152 us; 11008 x 4096 training step, groups of 64, T = 500: 326 -> 289 us.)
-    int tile_t, tile_c;
+    // A split contraction is that many times the tiles, piece by piece.
+    int tile_t, tile_c, piece = 0;
+    const int split = PAIRED || a.split < 1 ? 1 : a.split;
     {
-        const int n = a.tiles_t * a.tiles_c, per = (n + 7) >> 3;
-        const int idx = (wg & 7) * per + (wg >> 3);
+        const int whole = a.tiles_t * a.tiles_c, n = whole * split, per = (n + 7) >> 3;
+        int idx = (wg & 7) * per + (wg >> 3);
         if ((wg >> 3) >= per || idx >= n) return;          // padding to a multiple of 8 (uniform per workgroup)
+        if (split > 1) {
+            piece = (int)((uint32_t)idx / (uint32_t)whole);
+            idx -= piece * whole;
+        }
         const int strip = a.patch_t * a.tiles_c;           // patch_t rows of tiles, walked column by column
         const int st = (int)((uint32_t)idx / (uint32_t)strip), r = idx - st * strip;
         const int left = a.tiles_t - st * a.patch_t, rows = left < a.patch_t ? left : a.patch_t;
@@ -95,13 +101,13 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
         nit = a.gsz / KSTEP;                               // >= 2 and even: the group size is a multiple of 64
         grp = 2 * (int)blockIdx.y + wk;
         half_on = grp < a.G;
-    } else if constexpr (KW == 2) {
-        kh0 = 0;
-        kh1 = KC >> 1;                                     // both halves take KC / 2
-        nit = kh1 / KSTEP;                                 // loop iterations (>= 2: KC % 128 == 0)
     } else {
-        kh0 = kh1 = 0;
-        nit = KC / KSTEP;                                  // a multiple of 4
+        // this piece's run of 128-deep units; nit is even (KW = 2) or a multiple of 4
+        const uint32_t units = (uint32_t)KC >> 7;
+        const int u0 = (int)(piece * units / (uint32_t)split), u1 = (int)((piece + 1) * units / (uint32_t)split);
+        kh0 = u0 * 128;
+        nit = (u1 - u0) * (KW == 2 ? 2 : 4);               // >= 2: both contraction halves take half of the run
+        kh1 = KW == 2 ? kh0 + (u1 - u0) * 64 : kh0;
     }
     const int kbeg = wk ? kh1 : kh0;
     const uint32_t magic = kMagic;
@@ -222,13 +228,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
         }
     };
     // Scales and offsets of the next fragments.  Along features fragment I needs entry I, the same for two steps; along
-    // channels element e of every fragment is channel 32 (m % 4) + 8 q + e of the block.
+    // channels element e of every fragment is channel 32 (m % 4) + 8 q + e of the block: entries 2 J and 2 J + 1 are read
+    // shortly before the registers J of all fragments are built (all eight at once cost registers that there are not).
     constexpr int NE = ALONG_CH ? 8 : 4;
     float sc[NE], bo[NE];
     const uint8_t *tbl_lane = lds + tbl_off + (ALONG_CH ? q * 64 : Unpacker::BY_PARITY ? cb * 64 + par * 8 : c * 32);
     auto read_table = [&](int m) __attribute__((always_inline)) {
-        const uint8_t *row = tbl_lane + ((m >> 2) & 1) * 1024 + (ALONG_CH ? (m & 3) * 256 : ((m >> 1) & 1) * 512);
-        if constexpr (!ALONG_CH && Unpacker::BY_PARITY) {
+        const uint8_t *row = tbl_lane + ((m >> 2) & 1) * 1024 + ((m >> 1) & 1) * 512;
+        if constexpr (Unpacker::BY_PARITY) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const f32x2 v = *reinterpret_cast<const f32x2 *>(row + 16 * i);
@@ -237,12 +244,18 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
             }
         } else {
 #pragma unroll
-            for (int h = 0; h < NE / 2; ++h) {
+            for (int h = 0; h < 2; ++h) {
                 const f32x4 v = *reinterpret_cast<const f32x4 *>(row + 16 * h);
                 sc[2 * h] = v[0]; bo[2 * h] = v[1]; sc[2 * h + 1] = v[2]; bo[2 * h + 1] = v[3];
             }
         }
     };
+    auto read_table_pair = [&](int m, int J) __attribute__((always_inline)) {
+        const f32x4 v = *reinterpret_cast<const f32x4 *>(tbl_lane + ((m >> 2) & 1) * 1024 + (m & 3) * 256 + 16 * J);
+        sc[2 * J] = v[0]; bo[2 * J] = v[1]; sc[2 * J + 1] = v[2]; bo[2 * J + 1] = v[3];
+    };
+    // register r (0..15, in the order in which they are built) of the next step's fragments: register J of fragment I
+    constexpr bool J_MAJOR = SCALED && ALONG_CH;
     auto next_frag_reg = [&](const Unpacker &up, auto i_c, auto j_c) __attribute__((always_inline)) -> uint32_t {
         constexpr int I = decltype(i_c)::value, J = decltype(j_c)::value;
         const uint32_t pr = up.template frag_reg<I, J>(magic);
@@ -322,7 +335,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
         read_b(std::integral_constant<int, 1>{}, bw[0]);
 #pragma unroll
         for (int rt = 0; rt < 8; ++rt) read_a(std::integral_constant<int, 0>{}, afrag, rt);
-        if constexpr (SCALED) read_table(m0);
+        if constexpr (SCALED) {
+            if constexpr (ALONG_CH) {
+#pragma unroll
+                for (int J = 0; J < 4; ++J) read_table_pair(m0, J);
+            } else {
+                read_table(m0);
+            }
+        }
         Unpacker up;
         up.prepare(bw[1], perm_sel);
         static_for<4>([&](auto i) {
@@ -361,7 +381,12 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
             // waits of three steps have passed when it is read first.
             // (m0 is even, so m's parity is that of S + 1.)
             const int m = m0 + it + 1;
-            if constexpr (ALONG_CH || (S & 1)) read_table(m);
+            if constexpr (ALONG_CH) {
+                read_table_pair(m, 0);
+                read_table_pair(m, 1);
+            } else if constexpr (S & 1) {
+                read_table(m);
+            }
             if constexpr (S & 1) {
                 if ((m & 3) == 0) issue_table((m >> 2) + 1);
             }
@@ -374,8 +399,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
                 constexpr int ct = ct_c.value, m = 4 * rt + ct;
                 mfma16_acc(acc[rt][ct], afrag[rt], bfrag[CUR][ct]);
                 constexpr int r = frag_reg_after(m);
-                if constexpr (r >= 0)
-                    bfrag[NXT][r >> 2][r & 3] = next_frag_reg(up, std::integral_constant<int, (r >> 2)>{}, std::integral_constant<int, (r & 3)>{});
+                if constexpr (r >= 0) {
+                    constexpr int I = J_MAJOR ? r & 3 : r >> 2, J = J_MAJOR ? r >> 2 : r & 3;
+                    bfrag[NXT][I][J] = next_frag_reg(up, std::integral_constant<int, I>{}, std::integral_constant<int, J>{});
+                    if constexpr (J_MAJOR && I == 3 && J < 2) read_table_pair(m0 + it + 1, J + 2);
+                }
                 if constexpr (m == 2) read_b(std::integral_constant<int, NNS>{}, bw[NXT]);
                 if constexpr (m == 5) dma16(a_voff, a_ptr, dst_a + PS * STAGE_BYTES);
                 if constexpr (m == 13) dma16(a_voff_2, a_ptr, dst_a + PS * STAGE_BYTES + A_DST_2);
@@ -490,6 +518,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
             const int up16 = 16 - 16 * par;
             dy_vec dyv[2][4];
             float rsv[2][4];
+            const float rs_on = piece == 0 ? 1.f : 0.f;    // the row-sum term belongs to the whole contraction: once
             auto load_rows = [&](auto rt_c, dy_vec *dst, float *rdst) __attribute__((always_inline)) {
                 constexpr int rt = decltype(rt_c)::value;
 #pragma unroll
@@ -513,7 +542,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
                 if constexpr (rt + 1 < 8) load_rows(std::integral_constant<int, rt + 1>{}, dyv[(rt + 1) & 1], rsv[(rt + 1) & 1]);
                 float dm[4];                                   // rows past T contribute nothing
 #pragma unroll
-                for (int j = 0; j < 4; ++j) dm[j] = row_of(rt, j) < T ? 1.f : 0.f;
+                for (int j = 0; j < 4; ++j) {
+                    dm[j] = row_of(rt, j) < T ? 1.f : 0.f;
+                    rsv[rt & 1][j] *= rs_on;
+                }
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const f32x4 v = read_acc(acc[rt][e]);      // one accumulator tile at a time leaves its AGPRs
@@ -539,7 +571,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
             colsum = columns_of(v, 0);
         }
         if constexpr (KW == 1) {
-            if (wave_on && q == 0) *reinterpret_cast<f32x4 *>(a.partial + (size_t)tile_t * a.C + colc) = colsum;
+            if (wave_on && q == 0) *reinterpret_cast<f32x4 *>(a.partial + (size_t)(piece * a.tiles_t + tile_t) * a.C + colc) = colsum;
         } else {
             float *red = reinterpret_cast<float *>(lds);   // [contraction half][256 columns]
             if (q == 0) *reinterpret_cast<f32x4 *>(red + wk * TILE_C + wn * WAVE_C + 4 * c) = colsum;
@@ -553,7 +585,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
                     dst[0] = red[tid];
                     if (g0 + 1 < a.G) dst[1] = red[TILE_C + tid];
                 } else {
-                    a.partial[(size_t)tile_t * a.C + n] = red[tid] + red[TILE_C + tid];
+                    a.partial[(size_t)(piece * a.tiles_t + tile_t) * a.C + n] = red[tid] + red[TILE_C + tid];
                 }
             }
         }
@@ -565,7 +597,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
             for (int j = 0; j < 4; ++j) {
                 const int t = row_of(rt, j);
                 f32x4 v = columns_of(sum, j);              // (every lane takes part)
-                if (t < T) {
+                if (split > 1) {                           // (uniform)
+                    if (t < T) *reinterpret_cast<f32x4 *>(a.acc_part + ((size_t)piece * T + t) * a.C + colc) = v;
+                } else if (t < T) {
                     if constexpr (!SCALED) {
                         if constexpr (MODE == MODE_Y) {
                             v -= ep_zoff * r[j];

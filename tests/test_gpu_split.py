@@ -1,0 +1,134 @@
+"""Contractions split along their length (few tokens, long contractions): forward, dX, scale gradient, the kept product
+and the trained zero-points against the oracle, and against the whole contraction, which a workspace of the smaller size
+gets.  Sizes at the edges: one column tile and a ragged one, one token tile and a ragged second, pieces of unequal
+length, groups that end inside a 128-feature unit."""
+import numpy as np
+import pytest
+
+from paper_2305_14152_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+Y_TOL = 2e-2
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    import torch
+    assert torch.cuda.is_available()
+    from paper_2305_14152_amd import peqa
+    peqa.lib()
+    import gpu_util
+    return gpu_util
+
+
+def _whole_bytes(peqa, need):
+    """What a call needs at least: the query while a form of the kernel is forced, which rules splits out."""
+    peqa.set_option(peqa.PEQA_OPT_GEMM_WAVES, 4)
+    try:
+        return need()
+    finally:
+        peqa.set_option(peqa.PEQA_OPT_GEMM_WAVES, 0)
+
+
+@pytest.mark.parametrize("bits,N,K,T,group", [
+    (4, 256, 8192, 40, 0), (3, 384, 5504, 130, 0), (4, 8192, 128, 17, 0), (3, 5504, 384, 129, 0),
+    (4, 128, 6144, 17, 64), (3, 256, 7680, 129, 192), (3, 6144, 256, 128, 128),
+])
+def test_split_contractions(gpu, oracle, bits, N, K, T, group):
+    import torch
+    from paper_2305_14152_amd import peqa
+    print("split bits=%d N=%d K=%d T=%d g=%d" % (bits, N, K, T, group), flush=True)
+    seed = 61000 + bits * 1000 + N + K + T + group
+    W = synth.normal_f32(seed, (N, K), 0.02)
+    X = synth.normal_bf16(seed + 1, (T, K), 1.0)
+    dY = synth.normal_bf16(seed + 2, (T, N), 1.0)
+    layer = gpu.GpuLayer(W, bits, group)
+    codes, s0, z0 = oracle.quantize(W, bits, group)
+    ds = synth.normal_f32(seed + 3, s0.shape, 1e-3)
+    dz = synth.normal_f32(seed + 4, s0.shape, 0.5)
+    fwd, bwd = peqa.PEQA_OP_FWD, peqa.PEQA_OP_BWD
+    split = {op: peqa.workspace_bytes(layer.L, T, op) for op in (fwd, bwd)}
+    whole = {op: _whole_bytes(peqa, lambda: peqa.workspace_bytes(layer.L, T, op)) for op in (fwd, bwd)}
+    assert split[fwd] > whole[fwd] or split[bwd] > whole[bwd]
+
+    def close(a, b):                               # the same products in another order: a last bf16 bit
+        a, b = gpu.bf16_dev_to_f64(a), gpu.bf16_dev_to_f64(b)
+        assert np.abs(a - b).max() <= 2.0 ** -7 * np.abs(b).max()
+
+    def near(got, ref):
+        assert np.abs(gpu.bf16_dev_to_f64(got) - ref).max() <= Y_TOL * np.abs(ref).max()
+
+    Y = layer.fwd(X, ds)
+    dX, g = layer.bwd(X, dY, ds)
+    near(Y, oracle.fwd(codes, s0, ds, z0, X, group))
+    dXref, gref, _ = oracle.bwd(codes, s0, ds, z0, X, dY, group)
+    near(dX, dXref)
+    gpu.assert_scale_grad_close(gpu.to_host(g), gref)
+    only_dX, _ = layer.bwd(X, dY, ds, want_dds=False)
+    _, only_g = layer.bwd(X, dY, ds, want_dX=False)
+    close(only_dX, dX)
+    gpu.assert_scale_grad_close(gpu.to_host(only_g), gref)
+
+    # a workspace of the smaller size: whole contractions
+    layer._ws[(T, fwd)] = (torch.empty(whole[fwd], dtype=torch.uint8, device="cuda"), whole[fwd])
+    layer._ws[(T, bwd)] = (torch.empty(whole[bwd], dtype=torch.uint8, device="cuda"), whole[bwd])
+    close(layer.fwd(X, ds), Y)
+    dXw, gw = layer.bwd(X, dY, ds)
+    close(dXw, dX)
+    gw, gs = gpu.to_host(gw).astype(np.float64), gpu.to_host(g).astype(np.float64)
+    assert np.linalg.norm(gw - gs) <= 1e-5 * np.linalg.norm(gw)
+    with pytest.raises(peqa.PeqaError):            # and less than that is still refused
+        peqa.linear_bwd(layer.L, layer.packed, layer.s0, None, layer.z0, gpu.to_dev(X), gpu.to_dev(dY), T, dX, g,
+                        layer._ws[(T, bwd)][0], whole[bwd] - 256)
+
+    near(layer.fwd_z(X, ds, dz), oracle.fwd_z(codes, s0, ds, z0, dz, X, group))
+    dXz, gz, ddz = layer.bwd_z(X, dY, ds, dz)
+    dXzref, gsref, gzref = oracle.bwd_z(codes, s0, ds, z0, dz, X, dY, group)
+    near(dXz, dXzref)
+    gpu.assert_scale_grad_close(gpu.to_host(gz), gsref)
+    gpu.assert_scale_grad_close(gpu.to_host(ddz), gzref, "d_dz")
+    if group == 0:
+        Yk, P = layer.fwd_keep(X, ds)
+        near(Yk, oracle.fwd(codes, s0, ds, z0, X, group))
+        dXk, gk = layer.bwd_kept(P, dY, ds)
+        near(dXk, dXref)
+        gpu.assert_scale_grad_close(gpu.to_host(gk), gref)
+
+
+@pytest.mark.parametrize("bits,group,T", [(4, 0, 40), (3, 0, 200), (3, 128, 33), (4, 64, 130)])
+def test_split_block(gpu, oracle, bits, group, T):
+    """Items of very different contraction lengths behind one call, with the workspace asked for and with the smallest."""
+    import torch
+    from paper_2305_14152_amd import peqa
+    print("split block bits=%d g=%d T=%d" % (bits, group, T), flush=True)
+    items, refs = [], []
+    for j, (N, K) in enumerate([(256, 6144), (5504, 384), (384, 512)]):
+        seed = 67000 + 100 * j + bits + group + T
+        W = synth.normal_f32(seed, (N, K), 0.02)
+        X = synth.normal_bf16(seed + 1, (T, K), 1.0)
+        dY = synth.normal_bf16(seed + 2, (T, N), 1.0)
+        layer = gpu.GpuLayer(W, bits, group)
+        codes, s0, z0 = oracle.quantize(W, bits, group)
+        refs.append((oracle.fwd(codes, s0, None, z0, X, group),) + tuple(oracle.bwd(codes, s0, None, z0, X, dY, group)[:2]))
+        items.append(dict(L=layer.L, packed=layer.packed, s0=layer.s0, z0=layer.z0, X=gpu.to_dev(X), dY=gpu.to_dev(dY),
+                          Y=torch.zeros((T, N), dtype=torch.int16, device="cuda"),
+                          dX=torch.zeros((T, K), dtype=torch.int16, device="cuda"),
+                          d_ds=torch.zeros((N, layer.G), dtype=torch.float32, device="cuda")))
+    handle = peqa.block_items(items)
+    for op, call in ((peqa.PEQA_OP_FWD, peqa.block_fwd), (peqa.PEQA_OP_BWD, peqa.block_bwd)):
+        nb = peqa.block_workspace_bytes(handle, T, op)
+        least = _whole_bytes(peqa, lambda: peqa.block_workspace_bytes(handle, T, op))
+        assert nb > least
+        ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+        for size in (nb, least):
+            call(handle, T, ws, size)
+            torch.cuda.synchronize()
+            for d, (Yref, dXref, gref) in zip(items, refs):
+                if op == peqa.PEQA_OP_FWD:
+                    assert np.abs(gpu.bf16_dev_to_f64(d["Y"]) - Yref).max() <= Y_TOL * np.abs(Yref).max()
+                    d["Y"].zero_()
+                else:
+                    assert np.abs(gpu.bf16_dev_to_f64(d["dX"]) - dXref).max() <= Y_TOL * np.abs(dXref).max()
+                    gpu.assert_scale_grad_close(gpu.to_host(d["d_ds"]), gref)
+                    d["dX"].zero_(), d["d_ds"].zero_()
