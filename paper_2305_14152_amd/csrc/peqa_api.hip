@@ -57,9 +57,9 @@ Workspace carve_whole(const peqa_layout *L, int32_t T, int32_t op)
         return w;
     }
     if ((op == PEQA_OP_FWD || op == PEQA_OP_FWD_Z) && T <= PEQA_GEMV_MAX_T) {
-        // with a trained zero-point offset a slice of a group-wise layer spans fewer groups: more slices
+        // the fewest slices (with a trained zero-point offset LDS holds fewer groups of a group-wise layer: more slices)
         const GemvItem one{L, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
-        w.partial = off; off += round256(gemv_partial_bytes(1, &one, T, false, op == PEQA_OP_FWD));
+        w.partial = off; off += round256(gemv_partial_bytes(1, &one, T, op == PEQA_OP_FWD, true));
         if (off == 0) off = 256;                               // a single slice needs none; 0 would read as "invalid"
         w.total = off;
         return w;
@@ -97,7 +97,12 @@ Workspace carve(const peqa_layout *L, int32_t T, int32_t op)
     w.min_total = w.total;
     w.split_y = w.split_dx = w.split_dds = w.split_dx_alone = 1;
     const bool fwd = op == PEQA_OP_FWD || op == PEQA_OP_FWD_Z || op == PEQA_OP_FWD_KEEP;
-    if (fwd && op != PEQA_OP_FWD_KEEP && T <= PEQA_GEMV_MAX_T) return w;
+    if (fwd && op != PEQA_OP_FWD_KEEP && T <= PEQA_GEMV_MAX_T) {
+        const GemvItem one{L, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
+        const size_t planned = w.partial + round256(gemv_partial_bytes(1, &one, T, op == PEQA_OP_FWD, false));
+        w.total = planned > w.total ? planned : w.total;
+        return w;
+    }
     const int N = L->n_out, K = L->k_in, tiles_t = (T + 127) / 128;
     const size_t y_bytes = (size_t)T * N * sizeof(float), dx_bytes = (size_t)T * K * sizeof(float);
     const peqa::SplitJob y{tiles_t * ((N + 255) / 256), K, y_bytes, 1}, dx{tiles_t * ((K + 255) / 256), N, dx_bytes, 1};
@@ -303,7 +308,7 @@ static peqa_status fwd_impl(const peqa_layout *L, const uint32_t *packed, const 
     const int N = L->n_out, K = L->k_in, ksplit = split_point(K);
     if (T <= PEQA_GEMV_MAX_T) {
         const GemvItem item{L, packed, s0, ds, z0, dz, X, Y};
-        return gemv_forward(1, &item, T, false, reinterpret_cast<float *>(ws + w.partial), s);
+        return gemv_forward(1, &item, T, reinterpret_cast<float *>(ws + w.partial), workspace_bytes - w.partial, s);
     }
     if (grouped(L)) {
         float *sb = reinterpret_cast<float *>(ws + w.table);
@@ -454,7 +459,7 @@ size_t peqa_workspace_bytes_fused(int32_t n, const peqa_fwd_item *items, int32_t
     if (T <= PEQA_GEMV_MAX_T) {
         GemvItem gi[PEQA_MAX_FUSED];
         for (int j = 0; j < n; ++j) gi[j] = GemvItem{&items[j].layout, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
-        const size_t b = round256(gemv_partial_bytes(n, gi, T, false, true));
+        const size_t b = round256(gemv_partial_bytes(n, gi, T, true, false));
         return b ? b : 256;
     }
     size_t need = 0;                                       // layer by layer: the largest single need
@@ -482,7 +487,10 @@ static peqa_status fwd_fused_impl(int32_t n, const peqa_fwd_item *items, const u
     if (!aligned16(X)) return PEQA_ERR_ALIGN;
     size_t need = 0;                                       // what whole contractions need at least
     if (T <= PEQA_GEMV_MAX_T) {
-        need = peqa_workspace_bytes_fused(n, items, T);
+        GemvItem gi[PEQA_MAX_FUSED];
+        for (int j = 0; j < n; ++j) gi[j] = GemvItem{&items[j].layout, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
+        need = round256(gemv_partial_bytes(n, gi, T, true, true));
+        need = need ? need : 256;
     } else {
         for (int j = 0; j < n; ++j) {
             const size_t b = carve(&items[j].layout, T, PEQA_OP_FWD).min_total;
@@ -495,7 +503,7 @@ static peqa_status fwd_fused_impl(int32_t n, const peqa_fwd_item *items, const u
         GemvItem gi[PEQA_MAX_FUSED];
         for (int j = 0; j < n; ++j)
             gi[j] = GemvItem{&items[j].layout, items[j].packed, items[j].s0, items[j].ds, items[j].z0, nullptr, X, items[j].Y};
-        return gemv_forward(n, gi, T, false, static_cast<float *>(workspace), static_cast<hipStream_t>(stream));
+        return gemv_forward(n, gi, T, static_cast<float *>(workspace), workspace_bytes, static_cast<hipStream_t>(stream));
     }
     // the tiled contraction runs the layers one by one; per-channel layers share the row sums of X
     if (!grouped(&items[0].layout)) {
@@ -851,41 +859,33 @@ peqa_status peqa_scale_update_multi(int32_t n, const peqa_update_item *items, co
 namespace peqa {
 namespace host {
 
-void gemv_slicing(int n, const GemvItem *items, int32_t T, bool block_plan, bool zbyte, int *S)
+peqa::GemvForm gemv_slicing(int n, const GemvItem *items, int32_t T, bool zbyte, bool least, int *S)
 {
-    if (block_plan) {
-        int N[GEMV_MAX_LAYERS], K[GEMV_MAX_LAYERS], chunk[GEMV_MAX_LAYERS];
-        for (int j = 0; j < n; ++j) {
-            N[j] = items[j].L->n_out;
-            K[j] = items[j].L->k_in;
-            chunk[j] = items[j].L->group_size > 0 ? items[j].L->group_size : items[j].L->k_in;
-        }
-        gemv_plan(n, N, K, chunk, items[0].L->bits, T, zbyte, S);
-        return;
+    int N[GEMV_MAX_LAYERS], K[GEMV_MAX_LAYERS], chunk[GEMV_MAX_LAYERS];
+    for (int j = 0; j < n; ++j) {
+        N[j] = items[j].L->n_out;
+        K[j] = items[j].L->k_in;
+        chunk[j] = items[j].L->group_size > 0 ? items[j].L->group_size : items[j].L->k_in;
     }
-    const peqa_layout *L = items[0].L;
-    int n_total = 0;
-    for (int j = 0; j < n; ++j) n_total += items[j].L->n_out;
-    const int s = gemv_slices(n_total, L->k_in, T, L->group_size > 0 ? L->group_size : L->k_in, zbyte);
-    for (int j = 0; j < n; ++j) S[j] = s;
+    return gemv_plan(n, N, K, chunk, items[0].L->bits, T, zbyte, least, S);
 }
 
-size_t gemv_partial_bytes(int n, const GemvItem *items, int32_t T, bool block_plan, bool zbyte)
+size_t gemv_partial_bytes(int n, const GemvItem *items, int32_t T, bool zbyte, bool least)
 {
     int S[GEMV_MAX_LAYERS];
-    gemv_slicing(n, items, T, block_plan, zbyte, S);
+    (void)gemv_slicing(n, items, T, zbyte, least, S);
     size_t bytes = 0;
     for (int j = 0; j < n; ++j)
         if (S[j] > 1) bytes += (size_t)S[j] * (size_t)T * (size_t)items[j].L->n_out * sizeof(float);
     return bytes;
 }
 
-peqa_status gemv_forward(int n, const GemvItem *items, int32_t T, bool block_plan, float *partial, hipStream_t s)
+peqa_status gemv_forward(int n, const GemvItem *items, int32_t T, float *partial, size_t partial_bytes, hipStream_t s)
 {
     int S[GEMV_MAX_LAYERS];
-    bool zbyte = true;                                         // the kernel takes the same decision from the same pointers
+    bool zbyte = true;                                         // the launch takes the same decision from the same pointers
     for (int j = 0; j < n; ++j) zbyte = zbyte && items[j].dz == nullptr;
-    gemv_slicing(n, items, T, block_plan, zbyte, S);
+    const GemvForm form = gemv_slicing(n, items, T, zbyte, gemv_partial_bytes(n, items, T, zbyte, false) > partial_bytes, S);
     GemvArgs g{};
     int wgs = 0;
     size_t poff = 0;                                           // in floats
@@ -901,15 +901,15 @@ peqa_status gemv_forward(int n, const GemvItem *items, int32_t T, bool block_pla
             l.S = S[j];
             l.partial = partial + poff;
             if (S[j] > 1) poff += (size_t)S[j] * (size_t)T * (size_t)L->n_out;
-            wgs += (L->n_out / 128) * S[j];
-            l.wg_end = wgs;
+            wgs += L->n_out / (64 * form.h) * S[j];
         } else {
             g.layer[j] = g.layer[n - 1];                       // never selected: its wg_end is the total
         }
+        g.wg_end[j] = wgs;
     }
     g.n_layers = n;
     g.T = T;
-    return dev_status(launch_gemv(items[0].L->bits, g, s));
+    return dev_status(launch_gemv(items[0].L->bits, form, g, s));
 }
 
 }  // namespace host

@@ -99,81 +99,15 @@ __device__ __forceinline__ uint32_t spare_pair3(uint32_t v0, uint32_t v1, uint32
 }
 
 // ---------------------------------------------------------------------------------
-// One 8x8 block of codes (8 channels x 8 features; 2*BITS words) -> eight operand
-// fragments of 8 bf16 (4 registers) each, produced one at a time so that callers can
-// spread the unpacking between matrix instructions.
-//
-// Along features: fragment r = channel r, elements = features 0..7 in order
-//   (the operand of a contraction over input features: forward, scale gradient).
-// Along channels: fragment f = feature f, elements = channels 0..7 in order
-//   (the operand of a contraction over output channels: dX).
-// Layout of the block's words: see peqa_bit_location() in peqa.h.
-// ---------------------------------------------------------------------------------
-template <int BITS, bool ALONG_CH>
-struct BlockUnpacker {
-    static constexpr int WPB = 2 * BITS;
-    uint32_t lo[4], hi[4];      // along channels: half-words of partner channels merged
-    uint32_t w[WPB];
-
-    __device__ __forceinline__ void prepare(const uint32_t *words)
-    {
-#pragma unroll
-        for (int i = 0; i < WPB; ++i) w[i] = words[i];
-        if constexpr (ALONG_CH) {
-            // After the merge the low half-word belongs to the even channel of a partner pair and
-            // the high half-word to the odd one, which is the element order of the fragment.
-#pragma unroll
-            for (int m = 0; m < BITS; ++m) {
-                lo[m] = __builtin_amdgcn_perm(w[2 * m + 1], w[2 * m], 0x05040100u);
-                hi[m] = __builtin_amdgcn_perm(w[2 * m + 1], w[2 * m], 0x07060302u);
-            }
-        }
-    }
-
-    // register J (0..3: elements 2J, 2J+1) of fragment I (0..7)
-    template <int I, int J>
-    __device__ __forceinline__ uint32_t frag_reg(uint32_t magic) const
-    {
-        if constexpr (!ALONG_CH) {
-            if constexpr (BITS == 4) {
-                return field_pair<4, J>(w[I], magic);
-            } else {
-                constexpr int par = I % 2, u = 4 * (I / 2) + J;
-                if constexpr (u < 15) return field_pair<3, u % 5>(w[2 * (u / 5) + par], magic);
-                else return spare_pair3(w[par], w[2 + par], w[4 + par], magic);
-            }
-        } else {
-            constexpr bool odd = I & 1;             // odd features live in the high half-words
-            constexpr int p = I >> 1;
-            if constexpr (BITS == 4) {
-                return field_pair<4, p>(odd ? hi[J] : lo[J], magic);
-            } else {
-                constexpr int u = 4 * J + p;
-                if constexpr (u < 15) return field_pair<3, u % 5>(odd ? hi[u / 5] : lo[u / 5], magic);
-                else return odd ? spare_pair3(hi[0], hi[1], hi[2], magic) : spare_pair3(lo[0], lo[1], lo[2], magic);
-            }
-        }
-    }
-
-    template <int I>
-    __device__ __forceinline__ u32x4 frag(uint32_t magic) const
-    {
-        u32x4 f;
-        f[0] = frag_reg<I, 0>(magic);
-        f[1] = frag_reg<I, 1>(magic);
-        f[2] = frag_reg<I, 2>(magic);
-        f[3] = frag_reg<I, 3>(magic);
-        return f;
-    }
-};
-
-// ---------------------------------------------------------------------------------
-// Half of an 8x8 block -> four operand fragments: the two lanes c = 2b, 2b + 1 of a 64-column wave share block b.
+// Half of an 8x8 block of codes (8 channels x 8 features; 2 BITS words; layout: peqa_bit_location() in peqa.h) -> four
+// operand fragments of 8 bf16 (4 registers) each, produced register by register so that callers can spread the unpacking
+// between matrix instructions.  The two lanes c = 2b, 2b + 1 of a wave of 64 columns share block b.
 //   along features, 4 bits: the lane has channels 4h .. 4h + 3 (h = c % 2): words 4h .. 4h + 3 of the block
 //   along features, 3 bits: channels p, 2 + p, 4 + p, 6 + p (p = c % 2), which are exactly words p, 2 + p, 4 + p
 //   along channels:         features p, 2 + p, 4 + p, 6 + p: the low (p = 0) or high half-words of all words, partner
 //                           channels merged by one byte permute per word pair
-// so that every lane runs the same shifts and masks.  Column of fragment I within the wave's 64: see half_col.
+// so that every lane runs the same shifts and masks.  Fragment I belongs to column 4 c + I of the wave's 64, or, by parity,
+// 8 (c / 2) + 2 I + c % 2.
 // ---------------------------------------------------------------------------------
 template <int BITS, bool ALONG_CH>
 struct HalfBlockUnpacker {

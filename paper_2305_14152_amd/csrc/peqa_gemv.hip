@@ -1,34 +1,32 @@
 // Deployment forward for T <= 16 tokens (Sec. 3.1 "Inference Latency": matrix-vector products bound
 // by the weight bytes streamed from memory).  Y[t,i] = sum_g s[i,g] * sum_{k in g} X[t,k] (Q[i,k] - z[i,g]).
 //
-// Every packed word is read from HBM exactly once, straight into registers: a wave owns 128 output
-// channels (lane (c, q): channel block c, feature block q of each 32-feature step) and walks a slice
-// of the input features; the up-to-16 token rows ride along as the 16-row operand of MFMA 16x16x32,
-// so T = 1 and T = 16 cost the same weight traffic.  Codes enter the MFMAs as exact bf16 (16 + Q);
-// a ninth MFMA per step against a fragment of ones yields the row sums of X over the same features,
-// and at the end of every scale group   y += s * (acc - (16 + z) * rowsum)   folds offset, zero-point
-// and scale in fp32.  Per-channel layers are one group spanning the whole slice.
+// Every packed word is read from HBM exactly once, straight into registers: a wave owns 64 output channels (lane (c, q):
+// half of channel block c / 2, feature block q of each 32-feature step) -- or two such halves of 128 -- and walks a range of
+// the input features; the up-to-16 token rows ride along as the 16-row operand of MFMA 16x16x32, so T = 1 and T = 16 cost
+// the same weight traffic.  Codes enter the MFMAs as exact bf16 (16 + Q); one more MFMA per step against a fragment of ones
+// yields the row sums of X over the same features, and at the end of every scale group   y += s * (acc - (16 + z) * rowsum)
+// folds offset, zero-point and scale in fp32.  Per-channel layers are one group spanning the whole range.
 //
-// Grid: one workgroup per (layer, channel tile of 128, feature slice); up to GEMV_MAX_LAYERS layers of different
-// shapes and inputs share a launch (a decoder block's linears: a single LLaMA-size layer at such T is too short
-// to fill the machine, and a launch costs as much as streaming several megabytes).  The K / 64 rounds of 64
-// features of a tile are dealt evenly to its S slices and, inside a slice, to the waves of the workgroup (a wave
-// may start or stop in the middle of a scale group: the fold above is linear in the features, so it is applied
-// to whatever part of a group the wave has seen); the waves are summed through LDS at the end.
-// S > 1 leaves fp32 partials [S, T, N] in the workspace for gemv_finish_kernel to add up in a fixed
-// order.  Two shapes of workgroup: 4 waves (two or three workgroups per compute unit, S chosen so that
-// the machine is full), and, for per-channel layers of 128 to 256 channel tiles, 12 waves that take
-// the whole of K (S = 1): the same twelve waves per compute unit, but the sum over the feature ranges
-// stays in LDS, so there are no partials and no second launch.  (With fewer tiles than that the
-// compute units left idle cost more than the second launch saves: measured.)
+// Grid: one workgroup per (layer, channel tile, feature slice); up to GEMV_MAX_LAYERS layers of different shapes and inputs
+// share a launch (a decoder block's linears: a single LLaMA-size layer at such T is too short to fill the machine, and a
+// launch costs as much as streaming several megabytes).  The K / 64 rounds of 64 features of a tile are dealt evenly to its
+// S slices and, inside a slice, to the waves of the workgroup (a wave may start or stop in the middle of a scale group: the
+// fold above is linear in the features, so it is applied to whatever part of a group the wave has seen); the waves are
+// summed through LDS at the end.  S > 1 leaves fp32 partials [S, T, N] in the workspace for gemv_finish_kernel to add up in
+// a fixed order, a second launch of 4 us.  Waves per workgroup, channels and slices: see gemv_plan.
 //
-// A wave moves its operands in rounds of 64 features (two MFMA steps): the packed blocks of its 16
-// channel-block rows and the matching 128 bytes of each of the 16 token rows, by global -> LDS DMA
-// into a private double buffer, from which each lane reads back its own blocks and activation
-// fragments.  The LDS placement is chosen for conflict-free read-back: at 4 bits every lane's two
-// 16-byte block halves sit at 16 * lane of two 1 KB planes per step; at 3 bits the 96 16-byte
-// chunks of a step lie in address order (rows of 96 B).  No barrier is involved: a wave waits for
-// its own DMA only.
+// What bounds it.  HBM for a whole block (4.7 TB/s of the 4.8 to 5.2 that a copy or a read reaches), latency and the second
+// launch for single layers, and below one workgroup per compute unit the unpacking (2 vector instructions per weight pair).
+// Tiles of 64 channels instead of 128 need no slices where 128 needed two to six, i.e. no second launch, and put twice the
+// workgroups behind a layer.  us per call at T = 5, 128 channels -> this form: 13B 3-bit g128 qkv 18.3 -> 11.9, o 13.7 -> 10.4,
+// gate/up 22.7 -> 18.1, down 18.9 -> 14.5, whole block 36.1 -> 34.6; 7B 4-bit qkv 14.2 -> 9.3, o 11.4 -> 8.1, gate/up 18.4 -> 13.6,
+// down 15.1 -> 11.8, whole block 29.5 -> 26.3.
+//
+// A wave moves its operands in rounds of 64 features (two MFMA steps): its packed words and the matching 128 bytes of each
+// token row, by global -> LDS DMA into a private double buffer, from which each lane reads back its own words and
+// activation fragments (token rows' 16-byte chunks XOR-swizzled by row, so that the reads of 16 rows spread over the
+// banks).  No barrier is involved: a wave waits for its own DMA only.
 #include <stddef.h>
 
 #include <type_traits>
@@ -40,17 +38,17 @@ namespace peqa {
 
 namespace {
 
-constexpr int GV_WAVES = 4;          // waves of the sliced workgroup
-constexpr int GV_WAVES_WHOLE = 12;   // waves of the workgroup that takes all of K
-constexpr int GV_WHOLE_MIN_TILES = 128, GV_WHOLE_MAX_TILES = 256;
-constexpr int GV_MAX_PER = 16;       // most scale groups a slice may touch (bounds the scale tile in LDS): trained zero-points
-constexpr int NB_PC = 2, NB_G31 = 2; // ring depth of the per-channel instantiations / of the 3-bit group-wise one for T <= 8
-constexpr int GV_MAX_PER_Z8 = 48;    // the same with integer zero-points, kept as bytes (5 instead of 8 bytes per entry)
-// One round of one wave in LDS: its packed blocks (4 KB at 4 bits, 3 KB at 3 bits), then NX KB of token rows
+// A workgroup owns 64 H channels (H = 1 or 2).
+constexpr int gv_srow(int h) { return 64 * h + 4; }   // padded rows of the scale tile (floats) and of byte zero-points
+constexpr int gv_zrow(int h) { return 64 * h + 8; }
+constexpr int GV_LDS_MAX = 160 * 1024;
+constexpr int GV_NBUF = 2;           // rounds a wave keeps in flight (three measured the same or slower in every form)
+// One round (64 features) of one wave in LDS: its packed words (2 KB; 1.5 KB of it at 3 bits), then NX KB of token rows
 // (8 rows x 128 B per KB: one DMA when T <= 8, two otherwise).
-constexpr int gv_b_bytes(int bits) { return bits == 4 ? 4096 : 3072; }
-constexpr int gv_round_bytes(int bits, int nx) { return gv_b_bytes(bits) + nx * 1024; }
-
+constexpr int GV_B_BYTES = 2048;
+constexpr int gv_round_bytes(int h, int nx) { return h * GV_B_BYTES + nx * 1024; }
+// Bytes of LDS per scale group of a workgroup's tile: 64 scales, and 64 zero-points as bytes or, with a trained offset, fp32.
+constexpr int gv_group_bytes(int h, bool zbyte) { return gv_srow(h) * 4 + (zbyte ? gv_zrow(h) : gv_srow(h) * 4); }
 
 __device__ __forceinline__ void gv_dma16(uint32_t voff, const void *sbase, uint32_t lds_dst)
 {
@@ -63,25 +61,25 @@ __device__ __forceinline__ void gv_wait_vmcnt()
     __builtin_amdgcn_s_waitcnt((N & 0xF) | (0x7 << 4) | (0xF << 8) | ((N >> 4) << 14));
 }
 
-// GROUPS_MAX: most scale groups a workgroup may touch: 1 for per-channel layers (1 KB scale tile),
-// GV_MAX_PER for group-wise ones (16 KB).  NBUF: rounds a wave keeps in flight (its private ring in LDS).
-// NX: KB of token rows per round (1: T <= 8, 2: T <= 16).
-// ZBYTE: zero-points are the stored integers (no trained offset dz): they stay bytes in LDS, which lets a
-// workgroup hold the scales of GV_MAX_PER_Z8 groups -- a whole row of LLaMA-13B's 40 -- and take all of K.
-template <int BITS, int GROUPS_MAX, int WAVES, int NBUF, int NX, bool ZBYTE>
-__global__ __launch_bounds__(WAVES * 64, WAVES > 4 ? 1 : 2) void gemv_kernel(GemvArgs a)
+// H: 64-channel halves of a workgroup.  NX: KB of token rows per round (1: T <= 8, 2: T <= 16).
+// ZBYTE: zero-points are the stored integers (no trained offset dz), kept as bytes in LDS.
+template <int BITS, int H, int WAVES, int NX, bool ZBYTE>
+__global__ __launch_bounds__(WAVES * 64, H == 2 ? 2 : 3) void gemv_kernel(GemvArgs a)
 {
-    // [wave][NBUF rounds][round]; reused as [wave][column tile][row][lane] fp32 (8 KB per wave) for the final sum
-    extern __shared__ __align__(16) uint8_t stage[];
-    // scale s0 + ds and zero-point (16 + z0 + dz as fp32, or z0 as stored) of [group of the slice][channel]
+    // [wave][NBUF rounds][round], reused as [wave][column tile][row in lane][lane] fp32 (4 KB per wave) for the final sum;
+    // then the scale tile: scale s0 + ds and zero-point (16 + z0 + dz as fp32, or z0 as stored) of [group of the slice][channel]
     // (rows padded: the transposing writes of consecutive groups of one channel then fall into different banks)
-    __shared__ __align__(16) float sS[GROUPS_MAX][128 + 4];
-    __shared__ __align__(16) typename std::conditional<ZBYTE, uint8_t, float>::type sZ[GROUPS_MAX][128 + (ZBYTE ? 8 : 4)];
-    constexpr int WPB = 2 * BITS;
-    constexpr int GV_B_BYTES = gv_b_bytes(BITS), GV_ROUND_BYTES = gv_round_bytes(BITS, NX);
-    static_assert(NBUF * GV_ROUND_BYTES >= 8192, "the final sum reuses a wave's ring");
-    constexpr int NDMA_B = 2 * 64 * WPB * 4 / 1024;               // 1 KB DMAs for the blocks of a round: 4 / 3
-    constexpr int NDMA = NDMA_B + NX;                             // + the token rows
+    extern __shared__ __align__(16) uint8_t stage[];
+    typedef HalfBlockUnpacker<BITS, false> Unpacker;
+    constexpr int WORDS = Unpacker::WORDS;
+    constexpr int NBUF = GV_NBUF, ROUND = gv_round_bytes(H, NX), NDMA = 2 * H + NX, THREADS = WAVES * 64;
+    constexpr int GV_C = 64 * H, GV_SROW = gv_srow(H), GV_ZROW = gv_zrow(H);
+    static_assert(NBUF == 2, "the waits below");
+    static_assert(NBUF * ROUND >= 4096 * H, "the final sum reuses a wave's ring");
+    typedef typename std::conditional<ZBYTE, uint8_t, float>::type zp_t;
+    constexpr int ZROW = ZBYTE ? GV_ZROW : GV_SROW;
+    float *sS = reinterpret_cast<float *>(stage + WAVES * NBUF * ROUND);
+    zp_t *sZ = reinterpret_cast<zp_t *>(sS + a.groups_cap * GV_SROW);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15, q = lane >> 4;
@@ -90,17 +88,15 @@ __global__ __launch_bounds__(WAVES * 64, WAVES > 4 ? 1 : 2) void gemv_kernel(Gem
     int li = 0, wg0 = 0;
 #pragma unroll
     for (int i = 0; i < GEMV_MAX_LAYERS - 1; ++i) {
-        const int e = kernarg_load<int>((uint32_t)(i * sizeof(GemvLayer) + offsetof(GemvLayer, wg_end)));
+        const int e = a.wg_end[i];
         if (bx >= e) { li = i + 1; wg0 = e; }
     }
     const GemvLayer L = kernarg_load<GemvLayer>((uint32_t)(li * sizeof(GemvLayer)));
-    const uint32_t *l_packed = L.packed;
     const float *l_s0 = L.s0, *l_ds = L.ds, *l_dz = L.dz;
     const uint8_t *l_z0 = L.z0;
-    uint16_t *l_Y = L.Y;
     const int l_N = L.N, l_S = L.S;
     const int tile = (int)((uint32_t)(bx - wg0) / (uint32_t)l_S), slice = (bx - wg0) - tile * l_S;
-    const int n0 = tile * 128;                                   // first channel, within its layer
+    const int n0 = tile * GV_C;                                  // first channel, within its layer
     const int K = L.K, G = L.G;
     const int chunk_rounds = L.chunk >> 6;                        // 64-feature rounds per scale group
     // this workgroup's rounds [rbeg, rend); wave w takes the w-th of WAVES equal parts of them
@@ -108,255 +104,237 @@ __global__ __launch_bounds__(WAVES * 64, WAVES > 4 ? 1 : 2) void gemv_kernel(Gem
     const int rbeg = (int)((uint32_t)slice * R / (uint32_t)l_S), rend = (int)((uint32_t)(slice + 1) * R / (uint32_t)l_S);
     const int wr0 = rbeg + (int)((uint32_t)(wave * (rend - rbeg)) / (uint32_t)WAVES);
     const int nrounds = rbeg + (int)((uint32_t)((wave + 1) * (rend - rbeg)) / (uint32_t)WAVES) - wr0;
-    const int k0 = wr0 << 6;                                      // first feature of this wave
     const int g_lo = (uint32_t)rbeg / (uint32_t)chunk_rounds;     // first scale group this workgroup touches
 
     const uint32_t magic = kMagic;
     const u32x4 ones = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
-    // the wave's tiles (128 channels x 32 features, TILE bytes each) are contiguous along the features
-    constexpr uint32_t TILE = 64 * WPB * 4;
-    const uint8_t *bbase = reinterpret_cast<const uint8_t *>(l_packed) +
-                           ((size_t)tile * (K >> 5) + (k0 >> 5)) * TILE;
-    const uint8_t *xbase = reinterpret_cast<const uint8_t *>(L.X + k0);
-    const uint32_t lds_stage = (uint32_t)(uintptr_t)stage + wave * NBUF * GV_ROUND_BYTES;
-    uint32_t b_voff[NDMA_B], x_voff[NX];
+    // A step of the wave (64 channels x 32 features) is half of a 128-channel tile of TILE bytes: contiguous; tiles follow
+    // each other along the features.
+    constexpr uint32_t BLK = 2 * BITS * 4, TILE = 64 * BLK, HALF = TILE / 2;
+    const uint8_t *bsrc = reinterpret_cast<const uint8_t *>(L.packed) +
+                          ((size_t)(n0 >> 7) * (K >> 5) + 2 * (size_t)wr0) * TILE + (size_t)((n0 >> 6) & 1) * HALF;
+    const uint8_t *xsrc = reinterpret_cast<const uint8_t *>(L.X + ((size_t)wr0 << 6));
+    const uint32_t ring = (uint32_t)(uintptr_t)stage + wave * NBUF * ROUND;
+    uint32_t b_voff[2], x_voff[NX];
     if constexpr (BITS == 4) {
-        // DMA (step s, half h): lane (c, q) fetches half h of its own block (c * 4 + q of tile s)
+        // DMA of step s: lane (c, q) fetches its own words, half c % 2 of block (c / 2, q)
 #pragma unroll
-        for (int i = 0; i < NDMA_B; ++i)
-            b_voff[i] = (uint32_t)(i >> 1) * TILE + (uint32_t)(c * 4 + q) * 32u + (uint32_t)(i & 1) * 16u;
+        for (int i = 0; i < 2; ++i) b_voff[i] = (uint32_t)i * TILE + (uint32_t)((c >> 1) * 4 + q) * BLK + (uint32_t)(c & 1) * 16u;
     } else {
-        // the 192 16-byte chunks of the round's two tiles, in address order
+        // the 96 16-byte chunks of the round's two steps in address order (the last 32 lanes repeat the second DMA's first 32
+        // into the buffer's unused tail)
 #pragma unroll
-        for (int i = 0; i < NDMA_B; ++i) b_voff[i] = (uint32_t)(64 * i + lane) * 16u;
+        for (int i = 0; i < 2; ++i) {
+            const int x = 64 * i + (i == 0 ? lane : lane & 31);
+            b_voff[i] = (uint32_t)(x / 48) * TILE + (uint32_t)(x % 48) * 16u;
+        }
     }
 #pragma unroll
     for (int i = 0; i < NX; ++i) {
-        const int x = 64 * i + lane;                              // chunk x: token row x / 8, 16 bytes x % 8
-        const int t = (x >> 3) < a.T ? (x >> 3) : a.T - 1;        // rows beyond T repeat the last one (never stored)
-        x_voff[i] = (uint32_t)t * (uint32_t)K * 2u + (uint32_t)(x & 7) * 16u;
+        const int x = 64 * i + lane, row = x >> 3;                // token row x / 8; its eight 16-byte chunks XOR-swizzled by row
+        const int t = row < a.T ? row : a.T - 1;                  // rows beyond T repeat the last one (never stored)
+        x_voff[i] = (uint32_t)t * (uint32_t)K * 2u + (uint32_t)((x & 7) ^ (row & 7)) * 16u;
     }
     // round r lives in ring slot r % NBUF; `slot` is the slot of the next round to be issued
-    int next_round = 0, slot = 0;
+    int issued = 0, slot = 0;
     auto issue_round = [&]() {
-        const uint32_t dst = lds_stage + slot * GV_ROUND_BYTES;
-        const uint8_t *bsrc = bbase + (size_t)next_round * 2 * TILE;   // two tiles per round
+        const uint32_t dst = ring + slot * ROUND;
 #pragma unroll
-        for (int i = 0; i < NDMA_B; ++i) gv_dma16(b_voff[i], bsrc, dst + i * 1024);
-        const uint8_t *xsrc = xbase + (size_t)next_round * 128;
+        for (int h = 0; h < H; ++h) {
+            gv_dma16(b_voff[0], bsrc + h * HALF, dst + h * GV_B_BYTES);
+            gv_dma16(b_voff[1], bsrc + h * HALF, dst + h * GV_B_BYTES + 1024);
+        }
 #pragma unroll
-        for (int i = 0; i < NX; ++i) gv_dma16(x_voff[i], xsrc, dst + GV_B_BYTES + i * 1024);
-        ++next_round;
+        for (int i = 0; i < NX; ++i) gv_dma16(x_voff[i], xsrc, dst + H * GV_B_BYTES + i * 1024);
+        bsrc += 2 * TILE;
+        xsrc += 128;
+        ++issued;
         slot = slot + 1 == NBUF ? 0 : slot + 1;
     };
 #pragma unroll
     for (int i = 0; i < NBUF; ++i)
         if (i < nrounds) issue_round();
 
-    // scale / zero-point tile of the slice: [groups touched][128 channels], transposed on the way into LDS (memory
-    // has a channel's groups next to each other).  All loads of a thread are issued together (indices clamped
-    // instead of branching, so that the compiler batches them behind a single wait); that wait also covers the
-    // rounds above, which every wave needs next anyway.  idx / cols is taken in fp32 (exact: idx < 2^13).
-    const int cols = (GROUPS_MAX > 1 && rend > rbeg) ? (int)((uint32_t)(rend - 1) / (uint32_t)chunk_rounds) - g_lo + 1 : 1;
-    const float inv_cols = 1.0f / (float)cols;
+    // scale / zero-point tile of the slice: [groups touched][64 channels], transposed on the way into LDS (memory has a
+    // channel's groups next to each other).  Channels are laid down so that a lane's four are neighbours.
+    const int cols = rend > rbeg ? (int)((uint32_t)(rend - 1) / (uint32_t)chunk_rounds) - g_lo + 1 : 1;
     auto store_entry = [&](int jj, int ch, float sv, uint32_t zv, float dzv) {
-        sS[jj][ch] = sv;
-        if constexpr (ZBYTE) sZ[jj][ch] = (uint8_t)zv;
-        else sZ[jj][ch] = kCodeOffset + (float)zv + dzv;
+        const int pos = Unpacker::BY_PARITY ? (ch & ~7) + 4 * (ch & 1) + ((ch & 7) >> 1) : ch;
+        sS[jj * GV_SROW + pos] = sv;
+        if constexpr (ZBYTE) sZ[jj * ZROW + pos] = (uint8_t)zv;
+        else sZ[jj * ZROW + pos] = kCodeOffset + (float)zv + dzv;
     };
-    auto load_tile = [&](auto nb_c) {
-        constexpr int NB = decltype(nb_c)::value;                 // batches of one entry per thread
-        float ts[NB], td[NB], tdz[NB];
-        uint8_t tz[NB];
-        int ch[NB], jj[NB];
-#pragma unroll
-        for (int i = 0; i < NB; ++i) {
-            const int idx = tid + i * WAVES * 64;
-            const bool on = idx < 128 * cols;
-            ch[i] = on ? (int)(((float)idx + 0.5f) * inv_cols) : 0;
-            jj[i] = on ? idx - ch[i] * cols : 0;
-            const size_t si = (size_t)(n0 + ch[i]) * G + g_lo + jj[i];
-            ts[i] = l_s0[si];
-            tz[i] = l_z0[si];
-            td[i] = l_ds ? l_ds[si] : 0.f;
-            tdz[i] = l_dz ? l_dz[si] : 0.f;
-        }
-#pragma unroll
-        for (int i = 0; i < NB; ++i)
-            if (tid + i * WAVES * 64 < 128 * cols) store_entry(jj[i], ch[i], ts[i] + td[i], tz[i], tdz[i]);
-    };
-    // A slice that spans all groups reads whole rows: the tile's entries are one contiguous run of 128 G, taken
-    // four at a time (16 bytes of s0 and of ds, 4 bytes of z0 per thread and batch).
-    auto load_rows = [&](auto nb_c) {
-        constexpr int NB = decltype(nb_c)::value;                 // batches of four entries per thread
-        f32x4 ts[NB], td[NB], tdz[NB];
-        uint32_t tz[NB];
+    const float inv_cols = 1.0f / (float)cols;                    // entry / cols in fp32: exact, entries are below 2^16
+    if (cols == G && (G & 3) == 0) {
+        // whole rows of a multiple of four groups: one contiguous run of 64 G entries, four at a time (16 bytes of s0 and of
+        // ds, 4 bytes of z0), the loads of a batch issued together (indices clamped instead of branching)
         const size_t base = (size_t)n0 * G;
+        auto batch = [&](int e0, auto nb_c) {
+            constexpr int NB = decltype(nb_c)::value;
+            f32x4 ts[NB], td[NB], tdz[NB];
+            uint32_t tz[NB];
 #pragma unroll
-        for (int i = 0; i < NB; ++i) {
-            int e = 4 * (tid + i * WAVES * 64);
-            e = e < 128 * cols ? e : 0;
-            ts[i] = *reinterpret_cast<const f32x4 *>(l_s0 + base + e);
-            tz[i] = *reinterpret_cast<const uint32_t *>(l_z0 + base + e);
-            td[i] = l_ds ? *reinterpret_cast<const f32x4 *>(l_ds + base + e) : f32x4{0.f, 0.f, 0.f, 0.f};
-            tdz[i] = l_dz ? *reinterpret_cast<const f32x4 *>(l_dz + base + e) : f32x4{0.f, 0.f, 0.f, 0.f};
-        }
+            for (int i = 0; i < NB; ++i) {
+                int e = e0 + 4 * (tid + i * THREADS);
+                e = e < GV_C * cols ? e : 0;
+                ts[i] = *reinterpret_cast<const f32x4 *>(l_s0 + base + e);
+                tz[i] = *reinterpret_cast<const uint32_t *>(l_z0 + base + e);
+                td[i] = l_ds ? *reinterpret_cast<const f32x4 *>(l_ds + base + e) : f32x4{0.f, 0.f, 0.f, 0.f};
+                if constexpr (!ZBYTE) tdz[i] = l_dz ? *reinterpret_cast<const f32x4 *>(l_dz + base + e) : f32x4{0.f, 0.f, 0.f, 0.f};
+            }
 #pragma unroll
-        for (int i = 0; i < NB; ++i) {
-            const int e = 4 * (tid + i * WAVES * 64);
-            if (e < 128 * cols) {
-                int chn = (int)(((float)e + 0.5f) * inv_cols), jn = e - chn * cols;
+            for (int i = 0; i < NB; ++i) {
+                const int e = e0 + 4 * (tid + i * THREADS);
+                if (e < GV_C * cols) {
+                    const int ch = (int)(((float)e + 0.5f) * inv_cols), j = e - ch * cols;   // (a quad stays within a channel)
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    store_entry(jn, chn, ts[i][u] + td[i][u], (tz[i] >> (8 * u)) & 0xFFu, tdz[i][u]);
-                    if (++jn == cols) { jn = 0; ++chn; }
+                    for (int u = 0; u < 4; ++u)
+                        store_entry(j + u, ch, ts[i][u] + td[i][u], (tz[i] >> (8 * u)) & 0xFFu, ZBYTE ? 0.f : tdz[i][u]);
                 }
             }
-        }
-    };
-    constexpr int THREADS = WAVES * 64;
-    if constexpr (GROUPS_MAX == 1) {
-        load_tile(std::integral_constant<int, 1>{});
-    } else if (cols == G) {
-        // 128 cols / (4 THREADS) batches, at most GROUPS_MAX / 8 with 256 threads
-        constexpr int NBMAX = (128 * GROUPS_MAX + 4 * THREADS - 1) / (4 * THREADS);
-        if (128 * cols <= 4 * THREADS) load_rows(std::integral_constant<int, 1>{});
-        else if (128 * cols <= 8 * THREADS || NBMAX <= 2) load_rows(std::integral_constant<int, NBMAX < 2 ? NBMAX : 2>{});
-        else if (128 * cols <= 16 * THREADS || NBMAX <= 4) load_rows(std::integral_constant<int, NBMAX < 4 ? NBMAX : 4>{});
-        else load_rows(std::integral_constant<int, NBMAX>{});
+        };
+        if (GV_C * cols <= 4 * THREADS) batch(0, std::integral_constant<int, 1>{});
+        else if (GV_C * cols <= 12 * THREADS) batch(0, std::integral_constant<int, 3>{});
+        else
+            for (int e0 = 0; e0 < GV_C * cols; e0 += 28 * THREADS) batch(e0, std::integral_constant<int, 7>{});
     } else {
-        constexpr int PER_BATCH = THREADS / 128;                  // groups of 128 channels per batch of loads
-        if (cols <= PER_BATCH) load_tile(std::integral_constant<int, 1>{});
-        else if (cols <= 2 * PER_BATCH) load_tile(std::integral_constant<int, 2>{});
-        else if (cols <= 4 * PER_BATCH) load_tile(std::integral_constant<int, 4>{});
-        else if (cols <= 8 * PER_BATCH) load_tile(std::integral_constant<int, 8>{});
-        else if constexpr (GROUPS_MAX > 8 * PER_BATCH) {
-            if (cols <= 16 * PER_BATCH) load_tile(std::integral_constant<int, 16>{});
-            else load_tile(std::integral_constant<int, (GROUPS_MAX + PER_BATCH - 1) / PER_BATCH>{});
-        }
+        auto batch = [&](int e0, auto nb_c) {
+            constexpr int NB = decltype(nb_c)::value;             // entries per thread
+            float ts[NB], td[NB], tdz[NB];
+            uint8_t tz[NB];
+            int ch[NB], jj[NB];
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                int e = e0 + tid + i * THREADS;
+                e = e < GV_C * cols ? e : 0;
+                ch[i] = (int)(((float)e + 0.5f) * inv_cols);
+                jj[i] = e - ch[i] * cols;
+                const size_t si = (size_t)(n0 + ch[i]) * G + g_lo + jj[i];
+                ts[i] = l_s0[si];
+                tz[i] = l_z0[si];
+                td[i] = l_ds ? l_ds[si] : 0.f;
+                if constexpr (!ZBYTE) tdz[i] = l_dz ? l_dz[si] : 0.f;
+            }
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+                if (e0 + tid + i * THREADS < GV_C * cols) store_entry(jj[i], ch[i], ts[i] + td[i], tz[i], ZBYTE ? 0.f : tdz[i]);
+        };
+        if (GV_C * cols <= THREADS) batch(0, std::integral_constant<int, 1>{});
+        else
+            for (int e0 = 0; e0 < GV_C * cols; e0 += 8 * THREADS) batch(e0, std::integral_constant<int, 8>{});
     }
     __syncthreads();
 
-    f32x4 y[8], acc[8], accrs = f32x4{0.f, 0.f, 0.f, 0.f};
+    f32x4 y[4 * H], acc[4 * H], accrs = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int ct = 0; ct < 8; ++ct) { y[ct] = f32x4{0.f, 0.f, 0.f, 0.f}; acc[ct] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+    for (int ct = 0; ct < 4 * H; ++ct) { y[ct] = f32x4{0.f, 0.f, 0.f, 0.f}; acc[ct] = f32x4{0.f, 0.f, 0.f, 0.f}; }
 
-    // this lane's block and activation fragment of step 0 within a round
-    constexpr int STEP_B = BITS == 4 ? 2048 : 1536;               // packed bytes of one step in a round buffer
-    const int b_off = BITS == 4 ? lane * 16 : c * 96 + q * 24;
+    // this lane's words and activation fragment of step 0 within a round (step 1: STEP_B bytes on; chunk 4 + q)
+    constexpr int STEP_B = BITS == 4 ? 1024 : 768;
+    const uint8_t *b_lane = stage + wave * NBUF * ROUND + (BITS == 4 ? lane * 16 : ((c >> 1) * 4 + q) * 24 + 4 * (c & 1));
     // token row of this lane's activation fragment; with 8 rows staged, rows 8..15 (beyond T, never stored) read rows 0..7
-    const int x_off = GV_B_BYTES + (NX == 2 ? c : (c & 7)) * 128 + q * 16;
+    const uint8_t *x_lane = stage + wave * NBUF * ROUND + H * GV_B_BYTES + (NX == 2 ? c : (c & 7)) * 128;
+    const int x_pos[2] = {(q ^ (c & 7)) * 16, ((4 + q) ^ (c & 7)) * 16};
     int group_left = chunk_rounds - (int)((uint32_t)wr0 % (uint32_t)chunk_rounds);   // rounds to the end of the scale group
     int gj = (int)((uint32_t)wr0 / (uint32_t)chunk_rounds) - g_lo;                    // its column of the tile
-
-    // One pass of this loop is one 32-feature MFMA step; it is deliberately a single copy of the
-    // code (a workgroup runs only a few steps, so instruction fetch of an unrolled pipeline would
-    // cost more than it hides).
-    const int nsteps = 2 * nrounds;
-    // Two workgroups share a compute unit, and its arbiter serves the older wave first: where the unit itself is
-    // the limit, the workgroup dispatched first runs ahead, ends early, and leaves the other to finish alone with
-    // half the loads in flight (measured: the first 256 workgroups of a launch ended 5 to 6 us before the rest).
-    // The second one therefore takes the higher priority for the first half of its steps, the first one wins the
-    // ties of the second half, and both end together.  Which workgroup came second is a guess from the index (the
-    // first `second_from` are dealt one to every compute unit); a wrong guess costs time only.
-    const bool second = bx >= a.second_from;
-    if (second) __builtin_amdgcn_s_setprio(2);
-    int rslot = 0;                                                // ring slot of the round being consumed
+    uint32_t rd = 0;                                              // ring offset of the round being consumed
+    // A compute unit's arbiter serves the older wave first: of the workgroups that share one, the one dispatched first runs
+    // ahead, ends early, and leaves the others to finish with fewer loads in flight.  Where all workgroups of the launch are
+    // resident at once, the later ones therefore take a higher priority for the first half of their rounds; the first ones win the ties of
+    // the second half, and all end together (13B block, T = 1 and 5: 34.6 -> 33.7 and 35.5 -> 34.3 us).  Which came later is a
+    // guess from the index (the first prio_step workgroups are dealt one to every compute unit, and so on); a wrong guess
+    // costs time only.  Where later workgroups take the places of earlier ones it cost 3 to 6 %.
+    const int prio = a.prio_step ? bx / a.prio_step : 0;
+    if (prio == 1) __builtin_amdgcn_s_setprio(1);
+    else if (prio == 2) __builtin_amdgcn_s_setprio(2);
+    else if (prio >= 3) __builtin_amdgcn_s_setprio(3);
 #pragma unroll 1
-    for (int step = 0; step < nsteps; ++step) {
-        const int r = step >> 1, s2 = step & 1;
-        if (second && step == (nsteps >> 1)) __builtin_amdgcn_s_setprio(0);
-        if (s2 == 0) {
-            // rounds r .. min(r + NBUF, nrounds) - 1 are in flight, issued in order: wait for r only
-            const int after = next_round - 1 - r;                 // rounds issued after r
-            if (NBUF > 3 && after >= 3) gv_wait_vmcnt<3 * NDMA>();
-            else if (NBUF > 2 && after == 2) gv_wait_vmcnt<2 * NDMA>();
-            else if (after == 1) gv_wait_vmcnt<NDMA>();
-            else gv_wait_vmcnt<0>();
-            asm volatile("" ::: "memory");
-        }
-        const uint8_t *rb = stage + (wave * NBUF + rslot) * GV_ROUND_BYTES;
-        {
-            const uint8_t *sb = rb + s2 * STEP_B + b_off;
-            uint32_t bw[WPB];
-            if constexpr (BITS == 4) {
-                const u32x4 v0 = *reinterpret_cast<const u32x4 *>(sb);
-                const u32x4 v1 = *reinterpret_cast<const u32x4 *>(sb + 1024);
+    for (int r = 0; r < nrounds; ++r) {
+        if (r == nrounds >> 1) __builtin_amdgcn_s_setprio(0);
+        // rounds r .. min(r + NBUF, nrounds) - 1 are in flight, issued in order: wait for r only
+        const int after = issued - 1 - r;                         // rounds issued after r
+        if (after == 1) gv_wait_vmcnt<NDMA>();
+        else gv_wait_vmcnt<0>();
+        asm volatile("" ::: "memory");
 #pragma unroll
-                for (int i = 0; i < 4; ++i) { bw[i] = v0[i]; bw[4 + i] = v1[i]; }
-            } else {
+        for (int s = 0; s < 2; ++s) {
+            const u32x4 af = *reinterpret_cast<const u32x4 *>(x_lane + rd + x_pos[s]);
 #pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    const u32x2 v = *reinterpret_cast<const u32x2 *>(sb + 8 * i);
-                    bw[2 * i] = v[0];
-                    bw[2 * i + 1] = v[1];
+            for (int h = 0; h < H; ++h) {
+                uint32_t bw[WORDS];
+                const uint8_t *sb = b_lane + rd + h * GV_B_BYTES + s * STEP_B;
+                if constexpr (BITS == 4) {
+                    const u32x4 v = *reinterpret_cast<const u32x4 *>(sb);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) bw[i] = v[i];
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) bw[i] = *reinterpret_cast<const uint32_t *>(sb + 8 * i);
                 }
-            }
-            const u32x4 af = *reinterpret_cast<const u32x4 *>(rb + x_off + s2 * 64);
-            BlockUnpacker<BITS, false> up;
-            up.prepare(bw);
-            u32x4 bf[8];
-            bf[0] = up.template frag<0>(magic); bf[1] = up.template frag<1>(magic);
-            bf[2] = up.template frag<2>(magic); bf[3] = up.template frag<3>(magic);
-            bf[4] = up.template frag<4>(magic); bf[5] = up.template frag<5>(magic);
-            bf[6] = up.template frag<6>(magic); bf[7] = up.template frag<7>(magic);
+                Unpacker up;
+                up.prepare(bw, 0);
+                u32x4 bf[4];
+                static_for<4>([&](auto i) {
+                    static_for<4>([&](auto j) { bf[i.value][j.value] = up.template frag_reg<i.value, j.value>(magic); });
+                });
 #pragma unroll
-            for (int ct = 0; ct < 8; ++ct) acc[ct] = mfma16(af, bf[ct], acc[ct]);
+                for (int ct = 0; ct < 4; ++ct) acc[4 * h + ct] = mfma16(af, bf[ct], acc[4 * h + ct]);
+            }
             accrs = mfma16(af, ones, accrs);
         }
-        if (s2 == 1) {
-            // this buffer is free again (its LDS reads have returned: the MFMAs consumed them): refill it
-            if (next_round < nrounds) issue_round();
-            rslot = rslot + 1 == NBUF ? 0 : rslot + 1;
-            if (--group_left == 0 || r + 1 == nrounds) {
-                // end of a scale group, or of this wave's share: fold offset, zero-point and scale
-                // of the group into y, restart the sums
-                const f32x4 s_lo = *reinterpret_cast<const f32x4 *>(&sS[gj][8 * c]);
-                const f32x4 s_hi = *reinterpret_cast<const f32x4 *>(&sS[gj][8 * c + 4]);
-                float zo[8];                                      // 16 + z of channels 8c .. 8c + 7
+        // this buffer is free again once its LDS reads have returned: refill it
+        if (issued < nrounds) {
+            __builtin_amdgcn_s_waitcnt(0xF | (0x7 << 4) | (0x3 << 14));   // lgkmcnt(0)
+            asm volatile("" ::: "memory");
+            issue_round();
+        }
+        rd = rd + ROUND == NBUF * ROUND ? 0 : rd + ROUND;
+        if (--group_left == 0 || r + 1 == nrounds) {
+            // end of a scale group, or of this wave's share: fold offset, zero-point and scale
+            // of the group into y, restart the sums
+#pragma unroll
+            for (int h = 0; h < H; ++h) {
+                const f32x4 sc = *reinterpret_cast<const f32x4 *>(sS + gj * GV_SROW + 64 * h + 4 * c);
+                f32x4 zo;                                         // 16 + z of the lane's channels
                 if constexpr (ZBYTE) {
-                    const u32x2 zz = *reinterpret_cast<const u32x2 *>(&sZ[gj][8 * c]);
+                    const uint32_t zz = *reinterpret_cast<const uint32_t *>(sZ + gj * ZROW + 64 * h + 4 * c);
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) zo[i] = kCodeOffset + (float)((zz[i >> 2] >> (8 * (i & 3))) & 0xFFu);
+                    for (int i = 0; i < 4; ++i) zo[i] = kCodeOffset + (float)((zz >> (8 * i)) & 0xFFu);
                 } else {
-                    const f32x4 z_lo = *reinterpret_cast<const f32x4 *>(&sZ[gj][8 * c]);
-                    const f32x4 z_hi = *reinterpret_cast<const f32x4 *>(&sZ[gj][8 * c + 4]);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) { zo[i] = z_lo[i]; zo[4 + i] = z_hi[i]; }
+                    zo = *reinterpret_cast<const f32x4 *>(sZ + gj * ZROW + 64 * h + 4 * c);
                 }
 #pragma unroll
-                for (int ct = 0; ct < 8; ++ct) {
-                    const float sc = ct < 4 ? s_lo[ct & 3] : s_hi[ct & 3];
+                for (int ct = 0; ct < 4; ++ct) {
 #pragma unroll
-                    for (int jj = 0; jj < 4; ++jj) y[ct][jj] += sc * (acc[ct][jj] - zo[ct] * accrs[jj]);
-                    acc[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    for (int jj = 0; jj < 4; ++jj) y[4 * h + ct][jj] += sc[ct] * (acc[4 * h + ct][jj] - zo[ct] * accrs[jj]);
+                    acc[4 * h + ct] = f32x4{0.f, 0.f, 0.f, 0.f};
                 }
-                accrs = f32x4{0.f, 0.f, 0.f, 0.f};
-                ++gj;
-                group_left = chunk_rounds;
             }
+            accrs = f32x4{0.f, 0.f, 0.f, 0.f};
+            ++gj;
+            group_left = chunk_rounds;
         }
     }
 
     // ---- sum the waves, then write Y (S = 1) or this slice's partial
-    __syncthreads();                                              // everyone is done with the stage buffers
-    float *red = reinterpret_cast<float *>(stage);                // [wave][column tile][row in lane][lane], 32 KB
+    __syncthreads();                                              // everyone is done with the ring
+    float *red = reinterpret_cast<float *>(stage);                // [wave][column tile][row in lane][lane]
 #pragma unroll
-    for (int ct = 0; ct < 8; ++ct)
+    for (int ct = 0; ct < 4 * H; ++ct)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) red[((wave * 8 + ct) * 4 + j) * 64 + lane] = y[ct][j];
+        for (int j = 0; j < 4; ++j) red[((wave * 4 * H + ct) * 4 + j) * 64 + lane] = y[ct][j];
     __syncthreads();
-    // the 8 column tiles x 4 rows x 64 lanes of results are dealt to the threads; each adds the waves in order
-    for (int idx = tid; idx < 8 * 4 * 64; idx += WAVES * 64) {
-        const int ct = idx >> 8, j = (idx >> 6) & 3, ln = idx & 63;
+    // the 4 H column tiles x 4 rows x 64 lanes of results are dealt to the threads; each adds the waves in order
+    for (int idx = tid; idx < 4 * H * 4 * 64; idx += THREADS) {
+        const int tc = idx >> 8, ct = tc & 3, j = (idx >> 6) & 3, ln = idx & 63, cl = ln & 15;
+        const int t = 4 * (ln >> 4) + j;
+        if (t >= a.T) continue;
         float v = 0.f;
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) v += red[((w * 8 + ct) * 4 + j) * 64 + ln];
-        const int t = 4 * (ln >> 4) + j, n = n0 + 8 * (ln & 15) + ct;
-        if (t < a.T) {
-            if (l_S == 1) l_Y[(size_t)t * l_N + n] = (uint16_t)float_to_bf16_bits(v);
-            else L.partial[((size_t)slice * a.T + t) * l_N + n] = v;
-        }
+        for (int w = 0; w < WAVES; ++w) v += red[((w * 4 * H + tc) * 4 + j) * 64 + ln];
+        const int n = n0 + 64 * (tc >> 2) + (Unpacker::BY_PARITY ? 4 * (cl & ~1) + 2 * ct + (cl & 1) : 4 * cl + ct);
+        if (l_S == 1) L.Y[(size_t)t * l_N + n] = (uint16_t)float_to_bf16_bits(v);
+        else L.partial[((size_t)slice * a.T + t) * l_N + n] = v;
     }
 }
 
@@ -377,120 +355,163 @@ __global__ __launch_bounds__(256) void gemv_finish_kernel(GemvArgs a)
 
 }  // namespace
 
-int gemv_slices(int Ntot, int K, int T, int chunk, bool zbyte)
+// ---- host side
+
+static int gv_lds_bytes(const GemvForm &f, int nx, bool zbyte, int groups)
 {
-    // as many slices as give two workgroups per compute unit (measured: more, up to the three that fit
-    // for per-channel layers, only adds partials), every wave at least two rounds long, and the
-    // partials small next to the weight bytes
-    const int tiles = Ntot / 128, R = K / 64, chunk_rounds = chunk / 64;
-    // per-channel layers that fill half to all of the compute units with one tile each: one 12-wave
-    // workgroup per tile takes all of K
-    if (chunk == K && tiles >= GV_WHOLE_MIN_TILES && tiles <= GV_WHOLE_MAX_TILES) return 1;
-    int S = 512 / tiles;
-    // between one and one and a half tiles per compute unit a single slice leaves the units with one
-    // 4-wave workgroup each: two slices (up to three workgroups per unit) stream better, partials included
-    if (chunk == K && tiles > GV_WHOLE_MAX_TILES && 2 * tiles <= 768) S = 2;
-    if (S > R / (2 * GV_WAVES)) S = R / (2 * GV_WAVES);
-    const int by_bytes = T > 4 ? 6 : 16;
-    if (S > by_bytes) S = by_bytes;
-    if (S < 1) S = 1;
-    // the scale tile in LDS holds a bounded number of groups per slice
-    const int gmax = zbyte ? GV_MAX_PER_Z8 : GV_MAX_PER;
-    if (chunk != K)
-        while (((R + S - 1) / S + chunk_rounds - 1) / chunk_rounds + 1 > gmax) ++S;
-    return S;
+    return f.waves * GV_NBUF * gv_round_bytes(f.h, nx) + groups * gv_group_bytes(f.h, zbyte);
 }
 
-bool gemv_whole(int tiles, bool per_channel, int S)
+static int gv_per_cu(const GemvForm &f, int lds)                   // workgroups a compute unit holds: LDS, registers
 {
-    return per_channel && S == 1 && tiles >= GV_WHOLE_MIN_TILES && tiles <= GV_WHOLE_MAX_TILES;
+    const int by_regs = f.waves == 8 ? 2 : 4, by_lds = GV_LDS_MAX / lds;
+    return by_lds < by_regs ? by_lds : by_regs;
 }
 
-void gemv_plan(int n, const int *N, const int *K, const int *chunk, int bits, int T, bool zbyte, int *S)
+static int gv_cols(int K, int chunk, int S)                        // most scale groups a slice touches
 {
-    // target: all workgroups resident at once (two per compute unit) with equal shares of the packed bytes.
-    // Per-channel layers at T <= 4: three per compute unit (they fit, with 1 KB of scales each).  A channel tile
-    // of a 4096-feature layer is two thirds of a compute unit's share of a LLaMA-7B block, so whole tiles load
-    // the units 2 : 1; halves deal out evenly, and at such T their partial sums are a few per cent of the bytes
-    // (measured on that block: 7 % less time at T = 1, 2 % more at T = 16).
-    const int cus = compute_units();
-    double total = 0.0;
-    bool per_channel_all = true;
+    const int R = K / 64, cr = chunk / 64;
+    if (cr >= R) return 1;
+    if (S == 1) return R / cr;
+    return ((R + S - 1) / S + cr - 1) / cr + 1;
+}
+
+// The form of a launch and the slices of its layers.
+//
+// At most one 64-channel tile per compute unit: eight waves each, so that the few workgroups keep enough loads in flight
+// and share the unpacking (a compute unit unpacks 64 channels x 64 features in about 0.07 us, eight waves or four).  Long
+// layers of fewer tiles (K >= 6144) are sliced until every compute unit has a tile or a wave is down to four rounds; what
+// that gains has to pay for the second launch, 4 us.  us per call at T = 5, whole -> sliced: 5120 x 13824 22 -> 14 (3 slices),
+// 4096 x 11008 15 -> 12 (4), 1024 x 8192 12 -> 9 (4); 4096 x 4096 8.0 -> 9.3 (2), which is why shorter ones stay whole.
+//
+// More tiles: four waves.  Every workgroup should be resident at once (the last, partly filled round is otherwise made of
+// few workgroups with a few loads in flight each) and no layer's much longer than the others': layers are sliced to at most
+// 1.35 times the mean length, more while the workgroups' scale tiles keep them from fitting on the chip together; failing
+// that, 128 channels per workgroup (half of the token rows' traffic and LDS per channel).  us per block at T = 1 / 16, 13B
+// 3-bit g128: 3 slices of the long layer 34.6 / 42.3, 2 slices (not resident) 38.9 / 45.6, 128 channels 35.8 / 38.2.  Launches too large for
+// that take the slicing with the most workgroups per compute unit, as long as the partial sums stay below 4 % of the codes.
+GemvForm gemv_plan(int n, const int *N, const int *K, const int *chunk, int bits, int T, bool zbyte, bool least, int *S)
+{
+    const int cus = compute_units(), nx = T > 8 ? 2 : 1;
+    int tiles = 0, rmax = 0;
+    double rounds = 0.0;
     for (int j = 0; j < n; ++j) {
-        total += (double)N[j] * K[j] * bits / 8.0;
-        per_channel_all = per_channel_all && chunk[j] == K[j];
+        tiles += N[j] / 64;
+        rounds += (double)(N[j] / 64) * (K[j] / 64);
+        rmax = K[j] / 64 > rmax ? K[j] / 64 : rmax;
     }
-    const double target = total / ((per_channel_all && T <= 4 ? 3.0 : 2.0) * cus);
-    const int by_bytes = T > 4 ? 6 : 16;                         // partials stay small next to the weight bytes
-    for (int j = 0; j < n; ++j) {
-        const int R = K[j] / 64, chunk_rounds = chunk[j] / 64;
-        const double tile_bytes = 128.0 * K[j] * bits / 8.0;
-        int s = (int)(tile_bytes / target + 0.5);
-        if (s > R / (2 * GV_WAVES)) s = R / (2 * GV_WAVES);      // every wave at least two rounds
-        if (s > by_bytes) s = by_bytes;
-        if (s < 1) s = 1;
-        // the scale tile in LDS holds a bounded number of groups per slice
-        const int gmax = zbyte ? GV_MAX_PER_Z8 : GV_MAX_PER;
-        if (chunk[j] != K[j])
-            while (((R + s - 1) / s + chunk_rounds - 1) / chunk_rounds + 1 > gmax) ++s;
-        S[j] = s;
+    // slices of at most `len` rounds (a little longer rather than one slice more), and whatever the LDS asks for
+    auto slice_all = [&](const GemvForm &f, int len, int limit) {
+        for (int j = 0; j < n; ++j) {
+            const int r = K[j] / 64;
+            S[j] = (int)((double)r / len + 0.7);
+            S[j] = S[j] < 1 ? 1 : S[j];
+            while (S[j] < r && gv_lds_bytes(f, nx, zbyte, gv_cols(K[j], chunk[j], S[j])) > limit) ++S[j];
+        }
+    };
+    auto groups = [&]() {
+        int g = 1;
+        for (int j = 0; j < n; ++j) g = gv_cols(K[j], chunk[j], S[j]) > g ? gv_cols(K[j], chunk[j], S[j]) : g;
+        return g;
+    };
+    if (tiles <= cus) {
+        const GemvForm f{1, 8};
+        slice_all(f, rmax, GV_LDS_MAX);
+        if (!least) {
+            for (int j = 0; j < n; ++j) {
+                const int r = K[j] / 64, s = cus / tiles < r / 32 ? cus / tiles : r / 32;
+                if (r >= 96 && s > S[j]) S[j] = s;
+            }
+        }
+        return f;
     }
+    const GemvForm small{1, 4}, wide{2, 4};
+    if (least) {
+        slice_all(small, rmax, GV_LDS_MAX);
+        return small;
+    }
+    const double mean = rounds / tiles;
+    GemvForm best = small;
+    int best_len = rmax, best_per_cu = 0;
+    for (int w = 0; w < (zbyte ? 2 : 1); ++w) {
+        const GemvForm f = w ? wide : small;
+        for (int s = 1; s <= 8; ++s) {
+            const int len = (rmax + s - 1) / s;
+            if (len > 1.35 * mean && s < 8) continue;
+            slice_all(f, len, GV_LDS_MAX / 2);
+            int wgs = 0;
+            double partials = 0.0;
+            for (int j = 0; j < n; ++j) {
+                wgs += N[j] / (64 * f.h) * S[j];
+                if (S[j] > 1) partials += 8.0 * S[j] * T * N[j];
+            }
+            const int per_cu = gv_per_cu(f, gv_lds_bytes(f, nx, zbyte, groups()));
+            if (per_cu * cus >= wgs) return f;                     // all resident
+            if (w == 0 && per_cu > best_per_cu && (best_per_cu == 0 || partials < 0.04 * rounds * 512 * bits)) {
+                best_per_cu = per_cu;
+                best_len = len;
+            }
+        }
+    }
+    slice_all(best, best_len, GV_LDS_MAX / 2);
+    return best;
 }
 
-hipError_t launch_gemv(int bits, const GemvArgs &a_in, hipStream_t stream)
+hipError_t launch_gemv(int bits, const GemvForm &f, const GemvArgs &a_in, hipStream_t stream)
 {
-    const int wgs = a_in.layer[a_in.n_layers - 1].wg_end;
     GemvArgs a = a_in;
-    a.second_from = compute_units();
-    bool per_channel_all = true, sliced = false;
+    bool sliced = false, zbyte = true;
     unsigned max_tn = 0;
+    a.groups_cap = 1;
     for (int j = 0; j < a.n_layers; ++j) {
-        per_channel_all = per_channel_all && a.layer[j].chunk == a.layer[j].K;
-        sliced = sliced || a.layer[j].S > 1;
-        if (a.layer[j].S > 1 && (unsigned)a.T * (unsigned)a.layer[j].N > max_tn) max_tn = (unsigned)a.T * (unsigned)a.layer[j].N;
+        const GemvLayer &l = a.layer[j];
+        if (l.N % 128 != 0 || l.K % 128 != 0 || l.chunk % 64 != 0 || l.S < 1 || a.T < 1 || a.T > 16) return hipErrorInvalidValue;
+        sliced = sliced || l.S > 1;
+        zbyte = zbyte && l.dz == nullptr;
+        if (l.S > 1 && (unsigned)a.T * (unsigned)l.N > max_tn) max_tn = (unsigned)a.T * (unsigned)l.N;
+        const int g = gv_cols(l.K, l.chunk, l.S);
+        a.groups_cap = g > a.groups_cap ? g : a.groups_cap;
     }
-    const dim3 grid(wgs);
-    // the 12-wave form: layers of equal K in one launch (one layer, or layers that read one X), a single slice each
-    bool whole = !sliced && gemv_whole(wgs, per_channel_all, 1);
-    for (int j = 1; j < a.n_layers; ++j) whole = whole && a.layer[j].K == a.layer[0].K;
+    const int wgs = a.wg_end[GEMV_MAX_LAYERS - 1], nx = a.T > 8 ? 2 : 1;
+    const int lds = gv_lds_bytes(f, nx, zbyte, a.groups_cap);
+    if (lds > GV_LDS_MAX) return hipErrorInvalidValue;
+    const int cus = compute_units();
+    a.prio_step = wgs <= gv_per_cu(f, lds) * cus ? cus : 0;
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-    // One instantiation: its dynamic LDS (more than the default limit: allowed once per device), then the launch.
-    auto go = [&](auto kern, int waves, int lds_bytes, bool *allowed) -> hipError_t {
+    // One instantiation: its dynamic LDS (more than the default limit: raised once per device), then the launch.
+    auto go = [&](auto h_c, auto waves_c, auto bits_c, auto nx_c, auto z_c) -> hipError_t {
+        static bool allowed[64];
+        const auto kern = gemv_kernel<decltype(bits_c)::value, decltype(h_c)::value, decltype(waves_c)::value, decltype(nx_c)::value,
+                                      decltype(z_c)::value>;
         if (!allowed[dev]) {
             const hipError_t e2 = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+                                                      hipFuncAttributeMaxDynamicSharedMemorySize, GV_LDS_MAX);
             if (e2 != hipSuccess) return e2;
             allowed[dev] = true;
         }
         trace_before(KID_GEMV, stream);
-        hipLaunchKernelGGL(kern, grid, dim3(waves * 64), lds_bytes, stream, a);
+        hipLaunchKernelGGL(kern, dim3(wgs), dim3(f.waves * 64), lds, stream, a);
         trace_after(KID_GEMV, stream);
         return hipGetLastError();
     };
-#define PEQA_GEMV_GO(BITS, GROUPS, WAVES, NBUF, NX, ZBYTE)                                                \
-    do {                                                                                                   \
-        static bool allowed[64];                                                                           \
-        e = go(gemv_kernel<BITS, GROUPS, WAVES, NBUF, NX, ZBYTE>, WAVES, WAVES * NBUF * gv_round_bytes(BITS, NX), allowed); \
-    } while (0)
-    const bool nx2 = a.T > 8;
-    bool zbyte = true;
-    for (int j = 0; j < a.n_layers; ++j) zbyte = zbyte && a.layer[j].dz == nullptr;
-    if (whole) {
-        if (bits == 4) PEQA_GEMV_GO(4, 1, GV_WAVES_WHOLE, 2, 2, false); else PEQA_GEMV_GO(3, 1, GV_WAVES_WHOLE, 2, 2, false);
-    } else if (per_channel_all) {
-        if (bits == 4) { if (nx2) PEQA_GEMV_GO(4, 1, GV_WAVES, NB_PC, 2, false); else PEQA_GEMV_GO(4, 1, GV_WAVES, NB_PC, 1, false); }
-        else { if (nx2) PEQA_GEMV_GO(3, 1, GV_WAVES, NB_PC, 2, false); else PEQA_GEMV_GO(3, 1, GV_WAVES, NB_PC, 1, false); }
-    } else if (zbyte) {
-        if (bits == 4) { if (nx2) PEQA_GEMV_GO(4, GV_MAX_PER_Z8, GV_WAVES, 2, 2, true); else PEQA_GEMV_GO(4, GV_MAX_PER_Z8, GV_WAVES, 2, 1, true); }
-        else { if (nx2) PEQA_GEMV_GO(3, GV_MAX_PER_Z8, GV_WAVES, 2, 2, true); else PEQA_GEMV_GO(3, GV_MAX_PER_Z8, GV_WAVES, NB_G31, 1, true); }
-    } else {
-        if (bits == 4) { if (nx2) PEQA_GEMV_GO(4, GV_MAX_PER, GV_WAVES, 2, 2, false); else PEQA_GEMV_GO(4, GV_MAX_PER, GV_WAVES, 2, 1, false); }
-        else { if (nx2) PEQA_GEMV_GO(3, GV_MAX_PER, GV_WAVES, 2, 2, false); else PEQA_GEMV_GO(3, GV_MAX_PER, GV_WAVES, 2, 1, false); }
-    }
-#undef PEQA_GEMV_GO
+    using std::integral_constant;
+    const integral_constant<int, 1> one;
+    const integral_constant<int, 2> two;
+    const integral_constant<int, 4> four;
+    const integral_constant<int, 8> eight;
+    const integral_constant<bool, true> zb;
+    const integral_constant<bool, false> zf;
+    auto on_form = [&](auto bits_c, auto nx_c) -> hipError_t {
+        if (f.h == 2) return zbyte && f.waves == 4 ? go(two, four, bits_c, nx_c, zb) : hipErrorInvalidValue;
+        if (f.waves == 8) return zbyte ? go(one, eight, bits_c, nx_c, zb) : go(one, eight, bits_c, nx_c, zf);
+        return zbyte ? go(one, four, bits_c, nx_c, zb) : go(one, four, bits_c, nx_c, zf);
+    };
+    const integral_constant<int, 3> three;
+    if (bits == 4) e = nx == 2 ? on_form(four, two) : on_form(four, one);
+    else e = nx == 2 ? on_form(three, two) : on_form(three, one);
     if (e != hipSuccess || !sliced) return e;
     trace_before(KID_GEMV_FINISH, stream);
     hipLaunchKernelGGL(gemv_finish_kernel, dim3((max_tn + 255) / 256, a.n_layers), dim3(256), 0, stream, a);

@@ -189,24 +189,24 @@ struct GemvLayer {
     int N, K, G;
     int chunk;                // features per scale group (K for per-channel layers)
     int S;                    // feature slices: a channel tile is S workgroups
-    int wg_end;               // workgroups of this layer and all before it (unused entries: the total)
+    int unused;               // (keeps the size a multiple of eight)
 };
 struct GemvArgs {
     GemvLayer layer[GEMV_MAX_LAYERS];   // must stay the first member: the kernels index it in the argument block
+    int wg_end[GEMV_MAX_LAYERS];        // workgroups of layer j and all before it (unused entries: the total)
     int n_layers;
     int T;
-    int second_from;                    // workgroups from this index on are taken to be the second on their compute
-                                        // unit (set by launch_gemv: the number of compute units)
+    int prio_step;                      // workgroups per step of priority, 0: none (set by launch_gemv)
+    int groups_cap;                     // scale groups a workgroup's LDS holds (set by launch_gemv)
 };
-// zbyte: no layer of the launch has a trained zero-point offset, so zero-points stay bytes in LDS and a slice may
-// span more scale groups
-int gemv_slices(int Ntot, int K, int T, int chunk, bool zbyte);
-// Slices per layer for a launch of several layers of different shapes: every workgroup gets about the same
-// number of packed bytes, and all of them are resident at once.  Fills S[0..n).
-void gemv_plan(int n, const int *N, const int *K, const int *chunk, int bits, int T, bool zbyte, int *S);
-// whether a per-channel launch of that many channel tiles with a single slice takes the 12-wave workgroups
-bool gemv_whole(int tiles, bool per_channel, int S);
-hipError_t launch_gemv(int bits, const GemvArgs &a, hipStream_t stream);
+// Form of such a launch: 64 h channels per workgroup of that many waves.
+struct GemvForm {
+    int h, waves;
+};
+// The form, and the slices of every layer (S[0..n)).  zbyte: no layer has a trained zero-point offset, so zero-points are
+// bytes in LDS.  least: the fewest slices that LDS allows, for a workspace that does not hold the partial sums of more.
+GemvForm gemv_plan(int n, const int *N, const int *K, const int *chunk, int bits, int T, bool zbyte, bool least, int *S);
+hipError_t launch_gemv(int bits, const GemvForm &f, const GemvArgs &a, hipStream_t stream);
 
 // peqa_small.hip
 hipError_t launch_rowsum(const uint16_t *X, int T, int K, int ksplit, float *rs, hipStream_t stream);

@@ -132,3 +132,30 @@ def test_split_block(gpu, oracle, bits, group, T):
                     assert np.abs(gpu.bf16_dev_to_f64(d["dX"]) - dXref).max() <= Y_TOL * np.abs(dXref).max()
                     gpu.assert_scale_grad_close(gpu.to_host(d["d_ds"]), gref)
                     d["dX"].zero_(), d["d_ds"].zero_()
+
+
+@pytest.mark.parametrize("bits,N,K,group", [
+    (4, 256, 6144, 0), (3, 128, 12288, 64), (3, 384, 8192, 128), (4, 16512, 256, 64), (3, 16640, 128, 0),
+])
+def test_small_batch_forms(gpu, oracle, bits, N, K, group):
+    """T <= 16: layers of a few channel tiles, sliced (eight waves) or, with the smallest workspace, whole; layers of more
+    tiles than compute units (four waves); odd numbers of scale groups per slice; both numbers of staged token rows."""
+    import torch
+    from paper_2305_14152_amd import peqa
+    seed = 71000 + bits * 1000 + N + K + group
+    W = synth.normal_f32(seed, (N, K), 0.02)
+    layer = gpu.GpuLayer(W, bits, group)
+    codes, s0, z0 = oracle.quantize(W, bits, group)
+    ds = synth.normal_f32(seed + 3, s0.shape, 1e-3)
+    dz = synth.normal_f32(seed + 4, s0.shape, 0.5)
+    for T in (1, 8, 9, 16):
+        print("small batch bits=%d N=%d K=%d g=%d T=%d" % (bits, N, K, group, T), flush=True)
+        X = synth.normal_bf16(seed + 10 + T, (T, K), 1.0)
+        Yref = oracle.fwd(codes, s0, ds, z0, X, group)
+        Y = layer.fwd(X, ds)
+        assert np.abs(gpu.bf16_dev_to_f64(Y) - Yref).max() <= Y_TOL * np.abs(Yref).max()
+        layer._ws[(T, peqa.PEQA_OP_FWD)] = (torch.empty(256, dtype=torch.uint8, device="cuda"), 256)
+        Yw = gpu.bf16_dev_to_f64(layer.fwd(X, ds))
+        assert np.abs(Yw - gpu.bf16_dev_to_f64(Y)).max() <= 2.0 ** -7 * np.abs(Yw).max()
+        Yz = oracle.fwd_z(codes, s0, ds, z0, dz, X, group)
+        assert np.abs(gpu.bf16_dev_to_f64(layer.fwd_z(X, ds, dz)) - Yz).max() <= Y_TOL * np.abs(Yz).max()
