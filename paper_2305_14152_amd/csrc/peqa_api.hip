@@ -648,14 +648,15 @@ static peqa_status bwd_impl(const peqa_layout *L, const uint32_t *packed, const 
     bool pair = d_ds && dX && peqa::gemm_four_waves(1 << 30);
     if (peqa::options().bwd_pair >= 0) pair = d_ds && dX && peqa::options().bwd_pair == 1;
     peqa::GemmArgs a_dds{}, a_dx{};
-    // a split scale gradient leaves one row of partials per token tile and piece
+    // a split scale gradient (paired with dX only) leaves one row of partials per token tile and piece
+    if (!pair) w.split_dds = 1;
     float *partial = reinterpret_cast<float *>(ws + (w.split_dds > 1 ? w.acc_dds : w.partial));
     const int partial_rows = tiles_t * w.split_dds;
     float *acc = reinterpret_cast<float *>(ws + w.acc);
     if (d_ds) {
-        // row sums of X over the two contraction halves: the caller's (peqa_row_sums), or taken here
+        // row sums of X over the two contraction halves: the caller's (peqa_row_sums), or taken here (pieces take their own)
         const float *rs = row_sums;
-        if (!rs) {
+        if (!rs && w.split_dds == 1) {
             float *own = reinterpret_cast<float *>(ws + w.rs);
             if (peqa::launch_rowsum(X, T, K, split_point(K), own, s) != hipSuccess) return PEQA_ERR_DEVICE;
             rs = own;

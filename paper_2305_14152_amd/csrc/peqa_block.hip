@@ -337,7 +337,7 @@ peqa_status peqa_block_bwd(int32_t n, const peqa_block_item *items, int32_t T, v
             float *dst = nullptr;
             for (int j = 0; j < n; ++j)
                 if (xi[j] == i && !grouped(&items[j].layout)) {
-                    wanted = wanted || items[j].d_ds != nullptr;
+                    wanted = wanted || (items[j].d_ds != nullptr && w.split_dds[j] == 1);   // pieces take their own
                     if (items[j].row_sums) have = items[j].row_sums;
                     if (!dst) dst = reinterpret_cast<float *>(ws + w.rs[j]);
                 }

@@ -55,6 +55,13 @@ __device__ __forceinline__ uint32_t scale_pair(uint32_t pair, float s_lo, float 
     return d;
 }
 
+// c + a.lo + a.hi of a bf16 pair, in fp32 (one dot instruction against ones).
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ float add_pair(uint32_t a, float c)
+{
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a), __builtin_bit_cast(bf16x2, 0x3F803F80u), c, false);
+}
+
 // ((x shifted) & mask) | magic in two VALU ops (one when no shift is needed).  mask rides the
 // constant bus (SGPR), magic a VGPR.  Volatile assembly, shift included, so that the unpacking
 // stays exactly where the caller interleaves it with matrix instructions.

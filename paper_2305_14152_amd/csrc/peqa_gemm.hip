@@ -78,6 +78,7 @@ __global__ __launch_bounds__(256, 2) void gemm_bwd_pair_kernel(GemmArgs a_dds, G
     const bool first = b < n_first;
     const int wg = first ? b : b - n_first;
     if (first == (dx_first != 0)) gemm_tile<BITS, MODE_DX, false, 1>(a_dx, wg, lds);
+    else if (a_dds.split > 1) gemm_tile<BITS, MODE_DDS, false, 1, true>(a_dds, wg, lds);
     else gemm_tile<BITS, MODE_DDS, false, 1>(a_dds, wg, lds);
 }
 
@@ -159,6 +160,7 @@ __global__ __launch_bounds__(256, 2) void gemm_multi_kernel(MultiArgs m)
     } else {
         const int mode = kernarg_load<int>((uint32_t)(j * sizeof(MultiJob) + offsetof(MultiJob, mode)));
         if (mode == MODE_Y) gemm_tile<BITS, MODE_Y, false, 1>(a, b - wg0, lds);
+        else if (mode == MODE_DDS && a.split > 1) gemm_tile<BITS, MODE_DDS, false, 1, true>(a, b - wg0, lds);
         else if (mode == MODE_DDS) gemm_tile<BITS, MODE_DDS, false, 1>(a, b - wg0, lds);
         else gemm_tile<BITS, MODE_DX, false, 1>(a, b - wg0, lds);
     }

@@ -43,7 +43,8 @@ struct GemmArgs {
     uint16_t *tp_Xt, *tp_dYt;
     uint16_t *out;            // [T, C] bf16    (MODE_Y: Y, MODE_DX: dX)
     // pieces of the contraction per tile (0 or 1: whole).  MODE_Y, MODE_DX: piece p leaves its sums in acc_part [split, T, C]
-    // fp32 for launch_split_finish; MODE_DDS: its column sums in row p tiles_t + tile_t of `partial`.
+    // fp32 for launch_split_finish; MODE_DDS (launches of several contractions only): its column sums in row
+    // p tiles_t + tile_t of `partial`, and needs no rs.
     int split;
     float *acc_part;
     float *P;                 // [T, N] fp32 or NULL (MODE_Y, per-channel): sum_k X[t,k] (Q[i,k] - z0[i]), kept

@@ -46,13 +46,18 @@ constexpr int frag_reg_after(int m)
     return -1;
 }
 
-template <int BITS, int MODE, bool GROUPED, int KW>
+// ROW_SUMS (the scale gradient in pieces): the row sums of X over the piece, which take the code offset and the zero-point out
+// of its sums before they are added to the other pieces' (taken out of the total only, they cost a digit of the result), are
+// added up beside the matrix instructions: eight dot instructions per wave and step, 6 % of the launch, which is why whole
+// contractions are handed the sums over the halves of K (8 bytes per row, one short launch per step and input).
+template <int BITS, int MODE, bool GROUPED, int KW, bool ROW_SUMS = false>
 __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8_t *lds)
 {
     constexpr int STAGE_BYTES = stage_bytes(KW);
     constexpr bool ALONG_CH = (MODE == MODE_DX);           // contraction over output channels
     constexpr bool SCALED = GROUPED && MODE != MODE_DDS;   // the scale is applied inside the loop: weights enter the MFMA scaled
     constexpr bool PAIRED = GROUPED && MODE == MODE_DDS;   // one scale group per contraction half
+    static_assert(!ROW_SUMS || (!GROUPED && MODE == MODE_DDS && KW == 1), "row sums per piece: scale gradient, four waves");
     static_assert(KW == 2 || (KW == 1 && !PAIRED), "the paired scale gradient needs both contraction halves");
     typedef HalfBlockUnpacker<BITS, ALONG_CH> Unpacker;
     constexpr int WORDS = Unpacker::WORDS;
@@ -274,15 +279,22 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
     // addressed from one lane-dependent base register each (kept live across the loop), the rest is literal.
     constexpr int HALF_RING = (NSTAGE / 2) * STAGE_BYTES;
     static_assert((NSTAGE / 2 - 1) * STAGE_BYTES + 8192 <= 65536, "literal offsets of LDS reads");
-    // row 16 rt + c (the swizzle only looks at row % 16)
-    const uint8_t *a_rd[2], *b_rd[2];
-    a_rd[0] = lds + wk * A_HALF_BYTES + c * 64 + ((q ^ a_swizzle(c)) << 4);
-    a_rd[1] = a_rd[0] + HALF_RING;
+    // row 16 rt' + c (the swizzle only looks at row % 16).  Where the row sums are taken, row tile rt of the wave's registers is row
+    // tile rt' = rt ^ 2 wn of the tile: registers 0 and 1 are then other rows in each of the four waves, which together add
+    // up all 128 rows (two dot instructions per register: 8 per wave and step).
+    constexpr int NPAIR = ROW_SUMS ? 4 : 1;                // pairs of row tiles with a base register of their own
+    const uint8_t *a_rd[2][NPAIR], *b_rd[2];
+#pragma unroll
+    for (int p = 0; p < NPAIR; ++p) {
+        a_rd[0][p] = lds + wk * A_HALF_BYTES + c * 64 + ((q ^ a_swizzle(c)) << 4) + (ROW_SUMS ? (p ^ wn) * 2048 : 0);
+        a_rd[1][p] = a_rd[0][p] + HALF_RING;
+    }
     b_rd[0] = lds + KW * A_HALF_BYTES + wave * B_WAVE_BYTES + b_lane_off;
     b_rd[1] = b_rd[0] + HALF_RING;
     auto read_a = [&](auto st_c, u32x4 *af, int rt) __attribute__((always_inline)) {
         constexpr int ST = decltype(st_c)::value;
-        af[rt] = *reinterpret_cast<const u32x4 *>(a_rd[ST / (NSTAGE / 2)] + (ST % (NSTAGE / 2)) * STAGE_BYTES + rt * 16 * 64);
+        af[rt] = *reinterpret_cast<const u32x4 *>(a_rd[ST / (NSTAGE / 2)][NPAIR == 4 ? rt >> 1 : 0] + (ST % (NSTAGE / 2)) * STAGE_BYTES +
+                                                  (NPAIR == 4 ? rt & 1 : rt) * 16 * 64);
     };
     auto read_b = [&](auto st_c, uint32_t *w) __attribute__((always_inline)) {
         constexpr int ST = decltype(st_c)::value;
@@ -306,6 +318,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
             for (int i = 0; i < 3; ++i) w[i] = *reinterpret_cast<const uint32_t *>(st + 8 * i);
         }
     };
+    float rsum[2] = {0.f, 0.f};                            // row sums of row tiles 0 and 1 of the registers, this lane's part
     const uint32_t perm_sel = par ? 0x07060302u : 0x05040100u;
 
     // ---- prologue: queue NSTAGE - 1 stages (and the packed weights of one more), wait for the first two, fetch the operands
@@ -404,6 +417,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
                     bfrag[NXT][I][J] = next_frag_reg(up, std::integral_constant<int, I>{}, std::integral_constant<int, J>{});
                     if constexpr (J_MAJOR && I == 3 && J < 2) read_table_pair(m0 + it + 1, J + 2);
                 }
+                if constexpr (ROW_SUMS && rt < 2) rsum[rt] = add_pair(afrag[rt][ct], rsum[rt]);
                 if constexpr (m == 2) read_b(std::integral_constant<int, NNS>{}, bw[NXT]);
                 if constexpr (m == 5) dma16(a_voff, a_ptr, dst_a + PS * STAGE_BYTES);
                 if constexpr (m == 13) dma16(a_voff_2, a_ptr, dst_a + PS * STAGE_BYTES + A_DST_2);
@@ -461,16 +475,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
     auto own_col = [&](int e) __attribute__((always_inline)) {
         return Unpacker::BY_PARITY ? col0 + 4 * (c & ~1) + 2 * e + par : colc + e;
     };
-    // correction term of token row t (clamped by the caller): the row sum of X (MODE_Y) or crow (MODE_DX)
-    auto row_term = [&](int t) __attribute__((always_inline)) -> float {
-        if constexpr (MODE == MODE_Y) {
-            const u32x2 r2 = *reinterpret_cast<const u32x2 *>(a.rs + 2 * t);
-            return __uint_as_float(r2[0]) + __uint_as_float(r2[1]);
-        } else {
-            return a.crow[t];
-        }
-    };
-    auto row_of = [&](int rt, int j) __attribute__((always_inline)) { return t0 + rt * 16 + 4 * q + j; };
+    // rows 4 q + j of the registers' row tile rt
+    auto local_row = [&](int rt) __attribute__((always_inline)) { return (ROW_SUMS ? rt ^ (2 * wn) : rt) * 16 + 4 * q; };
+    auto row_of = [&](int rt, int j) __attribute__((always_inline)) { return t0 + local_row(rt) + j; };
     auto clamped = [&](int t) __attribute__((always_inline)) { return t < T ? t : T - 1; };
     // Epilogue parameters are fetched while the last DMAs drain: scale and zero-point of this lane's four columns
     f32x4 ep_sc = {0.f, 0.f, 0.f, 0.f}, ep_zoff = {0.f, 0.f, 0.f, 0.f};
@@ -503,6 +510,17 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
     wait_vmcnt<0>();
     __syncthreads();
     mfma_result_fence();
+    // Row sums: the four lanes of a row meet (fixed order), the waves' rows meet in LDS.
+    float *rs_lds = reinterpret_cast<float *>(lds);        // [128]
+    if constexpr (ROW_SUMS) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            rsum[i] += __shfl_xor(rsum[i], 16);
+            rsum[i] += __shfl_xor(rsum[i], 32);
+            if (q == 0) rs_lds[32 * wn + 16 * i + c] = rsum[i];
+        }
+        __syncthreads();
+    }
 
     // ---- epilogues
     if constexpr (MODE == MODE_DDS) {
@@ -516,23 +534,25 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
             typedef uint32_t dy_vec __attribute__((ext_vector_type(DW)));
             const uint16_t *dy0 = a.dY + col0 + (Unpacker::BY_PARITY ? 4 * (c & ~1) : 4 * c);
             const int up16 = 16 - 16 * par;
+            f32x4 pairsum = {0.f, 0.f, 0.f, 0.f}, first = {0.f, 0.f, 0.f, 0.f};
             dy_vec dyv[2][4];
             float rsv[2][4];
-            const float rs_on = piece == 0 ? 1.f : 0.f;    // the row-sum term belongs to the whole contraction: once
             auto load_rows = [&](auto rt_c, dy_vec *dst, float *rdst) __attribute__((always_inline)) {
                 constexpr int rt = decltype(rt_c)::value;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const int tc = clamped(row_of(rt, j));
                     dst[j] = *reinterpret_cast<const dy_vec *>(dy0 + (size_t)tc * a.C);
-                    // row sum of X over this contraction half, or over this half's scale group
-                    if constexpr (PAIRED) {
+                    // row sum of X over what this wave contracted
+                    if constexpr (ROW_SUMS) {
+                        rdst[j] = rs_lds[local_row(rt) + j];
+                    } else if constexpr (PAIRED) {
                         rdst[j] = a.rs[(size_t)tc * a.G + (half_on ? grp : a.G - 1)];
                     } else if constexpr (KW == 2) {
                         rdst[j] = a.rs[2 * tc + wk];
                     } else {
-                        const u32x2 r2 = *reinterpret_cast<const u32x2 *>(a.rs + 2 * tc);
-                        rdst[j] = __uint_as_float(r2[0]) + __uint_as_float(r2[1]);
+                        const f32x2 r2 = *reinterpret_cast<const f32x2 *>(a.rs + 2 * tc);
+                        rdst[j] = r2[0] + r2[1];
                     }
                 }
             };
@@ -542,10 +562,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
                 if constexpr (rt + 1 < 8) load_rows(std::integral_constant<int, rt + 1>{}, dyv[(rt + 1) & 1], rsv[(rt + 1) & 1]);
                 float dm[4];                                   // rows past T contribute nothing
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    dm[j] = row_of(rt, j) < T ? 1.f : 0.f;
-                    rsv[rt & 1][j] *= rs_on;
-                }
+                for (int j = 0; j < 4; ++j) dm[j] = row_of(rt, j) < T ? 1.f : 0.f;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const f32x4 v = read_acc(acc[rt][e]);      // one accumulator tile at a time leaves its AGPRs
@@ -554,9 +571,20 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
                         float d;
                         if constexpr (Unpacker::BY_PARITY) d = __uint_as_float((dyv[rt & 1][j][e] << up16) & 0xFFFF0000u);
                         else d = (e & 1) ? bf16_hi(dyv[rt & 1][j][e >> 1]) : bf16_lo(dyv[rt & 1][j][e >> 1]);
-                        colsum[e] += d * dm[j] * (v[j] - ep_zoff[e] * rsv[rt & 1][j]);
+                        pairsum[e] += d * dm[j] * (v[j] - ep_zoff[e] * rsv[rt & 1][j]);
                     }
                 }
+                // (r0 + r1) + (r2 + r3) over the pairs of row tiles: the same bits in whatever order a wave has them
+                // (pair p of the registers is pair p ^ wn of the tile), so that a column's sum does not depend on its wave
+                if constexpr (rt == 1 || rt == 5) {
+                    first = pairsum;
+                    pairsum = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+                if constexpr (rt == 3) {
+                    colsum = first + pairsum;
+                    pairsum = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+                if constexpr (rt == 7) colsum += first + pairsum;
             });
         }
 #pragma unroll
@@ -619,7 +647,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
         auto load_terms = [&](int rt, float *r) __attribute__((always_inline)) {
             if constexpr (!SCALED) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) r[j] = row_term(clamped(row_of(rt, j)));
+                for (int j = 0; j < 4; ++j) {
+                    if constexpr (MODE == MODE_Y) {
+                        const f32x2 r2 = *reinterpret_cast<const f32x2 *>(a.rs + 2 * clamped(row_of(rt, j)));
+                        r[j] = r2[0] + r2[1];
+                    } else {
+                        r[j] = a.crow[clamped(row_of(rt, j))];
+                    }
+                }
             }
         };
         float terms[2][4];                                 // of this row tile and the next
