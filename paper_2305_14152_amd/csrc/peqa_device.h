@@ -21,8 +21,11 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 // out afterwards through row sums of the other operand.
 constexpr float kCodeOffset = 16.0f;
 constexpr uint32_t kMagic = 0x41804180u;   // two bf16 16.0
-constexpr uint32_t kMask4 = 0x00780078u;   // 4-bit field at bits 3..6 of each half-word
-constexpr uint32_t kMask3 = 0x00380038u;   // 3-bit field at bits 3..5 of each half-word
+// The same trick in fp16: bits 6.. of 16.0 (0x4C00), for weights that are scaled before they enter the contraction.
+constexpr uint32_t kMagicF16 = 0x4C004C00u;
+// lowest mantissa bit of the field: 3 (bf16) or 6 (fp16); a b-bit field there in each half-word
+constexpr int kFieldBf16 = 3, kFieldF16 = 6;
+constexpr uint32_t field_mask(int bits, int at) { return ((1u << bits) - 1u) * 0x00010001u << at; }
 
 __device__ __forceinline__ float bf16_bits_to_float(uint32_t h) { return __uint_as_float(h << 16); }
 __device__ __forceinline__ float bf16_lo(uint32_t pair) { return __uint_as_float(pair << 16); }
@@ -40,16 +43,20 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
     return float_to_bf16_bits(lo) | (float_to_bf16_bits(hi) << 16);
 }
 
-// A pair of bf16 (16 + code), scaled and shifted in fp32 and rounded once (to nearest even) back to a
-// bf16 pair:  lo -> s_lo * lo + b_lo,  hi -> s_hi * hi + b_hi.  The conversion is volatile assembly so that it stays where
-// the caller put it among its matrix instructions: those are assembly too, and the wait states that the hardware wants
-// between a vector write and a matrix read of the same register are the distance the caller keeps (the compiler, free to
-// move the conversion, put it right before its use, and the matrix instruction read the old value).
+// A pair of fp16 (16 + code), scaled and shifted in fp32 and rounded once (to nearest even) to a bf16 pair:
+// lo -> s_lo * lo + b_lo,  hi -> s_hi * hi + b_hi: two mixed-precision fused multiply-adds that take a half of the register
+// as it stands (as bf16 the halves have to be moved into place first: two instructions more), and a conversion.  The
+// conversion is volatile assembly so that it stays where the caller put it among its matrix instructions: those are
+// assembly too, and the wait states that the hardware wants between a vector write and a matrix read of the same register
+// are the distance the caller keeps (the compiler, free to move the conversion, put it right before its use, and the matrix
+// instruction read the old value).
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t scale_pair(uint32_t pair, float s_lo, float b_lo, float s_hi, float b_hi)
 {
-    const float lo = __builtin_fmaf(__uint_as_float(pair << 16), s_lo, b_lo);
-    const float hi = __builtin_fmaf(__uint_as_float(pair & 0xFFFF0000u), s_hi, b_hi);
+    const f16x2 h = __builtin_bit_cast(f16x2, pair);
+    const float lo = __builtin_fmaf((float)h[0], s_lo, b_lo);
+    const float hi = __builtin_fmaf((float)h[1], s_hi, b_hi);
     uint32_t d;
     asm volatile("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(d) : "v"(lo), "v"(hi));
     return d;
@@ -86,23 +93,25 @@ __device__ __forceinline__ uint32_t shl_and_or(uint32_t x, uint32_t sh, uint32_t
     return d;
 }
 
-// Field number F (of width b) of both half-words of v -> pair of bf16 (16 + code).
-template <int BITS, int F>
+// Field number F (of width b) of both half-words of v -> pair of (16 + code): bf16, or, with AT = kFieldF16 and the matching
+// magic, fp16.
+template <int BITS, int F, int AT>
 __device__ __forceinline__ uint32_t field_pair(uint32_t v, uint32_t magic)
 {
-    constexpr uint32_t mask = BITS == 4 ? kMask4 : kMask3;
-    constexpr int sh = BITS * F - 3;
-    if constexpr (sh < 0) return shl_and_or(v, 3, mask, magic);
+    constexpr uint32_t mask = field_mask(BITS, AT);
+    constexpr int sh = BITS * F - AT;
+    if constexpr (sh < 0) return shl_and_or(v, -sh, mask, magic);
     else if constexpr (sh == 0) return and_or(v, mask, magic);
     else return shr_and_or(v, sh, mask, magic);
 }
 
 // The 3-bit cell that lives in the spare top bits (15 and 31) of three words.
+template <int AT>
 __device__ __forceinline__ uint32_t spare_pair3(uint32_t v0, uint32_t v1, uint32_t v2, uint32_t magic)
 {
-    uint32_t t = shr_and_or(v0, 12, 0x00080008u, magic);
-    t = shr_and_or(v1, 11, 0x00100010u, t);
-    return shr_and_or(v2, 10, 0x00200020u, t);
+    uint32_t t = shr_and_or(v0, 15 - AT, 0x00010001u << AT, magic);
+    t = shr_and_or(v1, 14 - AT, 0x00020002u << AT, t);
+    return shr_and_or(v2, 13 - AT, 0x00040004u << AT, t);
 }
 
 // ---------------------------------------------------------------------------------
@@ -116,7 +125,7 @@ __device__ __forceinline__ uint32_t spare_pair3(uint32_t v0, uint32_t v1, uint32
 // so that every lane runs the same shifts and masks.  Fragment I belongs to column 4 c + I of the wave's 64, or, by parity,
 // 8 (c / 2) + 2 I + c % 2.
 // ---------------------------------------------------------------------------------
-template <int BITS, bool ALONG_CH>
+template <int BITS, bool ALONG_CH, int AT = kFieldBf16>
 struct HalfBlockUnpacker {
     static constexpr int WORDS = ALONG_CH ? 2 * BITS : BITS;      // words a lane reads
     static constexpr bool BY_PARITY = ALONG_CH || BITS == 3;
@@ -137,12 +146,12 @@ struct HalfBlockUnpacker {
     __device__ __forceinline__ uint32_t frag_reg(uint32_t magic) const
     {
         if constexpr (BITS == 4) {
-            if constexpr (ALONG_CH) return field_pair<4, I>(w[J], magic);
-            else return field_pair<4, J>(w[I], magic);
+            if constexpr (ALONG_CH) return field_pair<4, I, AT>(w[J], magic);
+            else return field_pair<4, J, AT>(w[I], magic);
         } else {
             constexpr int u = ALONG_CH ? 4 * J + I : 4 * I + J;
-            if constexpr (u < 15) return field_pair<3, u % 5>(w[u / 5], magic);
-            else return spare_pair3(w[0], w[1], w[2], magic);
+            if constexpr (u < 15) return field_pair<3, u % 5, AT>(w[u / 5], magic);
+            else return spare_pair3<AT>(w[0], w[1], w[2], magic);
         }
     }
 };

@@ -7,14 +7,14 @@
 // What bounds it and why this split.  Per 32-deep step and SIMD (two waves) the matrix instructions take 1024 cycles;
 // the vector instructions of two waves take 4 cycles each beside them, and LDS delivers 128 bytes per cycle to the
 // compute unit.  With 128 x 64 per wave every weight of the tile is unpacked (and, group-wise, scaled) by one wave only:
-// 2 instructions per weight pair per channel and 7 group-wise make 256 and 900 cycles per step.  The split this
-// replaced, 64 x 128 per wave, had every weight unpacked by two waves: 512 and 1800 cycles, which made the group-wise
-// contractions vector-bound.  The price is that a wave reads the whole activation tile from LDS: 8 + 1 reads of 1 KB per
+// 2 instructions per weight pair per channel and 5 group-wise (scale_pair) make 256 and 640 cycles per step.  The split this
+// replaced, 64 x 128 per wave, had every weight unpacked by two waves: 512 and, at the 7 instructions per pair it took to
+// scale bf16 codes, 1800 cycles, which made the group-wise contractions vector-bound.  The price is that a wave reads the whole activation tile from LDS: 8 + 1 reads of 1 KB per
 // wave and step instead of 4 + 2, 576 instead of 384 cycles of the compute unit.  Measured, 64 x 128 -> 128 x 64:
 // LLaMA-13B block, 3 bits, groups of 128, T = 2048: forward launch 1537 -> 1239 us, dX 1654 -> 1445 us (with
-// that split dX scaled its activation fragments instead of the weights; here the weights are cheaper to scale);
-// 11008 x 4096, 4 bits, groups of 64, T = 500: forward 102 -> 72 us, dX 244 -> 176 us; per-channel training steps of the
-// 7B and 65B blocks 2.1 and 2.9 % shorter.
+// that split dX scaled its activation fragments instead of the weights; here the weights are cheaper to scale), and with
+// fp16 codes for the scaling 1129 and 1259 us; 11008 x 4096, 4 bits, groups of 64, T = 500: forward 102 -> 72 -> 67 us;
+// per-channel training steps of the 7B and 65B blocks 2.1 and 2.9 % shorter.
 #pragma once
 
 #include <type_traits>
@@ -59,7 +59,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
     constexpr bool PAIRED = GROUPED && MODE == MODE_DDS;   // one scale group per contraction half
     static_assert(!ROW_SUMS || (!GROUPED && MODE == MODE_DDS && KW == 1), "row sums per piece: scale gradient, four waves");
     static_assert(KW == 2 || (KW == 1 && !PAIRED), "the paired scale gradient needs both contraction halves");
-    typedef HalfBlockUnpacker<BITS, ALONG_CH> Unpacker;
+    typedef HalfBlockUnpacker<BITS, ALONG_CH, SCALED ? kFieldF16 : kFieldBf16> Unpacker;
     constexpr int WORDS = Unpacker::WORDS;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -115,7 +115,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
         kh1 = KW == 2 ? kh0 + (u1 - u0) * 64 : kh0;
     }
     const int kbeg = wk ? kh1 : kh0;
-    const uint32_t magic = kMagic;
+    const uint32_t magic = SCALED ? kMagicF16 : kMagic;
     const uint32_t lds_base = (uint32_t)(uintptr_t)lds;
 
     // ---- activation tiles: global -> LDS by DMA, wave-loads of 1 KB (16 rows; 2 per wave and step).  Lane s of a
