@@ -18,7 +18,7 @@ namespace {
 constexpr int PEQA_GEMV_MAX_T = GEMV_MAX_T;
 
 struct Workspace {
-    size_t rs, dys, crow, partial, table, rsz, zpartial, xt, dyt, pc, total;
+    size_t rs, dys, crow, partial, table, zpartial, xt, dyt, pc, total;
     // Pieces of the contractions (1 = whole) and the regions of their partial results.  `total` includes these regions; a
     // workspace of at least `min_total` but less than `total` bytes is served too, with whole contractions.
     size_t min_total;
@@ -31,11 +31,10 @@ Workspace carve_whole(const peqa_layout *L, int32_t T, int32_t op)
 {
     if (op == PEQA_OP_FWD_Z && T > PEQA_GEMV_MAX_T) return carve_whole(L, T, PEQA_OP_FWD);
     if (op == PEQA_OP_BWD_Z) {
-        // the plain backward's needs, then the group sums of X and the partials of the zero-point gradient
+        // the plain backward's needs (sums of X among them), then the partials of the zero-point gradient
         Workspace w = carve_whole(L, T, PEQA_OP_BWD);
         const size_t slices = ((size_t)T + peqa::KEPT_ROWS - 1) / peqa::KEPT_ROWS;
         const size_t NG = (size_t)L->n_out * (size_t)groups(L);
-        w.rsz = w.total;      w.total += round256((size_t)T * groups(L) * sizeof(float));
         w.zpartial = w.total; w.total += round256(slices * NG * sizeof(float));
         return w;
     }
@@ -582,7 +581,7 @@ static peqa_status bwd_impl(const peqa_layout *L, const uint32_t *packed, const 
         if (d_dz) {
             float *zp = reinterpret_cast<float *>(ws + w.zpartial);
             if (peqa::launch_dz_partial(dY, rsb, T, N, G, zp, s) != hipSuccess) return PEQA_ERR_DEVICE;
-            if (peqa::launch_dz_finish(zp, slices, (size_t)N * G, s0, ds, d_dz, s) != hipSuccess) return PEQA_ERR_DEVICE;
+            if (peqa::launch_dz_finish(zp, slices, (size_t)N * G, s0, ds, d_dz, nullptr, 0, 0, nullptr, s) != hipSuccess) return PEQA_ERR_DEVICE;
         }
         const int Tp = (T + 63) / 64 * 64;
         uint16_t *xt = reinterpret_cast<uint16_t *>(ws + w.xt), *dyt = reinterpret_cast<uint16_t *>(ws + w.dyt);
@@ -652,15 +651,17 @@ static peqa_status bwd_impl(const peqa_layout *L, const uint32_t *packed, const 
     if (!pair) w.split_dds = 1;
     float *partial = reinterpret_cast<float *>(ws + (w.split_dds > 1 ? w.acc_dds : w.partial));
     const int partial_rows = tiles_t * w.split_dds;
+    if (d_ds && partial_rows == 1) partial = d_ds;             // one row of partials is the gradient
+    // row sums of X over the two contraction halves: the caller's (peqa_row_sums), or taken here, with the scaling of
+    // dY where that comes before the contractions.  (Pieces take their own; the zero-point gradient reads them too.)
+    const float *rs = row_sums;
+    float *rs_own = nullptr;
+    if (!rs && (d_dz || (d_ds && w.split_dds == 1))) {
+        rs = rs_own = reinterpret_cast<float *>(ws + w.rs);
+        if (!pair && peqa::launch_rowsum(X, T, K, split_point(K), rs_own, s) != hipSuccess) return PEQA_ERR_DEVICE;
+    }
     float *acc = reinterpret_cast<float *>(ws + w.acc);
     if (d_ds) {
-        // row sums of X over the two contraction halves: the caller's (peqa_row_sums), or taken here (pieces take their own)
-        const float *rs = row_sums;
-        if (!rs && w.split_dds == 1) {
-            float *own = reinterpret_cast<float *>(ws + w.rs);
-            if (peqa::launch_rowsum(X, T, K, split_point(K), own, s) != hipSuccess) return PEQA_ERR_DEVICE;
-            rs = own;
-        }
         peqa::GemmArgs &a = a_dds;
         a.packed = packed; a.A = X; a.T = T; a.KC = K; a.C = N; a.K = K;
         a.tiles_c = (N + 255) / 256; a.tiles_t = tiles_t;
@@ -676,7 +677,7 @@ static peqa_status bwd_impl(const peqa_layout *L, const uint32_t *packed, const 
     uint16_t *dys = reinterpret_cast<uint16_t *>(ws + w.dys);
     float *crow = reinterpret_cast<float *>(ws + w.crow);
     if (pair) {
-        if (peqa::launch_scale_dy(dY, s0, ds, z0, dz, T, N, dys, crow, nullptr, 0, 0, nullptr, s) != hipSuccess)
+        if (peqa::launch_scale_dy(dY, s0, ds, z0, dz, T, N, dys, crow, nullptr, 0, 0, nullptr, X, K, rs_own, s) != hipSuccess)
             return PEQA_ERR_DEVICE;
         a_dx.split = w.split_dx;
         a_dx.acc_part = acc;
@@ -688,30 +689,31 @@ static peqa_status bwd_impl(const peqa_layout *L, const uint32_t *packed, const 
             f.n = 1;
             if (peqa::launch_split_finish(f, s) != hipSuccess) return PEQA_ERR_DEVICE;
         }
-        if (peqa::launch_reduce_partials(partial, partial_rows, (size_t)N, d_ds, s) != hipSuccess) return PEQA_ERR_DEVICE;
+        if (!d_dz && partial_rows > 1 && peqa::launch_reduce_partials(partial, partial_rows, (size_t)N, d_ds, s) != hipSuccess)
+            return PEQA_ERR_DEVICE;
     } else {
         // one after the other; when dX follows the scale gradient, the sum of its partials rides in the launch
         // that scales dY
         if (d_ds) {
             if (peqa::launch_gemm(L->bits, peqa::MODE_DDS, a_dds, s) != hipSuccess) return PEQA_ERR_DEVICE;
-            if (!dX && peqa::launch_reduce_partials(partial, partial_rows, (size_t)N, d_ds, s) != hipSuccess)
+            if (!dX && partial_rows > 1 && peqa::launch_reduce_partials(partial, partial_rows, (size_t)N, d_ds, s) != hipSuccess)
                 return PEQA_ERR_DEVICE;
         }
         if (dX) {
-            if (peqa::launch_scale_dy(dY, s0, ds, z0, dz, T, N, dys, crow, partial, partial_rows, d_ds ? (size_t)N : 0, d_ds,
-                                      s) != hipSuccess)
+            if (peqa::launch_scale_dy(dY, s0, ds, z0, dz, T, N, dys, crow, partial, partial_rows,
+                                      d_ds && partial_rows > 1 ? (size_t)N : 0, d_ds, nullptr, 0, nullptr, s) != hipSuccess)
                 return PEQA_ERR_DEVICE;
             const peqa_status st = run_contraction(L->bits, peqa::MODE_DX, a_dx, w.split_dx_alone, acc, s);
             if (st != PEQA_OK) return st;
         }
     }
     if (d_dz) {
-        // sums of every row of X (one group spanning K), then the two-stage column reduction
-        float *rsz = reinterpret_cast<float *>(ws + w.rsz);
+        // column sums by slices of token rows; their sum, and that of the paired launch's scale-gradient partials
         float *zp = reinterpret_cast<float *>(ws + w.zpartial);
-        if (peqa::launch_rowsum_groups(X, T, K, K, rsz, s) != hipSuccess) return PEQA_ERR_DEVICE;
-        if (peqa::launch_dz_partial(dY, rsz, T, N, 1, zp, s) != hipSuccess) return PEQA_ERR_DEVICE;
-        if (peqa::launch_dz_finish(zp, slices, (size_t)N, s0, ds, d_dz, s) != hipSuccess) return PEQA_ERR_DEVICE;
+        if (peqa::launch_dz_rows(dY, rs, T, N, zp, s) != hipSuccess) return PEQA_ERR_DEVICE;
+        if (peqa::launch_dz_finish(zp, slices, (size_t)N, s0, ds, d_dz, partial, partial_rows,
+                                   pair && partial_rows > 1 ? (size_t)N : 0, d_ds, s) != hipSuccess)
+            return PEQA_ERR_DEVICE;
     }
     return PEQA_OK;
 }
@@ -782,7 +784,7 @@ peqa_status peqa_linear_bwd_kept(const peqa_layout *L, const uint32_t *packed, c
         float *crow = reinterpret_cast<float *>(ws + w.crow);
         const int slices = (T + peqa::KEPT_ROWS - 1) / peqa::KEPT_ROWS;
         if (peqa::launch_scale_dy(dY, s0, ds, z0, nullptr, T, N, dys, crow, reinterpret_cast<const float *>(ws + w.partial),
-                                  slices, d_ds ? (size_t)N : 0, d_ds, s) != hipSuccess)
+                                  slices, d_ds ? (size_t)N : 0, d_ds, nullptr, 0, nullptr, s) != hipSuccess)
             return PEQA_ERR_DEVICE;
         peqa::GemmArgs a{};
         a.packed = packed; a.A = dys; a.T = T; a.KC = N; a.C = K; a.K = K;

@@ -363,6 +363,8 @@ peqa_status peqa_block_bwd(int32_t n, const peqa_block_item *items, int32_t T, v
         uint16_t *dys = reinterpret_cast<uint16_t *>(ws + w.dys[j]);
         float *crow = reinterpret_cast<float *>(ws + w.crow[j]);
         float *partial = reinterpret_cast<float *>(ws + (w.split_dds[j] > 1 ? w.acc_dds[j] : w.partial[j]));
+        const int partial_rows = tiles_t * w.split_dds[j];
+        if (it.d_ds && partial_rows == 1) partial = it.d_ds;   // one row of partials is the gradient
         if (it.d_ds) {
             peqa::MultiJob &job = ma.job[ma.n_jobs++];
             job.mode = peqa::MODE_DDS;
@@ -371,10 +373,12 @@ peqa_status peqa_block_bwd(int32_t n, const peqa_block_item *items, int32_t T, v
             a.tiles_c = (N + 255) / 256; a.tiles_t = tiles_t;
             a.z0 = it.z0; a.rs = rs[xi[j]]; a.dY = it.dY; a.partial = partial;
             a.split = w.split_dds[j];
-            peqa::ReduceJob &r = mb.red[mb.n_red++];
-            r.partial = partial; r.out = it.d_ds; r.ntiles = tiles_t * w.split_dds[j]; r.n = N;
-            red_chunks += (N + 255) / 256;
-            r.chunk_end = red_chunks;
+            if (partial_rows > 1) {
+                peqa::ReduceJob &r = mb.red[mb.n_red++];
+                r.partial = partial; r.out = it.d_ds; r.ntiles = partial_rows; r.n = N;
+                red_chunks += (N + 255) / 256;
+                r.chunk_end = red_chunks;
+            }
         }
         if (it.dX) {
             peqa::ScaleDyJob &sd = ma.sdy[ma.n_sdy++];

@@ -225,11 +225,9 @@ __device__ __forceinline__ void scale_dy_rows(const uint16_t *__restrict__ dY, c
     if (tid < rows) crow[t0 + tid] = (red[tid * 4] + red[tid * 4 + 1]) + (red[tid * 4 + 2] + red[tid * 4 + 3]);
 }
 
-// out[j] = partial[0][j] + partial[1][j] + ... in that order (deterministic).
-__device__ __forceinline__ void reduce_partials_at(const float *__restrict__ partial, int ntiles, size_t n, size_t j,
-                                                   float *__restrict__ out)
+// partial[0][j] + partial[1][j] + ... in that order (deterministic).
+__device__ __forceinline__ float partials_sum(const float *__restrict__ partial, int ntiles, size_t n, size_t j)
 {
-    if (j >= n) return;
     // eight loads in flight, added in tile order
     float s = 0.f;
     int tt = 0;
@@ -241,7 +239,14 @@ __device__ __forceinline__ void reduce_partials_at(const float *__restrict__ par
         for (int u = 0; u < 8; ++u) s += p[u];
     }
     for (; tt < ntiles; ++tt) s += partial[(size_t)tt * n + j];
-    out[j] = s;
+    return s;
+}
+
+// out[j] = that sum
+__device__ __forceinline__ void reduce_partials_at(const float *__restrict__ partial, int ntiles, size_t n, size_t j,
+                                                   float *__restrict__ out)
+{
+    if (j < n) out[j] = partials_sum(partial, ntiles, n, j);
 }
 
 // One 64 x 64 tile of the step-major transposed copy that the token contraction of group-wise layers reads:

@@ -221,10 +221,11 @@ struct RowsumMulti {
 };
 hipError_t launch_rowsum_multi(const RowsumMulti &a, hipStream_t stream);
 // dYs = bf16(dY (s0 + ds)) and crow; with n_red > 0 the same launch also sums `ntiles` partial vectors of n_red
-// floats into red_out (launch_reduce_partials' job), an independent piece of work of the same backward
+// floats into red_out (launch_reduce_partials' job), with rs != NULL it takes the row sums of X [T, K] into rs
+// (launch_rowsum's): independent pieces of work of the same backward
 hipError_t launch_scale_dy(const uint16_t *dY, const float *s0, const float *ds, const uint8_t *z0, const float *dz,
                            int T, int N, uint16_t *dYs, float *crow, const float *partial, int ntiles, size_t n_red,
-                           float *red_out, hipStream_t stream);
+                           float *red_out, const uint16_t *X, int K, float *rs, hipStream_t stream);
 hipError_t launch_rowsum_groups(const uint16_t *X, int T, int K, int gsz, float *rsg, hipStream_t stream);
 // sb [G, N, 2] = (s, -s (16 + z))
 hipError_t launch_group_table(const float *s0, const float *ds, const uint8_t *z0, const float *dz, int N, int G,
@@ -233,8 +234,11 @@ hipError_t launch_group_table(const float *s0, const float *ds, const uint8_t *z
 // d_dz[j] = -(s0 + ds)[j] * (sum of the partials)
 hipError_t launch_dz_partial(const uint16_t *dY, const float *rsg, int T, int N, int G, float *partial,
                              hipStream_t stream);
+// the same partials of a per-channel layer from the row sums rs [T, 2] (launch_rowsum's)
+hipError_t launch_dz_rows(const uint16_t *dY, const float *rs, int T, int N, float *partial, hipStream_t stream);
+// with n_red > 0 also launch_reduce_partials' job over red [red_rows, n_red]
 hipError_t launch_dz_finish(const float *partial, int slices, size_t n, const float *s0, const float *ds, float *d_dz,
-                            hipStream_t stream);
+                            const float *red, int red_rows, size_t n_red, float *red_out, hipStream_t stream);
 constexpr int KEPT_ROWS = 64;   // token rows per partial of launch_dds_kept
 hipError_t launch_dds_kept(const uint16_t *dY, const float *P, int T, int N, float *partial, hipStream_t stream);
 hipError_t launch_reduce_partials(const float *partial, int ntiles, size_t n, float *out, hipStream_t stream);

@@ -16,9 +16,9 @@ __device__ __forceinline__ float wave_sum(float v)
 
 // rs[t, h] = sum of X[t, k] over contraction half h (k < ksplit, k >= ksplit), fp32.
 // One wave per token row; 16-byte loads.
-__device__ __forceinline__ void rowsum_rows(const uint16_t *__restrict__ X, int T, int K, int ksplit, float *__restrict__ rs)
+__device__ __forceinline__ void rowsum_rows(const uint16_t *__restrict__ X, int T, int K, int ksplit, float *__restrict__ rs, int blk)
 {
-    const int lane = threadIdx.x & 63, t = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, t = blk * 4 + (threadIdx.x >> 6);
     if (t >= T) return;
     const u32x4 *row = reinterpret_cast<const u32x4 *>(X + (size_t)t * K);
     float s[2] = {0.f, 0.f};
@@ -47,7 +47,7 @@ __device__ __forceinline__ void rowsum_rows(const uint16_t *__restrict__ X, int 
 __global__ __launch_bounds__(256) void rowsum_kernel(const uint16_t *__restrict__ X, int T, int K, int ksplit,
                                                       float *__restrict__ rs)
 {
-    rowsum_rows(X, T, K, ksplit, rs);
+    rowsum_rows(X, T, K, ksplit, rs, (int)blockIdx.x);
 }
 
 // rowsum_kernel's work for several inputs of T rows each: blockIdx.y selects the input.
@@ -60,7 +60,7 @@ __global__ __launch_bounds__(256) void rowsum_multi_kernel(RowsumMulti a)
 #pragma unroll
     for (int i = 1; i < ROWSUM_MAX; ++i)
         if (y == i) { X = a.X[i]; rs = a.rs[i]; K = a.K[i]; }
-    rowsum_rows(X, a.T, K, K / 2, rs);
+    rowsum_rows(X, a.T, K, K / 2, rs, (int)blockIdx.x);
 }
 
 // rsg[t, g] = sum of X[t, k] over scale group g (gsz features, a multiple of 64), fp32.
@@ -188,20 +188,24 @@ __global__ __launch_bounds__(256) void group_table_multi_entry_kernel(GroupTable
     group_table_entry(s0, ds, z0, nullptr, N, G, sb, j);
 }
 
-// scale_dy_rows (peqa_device.h) for every block of SDY_ROWS token rows.  Workgroups past the last row block do an
-// independent job in the same launch: the fixed-order sum of the scale-gradient partials (n_red = 0: none),
-// which the backward needs between its two contractions too.
+// scale_dy_rows (peqa_device.h) for every block of SDY_ROWS token rows.  Workgroups past the last row block do
+// independent jobs of the same backward: the row sums of X for the scale gradient that follows (rs = NULL: none), or the
+// fixed-order sum of the scale-gradient partials (n_red = 0: none).  A launch saved is 3 us of host time and 1 to 3 us
+// of the GPU's: a 256 x 256 layer's step at T = 512, all of it launches, went from 36.2 to 31.6 us with the row sums here.
 __global__ __launch_bounds__(256) void scale_dy_kernel(const uint16_t *__restrict__ dY, const float *__restrict__ s0,
                                                         const float *__restrict__ ds, const uint8_t *__restrict__ z0,
                                                         const float *__restrict__ dz, int T, int N,
                                                         uint16_t *__restrict__ dYs, float *__restrict__ crow,
                                                         const float *__restrict__ partial, int ntiles, size_t n_red,
-                                                        float *__restrict__ red_out)
+                                                        float *__restrict__ red_out, const uint16_t *__restrict__ X, int K,
+                                                        float *__restrict__ rs)
 {
     __shared__ float red[SDY_ROWS * 4];
     const int row_blocks = (T + SDY_ROWS - 1) / SDY_ROWS;
     if ((int)blockIdx.x >= row_blocks) {
-        reduce_partials_at(partial, ntiles, n_red, (size_t)((int)blockIdx.x - row_blocks) * 256 + threadIdx.x, red_out);
+        const int past = (int)blockIdx.x - row_blocks, sum_blocks = rs ? (T + 3) / 4 : 0;
+        if (past < sum_blocks) rowsum_rows(X, T, K, K / 2, rs, past);
+        else reduce_partials_at(partial, ntiles, n_red, (size_t)(past - sum_blocks) * 256 + threadIdx.x, red_out);
         return;
     }
     scale_dy_rows(dY, s0, ds, z0, dz, T, N, dYs, crow, (int)blockIdx.x, red);
@@ -230,6 +234,40 @@ __global__ __launch_bounds__(256) void dds_kept_kernel(const uint16_t *__restric
             acc[1] += bf16_hi(d[0]) * p[1];
             acc[2] += bf16_lo(d[1]) * p[2];
             acc[3] += bf16_hi(d[1]) * p[3];
+        }
+    }
+    part[w][q] = acc;
+    __syncthreads();
+    if (w == 0 && col < N) {
+        const f32x4 s = ((part[0][q] + part[1][q]) + part[2][q]) + part[3][q];
+        *reinterpret_cast<f32x4 *>(partial + (size_t)blockIdx.x * N + col) = s;
+    }
+}
+
+// Zero-point gradient of a per-channel layer, first stage: partial[slice, i] = sum over the slice's KEPT_ROWS token rows
+// of dY[t,i] * (rs[t,0] + rs[t,1]).  Bound by the one pass over dY: a wave loads its 16 rows eight at a time, the row sums
+// come by scalar loads.  (dz_partial_kernel, made for many groups, spent seven eighths of its sums on groups that are not
+// there and 10 us on dY of 2048 x 4096.)
+__global__ __launch_bounds__(256) void dz_rows_kernel(const uint16_t *__restrict__ dY, const float *__restrict__ rs, int T,
+                                                       int N, float *__restrict__ partial)
+{
+    __shared__ f32x4 part[4][64];
+    const int q = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int col = blockIdx.y * 256 + 4 * q;
+    const int tbeg = blockIdx.x * KEPT_ROWS;
+    const int nrows = min(KEPT_ROWS, T - tbeg);
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    if (col < N) {
+        const uint16_t *base = dY + (size_t)tbeg * N + col;
+#pragma unroll 8
+        for (int r = w; r < nrows; r += 4) {
+            const u32x2 d = *reinterpret_cast<const u32x2 *>(base + (size_t)r * N);
+            const float R = rs[2 * (tbeg + r)] + rs[2 * (tbeg + r) + 1];
+            acc[0] += bf16_lo(d[0]) * R;
+            acc[1] += bf16_hi(d[0]) * R;
+            acc[2] += bf16_lo(d[1]) * R;
+            acc[3] += bf16_hi(d[1]) * R;
         }
     }
     part[w][q] = acc;
@@ -293,17 +331,21 @@ __global__ __launch_bounds__(256) void dz_partial_kernel(const uint16_t *__restr
     }
 }
 
-// d_dz[j] = -(s0 + ds)[j] * (partial[0][j] + partial[1][j] + ...) in that order.
+// d_dz[j] = -(s0 + ds)[j] * (partial[0][j] + partial[1][j] + ...) in that order.  Workgroups past those carry the
+// independent sum of the same backward's scale-gradient partials (n_red = 0: none).
 __global__ __launch_bounds__(256) void dz_finish_kernel(const float *__restrict__ partial, int slices, size_t n,
                                                          const float *__restrict__ s0, const float *__restrict__ ds,
-                                                         float *__restrict__ d_dz)
+                                                         float *__restrict__ d_dz, const float *__restrict__ red,
+                                                         int red_rows, size_t n_red, float *__restrict__ red_out)
 {
-    const size_t j = (size_t)blockIdx.x * 256 + threadIdx.x;
+    const size_t j = (size_t)blockIdx.x * 256 + threadIdx.x, dz_end = (n + 255) / 256 * 256;
+    if (j >= dz_end) {
+        reduce_partials_at(red, red_rows, n_red, j - dz_end, red_out);
+        return;
+    }
     if (j >= n) return;
-    float s = 0.f;
-    for (int tt = 0; tt < slices; ++tt) s += partial[(size_t)tt * n + j];
     const float sc = ds ? s0[j] + ds[j] : s0[j];
-    d_dz[j] = -sc * s;
+    d_dz[j] = -sc * partials_sum(partial, slices, n, j);
 }
 
 __global__ __launch_bounds__(256) void reduce_partials_kernel(const float *__restrict__ partial, int ntiles, size_t n,
@@ -430,12 +472,12 @@ hipError_t launch_group_table_multi(const GroupTableMulti &a, hipStream_t stream
 
 hipError_t launch_scale_dy(const uint16_t *dY, const float *s0, const float *ds, const uint8_t *z0, const float *dz,
                            int T, int N, uint16_t *dYs, float *crow, const float *partial, int ntiles, size_t n_red,
-                           float *red_out, hipStream_t stream)
+                           float *red_out, const uint16_t *X, int K, float *rs, hipStream_t stream)
 {
     trace_before(KID_SCALE_DY, stream);
-    const unsigned blocks = (unsigned)((T + SDY_ROWS - 1) / SDY_ROWS) + (unsigned)((n_red + 255) / 256);
+    const unsigned blocks = (unsigned)((T + SDY_ROWS - 1) / SDY_ROWS) + (rs ? (unsigned)((T + 3) / 4) : 0u) + (unsigned)((n_red + 255) / 256);
     hipLaunchKernelGGL(scale_dy_kernel, dim3(blocks), dim3(256), 0, stream, dY, s0, ds, z0, dz, T, N, dYs, crow, partial,
-                       ntiles, n_red, red_out);
+                       ntiles, n_red, red_out, X, K, rs);
     trace_after(KID_SCALE_DY, stream);
     return hipGetLastError();
 }
@@ -459,12 +501,21 @@ hipError_t launch_dz_partial(const uint16_t *dY, const float *rsg, int T, int N,
     return hipGetLastError();
 }
 
+hipError_t launch_dz_rows(const uint16_t *dY, const float *rs, int T, int N, float *partial, hipStream_t stream)
+{
+    trace_before(KID_DZ_PARTIAL, stream);
+    hipLaunchKernelGGL(dz_rows_kernel, dim3((T + KEPT_ROWS - 1) / KEPT_ROWS, (N + 255) / 256), dim3(256), 0, stream, dY,
+                       rs, T, N, partial);
+    trace_after(KID_DZ_PARTIAL, stream);
+    return hipGetLastError();
+}
+
 hipError_t launch_dz_finish(const float *partial, int slices, size_t n, const float *s0, const float *ds, float *d_dz,
-                            hipStream_t stream)
+                            const float *red, int red_rows, size_t n_red, float *red_out, hipStream_t stream)
 {
     trace_before(KID_DZ_FINISH, stream);
-    hipLaunchKernelGGL(dz_finish_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, partial, slices, n,
-                       s0, ds, d_dz);
+    hipLaunchKernelGGL(dz_finish_kernel, dim3((unsigned)((n + 255) / 256 + (n_red + 255) / 256)), dim3(256), 0, stream,
+                       partial, slices, n, s0, ds, d_dz, red, red_rows, n_red, red_out);
     trace_after(KID_DZ_FINISH, stream);
     return hipGetLastError();
 }

@@ -178,3 +178,27 @@ def test_small_batch_forms(gpu, oracle, bits, N, K, group):
         assert np.abs(Yw - gpu.bf16_dev_to_f64(Y)).max() <= 2.0 ** -7 * np.abs(Yw).max()
         Yz = oracle.fwd_z(codes, s0, ds, z0, dz, X, group)
         assert np.abs(gpu.bf16_dev_to_f64(layer.fwd_z(X, ds, dz)) - Yz).max() <= Y_TOL * np.abs(Yz).max()
+
+
+@pytest.mark.parametrize("bits,N,K,T", [(4, 128, 512, 33), (4, 384, 512, 65), (3, 256, 640, 300), (3, 128, 8192, 40)])
+def test_zero_point_gradient_beside_the_others(gpu, oracle, bits, N, K, T):
+    """One slice of token rows, two, a ragged last one, a split scale gradient: d_ds and d_dz, whose sums share a launch,
+    against the oracle, and the same bits whatever else is wanted."""
+    seed = 73000 + bits * 1000 + N + K + T
+    W = synth.normal_f32(seed, (N, K), 0.02)
+    layer = gpu.GpuLayer(W, bits, 0)
+    codes, s0, z0 = oracle.quantize(W, bits, 0)
+    ds, dz = synth.normal_f32(seed + 1, (N, 1), 1e-3), synth.normal_f32(seed + 2, (N, 1), 0.5)
+    X, dY = synth.normal_bf16(seed + 3, (T, K), 1.0), synth.normal_bf16(seed + 4, (T, N), 1.0)
+    _, gref, zref = oracle.bwd_z(codes, s0, ds, z0, dz, X, dY, 0)
+    _, g, z = layer.bwd_z(X, dY, ds, dz)
+    gpu.assert_scale_grad_close(gpu.to_host(g), gref)
+    gpu.assert_scale_grad_close(gpu.to_host(z), zref, "d_dz")
+    for want_dX, want_dds in ((True, False), (False, True), (False, False)):
+        _, g1, z1 = layer.bwd_z(X, dY, ds, dz, want_dX=want_dX, want_dds=want_dds)
+        assert (gpu.to_host(z1) == gpu.to_host(z)).all()
+        if want_dds:
+            gpu.assert_scale_grad_close(gpu.to_host(g1), gref)
+    _, g2 = layer.bwd(X, dY, ds)
+    _, g3, _ = layer.bwd_z(X, dY, ds, None)
+    assert (gpu.to_host(g2) == gpu.to_host(g3)).all()
