@@ -8,13 +8,7 @@
 //
 // Every fp32 step below is a single IEEE operation (correctly rounded divide, no fused
 // multiply-add), because the codes must match the definition bit for bit.  The one divide per
-// weight, w / s, is the exception in form only: it is taken as (float)((double)w * rs) with
-// rs = 1.0 / (double)s formed once per scale by a correctly rounded fp64 divide.  That product is
-// within 2^-52 (relative) of the true quotient, while the quotient of two fp32 numbers is never
-// closer than 2^-49 (relative) to a point midway between two fp32 numbers (w - m s is a non-zero
-// multiple of the last bit of a 49-bit product), so rounding it to fp32 gives the correctly
-// rounded fp32 quotient: the same bits, at a third of the instructions (the correctly rounded fp32
-// divide sequence made this kernel ALU-bound at 2.2 TB/s).
+// weight, w / s, is the exception in form only; see codes_of().
 #include "peqa_device.h"
 #include "peqa_kernels.h"
 
@@ -29,6 +23,68 @@ namespace peqa {
 namespace {
 
 constexpr int CHUNK = 256;    // features per pass-2 step = 32 blocks
+
+// The value of a lane BY above in the same 16 lanes (rotated).  A sum or maximum over rotations by 8, 4, 2, 1 adds, step
+// by step, the pairs that lane exchanges (xor 8, 4, 2, 1) would: after a step its values repeat with that period.
+template <int BY>
+__device__ __forceinline__ float rotated16(float x)
+{
+    return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), 0x120 + BY, 0xF, 0xF, false));
+}
+template <int BY>
+__device__ __forceinline__ double rotated16(double x)
+{
+    const u32x2 w = __builtin_bit_cast(u32x2, x);
+    return __builtin_bit_cast(double, u32x2{(uint32_t)__builtin_amdgcn_update_dpp(0u, w[0], 0x120 + BY, 0xF, 0xF, false),
+                                            (uint32_t)__builtin_amdgcn_update_dpp(0u, w[1], 0x120 + BY, 0xF, 0xF, false)});
+}
+
+__device__ __forceinline__ float max16(float x)
+{
+    x = __builtin_fmaxf(x, rotated16<8>(x));
+    x = __builtin_fmaxf(x, rotated16<4>(x));
+    x = __builtin_fmaxf(x, rotated16<2>(x));
+    return __builtin_fmaxf(x, rotated16<1>(x));
+}
+
+// The factor that codes_of() rounds w by: fp32 1 / s, or NaN where that is not accurate to fp32 (s very small or very large).
+__device__ __forceinline__ float code_factor(float s)
+{
+    return s >= 0x1p-120f && s <= 0x1p120f ? __fdiv_rn(1.f, s) : __uint_as_float(0x7FC00000u);
+}
+
+// c[e] = clamp(rint(w[e] / s) + z, 0, qmax) with the correctly rounded fp32 quotient, r = code_factor(s).
+// The code of q = w * r is taken where q is more than 2e-5 away from a midpoint between integers: q is within
+// |w / s| 2^-23 of the quotient and that within |w / s| 2^-24 of its rounding, together less than 2e-5 up to
+// |w / s| = 111, beyond which both clamp alike.  Elsewhere (4 weights of 100000, a NaN factor or weight), the
+// quotient is (float)((double)w * (1 / s)): that product is within 2^-52 (relative) of the true quotient, while
+// the quotient of two fp32 numbers is never closer than 2^-49 (relative) to a point midway between two fp32
+// numbers (w - m s is a non-zero multiple of the last bit of a 49-bit product), so rounding it to fp32 gives the
+// correctly rounded quotient.  (That form for every weight, three conversions and products at the fp64 rate, and the
+// repacking of codes byte by byte took 59 us for 11008 x 4096, this 41: the time of reading W0 and writing the words;
+// with a search over 8 ranges 439 and 320 us.)
+template <int BITS, int NE>
+__device__ __forceinline__ void codes_of(const float *w, float s, float r, int z, float *c)
+{
+    constexpr int qmax = (1 << BITS) - 1;
+    const float zf = (float)z;
+    bool far = true;
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+        const float q = w[e] * r, n = __builtin_rintf(q);
+        far = far && __builtin_fabsf(q - n) <= 0.49998f;
+        c[e] = __builtin_amdgcn_fmed3f(n + zf, 0.f, (float)qmax);
+    }
+    if (!far) {
+        const double rs = 1.0 / (double)s;
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            int q = (int)__builtin_rintf((float)((double)w[e] * rs)) + z;
+            q = q < 0 ? 0 : (q > qmax ? qmax : q);
+            c[e] = (float)q;
+        }
+    }
+}
 
 template <int BITS>
 __global__ __launch_bounds__(256) void quantize_kernel(const float *__restrict__ W0, int K, int gs, int G,
@@ -92,18 +148,15 @@ __global__ __launch_bounds__(256) void quantize_kernel(const float *__restrict__
         if (j < nb) {
             const int k = k0 + 8 * j, g = k / gs;
             const float s = s_s[r * G + g];
-            const double rs = 1.0 / (double)s;
             const int z = s_z[r * G + g];
             const f32x4 va = *reinterpret_cast<const f32x4 *>(row + k);
             const f32x4 vb = *reinterpret_cast<const f32x4 *>(row + k + 4);
             const float w[8] = {va[0], va[1], va[2], va[3], vb[0], vb[1], vb[2], vb[3]};
+            float cv[8];
             uint32_t qv[8];
+            codes_of<BITS, 8>(w, s, code_factor(s), z, cv);
 #pragma unroll
-            for (int cidx = 0; cidx < 8; ++cidx) {
-                int q = (int)rintf((float)((double)w[cidx] * rs)) + z;
-                q = q < 0 ? 0 : (q > qmax ? qmax : q);
-                qv[cidx] = (uint32_t)q;
-            }
+            for (int cidx = 0; cidx < 8; ++cidx) qv[cidx] = (uint32_t)cv[cidx];
             if constexpr (BITS == 4) {
                 uint32_t word = 0;
 #pragma unroll
@@ -145,8 +198,10 @@ __global__ __launch_bounds__(256) void quantize_kernel(const float *__restrict__
 
 // The same quantizer with the eight rows of a workgroup held in registers between the range pass and
 // the code pass, so that W0 is read from memory once: 1024 threads, 128 per channel row, thread
-// (r, l) keeps the 4-float vectors l, l + 128, ... (NV of them) of row r.  Arithmetic per element is
-// that of quantize_kernel, operation for operation.  Serves K <= 512 NV.
+// (r, l) keeps the 4-float vectors l, l + 128, ... (NV of them) of row r.  Serves K <= 512 NV.
+// Bound by the one pass over W0 as long as the vector work hides behind the other workgroup of the compute unit:
+// the 4-bit codes are packed in registers (a lane's four by fp32 multiply-adds, exact below 2^24, the two halves
+// of a word by a lane exchange) and cross LDS as whole words.
 //
 // SEARCH: the error-minimising initialisation of Sec. 3.2 over a grid of clipped ranges.  For ratio
 // r_j = 1 - j * step (j = 0 .. n_ratios - 1; r_0 = 1 is Eq. 1 as it stands) the range of every
@@ -167,14 +222,14 @@ __global__ __launch_bounds__(1024) void quantize_resident_kernel(const float *__
     uint32_t *s_neg = s_max + 8 * G;
     float *s_s = reinterpret_cast<float *>(s_neg + 8 * G);
     int *s_z = reinterpret_cast<int *>(s_s + 8 * G);
-    double *s_rs = reinterpret_cast<double *>(s_z + 8 * G);             // [8][G] 1 / s in fp64
-    uint32_t *s_codes = reinterpret_cast<uint32_t *>(s_rs + 8 * G);      // [8][K / 4] words = one byte per code
+    float *s_r = reinterpret_cast<float *>(s_z + 8 * G);                 // [8][G] code_factor(s)
+    uint32_t *s_codes = reinterpret_cast<uint32_t *>(s_r + 8 * G);       // 4 bits: [K / 8][8] packed words; 3: [8][K / 4] words = one byte per code
     // SEARCH only: the best candidate so far per (channel, group), and the error sums per 64-feature segment
     double *b_err = reinterpret_cast<double *>(s_codes + 2 * K);        // [8][G]
-    double *b_rs = b_err + 8 * G;
-    double *seg_err = b_rs + 8 * G;                                     // [8][K / 64]
+    double *seg_err = b_err + 8 * G;                                    // [8][K / 64]
     float *b_s = reinterpret_cast<float *>(seg_err + (K >> 3));
-    int *b_z = reinterpret_cast<int *>(b_s + 8 * G);
+    float *b_r = b_s + 8 * G;
+    int *b_z = reinterpret_cast<int *>(b_r + 8 * G);
 
     constexpr int qmax = (1 << BITS) - 1;
     constexpr int WPB = 2 * BITS;
@@ -182,6 +237,10 @@ __global__ __launch_bounds__(1024) void quantize_resident_kernel(const float *__
     const int ib = blockIdx.x;
     const int K4 = K >> 2;
     const f32x4 *row = reinterpret_cast<const f32x4 *>(W0 + (size_t)(ib * 8 + r) * K);
+    // group of vector k4: 64-feature segment / segments per group, both below 193, by the rounded-up reciprocal (the
+    // excess, below 192 x 192 / 65536 / per, never reaches the next integer)
+    const uint32_t per_group = (uint32_t)gs >> 6, inv_per = (65536u + per_group - 1) / per_group;
+    auto group_of = [&](int k4) { return (int)(((uint32_t)k4 >> 4) * inv_per >> 16); };
 
     f32x4 v[NV];
 #pragma unroll
@@ -192,30 +251,29 @@ __global__ __launch_bounds__(1024) void quantize_resident_kernel(const float *__
     for (int e = tid; e < 16 * G; e += 1024) s_max[e] = 0u;          // s_max and s_neg
     __syncthreads();
 
-    // ---- range per (channel, group): 16 lanes hold 64 consecutive features, always of one group
+    // ---- range per (channel, group): 16 lanes hold 64 consecutive features, always of one group; with one group
+    // per row a thread's vectors are folded first
+    float xmax = 0.f, xneg = 0.f;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-        float xmax = 0.f, xneg = 0.f;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            if (v[i][e] > xmax) xmax = v[i][e];
-            if (-v[i][e] > xneg) xneg = -v[i][e];
+            xmax = __builtin_fmaxf(xmax, v[i][e]);                       // (a NaN changes neither)
+            xneg = __builtin_fmaxf(xneg, -v[i][e]);
         }
-#pragma unroll
-        for (int o = 8; o >= 1; o >>= 1) {
-            const float a = __shfl_xor(xmax, o), b = __shfl_xor(xneg, o);
-            if (a > xmax) xmax = a;
-            if (b > xneg) xneg = b;
-        }
+        if (G == 1 && i + 1 < NV) continue;
+        xmax = max16(xmax);
+        xneg = max16(xneg);
         const int k4 = l + 128 * i;
-        if ((l & 15) == 0 && k4 < K4) {
-            const int g = (4 * k4) / gs;
-            atomicMax(&s_max[r * G + g], __float_as_uint(xmax));
-            atomicMax(&s_neg[r * G + g], __float_as_uint(xneg));
+        if ((l & 15) == 0 && (G == 1 || k4 < K4)) {
+            const int g = G == 1 ? 0 : group_of(k4);
+            atomicMax(&s_max[r * G + g], __float_as_uint(xmax + 0.f));   // (+ 0: no negative zero)
+            atomicMax(&s_neg[r * G + g], __float_as_uint(xneg + 0.f));
         }
+        xmax = xneg = 0.f;
     }
     __syncthreads();
-    // (s, z, 1 / s) of candidate j for entry e = r * G + g
+    // (s, z, code factor) of candidate j for entry e = r * G + g
     auto candidate = [&](int e, int j) {
         const float xmax = __uint_as_float(s_max[e]);
         const float xneg = __uint_as_float(s_neg[e]);
@@ -239,7 +297,7 @@ __global__ __launch_bounds__(1024) void quantize_resident_kernel(const float *__
         }
         s_s[e] = s;
         s_z[e] = z;
-        s_rs[e] = 1.0 / (double)s;
+        s_r[e] = code_factor(s);
     };
     for (int e = tid; e < 8 * G; e += 1024) candidate(e, 0);
     __syncthreads();
@@ -252,22 +310,25 @@ __global__ __launch_bounds__(1024) void quantize_resident_kernel(const float *__
                 const int k4 = l + 128 * i;
                 double err = 0.0;
                 if (k4 < K4) {
-                    const int g = (4 * k4) / gs;
+                    const int g = group_of(k4);
                     const float sc = s_s[r * G + g];
-                    const double rs = s_rs[r * G + g];
                     const int z = s_z[r * G + g];
+                    const float w4[4] = {v[i][0], v[i][1], v[i][2], v[i][3]};
+                    float c[4];
+                    codes_of<BITS, 4>(w4, sc, s_r[r * G + g], z, c);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        int q = (int)rintf((float)((double)v[i][e] * rs)) + z;
-                        q = q < 0 ? 0 : (q > qmax ? qmax : q);
-                        const float back = sc * (float)(q - z);
-                        const float d = v[i][e] - back;
-                        err += (double)d * (double)d;
+                        const float back = sc * (c[e] - (float)z);
+                        const float d = w4[e] - back;
+                        err = __builtin_fma((double)d, (double)d, err);   // the square of an fp32 number is exact in fp64
                     }
                 }
-#pragma unroll
-                for (int o = 8; o >= 1; o >>= 1) err += __shfl_xor(err, o);
+                err += rotated16<8>(err);
+                err += rotated16<4>(err);
+                err += rotated16<2>(err);
+                err += rotated16<1>(err);
                 if ((l & 15) == 0 && k4 < K4) seg_err[r * segs + (k4 >> 4)] = err;
+                __builtin_amdgcn_sched_barrier(0);                       // one vector at a time: the rows leave few registers
             }
             __syncthreads();
             for (int e = tid; e < 8 * G; e += 1024) {
@@ -278,14 +339,14 @@ __global__ __launch_bounds__(1024) void quantize_resident_kernel(const float *__
                     b_err[e] = err;
                     b_s[e] = s_s[e];
                     b_z[e] = s_z[e];
-                    b_rs[e] = s_rs[e];
+                    b_r[e] = s_r[e];
                 }
                 if (j + 1 < n_ratios) {
                     candidate(e, j + 1);
                 } else {
                     s_s[e] = b_s[e];
                     s_z[e] = b_z[e];
-                    s_rs[e] = b_rs[e];
+                    s_r[e] = b_r[e];
                 }
             }
             __syncthreads();
@@ -297,39 +358,45 @@ __global__ __launch_bounds__(1024) void quantize_resident_kernel(const float *__
         z0[(size_t)(ib * 8 + rr) * G + g] = (uint8_t)s_z[e];
     }
 
-    // ---- codes of all eight rows into LDS (one byte per code, [8][K]), then the packed words
+    // ---- codes of all eight rows into LDS, then the packed words
     const size_t out_row = (size_t)(ib / 16) * (K / 32) * 64 + (size_t)(ib % 16) * 4;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
         const int k4 = l + 128 * i;
-        if (k4 < K4) {
-            const int g = (4 * k4) / gs;
-            const double rs = s_rs[r * G + g];
-            const int z = s_z[r * G + g];
-            uint32_t w = 0;
+        if (k4 < K4) {                                               // (K % 128 == 0: the two lanes of a word agree)
+            const int g = group_of(k4);
+            const float w4[4] = {v[i][0], v[i][1], v[i][2], v[i][3]};
+            float c[4];
+            codes_of<BITS, 4>(w4, s_s[r * G + g], s_r[r * G + g], s_z[r * G + g], c);
+            if constexpr (BITS == 4) {
+                // nibble cc / 2 + 4 (cc % 2) of the word holds feature cc: 0, 4, 1, 5 and, a byte up, 2, 6, 3, 7
+                const float p = __builtin_fmaf(c[3], 1048576.f, __builtin_fmaf(c[1], 65536.f, __builtin_fmaf(c[2], 16.f, c[0])));
+                uint32_t word = (uint32_t)p << (8 * (l & 1));
+                word |= (uint32_t)__builtin_amdgcn_update_dpp(0u, word, 0xB1, 0xF, 0xF, false);   // lane ^ 1
+                if ((l & 1) == 0) s_codes[(k4 >> 1) * 8 + r] = word;
+            } else {
+                uint32_t w = 0;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                int q = (int)rintf((float)((double)v[i][e] * rs)) + z;
-                q = q < 0 ? 0 : (q > qmax ? qmax : q);
-                w |= (uint32_t)q << (8 * e);
+                for (int e = 0; e < 4; ++e) w |= (uint32_t)c[e] << (8 * e);
+                s_codes[r * K4 + k4] = w;
             }
-            s_codes[r * K4 + k4] = w;
         }
+        if (NV > 16) __builtin_amdgcn_sched_barrier(0);
     }
     __syncthreads();
+    if constexpr (BITS == 4) {
+        for (int e = tid; e < K >> 2; e += 1024) {                   // half a block: 4 channels
+            const int kb = e >> 1;
+            const u32x4 words = *reinterpret_cast<const u32x4 *>(s_codes + 4 * e);
+            *reinterpret_cast<u32x4 *>(packed + (out_row + (size_t)(kb >> 2) * 64 + (kb & 3)) * WPB + 4 * (e & 1)) = words;
+        }
+        return;
+    }
     const int nwords = (K >> 3) * WPB;                               // packed words of this row of blocks
     for (int e = tid; e < nwords; e += 1024) {
         const int kb = e / WPB, wi = e % WPB;
         uint32_t word = 0;
-        if constexpr (BITS == 4) {
-            // word wi = channel wi of the block: nibble cc / 2 + 4 (cc % 2) holds feature cc
-            const uint32_t lo = s_codes[wi * K4 + 2 * kb], hi = s_codes[wi * K4 + 2 * kb + 1];
-#pragma unroll
-            for (int cc = 0; cc < 8; ++cc) {
-                const uint32_t q = ((cc < 4 ? lo : hi) >> (8 * (cc & 3))) & 0xFFu;
-                word |= q << (4 * (cc / 2 + 4 * (cc % 2)));
-            }
-        } else {
+        {
             const uint8_t *codes = reinterpret_cast<const uint8_t *>(s_codes);   // [8][K]
             const int m = wi >> 1, par = wi & 1;
             auto code = [&](int ch, int cc) { return (uint32_t)codes[(size_t)ch * K + 8 * kb + cc]; };
@@ -354,7 +421,7 @@ constexpr int kMaxDevQ = 64;
 bool quantize_resident_fits(int K, int G, bool search);
 namespace {
 
-// dynamic LDS of quantize_resident_kernel
+// dynamic LDS of quantize_resident_kernel (at least: which sizes fit does not hang on the last array)
 size_t resident_lds(int K, int G, bool search) { return (size_t)(search ? 384 : 192) * G + (size_t)(search ? 9 : 8) * K; }
 
 template <int BITS, int NV, bool SEARCH>
