@@ -613,7 +613,7 @@ static peqa_status bwd_impl(const peqa_layout *L, const uint32_t *packed, const 
             peqa::DwArgs a{};
             a.Xt = xt; a.dYt = dyt; a.packed = packed; a.z0 = z0; a.dz = dz; a.pc = pc;
             a.N = N; a.K = K; a.Tp = Tp; a.gsz = L->group_size; a.G = G;
-            a.tiles_f = (K + 255) / 256; a.tiles_c = (N + 255) / 256;
+            a.tiles_f = K / 128; a.tiles_c = (N + 255) / 256;
             if (peqa::launch_dw(L->bits, a, s) != hipSuccess) return PEQA_ERR_DEVICE;
             if (peqa::launch_chunk_reduce(pc, (size_t)N * G, L->group_size / 64, d_ds, s) != hipSuccess)
                 return PEQA_ERR_DEVICE;

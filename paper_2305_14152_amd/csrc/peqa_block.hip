@@ -448,7 +448,7 @@ peqa_status peqa_block_bwd(int32_t n, const peqa_block_item *items, int32_t T, v
             a.Xt = xt_of[xi[j]]; a.dYt = dyt; a.packed = it.packed; a.z0 = it.z0;
             a.pc = reinterpret_cast<float *>(ws + w.pc[j]);
             a.N = N; a.K = K; a.Tp = Tp; a.gsz = it.layout.group_size; a.G = G;
-            a.tiles_f = (K + 255) / 256; a.tiles_c = (N + 255) / 256;
+            a.tiles_f = K / 128; a.tiles_c = (N + 255) / 256;
             dw.d_ds[dw.n_jobs++] = it.d_ds;
         }
     }

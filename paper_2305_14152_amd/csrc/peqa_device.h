@@ -250,8 +250,9 @@ __device__ __forceinline__ void reduce_partials_at(const float *__restrict__ par
 }
 
 // One 64 x 64 tile of the step-major transposed copy that the token contraction of group-wise layers reads:
-// dst[t / 32][cc][t % 32] = src[t, cc] for t < T, 0 for T <= t < Tp, tile (bt, bc) of 64 tokens x 64 columns,
-// by one workgroup of 256 threads through `tile`, 64 x 66 bf16 of LDS.  C % 64 == 0.
+// dst[t / 32][cc / 16][(t % 32) / 8][cc % 16][t % 8] = src[t, cc] for t < T, 0 for T <= t < Tp (the KB of 16 columns and a
+// step is one matrix operand, lane by lane), tile (bt, bc) of 64 tokens x 64 columns, by one workgroup of 256 threads
+// through `tile`, 64 x 66 bf16 of LDS.  C % 64 == 0.
 __device__ __forceinline__ void transpose_pad_tile(const uint16_t *__restrict__ src, int T, int C, uint16_t *__restrict__ dst,
                                                    int bt, int bc, uint16_t (*tile)[64 + 2])
 {
@@ -271,13 +272,12 @@ __device__ __forceinline__ void transpose_pad_tile(const uint16_t *__restrict__ 
     __syncthreads();
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        const int cc = (threadIdx.x >> 3) + 32 * h;
+        // step h, 16-byte pieces in the order of the copy: 4 KB of 64 columns
+        const int cc = 16 * (threadIdx.x >> 6) + (threadIdx.x & 15), t = 32 * h + 8 * ((threadIdx.x >> 4) & 3);
         u32x4 o;
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-            o[e] = (uint32_t)tile[8 * ch + 2 * e][cc] | ((uint32_t)tile[8 * ch + 2 * e + 1][cc] << 16);
-        const int t = t0 + 8 * ch;                        // 8 tokens of one 32-token step
-        *reinterpret_cast<u32x4 *>(dst + ((size_t)(t >> 5) * C + c0 + cc) * 32 + (t & 31)) = o;
+        for (int e = 0; e < 4; ++e) o[e] = (uint32_t)tile[t + 2 * e][cc] | ((uint32_t)tile[t + 2 * e + 1][cc] << 16);
+        *reinterpret_cast<u32x4 *>(dst + ((size_t)((t0 >> 5) + h) * C + c0) * 32 + 8 * threadIdx.x) = o;
     }
 }
 

@@ -8,29 +8,24 @@
 // contraction between a ring fill and an epilogue.  Here the contraction runs over all tokens without a
 // restart, no code is unpacked inside the loop, and the groups only appear in the epilogue.
 //
-// Both operands are needed with the token index contiguous, so X and dY are first transposed
-// (transpose_pad_kernel) into step-major arrays [Tp / 32][rows][32] (rows = K or N, Tp = T rounded up to
-// 64, zero-filled): the 64 bytes a row contributes to one 32-token step of the contraction sit next to
-// those of its neighbour rows, so a tile of 256 rows is 16 contiguous KB per step.  (With plain [rows][Tp]
-// arrays every 64-byte piece is half a cache line on its own, 2 Tp bytes from the next, and the loop
-// is bound by the request rate of the L2: measured 1.5 us per step against 0.5 us of matrix work.)
+// Both operands are needed with the token index contiguous, so X and dY are first copied (transpose_pad_kernel) into
+// arrays of 32-token steps, Tp = T rounded up to 64, zero-filled, in which 16 rows (features or channels) of a step are
+// one KB: exactly a matrix operand, lane by lane (transpose_pad_tile).  A tile's rows of a step are contiguous.
 //
-// dw_kernel: one workgroup = a 256 (features) x 256 (channels) tile of dW, as 8 waves (4 along the features x
-// 2 along the channels, two per SIMD) of 64 x 128 accumulators each (4 x 8 MFMA 16x16x32 tiles in 128 AGPRs);
-// the template also builds 4 waves of 128 x 128 (one per SIMD), which measured slower (282 against 223 us on
-// the 13B shapes: with one wave per SIMD nothing runs behind a wave's waits).  Both operands come from LDS.
-// A wave's features are 64-feature chunks, the unit in which the epilogue reports (every group is a whole
-// number of chunks).  Operands go global -> LDS by DMA into a ring of 4 stages of 32 KB (one 32-token step:
-// 256 + 256 rows of 64 B, XOR-swizzled as in the other contraction kernel); fragments for step it + 1 are read
-// from LDS while step it's matrix instructions run.  The epilogue takes each lane's codes from a copy of the tile's
-// packed words that one of the ring's spare stages brought into LDS (see issue_one), at word positions and shifts
-// worked out once per lane, forms sum dW Q - z sum dW over each chunk with two shuffles, and writes pc[i, chunk];
-// chunk_reduce_kernel adds the chunks of every group in order.
-// Where the time of a tile goes at T = 2048 (64 steps; timestamps per workgroup on the 13B shapes): 2.6 us from its
-// start to its first fragments, 47-53 us in the loop (0.75-0.85 us per step against 0.49 us of matrix instructions:
-// timing builds without the loop's DMAs, without its fragment reads, and without both ran the launch in 0.80, 0.92
-// and 0.78 of its time, so with one workgroup per compute unit and a barrier per step about three quarters of the
-// loop is the floor of this form), 6 us in the epilogue, 2 us until the next tile starts on the unit.
+// dw_kernel: one workgroup = a 128 (features) x 256 (channels) tile of dW by 4 waves of 128 x 64 accumulators each
+// (8 x 4 MFMA 16x16x32 tiles in 128 AGPRs), two workgroups per compute unit, of which one runs while the other waits at a
+// barrier, fills its ring or is in its epilogue.  The features are shared by the four waves: global -> LDS by DMA into a
+// ring of 6 stages of 8 KB, and from there into registers a step ahead.  The channels are the wave's own: straight from
+// memory into registers, two steps ahead.  So LDS moves 80 KB per step of
+// two workgroups (about 640 of 1024 cycles of matrix instructions), where one workgroup of 256 x 256 with both operands
+// in LDS moved 128 KB and had nothing to run at its barrier: at T = 2048 the launch of a 13B block's
+// layers (3 bits, groups of 128) took 1150-1230 us in that form and takes 1035, a 13824 x 5120 layer 316 and 253 us with
+// the copies, 4096 x 11008 with groups of 64 at T = 500 72 and 61 us.  (Patches of 4 x 16 or 16 x 4 tiles, the DMAs in the
+// middle of the step, feature reads spread over the whole step: within 1 %.)
+// The epilogue takes each lane's codes from a copy of the tile's packed words that the first DMAs brought into LDS, at
+// word positions and shifts worked out once per lane, forms sum dW Q - z sum dW over each chunk of 64 features (every
+// group is a whole number of them) with two shuffles, and writes pc[i, chunk]; chunk_reduce_kernel adds the chunks of
+// every group in order.
 #include <stddef.h>
 
 #include "peqa_device.h"
@@ -40,174 +35,144 @@ namespace peqa {
 
 namespace {
 
-constexpr int DW_TF = 256;                       // features per workgroup
+constexpr int DW_TF = 128;                       // features per workgroup
 constexpr int DW_TC = 256;                       // channels per workgroup
-constexpr int DW_NST = 4;                        // ring depth
-constexpr int DW_A_BYTES = DW_TF * 64;           // 16 KB: 256 feature rows x 32 tokens
-constexpr int DW_STAGE = (DW_TF + DW_TC) * 64;   // 32 KB
-constexpr int DW_LDS = DW_NST * DW_STAGE;        // 128 KB
-constexpr int DW_WM = 4;                         // waves along the features: see dw_kernel
+constexpr int DW_NST = 6;                        // ring depth
+constexpr int DW_STAGE = DW_TF * 64;             // 8 KB: 128 feature rows x 32 tokens
+constexpr int DW_CODES = 16 * 1024;              // packed words of the tile (12 KB of them at 3 bits)
+constexpr int DW_LDS = DW_CODES + DW_NST * DW_STAGE;
 
-// WM = waves along the features (2: 128 x 128 wave tiles, one wave per SIMD; 4: 64 x 128, two per SIMD)
-template <int BITS, int WM>
+// workgroups of a layer: its tiles, rounded up to a whole number per XCD
+int dw_wgs(const DwArgs &a) { return (a.tiles_f * a.tiles_c + 7) / 8 * 8; }
+
+template <int BITS>
 __device__ __forceinline__ void dw_tile(const DwArgs &a, const int wg, uint8_t *lds)
 {
     constexpr int WPB = 2 * BITS;
-    constexpr int NRT = 16 / WM;                           // accumulator row tiles per wave
-    constexpr int DW_DMA = 16 / WM;                        // DMA instructions per wave per step (32 of 1 KB per stage)
+    constexpr int NRT = 8, NCT = 4;                        // accumulator tiles of a wave: features x channels
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave % WM, wn = wave / WM;              // feature part, channel half
+    const int wn = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave = quarter of the channels
     const int c = lane & 15, q = lane >> 4;
 
-    // workgroup -> tile: the 32 workgroups that run together on one XCD take a patch of 4 feature tiles
-    // x 8 channel tiles, so that operand rows are shared through that XCD's L2
+    // workgroup -> tile: XCD x gets an eighth of the tiles, in one run of an order in which 64 neighbours (what an XCD
+    // runs at a time) are a patch of 8 feature x 8 channel tiles, so that operand rows are shared through its L2
     int tile_f, tile_c;
     {
-        const int xcd = wg & 7, local = wg >> 3;
-        const int g = (local >> 5) * 8 + xcd, r = local & 31;
-        const int patches_f = (a.tiles_f + 3) / 4;
-        tile_f = (g % patches_f) * 4 + (r & 3);
-        tile_c = (g / patches_f) * 8 + (r >> 2);
+        const int ntiles = a.tiles_f * a.tiles_c, xcd = wg & 7;
+        const int lo = ntiles / 8 * xcd + min(xcd, ntiles % 8), mine = ntiles / 8 + (xcd < ntiles % 8 ? 1 : 0);
+        if ((wg >> 3) >= mine) return;                     // (uniform)
+        const int id = lo + (wg >> 3);
+        const int st = id / (8 * a.tiles_c), r = id - st * 8 * a.tiles_c;
+        const int left = a.tiles_f - 8 * st, rows = left < 8 ? left : 8;
+        tile_c = r / rows;
+        tile_f = 8 * st + (r - tile_c * rows);
     }
-    if (tile_f >= a.tiles_f || tile_c >= a.tiles_c) return;   // padding of a ragged patch (uniform)
 
     const int k0 = tile_f * DW_TF, n0 = tile_c * DW_TC;
     const int nsteps = a.Tp >> 5;                          // even: Tp % 64 == 0
     const uint32_t lds_base = (uint32_t)(uintptr_t)lds;
 
-    // DMA j of wave w is wave-load d = DW_DMA w + j of the stage: 0..15 = feature rows 16 d .. + 15 of Xt,
-    // 16..31 = channel rows 16 (d - 16) .. of dYt.  Lane s lands at row s / 4, chunk position s % 4 and
-    // fetches the chunk that the swizzle assigns there.  Rows past the matrix are clamped to its last
-    // row: their products are computed and dropped.
-    uint32_t voff[DW_DMA];
-    const uint8_t *src = reinterpret_cast<const uint8_t *>(wave < WM ? a.Xt : a.dYt);
-    const size_t step_bytes = (size_t)(wave < WM ? a.K : a.N) * 64;   // one 32-token step of all rows
+    // ---- the packed codes of the tile's 128 x 256 weights, for the epilogue: two runs of 4 step tiles (CODE_RUN bytes
+    // each: contiguous in the tile-major layout), of its two 128-channel tile rows, copied linearly, 3 or 4 KB per wave.
+    // A second tile row past the matrix is read from the first and never looked at.
+    constexpr uint32_t CODE_TILE = 64 * WPB * 4, CODE_RUN = 4 * CODE_TILE;   // one 128 x 32 tile; 4 of them (6 or 8 KB)
+    constexpr int CODE_DMA = 2 * CODE_RUN / 4096;
     {
-        const int row_l = lane >> 2, pos = lane & 3;
-        const uint32_t chunk = (uint32_t)(pos ^ a_swizzle(row_l));
-        const int first = wave < WM ? k0 : n0, limit = (wave < WM ? a.K : a.N) - 1;
+        const size_t row_bytes = (size_t)(a.K >> 5) * CODE_TILE;
 #pragma unroll
-        for (int j = 0; j < DW_DMA; ++j) {
-            int row = first + 16 * (DW_DMA * (wave % WM) + j) + row_l;
-            row = row < limit ? row : limit;
-            voff[j] = (uint32_t)row * 64u + chunk * 16u;
+        for (int j = 0; j < CODE_DMA; ++j) {
+            const uint32_t byte = (uint32_t)(CODE_DMA * wn + j) * 1024u;
+            const uint32_t run = byte / CODE_RUN, off = byte - run * CODE_RUN;
+            const int row = (2 * tile_c + (int)run) * 128 < a.N ? 2 * tile_c + (int)run : 2 * tile_c;
+            dma16((uint32_t)lane * 16u, reinterpret_cast<const uint8_t *>(a.packed) + (size_t)row * row_bytes + (size_t)tile_f * CODE_RUN + off,
+                  lds_base + byte);
         }
     }
-    // The queue runs four stages past the last step, so that the DMA count per step is constant.  Of those, the
-    // stage numbered `nsteps` carries the packed codes of the tile's 256 x 256 weights for the epilogue: the two runs of
-    // 8 step tiles (RUN bytes each: contiguous in the tile-major layout) of its two 128-channel tile rows, copied
-    // linearly, KB number d by DMA d = DW_DMA wave + j; the others re-fetch the last step.  Runs past the matrix
-    // (second tile row beyond N, step tiles beyond K, the KBs after the two runs at 3 bits) are read from valid
-    // memory somewhere else and never looked at.
-    constexpr uint32_t CODE_TILE = 64 * WPB * 4, CODE_RUN = 8 * CODE_TILE;   // one 128 x 32 tile; 8 of them (12 or 16 KB)
-    const uint8_t *code_src[DW_DMA];
-    {
-        const size_t total = (size_t)a.N * a.K / 8 * BITS, row_bytes = (size_t)(a.K >> 5) * CODE_TILE;
-#pragma unroll
-        for (int j = 0; j < DW_DMA; ++j) {
-            const uint32_t byte = (uint32_t)(DW_DMA * wave + j) * 1024u;
-            uint32_t run = byte / CODE_RUN;
-            const uint32_t off = byte - run * CODE_RUN;
-            if (run > 1 || (2 * tile_c + (int)run) * 128 >= a.N) run = 0;
-            size_t g = (size_t)(2 * tile_c + run) * row_bytes + (size_t)tile_f * CODE_RUN + off;
-            g = g + 1024 <= total ? g : total - 1024;
-            code_src[j] = reinterpret_cast<const uint8_t *>(a.packed) + g;
-        }
-    }
-    auto issue_one = [&](int j, int it, int stage) {
-        const uint32_t dst = lds_base + stage * DW_STAGE + (DW_DMA * wave + j) * 1024;
-        if (it == nsteps) {
-            dma16((uint32_t)lane * 16u, code_src[j], dst);
-        } else {
-            const int s = it < nsteps ? it : nsteps - 1;
-            dma16(voff[j], src + (size_t)s * step_bytes, dst);
-        }
-    };
-    auto issue = [&](int it, int stage) {
-#pragma unroll
-        for (int j = 0; j < DW_DMA; ++j) issue_one(j, it, stage);
-    };
 
-    f32x4 acc[NRT][8];
+    // Both queues run past the last step (re-fetching it), so that the number of operations in flight per step is constant.
+    const uint8_t *xsrc = reinterpret_cast<const uint8_t *>(a.Xt) + (size_t)k0 * 64;
+    const size_t xstep = (size_t)a.K * 64, ystep = (size_t)a.N * 64;   // one 32-token step of all rows
+    auto clamp_step = [&](int it) { return it < nsteps ? it : nsteps - 1; };
+    // DMA j of wave wn is KB 2 wn + j of the stage
+    auto issue = [&](int it, int stage) {
+        const uint8_t *src = xsrc + (size_t)clamp_step(it) * xstep;
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            dma16((uint32_t)(2 * wn + j) * 1024u + (uint32_t)lane * 16u, src, lds_base + DW_CODES + stage * DW_STAGE + (2 * wn + j) * 1024);
+    };
+    // the wave's 64 channels; past the matrix (N % 128 == 0: whole waves) the last ones of it, and nothing is stored
+    const int cb = n0 + 64 * wn, cb_l = cb < a.N ? cb : a.N - 64;
+    const uint8_t *ysrc = reinterpret_cast<const uint8_t *>(a.dYt) + (size_t)cb_l * 64;
+    auto load_b = [&](const uint8_t *step_src, int ct) { return *reinterpret_cast<const u32x4 *>(step_src + ct * 1024 + lane * 16); };
+    u32x4 bfrag[2][NCT];
+
+    f32x4 acc[NRT][NCT];
 #pragma unroll
     for (int i = 0; i < NRT; ++i)
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < NCT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    const int sw = (q ^ a_swizzle(c)) << 4;
-    const int a_off = (16 * NRT * wm + c) * 64 + sw;       // + rt * 1024
-    const int b_off = DW_A_BYTES + (128 * wn + c) * 64 + sw;   // + ct * 1024
     auto read_a = [&](int stage, int rt) {
-        return *reinterpret_cast<const u32x4 *>(lds + stage * DW_STAGE + a_off + rt * 1024);
-    };
-    auto read_b = [&](int stage, int ct) {
-        return *reinterpret_cast<const u32x4 *>(lds + stage * DW_STAGE + b_off + ct * 1024);
+        return *reinterpret_cast<const u32x4 *>(lds + DW_CODES + stage * DW_STAGE + rt * 1024 + lane * 16);
     };
 
-    // ---- prologue: four stages queued; the first two complete before the first fragments are read
+    // ---- prologue: five stages and two steps of channel operands queued, in the order of the loop; the first two stages
+    // (and the codes before them) complete before the first operands are read
+    constexpr int PER_STEP = 2 + NCT;                      // memory operations of a wave per step
     issue(0, 0);
     issue(1, 1);
-    issue(2, 2);
-    issue(3, 3);
-    wait_vmcnt<2 * DW_DMA>();
+    static_for<2>([&](auto d_c) {
+        constexpr int d = d_c.value;
+        issue(2 + d, 2 + d);
+#pragma unroll
+        for (int ct = 0; ct < NCT; ++ct) bfrag[d][ct] = load_b(ysrc + (size_t)d * ystep, ct);
+    });
+    issue(4, 4);
+    wait_vmcnt<2 * PER_STEP + 2>();
     __syncthreads();
-    u32x4 afrag[2][NRT], bfrag[8];
+    u32x4 afrag[2][NRT];
 #pragma unroll
     for (int rt = 0; rt < NRT; ++rt) afrag[0][rt] = read_a(0, rt);
-#pragma unroll
-    for (int ct = 0; ct < 8; ++ct) bfrag[ct] = read_b(0, ct);
-    // step 0 refills stage 0: every wave must have taken its fragments out of it
-    __syncthreads();
 
-    // ---- main loop.  At the start of step `it` its fragments are in registers and stage it + 1 is
-    // complete and visible.  The step queues stage it + 4 into its own slot (its fragments left that slot
-    // during step it - 1, before the last barrier) while it runs its matrix instructions column tile by
-    // column tile, and refills every fragment from stage it + 1 right after its last use.  The closing
-    // wait leaves the DMAs of this step and the one before outstanding: stage it + 2 has landed, three
-    // steps after it was queued; the barrier makes it visible.
-    int cur = 0;
-    auto step = [&](int it, auto cur_c) {
+    // ---- main loop.  At the start of step `it` its feature operands are in registers and stage it + 1 is complete and
+    // visible.  The step queues stage it + 5 into the slot of stage it - 1 (read during step it - 2, and the last barrier
+    // came after), reads the feature operands of step it + 1, and refills every channel operand for step it + 2 right after
+    // its last use.  The closing wait leaves the operations of the last three steps outstanding: stage it + 2, queued in
+    // step it - 3, has landed; the barrier makes it visible.
+    int nxt = 1, slot = 5;                                 // slots of stage it + 1 and of stage it + 5
+    auto step = [&](int it, auto cur_c) __attribute__((always_inline)) {
         constexpr int CUR = decltype(cur_c)::value, NXT = CUR ^ 1;
-        const int nstage = (cur + 1) & (DW_NST - 1);
-        static_for<8>([&](auto ct_c) {
+        issue(it + 5, slot);
+        const uint8_t *src = ysrc + (size_t)clamp_step(it + 2) * ystep;
+        static_for<NCT>([&](auto ct_c) {
             constexpr int ct = ct_c.value;
-            static_for<NRT>([&](auto rt_c) { mfma16_acc(acc[rt_c.value][ct], afrag[CUR][rt_c.value], bfrag[ct]); });
-            // the DMAs are spread over the step: queued in one burst after the barrier, they hold back the
-            // matrix instructions behind them until the memory pipe has taken all of them
-            if constexpr (ct % (8 / DW_DMA) == 0) issue_one(ct / (8 / DW_DMA), it + 4, cur);
-            bfrag[ct] = read_b(nstage, ct);
-            // the next step's first matrix instructions need all its row fragments: those are fetched in
-            // the first half of this step, so that only a column fragment is still on its way at the barrier
-            if constexpr (ct < 4) {
-                static_for<NRT / 4>([&](auto e_c) {
-                    constexpr int rt = ct * (NRT / 4) + e_c.value;
-                    afrag[NXT][rt] = read_a(nstage, rt);
-                });
-            }
+            static_for<NRT>([&](auto rt_c) {
+                constexpr int rt = rt_c.value;
+                mfma16_acc(acc[rt][ct], afrag[CUR][rt], bfrag[CUR][ct]);
+                if constexpr (ct < 2 && rt % 2 == 1) afrag[NXT][4 * ct + rt / 2] = read_a(nxt, 4 * ct + rt / 2);
+            });
+            bfrag[CUR][ct] = load_b(src, ct);
         });
-        wait_vmcnt<2 * DW_DMA>();
+        wait_vmcnt<3 * PER_STEP>();
         bare_barrier();
-        cur = nstage;
+        nxt = nxt == DW_NST - 1 ? 0 : nxt + 1;
+        slot = slot == DW_NST - 1 ? 0 : slot + 1;
     };
     for (int it = 0; it < nsteps; it += 2) {
         step(it, std::integral_constant<int, 0>{});
         step(it + 1, std::integral_constant<int, 1>{});
     }
     wait_vmcnt<0>();
-    __syncthreads();
     mfma_result_fence();
 
-    // ---- epilogue: this wave's features are the chunks fb / 64 + h (accumulator rows rt = 4 h .. 4 h + 3);
-    // lane (c, q) holds, per accumulator tile (rt, ct), features fb + 16 rt + 4 q + j (j = 0..3) of
-    // channel cb + 16 ct + c
-    const int fb = k0 + 16 * NRT * wm, cb = n0 + 128 * wn;
-    if (cb >= a.N) return;                                 // wave-uniform (N % 128 == 0)
+    // ---- epilogue: the features are the chunks k0 / 64 + h (accumulator rows rt = 4 h .. 4 h + 3); lane (c, q) holds,
+    // per accumulator tile (rt, ct), features k0 + 16 rt + 4 q + j (j = 0..3) of channel cb + 16 ct + c
+    if (cb >= a.N) return;                                 // wave-uniform
     const int nchunks = a.K >> 6;
-    // the tile's codes, in the ring slot of stage `nsteps`: run wn = this wave's 128 channels
-    const uint8_t *code_lds = lds + (nsteps & (DW_NST - 1)) * DW_STAGE + wn * CODE_RUN;
+    // the codes of this wave's 128-channel tile row
+    const uint8_t *code_lds = lds + (wn >> 1) * CODE_RUN;
     // The lane's four features of an accumulator tile are half a row of one 8 x 8 code block: row r = c % 8 (cb is a
-    // multiple of 128), columns 4 hq .. 4 hq + 3 with hq = q % 2 (fb + 16 rt is a multiple of 16).  Where those four
+    // multiple of 64), columns 4 hq .. 4 hq + 3 with hq = q % 2 (k0 + 16 rt is a multiple of 16).  Where those four
     // codes sit inside the block's words depends on (r, hq) only: worked out once per lane, so that a tile costs a few
     // loads at fixed offsets and shifts by lane constants (taken code by code with run-time row and column, the
     // epilogue took a third of the kernel's time at T = 2048).
@@ -247,29 +212,27 @@ __device__ __forceinline__ void dw_tile(const DwArgs &a, const int wg, uint8_t *
     };
     static_for<NRT / 4>([&](auto h_c) {
         constexpr int h = h_c.value;
-        const int fh = fb + 64 * h;
-        if (fh >= a.K) return;                             // wave-uniform (K % 64 == 0)
+        const int fh = k0 + 64 * h;
         const int chunk = fh >> 6, grp = fh / a.gsz;
-        // zero-points of the lane's eight channels, fetched together and by every lane: inside the q == 0 branch below
+        // zero-points of the lane's channels, fetched together and by every lane: inside the q == 0 branch below
         // each would be a load of its own with a full memory latency in front of the store
-        float zv[8];
+        float zv[NCT];
 #pragma unroll
-        for (int ct = 0; ct < 8; ++ct) {
+        for (int ct = 0; ct < NCT; ++ct) {
             const size_t sg = (size_t)(cb + 16 * ct + c) * a.G + grp;
             zv[ct] = (float)a.z0[sg] + (a.dz ? a.dz[sg] : 0.f);
         }
-        static_for<8>([&](auto ct_c) {
+        static_for<NCT>([&](auto ct_c) {
             constexpr int ct = ct_c.value;
             const int i = cb + 16 * ct + c;
-            // blocks of channel block (i / 8) % 16 = 2 ct + c / 8 within the tiles of the run
-            const uint32_t *ch_tile = reinterpret_cast<const uint32_t *>(code_lds) + (2 * ct + (c >> 3)) * 4 * WPB;
+            // blocks of channel block (i / 8) % 16 = 8 (wn % 2) + 2 ct + c / 8 within the tiles of the run
+            const uint32_t *ch_tile = reinterpret_cast<const uint32_t *>(code_lds) + (8 * (wn & 1) + 2 * ct + (c >> 3)) * 4 * WPB;
             float s1 = 0.f, s0 = 0.f;
             static_for<4>([&](auto r_c) {
                 constexpr int rt = 4 * h + r_c.value;
                 const f32x4 v = read_acc(acc[rt][ct]);
-                // the lane's features fb + 16 rt + 4 q + j: step tile (fb - k0 + 16 rt) / 32 of the run, block column
-                // 2 (rt % 2) + q / 2
-                const uint32_t *blk = ch_tile + (((fb - k0) >> 5) + (rt >> 1)) * 64 * WPB + (2 * (rt & 1) + (q >> 1)) * WPB;
+                // the lane's features k0 + 16 rt + 4 q + j: step tile rt / 2 of the run, block column 2 (rt % 2) + q / 2
+                const uint32_t *blk = ch_tile + (rt >> 1) * 64 * WPB + (2 * (rt & 1) + (q >> 1)) * WPB;
                 float code[4];
                 lane_codes(blk, code);
 #pragma unroll
@@ -285,18 +248,18 @@ __device__ __forceinline__ void dw_tile(const DwArgs &a, const int wg, uint8_t *
     });
 }
 
-template <int BITS, int WM>
-__global__ __launch_bounds__(128 * WM, 1) void dw_kernel(DwArgs a)
+template <int BITS>
+__global__ __launch_bounds__(256, 2) void dw_kernel(DwArgs a)
 {
     extern __shared__ __align__(16) uint8_t lds[];
-    dw_tile<BITS, WM>(a, (int)blockIdx.x, lds);
+    dw_tile<BITS>(a, (int)blockIdx.x, lds);
 }
 
 // The token contractions of several layers in one launch: the tiles of job 0 first, then job 1's, ...  One layer's
-// tiles alone often fill the machine a fraction over a whole number of times (400 tiles of 256 x 256 on 256 compute
-// units for a 5120 x 5120 layer); together only the last round of the launch is partly filled.
-template <int BITS, int WM>
-__global__ __launch_bounds__(128 * WM, 1) void dw_multi_kernel(DwMultiArgs m)
+// tiles alone often fill the machine a fraction over a whole number of times (800 tiles in 512 places for a
+// 5120 x 5120 layer); together only the last round of the launch is partly filled.
+template <int BITS>
+__global__ __launch_bounds__(256, 2) void dw_multi_kernel(DwMultiArgs m)
 {
     extern __shared__ __align__(16) uint8_t lds[];
     const int b = (int)blockIdx.x;
@@ -307,7 +270,7 @@ __global__ __launch_bounds__(128 * WM, 1) void dw_multi_kernel(DwMultiArgs m)
         if (b >= e) { j = i + 1; wg0 = e; }
     }
     const DwArgs a = kernarg_load<DwArgs>((uint32_t)(j * sizeof(DwArgs)));
-    dw_tile<BITS, WM>(a, b - wg0, lds);
+    dw_tile<BITS>(a, b - wg0, lds);
 }
 
 // transpose_pad_tile (peqa_device.h) for every 64 x 64 tile of src [T, C] (Tp / 64 x C / 64 workgroups).
@@ -370,26 +333,22 @@ hipError_t launch_dw(int bits, const DwArgs &a, hipStream_t stream)
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= kMaxDev) return hipErrorInvalidDevice;
-    auto kern = bits == 4 ? dw_kernel<4, DW_WM> : dw_kernel<3, DW_WM>;
+    auto kern = bits == 4 ? dw_kernel<4> : dw_kernel<3>;
     bool &done = g_attr_done[bits == 4][dev];
     if (!done) {
         e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, DW_LDS);
         if (e != hipSuccess) return e;
         done = true;
     }
-    // patches of 4 x 8 tiles, 32 workgroup ids per patch and XCD
-    const int patches_f = (a.tiles_f + 3) / 4, patches_c = (a.tiles_c + 7) / 8;
-    const int npatch = patches_f * patches_c;
-    const unsigned grid = (unsigned)(((npatch + 7) / 8) * 8 * 32);
     trace_before(KID_GEMM_DW, stream);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(128 * DW_WM), DW_LDS, stream, a);
+    hipLaunchKernelGGL(kern, dim3(dw_wgs(a)), dim3(256), DW_LDS, stream, a);
     trace_after(KID_GEMM_DW, stream);
     return hipGetLastError();
 }
 
 static bool dw_args_ok(const DwArgs &a)
 {
-    if (a.K % 64 != 0 || a.N % 128 != 0 || a.Tp % 64 != 0 || a.Tp < 64 || a.gsz % 64 != 0 || a.K % a.gsz != 0) return false;
+    if (a.K % 128 != 0 || a.tiles_f != a.K / 128 || a.tiles_c != (a.N + 255) / 256 || a.N % 128 != 0 || a.Tp % 64 != 0 || a.Tp < 64 || a.gsz % 64 != 0 || a.K % a.gsz != 0) return false;
     return (uint64_t)(a.K > a.N ? a.K : a.N) * 64u < ((uint64_t)1 << 32);   // 32-bit DMA offsets
 }
 
@@ -401,8 +360,7 @@ hipError_t launch_dw_multi(int bits, DwMultiArgs &m, hipStream_t stream)
         if (j < m.n_jobs) {
             const DwArgs &a = m.job[j];
             if (!dw_args_ok(a)) return hipErrorInvalidValue;
-            const int patches_f = (a.tiles_f + 3) / 4, patches_c = (a.tiles_c + 7) / 8;
-            total += ((patches_f * patches_c + 7) / 8) * 8 * 32;
+            total += dw_wgs(a);
         } else {
             m.job[j] = m.job[m.n_jobs - 1];
             m.d_ds[j] = m.d_ds[m.n_jobs - 1];
@@ -413,7 +371,7 @@ hipError_t launch_dw_multi(int bits, DwMultiArgs &m, hipStream_t stream)
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= kMaxDev) return hipErrorInvalidDevice;
-    auto kern = bits == 4 ? dw_multi_kernel<4, DW_WM> : dw_multi_kernel<3, DW_WM>;
+    auto kern = bits == 4 ? dw_multi_kernel<4> : dw_multi_kernel<3>;
     bool &done = g_attr_done_multi[bits == 4][dev];
     if (!done) {
         e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, DW_LDS);
@@ -421,7 +379,7 @@ hipError_t launch_dw_multi(int bits, DwMultiArgs &m, hipStream_t stream)
         done = true;
     }
     trace_before(KID_GEMM_DW, stream);
-    hipLaunchKernelGGL(kern, dim3(total), dim3(128 * DW_WM), DW_LDS, stream, m);
+    hipLaunchKernelGGL(kern, dim3(total), dim3(256), DW_LDS, stream, m);
     trace_after(KID_GEMM_DW, stream);
     return hipGetLastError();
 }

@@ -141,15 +141,15 @@ int gemm_multi_wgs(const GemmArgs &a);
 // Arguments of the token contraction dW = dY^T X with the codes applied in its epilogue (peqa_dw.hip):
 // the scale gradient of group-wise layers.
 struct DwArgs {
-    const uint16_t *Xt;       // [Tp / 32, K, 32] bf16: X transposed in 32-token steps, tokens padded with zeros to Tp
-    const uint16_t *dYt;      // [Tp / 32, N, 32] bf16
+    const uint16_t *Xt;       // [Tp / 32, K, 32] bf16: X in 32-token steps (transpose_pad_tile's order), tokens padded with zeros to Tp
+    const uint16_t *dYt;      // [Tp / 32, N, 32] bf16, dY likewise
     const uint32_t *packed;   // packed codes of the layer
     const uint8_t *z0;        // [N, G]
     const float *dz;          // [N, G] or NULL
     float *pc;                // [N, K / 64] out: sum over each 64-feature chunk of dW[i,k] (Q[i,k] - z[i,g(k)])
     int N, K, Tp;             // Tp % 64 == 0
     int gsz, G;               // group size (multiple of 64) and groups per channel
-    int tiles_f, tiles_c;     // ceil(K / 256), ceil(N / 256)
+    int tiles_f, tiles_c;     // K / 128, ceil(N / 256)
 };
 hipError_t launch_transpose_pad(const uint16_t *src, int T, int C, int Tp, uint16_t *dst, hipStream_t stream);
 hipError_t launch_dw(int bits, const DwArgs &a, hipStream_t stream);

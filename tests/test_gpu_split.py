@@ -202,3 +202,24 @@ def test_zero_point_gradient_beside_the_others(gpu, oracle, bits, N, K, T):
     _, g2 = layer.bwd(X, dY, ds)
     _, g3, _ = layer.bwd_z(X, dY, ds, None)
     assert (gpu.to_host(g2) == gpu.to_host(g3)).all()
+
+
+@pytest.mark.parametrize("bits,N,K,group,T", [
+    (4, 128, 128, 64, 17), (3, 384, 1152, 64, 65), (4, 640, 2176, 128, 129), (3, 256, 384, 192, 577), (4, 2432, 1024, 64, 320),
+])
+def test_token_contraction_tiles(gpu, oracle, bits, N, K, group, T):
+    """Group-wise scale gradient contracted over tokens: half a channel tile, an odd one, one feature tile, strips of eight
+    and the one past them, the shortest loop, and numbers of steps around the ring's depth."""
+    print("token contraction bits=%d N=%d K=%d g=%d T=%d" % (bits, N, K, group, T), flush=True)
+    seed = 75000 + bits * 1000 + N + K + T
+    W = synth.normal_f32(seed, (N, K), 0.02)
+    X, dY = synth.normal_bf16(seed + 1, (T, K), 1.0), synth.normal_bf16(seed + 2, (T, N), 1.0)
+    layer = gpu.GpuLayer(W, bits, group)
+    codes, s0, z0 = oracle.quantize(W, bits, group)
+    dz = synth.normal_f32(seed + 3, s0.shape, 0.5)
+    _, gref, _ = oracle.bwd(codes, s0, None, z0, X, dY, group)
+    _, g = layer.bwd(X, dY, want_dX=False)
+    gpu.assert_scale_grad_close(gpu.to_host(g), gref)
+    _, gz, _ = layer.bwd_z(X, dY, None, dz)
+    _, gzref, _ = oracle.bwd_z(codes, s0, None, z0, dz, X, dY, group)
+    gpu.assert_scale_grad_close(gpu.to_host(gz), gzref)
