@@ -606,10 +606,7 @@ static peqa_status bwd_impl(const peqa_layout *L, const uint32_t *packed, const 
         }
         if (d_ds && by_tokens) {
             float *pc = reinterpret_cast<float *>(ws + w.pc);
-            if (!tp_in_dx) {
-                if (peqa::launch_transpose_pad(X, T, K, Tp, xt, s) != hipSuccess) return PEQA_ERR_DEVICE;
-                if (peqa::launch_transpose_pad(dY, T, N, Tp, dyt, s) != hipSuccess) return PEQA_ERR_DEVICE;
-            }
+            if (!tp_in_dx && peqa::launch_transpose_pad(X, K, xt, dY, N, dyt, T, s) != hipSuccess) return PEQA_ERR_DEVICE;
             peqa::DwArgs a{};
             a.Xt = xt; a.dYt = dyt; a.packed = packed; a.z0 = z0; a.dz = dz; a.pc = pc;
             a.N = N; a.K = K; a.Tp = Tp; a.gsz = L->group_size; a.G = G;

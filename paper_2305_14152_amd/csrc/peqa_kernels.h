@@ -151,7 +151,9 @@ struct DwArgs {
     int gsz, G;               // group size (multiple of 64) and groups per channel
     int tiles_f, tiles_c;     // K / 128, ceil(N / 256)
 };
-hipError_t launch_transpose_pad(const uint16_t *src, int T, int C, int Tp, uint16_t *dst, hipStream_t stream);
+// X [T, K] -> xt, dY [T, N] -> dyt
+hipError_t launch_transpose_pad(const uint16_t *X, int K, uint16_t *xt, const uint16_t *dY, int N, uint16_t *dyt, int T,
+                                hipStream_t stream);
 hipError_t launch_dw(int bits, const DwArgs &a, hipStream_t stream);
 hipError_t launch_chunk_reduce(const float *pc, size_t n, int per, float *d_ds, hipStream_t stream);
 // The token contractions of up to DW_MAX_JOBS layers in one launch, and the sums of their chunks in another.
