@@ -49,7 +49,8 @@
  * contraction), contractions are split along their length into pieces whose fp32 sums meet in the workspace.  The size
  * queries include that room.  A workspace that has room for everything but the pieces (what the queries return while
  * PEQA_OPT_GEMM_WAVES or PEQA_OPT_BWD_PAIR forces a form) is served too, with whole contractions: the same products
- * in another order.  For a given shape, T and workspace size results are always the same bits.
+ * in another order; so is, at T <= 16, one that holds the partial sums of the fewest slices the layers need, with those.
+ * For a given shape, T and workspace size results are always the same bits.
  */
 #ifndef PEQA_H
 #define PEQA_H
@@ -174,8 +175,8 @@ peqa_status peqa_linear_fwd(const peqa_layout *L, const uint32_t *packed, const 
  * result bit for bit as peqa_linear_fwd; the scratch a forward needs (row sums of X, the group table, or the
  * partial sums of the T <= 16 path) lives in an array of PEQA_STATIC_SCRATCH_BYTES that is part of the library's
  * device image (every GPU the library runs on holds its own copy until the process ends).  The call allocates
- * nothing and frees nothing.  A forward that needs more scratch than that (peqa_workspace_bytes(L, T,
- * PEQA_OP_FWD) > PEQA_STATIC_SCRATCH_BYTES) is refused with PEQA_ERR_WORKSPACE before anything is enqueued.
+ * nothing and frees nothing.  A forward that needs more scratch than that even with whole contractions (see Workspaces)
+ * is refused with PEQA_ERR_WORKSPACE before anything is enqueued.
  * All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (two streams, two
  * threads) race on it; calls on one stream are ordered and safe.  Nothing in the array needs to start at zero.
  * The array's device address is looked up once per device, at the first call on that device (not a stream

@@ -20,7 +20,7 @@
 // two workgroups (about 640 of 1024 cycles of matrix instructions), where one workgroup of 256 x 256 with both operands
 // in LDS moved 128 KB and had nothing to run at its barrier: at T = 2048 the launch of a 13B block's
 // layers (3 bits, groups of 128) took 1150-1230 us in that form and takes 1035, a 13824 x 5120 layer 316 and 253 us with
-// the copies, 4096 x 11008 with groups of 64 at T = 500 72 and 61 us.  (Patches of 4 x 16 or 16 x 4 tiles, the DMAs in the
+// the copies, 11008 x 4096 with groups of 64 at T = 500 72 and 61 us.  (Patches of 4 x 16 or 16 x 4 tiles, the DMAs in the
 // middle of the step, feature reads spread over the whole step: within 1 %.)
 // The epilogue takes each lane's codes from a copy of the tile's packed words that the first DMAs brought into LDS, at
 // word positions and shifts worked out once per lane, forms sum dW Q - z sum dW over each chunk of 64 features (every

@@ -191,7 +191,7 @@ __global__ __launch_bounds__(256) void group_table_multi_entry_kernel(GroupTable
 // scale_dy_rows (peqa_device.h) for every block of SDY_ROWS token rows.  Workgroups past the last row block do
 // independent jobs of the same backward: the row sums of X for the scale gradient that follows (rs = NULL: none), or the
 // fixed-order sum of the scale-gradient partials (n_red = 0: none).  A launch saved is 3 us of host time and 1 to 3 us
-// of the GPU's: a 256 x 256 layer's step at T = 512, all of it launches, went from 36.2 to 31.6 us with the row sums here.
+// of the GPU's: a 256 x 256 layer's step at T = 64, all of it launches, went from 36.2 to 31.6 us with the row sums here.
 __global__ __launch_bounds__(256) void scale_dy_kernel(const uint16_t *__restrict__ dY, const float *__restrict__ s0,
                                                         const float *__restrict__ ds, const uint8_t *__restrict__ z0,
                                                         const float *__restrict__ dz, int T, int N,
