@@ -608,11 +608,13 @@ static peqa_status bwd_impl(const peqa_layout *L, const uint32_t *packed, const 
             float *pc = reinterpret_cast<float *>(ws + w.pc);
             if (!tp_in_dx && peqa::launch_transpose_pad(X, K, xt, dY, N, dyt, T, s) != hipSuccess) return PEQA_ERR_DEVICE;
             peqa::DwArgs a{};
-            a.Xt = xt; a.dYt = dyt; a.packed = packed; a.z0 = z0; a.dz = dz; a.pc = pc;
+            a.Xt = xt; a.dYt = dyt; a.packed = packed; a.z0 = z0; a.dz = dz;
+            const bool whole = peqa::dw_whole_groups(L->group_size);
+            a.pc = whole ? d_ds : pc;
             a.N = N; a.K = K; a.Tp = Tp; a.gsz = L->group_size; a.G = G;
             a.tiles_f = K / 128; a.tiles_c = (N + 255) / 256;
             if (peqa::launch_dw(L->bits, a, s) != hipSuccess) return PEQA_ERR_DEVICE;
-            if (peqa::launch_chunk_reduce(pc, (size_t)N * G, L->group_size / 64, d_ds, s) != hipSuccess)
+            if (!whole && peqa::launch_chunk_reduce(pc, (size_t)N * G, L->group_size / 64, d_ds, s) != hipSuccess)
                 return PEQA_ERR_DEVICE;
         } else if (d_ds) {
             float *partial = reinterpret_cast<float *>(ws + w.partial);

@@ -446,7 +446,7 @@ peqa_status peqa_block_bwd(int32_t n, const peqa_block_item *items, int32_t T, v
             t.tile_end = tp_tiles;
             peqa::DwArgs &a = dw.job[dw.n_jobs];
             a.Xt = xt_of[xi[j]]; a.dYt = dyt; a.packed = it.packed; a.z0 = it.z0;
-            a.pc = reinterpret_cast<float *>(ws + w.pc[j]);
+            a.pc = peqa::dw_whole_groups(it.layout.group_size) ? it.d_ds : reinterpret_cast<float *>(ws + w.pc[j]);
             a.N = N; a.K = K; a.Tp = Tp; a.gsz = it.layout.group_size; a.G = G;
             a.tiles_f = K / 128; a.tiles_c = (N + 255) / 256;
             dw.d_ds[dw.n_jobs++] = it.d_ds;

@@ -146,7 +146,8 @@ struct DwArgs {
     const uint32_t *packed;   // packed codes of the layer
     const uint8_t *z0;        // [N, G]
     const float *dz;          // [N, G] or NULL
-    float *pc;                // [N, K / 64] out: sum over each 64-feature chunk of dW[i,k] (Q[i,k] - z[i,g(k)])
+    float *pc;                // out: sums of dW[i,k] (Q[i,k] - z[i,g(k)]) over each 64-feature chunk [N, K / 64], or, if
+                              // dw_whole_groups(gsz), over each group [N, G]: d_ds itself
     int N, K, Tp;             // Tp % 64 == 0
     int gsz, G;               // group size (multiple of 64) and groups per channel
     int tiles_f, tiles_c;     // K / 128, ceil(N / 256)
@@ -154,6 +155,8 @@ struct DwArgs {
 // X [T, K] -> xt, dY [T, N] -> dyt
 hipError_t launch_transpose_pad(const uint16_t *X, int K, uint16_t *xt, const uint16_t *dY, int N, uint16_t *dyt, int T,
                                 hipStream_t stream);
+// groups of 64 or 128 features lie within one tile of 128: no chunk sums to add up
+constexpr bool dw_whole_groups(int gsz) { return gsz <= 128; }
 hipError_t launch_dw(int bits, const DwArgs &a, hipStream_t stream);
 hipError_t launch_chunk_reduce(const float *pc, size_t n, int per, float *d_ds, hipStream_t stream);
 // The token contractions of up to DW_MAX_JOBS layers in one launch, and the sums of their chunks in another.

@@ -206,6 +206,7 @@ def test_zero_point_gradient_beside_the_others(gpu, oracle, bits, N, K, T):
 
 @pytest.mark.parametrize("bits,N,K,group,T", [
     (4, 128, 128, 64, 17), (3, 384, 1152, 64, 65), (4, 640, 2176, 128, 129), (3, 256, 384, 192, 577), (4, 2432, 1024, 64, 320),
+    (3, 384, 1280, 128, 40), (4, 256, 1024, 256, 96),
 ])
 def test_token_contraction_tiles(gpu, oracle, bits, N, K, group, T):
     """Group-wise scale gradient contracted over tokens: half a channel tile, an odd one, one feature tile, strips of eight
