@@ -1,7 +1,10 @@
 """Builds libpeqa_hip.so (the C-ABI library) in-tree with hipcc for gfx950."""
 import os
+import re
+import shutil
 import subprocess
 import sys
+import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -30,6 +33,73 @@ def check_no_scratch(remarks):
             if size > 0 and any(k in name for k in NO_SCRATCH):
                 bad.append("%s uses %d bytes of scratch per lane" % (name, size))
     return bad
+
+
+# Wait states that gfx950 wants between a vector instruction and a matrix instruction that reads a register it wrote.  The
+# compiler keeps them for what it emits itself; a write in inline assembly is unknown to it, so the built code is looked at.
+MATRIX_READ_WAIT = 2
+_REGISTERS = re.compile(r"\b([va])(?:\[(\d+):(\d+)\]|(\d+)\b)")
+_TARGET = re.compile(r"<(\S+?)(?:\+0x([0-9a-f]+))?>\s*$")
+
+
+def _registers(operand):
+    found = set()
+    for kind, lo, hi, one in _REGISTERS.findall(operand):
+        found.update((kind, i) for i in range(int(lo or one), int(hi or one) + 1))
+    return found
+
+
+def early_matrix_reads(listing):
+    """Matrix instructions of a disassembly (llvm-objdump -d) that read a register fewer than MATRIX_READ_WAIT wait states
+    after a vector instruction wrote it, on any path into them: one line of text each."""
+    code, entry, function = [], {}, None                   # code: (function, address, mnemonic, operands, branch target)
+    for line in listing.splitlines():
+        label = re.match(r"([0-9a-f]+) <(.+)>:$", line)
+        if label:
+            function = label.group(2)
+            entry[function] = int(label.group(1), 16)
+        elif "//" in line and function is not None:
+            text, _, tail = line.partition("//")
+            mnemonic, _, operands = text.strip().partition(" ")
+            target = _TARGET.search(tail) if "branch" in mnemonic else None
+            code.append((function, int(tail.split(":")[0], 16), mnemonic, operands.split(","),
+                         target and (target.group(1), int(target.group(2) or "0", 16))))
+    index = {c[1]: i for i, c in enumerate(code)}
+    jumps = {}
+    for i, c in enumerate(code):
+        if c[4]:
+            jumps.setdefault(index[entry[c[4][0]] + c[4][1]], []).append(i)
+    bad = []
+    for i, (function, address, mnemonic, operands, _) in enumerate(code):
+        if not mnemonic.startswith(("v_mfma", "v_smfmac")):
+            continue
+        reads = set().union(*(_registers(o) for o in operands[1:]))
+        front = [(i, 0)]                                   # (instruction, wait states from its end to the matrix instruction)
+        while front:
+            here, waited = front.pop()
+            before = list(jumps.get(here, ()))
+            if here > 0 and code[here - 1][0] == function and code[here - 1][2] not in ("s_branch", "s_endpgm", "s_setpc_b64"):
+                before.append(here - 1)
+            for p in before:
+                _, at, name, ops, _ = code[p]
+                if name.startswith("v_") and not name.startswith(("v_mfma", "v_smfmac")) and _registers(ops[0]) & reads:
+                    bad.append("%s: %s at %x reads what %s at %x wrote, after %d wait states" %
+                               (function, mnemonic, address, name, at, waited))
+                states = waited + (int(ops[0]) + 1 if name == "s_nop" else 1)
+                if states < MATRIX_READ_WAIT:
+                    front.append((p, states))
+    return bad
+
+
+def device_listings(lib):
+    """Disassembly of every code object in a library built here."""
+    objdump = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-objdump")
+    with tempfile.TemporaryDirectory() as tmp:
+        name = os.path.basename(lib)
+        shutil.copy(lib, tmp)
+        subprocess.run([objdump, "--offloading", name], cwd=tmp, check=True, stdout=subprocess.DEVNULL)
+        objects = [f for f in sorted(os.listdir(tmp)) if "amdgcn" in f]
+        return [subprocess.run([objdump, "-d", f], cwd=tmp, check=True, stdout=subprocess.PIPE, text=True).stdout for f in objects]
 
 
 def _quiet(text):
@@ -71,6 +141,10 @@ def build(verbose=False, extra=(), jobs=None):
     r = subprocess.run(link, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + _quiet(r.stdout))
+    early = [b for text in device_listings(LIB) for b in early_matrix_reads(text)]
+    if early:
+        os.remove(LIB)
+        raise RuntimeError("matrix instructions too close behind the vector instructions they depend on:\n" + "\n".join(early))
     out = _quiet(remarks)
     if verbose and out.strip():
         print(out)

@@ -69,49 +69,45 @@ __device__ __forceinline__ float add_pair(uint32_t a, float c)
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a), __builtin_bit_cast(bf16x2, 0x3F803F80u), c, false);
 }
 
-// ((x shifted) & mask) | magic in two VALU ops (one when no shift is needed).  mask rides the
-// constant bus (SGPR), magic a VGPR.  Volatile assembly, shift included, so that the unpacking
-// stays exactly where the caller interleaves it with matrix instructions.
+// ((x >> SH) & mask) | magic (a left shift where SH < 0) in two VALU ops, one when no shift is needed.  mask rides the
+// constant bus (SGPR), magic a VGPR.  PINNED: volatile assembly, shift included, so that the unpacking stays exactly where
+// the caller interleaves it with matrix instructions.  The hardware wants two wait states between a vector write and a matrix
+// instruction that reads the register, and the compiler, which keeps them for every write that it emits itself, does not
+// know of writes in assembly: PINNED is for callers whose matrix instructions are assembly too and a step away.
+template <int SH, bool PINNED>
 __device__ __forceinline__ uint32_t and_or(uint32_t x, uint32_t mask, uint32_t magic)
 {
-    uint32_t d;
-    asm volatile("v_and_or_b32 %0, %1, %2, %3" : "=v"(d) : "v"(x), "s"(mask), "v"(magic));
-    return d;
-}
-__device__ __forceinline__ uint32_t shr_and_or(uint32_t x, uint32_t sh, uint32_t mask, uint32_t magic)
-{
-    uint32_t d;
-    asm volatile("v_lshrrev_b32 %0, %1, %2\n\tv_and_or_b32 %0, %0, %3, %4"
-                 : "=&v"(d) : "n"(sh), "v"(x), "s"(mask), "v"(magic));
-    return d;
-}
-__device__ __forceinline__ uint32_t shl_and_or(uint32_t x, uint32_t sh, uint32_t mask, uint32_t magic)
-{
-    uint32_t d;
-    asm volatile("v_lshlrev_b32 %0, %1, %2\n\tv_and_or_b32 %0, %0, %3, %4"
-                 : "=&v"(d) : "n"(sh), "v"(x), "s"(mask), "v"(magic));
-    return d;
+    if constexpr (!PINNED) {
+        return ((SH >= 0 ? x >> (SH & 31) : x << (-SH & 31)) & mask) | magic;
+    } else {
+        uint32_t d;
+        if constexpr (SH == 0)
+            asm volatile("v_and_or_b32 %0, %1, %2, %3" : "=v"(d) : "v"(x), "s"(mask), "v"(magic));
+        else if constexpr (SH > 0)
+            asm volatile("v_lshrrev_b32 %0, %1, %2\n\tv_and_or_b32 %0, %0, %3, %4"
+                         : "=&v"(d) : "n"(SH), "v"(x), "s"(mask), "v"(magic));
+        else
+            asm volatile("v_lshlrev_b32 %0, %1, %2\n\tv_and_or_b32 %0, %0, %3, %4"
+                         : "=&v"(d) : "n"(-SH), "v"(x), "s"(mask), "v"(magic));
+        return d;
+    }
 }
 
 // Field number F (of width b) of both half-words of v -> pair of (16 + code): bf16, or, with AT = kFieldF16 and the matching
 // magic, fp16.
-template <int BITS, int F, int AT>
+template <int BITS, int F, int AT, bool PINNED>
 __device__ __forceinline__ uint32_t field_pair(uint32_t v, uint32_t magic)
 {
-    constexpr uint32_t mask = field_mask(BITS, AT);
-    constexpr int sh = BITS * F - AT;
-    if constexpr (sh < 0) return shl_and_or(v, -sh, mask, magic);
-    else if constexpr (sh == 0) return and_or(v, mask, magic);
-    else return shr_and_or(v, sh, mask, magic);
+    return and_or<BITS * F - AT, PINNED>(v, field_mask(BITS, AT), magic);
 }
 
 // The 3-bit cell that lives in the spare top bits (15 and 31) of three words.
-template <int AT>
+template <int AT, bool PINNED>
 __device__ __forceinline__ uint32_t spare_pair3(uint32_t v0, uint32_t v1, uint32_t v2, uint32_t magic)
 {
-    uint32_t t = shr_and_or(v0, 15 - AT, 0x00010001u << AT, magic);
-    t = shr_and_or(v1, 14 - AT, 0x00020002u << AT, t);
-    return shr_and_or(v2, 13 - AT, 0x00040004u << AT, t);
+    uint32_t t = and_or<15 - AT, PINNED>(v0, 0x00010001u << AT, magic);
+    t = and_or<14 - AT, PINNED>(v1, 0x00020002u << AT, t);
+    return and_or<13 - AT, PINNED>(v2, 0x00040004u << AT, t);
 }
 
 // ---------------------------------------------------------------------------------
@@ -125,7 +121,7 @@ __device__ __forceinline__ uint32_t spare_pair3(uint32_t v0, uint32_t v1, uint32
 // so that every lane runs the same shifts and masks.  Fragment I belongs to column 4 c + I of the wave's 64, or, by parity,
 // 8 (c / 2) + 2 I + c % 2.
 // ---------------------------------------------------------------------------------
-template <int BITS, bool ALONG_CH, int AT = kFieldBf16>
+template <int BITS, bool ALONG_CH, int AT = kFieldBf16, bool PINNED = true>
 struct HalfBlockUnpacker {
     static constexpr int WORDS = ALONG_CH ? 2 * BITS : BITS;      // words a lane reads
     static constexpr bool BY_PARITY = ALONG_CH || BITS == 3;
@@ -146,12 +142,12 @@ struct HalfBlockUnpacker {
     __device__ __forceinline__ uint32_t frag_reg(uint32_t magic) const
     {
         if constexpr (BITS == 4) {
-            if constexpr (ALONG_CH) return field_pair<4, I, AT>(w[J], magic);
-            else return field_pair<4, J, AT>(w[I], magic);
+            if constexpr (ALONG_CH) return field_pair<4, I, AT, PINNED>(w[J], magic);
+            else return field_pair<4, J, AT, PINNED>(w[I], magic);
         } else {
             constexpr int u = ALONG_CH ? 4 * J + I : 4 * I + J;
-            if constexpr (u < 15) return field_pair<3, u % 5, AT>(w[u / 5], magic);
-            else return spare_pair3<AT>(w[0], w[1], w[2], magic);
+            if constexpr (u < 15) return field_pair<3, u % 5, AT, PINNED>(w[u / 5], magic);
+            else return spare_pair3<AT, PINNED>(w[0], w[1], w[2], magic);
         }
     }
 };

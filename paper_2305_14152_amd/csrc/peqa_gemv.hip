@@ -70,7 +70,8 @@ __global__ __launch_bounds__(WAVES * 64, H == 2 ? 2 : 3) void gemv_kernel(GemvAr
     // then the scale tile: scale s0 + ds and zero-point (16 + z0 + dz as fp32, or z0 as stored) of [group of the slice][channel]
     // (rows padded: the transposing writes of consecutive groups of one channel then fall into different banks)
     extern __shared__ __align__(16) uint8_t stage[];
-    typedef HalfBlockUnpacker<BITS, false> Unpacker;
+    // (not pinned: the compiler places the unpacking and the matrix instructions, and the wait states between them)
+    typedef HalfBlockUnpacker<BITS, false, kFieldBf16, false> Unpacker;
     constexpr int WORDS = Unpacker::WORDS;
     constexpr int NBUF = GV_NBUF, ROUND = gv_round_bytes(H, NX), NDMA = 2 * H + NX, THREADS = WAVES * 64;
     constexpr int GV_C = 64 * H, GV_SROW = gv_srow(H), GV_ZROW = gv_zrow(H);
@@ -106,7 +107,8 @@ __global__ __launch_bounds__(WAVES * 64, H == 2 ? 2 : 3) void gemv_kernel(GemvAr
     const int nrounds = rbeg + (int)((uint32_t)((wave + 1) * (rend - rbeg)) / (uint32_t)WAVES) - wr0;
     const int g_lo = (uint32_t)rbeg / (uint32_t)chunk_rounds;     // first scale group this workgroup touches
 
-    const uint32_t magic = kMagic;
+    uint32_t magic = kMagic;
+    asm("" : "+v"(magic));                                      // in a register: as a constant, and-or takes two instructions
     const u32x4 ones = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
     // A step of the wave (64 channels x 32 features) is half of a 128-channel tile of TILE bytes: contiguous; tiles follow
     // each other along the features.
