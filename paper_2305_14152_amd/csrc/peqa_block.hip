@@ -326,7 +326,7 @@ peqa_status peqa_block_bwd(int32_t n, const peqa_block_item *items, int32_t T, v
     const int bits = items[0].layout.bits;
 
     // ---- per-channel items.  Row sums of the inputs whose scale gradient is wanted: the caller's (kept from the
-    // forward), else taken here, all in one launch.
+    // forward, which stores none at T <= 16), else taken here, all in one launch.
     const float *rs[PEQA_MAX_BLOCK] = {nullptr};
     {
         peqa::RowsumMulti r{};
@@ -338,7 +338,7 @@ peqa_status peqa_block_bwd(int32_t n, const peqa_block_item *items, int32_t T, v
             for (int j = 0; j < n; ++j)
                 if (xi[j] == i && !grouped(&items[j].layout)) {
                     wanted = wanted || (items[j].d_ds != nullptr && w.split_dds[j] == 1);   // pieces take their own
-                    if (items[j].row_sums) have = items[j].row_sums;
+                    if (items[j].row_sums && T > GEMV_MAX_T) have = items[j].row_sums;
                     if (!dst) dst = reinterpret_cast<float *>(ws + w.rs[j]);
                 }
             if (have || !wanted) { rs[i] = have; continue; }

@@ -114,6 +114,47 @@ def test_block_backward_parity(gpu, oracle, bits, group, shapes, T):
             gpu.assert_scale_grad_close(gpu.to_host(d["d_ds"]), gref)
 
 
+@pytest.mark.parametrize("bits", [4, 3])
+@pytest.mark.parametrize("T", [1, 7, 16])
+def test_block_step_of_few_tokens_with_row_sums(gpu, oracle, bits, T):
+    """At T <= 16 the forward stores no row sums, so the backward must not read the items' arrays, whatever they hold.
+    Items short enough to stay whole and one that is split; the workspace asked for and the smallest."""
+    import torch
+    from paper_2305_14152_amd import peqa
+    print("few tokens with row sums bits=%d T=%d" % (bits, T), flush=True)
+    seed = 34000 + 100 * bits + T
+    X = synth.normal_bf16(seed, (T, 512), 1.0)
+    members = [Member(gpu, oracle, seed + 50, bits, 256, 512, 0, T, X=X), Member(gpu, oracle, seed + 100, bits, 384, 512, 0, T, X=X),
+               Member(gpu, oracle, seed + 150, bits, 128, 8192, 0, T)]
+    Xd = gpu.to_dev(X)
+    rs = [torch.full((T, 2), v, dtype=torch.float32, device="cuda") for v in (float("nan"), 1e30)]
+    dicts = []
+    for j, m in enumerate(members):
+        dicts.append(dict(L=m.layer.L, packed=m.layer.packed, s0=m.layer.s0, z0=m.layer.z0, ds=m.dsd,
+                          X=Xd if j < 2 else gpu.to_dev(m.X), dY=gpu.to_dev(m.dY), row_sums=rs[j // 2],
+                          Y=torch.zeros((T, m.N), dtype=torch.int16, device="cuda"),
+                          dX=torch.zeros((T, m.K), dtype=torch.int16, device="cuda"),
+                          d_ds=torch.zeros(m.s0.shape, dtype=torch.float32, device="cuda")))
+    items = peqa.block_items(dicts)
+    nbf, nbb = (peqa.block_workspace_bytes(items, T, op) for op in (peqa.PEQA_OP_FWD, peqa.PEQA_OP_BWD))
+    peqa.set_option(peqa.PEQA_OPT_GEMM_WAVES, 4)           # forced forms are whole contractions: the least a call needs
+    try:
+        least = peqa.block_workspace_bytes(items, T, peqa.PEQA_OP_BWD)
+    finally:
+        peqa.set_option(peqa.PEQA_OPT_GEMM_WAVES, 0)
+    assert nbb > least
+    ws = torch.empty(max(nbf, nbb), dtype=torch.uint8, device="cuda")
+    peqa.block_fwd(items, T, ws, nbf)
+    for size in (nbb, least):
+        peqa.block_bwd(items, T, ws, size)
+        torch.cuda.synchronize()
+        for m, d in zip(members, dicts):
+            dXref, gref, _ = oracle.bwd(m.codes, m.s0, m.ds, m.z0, m.X, m.dY, 0)
+            assert np.abs(gpu.bf16_dev_to_f64(d["dX"]) - dXref).max() <= Y_TOL * np.abs(dXref).max()
+            gpu.assert_scale_grad_close(gpu.to_host(d["d_ds"]), gref)
+            d["dX"].zero_(), d["d_ds"].zero_()
+
+
 def test_block_skips_and_errors(gpu, oracle):
     """NULL dX / d_ds per item are skipped; mixed bit widths and missing workspace are refused."""
     import ctypes
