@@ -239,22 +239,27 @@ peqa_status peqa_block_fwd(int32_t n, const peqa_block_item *items, int32_t T, v
     const uint16_t *xs[PEQA_MAX_BLOCK];
     const int nx = distinct_inputs(n, items, xi, xs, ks);
     const int bits = items[0].layout.bits;
-    // row sums of every distinct input of the per-channel items: one launch
+    // row sums of every distinct input of the per-channel items, into each array that its items bring: one launch
     const float *rs[PEQA_MAX_BLOCK] = {nullptr};
     {
         peqa::RowsumMulti r{};
         int nr = 0;
         for (int i = 0; i < nx; ++i) {
-            float *dst = nullptr;
+            const int first = nr;                              // this input's entries (at most one per item in all)
+            auto take = [&](float *dst) {
+                for (int e = first; e < nr; ++e)
+                    if (r.rs[e] == dst) return;
+                r.X[nr] = xs[i]; r.K[nr] = ks[i]; r.rs[nr++] = dst;
+            };
+            float *own = nullptr;
             for (int j = 0; j < n; ++j) {
                 if (xi[j] != i || grouped(&items[j].layout)) continue;
-                if (!dst) dst = reinterpret_cast<float *>(ws + w.rs[j]);
-                if (items[j].row_sums) { dst = items[j].row_sums; break; }
+                if (!own) own = reinterpret_cast<float *>(ws + w.rs[j]);
+                if (items[j].row_sums) take(items[j].row_sums);
             }
-            if (!dst) continue;
-            r.X[nr] = xs[i]; r.K[nr] = ks[i]; r.rs[nr] = dst;
-            ++nr;
-            rs[i] = dst;
+            if (!own) continue;
+            if (nr == first) take(own);
+            rs[i] = r.rs[first];
         }
         if (nr > 0) {
             for (int i = nr; i < peqa::ROWSUM_MAX; ++i) { r.X[i] = r.X[nr - 1]; r.K[i] = r.K[nr - 1]; r.rs[i] = r.rs[nr - 1]; }

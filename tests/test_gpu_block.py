@@ -155,6 +155,38 @@ def test_block_step_of_few_tokens_with_row_sums(gpu, oracle, bits, T):
             d["dX"].zero_(), d["d_ds"].zero_()
 
 
+def test_block_fills_every_row_sums_array(gpu, oracle):
+    """Items that share X may share one array of row sums or bring their own: each is filled, and a backward over any of
+    the items reads sums that are there."""
+    import torch
+    from paper_2305_14152_amd import peqa
+    T = 40
+    X, X2 = synth.normal_bf16(34900, (T, 512), 1.0), synth.normal_bf16(34901, (T, 256), 1.0)
+    members = [Member(gpu, oracle, 34910 + 50 * j, 4, N, K, 0, T, X=x)
+               for j, (N, K, x) in enumerate([(256, 512, X), (128, 512, X), (384, 512, X), (128, 256, X2), (256, 512, X)])]
+    xd = {id(X): gpu.to_dev(X), id(X2): gpu.to_dev(X2)}
+    rs = [torch.full((T, 2), float("nan"), dtype=torch.float32, device="cuda") for _ in range(3)]
+    own = [None, rs[0], rs[1], rs[2], rs[0]]               # none, its own, another, another input's, the second item's
+    dicts = [dict(L=m.layer.L, packed=m.layer.packed, s0=m.layer.s0, z0=m.layer.z0, ds=m.dsd, X=xd[id(m.X)], dY=gpu.to_dev(m.dY),
+                  Y=torch.zeros((T, m.N), dtype=torch.int16, device="cuda"), row_sums=r,
+                  d_ds=torch.zeros(m.s0.shape, dtype=torch.float32, device="cuda")) for m, r in zip(members, own)]
+    items = peqa.block_items(dicts)
+    nb = max(peqa.block_workspace_bytes(items, T, op) for op in (peqa.PEQA_OP_FWD, peqa.PEQA_OP_BWD))
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    peqa.block_fwd(items, T, ws, nb)
+    for x, K, r in ((X, 512, rs[0]), (X, 512, rs[1]), (X2, 256, rs[2])):
+        want = torch.empty((T, 2), dtype=torch.float32, device="cuda")
+        peqa.row_sums(xd[id(x)], T, K, want)
+        assert torch.equal(r, want)
+    for some in (dicts, dicts[1:3], dicts[2:3]):
+        peqa.block_bwd(peqa.block_items(some), T, ws, nb)
+        for d in some:
+            m = members[next(j for j, e in enumerate(dicts) if e is d)]
+            _, gref, _ = oracle.bwd(m.codes, m.s0, m.ds, m.z0, m.X, m.dY, 0, want_dX=False)
+            gpu.assert_scale_grad_close(gpu.to_host(d["d_ds"]), gref)
+            d["d_ds"].zero_()
+
+
 def test_block_skips_and_errors(gpu, oracle):
     """NULL dX / d_ds per item are skipped; mixed bit widths and missing workspace are refused."""
     import ctypes
