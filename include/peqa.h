@@ -175,8 +175,9 @@ peqa_status peqa_linear_fwd(const peqa_layout *L, const uint32_t *packed, const 
  * result bit for bit as peqa_linear_fwd; the scratch a forward needs (row sums of X, the group table, or the
  * partial sums of the T <= 16 path) lives in an array of PEQA_STATIC_SCRATCH_BYTES that is part of the library's
  * device image (every GPU the library runs on holds its own copy until the process ends).  The call allocates
- * nothing and frees nothing.  A forward that needs more scratch than that even with whole contractions (see Workspaces)
- * is refused with PEQA_ERR_WORKSPACE before anything is enqueued.
+ * nothing and frees nothing.  A forward that needs more scratch than that even with whole contractions or the fewest
+ * slices (see Workspaces) is refused with PEQA_ERR_WORKSPACE before anything is enqueued; one that does not is planned
+ * within it by both calls.
  * All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (two streams, two
  * threads) race on it; calls on one stream are ordered and safe.  Nothing in the array needs to start at zero.
  * The array's device address is looked up once per device, at the first call on that device (not a stream

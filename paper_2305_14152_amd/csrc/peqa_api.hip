@@ -25,6 +25,7 @@ struct Workspace {
     int split_y, split_dx, split_dds;      // split_dx, split_dds: of the backward that computes both gradients
     int split_dx_alone;
     size_t acc, acc_dds;
+    size_t gemv_most;                      // T <= 16: the most bytes that the plan's partial sums may take
 };
 
 Workspace carve_whole(const peqa_layout *L, int32_t T, int32_t op)
@@ -58,7 +59,7 @@ Workspace carve_whole(const peqa_layout *L, int32_t T, int32_t op)
     if ((op == PEQA_OP_FWD || op == PEQA_OP_FWD_Z) && T <= PEQA_GEMV_MAX_T) {
         // the fewest slices (with a trained zero-point offset LDS holds fewer groups of a group-wise layer: more slices)
         const GemvItem one{L, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
-        w.partial = off; off += round256(gemv_partial_bytes(1, &one, T, op == PEQA_OP_FWD, true));
+        w.partial = off; off += round256(gemv_partial_bytes(1, &one, T, op == PEQA_OP_FWD, 0));
         if (off == 0) off = 256;                               // a single slice needs none; 0 would read as "invalid"
         w.total = off;
         return w;
@@ -95,10 +96,13 @@ Workspace carve(const peqa_layout *L, int32_t T, int32_t op)
     Workspace w = carve_whole(L, T, op);
     w.min_total = w.total;
     w.split_y = w.split_dx = w.split_dds = w.split_dx_alone = 1;
+    w.gemv_most = GEMV_ANY;
     const bool fwd = op == PEQA_OP_FWD || op == PEQA_OP_FWD_Z || op == PEQA_OP_FWD_KEEP;
     if (fwd && op != PEQA_OP_FWD_KEEP && T <= PEQA_GEMV_MAX_T) {
         const GemvItem one{L, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
-        const size_t planned = w.partial + round256(gemv_partial_bytes(1, &one, T, op == PEQA_OP_FWD, false));
+        // as for T > 16 below: a forward that peqa_linear_fwd_static takes with the fewest slices is planned for its scratch
+        if (op == PEQA_OP_FWD && w.total <= (size_t)PEQA_STATIC_SCRATCH_BYTES) w.gemv_most = PEQA_STATIC_SCRATCH_BYTES;
+        const size_t planned = w.partial + round256(gemv_partial_bytes(1, &one, T, op == PEQA_OP_FWD, w.gemv_most));
         w.total = planned > w.total ? planned : w.total;
         return w;
     }
@@ -307,7 +311,7 @@ static peqa_status fwd_impl(const peqa_layout *L, const uint32_t *packed, const 
     const int N = L->n_out, K = L->k_in, ksplit = split_point(K);
     if (T <= PEQA_GEMV_MAX_T) {
         const GemvItem item{L, packed, s0, ds, z0, dz, X, Y};
-        return gemv_forward(1, &item, T, reinterpret_cast<float *>(ws + w.partial), workspace_bytes - w.partial, s);
+        return gemv_forward(1, &item, T, w.gemv_most, reinterpret_cast<float *>(ws + w.partial), workspace_bytes - w.partial, s);
     }
     if (grouped(L)) {
         float *sb = reinterpret_cast<float *>(ws + w.table);
@@ -458,7 +462,7 @@ size_t peqa_workspace_bytes_fused(int32_t n, const peqa_fwd_item *items, int32_t
     if (T <= PEQA_GEMV_MAX_T) {
         GemvItem gi[PEQA_MAX_FUSED];
         for (int j = 0; j < n; ++j) gi[j] = GemvItem{&items[j].layout, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
-        const size_t b = round256(gemv_partial_bytes(n, gi, T, true, false));
+        const size_t b = round256(gemv_partial_bytes(n, gi, T, true, GEMV_ANY));
         return b ? b : 256;
     }
     size_t need = 0;                                       // layer by layer: the largest single need
@@ -488,7 +492,7 @@ static peqa_status fwd_fused_impl(int32_t n, const peqa_fwd_item *items, const u
     if (T <= PEQA_GEMV_MAX_T) {
         GemvItem gi[PEQA_MAX_FUSED];
         for (int j = 0; j < n; ++j) gi[j] = GemvItem{&items[j].layout, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
-        need = round256(gemv_partial_bytes(n, gi, T, true, true));
+        need = round256(gemv_partial_bytes(n, gi, T, true, 0));
         need = need ? need : 256;
     } else {
         for (int j = 0; j < n; ++j) {
@@ -502,7 +506,7 @@ static peqa_status fwd_fused_impl(int32_t n, const peqa_fwd_item *items, const u
         GemvItem gi[PEQA_MAX_FUSED];
         for (int j = 0; j < n; ++j)
             gi[j] = GemvItem{&items[j].layout, items[j].packed, items[j].s0, items[j].ds, items[j].z0, nullptr, X, items[j].Y};
-        return gemv_forward(n, gi, T, static_cast<float *>(workspace), workspace_bytes, static_cast<hipStream_t>(stream));
+        return gemv_forward(n, gi, T, GEMV_ANY, static_cast<float *>(workspace), workspace_bytes, static_cast<hipStream_t>(stream));
     }
     // the tiled contraction runs the layers one by one; per-channel layers share the row sums of X
     if (!grouped(&items[0].layout)) {
@@ -861,7 +865,7 @@ peqa_status peqa_scale_update_multi(int32_t n, const peqa_update_item *items, co
 namespace peqa {
 namespace host {
 
-peqa::GemvForm gemv_slicing(int n, const GemvItem *items, int32_t T, bool zbyte, bool least, int *S)
+static peqa::GemvForm gemv_slicing(int n, const GemvItem *items, int32_t T, bool zbyte, size_t most, int *S, size_t *bytes)
 {
     int N[GEMV_MAX_LAYERS], K[GEMV_MAX_LAYERS], chunk[GEMV_MAX_LAYERS];
     for (int j = 0; j < n; ++j) {
@@ -869,25 +873,27 @@ peqa::GemvForm gemv_slicing(int n, const GemvItem *items, int32_t T, bool zbyte,
         K[j] = items[j].L->k_in;
         chunk[j] = items[j].L->group_size > 0 ? items[j].L->group_size : items[j].L->k_in;
     }
-    return gemv_plan(n, N, K, chunk, items[0].L->bits, T, zbyte, least, S);
+    const peqa::GemvForm form = gemv_plan(n, N, K, chunk, items[0].L->bits, T, zbyte, most, S);
+    *bytes = gemv_partials(n, N, T, S);
+    return form;
 }
 
-size_t gemv_partial_bytes(int n, const GemvItem *items, int32_t T, bool zbyte, bool least)
+size_t gemv_partial_bytes(int n, const GemvItem *items, int32_t T, bool zbyte, size_t most)
 {
     int S[GEMV_MAX_LAYERS];
-    (void)gemv_slicing(n, items, T, zbyte, least, S);
     size_t bytes = 0;
-    for (int j = 0; j < n; ++j)
-        if (S[j] > 1) bytes += (size_t)S[j] * (size_t)T * (size_t)items[j].L->n_out * sizeof(float);
+    (void)gemv_slicing(n, items, T, zbyte, most, S, &bytes);
     return bytes;
 }
 
-peqa_status gemv_forward(int n, const GemvItem *items, int32_t T, float *partial, size_t partial_bytes, hipStream_t s)
+peqa_status gemv_forward(int n, const GemvItem *items, int32_t T, size_t most, float *partial, size_t partial_bytes, hipStream_t s)
 {
     int S[GEMV_MAX_LAYERS];
+    size_t bytes = 0;
     bool zbyte = true;                                         // the launch takes the same decision from the same pointers
     for (int j = 0; j < n; ++j) zbyte = zbyte && items[j].dz == nullptr;
-    const GemvForm form = gemv_slicing(n, items, T, zbyte, gemv_partial_bytes(n, items, T, zbyte, false) > partial_bytes, S);
+    peqa::GemvForm form = gemv_slicing(n, items, T, zbyte, most, S, &bytes);
+    if (bytes > partial_bytes) form = gemv_slicing(n, items, T, zbyte, 0, S, &bytes);
     GemvArgs g{};
     int wgs = 0;
     size_t poff = 0;                                           // in floats

@@ -200,7 +200,7 @@ size_t peqa_block_workspace_bytes(int32_t n, const peqa_block_item *items, int32
     if (op == PEQA_OP_FWD && T <= GEMV_MAX_T) {
         GemvItem gi[PEQA_MAX_BLOCK];
         for (int j = 0; j < n; ++j) gi[j] = GemvItem{&items[j].layout, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
-        const size_t b = round256(gemv_partial_bytes(n, gi, T, true, false));
+        const size_t b = round256(gemv_partial_bytes(n, gi, T, true, GEMV_ANY));
         return b ? b : 256;
     }
     return carve_block(n, items, T, op).total;
@@ -226,10 +226,10 @@ peqa_status peqa_block_fwd(int32_t n, const peqa_block_item *items, int32_t T, v
         for (int j = 0; j < n; ++j)
             gi[j] = GemvItem{&items[j].layout, items[j].packed, items[j].s0, items[j].ds, items[j].z0, nullptr,
                              items[j].X, items[j].Y};
-        const size_t least = round256(gemv_partial_bytes(n, gi, T, true, true));
+        const size_t least = round256(gemv_partial_bytes(n, gi, T, true, 0));
         if (!workspace || workspace_bytes < (least ? least : 256)) return PEQA_ERR_WORKSPACE;
         if (!aligned16(workspace)) return PEQA_ERR_ALIGN;
-        return gemv_forward(n, gi, T, reinterpret_cast<float *>(ws), workspace_bytes, s);
+        return gemv_forward(n, gi, T, GEMV_ANY, reinterpret_cast<float *>(ws), workspace_bytes, s);
     }
 
     BlockSpace w = carve_block(n, items, T, PEQA_OP_FWD);

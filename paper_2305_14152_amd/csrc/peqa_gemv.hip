@@ -370,6 +370,14 @@ static int gv_per_cu(const GemvForm &f, int lds)                   // workgroups
     return by_lds < by_regs ? by_lds : by_regs;
 }
 
+size_t gemv_partials(int n, const int *N, int T, const int *S)
+{
+    size_t bytes = 0;
+    for (int j = 0; j < n; ++j)
+        if (S[j] > 1) bytes += (size_t)S[j] * (size_t)T * (size_t)N[j] * sizeof(float);
+    return bytes;
+}
+
 static int gv_cols(int K, int chunk, int S)                        // most scale groups a slice touches
 {
     const int R = K / 64, cr = chunk / 64;
@@ -392,7 +400,9 @@ static int gv_cols(int K, int chunk, int S)                        // most scale
 // that, 128 channels per workgroup (half of the token rows' traffic and LDS per channel).  us per block at T = 1 / 16, 13B
 // 3-bit g128: 3 slices of the long layer 34.6 / 42.3, 2 slices (not resident) 38.9 / 45.6, 128 channels 35.8 / 38.2.  Launches too large for
 // that take the slicing with the most workgroups per compute unit, as long as the partial sums stay below 4 % of the codes.
-GemvForm gemv_plan(int n, const int *N, const int *K, const int *chunk, int bits, int T, bool zbyte, bool least, int *S)
+//
+// Slicings whose partial sums take more than `most` bytes are left out; where none remains, the fewest slices are taken.
+GemvForm gemv_plan(int n, const int *N, const int *K, const int *chunk, int bits, int T, bool zbyte, size_t most, int *S)
 {
     const int cus = compute_units(), nx = T > 8 ? 2 : 1;
     int tiles = 0, rmax = 0;
@@ -419,19 +429,14 @@ GemvForm gemv_plan(int n, const int *N, const int *K, const int *chunk, int bits
     if (tiles <= cus) {
         const GemvForm f{1, 8};
         slice_all(f, rmax, GV_LDS_MAX);
-        if (!least) {
-            for (int j = 0; j < n; ++j) {
-                const int r = K[j] / 64, s = cus / tiles < r / 32 ? cus / tiles : r / 32;
-                if (r >= 96 && s > S[j]) S[j] = s;
-            }
+        for (int j = 0; j < n; ++j) {
+            const int r = K[j] / 64, s = cus / tiles < r / 32 ? cus / tiles : r / 32;
+            if (r >= 96 && s > S[j]) S[j] = s;
         }
+        if (gemv_partials(n, N, T, S) > most) slice_all(f, rmax, GV_LDS_MAX);
         return f;
     }
     const GemvForm small{1, 4}, wide{2, 4};
-    if (least) {
-        slice_all(small, rmax, GV_LDS_MAX);
-        return small;
-    }
     const double mean = rounds / tiles;
     GemvForm best = small;
     int best_len = rmax, best_per_cu = 0;
@@ -441,6 +446,7 @@ GemvForm gemv_plan(int n, const int *N, const int *K, const int *chunk, int bits
             const int len = (rmax + s - 1) / s;
             if (len > 1.35 * mean && s < 8) continue;
             slice_all(f, len, GV_LDS_MAX / 2);
+            if (gemv_partials(n, N, T, S) > most) continue;
             int wgs = 0;
             double partials = 0.0;
             for (int j = 0; j < n; ++j) {
@@ -455,7 +461,8 @@ GemvForm gemv_plan(int n, const int *N, const int *K, const int *chunk, int bits
             }
         }
     }
-    slice_all(best, best_len, GV_LDS_MAX / 2);
+    if (best_per_cu == 0) slice_all(small, rmax, GV_LDS_MAX);
+    else slice_all(best, best_len, GV_LDS_MAX / 2);
     return best;
 }
 

@@ -210,8 +210,10 @@ struct GemvForm {
     int h, waves;
 };
 // The form, and the slices of every layer (S[0..n)).  zbyte: no layer has a trained zero-point offset, so zero-points are
-// bytes in LDS.  least: the fewest slices that LDS allows, for a workspace that does not hold the partial sums of more.
-GemvForm gemv_plan(int n, const int *N, const int *K, const int *chunk, int bits, int T, bool zbyte, bool least, int *S);
+// bytes in LDS.  most: the most bytes that the partial sums of the slices may take; 0 gives the fewest slices that LDS allows.
+GemvForm gemv_plan(int n, const int *N, const int *K, const int *chunk, int bits, int T, bool zbyte, size_t most, int *S);
+// fp32 partial sums of the layers with S > 1
+size_t gemv_partials(int n, const int *N, int T, const int *S);
 hipError_t launch_gemv(int bits, const GemvForm &f, const GemvArgs &a, hipStream_t stream);
 
 // peqa_small.hip

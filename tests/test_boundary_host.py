@@ -260,3 +260,16 @@ def test_options_are_explicit_and_validated(peqa):
     src = "".join(open(os.path.join(ROOT, "paper_2305_14152_amd", "csrc", f)).read()
                   for f in os.listdir(os.path.join(ROOT, "paper_2305_14152_amd", "csrc")))
     assert "getenv" not in src
+
+
+@pytest.mark.parametrize("N,K,bits,group,T", [
+    (135808, 9216, 3, 64, 16), (144384, 15872, 4, 256, 13), (154624, 26112, 4, 192, 13), (409472, 8192, 4, 256, 10),
+    (4096, 4096, 4, 0, 16), (256, 49152, 3, 0, 5), (184576, 35200, 4, 64, 12), (5504, 4096, 3, 128, 17), (256, 8192, 4, 0, 40),
+])
+def test_static_forward_takes_only_what_runs_alike_in_its_scratch(peqa, N, K, bits, group, T):
+    """What peqa_linear_fwd_static accepts has to run as peqa_linear_fwd does with the workspace it asks for, so that
+    workspace must fit the static scratch: the same slices, the same pieces, the same bits."""
+    L = peqa.layout(N, K, bits, group)
+    refused = peqa.lib().peqa_linear_fwd_static(ctypes.byref(L), None, None, None, None, None, T, None, None)
+    assert refused in (peqa.PEQA_ERR_WORKSPACE, peqa.PEQA_ERR_NULL)     # (the size is looked at before the pointers)
+    assert (refused == peqa.PEQA_ERR_WORKSPACE) == (peqa.workspace_bytes(L, T, peqa.PEQA_OP_FWD) > peqa.STATIC_SCRATCH_BYTES)

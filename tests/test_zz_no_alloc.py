@@ -49,6 +49,28 @@ def test_static_forward_equals_workspace_forward(gpu, oracle, bits, N, K, group,
         assert np.abs(gpu.bf16_dev_to_f64(Y) - Yref).max() <= 2e-2 * np.abs(Yref).max()
 
 
+def test_static_forward_equals_workspace_forward_of_a_large_layer(gpu):
+    """T <= 16, a layer whose slices would be planned past the static scratch (25 MiB of partial sums): both calls plan
+    within it."""
+    import torch
+    from paper_2305_14152_amd import peqa
+    N, K, group, bits, T = 135808, 9216, 64, 3, 16
+    L = peqa.layout(N, K, bits, group)
+    g = torch.Generator(device="cuda").manual_seed(88500)
+    packed = torch.randint(-2 ** 31, 2 ** 31 - 1, (peqa.packed_words(L),), dtype=torch.int32, device="cuda", generator=g)
+    s0 = torch.rand((N, K // group), device="cuda", generator=g) + 0.5
+    z0 = torch.randint(0, 8, (N, K // group), dtype=torch.uint8, device="cuda", generator=g)
+    X = torch.randn((T, K), device="cuda", generator=g).bfloat16().view(torch.int16)
+    Y, want = (torch.zeros((T, N), dtype=torch.int16, device="cuda") for _ in range(2))
+    nb = peqa.workspace_bytes(L, T, peqa.PEQA_OP_FWD)
+    peqa.linear_fwd_static(L, packed, s0, None, z0, X, T, Y)
+    for size in (nb, nb + (32 << 20)):             # more room than asked for changes nothing
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        want.zero_()
+        peqa.linear_fwd(L, packed, s0, None, z0, X, T, want, ws, size)
+        assert torch.equal(Y, want)
+
+
 def test_static_forward_refuses_what_does_not_fit(gpu):
     """A forward whose scratch need exceeds the array is refused before anything runs; bad arguments likewise."""
     import ctypes
