@@ -42,6 +42,7 @@ namespace {
 constexpr int gv_srow(int h) { return 64 * h + 4; }   // padded rows of the scale tile (floats) and of byte zero-points
 constexpr int gv_zrow(int h) { return 64 * h + 8; }
 constexpr int GV_LDS_MAX = 160 * 1024;
+constexpr int GV_SIMD_WAVES = 4;     // waves per SIMD that the registers of every form allow: the plan counts on them
 constexpr int GV_NBUF = 2;           // rounds a wave keeps in flight (three measured the same or slower in every form)
 // One round (64 features) of one wave in LDS: its packed words (2 KB; 1.5 KB of it at 3 bits), then NX KB of token rows
 // (8 rows x 128 B per KB: one DMA when T <= 8, two otherwise).
@@ -64,7 +65,7 @@ __device__ __forceinline__ void gv_wait_vmcnt()
 // H: 64-channel halves of a workgroup.  NX: KB of token rows per round (1: T <= 8, 2: T <= 16).
 // ZBYTE: zero-points are the stored integers (no trained offset dz), kept as bytes in LDS.
 template <int BITS, int H, int WAVES, int NX, bool ZBYTE>
-__global__ __launch_bounds__(WAVES * 64, H == 2 ? 2 : 3) void gemv_kernel(GemvArgs a)
+__global__ __launch_bounds__(WAVES * 64, GV_SIMD_WAVES) void gemv_kernel(GemvArgs a)
 {
     // [wave][NBUF rounds][round], reused as [wave][column tile][row in lane][lane] fp32 (4 KB per wave) for the final sum;
     // then the scale tile: scale s0 + ds and zero-point (16 + z0 + dz as fp32, or z0 as stored) of [group of the slice][channel]
@@ -366,7 +367,7 @@ static int gv_lds_bytes(const GemvForm &f, int nx, bool zbyte, int groups)
 
 static int gv_per_cu(const GemvForm &f, int lds)                   // workgroups a compute unit holds: LDS, registers
 {
-    const int by_regs = f.waves == 8 ? 2 : 4, by_lds = GV_LDS_MAX / lds;
+    const int by_regs = 4 * GV_SIMD_WAVES / f.waves, by_lds = GV_LDS_MAX / lds;
     return by_lds < by_regs ? by_lds : by_regs;
 }
 
