@@ -281,16 +281,17 @@ __global__ __launch_bounds__(256, 2) void dw_multi_kernel(DwMultiArgs m)
     dw_tile<BITS>(a, b - wg0, lds);
 }
 
-// transpose_pad_tile (peqa_device.h) for every 64 x 64 tile of both operands, X [T, K] and dY [T, N] (Tp / 64 x
-// (K + N) / 64 workgroups): one launch, 1.4 us less than two in a step of 193.
+// transpose_pad_tile (peqa_device.h) for every 64 x 64 tile of both operands, X [T, K] and dY [T, N]: Tp / 64 x (K + N) / 64
+// workgroups, numbered along the tokens first (a grid's second dimension ends at 65536: K + N would too, at 2^22).  One
+// launch, 1.4 us less than two in a step of 193.
 __global__ __launch_bounds__(256) void transpose_pad_kernel(const uint16_t *__restrict__ X, int K, uint16_t *__restrict__ xt,
                                                              const uint16_t *__restrict__ dY, int N,
                                                              uint16_t *__restrict__ dyt, int T)
 {
     __shared__ uint16_t tile[64][64 + 2];
-    const int bc = (int)blockIdx.y, of_x = K >> 6;
+    const int bts = (T + 63) >> 6, bc = (int)blockIdx.x / bts, of_x = K >> 6;
     const bool x = bc < of_x;
-    transpose_pad_tile(x ? X : dY, T, x ? K : N, x ? xt : dyt, (int)blockIdx.x, x ? bc : bc - of_x, tile);
+    transpose_pad_tile(x ? X : dY, T, x ? K : N, x ? xt : dyt, (int)blockIdx.x - bc * bts, x ? bc : bc - of_x, tile);
 }
 
 // d_ds[i, g] = sum of pc[i, chunk] over the gsz / 64 chunks of group g, in order.
@@ -334,7 +335,7 @@ hipError_t launch_transpose_pad(const uint16_t *X, int K, uint16_t *xt, const ui
                                 hipStream_t stream)
 {
     trace_before(KID_TRANSPOSE, stream);
-    hipLaunchKernelGGL(transpose_pad_kernel, dim3((T + 63) / 64, (K + N) / 64), dim3(256), 0, stream, X, K, xt, dY, N, dyt, T);
+    hipLaunchKernelGGL(transpose_pad_kernel, dim3((T + 63) / 64 * ((K + N) / 64)), dim3(256), 0, stream, X, K, xt, dY, N, dyt, T);
     trace_after(KID_TRANSPOSE, stream);
     return hipGetLastError();
 }

@@ -224,3 +224,26 @@ def test_token_contraction_tiles(gpu, oracle, bits, N, K, group, T):
     _, gz, _ = layer.bwd_z(X, dY, None, dz)
     _, gzref, _ = oracle.bwd_z(codes, s0, None, z0, dz, X, dY, group)
     gpu.assert_scale_grad_close(gpu.to_host(gz), gzref)
+
+
+def test_token_contraction_of_very_many_channels(gpu):
+    """K + N past 65536 tiles of 64: the copies' launch in one grid dimension.  With all codes zero,
+    d_ds[n, g] = -z0[n, g] * sum_t dY[t, n] * (sum of X[t] over group g)."""
+    import torch
+    from paper_2305_14152_amd import peqa
+    N, K, group, T = 128 * 32767, 256, 128, 17
+    L = peqa.layout(N, K, 4, group)
+    g = torch.Generator(device="cuda").manual_seed(75900)
+    packed = torch.zeros(peqa.packed_words(L), dtype=torch.int32, device="cuda")
+    s0 = torch.ones((N, 2), device="cuda")
+    z0 = torch.randint(1, 16, (N, 2), dtype=torch.uint8, device="cuda", generator=g)
+    X = torch.randn((T, K), device="cuda", generator=g).bfloat16()
+    dY = torch.randn((T, N), device="cuda", generator=g).bfloat16()
+    d_ds = torch.zeros((N, 2), device="cuda")
+    nb = peqa.workspace_bytes(L, T, peqa.PEQA_OP_BWD)
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    peqa.linear_bwd(L, packed, s0, None, z0, X.view(torch.int16), dY.view(torch.int16), T, None, d_ds, ws, nb)
+    sums = X.double().view(T, 2, group).sum(2)
+    want = -z0.double() * torch.stack([(dY.double() * sums[:, i:i + 1]).sum(0) for i in range(2)], 1)
+    assert ((d_ds.double() - want).norm() / want.norm()).item() <= 1e-5
+    assert ((d_ds.double() - want).abs().max() / want.pow(2).mean().sqrt()).item() <= 1e-4
