@@ -1,6 +1,8 @@
-"""The built device code: no matrix instruction reads a register sooner after a vector write than the hardware allows.
-The compiler does not see writes in inline assembly, so nothing else would notice."""
+"""The built device code: no matrix instruction reads a register sooner after a vector write than the hardware allows (the
+compiler does not see writes in inline assembly, so nothing else would notice), and no kernel that counts its outstanding
+memory operations by hand may spill registers unnoticed."""
 import os
+import re
 
 from paper_2305_14152_amd import build, peqa
 
@@ -34,3 +36,16 @@ def test_no_matrix_instruction_reads_too_early():
     listings = build.device_listings(build.LIB)
     assert sum("v_mfma" in text for text in listings) >= 3           # the tiled, the token and the T <= 16 contraction
     assert [b for text in listings for b in build.early_matrix_reads(text)] == []
+
+
+def test_spills_are_refused_in_every_kernel_that_counts():
+    """Every kernel with a ring of DMAs (dynamic LDS and matrix instructions) is among those the build looks at."""
+    peqa.lib()
+    kernels = set()
+    for text in build.device_listings(build.LIB):
+        for part in re.split(r"\n(?=[0-9a-f]+ <)", text):
+            if "global_load_lds" in part:
+                kernels.add(re.match(r"[0-9a-f]+ <(.+)>:", part).group(1))
+    assert len(kernels) >= 20
+    remark = "f.hip:1:1: remark: Function Name: %s [-R]\nf.hip:1:1: remark:     ScratchSize [bytes/lane]: 8 [-R]\n"
+    assert [k for k in kernels if not build.check_no_scratch(remark % k)] == []
