@@ -72,10 +72,10 @@ Workspace carve_whole(const peqa_layout *L, int32_t T, int32_t op)
             const size_t Tp = ((size_t)T + 63) / 64 * 64, K = (size_t)L->k_in;
             w.rs = off;      off += round256((size_t)T * G * sizeof(float));
             w.partial = off; off += round256(tiles_t * N * G * sizeof(float));
-            // scale gradient by the token contraction: both operands transposed, per-chunk results
+            // scale gradient by the token contraction: both operands transposed, per-chunk results (of groups past 128)
             w.xt = off;      off += round256(K * Tp * sizeof(uint16_t));
             w.dyt = off;     off += round256(N * Tp * sizeof(uint16_t));
-            w.pc = off;      off += round256(N * (K / 64) * sizeof(float));
+            w.pc = off;      off += round256(peqa::dw_chunk_bytes(L->n_out, L->k_in, L->group_size));
         }
         w.total = off;
         return w;

@@ -51,7 +51,7 @@ struct BlockSpace {
     size_t table[PEQA_MAX_BLOCK];    // group-wise item j: its (s, b) table [G, N, 2]
     size_t xt[PEQA_MAX_BLOCK];       // backward, group-wise item j: step-major transposed copy of its input [K, T']
     size_t dyt[PEQA_MAX_BLOCK];      //   the same of its dY [N, T']
-    size_t pc[PEQA_MAX_BLOCK];       //   scale gradient per 64-feature chunk [N, K / 64]
+    size_t pc[PEQA_MAX_BLOCK];       //   scale gradient per 64-feature chunk [N, K / 64], groups past 128 only
     size_t total;
     // Pieces of the contractions (1 = whole) and the regions of their partial results, behind the others: `total` includes
     // them, and a workspace of at least `min_total` bytes is served with whole contractions.
@@ -73,7 +73,7 @@ BlockSpace carve_block(int32_t n, const peqa_block_item *items, int32_t T, int32
             if (op == PEQA_OP_BWD) {
                 w.xt[j] = off;  off += round256(K * Tp * sizeof(uint16_t));
                 w.dyt[j] = off; off += round256(N * Tp * sizeof(uint16_t));
-                w.pc[j] = off;  off += round256(N * (K / 64) * sizeof(float));
+                w.pc[j] = off;  off += round256(peqa::dw_chunk_bytes(L->n_out, L->k_in, L->group_size));
             }
             continue;
         }

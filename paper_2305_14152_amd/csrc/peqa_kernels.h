@@ -157,6 +157,8 @@ hipError_t launch_transpose_pad(const uint16_t *X, int K, uint16_t *xt, const ui
                                 hipStream_t stream);
 // groups of 64 or 128 features lie within one tile of 128: no chunk sums to add up
 constexpr bool dw_whole_groups(int gsz) { return gsz <= 128; }
+// bytes of the chunk sums [N, K / 64] of other groups
+constexpr size_t dw_chunk_bytes(int N, int K, int gsz) { return dw_whole_groups(gsz) ? 0 : (size_t)N * (size_t)(K / 64) * sizeof(float); }
 hipError_t launch_dw(int bits, const DwArgs &a, hipStream_t stream);
 hipError_t launch_chunk_reduce(const float *pc, size_t n, int per, float *d_ds, hipStream_t stream);
 // The token contractions of up to DW_MAX_JOBS layers in one launch, and the sums of their chunks in another.

@@ -273,3 +273,22 @@ def test_static_forward_takes_only_what_runs_alike_in_its_scratch(peqa, N, K, bi
     refused = peqa.lib().peqa_linear_fwd_static(ctypes.byref(L), None, None, None, None, None, T, None, None)
     assert refused in (peqa.PEQA_ERR_WORKSPACE, peqa.PEQA_ERR_NULL)     # (the size is looked at before the pointers)
     assert (refused == peqa.PEQA_ERR_WORKSPACE) == (peqa.workspace_bytes(L, T, peqa.PEQA_OP_FWD) > peqa.STATIC_SCRATCH_BYTES)
+
+
+@pytest.mark.parametrize("bits,N,K,group,T", [(4, 384, 1152, 64, 70), (3, 640, 1280, 128, 200), (3, 256, 768, 192, 33), (4, 128, 1024, 512, 300)])
+def test_group_wise_backward_asks_for_what_it_uses(peqa, bits, N, K, group, T):
+    """Whole contractions (a forced form): table, group sums and partials, transposed copies, and the chunk sums of groups
+    of more than 128 features; groups of 64 and 128 are complete in the token contraction's tiles."""
+    def r(n):
+        return (n + 255) // 256 * 256
+    G, Tp, tiles = K // group, (T + 63) // 64 * 64, (T + 127) // 128
+    chunks = r(4 * N * (K // 64)) if group > 128 else 0
+    L = peqa.layout(N, K, bits, group)
+    peqa.set_option(peqa.PEQA_OPT_GEMM_WAVES, 4)
+    try:
+        single = peqa.workspace_bytes(L, T, peqa.PEQA_OP_BWD)
+        block = peqa.block_workspace_bytes(peqa.block_items([dict(L=L, packed=None, s0=None, z0=None)]), T, peqa.PEQA_OP_BWD)
+    finally:
+        peqa.set_option(peqa.PEQA_OPT_GEMM_WAVES, 0)
+    assert single == r(8 * N * G) + r(4 * T * G) + r(4 * tiles * N * G) + r(2 * K * Tp) + r(2 * N * Tp) + chunks
+    assert block == r(8 * N * G) + r(2 * K * Tp) + r(2 * N * Tp) + chunks
