@@ -180,6 +180,59 @@ def test_small_batch_forms(gpu, oracle, bits, N, K, group):
         assert np.abs(gpu.bf16_dev_to_f64(layer.fwd_z(X, ds, dz)) - Yz).max() <= Y_TOL * np.abs(Yz).max()
 
 
+def _small_batch_form(peqa, shapes, bits, group, T):
+    """(64-channel halves per workgroup, waves, slices of every layer): the library's own plan of a T <= 16 launch."""
+    import ctypes
+
+    class Form(ctypes.Structure):
+        _fields_ = [("h", ctypes.c_int), ("waves", ctypes.c_int)]
+
+    plan = peqa.lib()._ZN4peqa9gemv_planEiPKiS1_S1_iibmPi      # peqa::gemv_plan
+    plan.restype = Form
+    ints = ctypes.c_int * len(shapes)
+    S = ints()
+    f = plan(len(shapes), ints(*[n for n, _ in shapes]), ints(*[k for _, k in shapes]),
+             ints(*[group or k for _, k in shapes]), bits, T, True, ctypes.c_size_t(2 ** 64 - 1), S)
+    return f.h, f.waves, list(S)
+
+
+@pytest.mark.parametrize("bits,group", [(4, 0), (3, 0), (4, 64), (3, 128)])
+def test_small_batch_form_of_128_channels(gpu, oracle, bits, group):
+    """T <= 16, more 64-channel tiles than fit on the chip at once: two per workgroup, with both numbers of staged token
+    rows; one layer, and several of which one is sliced."""
+    import torch
+    from paper_2305_14152_amd import peqa
+    shapes = [(33024, 256), (33024, 384), (256, 2048)]
+    seed = 72000 + bits * 1000 + group
+    layers = []
+    for j, (N, K) in enumerate([(65664, 384)] + shapes):
+        W = synth.normal_f32(seed + 10 * j, (N, K), 0.02)
+        codes, s0, z0 = oracle.quantize(W, bits, group)
+        layers.append((gpu.GpuLayer(W, bits, group), codes, s0, z0, synth.normal_f32(seed + 10 * j + 1, s0.shape, 1e-3)))
+    for T in (1, 8, 9, 16):
+        print("128 channels bits=%d g=%d T=%d" % (bits, group, T), flush=True)
+        assert _small_batch_form(peqa, [(65664, 384)], bits, group, T) == (2, 4, [1])
+        h, waves, S = _small_batch_form(peqa, shapes, bits, group, T)
+        assert (h, waves) == (2, 4) and S[:2] == [1, 1] and S[2] > 1
+        layer, codes, s0, z0, ds = layers[0]
+        X = synth.normal_bf16(seed + 100 + T, (T, 384), 1.0)
+        Yref = oracle.fwd(codes, s0, ds, z0, X, group)
+        assert np.abs(gpu.bf16_dev_to_f64(layer.fwd(X, ds)) - Yref).max() <= Y_TOL * np.abs(Yref).max()
+        dicts, refs = [], []
+        for j, (layer, codes, s0, z0, ds) in enumerate(layers[1:]):
+            X = synth.normal_bf16(seed + 200 + 20 * j + T, (T, shapes[j][1]), 1.0)
+            refs.append(oracle.fwd(codes, s0, ds, z0, X, group))
+            dicts.append(dict(L=layer.L, packed=layer.packed, s0=layer.s0, z0=layer.z0, ds=gpu.to_dev(ds), X=gpu.to_dev(X),
+                              Y=torch.zeros((T, shapes[j][0]), dtype=torch.int16, device="cuda")))
+        items = peqa.block_items(dicts)
+        nb = peqa.block_workspace_bytes(items, T, peqa.PEQA_OP_FWD)
+        ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+        peqa.block_fwd(items, T, ws, nb)
+        torch.cuda.synchronize()
+        for d, Yref in zip(dicts, refs):
+            assert np.abs(gpu.bf16_dev_to_f64(d["Y"]) - Yref).max() <= Y_TOL * np.abs(Yref).max()
+
+
 @pytest.mark.parametrize("bits,N,K,T", [(4, 128, 512, 33), (4, 384, 512, 65), (3, 256, 640, 300), (3, 128, 8192, 40)])
 def test_zero_point_gradient_beside_the_others(gpu, oracle, bits, N, K, T):
     """One slice of token rows, two, a ragged last one, a split scale gradient: d_ds and d_dz, whose sums share a launch,
