@@ -460,8 +460,8 @@ size_t peqa_workspace_bytes_fused(int32_t n, const peqa_fwd_item *items, int32_t
 {
     if (check_fused(n, items, T) != PEQA_OK) return 0;
     if (T <= PEQA_GEMV_MAX_T) {
-        GemvItem gi[PEQA_MAX_FUSED];
-        for (int j = 0; j < n; ++j) gi[j] = GemvItem{&items[j].layout, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
+        GemvItem gi[PEQA_MAX_FUSED]{};
+        for (int j = 0; j < n; ++j) gi[j].L = &items[j].layout;
         const size_t b = round256(gemv_partial_bytes(n, gi, T, true, GEMV_ANY));
         return b ? b : 256;
     }
@@ -490,8 +490,8 @@ static peqa_status fwd_fused_impl(int32_t n, const peqa_fwd_item *items, const u
     if (!aligned16(X)) return PEQA_ERR_ALIGN;
     size_t need = 0;                                       // what whole contractions need at least
     if (T <= PEQA_GEMV_MAX_T) {
-        GemvItem gi[PEQA_MAX_FUSED];
-        for (int j = 0; j < n; ++j) gi[j] = GemvItem{&items[j].layout, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
+        GemvItem gi[PEQA_MAX_FUSED]{};
+        for (int j = 0; j < n; ++j) gi[j].L = &items[j].layout;
         need = round256(gemv_partial_bytes(n, gi, T, true, 0));
         need = need ? need : 256;
     } else {
@@ -585,7 +585,8 @@ static peqa_status bwd_impl(const peqa_layout *L, const uint32_t *packed, const 
         if (d_dz) {
             float *zp = reinterpret_cast<float *>(ws + w.zpartial);
             if (peqa::launch_dz_partial(dY, rsb, T, N, G, zp, s) != hipSuccess) return PEQA_ERR_DEVICE;
-            if (peqa::launch_dz_finish(zp, slices, (size_t)N * G, s0, ds, d_dz, nullptr, 0, 0, nullptr, s) != hipSuccess) return PEQA_ERR_DEVICE;
+            if (peqa::launch_dz_finish(zp, slices, (size_t)N * G, s0, ds, d_dz, nullptr, 0, 0, nullptr, s) != hipSuccess)
+                return PEQA_ERR_DEVICE;
         }
         const int Tp = (T + 63) / 64 * 64;
         uint16_t *xt = reinterpret_cast<uint16_t *>(ws + w.xt), *dyt = reinterpret_cast<uint16_t *>(ws + w.dyt);
@@ -953,7 +954,8 @@ char g_trace_prefix[32] = "";     // only kernels whose name starts with this ar
 
 const char *const kKernelNames[peqa::KID_COUNT] = {
     "quantize", "rowsum", "gemm_y", "gemm_dds", "gemm_dx", "scale_dy", "reduce_partials", "adamw", "gemv",
-    "gemv_finish", "group_table", "dds_kept", "dz_partial", "dz_finish", "transpose_pad", "gemm_dw", "gemm_bwd", "gemm_multi_y", "gemm_multi_dds", "gemm_multi_dx", "gemm_finish"};
+    "gemv_finish", "group_table", "dds_kept", "dz_partial", "dz_finish", "transpose_pad", "gemm_dw", "gemm_bwd", "gemm_multi_y",
+    "gemm_multi_dds", "gemm_multi_dx", "gemm_finish"};
 
 }  // namespace
 namespace {

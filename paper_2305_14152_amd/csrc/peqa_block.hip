@@ -96,7 +96,8 @@ BlockSpace carve_block(int32_t n, const peqa_block_item *items, int32_t T, int32
             if (grouped(L) != gw) continue;
             const int C = mode == peqa::MODE_DX ? L->k_in : L->n_out, KC = mode == peqa::MODE_DX ? L->n_out : L->k_in;
             of[m] = j;
-            job[m++] = peqa::SplitJob{(int)tiles_t * ((C + 255) / 256), KC, mode == peqa::MODE_DDS ? 0 : (size_t)T * C * sizeof(float), 1};
+            const size_t out_bytes = mode == peqa::MODE_DDS ? 0 : (size_t)T * C * sizeof(float);
+            job[m++] = peqa::SplitJob{(int)tiles_t * ((C + 255) / 256), KC, out_bytes, 1};
         }
         if (m == 0) return;
         peqa::gemm_plan_splits(m, job, gw, false, ~(size_t)0);
@@ -198,8 +199,8 @@ size_t peqa_block_workspace_bytes(int32_t n, const peqa_block_item *items, int32
     if (check_items(n, items, T) != PEQA_OK) return 0;
     if (op != PEQA_OP_FWD && op != PEQA_OP_BWD) return 0;
     if (op == PEQA_OP_FWD && T <= GEMV_MAX_T) {
-        GemvItem gi[PEQA_MAX_BLOCK];
-        for (int j = 0; j < n; ++j) gi[j] = GemvItem{&items[j].layout, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
+        GemvItem gi[PEQA_MAX_BLOCK]{};
+        for (int j = 0; j < n; ++j) gi[j].L = &items[j].layout;
         const size_t b = round256(gemv_partial_bytes(n, gi, T, true, GEMV_ANY));
         return b ? b : 256;
     }

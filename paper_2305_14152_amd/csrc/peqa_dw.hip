@@ -85,7 +85,8 @@ __device__ __forceinline__ void dw_tile(const DwArgs &a, const int wg, uint8_t *
             const uint32_t byte = (uint32_t)(CODE_DMA * wn + j) * 1024u;
             const uint32_t run = byte / CODE_RUN, off = byte - run * CODE_RUN;
             const int row = (2 * tile_c + (int)run) * 128 < a.N ? 2 * tile_c + (int)run : 2 * tile_c;
-            dma16((uint32_t)lane * 16u, reinterpret_cast<const uint8_t *>(a.packed) + (size_t)row * row_bytes + (size_t)tile_f * CODE_RUN + off,
+            dma16((uint32_t)lane * 16u,
+                  reinterpret_cast<const uint8_t *>(a.packed) + (size_t)row * row_bytes + (size_t)tile_f * CODE_RUN + off,
                   lds_base + byte);
         }
     }
@@ -99,12 +100,15 @@ __device__ __forceinline__ void dw_tile(const DwArgs &a, const int wg, uint8_t *
         const uint8_t *src = xsrc + (size_t)clamp_step(it) * xstep;
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-            dma16((uint32_t)(2 * wn + j) * 1024u + (uint32_t)lane * 16u, src, lds_base + DW_CODES + stage * DW_STAGE + (2 * wn + j) * 1024);
+            dma16((uint32_t)(2 * wn + j) * 1024u + (uint32_t)lane * 16u, src,
+                  lds_base + DW_CODES + stage * DW_STAGE + (2 * wn + j) * 1024);
     };
     // the wave's 64 channels; past the matrix (N % 128 == 0: whole waves) the last ones of it, and nothing is stored
     const int cb = n0 + 64 * wn, cb_l = cb < a.N ? cb : a.N - 64;
     const uint8_t *ysrc = reinterpret_cast<const uint8_t *>(a.dYt) + (size_t)cb_l * 64;
-    auto load_b = [&](const uint8_t *step_src, int ct) { return *reinterpret_cast<const u32x4 *>(step_src + ct * 1024 + lane * 16); };
+    auto load_b = [&](const uint8_t *step_src, int ct) {
+        return *reinterpret_cast<const u32x4 *>(step_src + ct * 1024 + lane * 16);
+    };
     u32x4 bfrag[2][NCT];
 
     f32x4 acc[NRT][NCT];
@@ -363,7 +367,9 @@ hipError_t launch_dw(int bits, const DwArgs &a, hipStream_t stream)
 
 static bool dw_args_ok(const DwArgs &a)
 {
-    if (a.K % 128 != 0 || a.tiles_f != a.K / 128 || a.tiles_c != (a.N + 255) / 256 || a.N % 128 != 0 || a.Tp % 64 != 0 || a.Tp < 64 || a.gsz % 64 != 0 || a.K % a.gsz != 0) return false;
+    if (a.K % 128 != 0 || a.tiles_f != a.K / 128 || a.tiles_c != (a.N + 255) / 256 || a.N % 128 != 0 || a.Tp % 64 != 0 ||
+        a.Tp < 64 || a.gsz % 64 != 0 || a.K % a.gsz != 0)
+        return false;
     return (uint64_t)(a.K > a.N ? a.K : a.N) * 64u < ((uint64_t)1 << 32);   // 32-bit DMA offsets
 }
 

@@ -91,9 +91,12 @@ __device__ __forceinline__ void multi_aux(int n_sdy, int n_red, int n_tp, int au
     struct { int n_sdy, n_red, n_tp, aux_wgs; } m{n_sdy, n_red, n_tp, aux_wgs};
     float *red = reinterpret_cast<float *>(lds);
     constexpr uint32_t SDY0 = offsetof(MultiArgs, sdy), RED0 = offsetof(MultiArgs, red), TP0 = offsetof(MultiArgs, tp);
-    const int n_blk = m.n_sdy > 0 ? kernarg_load<int>(SDY0 + (uint32_t)((m.n_sdy - 1) * sizeof(ScaleDyJob) + offsetof(ScaleDyJob, blk_end))) : 0;
-    const int n_chunk = m.n_red > 0 ? kernarg_load<int>(RED0 + (uint32_t)((m.n_red - 1) * sizeof(ReduceJob) + offsetof(ReduceJob, chunk_end))) : 0;
-    const int n_tile = m.n_tp > 0 ? kernarg_load<int>(TP0 + (uint32_t)((m.n_tp - 1) * sizeof(TransposeJob) + offsetof(TransposeJob, tile_end))) : 0;
+    auto last = [](uint32_t table, int n, size_t size, size_t member) {   // a running total's value behind the last of n jobs
+        return n > 0 ? kernarg_load<int>(table + (uint32_t)((n - 1) * size + member)) : 0;
+    };
+    const int n_blk = last(SDY0, m.n_sdy, sizeof(ScaleDyJob), offsetof(ScaleDyJob, blk_end));
+    const int n_chunk = last(RED0, m.n_red, sizeof(ReduceJob), offsetof(ReduceJob, chunk_end));
+    const int n_tile = last(TP0, m.n_tp, sizeof(TransposeJob), offsetof(TransposeJob, tile_end));
     for (int u = w; u < n_blk + n_chunk + n_tile; u += m.aux_wgs) {
         if (u >= n_blk + n_chunk) {
             const int x = u - n_blk - n_chunk;
@@ -341,7 +344,8 @@ static hipError_t launch_halves(const GemmArgs &a, hipStream_t stream)
 {
     constexpr bool PAIRED = GROUPED && MODE == MODE_DDS;
     if constexpr (!PAIRED) {
-        if (halves_per_workgroup(a.tiles_t * a.tiles_c * pieces(a), false) == 1) return launch_one<BITS, MODE, GROUPED, 1>(a, stream);
+        if (halves_per_workgroup(a.tiles_t * a.tiles_c * pieces(a), false) == 1)
+            return launch_one<BITS, MODE, GROUPED, 1>(a, stream);
     }
     return launch_one<BITS, MODE, GROUPED, 2>(a, stream);
 }
@@ -388,7 +392,7 @@ static hipError_t launch_pair(const GemmArgs &a_dds, const GemmArgs &a_dx, hipSt
         if (e != hipSuccess) return e;
         attr_bytes[dev] = lds_bytes;
     }
-        // the tiles that take longer go first: the short ones fill the last round better
+    // the tiles that take longer go first: the short ones fill the last round better
     // (the numbers of workgroups are multiples of 8: both parts keep workgroup id % 8 = XCD)
     const int dx_first = a_dx.KC / pieces(a_dx) >= a_dds.KC / pieces(a_dds);
     const int n_first = gemm_multi_wgs(dx_first ? a_dx : a_dds), n_second = gemm_multi_wgs(dx_first ? a_dds : a_dx);
@@ -444,9 +448,12 @@ hipError_t launch_gemm_multi(int bits, bool grouped, MultiArgs &m, hipStream_t s
     trace_before(kid, stream);
     const dim3 grid(total + m.aux_wgs);
     hipError_t e;
-    if (!grouped) e = bits == 4 ? launch_multi<4, -1>(grid, lds_bytes, m, stream) : launch_multi<3, -1>(grid, lds_bytes, m, stream);
-    else if (mode0 == MODE_Y) e = bits == 4 ? launch_multi<4, MODE_Y>(grid, lds_bytes, m, stream) : launch_multi<3, MODE_Y>(grid, lds_bytes, m, stream);
-    else e = bits == 4 ? launch_multi<4, MODE_DX>(grid, lds_bytes, m, stream) : launch_multi<3, MODE_DX>(grid, lds_bytes, m, stream);
+    if (!grouped)
+        e = bits == 4 ? launch_multi<4, -1>(grid, lds_bytes, m, stream) : launch_multi<3, -1>(grid, lds_bytes, m, stream);
+    else if (mode0 == MODE_Y)
+        e = bits == 4 ? launch_multi<4, MODE_Y>(grid, lds_bytes, m, stream) : launch_multi<3, MODE_Y>(grid, lds_bytes, m, stream);
+    else
+        e = bits == 4 ? launch_multi<4, MODE_DX>(grid, lds_bytes, m, stream) : launch_multi<3, MODE_DX>(grid, lds_bytes, m, stream);
     trace_after(kid, stream);
     return e;
 }

@@ -1,7 +1,7 @@
 // Deployment forward for T <= 16 tokens (Sec. 3.1 "Inference Latency": matrix-vector products bound
 // by the weight bytes streamed from memory).  Y[t,i] = sum_g s[i,g] * sum_{k in g} X[t,k] (Q[i,k] - z[i,g]).
 //
-// Every packed word is read from HBM exactly once, straight into registers: a wave owns 64 output channels (lane (c, q):
+// Every packed word is read from HBM exactly once: a wave owns 64 output channels (lane (c, q):
 // half of channel block c / 2, feature block q of each 32-feature step) -- or two such halves of 128 -- and walks a range of
 // the input features; the up-to-16 token rows ride along as the 16-row operand of MFMA 16x16x32, so T = 1 and T = 16 cost
 // the same weight traffic.  Codes enter the MFMAs as exact bf16 (16 + Q); one more MFMA per step against a fragment of ones
@@ -243,10 +243,10 @@ __global__ __launch_bounds__(WAVES * 64, GV_SIMD_WAVES) void gemv_kernel(GemvArg
     uint32_t rd = 0;                                              // ring offset of the round being consumed
     // A compute unit's arbiter serves the older wave first: of the workgroups that share one, the one dispatched first runs
     // ahead, ends early, and leaves the others to finish with fewer loads in flight.  Where all workgroups of the launch are
-    // resident at once, the later ones therefore take a higher priority for the first half of their rounds; the first ones win the ties of
-    // the second half, and all end together (13B block, T = 1 and 5: 34.6 -> 33.7 and 35.5 -> 34.3 us).  Which came later is a
-    // guess from the index (the first prio_step workgroups are dealt one to every compute unit, and so on); a wrong guess
-    // costs time only.  Where later workgroups take the places of earlier ones it cost 3 to 6 %.
+    // resident at once, the later ones therefore take a higher priority for the first half of their rounds; the first ones
+    // win the ties of the second half, and all end together (13B block, T = 1 and 5: 34.6 -> 33.7 and 35.5 -> 34.3 us).
+    // Which came later is a guess from the index (the first prio_step workgroups are dealt one to every compute unit, and so
+    // on); a wrong guess costs time only.  Where later workgroups take the places of earlier ones it cost 3 to 6 %.
     const int prio = a.prio_step ? bx / a.prio_step : 0;
     if (prio == 1) __builtin_amdgcn_s_setprio(1);
     else if (prio == 2) __builtin_amdgcn_s_setprio(2);
@@ -399,8 +399,9 @@ static int gv_cols(int K, int chunk, int S)                        // most scale
 // few workgroups with a few loads in flight each) and no layer's much longer than the others': layers are sliced to at most
 // 1.35 times the mean length, more while the workgroups' scale tiles keep them from fitting on the chip together; failing
 // that, 128 channels per workgroup (half of the token rows' traffic and LDS per channel).  us per block at T = 1 / 16, 13B
-// 3-bit g128: 3 slices of the long layer 34.6 / 42.3, 2 slices (not resident) 38.9 / 45.6, 128 channels 35.8 / 38.2.  Launches too large for
-// that take the slicing with the most workgroups per compute unit, as long as the partial sums stay below 4 % of the codes.
+// 3-bit g128: 3 slices of the long layer 34.6 / 42.3, 2 slices (not resident) 38.9 / 45.6, 128 channels 35.8 / 38.2.
+// Launches too large for that take the slicing with the most workgroups per compute unit, as long as the partial sums stay
+// below 4 % of the codes.
 //
 // Slicings whose partial sums take more than `most` bytes are left out; where none remains, the fewest slices are taken.
 GemvForm gemv_plan(int n, const int *N, const int *K, const int *chunk, int bits, int T, bool zbyte, size_t most, int *S)
@@ -494,8 +495,8 @@ hipError_t launch_gemv(int bits, const GemvForm &f, const GemvArgs &a_in, hipStr
     // One instantiation: its dynamic LDS (more than the default limit: raised once per device), then the launch.
     auto go = [&](auto h_c, auto waves_c, auto bits_c, auto nx_c, auto z_c) -> hipError_t {
         static bool allowed[64];
-        const auto kern = gemv_kernel<decltype(bits_c)::value, decltype(h_c)::value, decltype(waves_c)::value, decltype(nx_c)::value,
-                                      decltype(z_c)::value>;
+        const auto kern = gemv_kernel<decltype(bits_c)::value, decltype(h_c)::value, decltype(waves_c)::value,
+                                      decltype(nx_c)::value, decltype(z_c)::value>;
         if (!allowed[dev]) {
             const hipError_t e2 = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                                       hipFuncAttributeMaxDynamicSharedMemorySize, GV_LDS_MAX);

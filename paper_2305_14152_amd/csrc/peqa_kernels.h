@@ -85,7 +85,8 @@ hipError_t launch_split_finish(const FinishMulti &f, hipStream_t stream);
 // for a huge count: whether the four-wave form is allowed at all (the option gemm_waves = 8 forbids it)
 bool gemm_four_waves(int tiles);
 // Per-channel layers: the MODE_DDS and the MODE_DX contraction of one backward (arguments as for launch_gemm) as one
-// launch of four-wave workgroups (measured faster than two launches at every T).  The dX arguments' input (the scaled dY) must be complete before the launch.
+// launch of four-wave workgroups (measured faster than two launches at every T).  The dX arguments' input (the scaled dY)
+// must be complete before the launch.
 hipError_t launch_gemm_bwd_pair(int bits, const GemmArgs &a_dds, const GemmArgs &a_dx, hipStream_t stream);
 
 // Several contractions in ONE launch of four-wave workgroups (gemm_multi_kernel): the tiles of job 0 first, then
@@ -118,7 +119,8 @@ struct ReduceJob {            // out[j] = sum over ntiles of partial[tile][j], f
     int ntiles, n;
     int chunk_end;            // 256-element chunks of this job and all before it
 };
-struct TransposeJob {         // dst[t / 32][c][t % 32] = src[t, c], zero-padded to Tp tokens      (transpose_pad_tile)
+// dst[t / 32][c / 16][(t % 32) / 8][c % 16][t % 8] = src[t, c], zeros from T to Tp   (transpose_pad_tile)
+struct TransposeJob {
     const uint16_t *src;
     uint16_t *dst;
     int T, C, Tp;
@@ -141,8 +143,8 @@ int gemm_multi_wgs(const GemmArgs &a);
 // Arguments of the token contraction dW = dY^T X with the codes applied in its epilogue (peqa_dw.hip):
 // the scale gradient of group-wise layers.
 struct DwArgs {
-    const uint16_t *Xt;       // [Tp / 32, K, 32] bf16: X in 32-token steps (transpose_pad_tile's order), tokens padded with zeros to Tp
-    const uint16_t *dYt;      // [Tp / 32, N, 32] bf16, dY likewise
+    const uint16_t *Xt;       // [Tp / 32, K / 16, 4, 16, 8] bf16: X in 32-token steps (transpose_pad_tile), zeros from T to Tp
+    const uint16_t *dYt;      // [Tp / 32, N / 16, 4, 16, 8] bf16, dY likewise
     const uint32_t *packed;   // packed codes of the layer
     const uint8_t *z0;        // [N, G]
     const float *dz;          // [N, G] or NULL
@@ -158,7 +160,10 @@ hipError_t launch_transpose_pad(const uint16_t *X, int K, uint16_t *xt, const ui
 // groups of 64 or 128 features lie within one tile of 128: no chunk sums to add up
 constexpr bool dw_whole_groups(int gsz) { return gsz <= 128; }
 // bytes of the chunk sums [N, K / 64] of other groups
-constexpr size_t dw_chunk_bytes(int N, int K, int gsz) { return dw_whole_groups(gsz) ? 0 : (size_t)N * (size_t)(K / 64) * sizeof(float); }
+constexpr size_t dw_chunk_bytes(int N, int K, int gsz)
+{
+    return dw_whole_groups(gsz) ? 0 : (size_t)N * (size_t)(K / 64) * sizeof(float);
+}
 hipError_t launch_dw(int bits, const DwArgs &a, hipStream_t stream);
 hipError_t launch_chunk_reduce(const float *pc, size_t n, int per, float *d_ds, hipStream_t stream);
 // The token contractions of up to DW_MAX_JOBS layers in one launch, and the sums of their chunks in another.
@@ -288,7 +293,9 @@ void trace_after(int kernel_id, hipStream_t stream);
 
 enum {
     KID_QUANTIZE = 0, KID_ROWSUM, KID_GEMM_Y, KID_GEMM_DDS, KID_GEMM_DX, KID_SCALE_DY,
-    KID_REDUCE, KID_ADAMW, KID_GEMV, KID_GEMV_FINISH, KID_GROUP_TABLE, KID_DDS_KEPT, KID_DZ_PARTIAL, KID_DZ_FINISH, KID_TRANSPOSE, KID_GEMM_DW, KID_GEMM_BWD, KID_GEMM_MULTI_Y, KID_GEMM_MULTI_DDS, KID_GEMM_MULTI_DX, KID_GEMM_FINISH, KID_COUNT
+    KID_REDUCE, KID_ADAMW, KID_GEMV, KID_GEMV_FINISH, KID_GROUP_TABLE, KID_DDS_KEPT, KID_DZ_PARTIAL, KID_DZ_FINISH,
+    KID_TRANSPOSE, KID_GEMM_DW, KID_GEMM_BWD, KID_GEMM_MULTI_Y, KID_GEMM_MULTI_DDS, KID_GEMM_MULTI_DX, KID_GEMM_FINISH,
+    KID_COUNT
 };
 
 }  // namespace peqa

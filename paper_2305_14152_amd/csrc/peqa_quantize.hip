@@ -223,7 +223,8 @@ __global__ __launch_bounds__(1024) void quantize_resident_kernel(const float *__
     float *s_s = reinterpret_cast<float *>(s_neg + 8 * G);
     int *s_z = reinterpret_cast<int *>(s_s + 8 * G);
     float *s_r = reinterpret_cast<float *>(s_z + 8 * G);                 // [8][G] code_factor(s)
-    uint32_t *s_codes = reinterpret_cast<uint32_t *>(s_r + 8 * G);       // 4 bits: [K / 8][8] packed words; 3: [8][K / 4] words = one byte per code
+    // 4 bits: [K / 8][8] packed words; 3 bits: [8][K / 4] words of one byte per code
+    uint32_t *s_codes = reinterpret_cast<uint32_t *>(s_r + 8 * G);
     // SEARCH only: the best candidate so far per (channel, group), and the error sums per 64-feature segment
     double *b_err = reinterpret_cast<double *>(s_codes + 2 * K);        // [8][G]
     double *seg_err = b_err + 8 * G;                                    // [8][K / 64]

@@ -16,7 +16,8 @@ __device__ __forceinline__ float wave_sum(float v)
 
 // rs[t, h] = sum of X[t, k] over contraction half h (k < ksplit, k >= ksplit), fp32.
 // One wave per token row; 16-byte loads.
-__device__ __forceinline__ void rowsum_rows(const uint16_t *__restrict__ X, int T, int K, int ksplit, float *__restrict__ rs, int blk)
+__device__ __forceinline__ void rowsum_rows(const uint16_t *__restrict__ X, int T, int K, int ksplit, float *__restrict__ rs,
+                                            int blk)
 {
     const int lane = threadIdx.x & 63, t = blk * 4 + (threadIdx.x >> 6);
     if (t >= T) return;
@@ -475,7 +476,8 @@ hipError_t launch_scale_dy(const uint16_t *dY, const float *s0, const float *ds,
                            float *red_out, const uint16_t *X, int K, float *rs, hipStream_t stream)
 {
     trace_before(KID_SCALE_DY, stream);
-    const unsigned blocks = (unsigned)((T + SDY_ROWS - 1) / SDY_ROWS) + (rs ? (unsigned)((T + 3) / 4) : 0u) + (unsigned)((n_red + 255) / 256);
+    const unsigned row_blocks = (unsigned)((T + SDY_ROWS - 1) / SDY_ROWS), sum_blocks = rs ? (unsigned)((T + 3) / 4) : 0u;
+    const unsigned blocks = row_blocks + sum_blocks + (unsigned)((n_red + 255) / 256);
     hipLaunchKernelGGL(scale_dy_kernel, dim3(blocks), dim3(256), 0, stream, dY, s0, ds, z0, dz, T, N, dYs, crow, partial,
                        ntiles, n_red, red_out, X, K, rs);
     trace_after(KID_SCALE_DY, stream);

@@ -9,8 +9,9 @@
 // compute unit.  With 128 x 64 per wave every weight of the tile is unpacked (and, group-wise, scaled) by one wave only:
 // 2 instructions per weight pair per channel and 5 group-wise (scale_pair) make 256 and 640 cycles per step.  The split this
 // replaced, 64 x 128 per wave, had every weight unpacked by two waves: 512 and, at the 7 instructions per pair it took to
-// scale bf16 codes, 1800 cycles, which made the group-wise contractions vector-bound.  The price is that a wave reads the whole activation tile from LDS: 8 + 1 reads of 1 KB per
-// wave and step instead of 4 + 2, 576 instead of 384 cycles of the compute unit.  Measured, 64 x 128 -> 128 x 64:
+// scale bf16 codes, 1800 cycles, which made the group-wise contractions vector-bound.  The price is that a wave reads the
+// whole activation tile from LDS: 8 + 1 reads of 1 KB per wave and step instead of 4 + 2, 576 instead of 384 cycles of the
+// compute unit.  Measured, 64 x 128 -> 128 x 64:
 // LLaMA-13B block, 3 bits, groups of 128, T = 2048: forward launch 1537 -> 1239 us, dX 1654 -> 1445 us (with
 // that split dX scaled its activation fragments instead of the weights; here the weights are cheaper to scale), and with
 // fp16 codes for the scaling 1129 and 1259 us; 11008 x 4096, 4 bits, groups of 64, T = 500: forward 102 -> 72 -> 67 us;
@@ -35,7 +36,8 @@ constexpr int B_WAVE_BYTES = 1024;                         // packed codes of on
 // codes of its four waves: 24 KB or 12 KB.
 constexpr int stage_bytes(int kw) { return kw * (A_HALF_BYTES + 4 * B_WAVE_BYTES); }
 constexpr int DMA_PER_ITER = 3;                            // DMA instructions per wave per iteration
-constexpr int ring_bytes(int kw) { return NSTAGE * stage_bytes(kw); }   // 144 KB (the epilogue's exchange of 128 KB reuses it) or 72 KB
+// 144 KB (the epilogue's exchange of 128 KB reuses it) or 72 KB
+constexpr int ring_bytes(int kw) { return NSTAGE * stage_bytes(kw); }
 constexpr int tbl_bytes(int kw) { return kw * 4 * 2 * 1024; }           // group-wise MODE_Y / MODE_DX: 2 x 1 KB of (s, b) per wave
 
 // The weight-fragment register (0..15) of the next step that is built after MFMA m of a step, or -1: spread over MFMAs 4..31.
@@ -201,7 +203,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
     //                   multiples of 64)
     const uint32_t tbl_off = NSTAGE * STAGE_BYTES + wave * 2048;
     const int last_block = (KC >> 7) - 1;
-    int tb_g = 0, tb_left = 0;                             // along features: group of the next block's first 64 features, features left in it
+    int tb_g = 0, tb_left = 0;                             // along features: group of the next block's start, features left in it
     const uint8_t *tb_src = reinterpret_cast<const uint8_t *>(a.sb);
     if constexpr (SCALED) {
         if constexpr (ALONG_CH) {
@@ -229,7 +231,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
             advance();
             const int g1 = tb_g;
             advance();
-            dma16((lane & 31) * 16 + (lane < 32 ? 0u : (uint32_t)(g1 - g0) * (uint32_t)a.N * 8u), tb_src + (size_t)g0 * a.N * 8, dst);
+            dma16((lane & 31) * 16 + (lane < 32 ? 0u : (uint32_t)(g1 - g0) * (uint32_t)a.N * 8u),
+                  tb_src + (size_t)g0 * a.N * 8, dst);
         }
     };
     // Scales and offsets of the next fragments.  Along features fragment I needs entry I, the same for two steps; along
@@ -279,9 +282,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
     // addressed from one lane-dependent base register each (kept live across the loop), the rest is literal.
     constexpr int HALF_RING = (NSTAGE / 2) * STAGE_BYTES;
     static_assert((NSTAGE / 2 - 1) * STAGE_BYTES + 8192 <= 65536, "literal offsets of LDS reads");
-    // row 16 rt' + c (the swizzle only looks at row % 16).  Where the row sums are taken, row tile rt of the wave's registers is row
-    // tile rt' = rt ^ 2 wn of the tile: registers 0 and 1 are then other rows in each of the four waves, which together add
-    // up all 128 rows (two dot instructions per register: 8 per wave and step).
+    // row 16 rt' + c (the swizzle only looks at row % 16).  Where the row sums are taken, row tile rt of the wave's registers is
+    // row tile rt' = rt ^ 2 wn of the tile: registers 0 and 1 are then other rows in each of the four waves, which together
+    // add up all 128 rows (two dot instructions per register: 8 per wave and step).
     constexpr int NPAIR = ROW_SUMS ? 4 : 1;                // pairs of row tiles with a base register of their own
     const uint8_t *a_rd[2][NPAIR], *b_rd[2];
 #pragma unroll
@@ -293,8 +296,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
     b_rd[1] = b_rd[0] + HALF_RING;
     auto read_a = [&](auto st_c, u32x4 *af, int rt) __attribute__((always_inline)) {
         constexpr int ST = decltype(st_c)::value;
-        af[rt] = *reinterpret_cast<const u32x4 *>(a_rd[ST / (NSTAGE / 2)][NPAIR == 4 ? rt >> 1 : 0] + (ST % (NSTAGE / 2)) * STAGE_BYTES +
-                                                  (NPAIR == 4 ? rt & 1 : rt) * 16 * 64);
+        const uint8_t *base = a_rd[ST / (NSTAGE / 2)][NPAIR == 4 ? rt >> 1 : 0] + (ST % (NSTAGE / 2)) * STAGE_BYTES;
+        af[rt] = *reinterpret_cast<const u32x4 *>(base + (NPAIR == 4 ? rt & 1 : rt) * 16 * 64);
     };
     auto read_b = [&](auto st_c, uint32_t *w) __attribute__((always_inline)) {
         constexpr int ST = decltype(st_c)::value;
@@ -599,7 +602,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
             colsum = columns_of(v, 0);
         }
         if constexpr (KW == 1) {
-            if (wave_on && q == 0) *reinterpret_cast<f32x4 *>(a.partial + (size_t)(piece * a.tiles_t + tile_t) * a.C + colc) = colsum;
+            if (wave_on && q == 0)
+                *reinterpret_cast<f32x4 *>(a.partial + (size_t)(piece * a.tiles_t + tile_t) * a.C + colc) = colsum;
         } else {
             float *red = reinterpret_cast<float *>(lds);   // [contraction half][256 columns]
             if (q == 0) *reinterpret_cast<f32x4 *>(red + wk * TILE_C + wn * WAVE_C + 4 * c) = colsum;
