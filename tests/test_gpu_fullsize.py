@@ -267,7 +267,8 @@ def test_full_size_block(gpu, oracle, cfg):
     if cfg not in (1, 4):
         return
     # deployment forward of the block: seven items (q, k, v and gate, up as slices of the stacked arrays), one call.
-    # (T = 1 and 4 take the three-workgroups-per-unit slicing on the per-channel 7B block, T = 16 the other.)
+    # (T = 1 and 4 stage 8 token rows, T = 16 sixteen; workgroups of 64 channels, of 128 on the 13B block at T = 16; the down
+    # projections are sliced.)
     for Ts in ((1, 16) if cfg == 4 else (1, 4, 16)):
         seven, refs = [], []
         for m, d, (N, K, li, xi) in zip(members, dicts, shapes):
