@@ -94,7 +94,8 @@ typedef enum {
 peqa_status peqa_check_layout(const peqa_layout *L);
 size_t peqa_packed_words(const peqa_layout *L);   /* N*K*bits/32 uint32 words; 0 if invalid */
 size_t peqa_num_scales(const peqa_layout *L);     /* N*G; 0 if invalid                      */
-/* Bytes of scratch the given call asks for with T tokens (0 if invalid; see Workspaces). */
+/* Bytes of scratch the given call asks for with T tokens (0 if invalid; see Workspaces).  This and the other size queries are
+ * for a whole MI355X (256 compute units); a call on a partition of one plans for its units, within what it was given. */
 size_t peqa_workspace_bytes(const peqa_layout *L, int32_t T, int32_t op);
 const char *peqa_status_string(int32_t status);
 

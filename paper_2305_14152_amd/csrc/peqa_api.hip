@@ -28,12 +28,12 @@ struct Workspace {
     size_t gemv_most;                      // T <= 16: the most bytes that the plan's partial sums may take
 };
 
-Workspace carve_whole(const peqa_layout *L, int32_t T, int32_t op)
+Workspace carve_whole(const peqa_layout *L, int32_t T, int32_t op, int cus)
 {
-    if (op == PEQA_OP_FWD_Z && T > PEQA_GEMV_MAX_T) return carve_whole(L, T, PEQA_OP_FWD);
+    if (op == PEQA_OP_FWD_Z && T > PEQA_GEMV_MAX_T) return carve_whole(L, T, PEQA_OP_FWD, cus);
     if (op == PEQA_OP_BWD_Z) {
         // the plain backward's needs (sums of X among them), then the partials of the zero-point gradient
-        Workspace w = carve_whole(L, T, PEQA_OP_BWD);
+        Workspace w = carve_whole(L, T, PEQA_OP_BWD, cus);
         const size_t slices = ((size_t)T + peqa::KEPT_ROWS - 1) / peqa::KEPT_ROWS;
         const size_t NG = (size_t)L->n_out * (size_t)groups(L);
         w.zpartial = w.total; w.total += round256(slices * NG * sizeof(float));
@@ -59,7 +59,7 @@ Workspace carve_whole(const peqa_layout *L, int32_t T, int32_t op)
     if ((op == PEQA_OP_FWD || op == PEQA_OP_FWD_Z) && T <= PEQA_GEMV_MAX_T) {
         // the fewest slices (with a trained zero-point offset LDS holds fewer groups of a group-wise layer: more slices)
         const GemvItem one{L, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
-        w.partial = off; off += round256(gemv_partial_bytes(1, &one, T, op == PEQA_OP_FWD, 0));
+        w.partial = off; off += round256(gemv_partial_bytes(1, &one, T, op == PEQA_OP_FWD, 0, cus));
         if (off == 0) off = 256;                               // a single slice needs none; 0 would read as "invalid"
         w.total = off;
         return w;
@@ -91,9 +91,9 @@ Workspace carve_whole(const peqa_layout *L, int32_t T, int32_t op)
 }
 
 // The regions of carve_whole, then those of the split contractions.
-Workspace carve(const peqa_layout *L, int32_t T, int32_t op)
+Workspace carve(const peqa_layout *L, int32_t T, int32_t op, int cus)
 {
-    Workspace w = carve_whole(L, T, op);
+    Workspace w = carve_whole(L, T, op, cus);
     w.min_total = w.total;
     w.split_y = w.split_dx = w.split_dds = w.split_dx_alone = 1;
     w.gemv_most = GEMV_ANY;
@@ -102,7 +102,7 @@ Workspace carve(const peqa_layout *L, int32_t T, int32_t op)
         const GemvItem one{L, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
         // as for T > 16 below: a forward that peqa_linear_fwd_static takes with the fewest slices is planned for its scratch
         if (op == PEQA_OP_FWD && w.total <= (size_t)PEQA_STATIC_SCRATCH_BYTES) w.gemv_most = PEQA_STATIC_SCRATCH_BYTES;
-        const size_t planned = w.partial + round256(gemv_partial_bytes(1, &one, T, op == PEQA_OP_FWD, w.gemv_most));
+        const size_t planned = w.partial + round256(gemv_partial_bytes(1, &one, T, op == PEQA_OP_FWD, w.gemv_most, cus));
         w.total = planned > w.total ? planned : w.total;
         return w;
     }
@@ -114,19 +114,19 @@ Workspace carve(const peqa_layout *L, int32_t T, int32_t op)
         size_t most = ~(size_t)0;
         if (w.total <= (size_t)PEQA_STATIC_SCRATCH_BYTES) most = (size_t)PEQA_STATIC_SCRATCH_BYTES - w.total;
         peqa::SplitJob j = y;
-        peqa::gemm_plan_splits(1, &j, grouped(L), true, most);
+        peqa::gemm_plan_splits(1, &j, grouped(L), true, most, cus);
         w.split_y = j.split;
         w.acc = w.total;
         if (j.split > 1) w.total += round256((size_t)j.split * y_bytes);
         return w;
     }
     peqa::SplitJob alone = dx;
-    peqa::gemm_plan_splits(1, &alone, grouped(L), true, ~(size_t)0);
+    peqa::gemm_plan_splits(1, &alone, grouped(L), true, ~(size_t)0, cus);
     w.split_dx = w.split_dx_alone = alone.split;
     if (!grouped(L) && op != PEQA_OP_BWD_KEPT) {
         peqa::SplitJob both[2] = {y, dx};
         both[0].out_bytes = 0;
-        peqa::gemm_plan_splits(2, both, false, false, ~(size_t)0);
+        peqa::gemm_plan_splits(2, both, false, false, ~(size_t)0, cus);
         w.split_dds = both[0].split;
         w.split_dx = both[1].split;
     }
@@ -142,6 +142,19 @@ Workspace carve(const peqa_layout *L, int32_t T, int32_t op)
 void fit_workspace(Workspace &w, size_t bytes)
 {
     if (bytes < w.total) w.split_y = w.split_dx = w.split_dds = w.split_dx_alone = 1;
+}
+
+// The regions of a call with a workspace of `bytes`, checked before the device is touched.
+peqa_status plan_call(Workspace &w, const peqa_layout *L, int32_t T, int32_t op, const void *workspace, size_t bytes)
+{
+    w = carve(L, T, op, peqa::PLAN_UNITS);
+    if (!workspace || bytes < w.min_total) return PEQA_ERR_WORKSPACE;
+    if (!aligned16(workspace)) return PEQA_ERR_ALIGN;
+    const int cus = peqa::compute_units();
+    if (cus != peqa::PLAN_UNITS) w = carve(L, T, op, cus);
+    if (bytes < w.min_total) return PEQA_ERR_WORKSPACE;
+    fit_workspace(w, bytes);
+    return PEQA_OK;
 }
 
 // One contraction with `split` pieces: the launch, and the sum of its pieces.
@@ -203,7 +216,7 @@ size_t peqa_workspace_bytes(const peqa_layout *L, int32_t T, int32_t op)
     } else if (op != PEQA_OP_FWD && op != PEQA_OP_BWD && op != PEQA_OP_FWD_Z && op != PEQA_OP_BWD_Z) {
         return 0;
     }
-    return carve(L, T, op).total;
+    return carve(L, T, op, peqa::PLAN_UNITS).total;
 }
 
 peqa_status peqa_set_option(int32_t option, int32_t value)
@@ -301,10 +314,9 @@ static peqa_status fwd_impl(const peqa_layout *L, const uint32_t *packed, const 
     if (!aligned16(packed) || !aligned16(s0) || !aligned16(z0) || !aligned16(X) || !aligned16(Y) ||
         (ds && !aligned16(ds)) || (dz && !aligned16(dz)))
         return PEQA_ERR_ALIGN;
-    Workspace w = carve(L, T, dz ? PEQA_OP_FWD_Z : PEQA_OP_FWD);
-    if (!workspace || workspace_bytes < w.min_total) return PEQA_ERR_WORKSPACE;
-    fit_workspace(w, workspace_bytes);
-    if (!aligned16(workspace)) return PEQA_ERR_ALIGN;
+    Workspace w;
+    st = plan_call(w, L, T, dz ? PEQA_OP_FWD_Z : PEQA_OP_FWD, workspace, workspace_bytes);
+    if (st != PEQA_OK) return st;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint8_t *ws = static_cast<uint8_t *>(workspace);
@@ -383,7 +395,7 @@ peqa_status peqa_linear_fwd_static(const peqa_layout *L, const uint32_t *packed,
     peqa_status st = peqa_check_layout(L);
     if (st != PEQA_OK) return st;
     if (T < 1 || T > (1 << 24)) return PEQA_ERR_SHAPE;
-    if (carve(L, T, PEQA_OP_FWD).min_total > (size_t)PEQA_STATIC_SCRATCH_BYTES) return PEQA_ERR_WORKSPACE;
+    if (carve(L, T, PEQA_OP_FWD, peqa::PLAN_UNITS).min_total > (size_t)PEQA_STATIC_SCRATCH_BYTES) return PEQA_ERR_WORKSPACE;
     if (!packed || !s0 || !z0 || !X || !Y) return PEQA_ERR_NULL;    // before the device is touched
     void *ws = nullptr;
     st = static_scratch(&ws);
@@ -410,10 +422,9 @@ peqa_status peqa_linear_fwd_keep(const peqa_layout *L, const uint32_t *packed, c
     if (!aligned16(packed) || !aligned16(s0) || !aligned16(z0) || !aligned16(X) || !aligned16(Y) || !aligned16(P) ||
         (ds && !aligned16(ds)))
         return PEQA_ERR_ALIGN;
-    Workspace w = carve(L, T, PEQA_OP_FWD_KEEP);
-    if (!workspace || workspace_bytes < w.min_total) return PEQA_ERR_WORKSPACE;
-    fit_workspace(w, workspace_bytes);
-    if (!aligned16(workspace)) return PEQA_ERR_ALIGN;
+    Workspace w;
+    st = plan_call(w, L, T, PEQA_OP_FWD_KEEP, workspace, workspace_bytes);
+    if (st != PEQA_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint8_t *ws = static_cast<uint8_t *>(workspace);
     float *rs = reinterpret_cast<float *>(ws + w.rs);
@@ -462,12 +473,12 @@ size_t peqa_workspace_bytes_fused(int32_t n, const peqa_fwd_item *items, int32_t
     if (T <= PEQA_GEMV_MAX_T) {
         GemvItem gi[PEQA_MAX_FUSED]{};
         for (int j = 0; j < n; ++j) gi[j].L = &items[j].layout;
-        const size_t b = round256(gemv_partial_bytes(n, gi, T, true, GEMV_ANY));
+        const size_t b = round256(gemv_partial_bytes(n, gi, T, true, GEMV_ANY, peqa::PLAN_UNITS));
         return b ? b : 256;
     }
     size_t need = 0;                                       // layer by layer: the largest single need
     for (int j = 0; j < n; ++j) {
-        const size_t b = carve(&items[j].layout, T, PEQA_OP_FWD).total;
+        const size_t b = carve(&items[j].layout, T, PEQA_OP_FWD, peqa::PLAN_UNITS).total;
         need = b > need ? b : need;
     }
     return need;
@@ -492,11 +503,11 @@ static peqa_status fwd_fused_impl(int32_t n, const peqa_fwd_item *items, const u
     if (T <= PEQA_GEMV_MAX_T) {
         GemvItem gi[PEQA_MAX_FUSED]{};
         for (int j = 0; j < n; ++j) gi[j].L = &items[j].layout;
-        need = round256(gemv_partial_bytes(n, gi, T, true, 0));
+        need = round256(gemv_partial_bytes(n, gi, T, true, 0, peqa::PLAN_UNITS));
         need = need ? need : 256;
     } else {
         for (int j = 0; j < n; ++j) {
-            const size_t b = carve(&items[j].layout, T, PEQA_OP_FWD).min_total;
+            const size_t b = carve(&items[j].layout, T, PEQA_OP_FWD, peqa::PLAN_UNITS).min_total;
             need = b > need ? b : need;
         }
     }
@@ -520,7 +531,7 @@ static peqa_status fwd_fused_impl(int32_t n, const peqa_fwd_item *items, const u
         }
         for (int j = 0; j < n; ++j) {
             const peqa_fwd_item &it = items[j];
-            Workspace w = carve(&it.layout, T, PEQA_OP_FWD);
+            Workspace w = carve(&it.layout, T, PEQA_OP_FWD, peqa::compute_units());
             fit_workspace(w, workspace_bytes);
             st = fwd_per_channel(&it.layout, it.packed, it.s0, it.ds, it.z0, nullptr, X, T, it.Y, nullptr, rs, w.split_y,
                                  reinterpret_cast<float *>(static_cast<uint8_t *>(workspace) + w.acc), s);
@@ -564,10 +575,9 @@ static peqa_status bwd_impl(const peqa_layout *L, const uint32_t *packed, const 
         (ds && !aligned16(ds)) || (dX && !aligned16(dX)) || (d_ds && !aligned16(d_ds)) || (dz && !aligned16(dz)) ||
         (d_dz && !aligned16(d_dz)))
         return PEQA_ERR_ALIGN;
-    Workspace w = carve(L, T, op);
-    if (!workspace || workspace_bytes < w.min_total) return PEQA_ERR_WORKSPACE;
-    fit_workspace(w, workspace_bytes);
-    if (!aligned16(workspace)) return PEQA_ERR_ALIGN;
+    Workspace w;
+    st = plan_call(w, L, T, op, workspace, workspace_bytes);
+    if (st != PEQA_OK) return st;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint8_t *ws = static_cast<uint8_t *>(workspace);
@@ -769,10 +779,9 @@ peqa_status peqa_linear_bwd_kept(const peqa_layout *L, const uint32_t *packed, c
     if (!aligned16(packed) || !aligned16(s0) || !aligned16(z0) || !aligned16(dY) || (P && !aligned16(P)) ||
         (ds && !aligned16(ds)) || (dX && !aligned16(dX)) || (d_ds && !aligned16(d_ds)))
         return PEQA_ERR_ALIGN;
-    Workspace w = carve(L, T, PEQA_OP_BWD_KEPT);
-    if (!workspace || workspace_bytes < w.min_total) return PEQA_ERR_WORKSPACE;
-    fit_workspace(w, workspace_bytes);
-    if (!aligned16(workspace)) return PEQA_ERR_ALIGN;
+    Workspace w;
+    st = plan_call(w, L, T, PEQA_OP_BWD_KEPT, workspace, workspace_bytes);
+    if (st != PEQA_OK) return st;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint8_t *ws = static_cast<uint8_t *>(workspace);
@@ -866,7 +875,8 @@ peqa_status peqa_scale_update_multi(int32_t n, const peqa_update_item *items, co
 namespace peqa {
 namespace host {
 
-static peqa::GemvForm gemv_slicing(int n, const GemvItem *items, int32_t T, bool zbyte, size_t most, int *S, size_t *bytes)
+static peqa::GemvForm gemv_slicing(int n, const GemvItem *items, int32_t T, bool zbyte, size_t most, int cus, int *S,
+                                   size_t *bytes)
 {
     int N[GEMV_MAX_LAYERS], K[GEMV_MAX_LAYERS], chunk[GEMV_MAX_LAYERS];
     for (int j = 0; j < n; ++j) {
@@ -874,16 +884,16 @@ static peqa::GemvForm gemv_slicing(int n, const GemvItem *items, int32_t T, bool
         K[j] = items[j].L->k_in;
         chunk[j] = items[j].L->group_size > 0 ? items[j].L->group_size : items[j].L->k_in;
     }
-    const peqa::GemvForm form = gemv_plan(n, N, K, chunk, items[0].L->bits, T, zbyte, most, S);
+    const peqa::GemvForm form = gemv_plan(n, N, K, chunk, items[0].L->bits, T, zbyte, most, cus, S);
     *bytes = gemv_partials(n, N, T, S);
     return form;
 }
 
-size_t gemv_partial_bytes(int n, const GemvItem *items, int32_t T, bool zbyte, size_t most)
+size_t gemv_partial_bytes(int n, const GemvItem *items, int32_t T, bool zbyte, size_t most, int cus)
 {
     int S[GEMV_MAX_LAYERS];
     size_t bytes = 0;
-    (void)gemv_slicing(n, items, T, zbyte, most, S, &bytes);
+    (void)gemv_slicing(n, items, T, zbyte, most, cus, S, &bytes);
     return bytes;
 }
 
@@ -893,8 +903,10 @@ peqa_status gemv_forward(int n, const GemvItem *items, int32_t T, size_t most, f
     size_t bytes = 0;
     bool zbyte = true;                                         // the launch takes the same decision from the same pointers
     for (int j = 0; j < n; ++j) zbyte = zbyte && items[j].dz == nullptr;
-    peqa::GemvForm form = gemv_slicing(n, items, T, zbyte, most, S, &bytes);
-    if (bytes > partial_bytes) form = gemv_slicing(n, items, T, zbyte, 0, S, &bytes);
+    const int cus = compute_units();
+    peqa::GemvForm form = gemv_slicing(n, items, T, zbyte, most, cus, S, &bytes);
+    if (bytes > partial_bytes) form = gemv_slicing(n, items, T, zbyte, 0, cus, S, &bytes);
+    if (bytes > partial_bytes) return PEQA_ERR_WORKSPACE;      // (the callers have seen to it)
     GemvArgs g{};
     int wgs = 0;
     size_t poff = 0;                                           // in floats
@@ -933,10 +945,10 @@ int compute_units()
 {
     static std::atomic<int> known[64];
     int dev = -1, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return PLAN_UNITS;
     cus = known[dev].load(std::memory_order_relaxed);
     if (cus > 0) return cus;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) return 256;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) return PLAN_UNITS;
     known[dev].store(cus, std::memory_order_relaxed);
     return cus;
 }

@@ -60,7 +60,7 @@ struct BlockSpace {
     size_t acc[PEQA_MAX_BLOCK], acc_dds[PEQA_MAX_BLOCK];
 };
 
-BlockSpace carve_block(int32_t n, const peqa_block_item *items, int32_t T, int32_t op)
+BlockSpace carve_block(int32_t n, const peqa_block_item *items, int32_t T, int32_t op, int cus)
 {
     BlockSpace w{};
     const size_t tiles_t = ((size_t)T + 127) / 128, Tp = ((size_t)T + 63) / 64 * 64;
@@ -100,7 +100,7 @@ BlockSpace carve_block(int32_t n, const peqa_block_item *items, int32_t T, int32
             job[m++] = peqa::SplitJob{(int)tiles_t * ((C + 255) / 256), KC, out_bytes, 1};
         }
         if (m == 0) return;
-        peqa::gemm_plan_splits(m, job, gw, false, ~(size_t)0);
+        peqa::gemm_plan_splits(m, job, gw, false, ~(size_t)0, cus);
         for (int i = 0; i < m; ++i) split[of[i]] = job[i].split;
     };
     if (op == PEQA_OP_FWD) {
@@ -122,13 +122,19 @@ BlockSpace carve_block(int32_t n, const peqa_block_item *items, int32_t T, int32
     return w;
 }
 
-// The regions for a workspace of `bytes`: whole contractions where it is too small for the split ones.
-bool fit_block(BlockSpace &w, int32_t n, const void *workspace, size_t bytes)
+// The regions of a call with a workspace of `bytes`, checked before the device is touched: whole contractions where it is
+// too small for the split ones.
+peqa_status plan_block(BlockSpace &w, int32_t n, const peqa_block_item *items, int32_t T, int32_t op, const void *workspace,
+                       size_t bytes)
 {
-    if (!workspace || bytes < w.min_total) return false;
+    w = carve_block(n, items, T, op, peqa::PLAN_UNITS);
+    if (!workspace || bytes < w.min_total) return PEQA_ERR_WORKSPACE;
+    if (!aligned16(workspace)) return PEQA_ERR_ALIGN;
+    const int cus = peqa::compute_units();
+    if (cus != peqa::PLAN_UNITS) w = carve_block(n, items, T, op, cus);      // (min_total does not hang on the units)
     if (bytes < w.total)
         for (int j = 0; j < n; ++j) w.split_y[j] = w.split_dx[j] = w.split_dds[j] = 1;
-    return true;
+    return PEQA_OK;
 }
 
 // A multi-contraction launch, and the sums of its split contractions.
@@ -201,10 +207,10 @@ size_t peqa_block_workspace_bytes(int32_t n, const peqa_block_item *items, int32
     if (op == PEQA_OP_FWD && T <= GEMV_MAX_T) {
         GemvItem gi[PEQA_MAX_BLOCK]{};
         for (int j = 0; j < n; ++j) gi[j].L = &items[j].layout;
-        const size_t b = round256(gemv_partial_bytes(n, gi, T, true, GEMV_ANY));
+        const size_t b = round256(gemv_partial_bytes(n, gi, T, true, GEMV_ANY, peqa::PLAN_UNITS));
         return b ? b : 256;
     }
-    return carve_block(n, items, T, op).total;
+    return carve_block(n, items, T, op, peqa::PLAN_UNITS).total;
 }
 
 peqa_status peqa_block_fwd(int32_t n, const peqa_block_item *items, int32_t T, void *workspace,
@@ -227,15 +233,15 @@ peqa_status peqa_block_fwd(int32_t n, const peqa_block_item *items, int32_t T, v
         for (int j = 0; j < n; ++j)
             gi[j] = GemvItem{&items[j].layout, items[j].packed, items[j].s0, items[j].ds, items[j].z0, nullptr,
                              items[j].X, items[j].Y};
-        const size_t least = round256(gemv_partial_bytes(n, gi, T, true, 0));
+        const size_t least = round256(gemv_partial_bytes(n, gi, T, true, 0, peqa::PLAN_UNITS));
         if (!workspace || workspace_bytes < (least ? least : 256)) return PEQA_ERR_WORKSPACE;
         if (!aligned16(workspace)) return PEQA_ERR_ALIGN;
         return gemv_forward(n, gi, T, GEMV_ANY, reinterpret_cast<float *>(ws), workspace_bytes, s);
     }
 
-    BlockSpace w = carve_block(n, items, T, PEQA_OP_FWD);
-    if (!fit_block(w, n, workspace, workspace_bytes)) return PEQA_ERR_WORKSPACE;
-    if (!aligned16(workspace)) return PEQA_ERR_ALIGN;
+    BlockSpace w;
+    st = plan_block(w, n, items, T, PEQA_OP_FWD, workspace, workspace_bytes);
+    if (st != PEQA_OK) return st;
     int xi[PEQA_MAX_BLOCK], ks[PEQA_MAX_BLOCK];
     const uint16_t *xs[PEQA_MAX_BLOCK];
     const int nx = distinct_inputs(n, items, xi, xs, ks);
@@ -320,9 +326,9 @@ peqa_status peqa_block_bwd(int32_t n, const peqa_block_item *items, int32_t T, v
             (it.d_ds && !aligned16(it.d_ds)) || (it.row_sums && !aligned16(it.row_sums)))
             return PEQA_ERR_ALIGN;
     }
-    BlockSpace w = carve_block(n, items, T, PEQA_OP_BWD);
-    if (!fit_block(w, n, workspace, workspace_bytes)) return PEQA_ERR_WORKSPACE;
-    if (!aligned16(workspace)) return PEQA_ERR_ALIGN;
+    BlockSpace w;
+    st = plan_block(w, n, items, T, PEQA_OP_BWD, workspace, workspace_bytes);
+    if (st != PEQA_OK) return st;
     uint8_t *ws = static_cast<uint8_t *>(workspace);
     hipStream_t s = static_cast<hipStream_t>(stream);
     int xi[PEQA_MAX_BLOCK], ks[PEQA_MAX_BLOCK];

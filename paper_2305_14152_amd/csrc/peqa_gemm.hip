@@ -265,9 +265,8 @@ int gemm_multi_wgs(const GemmArgs &a) { return (a.tiles_t * a.tiles_c * pieces(a
 //   13B block 3-bit g128, forward     239 ->  93      240 -> 113      whole
 //                         backward    708 -> 310      749 -> 393      953 -> 853
 //   4096 x 11008 4-bit alone, forward 103 ->  28      107 ->  37      112 ->  72
-void gemm_plan_splits(int n, SplitJob *jobs, bool grouped, bool single, size_t max_bytes)
+void gemm_plan_splits(int n, SplitJob *jobs, bool grouped, bool single, size_t max_bytes, int cus)
 {
-    const int cus = compute_units();
     int longest = 0;
     for (int j = 0; j < n; ++j) {
         jobs[j].split = 1;

@@ -404,9 +404,9 @@ static int gv_cols(int K, int chunk, int S)                        // most scale
 // below 4 % of the codes.
 //
 // Slicings whose partial sums take more than `most` bytes are left out; where none remains, the fewest slices are taken.
-GemvForm gemv_plan(int n, const int *N, const int *K, const int *chunk, int bits, int T, bool zbyte, size_t most, int *S)
+GemvForm gemv_plan(int n, const int *N, const int *K, const int *chunk, int bits, int T, bool zbyte, size_t most, int cus, int *S)
 {
-    const int cus = compute_units(), nx = T > 8 ? 2 : 1;
+    const int nx = T > 8 ? 2 : 1;
     int tiles = 0, rmax = 0;
     double rounds = 0.0;
     for (int j = 0; j < n; ++j) {

@@ -34,9 +34,9 @@ struct GemvItem {
 // fp32 partials of the sliced layers of a matrix-vector launch (gemv_plan).  `zbyte`: no item has a trained zero-point
 // offset (dz); `most`: GEMV_ANY, 0 for the fewest slices, or what the partials may take.
 constexpr size_t GEMV_ANY = ~(size_t)0;
-size_t gemv_partial_bytes(int n, const GemvItem *items, int32_t T, bool zbyte, size_t most);
+size_t gemv_partial_bytes(int n, const GemvItem *items, int32_t T, bool zbyte, size_t most, int cus);
 // One matrix-vector launch (plus the sum of the slices, if any) for n <= GEMV_MAX_LAYERS layers of one bit width, planned
-// with `most`; with the fewest slices where `partial_bytes` is less than that plan's need.
+// with `most` for the current device; with the fewest slices where `partial_bytes` is less than that plan's need.
 peqa_status gemv_forward(int n, const GemvItem *items, int32_t T, size_t most, float *partial, size_t partial_bytes, hipStream_t s);
 
 }  // namespace host

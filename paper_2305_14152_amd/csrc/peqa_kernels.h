@@ -67,8 +67,8 @@ struct SplitJob {
     int split;                // out
 };
 // single: the jobs are one contraction that runs by itself (launch_gemm), which may take the eight-wave form.
-// max_bytes: the most the partial results may take.
-void gemm_plan_splits(int n, SplitJob *jobs, bool grouped, bool single, size_t max_bytes);
+// max_bytes: the most the partial results may take.  cus: compute units.
+void gemm_plan_splits(int n, SplitJob *jobs, bool grouped, bool single, size_t max_bytes, int cus);
 // Epilogue of the split MODE_Y / MODE_DX contractions of a launch: adds the pieces in order, then does what the tile's own
 // epilogue would have done.  Jobs with split 1 are skipped.
 constexpr int FINISH_MAX = 8;
@@ -218,7 +218,8 @@ struct GemvForm {
 };
 // The form, and the slices of every layer (S[0..n)).  zbyte: no layer has a trained zero-point offset, so zero-points are
 // bytes in LDS.  most: the most bytes that the partial sums of the slices may take; 0 gives the fewest slices that LDS allows.
-GemvForm gemv_plan(int n, const int *N, const int *K, const int *chunk, int bits, int T, bool zbyte, size_t most, int *S);
+// cus: compute units.
+GemvForm gemv_plan(int n, const int *N, const int *K, const int *chunk, int bits, int T, bool zbyte, size_t most, int cus, int *S);
 // fp32 partial sums of the layers with S > 1
 size_t gemv_partials(int n, const int *N, int T, const int *S);
 hipError_t launch_gemv(int bits, const GemvForm &f, const GemvArgs &a, hipStream_t stream);
@@ -284,7 +285,10 @@ bool quantize_resident_fits(int K, int G, bool search);
 hipError_t launch_quantize_search(const float *W0, int N, int K, int bits, int group, int n_ratios, float step,
                                   uint32_t *packed, float *s0, uint8_t *z0, hipStream_t stream);
 
-// Compute units of the current device (looked up once per device; 256, an MI355X's, where there is none).
+// What the size queries, and the checks that a call makes before it touches the device, plan for: a whole MI355X.  A call on
+// a device of fewer units (a partition of one) then plans for those, which needs no more at least.
+constexpr int PLAN_UNITS = 256;
+// Compute units of the current device (looked up once per device; PLAN_UNITS where there is none).
 int compute_units();
 
 // Tracing hook: every launch goes through these so that peqa_trace_* can time it.

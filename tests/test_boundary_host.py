@@ -292,3 +292,48 @@ def test_group_wise_backward_asks_for_what_it_uses(peqa, bits, N, K, group, T):
         peqa.set_option(peqa.PEQA_OPT_GEMM_WAVES, 0)
     assert single == r(8 * N * G) + r(4 * T * G) + r(4 * tiles * N * G) + r(2 * K * Tp) + r(2 * N * Tp) + chunks
     assert block == r(8 * N * G) + r(2 * K * Tp) + r(2 * N * Tp) + chunks
+
+
+_QUERIES = """
+import ctypes, sys
+lib = ctypes.CDLL(sys.argv[1])
+class Layout(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in ("n_out", "k_in", "bits", "group_size")]
+class Fused(ctypes.Structure):
+    _fields_ = [("layout", Layout)] + [(n, ctypes.c_void_p) for n in ("packed", "s0", "ds", "z0", "Y")]
+class Item(ctypes.Structure):
+    _fields_ = [("layout", Layout)] + [(n, ctypes.c_void_p) for n in ("packed", "s0", "ds", "z0", "X", "Y", "dY", "dX", "d_ds", "row_sums")]
+p = ctypes.c_void_p(4096)
+for group in (0, 128):
+    L = Layout(4096, 11008, 4, group)
+    fused, item = Fused(layout=L), Item(layout=L, packed=4096, s0=4096, z0=4096, X=4096, Y=4096, dY=4096, d_ds=4096)
+    for T in (1, 40, 2048):
+        for op in range(6):
+            lib.peqa_workspace_bytes(ctypes.byref(L), T, op)
+        lib.peqa_workspace_bytes_fused(1, ctypes.byref(fused), T)
+        for op in (0, 1):
+            lib.peqa_block_workspace_bytes(1, ctypes.byref(item), T, op)
+        # calls that are refused: no workspace
+        assert lib.peqa_linear_fwd(ctypes.byref(L), p, p, None, p, p, T, p, None, ctypes.c_size_t(0), None) == 6
+        assert lib.peqa_linear_bwd(ctypes.byref(L), p, p, None, p, p, p, T, p, p, None, ctypes.c_size_t(0), None) == 6
+        assert lib.peqa_block_fwd(1, ctypes.byref(item), T, None, ctypes.c_size_t(0), None) == 6
+        assert lib.peqa_block_bwd(1, ctypes.byref(item), T, None, ctypes.c_size_t(0), None) == 6
+        assert lib.peqa_linear_fwd_static(ctypes.byref(L), None, p, None, p, p, T, p, None) in (1, 6)
+print("QUERIES DONE", file=sys.stderr, flush=True)
+a, b = ctypes.c_int32(), ctypes.c_int32()
+lib.peqa_device_info(ctypes.byref(a), ctypes.byref(b))
+"""
+
+
+def test_queries_and_refusals_do_not_touch_the_device(peqa):
+    """The size queries are host-only, and a call that is refused is refused before the runtime is asked for a device: the
+    HIP runtime's own call log stays empty until the one call that does ask."""
+    import subprocess
+    import sys
+    r = subprocess.run([sys.executable, "-c", _QUERIES, peqa.LIB_PATH], stderr=subprocess.PIPE, text=True, timeout=120,
+                       env=dict(os.environ, AMD_LOG_LEVEL="3"))
+    assert r.returncode == 0, r.stderr[-2000:]
+    before, _, after = r.stderr.partition("QUERIES DONE")
+    if "hipGetDevice" not in after:
+        pytest.skip("this HIP runtime writes no call log")
+    assert "hip" not in before.replace(peqa.LIB_PATH, ""), before[-2000:]

@@ -187,12 +187,13 @@ def _small_batch_form(peqa, shapes, bits, group, T):
     class Form(ctypes.Structure):
         _fields_ = [("h", ctypes.c_int), ("waves", ctypes.c_int)]
 
-    plan = peqa.lib()._ZN4peqa9gemv_planEiPKiS1_S1_iibmPi      # peqa::gemv_plan
+    plan = peqa.lib()._ZN4peqa9gemv_planEiPKiS1_S1_iibmiPi      # peqa::gemv_plan
     plan.restype = Form
     ints = ctypes.c_int * len(shapes)
     S = ints()
     f = plan(len(shapes), ints(*[n for n, _ in shapes]), ints(*[k for _, k in shapes]),
-             ints(*[group or k for _, k in shapes]), bits, T, True, ctypes.c_size_t(2 ** 64 - 1), S)
+             ints(*[group or k for _, k in shapes]), bits, T, True, ctypes.c_size_t(2 ** 64 - 1),
+             256, S)
     return f.h, f.waves, list(S)
 
 
