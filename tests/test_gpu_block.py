@@ -155,6 +155,24 @@ def test_block_step_of_few_tokens_with_row_sums(gpu, oracle, bits, T):
             d["dX"].zero_(), d["d_ds"].zero_()
 
 
+@pytest.mark.parametrize("bits,T", [(4, 9), (3, 40), (4, 200)])
+def test_block_of_mixed_group_sizes(gpu, oracle, bits, T):
+    """Per-channel items, groups that the token contraction completes (64, 128) and groups whose chunks are added up after it
+    (192, 384) behind one call, some of them on one input."""
+    print("mixed groups bits=%d T=%d" % (bits, T), flush=True)
+    seed = 34600 + 100 * bits + T
+    X, X2 = synth.normal_bf16(seed, (T, 384), 1.0), synth.normal_bf16(seed + 1, (T, 768), 1.0)
+    members = [Member(gpu, oracle, seed + 50 * j, bits, N, x.shape[1], group, T, X=x, with_ds=j % 2 == 0)
+               for j, (N, x, group) in enumerate([(256, X, 192), (128, X, 0), (384, X, 128), (128, X2, 384), (256, X2, 64),
+                                                  (384, X2, 0), (256, X2, 192)])]
+    for m, d in zip(members, _run_block(gpu, members, T, backward=True)):
+        Yref = oracle.fwd(m.codes, m.s0, m.ds, m.z0, m.X, m.group)
+        assert np.abs(gpu.bf16_dev_to_f64(d["Y"]) - Yref).max() <= Y_TOL * np.abs(Yref).max(), (m.N, m.K, m.group)
+        dXref, gref, _ = oracle.bwd(m.codes, m.s0, m.ds, m.z0, m.X, m.dY, m.group)
+        assert np.abs(gpu.bf16_dev_to_f64(d["dX"]) - dXref).max() <= Y_TOL * np.abs(dXref).max(), (m.N, m.K, m.group)
+        gpu.assert_scale_grad_close(gpu.to_host(d["d_ds"]), gref)
+
+
 def test_block_fills_every_row_sums_array(gpu, oracle):
     """Items that share X may share one array of row sums or bring their own: each is filled, and a backward over any of
     the items reads sums that are there."""
