@@ -35,23 +35,33 @@ def check_no_scratch(remarks):
     return bad
 
 
-# Wait states that gfx950 wants between a vector instruction and a matrix instruction that reads a register it wrote.  The
-# compiler keeps them for what it emits itself; a write in inline assembly is unknown to it, so the built code is looked at.
-MATRIX_READ_WAIT = 2
-_REGISTERS = re.compile(r"\b([va])(?:\[(\d+):(\d+)\]|(\d+)\b)")
+# Wait states that gfx950 wants between an instruction that writes a register and one that reads it, where the hardware does not
+# wait by itself.  The compiler keeps them between instructions that it emits itself; reads and writes in inline assembly are
+# unknown to it, so the built code is looked at.  Of every rule: the readers, the writers, the registers, the wait states.
+_MATRIX, _MEMORY = ("v_mfma", "v_smfmac"), ("global_", "buffer_", "flat_", "scratch_")
+_RULES = (
+    (lambda name: name.startswith(_MATRIX), lambda name: name.startswith("v_") and not name.startswith(_MATRIX), "va", 2),
+    (lambda name: name.startswith(_MEMORY), lambda name: name.startswith("v_"), "s", 5),
+    (lambda name: name.endswith("_dpp"), lambda name: name.startswith("v_") and not name.startswith(_MATRIX), "v", 2),
+)
+_REGISTERS = re.compile(r"\b([vas])(?:\[(\d+):(\d+)\]|(\d+)\b)")
 _TARGET = re.compile(r"<(\S+?)(?:\+0x([0-9a-f]+))?>\s*$")
 
 
-def _registers(operand):
+def _registers(operands, kinds):
     found = set()
-    for kind, lo, hi, one in _REGISTERS.findall(operand):
-        found.update((kind, i) for i in range(int(lo or one), int(hi or one) + 1))
+    for operand in operands:
+        for kind, lo, hi, one in _REGISTERS.findall(operand):
+            if kind in kinds:
+                found.update((kind, i) for i in range(int(lo or one), int(hi or one) + 1))
+        if "s" in kinds and "vcc" in operand:
+            found.add("vcc")
     return found
 
 
-def early_matrix_reads(listing):
-    """Matrix instructions of a disassembly (llvm-objdump -d) that read a register fewer than MATRIX_READ_WAIT wait states
-    after a vector instruction wrote it, on any path into them: one line of text each."""
+def early_reads(listing):
+    """Instructions of a disassembly (llvm-objdump -d) that read a register too few wait states after it was written, on any
+    path into them: one line of text each."""
     code, entry, function = [], {}, None                   # code: (function, address, mnemonic, operands, branch target)
     for line in listing.splitlines():
         label = re.match(r"([0-9a-f]+) <(.+)>:$", line)
@@ -71,23 +81,26 @@ def early_matrix_reads(listing):
             jumps.setdefault(index[entry[c[4][0]] + c[4][1]], []).append(i)
     bad = []
     for i, (function, address, mnemonic, operands, _) in enumerate(code):
-        if not mnemonic.startswith(("v_mfma", "v_smfmac")):
-            continue
-        reads = set().union(*(_registers(o) for o in operands[1:]))
-        front = [(i, 0)]                                   # (instruction, wait states from its end to the matrix instruction)
-        while front:
-            here, waited = front.pop()
-            before = list(jumps.get(here, ()))
-            if here > 0 and code[here - 1][0] == function and code[here - 1][2] not in ("s_branch", "s_endpgm", "s_setpc_b64"):
-                before.append(here - 1)
-            for p in before:
-                _, at, name, ops, _ = code[p]
-                if name.startswith("v_") and not name.startswith(("v_mfma", "v_smfmac")) and _registers(ops[0]) & reads:
-                    bad.append("%s: %s at %x reads what %s at %x wrote, after %d wait states" %
-                               (function, mnemonic, address, name, at, waited))
-                states = waited + (int(ops[0]) + 1 if name == "s_nop" else 1)
-                if states < MATRIX_READ_WAIT:
-                    front.append((p, states))
+        for reads_here, writes_there, kinds, wanted in _RULES:
+            if not reads_here(mnemonic):
+                continue
+            # everything but a destination is read (of a store or a load into LDS, the first operand too)
+            reads = _registers(operands if kinds == "s" else operands[1:], kinds)
+            front = [(i, 0)]                               # (instruction, wait states from its end to the reader)
+            while front and reads:
+                here, waited = front.pop()
+                before = list(jumps.get(here, ()))
+                if here > 0 and code[here - 1][0] == function and code[here - 1][2] not in ("s_branch", "s_endpgm", "s_setpc_b64"):
+                    before.append(here - 1)
+                for p in before:
+                    _, at, name, ops, _ = code[p]
+                    written = ops[:2] if "_co_" in name or "div_scale" in name else ops[:1]
+                    if writes_there(name) and _registers(written, kinds) & reads:
+                        bad.append("%s: %s at %x reads what %s at %x wrote, after %d wait states instead of %d" %
+                                   (function, mnemonic, address, name, at, waited, wanted))
+                    states = waited + (int(ops[0]) + 1 if name == "s_nop" else 1)
+                    if states < wanted:
+                        front.append((p, states))
     return bad
 
 
@@ -141,10 +154,10 @@ def build(verbose=False, extra=(), jobs=None):
     r = subprocess.run(link, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + _quiet(r.stdout))
-    early = [b for text in device_listings(LIB) for b in early_matrix_reads(text)]
+    early = [b for text in device_listings(LIB) for b in early_reads(text)]
     if early:
         os.remove(LIB)
-        raise RuntimeError("matrix instructions too close behind the vector instructions they depend on:\n" + "\n".join(early))
+        raise RuntimeError("reads too close behind the writes they depend on:\n" + "\n".join(early))
     out = _quiet(remarks)
     if verbose and out.strip():
         print(out)

@@ -334,7 +334,9 @@ __device__ __forceinline__ void mfma_result_fence()
 // serialise the ring with a conservative vmcnt(0); completion is tracked by hand with wait_vmcnt().
 __device__ __forceinline__ void dma16(uint32_t voff, const void *sbase, uint32_t lds_dst)
 {
-    // sbase is the same in every lane; saying so keeps it in scalar registers wherever the compiler cannot tell
+    // sbase is the same in every lane; saying so keeps it in scalar registers wherever the compiler cannot tell.  Where that
+    // takes an instruction, a vector one, the hardware wants five wait states before the DMA and gets two here: callers keep
+    // their pointers scalar, or form them well ahead (the build looks at the code that comes out, see build.py).
     const uint64_t u = (uint64_t)(uintptr_t)sbase;
     const uint64_t ub = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(u >> 32)) << 32) |
                         (uint32_t)__builtin_amdgcn_readfirstlane((int)u);

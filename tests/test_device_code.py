@@ -1,5 +1,5 @@
-"""The built device code: no matrix instruction reads a register sooner after a vector write than the hardware allows (the
-compiler does not see writes in inline assembly, so nothing else would notice), and no kernel that counts its outstanding
+"""The built device code: no instruction reads a register sooner after it was written than the hardware allows (the compiler
+does not see reads and writes in inline assembly, so nothing else would notice), and no kernel that counts its outstanding
 memory operations by hand may spill registers unnoticed."""
 import os
 import re
@@ -18,24 +18,38 @@ LISTING = """
 	s_cbranch_scc1 65530                                       // 000000001024: 00000000 <kernel+0x8>
 	ds_read_b128 v[8:11], v2                                   // 000000001028: 00000000 00000000
 	v_mfma_f32_16x16x32_bf16 a[0:3], v[8:11], v[12:15], a[0:3] // 000000001030: 00000000 00000000
-	s_endpgm                                                   // 000000001038: 00000000
+	v_readfirstlane_b32 s5, v5                                 // 000000001038: 00000000
+	v_readfirstlane_b32 s8, v6                                 // 00000000103C: 00000000
+	s_mov_b32 m0, s11                                          // 000000001040: 00000000
+	s_nop 2                                                    // 000000001044: 00000000
+	global_load_lds_dwordx4 v82, s[4:5]                        // 000000001048: 00000000 00000000
+	global_load_lds_dwordx4 v82, s[8:9]                        // 000000001050: 00000000 00000000
+	v_mov_b32_e32 v1, v2                                       // 000000001058: 00000000
+	s_nop 0                                                    // 00000000105C: 00000000
+	v_mov_b32_dpp v3, v1 quad_perm:[1,0,3,2]                   // 000000001060: 00000000 00000000
+	s_endpgm                                                   // 000000001068: 00000000
 """
 
 
 def test_the_check_sees_what_it_is_for():
-    """One wait state in straight-line code; one over a backward branch; two, and writes of other registers, pass."""
-    found = build.early_matrix_reads(LISTING)
-    assert len(found) == 2
-    assert "1008 reads what v_and_or_b32 at 1000 wrote, after 1 wait" in found[0]
-    assert "1008 reads what v_lshrrev_b32_e32 at 1020 wrote, after 1 wait" in found[1]
+    """Matrix operands: one wait state of two, in straight-line code and over a backward branch.  A lane exchange: one of two.
+    A memory instruction's scalar address: five, and four once the s_nop is shorter.  What waits long enough passes."""
+    found = build.early_reads(LISTING)
+    expected = ["1008 reads what v_and_or_b32 at 1000 wrote, after 1", "1008 reads what v_lshrrev_b32_e32 at 1020 wrote, after 1",
+                "1060 reads what v_mov_b32_e32 at 1058 wrote, after 1"]
+    assert len(found) == len(expected), found
+    for text, want in zip(found, expected):
+        assert want in text
+    closer = build.early_reads(LISTING.replace("s_nop 2 ", "s_nop 1 "))
+    assert [f for f in closer if f not in found and "1048 reads what v_readfirstlane_b32 at 1038 wrote, after 4" in f]
 
 
-def test_no_matrix_instruction_reads_too_early():
+def test_no_instruction_reads_too_early():
     peqa.lib()
     assert os.path.exists(build.LIB)
     listings = build.device_listings(build.LIB)
     assert sum("v_mfma" in text for text in listings) >= 3           # the tiled, the token and the T <= 16 contraction
-    assert [b for text in listings for b in build.early_matrix_reads(text)] == []
+    assert [b for text in listings for b in build.early_reads(text)] == []
 
 
 def test_spills_are_refused_in_every_kernel_that_counts():
