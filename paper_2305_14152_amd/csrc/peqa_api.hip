@@ -24,6 +24,7 @@ struct Workspace {
     size_t min_total;
     int split_y, split_dx, split_dds;      // split_dx, split_dds: of the backward that computes both gradients
     int split_dx_alone;
+    int rt_y, rt_dx_alone;                 // row tiles per tile of those launches (the pair's: gemm_row_tiles(T))
     size_t acc, acc_dds;
     size_t gemv_most;                      // T <= 16: the most bytes that the plan's partial sums may take
 };
@@ -107,26 +108,27 @@ Workspace carve(const peqa_layout *L, int32_t T, int32_t op, int cus)
         return w;
     }
     const int N = L->n_out, K = L->k_in, tiles_t = (T + 127) / 128;
+    w.rt_y = w.rt_dx_alone = peqa::gemm_row_tiles(T);
     const size_t y_bytes = (size_t)T * N * sizeof(float), dx_bytes = (size_t)T * K * sizeof(float);
-    const peqa::SplitJob y{tiles_t * ((N + 255) / 256), K, y_bytes, 1}, dx{tiles_t * ((K + 255) / 256), N, dx_bytes, 1};
+    const peqa::SplitJob y{(N + 255) / 256, K, y_bytes, 1}, dx{(K + 255) / 256, N, dx_bytes, 1};
     if (fwd) {
         // a forward that fits peqa_linear_fwd_static's scratch whole is split within it: both calls run the same contraction
         size_t most = ~(size_t)0;
         if (w.total <= (size_t)PEQA_STATIC_SCRATCH_BYTES) most = (size_t)PEQA_STATIC_SCRATCH_BYTES - w.total;
         peqa::SplitJob j = y;
-        peqa::gemm_plan_splits(1, &j, grouped(L), true, most, cus);
+        w.rt_y = peqa::gemm_plan(1, &j, T, grouped(L), true, false, most, cus);
         w.split_y = j.split;
         w.acc = w.total;
         if (j.split > 1) w.total += round256((size_t)j.split * y_bytes);
         return w;
     }
     peqa::SplitJob alone = dx;
-    peqa::gemm_plan_splits(1, &alone, grouped(L), true, ~(size_t)0, cus);
+    w.rt_dx_alone = peqa::gemm_plan(1, &alone, T, grouped(L), true, false, ~(size_t)0, cus);
     w.split_dx = w.split_dx_alone = alone.split;
     if (!grouped(L) && op != PEQA_OP_BWD_KEPT) {
         peqa::SplitJob both[2] = {y, dx};
         both[0].out_bytes = 0;
-        peqa::gemm_plan_splits(2, both, false, false, ~(size_t)0, cus);
+        (void)peqa::gemm_plan(2, both, T, false, false, true, ~(size_t)0, cus);
         w.split_dds = both[0].split;
         w.split_dx = both[1].split;
     }
@@ -173,7 +175,7 @@ peqa_status run_contraction(int bits, int mode, peqa::GemmArgs &a, int split, fl
 
 peqa_status fwd_per_channel(const peqa_layout *L, const uint32_t *packed, const float *s0, const float *ds,
                             const uint8_t *z0, const float *dz, const uint16_t *X, int32_t T, uint16_t *Y, float *P,
-                            const float *rs, int split, float *acc, hipStream_t s);
+                            const float *rs, int rt, int split, float *acc, hipStream_t s);
 
 // Scale gradient of group-wise layers: by the contraction over tokens (default), or, with the option
 // grouped_dds = 1, by the contraction over features, one pair of scale groups per workgroup: the older,
@@ -330,13 +332,13 @@ static peqa_status fwd_impl(const peqa_layout *L, const uint32_t *packed, const 
         if (peqa::launch_group_table(s0, ds, z0, dz, N, groups(L), sb, s) != hipSuccess) return PEQA_ERR_DEVICE;
         peqa::GemmArgs a{};
         a.packed = packed; a.A = X; a.T = T; a.KC = K; a.C = N; a.K = K;
-        a.tiles_c = (N + 255) / 256; a.tiles_t = (T + 127) / 128;
+        a.rt = w.rt_y; a.tiles_c = (N + 255) / 256; a.tiles_t = peqa::gemm_tiles_t(T, a.rt);
         a.N = N; a.gsz = L->group_size; a.G = groups(L); a.sb = sb; a.out = Y;
         return run_contraction(L->bits, peqa::MODE_Y, a, w.split_y, reinterpret_cast<float *>(ws + w.acc), s);
     }
     float *rs = reinterpret_cast<float *>(ws + w.rs);
     if (peqa::launch_rowsum(X, T, K, ksplit, rs, s) != hipSuccess) return PEQA_ERR_DEVICE;
-    return fwd_per_channel(L, packed, s0, ds, z0, dz, X, T, Y, nullptr, rs, w.split_y, reinterpret_cast<float *>(ws + w.acc), s);
+    return fwd_per_channel(L, packed, s0, ds, z0, dz, X, T, Y, nullptr, rs, w.rt_y, w.split_y, reinterpret_cast<float *>(ws + w.acc), s);
 }
 
 peqa_status peqa_quantize_search(const peqa_layout *L, const float *W0, int32_t n_ratios, float min_ratio,
@@ -429,7 +431,7 @@ peqa_status peqa_linear_fwd_keep(const peqa_layout *L, const uint32_t *packed, c
     uint8_t *ws = static_cast<uint8_t *>(workspace);
     float *rs = reinterpret_cast<float *>(ws + w.rs);
     if (peqa::launch_rowsum(X, T, L->k_in, split_point(L->k_in), rs, s) != hipSuccess) return PEQA_ERR_DEVICE;
-    return fwd_per_channel(L, packed, s0, ds, z0, nullptr, X, T, Y, P, rs, w.split_y, reinterpret_cast<float *>(ws + w.acc), s);
+    return fwd_per_channel(L, packed, s0, ds, z0, nullptr, X, T, Y, P, rs, w.rt_y, w.split_y, reinterpret_cast<float *>(ws + w.acc), s);
 }
 
 }  // extern "C"
@@ -438,12 +440,12 @@ namespace {
 // Per-channel forward contraction for T > 16, the row sums of X already in `rs`.
 peqa_status fwd_per_channel(const peqa_layout *L, const uint32_t *packed, const float *s0, const float *ds,
                             const uint8_t *z0, const float *dz, const uint16_t *X, int32_t T, uint16_t *Y, float *P,
-                            const float *rs, int split, float *acc, hipStream_t s)
+                            const float *rs, int rt, int split, float *acc, hipStream_t s)
 {
     const int N = L->n_out, K = L->k_in;
     peqa::GemmArgs a{};
     a.packed = packed; a.A = X; a.T = T; a.KC = K; a.C = N; a.K = K;
-    a.tiles_c = (N + 255) / 256; a.tiles_t = (T + 127) / 128;
+    a.rt = rt; a.tiles_c = (N + 255) / 256; a.tiles_t = peqa::gemm_tiles_t(T, rt);
     a.s0 = s0; a.ds = ds; a.z0 = z0; a.dz = dz; a.rs = rs; a.out = Y; a.P = P;
     return run_contraction(L->bits, peqa::MODE_Y, a, split, acc, s);
 }
@@ -533,7 +535,7 @@ static peqa_status fwd_fused_impl(int32_t n, const peqa_fwd_item *items, const u
             const peqa_fwd_item &it = items[j];
             Workspace w = carve(&it.layout, T, PEQA_OP_FWD, peqa::compute_units());
             fit_workspace(w, workspace_bytes);
-            st = fwd_per_channel(&it.layout, it.packed, it.s0, it.ds, it.z0, nullptr, X, T, it.Y, nullptr, rs, w.split_y,
+            st = fwd_per_channel(&it.layout, it.packed, it.s0, it.ds, it.z0, nullptr, X, T, it.Y, nullptr, rs, w.rt_y, w.split_y,
                                  reinterpret_cast<float *>(static_cast<uint8_t *>(workspace) + w.acc), s);
             if (st != PEQA_OK) return st;
         }
@@ -602,13 +604,13 @@ static peqa_status bwd_impl(const peqa_layout *L, const uint32_t *packed, const 
         uint16_t *xt = reinterpret_cast<uint16_t *>(ws + w.xt), *dyt = reinterpret_cast<uint16_t *>(ws + w.dyt);
         // When dX is wanted too and its contraction runs two workgroups per compute unit, it goes first and spare
         // workgroups of its launch write the transposed copies that the token contraction needs.
-        const bool tp_in_dx = d_ds && by_tokens && dX && peqa::gemm_four_waves(tiles_t * ((K + 255) / 256) * w.split_dx);
+        const bool tp_in_dx = d_ds && by_tokens && dX && peqa::gemm_four_waves(peqa::gemm_tiles_t(T, w.rt_dx_alone) * ((K + 255) / 256) * w.split_dx);
         auto run_dx = [&](bool with_transposes) -> peqa_status {
             float *sb = reinterpret_cast<float *>(ws + w.table);
             if (peqa::launch_group_table(s0, ds, z0, dz, N, G, sb, s) != hipSuccess) return PEQA_ERR_DEVICE;
             peqa::GemmArgs a{};
             a.packed = packed; a.A = dY; a.T = T; a.KC = N; a.C = K; a.K = K;
-            a.tiles_c = (K + 255) / 256; a.tiles_t = tiles_t;
+            a.rt = w.rt_dx_alone; a.tiles_c = (K + 255) / 256; a.tiles_t = peqa::gemm_tiles_t(T, a.rt);
             a.N = N; a.gsz = L->group_size; a.G = G; a.sb = sb; a.out = dX;
             if (with_transposes) {
                 a.tp_blocks = (Tp / 64) * (K / 64 + N / 64); a.tp_Tp = Tp; a.tp_X = X; a.tp_Xt = xt; a.tp_dYt = dyt;
@@ -635,7 +637,7 @@ static peqa_status bwd_impl(const peqa_layout *L, const uint32_t *packed, const 
             float *partial = reinterpret_cast<float *>(ws + w.partial);
             peqa::GemmArgs a{};
             a.packed = packed; a.A = X; a.T = T; a.KC = K; a.C = N; a.K = K;
-            a.tiles_c = (N + 255) / 256; a.tiles_t = tiles_t;
+            a.rt = 8; a.tiles_c = (N + 255) / 256; a.tiles_t = tiles_t;   // (this route has tiles of 128 rows only)
             a.N = N; a.gsz = L->group_size; a.G = G;
             a.z0 = z0; a.dz = dz; a.rs = rsb; a.dY = dY; a.partial = partial;
             if (peqa::launch_gemm(L->bits, peqa::MODE_DDS, a, s) != hipSuccess) return PEQA_ERR_DEVICE;
@@ -678,14 +680,14 @@ static peqa_status bwd_impl(const peqa_layout *L, const uint32_t *packed, const 
     if (d_ds) {
         peqa::GemmArgs &a = a_dds;
         a.packed = packed; a.A = X; a.T = T; a.KC = K; a.C = N; a.K = K;
-        a.tiles_c = (N + 255) / 256; a.tiles_t = tiles_t;
+        a.rt = peqa::gemm_row_tiles(T); a.tiles_c = (N + 255) / 256; a.tiles_t = tiles_t;
         a.z0 = z0; a.dz = dz; a.rs = rs; a.dY = dY; a.partial = partial;
         a.split = w.split_dds;
     }
     if (dX) {
         peqa::GemmArgs &a = a_dx;
         a.packed = packed; a.A = reinterpret_cast<uint16_t *>(ws + w.dys); a.T = T; a.KC = N; a.C = K; a.K = K;
-        a.tiles_c = (K + 255) / 256; a.tiles_t = tiles_t;
+        a.rt = pair ? peqa::gemm_row_tiles(T) : w.rt_dx_alone; a.tiles_c = (K + 255) / 256; a.tiles_t = peqa::gemm_tiles_t(T, a.rt);
         a.crow = reinterpret_cast<float *>(ws + w.crow); a.out = dX;
     }
     uint16_t *dys = reinterpret_cast<uint16_t *>(ws + w.dys);
@@ -801,7 +803,7 @@ peqa_status peqa_linear_bwd_kept(const peqa_layout *L, const uint32_t *packed, c
             return PEQA_ERR_DEVICE;
         peqa::GemmArgs a{};
         a.packed = packed; a.A = dys; a.T = T; a.KC = N; a.C = K; a.K = K;
-        a.tiles_c = (K + 255) / 256; a.tiles_t = (T + 127) / 128;
+        a.rt = w.rt_dx_alone; a.tiles_c = (K + 255) / 256; a.tiles_t = peqa::gemm_tiles_t(T, a.rt);
         a.crow = crow; a.out = dX;
         return run_contraction(L->bits, peqa::MODE_DX, a, w.split_dx_alone, reinterpret_cast<float *>(ws + w.acc), s);
     }

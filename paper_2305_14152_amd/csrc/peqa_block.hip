@@ -57,6 +57,7 @@ struct BlockSpace {
     // them, and a workspace of at least `min_total` bytes is served with whole contractions.
     size_t min_total;
     int split_y[PEQA_MAX_BLOCK], split_dx[PEQA_MAX_BLOCK], split_dds[PEQA_MAX_BLOCK];
+    int rt_y[2], rt_dx[2];           // row tiles per tile of the launches of per-channel and of group-wise items
     size_t acc[PEQA_MAX_BLOCK], acc_dds[PEQA_MAX_BLOCK];
 };
 
@@ -97,19 +98,20 @@ BlockSpace carve_block(int32_t n, const peqa_block_item *items, int32_t T, int32
             const int C = mode == peqa::MODE_DX ? L->k_in : L->n_out, KC = mode == peqa::MODE_DX ? L->n_out : L->k_in;
             of[m] = j;
             const size_t out_bytes = mode == peqa::MODE_DDS ? 0 : (size_t)T * C * sizeof(float);
-            job[m++] = peqa::SplitJob{(int)tiles_t * ((C + 255) / 256), KC, out_bytes, 1};
+            job[m++] = peqa::SplitJob{(C + 255) / 256, KC, out_bytes, 1};
         }
-        if (m == 0) return;
-        peqa::gemm_plan_splits(m, job, gw, false, ~(size_t)0, cus);
+        if (m == 0) return peqa::gemm_row_tiles(T);
+        const int rt = peqa::gemm_plan(m, job, T, gw, false, mode == peqa::MODE_DDS, ~(size_t)0, cus);
         for (int i = 0; i < m; ++i) split[of[i]] = job[i].split;
+        return rt;
     };
     if (op == PEQA_OP_FWD) {
-        plan(false, peqa::MODE_Y, w.split_y);
-        plan(true, peqa::MODE_Y, w.split_y);
+        w.rt_y[0] = plan(false, peqa::MODE_Y, w.split_y);
+        w.rt_y[1] = plan(true, peqa::MODE_Y, w.split_y);
     } else {
         plan(false, peqa::MODE_DDS, w.split_dds);
-        plan(false, peqa::MODE_DX, w.split_dx);
-        plan(true, peqa::MODE_DX, w.split_dx);
+        w.rt_dx[0] = plan(false, peqa::MODE_DX, w.split_dx);
+        w.rt_dx[1] = plan(true, peqa::MODE_DX, w.split_dx);
     }
     for (int j = 0; j < n; ++j) {
         const size_t N = (size_t)items[j].layout.n_out, K = (size_t)items[j].layout.k_in;
@@ -287,7 +289,7 @@ peqa_status peqa_block_fwd(int32_t n, const peqa_block_item *items, int32_t T, v
         job.mode = peqa::MODE_Y;
         peqa::GemmArgs &a = job.a;
         a.packed = it.packed; a.A = it.X; a.T = T; a.KC = K; a.C = N; a.K = K;
-        a.tiles_c = (N + 255) / 256; a.tiles_t = (T + 127) / 128;
+        a.rt = w.rt_y[gw]; a.tiles_c = (N + 255) / 256; a.tiles_t = peqa::gemm_tiles_t(T, a.rt);
         a.out = it.Y;
         a.split = w.split_y[j]; a.acc_part = reinterpret_cast<float *>(ws + w.acc[j]);
         if (gw) {
@@ -382,7 +384,7 @@ peqa_status peqa_block_bwd(int32_t n, const peqa_block_item *items, int32_t T, v
             job.mode = peqa::MODE_DDS;
             peqa::GemmArgs &a = job.a;
             a.packed = it.packed; a.A = it.X; a.T = T; a.KC = K; a.C = N; a.K = K;
-            a.tiles_c = (N + 255) / 256; a.tiles_t = tiles_t;
+            a.rt = peqa::gemm_row_tiles(T); a.tiles_c = (N + 255) / 256; a.tiles_t = tiles_t;
             a.z0 = it.z0; a.rs = rs[xi[j]]; a.dY = it.dY; a.partial = partial;
             a.split = w.split_dds[j];
             if (partial_rows > 1) {
@@ -401,7 +403,7 @@ peqa_status peqa_block_bwd(int32_t n, const peqa_block_item *items, int32_t T, v
             job.mode = peqa::MODE_DX;
             peqa::GemmArgs &a = job.a;
             a.packed = it.packed; a.A = dys; a.T = T; a.KC = N; a.C = K; a.K = K;
-            a.tiles_c = (K + 255) / 256; a.tiles_t = tiles_t;
+            a.rt = w.rt_dx[0]; a.tiles_c = (K + 255) / 256; a.tiles_t = peqa::gemm_tiles_t(T, a.rt);
             a.crow = crow; a.out = it.dX;
             a.split = w.split_dx[j]; a.acc_part = reinterpret_cast<float *>(ws + w.acc[j]);
         }
@@ -437,7 +439,7 @@ peqa_status peqa_block_bwd(int32_t n, const peqa_block_item *items, int32_t T, v
             job.mode = peqa::MODE_DX;
             peqa::GemmArgs &a = job.a;
             a.packed = it.packed; a.A = it.dY; a.T = T; a.KC = N; a.C = K; a.K = K;
-            a.tiles_c = (K + 255) / 256; a.tiles_t = tiles_t;
+            a.rt = w.rt_dx[1]; a.tiles_c = (K + 255) / 256; a.tiles_t = peqa::gemm_tiles_t(T, a.rt);
             a.N = N; a.gsz = it.layout.group_size; a.G = G;
             a.sb = reinterpret_cast<const float *>(ws + w.table[j]); a.out = it.dX;
             a.split = w.split_dx[j]; a.acc_part = reinterpret_cast<float *>(ws + w.acc[j]);

@@ -25,7 +25,8 @@ struct GemmArgs {
     int KC;                   // contraction length: K (MODE_Y/DDS) or N (MODE_DX)
     int C;                    // output columns:     N (MODE_Y/DDS) or K (MODE_DX)
     int K;                    // input features of the layer (fixes the block stride of `packed`)
-    int tiles_c, tiles_t;     // ceil(C/256), ceil(T/128)
+    int tiles_c, tiles_t;     // ceil(C/256), ceil(T/(16 rt))
+    int rt;                   // row tiles (of 16 tokens) per tile: gemm_row_tiles(T), or 4 where gemm_plan asks for it
     int patch_t;              // token tiles per L2 patch (at most 4; set by the launches)
     const float *s0;          // [N]            (MODE_Y)
     const float *ds;          // [N] or NULL    (MODE_Y)
@@ -57,18 +58,22 @@ struct GemmArgs {
 };
 
 hipError_t launch_gemm(int bits, int mode, const GemmArgs &a, hipStream_t stream);
+// Row tiles (of 16 tokens: 4, 6, 7 or 8) of the tiles that T tokens are dealt to; there are ceil(T / 128) of them in any case.
+int gemm_row_tiles(int T);
+inline int gemm_tiles_t(int T, int rt) { return (T + 16 * rt - 1) / (16 * rt); }
 
 // Contractions of a launch whose tiles leave the machine idle (few tokens, or a few tiles of a long contraction) are split
-// along the contraction: GemmArgs::split pieces per tile.  gemm_plan_splits fills `split` of every job of one launch.
+// along the contraction: GemmArgs::split pieces per tile.  gemm_plan fills `split` of every job of one launch.
 struct SplitJob {
-    int tiles;                // of 128 x 256
+    int tiles_c;              // column tiles
     int KC;                   // contraction length
     size_t out_bytes;         // fp32 bytes of one piece's partial result (T C 4); 0 for MODE_DDS, whose pieces add partial rows
     int split;                // out
 };
-// single: the jobs are one contraction that runs by itself (launch_gemm), which may take the eight-wave form.
+// Returns the row tiles per tile of the launch.  single: the jobs are one contraction that runs by itself (launch_gemm), which
+// may take the eight-wave form.  dds: the launch has MODE_DDS jobs, whose partial rows go by gemm_row_tiles(T).
 // max_bytes: the most the partial results may take.  cus: compute units.
-void gemm_plan_splits(int n, SplitJob *jobs, bool grouped, bool single, size_t max_bytes, int cus);
+int gemm_plan(int n, SplitJob *jobs, int T, bool grouped, bool single, bool dds, size_t max_bytes, int cus);
 // Epilogue of the split MODE_Y / MODE_DX contractions of a launch: adds the pieces in order, then does what the tile's own
 // epilogue would have done.  Jobs with split 1 are skipped.
 constexpr int FINISH_MAX = 8;
@@ -137,6 +142,14 @@ struct MultiArgs {
 // Per-channel jobs (any mode), or, with `grouped`, group-wise MODE_Y / MODE_DX jobs (their tables in a.sb).
 static_assert(sizeof(MultiArgs) <= 4096, "kernel argument block");
 hipError_t launch_gemm_multi(int bits, bool grouped, MultiArgs &m, hipStream_t stream);
+// The launches themselves, of tiles of RT row tiles: a contraction, a backward pair, or `workgroups` of a multi-contraction
+// launch (gmode: -1 per channel, else the mode of the group-wise jobs).
+template <int RT>
+struct GemmRows {
+    static hipError_t one(int bits, int mode, const GemmArgs &a, hipStream_t stream);
+    static hipError_t pair(int bits, const GemmArgs &a_dds, const GemmArgs &a_dx, hipStream_t stream);
+    static hipError_t multi(int bits, int gmode, int workgroups, const MultiArgs &m, hipStream_t stream);
+};
 // workgroups a contraction's tiles (and pieces of tiles) take in a launch (a multiple of 8)
 int gemm_multi_wgs(const GemmArgs &a);
 

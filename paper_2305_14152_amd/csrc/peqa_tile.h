@@ -1,8 +1,9 @@
-// One 128 (tokens) x 256 (output columns) tile of a PEQA contraction: the code that every contraction launch of
+// One 16 RT (tokens) x 256 (output columns) tile of a PEQA contraction: the code that every contraction launch of
 // peqa_gemm.hip runs (what the modes compute: see there).
 //
-// Four waves side by side along the columns (per contraction half): a wave owns all 128 token rows of 64 columns, 8 x 4
-// MFMA 16x16x32 tiles in 128 AGPRs.
+// Four waves side by side along the columns (per contraction half): a wave owns all token rows of 64 columns, RT x 4
+// MFMA 16x16x32 tiles in 16 RT AGPRs.  RT is 8 where there are tokens enough (what follows is said of it), 4, 6 or 7 where tiles of
+// 128 rows would be mostly padding or leave the machine idle (gemm_row_tiles, gemm_plan).
 //
 // What bounds it and why this split.  Per 32-deep step and SIMD (two waves) the matrix instructions take 1024 cycles;
 // the vector instructions of two waves take 4 cycles each beside them, and LDS delivers 128 bytes per cycle to the
@@ -16,6 +17,11 @@
 // that split dX scaled its activation fragments instead of the weights; here the weights are cheaper to scale), and with
 // fp16 codes for the scaling 1129 and 1259 us; 11008 x 4096, 4 bits, groups of 64, T = 500: forward 102 -> 72 -> 67 us;
 // per-channel training steps of the 7B and 65B blocks 2.1 and 2.9 % shorter.
+//
+// Launches that fill the chip for long run at the power limit: their time follows the energy of a step, not its cycles.  Loops of
+// the same mix on random data, two waves per SIMD, us per step: MFMAs alone 0.509, with the unpacking 0.540, with the LDS reads
+// 0.562, with the DMAs 0.548, with all three 0.627 (the kernels: 0.66).  MFMA 32x32x16 with lanes exchanged to its operand
+// order took 5 (per channel) and 11 % (group-wise) fewer cycles in the kernels, at a clock lower by as much: no faster.
 #pragma once
 
 #include <type_traits>
@@ -25,41 +31,49 @@
 
 namespace peqa {
 
-constexpr int TILE_T = 128;
 constexpr int TILE_C = 256;
 constexpr int WAVE_C = 64;                                 // columns per wave
 constexpr int KSTEP = 32;                                  // contraction depth of one loop iteration
 constexpr int NSTAGE = 6;                                  // LDS ring depth
-constexpr int A_HALF_BYTES = TILE_T * KSTEP * 2;           // 8 KB: 128 rows x 32 bf16 of one contraction half
+// token rows of a stage's activation tile: the tile's, rounded up to what whole wave-loads of 16 rows by four waves bring
+constexpr int staged_rows(int rt) { return rt <= 4 ? 64 : 128; }
+constexpr int a_half_bytes(int rt) { return staged_rows(rt) * KSTEP * 2; }   // of one contraction half: 4 or 8 KB
 constexpr int B_WAVE_BYTES = 1024;                         // packed codes of one wave and step (64 columns x 32: 1 KB / 768 B)
-// A ring stage holds, per contraction half the workgroup runs (KW = 2 or 1), one 128 x 32 activation tile and the packed
-// codes of its four waves: 24 KB or 12 KB.
-constexpr int stage_bytes(int kw) { return kw * (A_HALF_BYTES + 4 * B_WAVE_BYTES); }
-constexpr int DMA_PER_ITER = 3;                            // DMA instructions per wave per iteration
-// 144 KB (the epilogue's exchange of 128 KB reuses it) or 72 KB
-constexpr int ring_bytes(int kw) { return NSTAGE * stage_bytes(kw); }
+// A ring stage holds, per contraction half the workgroup runs (KW = 2 or 1), one activation tile and the packed
+// codes of its four waves: 24 KB or 12 KB (16 and 8 KB with 64 rows).
+constexpr int stage_bytes(int kw, int rt) { return kw * (a_half_bytes(rt) + 4 * B_WAVE_BYTES); }
+// 144 KB (the epilogue's exchange of 128 KB reuses it) or 72 KB (96 and 48 KB with 64 rows)
+constexpr int ring_bytes(int kw, int rt) { return NSTAGE * stage_bytes(kw, rt); }
 constexpr int tbl_bytes(int kw) { return kw * 4 * 2 * 1024; }           // group-wise MODE_Y / MODE_DX: 2 x 1 KB of (s, b) per wave
 
-// The weight-fragment register (0..15) of the next step that is built after MFMA m of a step, or -1: spread over MFMAs 4..31.
-constexpr int frag_reg_after(int m)
+// The MFMA of a step (0 .. 4 rt - 1) after which weight-fragment register r (0..15) of the next step is built: spread over the
+// last seven eighths of them.
+constexpr int frag_reg_slot(int r, int rt) { return rt / 2 + ((4 * rt - 1 - rt / 2) * r) / 15; }
+// The first register of slot m or a later one.
+constexpr int frag_reg_from(int m, int rt)
 {
-    for (int r = 0; r < 16; ++r)
-        if (4 + (27 * r) / 15 == m) return r;
-    return -1;
+    int r = 0;
+    while (r < 16 && frag_reg_slot(r, rt) < m) ++r;
+    return r;
 }
 
 // ROW_SUMS (the scale gradient in pieces): the row sums of X over the piece, which take the code offset and the zero-point out
 // of its sums before they are added to the other pieces' (taken out of the total only, they cost a digit of the result), are
 // added up beside the matrix instructions: eight dot instructions per wave and step, 6 % of the launch, which is why whole
 // contractions are handed the sums over the halves of K (8 bytes per row, one short launch per step and input).
-template <int BITS, int MODE, bool GROUPED, int KW, bool ROW_SUMS = false>
+template <int BITS, int MODE, bool GROUPED, int KW, int RT, bool ROW_SUMS = false>
 __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8_t *lds)
 {
-    constexpr int STAGE_BYTES = stage_bytes(KW);
+    constexpr int STAGE_BYTES = stage_bytes(KW, RT), A_HALF_BYTES = a_half_bytes(RT);
+    constexpr int MFMAS = 4 * RT;                          // per wave and step
+    constexpr int NA = staged_rows(RT) / 64;               // activation DMAs per wave and step
+    constexpr int DMA_PER_ITER = NA + 1;                   // DMA instructions per wave per iteration
     constexpr bool ALONG_CH = (MODE == MODE_DX);           // contraction over output channels
     constexpr bool SCALED = GROUPED && MODE != MODE_DDS;   // the scale is applied inside the loop: weights enter the MFMA scaled
     constexpr bool PAIRED = GROUPED && MODE == MODE_DDS;   // one scale group per contraction half
-    static_assert(!ROW_SUMS || (!GROUPED && MODE == MODE_DDS && KW == 1), "row sums per piece: scale gradient, four waves");
+    static_assert(!ROW_SUMS || (!GROUPED && MODE == MODE_DDS && KW == 1 && (RT == 4 || RT == 8)),
+                  "row sums per piece: scale gradient, four waves, a power of two pairs of row tiles");
+    static_assert(RT >= 4 && RT <= 8, "row tiles");
     static_assert(KW == 2 || (KW == 1 && !PAIRED), "the paired scale gradient needs both contraction halves");
     typedef HalfBlockUnpacker<BITS, ALONG_CH, SCALED ? kFieldF16 : kFieldBf16> Unpacker;
     constexpr int WORDS = Unpacker::WORDS;
@@ -100,7 +114,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
         piece = __builtin_amdgcn_readfirstlane(piece);
     }
 
-    const int t0 = tile_t * TILE_T;
+    const int t0 = tile_t * (16 * RT);
     const int col0 = tile_c * TILE_C + wn * WAVE_C;        // first output column of this wave
     const bool wave_on = col0 < a.C;
     const int T = a.T, KC = a.KC;
@@ -128,11 +142,12 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
     const uint32_t magic = SCALED ? kMagicF16 : kMagic;
     const uint32_t lds_base = (uint32_t)(uintptr_t)lds;
 
-    // ---- activation tiles: global -> LDS by DMA, wave-loads of 1 KB (16 rows; 2 per wave and step).  Lane s of a
+    // ---- activation tiles: global -> LDS by DMA, wave-loads of 1 KB (16 rows; NA per wave and step).  Lane s of a
     // wave-load lands at byte 16 s, i.e. row s / 4, chunk position s % 4, and fetches the chunk that the XOR swizzle
-    // assigns to that position.  KW = 2: wave-load m = 8 i + wave covers contraction half m / 8, rows 16 (m % 8) .. +16;
-    // KW = 1: rows 16 wave .. and 64 + 16 wave .. (the swizzle only looks at row % 16).
-    uint32_t a_voff, a_voff_2;
+    // assigns to that position.  KW = 2: wave-load m = 8 i + wave covers contraction half m / 8, rows 16 (m % 8) .. +16
+    // (64 staged rows: wave-load `wave`, half m / 4, rows 16 (m % 4) ..); KW = 1: rows 16 wave .. and, of 128,
+    // 64 + 16 wave .. (the swizzle only looks at row % 16).
+    uint32_t a_voff, a_voff_2 = 0;
     {
         const int row_l = lane >> 2, pos = lane & 3;
         const int chunk = pos ^ a_swizzle(row_l);
@@ -140,8 +155,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
             row = t0 + row < T ? row : T - 1 - t0;
             return (uint32_t)row * (uint32_t)KC * 2u + (uint32_t)chunk * 16u;
         };
-        a_voff = voff_of(wave * 16 + row_l);
-        if constexpr (KW == 1) a_voff_2 = voff_of(64 + wave * 16 + row_l);
+        a_voff = voff_of((NA == 1 ? wn : wave) * 16 + row_l);
+        if constexpr (NA == 1) a_voff += (uint32_t)(kbeg - kh0) * 2u;
+        else if constexpr (KW == 1) a_voff_2 = voff_of(64 + wave * 16 + row_l);
         else a_voff_2 = a_voff + (uint32_t)(kh1 - kh0) * 2u;
     }
     constexpr int A_DST_2 = KW == 2 ? A_HALF_BYTES : A_HALF_BYTES / 2;
@@ -280,9 +296,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
         else return scale_pair(pr, sc[I], bo[I], sc[I], bo[I]);
     };
 
-    f32x4 acc[8][4];
+    f32x4 acc[RT][4];
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < RT; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
@@ -291,21 +307,22 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
     constexpr int HALF_RING = (NSTAGE / 2) * STAGE_BYTES;
     static_assert((NSTAGE / 2 - 1) * STAGE_BYTES + 8192 <= 65536, "literal offsets of LDS reads");
     // row 16 rt' + c (the swizzle only looks at row % 16).  Where the row sums are taken, row tile rt of the wave's registers is
-    // row tile rt' = rt ^ 2 wn of the tile: registers 0 and 1 are then other rows in each of the four waves, which together
-    // add up all 128 rows (two dot instructions per register: 8 per wave and step).
-    constexpr int NPAIR = ROW_SUMS ? 4 : 1;                // pairs of row tiles with a base register of their own
+    // row tile rt' = rt ^ 2 wp of the tile, wp = wn (of 128 rows) or wn % 2 (of 64): registers 0 and 1 are then other rows in
+    // each of the four (two) waves, which together add up all rows (two dot instructions per register: 8 per wave and step).
+    constexpr int NPAIR = ROW_SUMS ? RT / 2 : 1;           // pairs of row tiles with a base register of their own
+    const int wp = wn & (NPAIR - 1);
     const uint8_t *a_rd[2][NPAIR], *b_rd[2];
 #pragma unroll
     for (int p = 0; p < NPAIR; ++p) {
-        a_rd[0][p] = lds + wk * A_HALF_BYTES + c * 64 + ((q ^ a_swizzle(c)) << 4) + (ROW_SUMS ? (p ^ wn) * 2048 : 0);
+        a_rd[0][p] = lds + wk * A_HALF_BYTES + c * 64 + ((q ^ a_swizzle(c)) << 4) + (ROW_SUMS ? (p ^ wp) * 2048 : 0);
         a_rd[1][p] = a_rd[0][p] + HALF_RING;
     }
     b_rd[0] = lds + KW * A_HALF_BYTES + wave * B_WAVE_BYTES + b_lane_off;
     b_rd[1] = b_rd[0] + HALF_RING;
     auto read_a = [&](auto st_c, u32x4 *af, int rt) __attribute__((always_inline)) {
         constexpr int ST = decltype(st_c)::value;
-        const uint8_t *base = a_rd[ST / (NSTAGE / 2)][NPAIR == 4 ? rt >> 1 : 0] + (ST % (NSTAGE / 2)) * STAGE_BYTES;
-        af[rt] = *reinterpret_cast<const u32x4 *>(base + (NPAIR == 4 ? rt & 1 : rt) * 16 * 64);
+        const uint8_t *base = a_rd[ST / (NSTAGE / 2)][ROW_SUMS ? rt >> 1 : 0] + (ST % (NSTAGE / 2)) * STAGE_BYTES;
+        af[rt] = *reinterpret_cast<const u32x4 *>(base + (ROW_SUMS ? rt & 1 : rt) * 16 * 64);
     };
     auto read_b = [&](auto st_c, uint32_t *w) __attribute__((always_inline)) {
         constexpr int ST = decltype(st_c)::value;
@@ -334,12 +351,12 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
 
     // ---- prologue: queue NSTAGE - 1 stages (and the packed weights of one more), wait for the first two, fetch the operands
     // of step 0 and the packed weights of step 1
-    u32x4 bfrag[2][4], afrag[8];
+    u32x4 bfrag[2][4], afrag[RT];
     uint32_t bw[2][WORDS];                                 // packed weights of the next step / the one after
     if constexpr (SCALED) { issue_table(m0 >> 2); issue_table((m0 >> 2) + 1); }
     auto issue_a = [&](int stage) __attribute__((always_inline)) {
         dma16(a_voff, a_ptr, dst_a + stage * STAGE_BYTES);
-        dma16(a_voff_2, a_ptr, dst_a + stage * STAGE_BYTES + A_DST_2);
+        if constexpr (NA == 2) dma16(a_voff_2, a_ptr, dst_a + stage * STAGE_BYTES + A_DST_2);
     };
     auto issue_b = [&](int stage) __attribute__((always_inline)) {
         dma16(b_voff, b_next, dst_b + stage * STAGE_BYTES);
@@ -358,7 +375,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
         read_b(std::integral_constant<int, 0>{}, bw[1]);
         read_b(std::integral_constant<int, 1>{}, bw[0]);
 #pragma unroll
-        for (int rt = 0; rt < 8; ++rt) read_a(std::integral_constant<int, 0>{}, afrag, rt);
+        for (int rt = 0; rt < RT; ++rt) read_a(std::integral_constant<int, 0>{}, afrag, rt);
         if constexpr (SCALED) {
             if constexpr (ALONG_CH) {
 #pragma unroll
@@ -376,7 +393,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
     // (Step 0 refills the packed-weight slot of stage 0, which its own wave alone reads and has read; its activation tiles go to
     // stage NSTAGE - 1.  No barrier is needed before it.)
 
-    // ---- main loop.  A step is a 32-deep contraction: 32 MFMAs, one per accumulator.  When step `it` starts, its fragments
+    // ---- main loop.  A step is a 32-deep contraction: 4 RT MFMAs, one per accumulator (the slots below: of 32).  When step `it` starts, its fragments
     // and the packed weights of step it + 1 are in registers, and stages it + 1 and it + 2 are complete in LDS.  The MFMAs run
     // back to back from the first instruction after the barrier; everything else sits in their shadow, in fixed slots:
     //   after MFMA 2          LDS read of the packed weights of step it + 2
@@ -417,22 +434,22 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
         }
         Unpacker up;
         up.prepare(bw[CUR], perm_sel);
-        static_for<8>([&](auto rt_c) {
+        static_for<RT>([&](auto rt_c) {
             constexpr int rt = rt_c.value;
             static_for<4>([&](auto ct_c) {
                 constexpr int ct = ct_c.value, m = 4 * rt + ct;
                 mfma16_acc(acc[rt][ct], afrag[rt], bfrag[CUR][ct]);
-                constexpr int r = frag_reg_after(m);
-                if constexpr (r >= 0) {
-                    constexpr int I = J_MAJOR ? r & 3 : r >> 2, J = J_MAJOR ? r >> 2 : r & 3;
+                constexpr int r0 = frag_reg_from(m, RT), r1 = frag_reg_from(m + 1, RT);
+                static_for<r1 - r0>([&](auto r_c) {
+                    constexpr int r = r0 + r_c.value, I = J_MAJOR ? r & 3 : r >> 2, J = J_MAJOR ? r >> 2 : r & 3;
                     bfrag[NXT][I][J] = next_frag_reg(up, std::integral_constant<int, I>{}, std::integral_constant<int, J>{});
                     if constexpr (J_MAJOR && I == 3 && J < 2) read_table_pair(m0 + it + 1, J + 2);
-                }
+                });
                 if constexpr (ROW_SUMS && rt < 2) rsum[rt] = add_pair(afrag[rt][ct], rsum[rt]);
                 if constexpr (m == 2) read_b(std::integral_constant<int, NNS>{}, bw[NXT]);
-                if constexpr (m == 5) dma16(a_voff, a_ptr, dst_a + PS * STAGE_BYTES);
-                if constexpr (m == 13) dma16(a_voff_2, a_ptr, dst_a + PS * STAGE_BYTES + A_DST_2);
-                if constexpr (m == 21) {
+                if constexpr (m == MFMAS / 8 + 1) dma16(a_voff, a_ptr, dst_a + PS * STAGE_BYTES);
+                if constexpr (NA == 2 && m == 3 * MFMAS / 8 + 1) dma16(a_voff_2, a_ptr, dst_a + PS * STAGE_BYTES + A_DST_2);
+                if constexpr (m == 5 * MFMAS / 8 + 1) {
                     issue_b(S);
                     a_ptr += it + NSTAGE - 1 < nit - 1 ? KSTEP * 2 : 0;
                 }
@@ -461,7 +478,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
     // The loop's exits meet here; this keeps the accumulators in their AGPRs past that point (the compiler would
     // otherwise copy all 128 of them into VGPRs at once, more than there are)
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < RT; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) asm volatile("" : "+a"(acc[i][j]));
     // The epilogue works out its lane indices afresh (from a copy of the thread index that the compiler cannot
@@ -487,7 +504,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
         return Unpacker::BY_PARITY ? col0 + 4 * (c & ~1) + 2 * e + par : colc + e;
     };
     // rows 4 q + j of the registers' row tile rt
-    auto local_row = [&](int rt) __attribute__((always_inline)) { return (ROW_SUMS ? rt ^ (2 * wn) : rt) * 16 + 4 * q; };
+    auto local_row = [&](int rt) __attribute__((always_inline)) { return (ROW_SUMS ? rt ^ (2 * wp) : rt) * 16 + 4 * q; };
     auto row_of = [&](int rt, int j) __attribute__((always_inline)) { return t0 + local_row(rt) + j; };
     auto clamped = [&](int t) __attribute__((always_inline)) { return t < T ? t : T - 1; };
     // Epilogue parameters are fetched while the last DMAs drain: scale and zero-point of this lane's four columns
@@ -522,13 +539,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
     __syncthreads();
     mfma_result_fence();
     // Row sums: the four lanes of a row meet (fixed order), the waves' rows meet in LDS.
-    float *rs_lds = reinterpret_cast<float *>(lds);        // [128]
+    // (of 64 rows: two waves bring the same sums)
+    float *rs_lds = reinterpret_cast<float *>(lds);        // [16 RT]
     if constexpr (ROW_SUMS) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             rsum[i] += __shfl_xor(rsum[i], 16);
             rsum[i] += __shfl_xor(rsum[i], 32);
-            if (q == 0) rs_lds[32 * wn + 16 * i + c] = rsum[i];
+            if (q == 0) rs_lds[32 * wp + 16 * i + c] = rsum[i];
         }
         __syncthreads();
     }
@@ -568,9 +586,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
                 }
             };
             load_rows(std::integral_constant<int, 0>{}, dyv[0], rsv[0]);
-            static_for<8>([&](auto rt_c) {
+            static_for<RT>([&](auto rt_c) {
                 constexpr int rt = rt_c.value;
-                if constexpr (rt + 1 < 8) load_rows(std::integral_constant<int, rt + 1>{}, dyv[(rt + 1) & 1], rsv[(rt + 1) & 1]);
+                if constexpr (rt + 1 < RT) load_rows(std::integral_constant<int, rt + 1>{}, dyv[(rt + 1) & 1], rsv[(rt + 1) & 1]);
                 float dm[4];                                   // rows past T contribute nothing
 #pragma unroll
                 for (int j = 0; j < 4; ++j) dm[j] = row_of(rt, j) < T ? 1.f : 0.f;
@@ -586,16 +604,16 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
                     }
                 }
                 // (r0 + r1) + (r2 + r3) over the pairs of row tiles: the same bits in whatever order a wave has them
-                // (pair p of the registers is pair p ^ wn of the tile), so that a column's sum does not depend on its wave
-                if constexpr (rt == 1 || rt == 5) {
+                // (pair p of the registers is pair p ^ wp of the tile), so that a column's sum does not depend on its wave
+                if constexpr (rt % 4 == 1 || (rt == RT - 1 && rt % 4 == 0)) {
                     first = pairsum;
                     pairsum = f32x4{0.f, 0.f, 0.f, 0.f};
                 }
-                if constexpr (rt == 3) {
-                    colsum = first + pairsum;
+                if constexpr (rt % 4 == 3 || rt == RT - 1) {
+                    if constexpr (rt < 4) colsum = first + pairsum;
+                    else colsum += first + pairsum;
                     pairsum = f32x4{0.f, 0.f, 0.f, 0.f};
                 }
-                if constexpr (rt == 7) colsum += first + pairsum;
             });
         }
 #pragma unroll
@@ -674,34 +692,37 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
             // one contraction range per workgroup: every wave holds the finished sums of its row tiles
             if (!wave_on) return;
             load_terms(0, terms[0]);
-            static_for<8>([&](auto rt_c) {
+            static_for<RT>([&](auto rt_c) {
                 constexpr int rt = rt_c.value;
-                if constexpr (rt + 1 < 8) load_terms(rt + 1, terms[(rt + 1) & 1]);
+                if constexpr (rt + 1 < RT) load_terms(rt + 1, terms[(rt + 1) & 1]);
                 f32x4 sum[4];
 #pragma unroll
                 for (int ct = 0; ct < 4; ++ct) sum[ct] = read_acc(acc[rt][ct]);
                 store_rows(rt, sum, terms[rt & 1]);
             });
         } else {
-            // sum the two contraction halves: wave wk keeps row tiles [4 wk, 4 wk + 4) and sends the others
-            f32x4 *xch = reinterpret_cast<f32x4 *>(lds);       // [8 waves][16 tiles][64 lanes]
+            // sum the two contraction halves: waves with wk = 0 keep the first half of the row tiles (rounded up) and send the
+            // others, waves with wk = 1 the other way round
+            f32x4 *xch = reinterpret_cast<f32x4 *>(lds);       // [8 waves][4 FIRST accumulator tiles][64 lanes]
+            constexpr int FIRST = (RT + 1) / 2;
+            static_assert(8 * 4 * FIRST * 1024 <= ring_bytes(2, RT), "the exchange reuses the ring");
             auto finish = [&](auto keep_c) __attribute__((always_inline)) {
                 constexpr int KEEP = decltype(keep_c)::value;  // first row tile this wave keeps
-                constexpr int SEND = 4 - KEEP;
+                constexpr int SEND = FIRST - KEEP, KEPT = KEEP ? RT - FIRST : FIRST, SENT = RT - KEPT;
                 {
-                    f32x4 *mine = xch + (size_t)wave * 16 * 64 + lane;
+                    f32x4 *mine = xch + (size_t)wave * (4 * FIRST) * 64 + lane;
 #pragma unroll
-                    for (int rtl = 0; rtl < 4; ++rtl)
+                    for (int rtl = 0; rtl < SENT; ++rtl)
 #pragma unroll
                         for (int ct = 0; ct < 4; ++ct) mine[(rtl * 4 + ct) * 64] = acc[SEND + rtl][ct];
                 }
                 __syncthreads();
                 if (!wave_on) return;
-                const f32x4 *theirs = xch + (size_t)(wave ^ 4) * 16 * 64 + lane;
+                const f32x4 *theirs = xch + (size_t)(wave ^ 4) * (4 * FIRST) * 64 + lane;
                 load_terms(KEEP, terms[0]);
-                static_for<4>([&](auto rt_c) {
+                static_for<KEPT>([&](auto rt_c) {
                     constexpr int rtl = rt_c.value;
-                    if constexpr (rtl + 1 < 4) load_terms(KEEP + rtl + 1, terms[(rtl + 1) & 1]);
+                    if constexpr (rtl + 1 < KEPT) load_terms(KEEP + rtl + 1, terms[(rtl + 1) & 1]);
                     f32x4 sum[4];
 #pragma unroll
                     for (int ct = 0; ct < 4; ++ct) sum[ct] = read_acc(acc[KEEP + rtl][ct]) + theirs[(rtl * 4 + ct) * 64];
@@ -709,7 +730,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
                 });
             };
             if (wk == 0) finish(std::integral_constant<int, 0>{});
-            else finish(std::integral_constant<int, 4>{});
+            else finish(std::integral_constant<int, FIRST>{});
         }
     }
     }
