@@ -924,7 +924,7 @@ peqa_status gemv_forward(int n, const GemvItem *items, int32_t T, size_t most, f
             l.S = S[j];
             l.partial = partial + poff;
             if (S[j] > 1) poff += (size_t)S[j] * (size_t)T * (size_t)L->n_out;
-            wgs += L->n_out / (64 * form.h) * S[j];
+            wgs += L->n_out / gemv_channels(form) * S[j];
         } else {
             g.layer[j] = g.layer[n - 1];                       // never selected: its wg_end is the total
         }

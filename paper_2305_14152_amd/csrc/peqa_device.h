@@ -294,6 +294,21 @@ __device__ __forceinline__ T kernarg_load(uint32_t byte_offset)
     return out;
 }
 
+// n / d and n % d of wavefront-uniform numbers with the host's magic = (2^32 - 1) / d: the product's high half is the quotient or
+// one less.  A few scalar instructions; the compiler's division is a chain of twenty vector instructions, 0.1 us each time
+// in the start of a kernel that lasts 5.
+struct Quotient {
+    uint32_t q, r;
+};
+__device__ __forceinline__ Quotient div_magic(uint32_t n, uint32_t d, uint32_t magic)
+{
+    uint32_t q = (uint32_t)(((uint64_t)n * magic) >> 32), r = n - q * d;
+    const bool up = r >= d;
+    r -= up ? d : 0u;
+    q = up ? q + 1u : q;
+    return {q, r};
+}
+
 // s_barrier alone: no implied wait on outstanding LDS or memory operations.
 __device__ __forceinline__ void bare_barrier() { asm volatile("s_barrier" ::: "memory"); }
 

@@ -191,7 +191,7 @@ int gemm_plan(int n, SplitJob *jobs, int T, bool grouped, bool single, bool dds,
                 const double chain = c.alone * piece + fixed, work = (c.shared * steps + fixed * wgs) / (2.0 * cus) + 0.3 * chain;
                 us = chain > work ? chain : work;
             }
-            if (bytes > 0) us += 5.0 + (double)bytes * 2.0 / 3.5e6;
+            if (bytes > 0) us += 4.0 + (double)bytes * 2.0 / 3.5e6;
             if (d == 1 && form == 0) {
                 best = 0.87 * us;
             } else if (us < (d == 1 ? best / 0.92 : best)) {       // (other tiles cost nothing beside: 5 % will do)

@@ -38,16 +38,18 @@ namespace peqa {
 
 namespace {
 
-// A workgroup owns 64 H channels (H = 1 or 2).
-constexpr int gv_srow(int h) { return 64 * h + 4; }   // padded rows of the scale tile (floats) and of byte zero-points
-constexpr int gv_zrow(int h) { return 64 * h + 8; }
+// A workgroup owns 64 H channels (H = 1 or 2), or 32 (H = 0, T <= 8).
+constexpr int gv_channels(int h) { return h == 0 ? 32 : 64 * h; }
+constexpr int gv_srow(int h) { return gv_channels(h) + 4; }   // padded rows of the scale tile (floats) and of byte zero-points
+constexpr int gv_zrow(int h) { return gv_channels(h) + 8; }
 constexpr int GV_LDS_MAX = 160 * 1024;
 constexpr int GV_SIMD_WAVES = 4;     // waves per SIMD that the registers of every form allow: the plan counts on them
-constexpr int GV_NBUF = 2;           // rounds a wave keeps in flight (three measured the same or slower in every form)
-// One round (64 features) of one wave in LDS: its packed words (2 KB; 1.5 KB of it at 3 bits), then NX KB of token rows
-// (8 rows x 128 B per KB: one DMA when T <= 8, two otherwise).
+// Rounds a wave keeps in flight (64 channels and more: three measured the same or slower).
+constexpr int gv_nbuf(int h) { return h == 0 ? 4 : 2; }
+// One round (64 features) of one wave in LDS: its packed words (2 KB per 64 channels; 1.5 KB of it at 3 bits), then NX KB of
+// token rows (8 rows x 128 B per KB: one DMA when T <= 8, two otherwise).
 constexpr int GV_B_BYTES = 2048;
-constexpr int gv_round_bytes(int h, int nx) { return h * GV_B_BYTES + nx * 1024; }
+constexpr int gv_round_bytes(int h, int nx) { return gv_channels(h) * (GV_B_BYTES / 64) + nx * 1024; }
 // Bytes of LDS per scale group of a workgroup's tile: 64 scales, and 64 zero-points as bytes or, with a trained offset, fp32.
 constexpr int gv_group_bytes(int h, bool zbyte) { return gv_srow(h) * 4 + (zbyte ? gv_zrow(h) : gv_srow(h) * 4); }
 
@@ -62,7 +64,13 @@ __device__ __forceinline__ void gv_wait_vmcnt()
     __builtin_amdgcn_s_waitcnt((N & 0xF) | (0x7 << 4) | (0xF << 8) | ((N >> 4) << 14));
 }
 
-// H: 64-channel halves of a workgroup.  NX: KB of token rows per round (1: T <= 8, 2: T <= 16).
+// H: 64-channel halves of a workgroup (0: half of one).  NX: KB of token rows per round (1: T <= 8, 2: T <= 16).
+//
+// H = 0: with at most 8 tokens, half of an MFMA's 16 rows would be padding.  Lanes c < 8 unpack the 8 half blocks of 32 channels for
+// features 0..31 of a round, lanes c >= 8 those for features 32..63, and rows 8..15 of the other operand are the same tokens'
+// features 32..63: of the product, rows 0..7 of columns c < 8 and rows 8..15 of columns c >= 8 are wanted (lanes (c, q) with
+// q / 2 = c / 8) and added up at the end, the rest is ignored.  As much unpacking per weight in workgroups half as large: for layers
+// of few channels, which the unpacking bounds on the compute units that they reach.
 // ZBYTE: zero-points are the stored integers (no trained offset dz), kept as bytes in LDS.
 template <int BITS, int H, int WAVES, int NX, bool ZBYTE>
 __global__ __launch_bounds__(WAVES * 64, GV_SIMD_WAVES) void gemv_kernel(GemvArgs a)
@@ -74,10 +82,14 @@ __global__ __launch_bounds__(WAVES * 64, GV_SIMD_WAVES) void gemv_kernel(GemvArg
     // (not pinned: the compiler places the unpacking and the matrix instructions, and the wait states between them)
     typedef HalfBlockUnpacker<BITS, false, kFieldBf16, false> Unpacker;
     constexpr int WORDS = Unpacker::WORDS;
-    constexpr int NBUF = GV_NBUF, ROUND = gv_round_bytes(H, NX), NDMA = 2 * H + NX, THREADS = WAVES * 64;
-    constexpr int GV_C = 64 * H, GV_SROW = gv_srow(H), GV_ZROW = gv_zrow(H);
-    static_assert(NBUF == 2, "the waits below");
-    static_assert(NBUF * ROUND >= 4096 * H, "the final sum reuses a wave's ring");
+    constexpr bool SMALL = H == 0;
+    static_assert(!SMALL || NX == 1, "32 channels: T <= 8");
+    constexpr int HH = SMALL ? 1 : H;                             // 16-column accumulators: 4 HH
+    constexpr int NBUF = gv_nbuf(H), ROUND = gv_round_bytes(H, NX), NDMA = (SMALL ? 1 : 2 * H) + NX, THREADS = WAVES * 64;
+    constexpr int X_AT = ROUND - NX * 1024;                       // token rows behind the packed words
+    constexpr int GV_C = gv_channels(H), GV_SROW = gv_srow(H), GV_ZROW = gv_zrow(H);
+    static_assert(NBUF == 2 || NBUF == 4, "the waits below");
+    static_assert(NBUF * ROUND >= 4 * HH * (4 * 64 + 16) * 4, "the final sum reuses a wave's ring");
     typedef typename std::conditional<ZBYTE, uint8_t, float>::type zp_t;
     constexpr int ZROW = ZBYTE ? GV_ZROW : GV_SROW;
     float *sS = reinterpret_cast<float *>(stage + WAVES * NBUF * ROUND);
@@ -85,8 +97,18 @@ __global__ __launch_bounds__(WAVES * 64, GV_SIMD_WAVES) void gemv_kernel(GemvArg
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15, q = lane >> 4;
+    const int hb = SMALL ? c & 7 : c;                             // the lane's half block within 64 (32) channels
     // which layer this workgroup belongs to, and that layer's descriptor: scalar loads from the argument block
     const int bx = blockIdx.x;
+    // (one word of every cache line of the descriptors, asked for together with the totals that choose among them: the
+    // choice then reads what is on its way already)
+    {
+        int touched[(sizeof(a.layer) + 63) / 64];
+#pragma unroll
+        for (unsigned i = 0; i < sizeof(a.layer) / 64; ++i) touched[i] = kernarg_load<int>(64 * i);
+#pragma unroll
+        for (unsigned i = 0; i < sizeof(a.layer) / 64; ++i) asm volatile("" :: "s"(touched[i]));
+    }
     int li = 0, wg0 = 0;
 #pragma unroll
     for (int i = 0; i < GEMV_MAX_LAYERS - 1; ++i) {
@@ -97,16 +119,17 @@ __global__ __launch_bounds__(WAVES * 64, GV_SIMD_WAVES) void gemv_kernel(GemvArg
     const float *l_s0 = L.s0, *l_ds = L.ds, *l_dz = L.dz;
     const uint8_t *l_z0 = L.z0;
     const int l_N = L.N, l_S = L.S;
-    const int tile = (int)((uint32_t)(bx - wg0) / (uint32_t)l_S), slice = (bx - wg0) - tile * l_S;
-    const int n0 = tile * GV_C;                                  // first channel, within its layer
+    const Quotient ts = div_magic((uint32_t)(bx - wg0), (uint32_t)l_S, L.s_magic);
+    const int slice = (int)ts.r;
+    const int n0 = (int)ts.q * GV_C;                             // first channel, within its layer
     const int K = L.K, G = L.G;
-    const int chunk_rounds = L.chunk >> 6;                        // 64-feature rounds per scale group
+    const int chunk_rounds = L.chunk_rounds;                      // 64-feature rounds per scale group
     // this workgroup's rounds [rbeg, rend); wave w takes the w-th of WAVES equal parts of them
-    const uint32_t R = (uint32_t)K >> 6;
-    const int rbeg = (int)((uint32_t)slice * R / (uint32_t)l_S), rend = (int)((uint32_t)(slice + 1) * R / (uint32_t)l_S);
-    const int wr0 = rbeg + (int)((uint32_t)(wave * (rend - rbeg)) / (uint32_t)WAVES);
-    const int nrounds = rbeg + (int)((uint32_t)((wave + 1) * (rend - rbeg)) / (uint32_t)WAVES) - wr0;
-    const int g_lo = (uint32_t)rbeg / (uint32_t)chunk_rounds;     // first scale group this workgroup touches
+    const int rbeg = slice * L.slice_rounds + (slice < L.slice_rem ? slice : L.slice_rem);
+    const int len = L.slice_rounds + (slice < L.slice_rem ? 1 : 0), rend = rbeg + len;
+    const int wr0 = rbeg + (int)((uint32_t)(wave * len) / (uint32_t)WAVES);
+    const int nrounds = rbeg + (int)((uint32_t)((wave + 1) * len) / (uint32_t)WAVES) - wr0;
+    const int g_lo = (int)div_magic((uint32_t)rbeg, (uint32_t)chunk_rounds, L.chunk_magic).q;   // first scale group touched
 
     uint32_t magic = kMagic;
     asm("" : "+v"(magic));                                      // in a register: as a constant, and-or takes two instructions
@@ -115,11 +138,19 @@ __global__ __launch_bounds__(WAVES * 64, GV_SIMD_WAVES) void gemv_kernel(GemvArg
     // each other along the features.
     constexpr uint32_t BLK = 2 * BITS * 4, TILE = 64 * BLK, HALF = TILE / 2;
     const uint8_t *bsrc = reinterpret_cast<const uint8_t *>(L.packed) +
-                          ((size_t)(n0 >> 7) * (K >> 5) + 2 * (size_t)wr0) * TILE + (size_t)((n0 >> 6) & 1) * HALF;
+                          ((size_t)(n0 >> 7) * (K >> 5) + 2 * (size_t)wr0) * TILE +
+                          (SMALL ? (size_t)((n0 >> 5) & 3) * (HALF / 2) : (size_t)((n0 >> 6) & 1) * HALF);
     const uint8_t *xsrc = reinterpret_cast<const uint8_t *>(L.X + ((size_t)wr0 << 6));
     const uint32_t ring = (uint32_t)(uintptr_t)stage + wave * NBUF * ROUND;
     uint32_t b_voff[2], x_voff[NX];
-    if constexpr (BITS == 4) {
+    if constexpr (SMALL) {
+        // one DMA: 4 bits, lane (c, q) its own words, half hb % 2 of block (hb / 2, q) of the tile of its features; 3 bits, the 48
+        // chunks of the two tiles in address order (the last 16 lanes repeat some into the buffer's unused tail)
+        const int x = lane < 48 ? lane : lane - 16;
+        b_voff[0] = BITS == 4 ? (uint32_t)(c >> 3) * TILE + (uint32_t)((hb >> 1) * 4 + q) * BLK + (uint32_t)(hb & 1) * 16u
+                              : (uint32_t)(x / 24) * TILE + (uint32_t)(x % 24) * 16u;
+        b_voff[1] = 0;
+    } else if constexpr (BITS == 4) {
         // DMA of step s: lane (c, q) fetches its own words, half c % 2 of block (c / 2, q)
 #pragma unroll
         for (int i = 0; i < 2; ++i) b_voff[i] = (uint32_t)i * TILE + (uint32_t)((c >> 1) * 4 + q) * BLK + (uint32_t)(c & 1) * 16u;
@@ -142,13 +173,14 @@ __global__ __launch_bounds__(WAVES * 64, GV_SIMD_WAVES) void gemv_kernel(GemvArg
     int issued = 0, slot = 0;
     auto issue_round = [&]() {
         const uint32_t dst = ring + slot * ROUND;
+        if constexpr (SMALL) gv_dma16(b_voff[0], bsrc, dst);
 #pragma unroll
         for (int h = 0; h < H; ++h) {
             gv_dma16(b_voff[0], bsrc + h * HALF, dst + h * GV_B_BYTES);
             gv_dma16(b_voff[1], bsrc + h * HALF, dst + h * GV_B_BYTES + 1024);
         }
 #pragma unroll
-        for (int i = 0; i < NX; ++i) gv_dma16(x_voff[i], xsrc, dst + H * GV_B_BYTES + i * 1024);
+        for (int i = 0; i < NX; ++i) gv_dma16(x_voff[i], xsrc, dst + X_AT + i * 1024);
         bsrc += 2 * TILE;
         xsrc += 128;
         ++issued;
@@ -160,14 +192,15 @@ __global__ __launch_bounds__(WAVES * 64, GV_SIMD_WAVES) void gemv_kernel(GemvArg
 
     // scale / zero-point tile of the slice: [groups touched][64 channels], transposed on the way into LDS (memory has a
     // channel's groups next to each other).  Channels are laid down so that a lane's four are neighbours.
-    const int cols = rend > rbeg ? (int)((uint32_t)(rend - 1) / (uint32_t)chunk_rounds) - g_lo + 1 : 1;
+    const int cols = rend > rbeg ? (int)div_magic((uint32_t)(rend - 1), (uint32_t)chunk_rounds, L.chunk_magic).q - g_lo + 1 : 1;
     auto store_entry = [&](int jj, int ch, float sv, uint32_t zv, float dzv) {
         const int pos = Unpacker::BY_PARITY ? (ch & ~7) + 4 * (ch & 1) + ((ch & 7) >> 1) : ch;
         sS[jj * GV_SROW + pos] = sv;
         if constexpr (ZBYTE) sZ[jj * ZROW + pos] = (uint8_t)zv;
         else sZ[jj * ZROW + pos] = kCodeOffset + (float)zv + dzv;
     };
-    const float inv_cols = 1.0f / (float)cols;                    // entry / cols in fp32: exact, entries are below 2^16
+    const float inv_cols = __builtin_amdgcn_rcpf((float)cols);    // (entry + 0.5) / cols in fp32: the entry's channel, exactly,
+                                                                  // at one unit in the last place off: entries are below 2^16
     if (cols == G && (G & 3) == 0) {
         // whole rows of a multiple of four groups: one contiguous run of 64 G entries, four at a time (16 bytes of s0 and of
         // ds, 4 bytes of z0), the loads of a batch issued together (indices clamped instead of branching)
@@ -228,18 +261,20 @@ __global__ __launch_bounds__(WAVES * 64, GV_SIMD_WAVES) void gemv_kernel(GemvArg
     }
     __syncthreads();
 
-    f32x4 y[4 * H], acc[4 * H], accrs = f32x4{0.f, 0.f, 0.f, 0.f};
+    f32x4 y[4 * HH], acc[4 * HH], accrs = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int ct = 0; ct < 4 * H; ++ct) { y[ct] = f32x4{0.f, 0.f, 0.f, 0.f}; acc[ct] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+    for (int ct = 0; ct < 4 * HH; ++ct) { y[ct] = f32x4{0.f, 0.f, 0.f, 0.f}; acc[ct] = f32x4{0.f, 0.f, 0.f, 0.f}; }
 
     // this lane's words and activation fragment of step 0 within a round (step 1: STEP_B bytes on; chunk 4 + q)
     constexpr int STEP_B = BITS == 4 ? 1024 : 768;
-    const uint8_t *b_lane = stage + wave * NBUF * ROUND + (BITS == 4 ? lane * 16 : ((c >> 1) * 4 + q) * 24 + 4 * (c & 1));
+    const uint8_t *b_lane = stage + wave * NBUF * ROUND +
+                            (BITS == 4 ? lane * 16 : (SMALL ? (c >> 3) * 384 : 0) + ((hb >> 1) * 4 + q) * 24 + 4 * (c & 1));
     // token row of this lane's activation fragment; with 8 rows staged, rows 8..15 (beyond T, never stored) read rows 0..7
-    const uint8_t *x_lane = stage + wave * NBUF * ROUND + H * GV_B_BYTES + (NX == 2 ? c : (c & 7)) * 128;
-    const int x_pos[2] = {(q ^ (c & 7)) * 16, ((4 + q) ^ (c & 7)) * 16};
-    int group_left = chunk_rounds - (int)((uint32_t)wr0 % (uint32_t)chunk_rounds);   // rounds to the end of the scale group
-    int gj = (int)((uint32_t)wr0 / (uint32_t)chunk_rounds) - g_lo;                    // its column of the tile
+    const uint8_t *x_lane = stage + wave * NBUF * ROUND + X_AT + (NX == 2 ? c : (c & 7)) * 128;
+    const int x_pos[2] = {((SMALL ? 4 * (c >> 3) + q : q) ^ (c & 7)) * 16, ((4 + q) ^ (c & 7)) * 16};
+    const Quotient wg = div_magic((uint32_t)wr0, (uint32_t)chunk_rounds, L.chunk_magic);
+    int group_left = chunk_rounds - (int)wg.r;                    // rounds to the end of the scale group
+    int gj = (int)wg.q - g_lo;                                    // its column of the tile
     uint32_t rd = 0;                                              // ring offset of the round being consumed
     // A compute unit's arbiter serves the older wave first: of the workgroups that share one, the one dispatched first runs
     // ahead, ends early, and leaves the others to finish with fewer loads in flight.  Where all workgroups of the launch are
@@ -247,23 +282,26 @@ __global__ __launch_bounds__(WAVES * 64, GV_SIMD_WAVES) void gemv_kernel(GemvArg
     // win the ties of the second half, and all end together (13B block, T = 1 and 5: 34.6 -> 33.7 and 35.5 -> 34.3 us).
     // Which came later is a guess from the index (the first prio_step workgroups are dealt one to every compute unit, and so
     // on); a wrong guess costs time only.  Where later workgroups take the places of earlier ones it cost 3 to 6 %.
-    const int prio = a.prio_step ? bx / a.prio_step : 0;
-    if (prio == 1) __builtin_amdgcn_s_setprio(1);
-    else if (prio == 2) __builtin_amdgcn_s_setprio(2);
-    else if (prio >= 3) __builtin_amdgcn_s_setprio(3);
+    if (a.prio_step && bx >= a.prio_step) {
+        if (bx < 2 * a.prio_step) __builtin_amdgcn_s_setprio(1);
+        else if (bx < 3 * a.prio_step) __builtin_amdgcn_s_setprio(2);
+        else __builtin_amdgcn_s_setprio(3);
+    }
 #pragma unroll 1
     for (int r = 0; r < nrounds; ++r) {
         if (r == nrounds >> 1) __builtin_amdgcn_s_setprio(0);
         // rounds r .. min(r + NBUF, nrounds) - 1 are in flight, issued in order: wait for r only
         const int after = issued - 1 - r;                         // rounds issued after r
-        if (after == 1) gv_wait_vmcnt<NDMA>();
+        if (NBUF > 3 && after == 3) gv_wait_vmcnt<3 * NDMA>();
+        else if (NBUF > 2 && after == 2) gv_wait_vmcnt<2 * NDMA>();
+        else if (after == 1) gv_wait_vmcnt<NDMA>();
         else gv_wait_vmcnt<0>();
         asm volatile("" ::: "memory");
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
+        for (int s = 0; s < (SMALL ? 1 : 2); ++s) {
             const u32x4 af = *reinterpret_cast<const u32x4 *>(x_lane + rd + x_pos[s]);
 #pragma unroll
-            for (int h = 0; h < H; ++h) {
+            for (int h = 0; h < HH; ++h) {
                 uint32_t bw[WORDS];
                 const uint8_t *sb = b_lane + rd + h * GV_B_BYTES + s * STEP_B;
                 if constexpr (BITS == 4) {
@@ -296,15 +334,15 @@ __global__ __launch_bounds__(WAVES * 64, GV_SIMD_WAVES) void gemv_kernel(GemvArg
             // end of a scale group, or of this wave's share: fold offset, zero-point and scale
             // of the group into y, restart the sums
 #pragma unroll
-            for (int h = 0; h < H; ++h) {
-                const f32x4 sc = *reinterpret_cast<const f32x4 *>(sS + gj * GV_SROW + 64 * h + 4 * c);
+            for (int h = 0; h < HH; ++h) {
+                const f32x4 sc = *reinterpret_cast<const f32x4 *>(sS + gj * GV_SROW + 64 * h + 4 * hb);
                 f32x4 zo;                                         // 16 + z of the lane's channels
                 if constexpr (ZBYTE) {
-                    const uint32_t zz = *reinterpret_cast<const uint32_t *>(sZ + gj * ZROW + 64 * h + 4 * c);
+                    const uint32_t zz = *reinterpret_cast<const uint32_t *>(sZ + gj * ZROW + 64 * h + 4 * hb);
 #pragma unroll
                     for (int i = 0; i < 4; ++i) zo[i] = kCodeOffset + (float)((zz >> (8 * i)) & 0xFFu);
                 } else {
-                    zo = *reinterpret_cast<const f32x4 *>(sZ + gj * ZROW + 64 * h + 4 * c);
+                    zo = *reinterpret_cast<const f32x4 *>(sZ + gj * ZROW + 64 * h + 4 * hb);
                 }
 #pragma unroll
                 for (int ct = 0; ct < 4; ++ct) {
@@ -321,23 +359,30 @@ __global__ __launch_bounds__(WAVES * 64, GV_SIMD_WAVES) void gemv_kernel(GemvArg
 
     // ---- sum the waves, then write Y (S = 1) or this slice's partial
     __syncthreads();                                              // everyone is done with the ring
-    float *red = reinterpret_cast<float *>(stage);                // [wave][column tile][row in lane][lane]
+    // [wave][column tile][row in lane][lane], column tiles 16 words further apart: those that share a bank otherwise are read together
+    float *red = reinterpret_cast<float *>(stage);
+    constexpr int CT = 4 * 64 + 16;
 #pragma unroll
-    for (int ct = 0; ct < 4 * H; ++ct)
+    for (int ct = 0; ct < 4 * HH; ++ct)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) red[((wave * 4 * H + ct) * 4 + j) * 64 + lane] = y[ct][j];
+        for (int j = 0; j < 4; ++j) red[(wave * 4 * HH + ct) * CT + j * 64 + lane] = y[ct][j];
     __syncthreads();
-    // the 4 H column tiles x 4 rows x 64 lanes of results are dealt to the threads; each adds the waves in order
-    for (int idx = tid; idx < 4 * H * 4 * 64; idx += THREADS) {
-        const int tc = idx >> 8, ct = tc & 3, j = (idx >> 6) & 3, ln = idx & 63, cl = ln & 15;
-        const int t = 4 * (ln >> 4) + j;
-        if (t >= a.T) continue;
+    // the T x GV_C results are dealt to the threads, channels fastest; each adds the waves in order
+    for (int idx = tid; idx < a.T * GV_C; idx += THREADS) {
+        const int t = SMALL ? idx >> 5 : H == 1 ? idx >> 6 : idx >> 7, nn = idx & (GV_C - 1);
+        const int cl = Unpacker::BY_PARITY ? 2 * ((nn >> 3) & 7) + (nn & 1) : (nn >> 2) & 15;   // lane (c, q) and column tile that hold it
+        const int tc = 4 * (nn >> 6) + (Unpacker::BY_PARITY ? (nn >> 1) & 3 : nn & 3);
+        const float *src = red + tc * CT + (t & 3) * 64 + 16 * (t >> 2) + cl;
         float v = 0.f;
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) v += red[((w * 4 * H + tc) * 4 + j) * 64 + ln];
-        const int n = n0 + 64 * (tc >> 2) + (Unpacker::BY_PARITY ? 4 * (cl & ~1) + 2 * ct + (cl & 1) : 4 * cl + ct);
-        if (l_S == 1) L.Y[(size_t)t * l_N + n] = (uint16_t)float_to_bf16_bits(v);
-        else L.partial[((size_t)slice * a.T + t) * l_N + n] = v;
+        for (int w = 0; w < WAVES; ++w) v += src[w * 4 * HH * CT];
+        if constexpr (SMALL) {                                    // the other 32 features of every round: columns c + 8, rows 8 + t
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) v += src[w * 4 * HH * CT + 2 * 16 + 8];
+        }
+        const uint32_t to = (uint32_t)t * (uint32_t)l_N + (uint32_t)(n0 + nn);   // (T N is below 2^31)
+        if (l_S == 1) L.Y[to] = (uint16_t)float_to_bf16_bits(v);
+        else L.partial[(size_t)slice * a.T * l_N + to] = v;
     }
 }
 
@@ -362,7 +407,7 @@ __global__ __launch_bounds__(256) void gemv_finish_kernel(GemvArgs a)
 
 static int gv_lds_bytes(const GemvForm &f, int nx, bool zbyte, int groups)
 {
-    return f.waves * GV_NBUF * gv_round_bytes(f.h, nx) + groups * gv_group_bytes(f.h, zbyte);
+    return f.waves * gv_nbuf(f.h) * gv_round_bytes(f.h, nx) + groups * gv_group_bytes(f.h, zbyte);
 }
 
 static int gv_per_cu(const GemvForm &f, int lds)                   // workgroups a compute unit holds: LDS, registers
@@ -394,6 +439,12 @@ static int gv_cols(int K, int chunk, int S)                        // most scale
 // layers of fewer tiles (K >= 6144) are sliced until every compute unit has a tile or a wave is down to four rounds; what
 // that gains has to pay for the second launch, 4 us.  us per call at T = 5, whole -> sliced: 5120 x 13824 22 -> 14 (3 slices),
 // 4096 x 11008 15 -> 12 (4), 1024 x 8192 12 -> 9 (4); 4096 x 4096 8.0 -> 9.3 (2), which is why shorter ones stay whole.
+//
+// At most 8 tokens, half a tile per compute unit and no layer long enough to be sliced: tiles of 32 channels, which bring twice
+// the units to bear.  A round of a wave is a chain of 0.4 us (its DMA's arrival, LDS, unpacking, MFMAs,
+// the fold), which two waves per SIMD do not fill: 16 waves from 72 rounds on.  us per call at T = 5, 64 channels -> 32 with 8 /
+// 16 waves: 768 x 768 g128 4.5 -> 4.3 / 5.0, 4096 x 4096 4-bit 7.7 -> 7.3 / 7.3, 5120 x 5120 3-bit g128 10.8 -> 9.9 / 9.1; with
+// slices before, 5120 x 13824 g128 14.8 -> 18.5 / 16.0, and 8064 x 28160 g64 17 us longer, which is why long ones stay.
 //
 // More tiles: four waves.  Every workgroup should be resident at once (the last, partly filled round is otherwise made of
 // few workgroups with a few loads in flight each) and no layer's much longer than the others': layers are sliced to at most
@@ -429,9 +480,10 @@ GemvForm gemv_plan(int n, const int *N, const int *K, const int *chunk, int bits
         return g;
     };
     if (tiles <= cus) {
-        const GemvForm f{1, 8};
+        const bool halves = T <= 8 && zbyte && 2 * tiles <= cus && rmax < 96;
+        const GemvForm f{halves ? 0 : 1, halves && rmax >= 72 ? 16 : 8};
         slice_all(f, rmax, GV_LDS_MAX);
-        for (int j = 0; j < n; ++j) {
+        for (int j = 0; j < n && !halves; ++j) {
             const int r = K[j] / 64, s = cus / tiles < r / 32 ? cus / tiles : r / 32;
             if (r >= 96 && s > S[j]) S[j] = s;
         }
@@ -475,11 +527,16 @@ hipError_t launch_gemv(int bits, const GemvForm &f, const GemvArgs &a_in, hipStr
     unsigned max_tn = 0;
     a.groups_cap = 1;
     for (int j = 0; j < a.n_layers; ++j) {
-        const GemvLayer &l = a.layer[j];
+        GemvLayer &l = a.layer[j];
         if (l.N % 128 != 0 || l.K % 128 != 0 || l.chunk % 64 != 0 || l.S < 1 || a.T < 1 || a.T > 16) return hipErrorInvalidValue;
         sliced = sliced || l.S > 1;
         zbyte = zbyte && l.dz == nullptr;
         if (l.S > 1 && (unsigned)a.T * (unsigned)l.N > max_tn) max_tn = (unsigned)a.T * (unsigned)l.N;
+        l.chunk_rounds = l.chunk / 64;
+        l.slice_rounds = l.K / 64 / l.S;
+        l.slice_rem = l.K / 64 % l.S;
+        l.s_magic = 0xFFFFFFFFu / (uint32_t)l.S;
+        l.chunk_magic = 0xFFFFFFFFu / (uint32_t)l.chunk_rounds;
         const int g = gv_cols(l.K, l.chunk, l.S);
         a.groups_cap = g > a.groups_cap ? g : a.groups_cap;
     }
@@ -509,13 +566,22 @@ hipError_t launch_gemv(int bits, const GemvForm &f, const GemvArgs &a_in, hipStr
         return hipGetLastError();
     };
     using std::integral_constant;
+    const integral_constant<int, 0> none;
     const integral_constant<int, 1> one;
     const integral_constant<int, 2> two;
     const integral_constant<int, 4> four;
     const integral_constant<int, 8> eight;
+    const integral_constant<int, 16> sixteen;
     const integral_constant<bool, true> zb;
     const integral_constant<bool, false> zf;
     auto on_form = [&](auto bits_c, auto nx_c) -> hipError_t {
+        if (f.h == 0) {
+            if constexpr (decltype(nx_c)::value == 1) {
+                if (zbyte && f.waves == 16) return go(none, sixteen, bits_c, nx_c, zb);
+                if (zbyte && f.waves == 8) return go(none, eight, bits_c, nx_c, zb);
+            }
+            return hipErrorInvalidValue;
+        }
         if (f.h == 2) return zbyte && f.waves == 4 ? go(two, four, bits_c, nx_c, zb) : hipErrorInvalidValue;
         if (f.waves == 8) return zbyte ? go(one, eight, bits_c, nx_c, zb) : go(one, eight, bits_c, nx_c, zf);
         return zbyte ? go(one, four, bits_c, nx_c, zb) : go(one, four, bits_c, nx_c, zf);

@@ -215,7 +215,10 @@ struct GemvLayer {
     int N, K, G;
     int chunk;                // features per scale group (K for per-channel layers)
     int S;                    // feature slices: a channel tile is S workgroups
-    int unused;               // (keeps the size a multiple of eight)
+    // set by launch_gemv: rounds of 64 features per scale group; rounds of a slice, one more in the first slice_rem slices;
+    // reciprocals (div_magic) of S and of chunk_rounds
+    int chunk_rounds, slice_rounds, slice_rem;
+    uint32_t s_magic, chunk_magic;
 };
 struct GemvArgs {
     GemvLayer layer[GEMV_MAX_LAYERS];   // must stay the first member: the kernels index it in the argument block
@@ -225,10 +228,11 @@ struct GemvArgs {
     int prio_step;                      // workgroups per step of priority, 0: none (set by launch_gemv)
     int groups_cap;                     // scale groups a workgroup's LDS holds (set by launch_gemv)
 };
-// Form of such a launch: 64 h channels per workgroup of that many waves.
+// Form of such a launch: 64 h channels (h = 0: 32) per workgroup of that many waves.
 struct GemvForm {
     int h, waves;
 };
+inline int gemv_channels(const GemvForm &f) { return f.h == 0 ? 32 : 64 * f.h; }
 // The form, and the slices of every layer (S[0..n)).  zbyte: no layer has a trained zero-point offset, so zero-points are
 // bytes in LDS.  most: the most bytes that the partial sums of the slices may take; 0 gives the fewest slices that LDS allows.
 // cus: compute units.
