@@ -24,7 +24,8 @@ struct Workspace {
     size_t min_total;
     int split_y, split_dx, split_dds;      // split_dx, split_dds: of the backward that computes both gradients
     int split_dx_alone;
-    int rt_y, rt_dx_alone;                 // row tiles per tile of those launches (the pair's: gemm_row_tiles(T))
+    int rt_y, rt_dx, rt_dx_alone;          // row tiles per tile of those launches
+    bool one_launch;                       // group-wise backward of both gradients: launch_gemm_dw
     size_t acc, acc_dds;
     size_t gemv_most;                      // T <= 16: the most bytes that the plan's partial sums may take
 };
@@ -108,7 +109,7 @@ Workspace carve(const peqa_layout *L, int32_t T, int32_t op, int cus)
         return w;
     }
     const int N = L->n_out, K = L->k_in, tiles_t = (T + 127) / 128;
-    w.rt_y = w.rt_dx_alone = peqa::gemm_row_tiles(T);
+    w.rt_y = w.rt_dx = w.rt_dx_alone = peqa::gemm_row_tiles(T);
     const size_t y_bytes = (size_t)T * N * sizeof(float), dx_bytes = (size_t)T * K * sizeof(float);
     const peqa::SplitJob y{(N + 255) / 256, K, y_bytes, 1}, dx{(K + 255) / 256, N, dx_bytes, 1};
     if (fwd) {
@@ -116,19 +117,29 @@ Workspace carve(const peqa_layout *L, int32_t T, int32_t op, int cus)
         size_t most = ~(size_t)0;
         if (w.total <= (size_t)PEQA_STATIC_SCRATCH_BYTES) most = (size_t)PEQA_STATIC_SCRATCH_BYTES - w.total;
         peqa::SplitJob j = y;
-        w.rt_y = peqa::gemm_plan(1, &j, T, grouped(L), true, false, most, cus);
+        w.rt_y = peqa::gemm_plan(1, &j, T, grouped(L), true, false, 0.0, most, cus);
         w.split_y = j.split;
         w.acc = w.total;
         if (j.split > 1) w.total += round256((size_t)j.split * y_bytes);
         return w;
     }
     peqa::SplitJob alone = dx;
-    w.rt_dx_alone = peqa::gemm_plan(1, &alone, T, grouped(L), true, false, ~(size_t)0, cus);
+    w.rt_dx_alone = peqa::gemm_plan(1, &alone, T, grouped(L), true, false, 0.0, ~(size_t)0, cus);
     w.split_dx = w.split_dx_alone = alone.split;
+    if (grouped(L)) {
+        w.rt_dx = w.rt_dx_alone;
+        const long long dw_tiles = (long long)(K / 128) * ((N + 255) / 256);
+        w.one_launch = peqa::bwd_one_launch((long long)tiles_t * dx.tiles_c + dw_tiles, cus);
+        if (w.one_launch) {
+            peqa::SplitJob beside = dx;
+            w.rt_dx = peqa::gemm_plan(1, &beside, T, true, false, false, dw_tiles * peqa::dw_tile_us(T), ~(size_t)0, cus);
+            w.split_dx = beside.split;
+        }
+    }
     if (!grouped(L) && op != PEQA_OP_BWD_KEPT) {
         peqa::SplitJob both[2] = {y, dx};
         both[0].out_bytes = 0;
-        (void)peqa::gemm_plan(2, both, T, false, false, true, ~(size_t)0, cus);
+        (void)peqa::gemm_plan(2, both, T, false, false, true, 0.0, ~(size_t)0, cus);
         w.split_dds = both[0].split;
         w.split_dx = both[1].split;
     }
@@ -604,33 +615,60 @@ static peqa_status bwd_impl(const peqa_layout *L, const uint32_t *packed, const 
         uint16_t *xt = reinterpret_cast<uint16_t *>(ws + w.xt), *dyt = reinterpret_cast<uint16_t *>(ws + w.dyt);
         // When dX is wanted too and its contraction runs two workgroups per compute unit, it goes first and spare
         // workgroups of its launch write the transposed copies that the token contraction needs.
-        const bool tp_in_dx = d_ds && by_tokens && dX && peqa::gemm_four_waves(peqa::gemm_tiles_t(T, w.rt_dx_alone) * ((K + 255) / 256) * w.split_dx);
-        auto run_dx = [&](bool with_transposes) -> peqa_status {
-            float *sb = reinterpret_cast<float *>(ws + w.table);
-            if (peqa::launch_group_table(s0, ds, z0, dz, N, G, sb, s) != hipSuccess) return PEQA_ERR_DEVICE;
+        const bool tp_in_dx = d_ds && by_tokens && dX && peqa::gemm_four_waves(peqa::gemm_tiles_t(T, w.rt_dx_alone) * ((K + 255) / 256) * w.split_dx_alone);
+        float *sb = reinterpret_cast<float *>(ws + w.table), *pc = reinterpret_cast<float *>(ws + w.pc);
+        auto dx_args = [&](int rt) {
             peqa::GemmArgs a{};
             a.packed = packed; a.A = dY; a.T = T; a.KC = N; a.C = K; a.K = K;
-            a.rt = w.rt_dx_alone; a.tiles_c = (K + 255) / 256; a.tiles_t = peqa::gemm_tiles_t(T, a.rt);
+            a.rt = rt; a.tiles_c = (K + 255) / 256; a.tiles_t = peqa::gemm_tiles_t(T, rt);
             a.N = N; a.gsz = L->group_size; a.G = G; a.sb = sb; a.out = dX;
+            return a;
+        };
+        const bool whole = peqa::dw_whole_groups(L->group_size);
+        auto dw_args = [&]() {
+            peqa::DwArgs a{};
+            a.Xt = xt; a.dYt = dyt; a.packed = packed; a.z0 = z0; a.dz = dz;
+            a.pc = whole ? d_ds : pc;
+            a.N = N; a.K = K; a.Tp = Tp; a.gsz = L->group_size; a.G = G;
+            a.tiles_f = K / 128; a.tiles_c = (N + 255) / 256;
+            return a;
+        };
+        auto run_dx = [&](bool with_transposes) -> peqa_status {
+            if (peqa::launch_group_table(s0, ds, z0, dz, N, G, sb, s) != hipSuccess) return PEQA_ERR_DEVICE;
+            peqa::GemmArgs a = dx_args(w.rt_dx_alone);
             if (with_transposes) {
                 a.tp_blocks = (Tp / 64) * (K / 64 + N / 64); a.tp_Tp = Tp; a.tp_X = X; a.tp_Xt = xt; a.tp_dYt = dyt;
             }
-            return run_contraction(L->bits, peqa::MODE_DX, a, w.split_dx, reinterpret_cast<float *>(ws + w.acc), s);
+            return run_contraction(L->bits, peqa::MODE_DX, a, w.split_dx_alone, reinterpret_cast<float *>(ws + w.acc), s);
         };
+        if (d_ds && dX && by_tokens && w.one_launch) {
+            // table and copies, both contractions, and what they leave in parts: three launches, or two
+            peqa::GroupPrep p{};
+            p.table.s0[0] = s0; p.table.ds[0] = ds; p.table.z0[0] = z0; p.table.sb[0] = sb; p.table.N[0] = N; p.table.G[0] = G;
+            p.table.n = 1; p.dz = dz;
+            p.tp[0] = peqa::TransposeJob{X, xt, T, K, Tp, (Tp / 64) * (K / 64)};
+            p.tp[1] = peqa::TransposeJob{dY, dyt, T, N, Tp, (Tp / 64) * (K / 64 + N / 64)};
+            p.n_tp = 2;
+            if (peqa::launch_group_prep(p, s) != hipSuccess) return PEQA_ERR_DEVICE;
+            peqa::GemmDwArgs m{};
+            m.job[0].a = dx_args(w.rt_dx);
+            m.job[0].a.split = w.split_dx; m.job[0].a.acc_part = reinterpret_cast<float *>(ws + w.acc);
+            m.job[0].mode = peqa::MODE_DX;
+            m.dw[0] = dw_args();
+            m.n_jobs = m.n_dw = 1;
+            if (peqa::launch_gemm_dw(L->bits, m, s) != hipSuccess) return PEQA_ERR_DEVICE;
+            peqa::FinishMulti f{};
+            if (w.split_dx > 1) f.job[f.n++] = peqa::FinishJob{m.job[0].a, peqa::MODE_DX};
+            if (!whole) f.sum[f.n_sums++] = peqa::chunk_sums(pc, d_ds, N, K, L->group_size);
+            return dev_status(peqa::launch_split_finish(f, s));
+        }
         if (tp_in_dx) {
             const peqa_status st = run_dx(true);
             if (st != PEQA_OK) return st;
         }
         if (d_ds && by_tokens) {
-            float *pc = reinterpret_cast<float *>(ws + w.pc);
             if (!tp_in_dx && peqa::launch_transpose_pad(X, K, xt, dY, N, dyt, T, s) != hipSuccess) return PEQA_ERR_DEVICE;
-            peqa::DwArgs a{};
-            a.Xt = xt; a.dYt = dyt; a.packed = packed; a.z0 = z0; a.dz = dz;
-            const bool whole = peqa::dw_whole_groups(L->group_size);
-            a.pc = whole ? d_ds : pc;
-            a.N = N; a.K = K; a.Tp = Tp; a.gsz = L->group_size; a.G = G;
-            a.tiles_f = K / 128; a.tiles_c = (N + 255) / 256;
-            if (peqa::launch_dw(L->bits, a, s) != hipSuccess) return PEQA_ERR_DEVICE;
+            if (peqa::launch_dw(L->bits, dw_args(), s) != hipSuccess) return PEQA_ERR_DEVICE;
             if (!whole && peqa::launch_chunk_reduce(pc, (size_t)N * G, L->group_size / 64, d_ds, s) != hipSuccess)
                 return PEQA_ERR_DEVICE;
         } else if (d_ds) {
@@ -698,15 +736,16 @@ static peqa_status bwd_impl(const peqa_layout *L, const uint32_t *packed, const 
         a_dx.split = w.split_dx;
         a_dx.acc_part = acc;
         if (peqa::launch_gemm_bwd_pair(L->bits, a_dds, a_dx, s) != hipSuccess) return PEQA_ERR_DEVICE;
+        // the pieces of dX and, if no later launch does it, the rows of the scale gradient: one launch
+        const bool rows = !d_dz && partial_rows > 1;
         if (w.split_dx > 1) {
             peqa::FinishMulti f{};
-            f.job[0].a = a_dx;
-            f.job[0].mode = peqa::MODE_DX;
-            f.n = 1;
+            f.job[f.n++] = peqa::FinishJob{a_dx, peqa::MODE_DX};
+            if (rows) f.sum[f.n_sums++] = peqa::SumJob{partial, d_ds, (size_t)N, 1, (size_t)N, partial_rows};
             if (peqa::launch_split_finish(f, s) != hipSuccess) return PEQA_ERR_DEVICE;
-        }
-        if (!d_dz && partial_rows > 1 && peqa::launch_reduce_partials(partial, partial_rows, (size_t)N, d_ds, s) != hipSuccess)
+        } else if (rows && peqa::launch_reduce_partials(partial, partial_rows, (size_t)N, d_ds, s) != hipSuccess) {
             return PEQA_ERR_DEVICE;
+        }
     } else {
         // one after the other; when dX follows the scale gradient, the sum of its partials rides in the launch
         // that scales dY

@@ -58,6 +58,7 @@ struct BlockSpace {
     size_t min_total;
     int split_y[PEQA_MAX_BLOCK], split_dx[PEQA_MAX_BLOCK], split_dds[PEQA_MAX_BLOCK];
     int rt_y[2], rt_dx[2];           // row tiles per tile of the launches of per-channel and of group-wise items
+    bool one_launch;                 // group-wise items: dX and token contractions in one launch (launch_gemm_dw)
     size_t acc[PEQA_MAX_BLOCK], acc_dds[PEQA_MAX_BLOCK];
 };
 
@@ -101,7 +102,18 @@ BlockSpace carve_block(int32_t n, const peqa_block_item *items, int32_t T, int32
             job[m++] = peqa::SplitJob{(C + 255) / 256, KC, out_bytes, 1};
         }
         if (m == 0) return peqa::gemm_row_tiles(T);
-        const int rt = peqa::gemm_plan(m, job, T, gw, false, mode == peqa::MODE_DDS, ~(size_t)0, cus);
+        double beside = 0.0;                                   // the token contractions in the launch of the group-wise dX
+        if (gw && mode == peqa::MODE_DX) {
+            long long dx_tiles = 0, dw_tiles = 0;
+            for (int i = 0; i < m; ++i) {
+                const peqa_layout *L = &items[of[i]].layout;
+                dx_tiles += (long long)tiles_t * job[i].tiles_c;
+                dw_tiles += (long long)(L->k_in / 128) * ((L->n_out + 255) / 256);
+            }
+            w.one_launch = peqa::bwd_one_launch(dx_tiles + dw_tiles, cus);
+            if (w.one_launch) beside = dw_tiles * peqa::dw_tile_us(T);
+        }
+        const int rt = peqa::gemm_plan(m, job, T, gw, false, mode == peqa::MODE_DDS, beside, ~(size_t)0, cus);
         for (int i = 0; i < m; ++i) split[of[i]] = job[i].split;
         return rt;
     };
@@ -424,8 +436,6 @@ peqa_status peqa_block_bwd(int32_t n, const peqa_block_item *items, int32_t T, v
     // ---- group-wise items.  Their (s, b) tables in one launch; every dX contraction in one launch, whose auxiliary
     // workgroups write the transposed copies of X (once per distinct input) and dY that the scale gradients read;
     // the token contractions of all scale gradients in one launch; the sums of their chunks in one launch.
-    st = group_tables(n, items, ws, w, true, s);
-    if (st != PEQA_OK) return st;
     peqa::MultiArgs mg{};
     peqa::DwMultiArgs dw{};
     const uint16_t *xt_of[PEQA_MAX_BLOCK] = {nullptr};
@@ -466,6 +476,36 @@ peqa_status peqa_block_bwd(int32_t n, const peqa_block_item *items, int32_t T, v
             dw.d_ds[dw.n_jobs++] = it.d_ds;
         }
     }
+    if (mg.n_jobs > 0 && dw.n_jobs > 0 && w.one_launch) {
+        // few tiles: tables and copies first, then both kinds of contraction, then what they leave in parts
+        peqa::GroupPrep p{};
+        for (int j = 0; j < n; ++j) {
+            const peqa_block_item &it = items[j];
+            if (!grouped(&it.layout) || !it.dX) continue;
+            const int i = p.table.n++;
+            p.table.s0[i] = it.s0; p.table.ds[i] = it.ds; p.table.z0[i] = it.z0;
+            p.table.sb[i] = reinterpret_cast<float *>(ws + w.table[j]);
+            p.table.N[i] = it.layout.n_out; p.table.G[i] = groups(&it.layout);
+        }
+        for (int i = 0; i < mg.n_tp; ++i) p.tp[i] = mg.tp[i];
+        p.n_tp = mg.n_tp;
+        if (peqa::launch_group_prep(p, s) != hipSuccess) return PEQA_ERR_DEVICE;
+        sort_jobs(mg);
+        peqa::GemmDwArgs m{};
+        for (int i = 0; i < mg.n_jobs; ++i) m.job[i] = mg.job[i];
+        for (int i = 0; i < dw.n_jobs; ++i) m.dw[i] = dw.job[i];
+        m.n_jobs = mg.n_jobs; m.n_dw = dw.n_jobs;
+        if (peqa::launch_gemm_dw(bits, m, s) != hipSuccess) return PEQA_ERR_DEVICE;
+        peqa::FinishMulti f{};
+        for (int i = 0; i < mg.n_jobs; ++i)
+            if (mg.job[i].a.split > 1) f.job[f.n++] = peqa::FinishJob{m.job[i].a, peqa::MODE_DX};
+        for (int i = 0; i < dw.n_jobs; ++i)
+            if (!peqa::dw_whole_groups(dw.job[i].gsz))
+                f.sum[f.n_sums++] = peqa::chunk_sums(dw.job[i].pc, dw.d_ds[i], dw.job[i].N, dw.job[i].K, dw.job[i].gsz);
+        return dev_status(peqa::launch_split_finish(f, s));
+    }
+    st = group_tables(n, items, ws, w, true, s);
+    if (st != PEQA_OK) return st;
     if (mg.n_jobs > 0 || mg.n_tp > 0) {
         sort_jobs(mg);
         place_aux(mg, 128);

@@ -5,6 +5,7 @@
 
 #include <stddef.h>
 
+#include "peqa_dw_tile.h"
 #include "peqa_tile.h"
 
 namespace peqa {
@@ -144,6 +145,35 @@ __global__ __launch_bounds__(256, 2) void gemm_multi_kernel(MultiArgs m)
     }
 }
 
+// The dX tiles and the token contractions of a group-wise backward (GemmDwArgs), which read nothing of each other's: the
+// workgroups that take longer first, so that the others fill the launch's end.  11008 x 4096, groups of 64, T = 500: FIGURES
+template <int BITS, int RT>
+__global__ __launch_bounds__(256, 2) void gemm_dw_kernel(GemmDwArgs m)
+{
+    extern __shared__ __align__(16) uint8_t lds[];
+    int b = (int)blockIdx.x;
+    int j = 0, wg0 = 0;
+    if (b >= m.dw_begin && b < m.dw_begin + m.dw_total) {
+        b -= m.dw_begin;
+#pragma unroll
+        for (int i = 0; i < DW_MAX_JOBS - 1; ++i) {
+            const int e = kernarg_load<int>((uint32_t)(offsetof(GemmDwArgs, dw_end) + 4 * i));
+            if (b >= e) { j = i + 1; wg0 = e; }
+        }
+        const DwArgs a = kernarg_load<DwArgs>((uint32_t)(offsetof(GemmDwArgs, dw) + j * sizeof(DwArgs)));
+        dw_tile<BITS>(a, b - wg0, lds);
+        return;
+    }
+    b -= m.gemm_begin;
+#pragma unroll
+    for (int i = 0; i < MULTI_MAX_JOBS - 1; ++i) {
+        const int e = kernarg_load<int>((uint32_t)(i * sizeof(MultiJob) + offsetof(MultiJob, wg_end)));
+        if (b >= e) { j = i + 1; wg0 = e; }
+    }
+    const GemmArgs a = kernarg_load<GemmArgs>((uint32_t)(j * sizeof(MultiJob) + offsetof(MultiJob, a)));
+    gemm_tile<BITS, MODE_DX, true, 1, RT>(a, b - wg0, lds);
+}
+
 }  // namespace
 
 template <int BITS, int MODE, bool GROUPED, int KW, int RT>
@@ -247,6 +277,29 @@ template <int RT>
 hipError_t GemmRows<RT>::pair(int bits, const GemmArgs &a_dds, const GemmArgs &a_dx, hipStream_t stream)
 {
     return bits == 4 ? launch_pair<4, RT>(a_dds, a_dx, stream) : launch_pair<3, RT>(a_dds, a_dx, stream);
+}
+
+template <int BITS, int RT>
+static hipError_t launch_with_dw(int workgroups, const GemmDwArgs &m, hipStream_t stream)
+{
+    constexpr int gemm_lds = ring_bytes(1, RT) + tbl_bytes(1), lds_bytes = gemm_lds > DW_LDS ? gemm_lds : DW_LDS;
+    static bool allowed[64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+    if (!allowed[dev]) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_dw_kernel<BITS, RT>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+        if (e != hipSuccess) return e;
+        allowed[dev] = true;
+    }
+    hipLaunchKernelGGL((gemm_dw_kernel<BITS, RT>), dim3(workgroups), dim3(256), lds_bytes, stream, m);
+    return hipGetLastError();
+}
+
+template <int RT>
+hipError_t GemmRows<RT>::with_dw(int bits, int workgroups, const GemmDwArgs &m, hipStream_t stream)
+{
+    return bits == 4 ? launch_with_dw<4, RT>(workgroups, m, stream) : launch_with_dw<3, RT>(workgroups, m, stream);
 }
 
 template <int RT>

@@ -35,6 +35,8 @@
 //                     partial per (token tile, channel, group).  This is the older of two routes to
 //                     the grouped scale gradient (the default contracts over tokens, peqa_dw.hip)
 //                     and runs only on request (option grouped_dds = 1).
+#include <stddef.h>
+
 #include "peqa_device.h"
 #include "peqa_kernels.h"
 
@@ -46,6 +48,24 @@ namespace {
 // HBM-bound, split x 4 + 2 bytes per element.
 __global__ __launch_bounds__(256) void split_finish_kernel(FinishMulti f)
 {
+    if ((int)blockIdx.y >= f.n) {
+        const SumJob S = kernarg_load<SumJob>((uint32_t)(offsetof(FinishMulti, sum) + (blockIdx.y - f.n) * sizeof(SumJob)));
+        const size_t j = (size_t)blockIdx.x * 256 + threadIdx.x;
+        if (j >= S.n) return;
+        const float *src = S.src + j * S.step_j;
+        float v = 0.f;
+        int i = 0;
+        for (; i + 8 <= S.count; i += 8) {                     // eight loads in flight, added in order
+            float p[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) p[u] = src[(size_t)(i + u) * S.step];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v += p[u];
+        }
+        for (; i < S.count; ++i) v += src[(size_t)i * S.step];
+        S.dst[j] = v;
+        return;
+    }
     const FinishJob J = kernarg_load<FinishJob>((uint32_t)(blockIdx.y * sizeof(FinishJob)));
     const GemmArgs &a = J.a;
     if (a.split < 2) return;
@@ -93,14 +113,16 @@ __global__ __launch_bounds__(256) void split_finish_kernel(FinishMulti f)
 
 hipError_t launch_split_finish(const FinishMulti &f, hipStream_t stream)
 {
-    size_t most = 0;
+    size_t most = 0;                                           // workgroups along x
     for (int j = 0; j < f.n; ++j) {
         const GemmArgs &a = f.job[j].a;
-        if (a.split > 1 && (size_t)a.T * a.C > most) most = (size_t)a.T * a.C;
+        const size_t wgs = a.split > 1 ? ((size_t)a.T * a.C + 1023) / 1024 : 0;
+        most = wgs > most ? wgs : most;
     }
+    for (int j = 0; j < f.n_sums; ++j) most = (f.sum[j].n + 255) / 256 > most ? (f.sum[j].n + 255) / 256 : most;
     if (most == 0) return hipSuccess;
     trace_before(KID_GEMM_FINISH, stream);
-    hipLaunchKernelGGL(split_finish_kernel, dim3((unsigned)((most + 1023) / 1024), f.n), dim3(256), 0, stream, f);
+    hipLaunchKernelGGL(split_finish_kernel, dim3((unsigned)most, f.n + f.n_sums), dim3(256), 0, stream, f);
     trace_after(KID_GEMM_FINISH, stream);
     return hipGetLastError();
 }
@@ -153,7 +175,7 @@ int gemm_multi_wgs(const GemmArgs &a) { return (a.tiles_t * a.tiles_c * gemm_pie
 //
 // Tiles of 64 rows where those of gemm_row_tiles leave the machine idle: a step of theirs is shorter by a third and more, and
 // there are up to twice as many.
-int gemm_plan(int n, SplitJob *jobs, int T, bool grouped, bool single, bool dds, size_t max_bytes, int cus)
+int gemm_plan(int n, SplitJob *jobs, int T, bool grouped, bool single, bool dds, double other_us, size_t max_bytes, int cus)
 {
     const int by_rows = gemm_row_tiles(T);
     int longest = 0, best_rt = by_rows;
@@ -195,7 +217,7 @@ int gemm_plan(int n, SplitJob *jobs, int T, bool grouped, bool single, bool dds,
                 const double mean = steps / wgs, more = wgs < 2 * cus ? (wgs > cus ? (double)(wgs - cus) / cus : 0.0) : 1.0;
                 const double beside = rt == 4 ? 0.0 : more * (mean < piece ? mean : piece);
                 const double chain = c.alone * (piece - beside) + c.shared * beside + fixed;
-                const double work = (c.shared * steps + fixed * wgs) / (2.0 * cus) + 0.3 * chain;
+                const double work = (c.shared * steps + fixed * wgs + other_us) / (2.0 * cus) + 0.3 * chain;
                 us = chain > work ? chain : work;
             }
             if (bytes > 0) us += 4.0 + (double)bytes * 2.0 / 3.5e6;
@@ -281,6 +303,50 @@ hipError_t launch_gemm_multi(int bits, bool grouped, MultiArgs &m, hipStream_t s
         return decltype(rows)::multi(bits, grouped ? mode0 : -1, total + m.aux_wgs, m, stream);
     });
     trace_after(kid, stream);
+    return e;
+}
+
+bool bwd_one_launch(long long tiles, int cus)
+{
+    return options().gemm_waves == 0 && options().bwd_pair < 0 && options().grouped_dds == 0 && tiles <= 8ll * cus;
+}
+
+hipError_t launch_gemm_dw(int bits, GemmDwArgs &m, hipStream_t stream)
+{
+    if (m.n_jobs < 1 || m.n_jobs > MULTI_MAX_JOBS || m.n_dw < 1 || m.n_dw > DW_MAX_JOBS) return hipErrorInvalidValue;
+    int total = 0, longest = 0, dw_steps = 0;
+    for (int j = 0; j < MULTI_MAX_JOBS; ++j) {
+        if (j < m.n_jobs) {
+            GemmArgs &a = m.job[j].a;
+            if (a.gsz <= 0 || a.tp_blocks || m.job[j].mode != MODE_DX || a.rt != m.job[0].a.rt) return hipErrorInvalidValue;
+            a.patch_t = a.tiles_t < 4 ? a.tiles_t : 4;
+            total += gemm_multi_wgs(a);
+            const int steps = a.KC / 32 / gemm_pieces(a);
+            longest = steps > longest ? steps : longest;
+        } else {
+            m.job[j] = m.job[m.n_jobs - 1];
+        }
+        m.job[j].wg_end = total;
+    }
+    m.dw_total = 0;
+    for (int j = 0; j < DW_MAX_JOBS; ++j) {
+        if (j < m.n_dw) {
+            if (!dw_args_ok(m.dw[j])) return hipErrorInvalidValue;
+            m.dw_total += dw_wgs(m.dw[j]);
+            dw_steps = m.dw[j].Tp / 32 > dw_steps ? m.dw[j].Tp / 32 : dw_steps;
+        } else {
+            m.dw[j] = m.dw[m.n_dw - 1];
+        }
+        m.dw_end[j] = m.dw_total;
+    }
+    // the longer workgroups first (a step of either takes about as long); both numbers of workgroups are multiples of 8
+    m.gemm_begin = dw_steps > longest ? m.dw_total : 0;
+    m.dw_begin = dw_steps > longest ? 0 : total;
+    trace_before(KID_GEMM_BWD, stream);
+    const hipError_t e = with_rows(m.job[0].a.rt, [&](auto rows) {
+        return decltype(rows)::with_dw(bits, total + m.dw_total, m, stream);
+    });
+    trace_after(KID_GEMM_BWD, stream);
     return e;
 }
 

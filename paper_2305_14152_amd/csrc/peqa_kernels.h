@@ -70,20 +70,29 @@ struct SplitJob {
     size_t out_bytes;         // fp32 bytes of one piece's partial result (T C 4); 0 for MODE_DDS, whose pieces add partial rows
     int split;                // out
 };
+// other_us: work of other tiles of the same launch, in us of one of two places per unit.
 // Returns the row tiles per tile of the launch.  single: the jobs are one contraction that runs by itself (launch_gemm), which
 // may take the eight-wave form.  dds: the launch has MODE_DDS jobs, whose partial rows go by gemm_row_tiles(T).
 // max_bytes: the most the partial results may take.  cus: compute units.
-int gemm_plan(int n, SplitJob *jobs, int T, bool grouped, bool single, bool dds, size_t max_bytes, int cus);
+int gemm_plan(int n, SplitJob *jobs, int T, bool grouped, bool single, bool dds, double other_us, size_t max_bytes, int cus);
 // Epilogue of the split MODE_Y / MODE_DX contractions of a launch: adds the pieces in order, then does what the tile's own
-// epilogue would have done.  Jobs with split 1 are skipped.
+// epilogue would have done.  Jobs with split 1 are skipped.  The same launch adds up what else the call has left in parts:
+// dst[j] = src[j step_j] + src[j step_j + step] + ... (count of them, in order) for j < n.
 constexpr int FINISH_MAX = 8;
 struct FinishJob {
     GemmArgs a;
     int mode;
 };
+struct SumJob {
+    const float *src;
+    float *dst;
+    size_t n, step_j, step;
+    int count;
+};
 struct FinishMulti {
     FinishJob job[FINISH_MAX];             // must stay the first member: indexed in the argument block
-    int n;
+    SumJob sum[FINISH_MAX];
+    int n, n_sums;
 };
 hipError_t launch_split_finish(const FinishMulti &f, hipStream_t stream);
 // whether a per-channel launch of that many 128 x 256 tiles takes the four-wave form (two workgroups per compute unit);
@@ -144,11 +153,13 @@ static_assert(sizeof(MultiArgs) <= 4096, "kernel argument block");
 hipError_t launch_gemm_multi(int bits, bool grouped, MultiArgs &m, hipStream_t stream);
 // The launches themselves, of tiles of RT row tiles: a contraction, a backward pair, or `workgroups` of a multi-contraction
 // launch (gmode: -1 per channel, else the mode of the group-wise jobs).
+struct GemmDwArgs;
 template <int RT>
 struct GemmRows {
     static hipError_t one(int bits, int mode, const GemmArgs &a, hipStream_t stream);
     static hipError_t pair(int bits, const GemmArgs &a_dds, const GemmArgs &a_dx, hipStream_t stream);
     static hipError_t multi(int bits, int gmode, int workgroups, const MultiArgs &m, hipStream_t stream);
+    static hipError_t with_dw(int bits, int workgroups, const GemmDwArgs &m, hipStream_t stream);
 };
 // workgroups a contraction's tiles (and pieces of tiles) take in a launch (a multiple of 8)
 int gemm_multi_wgs(const GemmArgs &a);
@@ -167,6 +178,9 @@ struct DwArgs {
     int gsz, G;               // group size (multiple of 64) and groups per channel
     int tiles_f, tiles_c;     // K / 128, ceil(N / 256)
 };
+// workgroups of a layer: its tiles, rounded up to a whole number per XCD
+inline int dw_wgs(const DwArgs &a) { return (a.tiles_f * a.tiles_c + 7) / 8 * 8; }
+bool dw_args_ok(const DwArgs &a);          // what the kernel's indexing assumes
 // X [T, K] -> xt, dY [T, N] -> dyt
 hipError_t launch_transpose_pad(const uint16_t *X, int K, uint16_t *xt, const uint16_t *dY, int N, uint16_t *dyt, int T,
                                 hipStream_t stream);
@@ -189,6 +203,27 @@ struct DwMultiArgs {
 };
 hipError_t launch_dw_multi(int bits, DwMultiArgs &m, hipStream_t stream);
 hipError_t launch_chunk_reduce_multi(const DwMultiArgs &m, hipStream_t stream);
+// Both contractions of a group-wise backward in ONE launch of four-wave workgroups: the dX tiles of the jobs and the tiles of
+// the token contractions.  Everything that either reads (tables, transposed copies: launch_group_prep) is complete before.
+struct GemmDwArgs {
+    MultiJob job[MULTI_MAX_JOBS];          // must stay the first member: indexed in the argument block.  MODE_DX, group-wise
+    DwArgs dw[DW_MAX_JOBS];
+    int dw_end[DW_MAX_JOBS];               // workgroups of token contraction j and all before it (unused entries: the total)
+    int n_jobs, n_dw;
+    int gemm_begin, dw_begin, dw_total;    // set by the launch: one of the begins is 0
+};
+static_assert(sizeof(GemmDwArgs) <= 4096, "kernel argument block");
+hipError_t launch_gemm_dw(int bits, GemmDwArgs &m, hipStream_t stream);
+// us that a tile of the token contraction takes with another beside it
+inline double dw_tile_us(int T) { return 0.66 * ((T + 63) / 64 * 2) + 8.0; }
+// its chunk sums pc [N, K / 64] -> d_ds [N, K / gsz]
+inline SumJob chunk_sums(const float *pc, float *d_ds, int N, int K, int gsz)
+{
+    return SumJob{pc, d_ds, (size_t)N * (size_t)(K / gsz), (size_t)(gsz / 64), 1, gsz / 64};
+}
+// Whether a group-wise backward of both gradients goes that way: `tiles` of dX (of gemm_row_tiles rows) and of the token
+// contractions together.  Launches of many rounds keep the copies in spare workgroups of the dX launch.
+bool bwd_one_launch(long long tiles, int cus);
 // The (s, b) tables of up to GT_MAX layers in one launch.
 constexpr int GT_MAX = 8;
 struct GroupTableMulti {
@@ -199,6 +234,15 @@ struct GroupTableMulti {
     int n;
 };
 hipError_t launch_group_table_multi(const GroupTableMulti &a, hipStream_t stream);
+// Tables and transposed copies in one launch.
+struct GroupPrep {
+    GroupTableMulti table;
+    TransposeJob tp[2 * MULTI_MAX_JOBS];   // tile_end: running totals
+    const float *dz;                       // of the only table, or NULL
+    int table_end[GT_MAX];                 // set by the launch
+    int n_tp, by_tiles;
+};
+hipError_t launch_group_prep(GroupPrep &a, hipStream_t stream);
 
 // Arguments of the T <= 16 forward (peqa_gemv.hip): up to GEMV_MAX_LAYERS layers in one launch, laid side by
 // side along the workgroup index.  Every layer has its own shape, input and slicing, so that the linears of a

@@ -1,5 +1,7 @@
 // Bandwidth-bound helper kernels around the MFMA contractions: row sums of X, the scaled
 // copy of dY, the fixed-order reduction of scale-gradient partials, and the AdamW step.
+#include <stddef.h>
+
 #include "peqa_device.h"
 #include "peqa_kernels.h"
 
@@ -154,6 +156,42 @@ __global__ __launch_bounds__(256) void group_table_tile_kernel(const float *__re
 {
     extern __shared__ __align__(16) float gt_lds[];
     group_table_tile(s0, ds, z0, dz, N, G, sb, (int)blockIdx.x * GT_CH, gt_lds);
+}
+
+// Tables and transposed copies of a group-wise backward (GroupPrep): the tables' workgroups first, then one per 64 x 64 tile of
+// the copies.  One launch where there were two, of 3 us and more each.
+__global__ __launch_bounds__(256) void group_prep_kernel(GroupPrep a)
+{
+    extern __shared__ __align__(16) float gt_lds[];
+    int b = (int)blockIdx.x;
+    if (b < a.table_end[GT_MAX - 1]) {
+        const float *s0 = a.table.s0[0], *ds = a.table.ds[0];
+        const uint8_t *z0 = a.table.z0[0];
+        float *sb = a.table.sb[0];
+        int N = a.table.N[0], G = a.table.G[0], b0 = 0;
+#pragma unroll
+        for (int i = 1; i < GT_MAX; ++i)
+            if (b >= a.table_end[i - 1]) {
+                s0 = a.table.s0[i]; ds = a.table.ds[i]; z0 = a.table.z0[i]; sb = a.table.sb[i]; N = a.table.N[i]; G = a.table.G[i];
+                b0 = a.table_end[i - 1];
+            }
+        if (a.by_tiles) {
+            group_table_tile(s0, ds, z0, a.dz, N, G, sb, (b - b0) * GT_CH, gt_lds);
+        } else {
+            const size_t j = (size_t)(b - b0) * 256 + threadIdx.x;
+            if (j < (size_t)N * G) group_table_entry(s0, ds, z0, a.dz, N, G, sb, j);
+        }
+        return;
+    }
+    b -= a.table_end[GT_MAX - 1];
+    int j = 0, b0 = 0;
+    for (int i = 0; i + 1 < a.n_tp; ++i) {
+        const int e = kernarg_load<int>((uint32_t)(offsetof(GroupPrep, tp) + i * sizeof(TransposeJob) + offsetof(TransposeJob, tile_end)));
+        if (b >= e) { j = i + 1; b0 = e; }
+    }
+    const TransposeJob J = kernarg_load<TransposeJob>((uint32_t)(offsetof(GroupPrep, tp) + j * sizeof(TransposeJob)));
+    const int bts = J.Tp >> 6;
+    transpose_pad_tile(J.src, J.T, J.C, J.dst, (b - b0) % bts, (b - b0) / bts, reinterpret_cast<uint16_t(*)[64 + 2]>(gt_lds));
 }
 
 // group_table_tile_kernel for several layers: blockIdx.y = layer.
@@ -448,6 +486,26 @@ hipError_t launch_group_table(const float *s0, const float *ds, const uint8_t *z
         const size_t n = (size_t)N * G;
         hipLaunchKernelGGL(group_table_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, s0, ds, z0, dz, N, G, sb);
     }
+    trace_after(KID_GROUP_TABLE, stream);
+    return hipGetLastError();
+}
+
+hipError_t launch_group_prep(GroupPrep &a, hipStream_t stream)
+{
+    const int n = a.table.n;
+    if (n < 0 || n > GT_MAX || a.n_tp < 0 || a.n_tp > 2 * MULTI_MAX_JOBS || (a.dz && n != 1)) return hipErrorInvalidValue;
+    int gmax = 0, blocks = 0;
+    for (int i = 0; i < n; ++i) gmax = a.table.G[i] > gmax ? a.table.G[i] : gmax;
+    a.by_tiles = gmax <= GT_TILE_MAX_G;
+    for (int i = 0; i < GT_MAX; ++i) {
+        if (i < n) blocks += a.by_tiles ? a.table.N[i] / GT_CH : (int)(((size_t)a.table.N[i] * a.table.G[i] + 255) / 256);
+        a.table_end[i] = blocks;
+    }
+    const int tp = a.n_tp > 0 ? a.tp[a.n_tp - 1].tile_end : 0;
+    if (blocks + tp == 0) return hipSuccess;
+    const int table_lds = a.by_tiles ? 2 * GT_CH * gmax * (int)sizeof(float) : 0, tp_lds = 64 * (64 + 2) * (int)sizeof(uint16_t);
+    trace_before(KID_GROUP_TABLE, stream);
+    hipLaunchKernelGGL(group_prep_kernel, dim3(blocks + tp), dim3(256), table_lds > tp_lds ? table_lds : tp_lds, stream, a);
     trace_after(KID_GROUP_TABLE, stream);
     return hipGetLastError();
 }
