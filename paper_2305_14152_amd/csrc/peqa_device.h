@@ -309,6 +309,14 @@ __device__ __forceinline__ Quotient div_magic(uint32_t n, uint32_t d, uint32_t m
     return {q, r};
 }
 
+// div_magic's reciprocal of a number from 1 to 8
+__device__ __forceinline__ uint32_t small_magic(int d)
+{
+    const uint32_t low = d == 1 ? 0xFFFFFFFFu : d == 2 ? 0x7FFFFFFFu : d == 3 ? 0x55555555u : 0x3FFFFFFFu;
+    const uint32_t high = d == 5 ? 0x33333333u : d == 6 ? 0x2AAAAAAAu : d == 7 ? 0x24924924u : 0x1FFFFFFFu;
+    return d < 5 ? low : high;
+}
+
 // s_barrier alone: no implied wait on outstanding LDS or memory operations.
 __device__ __forceinline__ void bare_barrier() { asm volatile("s_barrier" ::: "memory"); }
 

@@ -117,10 +117,11 @@ hipError_t launch_transpose_pad(const uint16_t *X, int K, uint16_t *xt, const ui
     return hipGetLastError();
 }
 
-hipError_t launch_dw(int bits, const DwArgs &a, hipStream_t stream)
+hipError_t launch_dw(int bits, const DwArgs &a_in, hipStream_t stream)
 {
-    // what the kernel's indexing assumes
-    if (!dw_args_ok(a)) return hipErrorInvalidValue;
+    if (!dw_args_ok(a_in)) return hipErrorInvalidValue;
+    DwArgs a = a_in;
+    a.strip_magic = 0xFFFFFFFFu / (8u * (uint32_t)a.tiles_c);
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
@@ -152,8 +153,9 @@ hipError_t launch_dw_multi(int bits, DwMultiArgs &m, hipStream_t stream)
     int total = 0;
     for (int j = 0; j < DW_MAX_JOBS; ++j) {
         if (j < m.n_jobs) {
-            const DwArgs &a = m.job[j];
+            DwArgs &a = m.job[j];
             if (!dw_args_ok(a)) return hipErrorInvalidValue;
+            a.strip_magic = 0xFFFFFFFFu / (8u * (uint32_t)a.tiles_c);
             total += dw_wgs(a);
         } else {
             m.job[j] = m.job[m.n_jobs - 1];

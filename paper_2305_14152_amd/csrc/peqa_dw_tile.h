@@ -32,10 +32,11 @@ __device__ __forceinline__ void dw_tile(const DwArgs &a, const int wg, uint8_t *
         const int lo = ntiles / 8 * xcd + min(xcd, ntiles % 8), mine = ntiles / 8 + (xcd < ntiles % 8 ? 1 : 0);
         if ((wg >> 3) >= mine) return;                     // (uniform)
         const int id = lo + (wg >> 3);
-        const int st = id / (8 * a.tiles_c), r = id - st * 8 * a.tiles_c;
-        const int left = a.tiles_f - 8 * st, rows = left < 8 ? left : 8;
-        tile_c = r / rows;
-        tile_f = 8 * st + (r - tile_c * rows);
+        const Quotient s = div_magic((uint32_t)id, 8u * (uint32_t)a.tiles_c, a.strip_magic);
+        const int left = a.tiles_f - 8 * (int)s.q, rows = left < 8 ? left : 8;
+        const Quotient t = div_magic(s.r, (uint32_t)rows, small_magic(rows));
+        tile_c = (int)t.q;
+        tile_f = 8 * (int)s.q + (int)t.r;
     }
 
     const int k0 = tile_f * DW_TF, n0 = tile_c * DW_TC;

@@ -173,8 +173,9 @@ int gemm_multi_wgs(const GemmArgs &a) { return (a.tiles_t * a.tiles_c * gemm_pie
 //                         backward    708 -> 310      749 -> 393      953 -> 853
 //   4096 x 11008 4-bit alone, forward 103 ->  28      107 ->  37      112 ->  72
 //
-// Tiles of 64 rows where those of gemm_row_tiles leave the machine idle: a step of theirs is shorter by a third and more, and
-// there are up to twice as many.
+// Tiles of fewer rows where those of gemm_row_tiles leave the machine idle: a step of 64 rows is shorter by a third and more, and
+// there are up to twice as many.  96 and 112 rows are weighed too: 11008 x 4096 in groups of 64, T = 500, has 172 tiles of 128 rows
+// for 256 units and 215 of 112, training step 184 -> 180 us.
 int gemm_plan(int n, SplitJob *jobs, int T, bool grouped, bool single, bool dds, double other_us, size_t max_bytes, int cus)
 {
     const int by_rows = gemm_row_tiles(T);
@@ -186,8 +187,10 @@ int gemm_plan(int n, SplitJob *jobs, int T, bool grouped, bool single, bool dds,
     if (options().gemm_waves != 0 || options().bwd_pair >= 0) return by_rows;   // forced forms are whole contractions
     constexpr int kMinPiece = 512;                             // shorter pieces are mostly fill and drain
     double best = 0.0;
-    for (int form = 0; form < (by_rows > 4 && !dds ? 2 : 1); ++form) {
-        const int rt = form ? 4 : by_rows, tiles_t = gemm_tiles_t(T, rt);
+    const int forms[4] = {by_rows, 4, 6, 7};
+    for (int form = 0; form < (by_rows > 4 && !dds ? 4 : 1); ++form) {
+        const int rt = forms[form], tiles_t = gemm_tiles_t(T, rt);
+        if (form && rt >= by_rows) continue;
         const StepTimes c = step_times(rt, grouped);
         const double fixed = rt == 4 ? 6.0 : 8.0;
         for (int d = 1; d <= 48; d += d < 6 ? 1 : (d < 12 ? 2 : 4)) {
@@ -206,16 +209,17 @@ int gemm_plan(int n, SplitJob *jobs, int T, bool grouped, bool single, bool dds,
                 if (s[j] > 1) bytes += s[j] * jobs[j].out_bytes;
             }
             if (d > 1 && bytes > max_bytes) continue;
-            if (form && wgs > 2 * cus) break;                          // not idle any more: 64 rows are the slower ones
+            if (form && wgs > 2 * cus) break;                          // not idle any more: fewer rows are the slower ones
             double us;
             if (single && wgs <= cus) {
                 us = c.halves * piece + fixed + 3.0;               // the eight-wave form
             } else {
                 // The longest shares its unit with others while they last (of average length), as far as there are more of them
-                // than units.  (Tiles of 64 rows: the weights' bytes bound what runs beside, the estimate without this was better:
-                // 3-bit block of d = 4736, T = 52, training step 145 against 154 us.)
-                const double mean = steps / wgs, more = wgs < 2 * cus ? (wgs > cus ? (double)(wgs - cus) / cus : 0.0) : 1.0;
-                const double beside = rt == 4 ? 0.0 : more * (mean < piece ? mean : piece);
+                // than units.  (T <= 64: the weights' bytes bound what runs beside, the estimate without this was better:
+                // 3-bit block of d = 4736, T = 52, training step 145 against 154 us.  Tiles of 64 rows of a larger T do share:
+                // 4-bit block of d = 2816, groups of 128, T = 111, forward 59 us in 304 of them, 48 in 304 pieces of 112 rows.)
+                const double mean = steps / wgs, more = wgs > cus ? 1.0 : 0.0;
+                const double beside = by_rows == 4 ? 0.0 : more * (mean < piece ? mean : piece);
                 const double chain = c.alone * (piece - beside) + c.shared * beside + fixed;
                 const double work = (c.shared * steps + fixed * wgs + other_us) / (2.0 * cus) + 0.3 * chain;
                 us = chain > work ? chain : work;
@@ -234,6 +238,16 @@ int gemm_plan(int n, SplitJob *jobs, int T, bool grouped, bool single, bool dds,
 }
 
 bool gemm_four_waves(int tiles) { return halves_per_workgroup(tiles, false) == 1; }
+
+// What a launch adds to a contraction's arguments.
+static void prepare_args(GemmArgs &a)
+{
+    a.patch_t = a.tiles_t < 4 ? a.tiles_t : 4;
+    a.whole_magic = 0xFFFFFFFFu / ((uint32_t)a.tiles_t * (uint32_t)a.tiles_c);
+    a.strip_magic = 0xFFFFFFFFu / ((uint32_t)a.patch_t * (uint32_t)a.tiles_c);
+    a.piece_units = a.KC / 128 / gemm_pieces(a);
+    a.unit_rem = a.KC / 128 % gemm_pieces(a);
+}
 
 // Calls f with the instantiation for tiles of rt row tiles.
 template <class F>
@@ -260,7 +274,7 @@ int gemm_row_tiles(int T)
 hipError_t launch_gemm(int bits, int mode, const GemmArgs &a_in, hipStream_t stream)
 {
     GemmArgs a = a_in;
-    a.patch_t = a.tiles_t < 4 ? a.tiles_t : 4;
+    prepare_args(a);
     const int kid = mode == MODE_Y ? KID_GEMM_Y : (mode == MODE_DDS ? KID_GEMM_DDS : KID_GEMM_DX);
     trace_before(kid, stream);
     const hipError_t e = with_rows(a.rt, [&](auto rows) { return decltype(rows)::one(bits, mode, a, stream); });
@@ -280,7 +294,7 @@ hipError_t launch_gemm_multi(int bits, bool grouped, MultiArgs &m, hipStream_t s
             GemmArgs &a = m.job[j].a;
             if ((a.gsz > 0) != grouped || a.tp_blocks) return hipErrorInvalidValue;
             if (grouped && m.job[j].mode == MODE_DDS) return hipErrorInvalidValue;
-            a.patch_t = a.tiles_t < 4 ? a.tiles_t : 4;
+            prepare_args(a);
             if (j > 0 && a.rt != rt) return hipErrorInvalidValue;
             rt = a.rt;
             total += gemm_multi_wgs(a);
@@ -319,7 +333,7 @@ hipError_t launch_gemm_dw(int bits, GemmDwArgs &m, hipStream_t stream)
         if (j < m.n_jobs) {
             GemmArgs &a = m.job[j].a;
             if (a.gsz <= 0 || a.tp_blocks || m.job[j].mode != MODE_DX || a.rt != m.job[0].a.rt) return hipErrorInvalidValue;
-            a.patch_t = a.tiles_t < 4 ? a.tiles_t : 4;
+            prepare_args(a);
             total += gemm_multi_wgs(a);
             const int steps = a.KC / 32 / gemm_pieces(a);
             longest = steps > longest ? steps : longest;
@@ -332,6 +346,7 @@ hipError_t launch_gemm_dw(int bits, GemmDwArgs &m, hipStream_t stream)
     for (int j = 0; j < DW_MAX_JOBS; ++j) {
         if (j < m.n_dw) {
             if (!dw_args_ok(m.dw[j])) return hipErrorInvalidValue;
+            m.dw[j].strip_magic = 0xFFFFFFFFu / (8u * (uint32_t)m.dw[j].tiles_c);
             m.dw_total += dw_wgs(m.dw[j]);
             dw_steps = m.dw[j].Tp / 32 > dw_steps ? m.dw[j].Tp / 32 : dw_steps;
         } else {
@@ -355,7 +370,8 @@ hipError_t launch_gemm_bwd_pair(int bits, const GemmArgs &dds_in, const GemmArgs
     GemmArgs a_dds = dds_in, a_dx = dx_in;
     if (a_dds.gsz > 0 || a_dx.gsz > 0 || a_dds.tp_blocks || a_dx.tp_blocks || a_dds.rt != a_dx.rt)
         return hipErrorInvalidValue;
-    a_dds.patch_t = a_dx.patch_t = a_dds.tiles_t < 4 ? a_dds.tiles_t : 4;
+    prepare_args(a_dds);
+    prepare_args(a_dx);
     trace_before(KID_GEMM_BWD, stream);
     const hipError_t e = with_rows(a_dds.rt, [&](auto rows) {
         return decltype(rows)::pair(bits, a_dds, a_dx, stream);

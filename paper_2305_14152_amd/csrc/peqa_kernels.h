@@ -27,7 +27,11 @@ struct GemmArgs {
     int K;                    // input features of the layer (fixes the block stride of `packed`)
     int tiles_c, tiles_t;     // ceil(C/256), ceil(T/(16 rt))
     int rt;                   // row tiles (of 16 tokens) per tile: gemm_row_tiles(T), or 4 where gemm_plan asks for it
-    int patch_t;              // token tiles per L2 patch (at most 4; set by the launches)
+    // set by the launches: token tiles per L2 patch (at most 4), reciprocals (div_magic) of the numbers of tiles and of tiles
+    // in patch_t rows, 128-deep units of a piece (one more in the first unit_rem pieces)
+    int patch_t;
+    uint32_t whole_magic, strip_magic;
+    int piece_units, unit_rem;
     const float *s0;          // [N]            (MODE_Y)
     const float *ds;          // [N] or NULL    (MODE_Y)
     const uint8_t *z0;        // [N]            (MODE_Y, MODE_DDS)
@@ -177,6 +181,7 @@ struct DwArgs {
     int N, K, Tp;             // Tp % 64 == 0
     int gsz, G;               // group size (multiple of 64) and groups per channel
     int tiles_f, tiles_c;     // K / 128, ceil(N / 256)
+    uint32_t strip_magic;     // reciprocal (div_magic) of 8 tiles_c, set by the launches
 };
 // workgroups of a layer: its tiles, rounded up to a whole number per XCD
 inline int dw_wgs(const DwArgs &a) { return (a.tiles_f * a.tiles_c + 7) / 8 * 8; }

@@ -96,15 +96,17 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
         int idx = (wg & 7) * per + (wg >> 3);
         if ((wg >> 3) >= per || idx >= n) return;          // padding to a multiple of 8 (uniform per workgroup)
         if (split > 1) {
-            piece = (int)((uint32_t)idx / (uint32_t)whole);
-            idx -= piece * whole;
+            const Quotient p = div_magic((uint32_t)idx, (uint32_t)whole, a.whole_magic);
+            piece = (int)p.q;
+            idx = (int)p.r;
         }
         const int strip = a.patch_t * a.tiles_c;           // patch_t rows of tiles, walked column by column
-        const int st = (int)((uint32_t)idx / (uint32_t)strip), r = idx - st * strip;
-        const int left = a.tiles_t - st * a.patch_t, rows = left < a.patch_t ? left : a.patch_t;
-        tile_c = (int)((uint32_t)r / (uint32_t)rows);
-        tile_t = st * a.patch_t + (r - tile_c * rows);
-        // The divisions are vector instructions.  Taken to scalar registers here, what follows from them is scalar too: left
+        const Quotient s = div_magic((uint32_t)idx, (uint32_t)strip, a.strip_magic);
+        const int left = a.tiles_t - (int)s.q * a.patch_t, rows = left < a.patch_t ? left : a.patch_t;
+        const Quotient t = div_magic(s.r, (uint32_t)rows, small_magic(rows));
+        tile_c = (int)t.q;
+        tile_t = (int)s.q * a.patch_t + (int)t.r;
+        // In scalar registers, so that what follows from them is scalar too: from divisions, which are vector instructions, left
         // to the compiler, the running pointers of the operands lived in vector registers and every DMA of the loop read
         // them back (an eighth more vector instructions, and a scalar register that a memory instruction reads two to four
         // wait states after a vector instruction wrote it, where the hardware wants five; with the waits instead of this,
@@ -132,8 +134,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
         half_on = grp < a.G;
     } else {
         // this piece's run of 128-deep units; nit is even (KW = 2) or a multiple of 4
-        const uint32_t units = (uint32_t)KC >> 7;
-        const int u0 = (int)(piece * units / (uint32_t)split), u1 = (int)((piece + 1) * units / (uint32_t)split);
+        const int u0 = piece * a.piece_units + (piece < a.unit_rem ? piece : a.unit_rem);
+        const int u1 = u0 + a.piece_units + (piece < a.unit_rem ? 1 : 0);
         kh0 = u0 * 128;
         nit = (u1 - u0) * (KW == 2 ? 2 : 4);               // >= 2: both contraction halves take half of the run
         kh1 = KW == 2 ? kh0 + (u1 - u0) * 64 : kh0;

@@ -79,3 +79,22 @@ def test_rows_of_a_tile_split_and_paired(gpu, oracle, bits, T):
         assert np.abs(gpu.bf16_dev_to_f64(Y) - Yref).max() <= Y_TOL * np.abs(Yref).max()
         assert np.abs(gpu.bf16_dev_to_f64(dX) - dXref).max() <= Y_TOL * np.abs(dXref).max()
         gpu.assert_scale_grad_close(gpu.to_host(g), gref)
+
+
+@pytest.mark.parametrize("N,T", [(14336, 530), (16384, 400)])
+@pytest.mark.parametrize("group", [0, 128])
+def test_fewer_rows_where_idle(gpu, N, T, group):
+    """Whole contractions that take tiles of 96 or 112 rows for their number: the bits of 128-row tiles, whose form is asked for."""
+    from paper_2305_14152_amd import peqa
+    print("fewer rows, N=%d T=%d group=%d" % (N, T, group), flush=True)
+    K, seed = 512, 83000 + N + T + group
+    layer = gpu.GpuLayer(synth.normal_f32(seed, (N, K), 0.02), 4, group)
+    X = synth.normal_bf16(seed + 1, (T, K), 1.0)
+    Y, forms = gpu.to_host(layer.fwd(X)), []
+    for waves in (4, 8):
+        peqa.set_option(peqa.PEQA_OPT_GEMM_WAVES, waves)
+        try:
+            forms.append(gpu.to_host(layer.fwd(X)))
+        finally:
+            peqa.set_option(peqa.PEQA_OPT_GEMM_WAVES, 0)
+    assert np.abs(Y).max() > 0 and any((Y == f).all() for f in forms)
