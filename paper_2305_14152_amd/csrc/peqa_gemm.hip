@@ -196,13 +196,14 @@ int gemm_plan(int n, SplitJob *jobs, int T, bool grouped, bool single, bool dds,
         for (int d = 1; d <= 48; d += d < 6 ? 1 : (d < 12 ? 2 : 4)) {
             const int target = (longest + d - 1) / d;              // features (or channels) per piece
             if (d > 1 && target < kMinPiece) break;
-            int s[FINISH_MAX], wgs = 0, piece = 0;
+            int s[FINISH_MAX], wgs = 0, slots = 0, piece = 0;
             double steps = 0.0;
             size_t bytes = 0;
             for (int j = 0; j < n; ++j) {
                 s[j] = (jobs[j].KC + target - 1) / target;
                 s[j] = s[j] < jobs[j].KC / kMinPiece ? s[j] : (jobs[j].KC < kMinPiece ? 1 : jobs[j].KC / kMinPiece);
                 wgs += jobs[j].tiles_c * tiles_t * s[j];
+                slots += (jobs[j].tiles_c * tiles_t * s[j] + 7) / 8 * 8;   // (as launched: gemm_multi_wgs)
                 const int len = (jobs[j].KC / 128 + s[j] - 1) / s[j] * 4;
                 piece = len > piece ? len : piece;
                 steps += (double)jobs[j].tiles_c * tiles_t * jobs[j].KC / 32;
@@ -218,7 +219,10 @@ int gemm_plan(int n, SplitJob *jobs, int T, bool grouped, bool single, bool dds,
                 // than units.  (T <= 64: the weights' bytes bound what runs beside, the estimate without this was better:
                 // 3-bit block of d = 4736, T = 52, training step 145 against 154 us.  Tiles of 64 rows of a larger T do share:
                 // 4-bit block of d = 2816, groups of 128, T = 111, forward 59 us in 304 of them, 48 in 304 pieces of 112 rows.)
-                const double mean = steps / wgs, more = wgs > cus ? 1.0 : 0.0;
+                // The workgroups that fill a job up to a multiple of 8 count: they end at once, but the dispatcher has dealt units to
+                // them, and the last tiles share (seven layers of a block of d = 896, T = 500: 250 pieces in 272 workgroups 35 us, the
+                // 400 pieces of 64 rows taken instead 28; in groups of 128 35.5, 216 pieces in 224 workgroups 29.5).
+                const double mean = steps / wgs, more = slots > cus ? 1.0 : 0.0;
                 const double beside = by_rows == 4 ? 0.0 : more * (mean < piece ? mean : piece);
                 const double chain = c.alone * (piece - beside) + c.shared * beside + fixed;
                 const double work = (c.shared * steps + fixed * wgs + other_us) / (2.0 * cus) + 0.3 * chain;
