@@ -132,8 +132,12 @@ Workspace carve(const peqa_layout *L, int32_t T, int32_t op, int cus)
         w.one_launch = peqa::bwd_one_launch((long long)tiles_t * dx.tiles_c + dw_tiles, cus);
         if (w.one_launch) {
             peqa::SplitJob beside = dx;
-            w.rt_dx = peqa::gemm_plan(1, &beside, T, true, false, false, dw_tiles * peqa::dw_tile_us(T), ~(size_t)0, cus);
-            w.split_dx = beside.split;
+            const int rt = peqa::gemm_plan(1, &beside, T, true, false, false, dw_tiles * peqa::dw_tile_us(T), ~(size_t)0, cus);
+            w.one_launch = !peqa::bwd_dx_chains(1, &beside, T, cus);
+            if (w.one_launch) {
+                w.rt_dx = rt;
+                w.split_dx = beside.split;
+            }
         }
     }
     if (!grouped(L) && op != PEQA_OP_BWD_KEPT) {

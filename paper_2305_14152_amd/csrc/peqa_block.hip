@@ -113,7 +113,11 @@ BlockSpace carve_block(int32_t n, const peqa_block_item *items, int32_t T, int32
             w.one_launch = peqa::bwd_one_launch(dx_tiles + dw_tiles, cus);
             if (w.one_launch) beside = dw_tiles * peqa::dw_tile_us(T);
         }
-        const int rt = peqa::gemm_plan(m, job, T, gw, false, mode == peqa::MODE_DDS, beside, ~(size_t)0, cus);
+        int rt = peqa::gemm_plan(m, job, T, gw, false, mode == peqa::MODE_DDS, beside, ~(size_t)0, cus);
+        if (beside > 0.0 && peqa::bwd_dx_chains(m, job, T, cus)) {
+            w.one_launch = false;
+            rt = peqa::gemm_plan(m, job, T, gw, false, false, 0.0, ~(size_t)0, cus);
+        }
         for (int i = 0; i < m; ++i) split[of[i]] = job[i].split;
         return rt;
     };

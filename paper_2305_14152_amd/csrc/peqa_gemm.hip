@@ -329,6 +329,23 @@ bool bwd_one_launch(long long tiles, int cus)
     return options().gemm_waves == 0 && options().bwd_pair < 0 && options().grouped_dds == 0 && tiles <= 8ll * cus;
 }
 
+// Whole contractions on no more than half of the units: their workgroups share with token tiles for as long as there are any and run
+// on alone, where a launch of their own has twice as many workgroups, in pieces or of 64 rows.  Backward in groups of 128, us, one
+// launch for both against one each: 15872 x 3840, T = 922, 299 against 240; 11008 x 4096, T = 922, 210 / 194; 7424 x 7168, T = 300,
+// 131 / 97; 4096 x 4096, T = 900, 88 / 84.  Short ones gain by the launches saved: 2048 x 2048, T = 1800, 47 / 64.  More tiles, or
+// pieces: 5120 x 5120, T = 1000, 114 / 136; 15872 x 3840, T = 250 (5 pieces), 81 / 94.
+bool bwd_dx_chains(int n, const SplitJob *jobs, int T, int cus)
+{
+    const int tiles_t = gemm_tiles_t(T, gemm_row_tiles(T));
+    int tiles = 0, longest = 0;
+    for (int j = 0; j < n; ++j) {
+        if (jobs[j].split > 1) return false;
+        tiles += tiles_t * jobs[j].tiles_c;
+        longest = jobs[j].KC > longest ? jobs[j].KC : longest;
+    }
+    return 2 * tiles <= cus && longest > 3072;
+}
+
 hipError_t launch_gemm_dw(int bits, GemmDwArgs &m, hipStream_t stream)
 {
     if (m.n_jobs < 1 || m.n_jobs > MULTI_MAX_JOBS || m.n_dw < 1 || m.n_dw > DW_MAX_JOBS) return hipErrorInvalidValue;

@@ -98,3 +98,35 @@ def test_fewer_rows_where_idle(gpu, N, T, group):
         finally:
             peqa.set_option(peqa.PEQA_OPT_GEMM_WAVES, 0)
     assert np.abs(Y).max() > 0 and any((Y == f).all() for f in forms)
+
+
+@pytest.mark.parametrize("group", [64, 128, 256])
+@pytest.mark.parametrize("N,K,T", [(4096, 4096, 900), (3072, 4096, 900), (3200, 4096, 1000)])
+def test_few_long_chains_of_the_backward(gpu, N, K, T, group):
+    """Group-wise backward on both sides of the rule that takes few, long and whole dX contractions out of the token
+    contractions' launch: whole contractions, so the bits of a forced form; the block call agrees."""
+    import torch
+    from paper_2305_14152_amd import peqa
+    print("chains, N=%d K=%d T=%d group=%d" % (N, K, T, group), flush=True)
+    seed = 84000 + N + T + group
+    layer = gpu.GpuLayer(synth.normal_f32(seed, (N, K), 0.02), 4, group)
+    X, dY = synth.normal_bf16(seed + 1, (T, K), 1.0), synth.normal_bf16(seed + 2, (T, N), 1.0)
+    dX, g = (gpu.to_host(v) for v in layer.bwd(X, dY))
+    forms = []
+    for waves in (4, 8):
+        peqa.set_option(peqa.PEQA_OPT_GEMM_WAVES, waves)
+        try:
+            forms.append([gpu.to_host(v) for v in layer.bwd(X, dY)])
+        finally:
+            peqa.set_option(peqa.PEQA_OPT_GEMM_WAVES, 0)
+    assert np.abs(dX).max() > 0 and any((dX == f[0]).all() for f in forms)
+    assert (g == forms[0][1]).all()
+    d = dict(L=layer.L, packed=layer.packed, s0=layer.s0, z0=layer.z0, X=gpu.to_dev(X), dY=gpu.to_dev(dY),
+             Y=torch.zeros((T, N), dtype=torch.int16, device="cuda"), dX=torch.zeros((T, K), dtype=torch.int16, device="cuda"),
+             d_ds=torch.zeros_like(layer.s0))
+    items = peqa.block_items([d])
+    nb = peqa.block_workspace_bytes(items, T, peqa.PEQA_OP_BWD)
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    peqa.block_bwd(items, T, ws, nb)
+    assert any((gpu.to_host(d["dX"]) == f[0]).all() for f in forms)
+    assert (gpu.to_host(d["d_ds"]).reshape(g.shape) == g).all()
