@@ -176,6 +176,8 @@ int gemm_multi_wgs(const GemmArgs &a) { return (a.tiles_t * a.tiles_c * gemm_pie
 // Tiles of fewer rows where those of gemm_row_tiles leave the machine idle: a step of 64 rows is shorter by a third and more, and
 // there are up to twice as many.  96 and 112 rows are weighed too: 11008 x 4096 in groups of 64, T = 500, has 172 tiles of 128 rows
 // for 256 units and 215 of 112, training step 184 -> 180 us.
+// Whole tiles of fewer rows may be estimated 8 % above the 13 % rule's bound, but not above a split that met it: 16000 x 11264 3-bit,
+// T = 131, forward 78 us in 189 whole tiles of 64 rows, 69 in 252 halves of 96; dX of 11008 x 4096, T = 922, see bwd_dx_chains.
 int gemm_plan(int n, SplitJob *jobs, int T, bool grouped, bool single, bool dds, double other_us, size_t max_bytes, int cus)
 {
     const int by_rows = gemm_row_tiles(T);
@@ -187,6 +189,7 @@ int gemm_plan(int n, SplitJob *jobs, int T, bool grouped, bool single, bool dds,
     if (options().gemm_waves != 0 || options().bwd_pair >= 0) return by_rows;   // forced forms are whole contractions
     constexpr int kMinPiece = 512;                             // shorter pieces are mostly fill and drain
     double best = 0.0;
+    bool whole = true;
     const int forms[4] = {by_rows, 4, 6, 7};
     for (int form = 0; form < (by_rows > 4 && !dds ? 4 : 1); ++form) {
         const int rt = forms[form], tiles_t = gemm_tiles_t(T, rt);
@@ -231,7 +234,8 @@ int gemm_plan(int n, SplitJob *jobs, int T, bool grouped, bool single, bool dds,
             if (bytes > 0) us += 4.0 + (double)bytes * 2.0 / 3.5e6;
             if (d == 1 && form == 0) {
                 best = 0.87 * us;
-            } else if (us < (d == 1 ? best / 0.92 : best)) {       // (other tiles cost nothing beside: 5 % will do)
+            } else if (us < (d == 1 && whole ? best / 0.92 : best)) {   // (other tiles cost nothing beside: 5 % will do, against
+                whole = d == 1;                                    // whole ones only)
                 best = us;
                 best_rt = rt;
                 for (int j = 0; j < n; ++j) jobs[j].split = s[j];
@@ -331,8 +335,8 @@ bool bwd_one_launch(long long tiles, int cus)
 
 // Whole contractions on no more than half of the units: their workgroups share with token tiles for as long as there are any and run
 // on alone, where a launch of their own has twice as many workgroups, in pieces or of 64 rows.  Backward in groups of 128, us, one
-// launch for both against one each: 15872 x 3840, T = 922, 299 against 240; 11008 x 4096, T = 922, 210 / 194; 7424 x 7168, T = 300,
-// 131 / 97; 4096 x 4096, T = 900, 88 / 84.  Short ones gain by the launches saved: 2048 x 2048, T = 1800, 47 / 64.  More tiles, or
+// launch for both against one each: 15872 x 3840, T = 922, 299 against 240; 11008 x 4096, T = 922, 210 / 180; 7424 x 7168, T = 300,
+// 131 / 97; 4096 x 4096, T = 900, 88 / 79.  Short ones gain by the launches saved: 2048 x 2048, T = 1800, 47 / 64.  More tiles, or
 // pieces: 5120 x 5120, T = 1000, 114 / 136; 15872 x 3840, T = 250 (5 pieces), 81 / 94.
 bool bwd_dx_chains(int n, const SplitJob *jobs, int T, int cus)
 {
