@@ -199,8 +199,11 @@ assert _UPDATE_ITEM.size == ctypes.sizeof(UpdateItem)
 
 def scale_update_multi(tensors, lr, beta1=0.9, beta2=0.999, eps=1e-8, weight_decay=0.0, step=1, stream=None):
     """tensors: sequence of (n_scales, ds, d_ds, m, v, s0)."""
-    items = b"".join([_UPDATE_ITEM.pack(int(n), _ptr(ds) or 0, _ptr(d_ds) or 0, _ptr(m) or 0, _ptr(v) or 0, _ptr(s0) or 0)
-                      for n, ds, d_ds, m, v, s0 in tensors])
+    try:
+        items = b"".join([_UPDATE_ITEM.pack(int(n), _ptr(ds) or 0, _ptr(d_ds) or 0, _ptr(m) or 0, _ptr(v) or 0, _ptr(s0) or 0)
+                          for n, ds, d_ds, m, v, s0 in tensors])
+    except struct.error:                       # numbers that C takes modulo 2^64 (a negative n_scales: refused by the library)
+        items = b"".join([bytes(UpdateItem(int(n), *map(_ptr, t))) for n, *t in tensors])
     opt = AdamW(lr, beta1, beta2, eps, weight_decay, int(step))
     _check(lib().peqa_scale_update_multi(len(tensors), items, ctypes.byref(opt), _stream(stream)),
            "peqa_scale_update_multi")
@@ -263,8 +266,12 @@ assert _FWD_ITEM.size == ctypes.sizeof(FwdItem)
 def _items(layers):
     """layers: sequence of (L, packed, s0, ds, z0, Y).  The bytes of an array of FwdItem (made field by field as ctypes
     structures they took 3.4 us for three, and take 2.4)."""
-    return b"".join([_FWD_ITEM.pack(bytes(L), _ptr(packed) or 0, _ptr(s0) or 0, _ptr(ds) or 0, _ptr(z0) or 0, _ptr(Y) or 0)
-                     for L, packed, s0, ds, z0, Y in layers])
+    try:
+        return b"".join([_FWD_ITEM.pack(bytes(L) if type(L) is Layout else bytes(FwdItem(L).layout),   # (a tuple, or TypeError)
+                                        _ptr(packed) or 0, _ptr(s0) or 0, _ptr(ds) or 0, _ptr(z0) or 0, _ptr(Y) or 0)
+                         for L, packed, s0, ds, z0, Y in layers])
+    except struct.error:                       # numbers that C takes modulo 2^64
+        return b"".join([bytes(FwdItem(L, *map(_ptr, t))) for L, *t in layers])
 
 
 def workspace_bytes_fused(layers, T):

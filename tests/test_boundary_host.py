@@ -337,3 +337,24 @@ def test_queries_and_refusals_do_not_touch_the_device(peqa):
     if "hipGetDevice" not in after:
         pytest.skip("this HIP runtime writes no call log")
     assert "hip" not in before.replace(peqa.LIB_PATH, ""), before[-2000:]
+
+
+def test_item_arrays_take_and_refuse_what_the_structures_do(peqa):
+    """Items of the fused forward and of the joint update, marshalled as bytes: the same bytes as ctypes' own structures, a
+    layout given as a tuple, numbers modulo 2^64, TypeError for what is no layout, PeqaError for a negative n_scales."""
+    L, good = peqa.layout(256, 512, 3, 128), 0x10000
+    want = bytes(peqa.FwdItem(L, good, good, None, good, 2 ** 63))
+    assert peqa._items([(L, good, good, None, good, 2 ** 63)] * 2) == 2 * want
+    assert peqa._items([((256, 512, 3, 128), good, good, None, good, 2 ** 63)]) == want
+    assert peqa._items([(L, good, good, 2 ** 64, good, 2 ** 63 - 2 ** 64)]) == want
+    assert peqa.workspace_bytes_fused([((256, 256, 4, 0), 16, 16, None, 16, 16)], 4) > 0
+    for bad in (b"x" * 16, b"x" * 40, 16, None, [256, 256, 4, 0], peqa.AdamW()):
+        with pytest.raises(TypeError):
+            peqa.workspace_bytes_fused([(bad, 16, 16, None, 16, 16)], 4)
+    for n, status in ((-1, peqa.PEQA_ERR_SHAPE), (2 ** 64, peqa.PEQA_ERR_SHAPE), (0, peqa.PEQA_ERR_SHAPE)):
+        with pytest.raises(peqa.PeqaError) as e:
+            peqa.scale_update_multi([(n, good, good, good, good, good)], 1e-3, stream=0)
+        assert e.value.status == status
+    with pytest.raises(peqa.PeqaError) as e:
+        peqa.scale_update_multi([(16, good, None, good, good, 2 ** 64 + good)], 1e-3, stream=0)
+    assert e.value.status == peqa.PEQA_ERR_NULL
