@@ -35,6 +35,7 @@
 //                     partial per (token tile, channel, group).  This is the older of two routes to
 //                     the grouped scale gradient (the default contracts over tokens, peqa_dw.hip)
 //                     and runs only on request (option grouped_dds = 1).
+#include <math.h>
 #include <stddef.h>
 
 #include "peqa_device.h"
@@ -162,8 +163,60 @@ int gemm_multi_wgs(const GemmArgs &a) { return (a.tiles_t * a.tiles_c * gemm_pie
 
 // A launch lasts as long as its longest workgroup (StepTimes; 8 us to fill the ring, drain and store, 6 with tiles of 64 rows) or
 // as the work that two workgroups per unit get through, plus about a
-// third of a workgroup for the last round.  Pieces of Y and dX cost a second launch and fp32 sums written and read again (3.5 TB/s).  Among
-// splits into pieces of equal length over the launch the one with the least estimate is taken, if that is 13 % below the
+// third of a workgroup for the last round.  Pieces of Y and dX cost a second launch and fp32 sums written and read again (3.5 TB/s).
+double gemm_form_us(int n, const SplitJob *jobs, int T, int rt, bool grouped, bool single, double other_us, int cus)
+{
+    const int tiles_t = gemm_tiles_t(T, rt);
+    const StepTimes c = step_times(rt, grouped);
+    const double fixed = rt == 4 ? 6.0 : 8.0;
+    int wgs = 0, slots = 0, piece = 0;
+    double steps = 0.0;
+    size_t bytes = 0;
+    for (int j = 0; j < n; ++j) {
+        const int s = jobs[j].split, len = (jobs[j].KC / 128 + s - 1) / s * 4;
+        wgs += jobs[j].tiles_c * tiles_t * s;
+        slots += (jobs[j].tiles_c * tiles_t * s + 7) / 8 * 8;          // (as launched: gemm_multi_wgs)
+        piece = len > piece ? len : piece;
+        steps += (double)jobs[j].tiles_c * tiles_t * jobs[j].KC / 32;
+        if (s > 1) bytes += s * jobs[j].out_bytes;
+    }
+    double us;
+    if (single && wgs <= cus) {
+        us = c.halves * piece + fixed + 3.0;                           // the eight-wave form
+    } else {
+        // The longest shares its unit with others while they last (of average length), as far as there are more of them
+        // than units.  (T <= 64: the weights' bytes bound what runs beside, the estimate without this was better:
+        // 3-bit block of d = 4736, T = 52, training step 145 against 154 us.  Tiles of 64 rows of a larger T do share:
+        // 4-bit block of d = 2816, groups of 128, T = 111, forward 59 us in 304 of them, 48 in 304 pieces of 112 rows.)
+        // The workgroups that fill a job up to a multiple of 8 count: they end at once, but the dispatcher has dealt units to
+        // them, and the last tiles share (seven layers of a block of d = 896, T = 500: 250 pieces in 272 workgroups 35 us, the
+        // 400 pieces of 64 rows taken instead 28; in groups of 128 35.5, 216 pieces in 224 workgroups 29.5).
+        const double mean = steps / wgs, more = slots > cus ? 1.0 : 0.0;
+        const double beside = gemm_row_tiles(T) == 4 ? 0.0 : more * (mean < piece ? mean : piece);
+        const double chain = c.alone * (piece - beside) + c.shared * beside + fixed;
+        const double work = (c.shared * steps + fixed * wgs + other_us) / (2.0 * cus) + 0.3 * chain;
+        us = chain > work ? chain : work;
+    }
+    return bytes > 0 ? us + 4.0 + (double)bytes * 2.0 / 3.5e6 : us;
+}
+
+constexpr int kMinPiece = 512;                                 // shorter pieces are mostly fill and drain
+
+// Cuts the longest contraction of a launch into d pieces and the others into as many of that length as they hold.  Returns the bytes
+// of the partial results.
+static size_t cut_jobs(int n, SplitJob *jobs, int longest, int d)
+{
+    const int target = (longest + d - 1) / d;
+    size_t bytes = 0;
+    for (int j = 0; j < n; ++j) {
+        const int s = (jobs[j].KC + target - 1) / target, most = jobs[j].KC < kMinPiece ? 1 : jobs[j].KC / kMinPiece;
+        jobs[j].split = s < most ? s : most;
+        if (jobs[j].split > 1) bytes += jobs[j].split * jobs[j].out_bytes;
+    }
+    return bytes;
+}
+
+// Among splits into pieces of equal length over the launch the one with the least estimate is taken, if that is 13 % below the
 // unsplit one: the estimate is no better than that, and splits with less to gain measured between 5 % faster and 7 %
 // slower (4096 x 11008 backward at T = 800 and 1200).  Measured, whole -> split, us per call:
 //                                     T = 17          T = 128         T = 500
@@ -176,73 +229,44 @@ int gemm_multi_wgs(const GemmArgs &a) { return (a.tiles_t * a.tiles_c * gemm_pie
 // Tiles of fewer rows where those of gemm_row_tiles leave the machine idle: a step of 64 rows is shorter by a third and more, and
 // there are up to twice as many.  96 and 112 rows are weighed too: 11008 x 4096 in groups of 64, T = 500, has 172 tiles of 128 rows
 // for 256 units and 215 of 112, training step 184 -> 180 us.
-// Whole tiles of fewer rows may be estimated 8 % above the 13 % rule's bound, but not above a split that met it: 16000 x 11264 3-bit,
-// T = 131, forward 78 us in 189 whole tiles of 64 rows, 69 in 252 halves of 96; dX of 11008 x 4096, T = 922, see bwd_dx_chains.
+// Of whole tiles of fewer rows, which cost nothing beside, the least estimate is taken if it is 5 % below; where pieces meet their 13 %
+// too, the lesser of the two estimates: 16000 x 11264 3-bit, T = 131, forward 78 us in 189 whole tiles of 64 rows, 69 in 252 halves
+// of 96; dX of 11008 x 4096, T = 922, see bwd_dx_chains.
 int gemm_plan(int n, SplitJob *jobs, int T, bool grouped, bool single, bool dds, double other_us, size_t max_bytes, int cus)
 {
     const int by_rows = gemm_row_tiles(T);
-    int longest = 0, best_rt = by_rows;
+    int longest = 0;
     for (int j = 0; j < n; ++j) {
         jobs[j].split = 1;
         longest = jobs[j].KC > longest ? jobs[j].KC : longest;
     }
     if (options().gemm_waves != 0 || options().bwd_pair >= 0) return by_rows;   // forced forms are whole contractions
-    constexpr int kMinPiece = 512;                             // shorter pieces are mostly fill and drain
-    double best = 0.0;
-    bool whole = true;
+    struct Form {
+        double us;
+        int rt, d;
+    };
+    Form plain{0.0, by_rows, 1}, whole{HUGE_VAL, by_rows, 1}, cut{HUGE_VAL, by_rows, 1};
     const int forms[4] = {by_rows, 4, 6, 7};
     for (int form = 0; form < (by_rows > 4 && !dds ? 4 : 1); ++form) {
         const int rt = forms[form], tiles_t = gemm_tiles_t(T, rt);
         if (form && rt >= by_rows) continue;
-        const StepTimes c = step_times(rt, grouped);
-        const double fixed = rt == 4 ? 6.0 : 8.0;
         for (int d = 1; d <= 48; d += d < 6 ? 1 : (d < 12 ? 2 : 4)) {
-            const int target = (longest + d - 1) / d;              // features (or channels) per piece
-            if (d > 1 && target < kMinPiece) break;
-            int s[FINISH_MAX], wgs = 0, slots = 0, piece = 0;
-            double steps = 0.0;
-            size_t bytes = 0;
-            for (int j = 0; j < n; ++j) {
-                s[j] = (jobs[j].KC + target - 1) / target;
-                s[j] = s[j] < jobs[j].KC / kMinPiece ? s[j] : (jobs[j].KC < kMinPiece ? 1 : jobs[j].KC / kMinPiece);
-                wgs += jobs[j].tiles_c * tiles_t * s[j];
-                slots += (jobs[j].tiles_c * tiles_t * s[j] + 7) / 8 * 8;   // (as launched: gemm_multi_wgs)
-                const int len = (jobs[j].KC / 128 + s[j] - 1) / s[j] * 4;
-                piece = len > piece ? len : piece;
-                steps += (double)jobs[j].tiles_c * tiles_t * jobs[j].KC / 32;
-                if (s[j] > 1) bytes += s[j] * jobs[j].out_bytes;
-            }
+            if (d > 1 && (longest + d - 1) / d < kMinPiece) break;     // features (or channels) per piece
+            const size_t bytes = cut_jobs(n, jobs, longest, d);
             if (d > 1 && bytes > max_bytes) continue;
+            int wgs = 0;
+            for (int j = 0; j < n; ++j) wgs += jobs[j].tiles_c * tiles_t * jobs[j].split;
             if (form && wgs > 2 * cus) break;                          // not idle any more: fewer rows are the slower ones
-            double us;
-            if (single && wgs <= cus) {
-                us = c.halves * piece + fixed + 3.0;               // the eight-wave form
-            } else {
-                // The longest shares its unit with others while they last (of average length), as far as there are more of them
-                // than units.  (T <= 64: the weights' bytes bound what runs beside, the estimate without this was better:
-                // 3-bit block of d = 4736, T = 52, training step 145 against 154 us.  Tiles of 64 rows of a larger T do share:
-                // 4-bit block of d = 2816, groups of 128, T = 111, forward 59 us in 304 of them, 48 in 304 pieces of 112 rows.)
-                // The workgroups that fill a job up to a multiple of 8 count: they end at once, but the dispatcher has dealt units to
-                // them, and the last tiles share (seven layers of a block of d = 896, T = 500: 250 pieces in 272 workgroups 35 us, the
-                // 400 pieces of 64 rows taken instead 28; in groups of 128 35.5, 216 pieces in 224 workgroups 29.5).
-                const double mean = steps / wgs, more = slots > cus ? 1.0 : 0.0;
-                const double beside = by_rows == 4 ? 0.0 : more * (mean < piece ? mean : piece);
-                const double chain = c.alone * (piece - beside) + c.shared * beside + fixed;
-                const double work = (c.shared * steps + fixed * wgs + other_us) / (2.0 * cus) + 0.3 * chain;
-                us = chain > work ? chain : work;
-            }
-            if (bytes > 0) us += 4.0 + (double)bytes * 2.0 / 3.5e6;
-            if (d == 1 && form == 0) {
-                best = 0.87 * us;
-            } else if (us < (d == 1 && whole ? best / 0.92 : best)) {   // (other tiles cost nothing beside: 5 % will do, against
-                whole = d == 1;                                    // whole ones only)
-                best = us;
-                best_rt = rt;
-                for (int j = 0; j < n; ++j) jobs[j].split = s[j];
-            }
+            const double us = gemm_form_us(n, jobs, T, rt, grouped, single, other_us, cus);
+            Form &least = d > 1 ? cut : form ? whole : plain;
+            if (us < least.us || (d == 1 && form == 0)) least = Form{us, rt, d};
         }
     }
-    return best_rt;
+    Form best = plain;
+    if (whole.us < 0.87 / 0.92 * plain.us) best = whole;
+    if (cut.us < 0.87 * plain.us && cut.us < best.us) best = cut;
+    (void)cut_jobs(n, jobs, longest, best.d);
+    return best.rt;
 }
 
 bool gemm_four_waves(int tiles) { return halves_per_workgroup(tiles, false) == 1; }

@@ -79,6 +79,8 @@ struct SplitJob {
 // may take the eight-wave form.  dds: the launch has MODE_DDS jobs, whose partial rows go by gemm_row_tiles(T).
 // max_bytes: the most the partial results may take.  cus: compute units.
 int gemm_plan(int n, SplitJob *jobs, int T, bool grouped, bool single, bool dds, double other_us, size_t max_bytes, int cus);
+// The estimate that it goes by: us of the launch of the jobs as split, in tiles of rt row tiles.
+double gemm_form_us(int n, const SplitJob *jobs, int T, int rt, bool grouped, bool single, double other_us, int cus);
 // Epilogue of the split MODE_Y / MODE_DX contractions of a launch: adds the pieces in order, then does what the tile's own
 // epilogue would have done.  Jobs with split 1 are skipped.  The same launch adds up what else the call has left in parts:
 // dst[j] = src[j step_j] + src[j step_j + step] + ... (count of them, in order) for j < n.

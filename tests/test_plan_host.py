@@ -1,0 +1,93 @@
+"""The plan of a tiled contraction launch (rows of a tile, pieces of a contraction) against its own estimate of every form that it
+weighs.  The planner is host code and works on 256 compute units here; no GPU needed."""
+import ctypes
+import random
+
+import pytest
+
+CUS = 256
+ANY = 2 ** 64 - 1
+
+
+class SplitJob(ctypes.Structure):
+    _fields_ = [("tiles_c", ctypes.c_int), ("KC", ctypes.c_int), ("out_bytes", ctypes.c_size_t), ("split", ctypes.c_int)]
+
+
+class Planner:
+    def __init__(self, lib):
+        i, b, d, z, p = ctypes.c_int, ctypes.c_bool, ctypes.c_double, ctypes.c_size_t, ctypes.POINTER(SplitJob)
+        self.plan_fn = lib._ZN4peqa9gemm_planEiPNS_8SplitJobEibbbdmi           # peqa::gemm_plan
+        self.plan_fn.argtypes, self.plan_fn.restype = [i, p, i, b, b, b, d, z, i], i
+        self.us_fn = lib._ZN4peqa12gemm_form_usEiPKNS_8SplitJobEiibbdi         # peqa::gemm_form_us
+        self.us_fn.argtypes, self.us_fn.restype = [i, p, i, i, b, b, d, i], d
+        self.rows_fn = lib._ZN4peqa14gemm_row_tilesEi                          # peqa::gemm_row_tiles
+
+    def rows(self, T):
+        return self.rows_fn(T)
+
+    def plan(self, jobs, T, grouped, single, dds=False, other=0.0, most=ANY):
+        """(row tiles per tile, pieces of every job); jobs: (columns, contraction length, bytes of a piece's results)."""
+        a = self._jobs(jobs, [1] * len(jobs))
+        return self.plan_fn(len(jobs), a, T, grouped, single, dds, other, most, CUS), [j.split for j in a]
+
+    def us(self, jobs, splits, T, rt, grouped, single, other=0.0):
+        return self.us_fn(len(jobs), self._jobs(jobs, splits), T, rt, grouped, single, other, CUS)
+
+    @staticmethod
+    def _jobs(jobs, splits):
+        return (SplitJob * len(jobs))(*[SplitJob((c + 255) // 256, kc, nb, s) for (c, kc, nb), s in zip(jobs, splits)])
+
+
+@pytest.fixture(scope="module")
+def planner():
+    from paper_2305_14152_amd import peqa
+    return Planner(peqa.lib())
+
+
+def _forward(layers, T):
+    return [(n, k, 4 * T * n) for n, k in layers]
+
+
+def _forms(planner, jobs, T, grouped, single, other):
+    """Every form that may be taken, with its estimate: (whole?, rows, pieces, us); the one of gemm_row_tiles rows, whole, first."""
+    longest, by_rows = max(kc for _, kc, _ in jobs), planner.rows(T)
+    for rt in [by_rows] + [r for r in (4, 6, 7) if r < by_rows]:
+        tiles_t = (T + 16 * rt - 1) // (16 * rt)
+        for d in (1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 28, 32, 36, 40, 44, 48):
+            if d > 1 and (longest + d - 1) // d < 512:
+                break
+            target = (longest + d - 1) // d
+            splits = [min((kc + target - 1) // target, max(1, kc // 512)) for _, kc, _ in jobs]
+            if rt != by_rows and sum((c + 255) // 256 * tiles_t * s for (c, _, _), s in zip(jobs, splits)) > 2 * CUS:
+                break
+            yield d == 1, rt, splits, planner.us(jobs, splits, T, rt, grouped, single, other)
+
+
+def test_no_form_over_one_with_a_lesser_estimate(planner):
+    """Of the forms that meet their bound (pieces 13 % below the whole contraction in its own rows, whole tiles of fewer rows
+    5 %), the one with the least estimate, in whatever order they are looked at."""
+    rng = random.Random(7)
+    shapes = [([(13184, 1536)], 571, False, True), ([(3456, 4096)], 1169, False, True), ([(14336, 512)], 530, False, True),
+              ([(384, 384)] * 4 + [(1024, 384)] * 2 + [(384, 1024)], 1092, False, False)]
+    for _ in range(1500):
+        d = 128 * max(1, round(2 ** rng.uniform(0, 6)))
+        f = 128 * round(d * rng.uniform(2.5, 3.5) / 128)
+        block = [(d, d)] * 4 + [(f, d)] * 2 + [(d, f)]
+        one = [(128 * rng.randint(1, 150), 128 * rng.randint(1, 100))]
+        shapes.append((rng.choice([block, [(3 * d, d), (d, d), (2 * f, d), (d, f)], one]), int(2 ** rng.uniform(4.1, 12)),
+                       rng.random() < 0.5, None))
+    taken = {"plain": 0, "rows": 0, "pieces": 0}
+    for layers, T, grouped, single in shapes:
+        single = single if single is not None else len(layers) == 1
+        jobs, other = _forward(layers, T), 0.0 if single else rng.choice([0.0, 500.0, 20000.0])
+        forms = list(_forms(planner, jobs, T, grouped, single, other))
+        unsplit = forms[0][3]
+        rows = [f for f in forms[1:] if f[0] and f[3] < 0.87 / 0.92 * unsplit]
+        pieces = [f for f in forms[1:] if not f[0] and f[3] < 0.87 * unsplit]
+        want = min(rows + pieces, key=lambda f: f[3], default=forms[0])
+        rt, splits = planner.plan(jobs, T, grouped, single, other=other)
+        got = planner.us(jobs, splits, T, rt, grouped, single, other)
+        assert got <= want[3], (layers, T, grouped, other, (rt, splits, got), want)
+        assert any((rt, splits) == (f[1], f[2]) for f in rows + pieces + forms[:1]), (layers, T, grouped, rt, splits)
+        taken["plain" if (rt, splits) == (forms[0][1], forms[0][2]) else "rows" if max(splits) == 1 else "pieces"] += 1
+    assert min(taken.values()) > 50, taken
