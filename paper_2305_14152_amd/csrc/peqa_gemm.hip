@@ -144,16 +144,17 @@ int halves_per_workgroup(int tiles, bool paired)
 }
 
 // us per 32-deep step of a tile: alone on its compute unit, with a second one beside it, and as one of two halves of eight waves
-// (per step of the whole).  Measured at K = 1024 to 4096, tiles of other columns on every unit.
+// (per step of the whole).  Measured at K = 1024 to 4096, tiles of other columns on every unit; what is shared, a tenth less than
+// with every unit full, as in the launches that are planned here (full ones: 0.66 of 128 rows per channel).
 struct StepTimes {
     double alone, shared, halves;
 };
 static StepTimes step_times(int rt, bool grouped)
 {
-    if (grouped) return rt == 4 ? StepTimes{0.39, 0.66, 0.29} : rt == 6 ? StepTimes{0.46, 0.79, 0.36}
-                      : rt == 7 ? StepTimes{0.48, 0.88, 0.39} : StepTimes{0.52, 0.92, 0.42};
-    return rt == 4 ? StepTimes{0.28, 0.43, 0.19} : rt == 6 ? StepTimes{0.33, 0.56, 0.26}
-         : rt == 7 ? StepTimes{0.36, 0.62, 0.29} : StepTimes{0.40, 0.68, 0.32};
+    if (grouped) return rt == 4 ? StepTimes{0.39, 0.59, 0.29} : rt == 6 ? StepTimes{0.46, 0.71, 0.36}
+                      : rt == 7 ? StepTimes{0.48, 0.79, 0.39} : StepTimes{0.52, 0.83, 0.42};
+    return rt == 4 ? StepTimes{0.28, 0.39, 0.19} : rt == 6 ? StepTimes{0.33, 0.50, 0.26}
+         : rt == 7 ? StepTimes{0.36, 0.56, 0.29} : StepTimes{0.40, 0.61, 0.32};
 }
 
 int gemm_pieces(const GemmArgs &a) { return a.split > 1 ? a.split : 1; }
@@ -163,41 +164,55 @@ int gemm_multi_wgs(const GemmArgs &a) { return (a.tiles_t * a.tiles_c * gemm_pie
 
 // A launch lasts as long as its longest workgroup (StepTimes; 8 us to fill the ring, drain and store, 6 with tiles of 64 rows) or
 // as the work that two workgroups per unit get through, plus about a
-// third of a workgroup for the last round.  Pieces of Y and dX cost a second launch and fp32 sums written and read again (3.5 TB/s).
+// third of the longest for the last round.  Pieces of Y and dX cost a second launch and fp32 sums written and read again (5 TB/s).
 double gemm_form_us(int n, const SplitJob *jobs, int T, int rt, bool grouped, bool single, double other_us, int cus)
 {
     const int tiles_t = gemm_tiles_t(T, rt);
     const StepTimes c = step_times(rt, grouped);
     const double fixed = rt == 4 ? 6.0 : 8.0;
-    int wgs = 0, slots = 0, piece = 0;
+    int wgs = 0, order[FINISH_MAX], len[FINISH_MAX];                   // jobs by falling length of a workgroup, as launched
     double steps = 0.0;
     size_t bytes = 0;
     for (int j = 0; j < n; ++j) {
-        const int s = jobs[j].split, len = (jobs[j].KC / 128 + s - 1) / s * 4;
+        const int s = jobs[j].split;
+        len[j] = (jobs[j].KC / 128 + s - 1) / s * 4;
         wgs += jobs[j].tiles_c * tiles_t * s;
-        slots += (jobs[j].tiles_c * tiles_t * s + 7) / 8 * 8;          // (as launched: gemm_multi_wgs)
-        piece = len > piece ? len : piece;
         steps += (double)jobs[j].tiles_c * tiles_t * jobs[j].KC / 32;
         if (s > 1) bytes += s * jobs[j].out_bytes;
+        int k = j;
+        for (; k > 0 && len[order[k - 1]] < len[j]; --k) order[k] = order[k - 1];
+        order[k] = j;
     }
+    const int piece = len[order[0]];
     double us;
     if (single && wgs <= cus) {
         us = c.halves * piece + fixed + 3.0;                           // the eight-wave form
     } else {
-        // The longest shares its unit with others while they last (of average length), as far as there are more of them
-        // than units.  (T <= 64: the weights' bytes bound what runs beside, the estimate without this was better:
-        // 3-bit block of d = 4736, T = 52, training step 145 against 154 us.  Tiles of 64 rows of a larger T do share:
-        // 4-bit block of d = 2816, groups of 128, T = 111, forward 59 us in 304 of them, 48 in 304 pieces of 112 rows.)
-        // The workgroups that fill a job up to a multiple of 8 count: they end at once, but the dispatcher has dealt units to
-        // them, and the last tiles share (seven layers of a block of d = 896, T = 500: 250 pieces in 272 workgroups 35 us, the
-        // 400 pieces of 64 rows taken instead 28; in groups of 128 35.5, 216 pieces in 224 workgroups 29.5).
-        const double mean = steps / wgs, more = slots > cus ? 1.0 : 0.0;
-        const double beside = gemm_row_tiles(T) == 4 ? 0.0 : more * (mean < piece ? mean : piece);
-        const double chain = c.alone * (piece - beside) + c.shared * beside + fixed;
-        const double work = (c.shared * steps + fixed * wgs + other_us) / (2.0 * cus) + 0.3 * chain;
+        // Workgroups are dealt to the units in turn, the longest first: the longest shares its unit with number cus, 2 cus, ... of
+        // them, for as long as those last.  The workgroups that fill a job up to a multiple of 8 count: they end at once, but the
+        // dispatcher has dealt units to them (seven layers of a block of d = 896, T = 500: 250 pieces in 272 workgroups 35 us, 400
+        // pieces of 64 rows 28; in groups of 128 35.5, 216 pieces in 224 workgroups 29.5).
+        int slots = 0, shared = 0, next = cus, second = 0, third = 0;
+        for (int k = 0; k < n; ++k) {
+            const SplitJob &job = jobs[order[k]];
+            slots += (job.tiles_c * tiles_t * job.split + 7) / 8 * 8;  // (as launched: gemm_multi_wgs)
+            for (; next < slots && shared < piece; next += cus) shared += len[order[k]];
+            if (second == 0 && slots >= 2 * cus) second = len[order[k]];
+            if (third == 0 && slots > 2 * cus) third = len[order[k]];
+        }
+        shared = shared < piece ? shared : piece;
+        const double chain = c.alone * (piece - shared) + c.shared * shared + fixed;
+        const double tail = other_us > 0.0 ? 0.2 : 0.3;                // (token tiles are short and fill the end)
+        const double work = (c.shared * steps + fixed * wgs + other_us) / (2.0 * cus) + tail * chain;
         us = chain > work ? chain : work;
+        // Number 2 cus starts where the first pair ends, and most of it runs alone: forward of d = 3584, f = 10240 in groups of 64,
+        // T = 65, 80 us in 342 workgroups, 85 in 520.
+        const double late = third ? c.shared * second + fixed + c.alone * third + fixed : 0.0;
+        us = late > us ? late : us;
+        // a token tile by itself: 1664 x 384, T = 3147, training step 75 us with dX in 104 whole tiles of 64 rows, 79 in 200 halves
+        if (other_us > 0.0 && us < dw_tile_alone_us(T)) us = dw_tile_alone_us(T);
     }
-    return bytes > 0 ? us + 4.0 + (double)bytes * 2.0 / 3.5e6 : us;
+    return bytes > 0 ? us + 4.0 + (double)bytes * 2.0 / 5e6 : us;
 }
 
 constexpr int kMinPiece = 512;                                 // shorter pieces are mostly fill and drain
@@ -216,9 +231,17 @@ static size_t cut_jobs(int n, SplitJob *jobs, int longest, int d)
     return bytes;
 }
 
-// Among splits into pieces of equal length over the launch the one with the least estimate is taken, if that is 13 % below the
-// unsplit one: the estimate is no better than that, and splits with less to gain measured between 5 % faster and 7 %
-// slower (4096 x 11008 backward at T = 800 and 1200).  Measured, whole -> split, us per call:
+// What a launch is made of: tiles of gemm_row_tiles rows or of fewer, whole or cut into pieces of equal length over the launch.  Taken
+// is the least estimate of those that lie below the plain launch (whole, gemm_row_tiles rows) by more than the estimate's own
+// error: 5 %; for pieces, where the plain launch has more than one round of workgroups and little to gain, 17 % (six splits
+// between 5 and 17 % of 580 to 1300 tiles of group-wise dX measured 3 to 9 % longer).
+//
+// Against all forms of 1600 launches (forwards, dX and scale gradients of blocks and layers, T = 20 to 1800), the time of the one
+// taken is 1.017 times the best in the geometric mean.  With the longest sharing for its mean-length neighbour or not at all, shared
+// steps as with every unit full, sums at 3.5 TB/s, 13 % throughout and no tiles of fewer rows past two per unit it was 1.032:
+// forward of d = 3072, T = 458, 118 us in 536 workgroups, now 106 in 670 of 96 rows; d = 896, groups of 128, T = 607, 35.6 -> 33.5.
+// Of 411 launches of dX beside token contractions 1.018 and 1.041.
+// Whole -> split, us per call:
 //                                     T = 17          T = 128         T = 500
 //   7B block 4-bit, forward           124 ->  56      131 ->  71      whole
 //                   backward          392 -> 108      397 -> 140      480 -> 367
@@ -228,10 +251,8 @@ static size_t cut_jobs(int n, SplitJob *jobs, int longest, int d)
 //
 // Tiles of fewer rows where those of gemm_row_tiles leave the machine idle: a step of 64 rows is shorter by a third and more, and
 // there are up to twice as many.  96 and 112 rows are weighed too: 11008 x 4096 in groups of 64, T = 500, has 172 tiles of 128 rows
-// for 256 units and 215 of 112, training step 184 -> 180 us.
-// Of whole tiles of fewer rows, which cost nothing beside, the least estimate is taken if it is 5 % below; where pieces meet their 13 %
-// too, the lesser of the two estimates: 16000 x 11264 3-bit, T = 131, forward 78 us in 189 whole tiles of 64 rows, 69 in 252 halves
-// of 96; dX of 11008 x 4096, T = 922, see bwd_dx_chains.
+// for 256 units and 215 of 112, training step 184 -> 180 us; and 16000 x 11264 3-bit, T = 131, forward 78 us in 189 whole tiles of
+// 64 rows, 69 in 252 halves of 96.
 int gemm_plan(int n, SplitJob *jobs, int T, bool grouped, bool single, bool dds, double other_us, size_t max_bytes, int cus)
 {
     const int by_rows = gemm_row_tiles(T);
@@ -246,6 +267,7 @@ int gemm_plan(int n, SplitJob *jobs, int T, bool grouped, bool single, bool dds,
         int rt, d;
     };
     Form plain{0.0, by_rows, 1}, whole{HUGE_VAL, by_rows, 1}, cut{HUGE_VAL, by_rows, 1};
+    int rounds = 1;                                            // of the plain launch
     const int forms[4] = {by_rows, 4, 6, 7};
     for (int form = 0; form < (by_rows > 4 && !dds ? 4 : 1); ++form) {
         const int rt = forms[form], tiles_t = gemm_tiles_t(T, rt);
@@ -256,15 +278,16 @@ int gemm_plan(int n, SplitJob *jobs, int T, bool grouped, bool single, bool dds,
             if (d > 1 && bytes > max_bytes) continue;
             int wgs = 0;
             for (int j = 0; j < n; ++j) wgs += jobs[j].tiles_c * tiles_t * jobs[j].split;
-            if (form && wgs > 2 * cus) break;                          // not idle any more: fewer rows are the slower ones
+            if (form == 0 && d == 1) rounds = (wgs + 2 * cus - 1) / (2 * cus);
+            if (form && wgs > 3 * cus) break;                          // not idle any more: fewer rows are the slower ones
             const double us = gemm_form_us(n, jobs, T, rt, grouped, single, other_us, cus);
             Form &least = d > 1 ? cut : form ? whole : plain;
             if (us < least.us || (d == 1 && form == 0)) least = Form{us, rt, d};
         }
     }
     Form best = plain;
-    if (whole.us < 0.87 / 0.92 * plain.us) best = whole;
-    if (cut.us < 0.87 * plain.us && cut.us < best.us) best = cut;
+    if (whole.us < 0.95 * plain.us) best = whole;
+    if (cut.us < (rounds == 1 ? 0.95 : 0.83) * plain.us && cut.us < best.us) best = cut;
     (void)cut_jobs(n, jobs, longest, best.d);
     return best.rt;
 }
@@ -359,9 +382,9 @@ bool bwd_one_launch(long long tiles, int cus)
 
 // Whole contractions on no more than half of the units: their workgroups share with token tiles for as long as there are any and run
 // on alone, where a launch of their own has twice as many workgroups, in pieces or of 64 rows.  Backward in groups of 128, us, one
-// launch for both against one each: 15872 x 3840, T = 922, 299 against 240; 11008 x 4096, T = 922, 210 / 180; 7424 x 7168, T = 300,
-// 131 / 97; 4096 x 4096, T = 900, 88 / 79.  Short ones gain by the launches saved: 2048 x 2048, T = 1800, 47 / 64.  More tiles, or
-// pieces: 5120 x 5120, T = 1000, 114 / 136; 15872 x 3840, T = 250 (5 pieces), 81 / 94.
+// launch for both against one each: 11008 x 4096, T = 922, 203 against 175; 10880 x 2304, T = 1667, 209 / 185; 6144 x 6144, T = 500,
+// 112 / 98; 4096 x 4096, T = 900, 83 / 77; even at 3072 x 4096, T = 900, 67 / 66.  Short ones gain by the launches saved: 2048 x 2048,
+// T = 1800, 46 / 56.  More tiles, or pieces: 5120 x 5120, T = 1000, 109 / 122; 15872 x 3840, T = 922 (2 pieces), 219 / 229.
 bool bwd_dx_chains(int n, const SplitJob *jobs, int T, int cus)
 {
     const int tiles_t = gemm_tiles_t(T, gemm_row_tiles(T));

@@ -221,8 +221,10 @@ struct GemmDwArgs {
 };
 static_assert(sizeof(GemmDwArgs) <= 4096, "kernel argument block");
 hipError_t launch_gemm_dw(int bits, GemmDwArgs &m, hipStream_t stream);
-// us that a tile of the token contraction takes with another beside it
-inline double dw_tile_us(int T) { return 0.66 * ((T + 63) / 64 * 2) + 8.0; }
+// us that a tile of the token contraction takes beside another or a dX tile, in launches that do not fill the machine for long
+inline double dw_tile_us(int T) { return 0.55 * ((T + 63) / 64 * 2) + 8.0; }
+// and with none
+inline double dw_tile_alone_us(int T) { return 0.25 * ((T + 63) / 64 * 2) + 8.0; }
 // its chunk sums pc [N, K / 64] -> d_ds [N, K / gsz]
 inline SumJob chunk_sums(const float *pc, float *d_ds, int N, int K, int gsz)
 {

@@ -58,14 +58,14 @@ def _forms(planner, jobs, T, grouped, single, other):
                 break
             target = (longest + d - 1) // d
             splits = [min((kc + target - 1) // target, max(1, kc // 512)) for _, kc, _ in jobs]
-            if rt != by_rows and sum((c + 255) // 256 * tiles_t * s for (c, _, _), s in zip(jobs, splits)) > 2 * CUS:
+            if rt != by_rows and sum((c + 255) // 256 * tiles_t * s for (c, _, _), s in zip(jobs, splits)) > 3 * CUS:
                 break
             yield d == 1, rt, splits, planner.us(jobs, splits, T, rt, grouped, single, other)
 
 
 def test_no_form_over_one_with_a_lesser_estimate(planner):
-    """Of the forms that meet their bound (pieces 13 % below the whole contraction in its own rows, whole tiles of fewer rows
-    5 %), the one with the least estimate, in whatever order they are looked at."""
+    """Of the forms that meet their bound (5 % below the whole contractions in their own rows; 17 % for pieces where those are more
+    than a round of workgroups), the one with the least estimate, in whatever order they are looked at."""
     rng = random.Random(7)
     shapes = [([(13184, 1536)], 571, False, True), ([(3456, 4096)], 1169, False, True), ([(14336, 512)], 530, False, True),
               ([(384, 384)] * 4 + [(1024, 384)] * 2 + [(384, 1024)], 1092, False, False)]
@@ -82,8 +82,9 @@ def test_no_form_over_one_with_a_lesser_estimate(planner):
         jobs, other = _forward(layers, T), 0.0 if single else rng.choice([0.0, 500.0, 20000.0])
         forms = list(_forms(planner, jobs, T, grouped, single, other))
         unsplit = forms[0][3]
-        rows = [f for f in forms[1:] if f[0] and f[3] < 0.87 / 0.92 * unsplit]
-        pieces = [f for f in forms[1:] if not f[0] and f[3] < 0.87 * unsplit]
+        round_1 = sum((c + 255) // 256 * ((T + 16 * forms[0][1] - 1) // (16 * forms[0][1])) for c, _, _ in jobs) <= 2 * CUS
+        rows = [f for f in forms[1:] if f[0] and f[3] < 0.95 * unsplit]
+        pieces = [f for f in forms[1:] if not f[0] and f[3] < (0.95 if round_1 else 0.83) * unsplit]
         want = min(rows + pieces, key=lambda f: f[3], default=forms[0])
         rt, splits = planner.plan(jobs, T, grouped, single, other=other)
         got = planner.us(jobs, splits, T, rt, grouped, single, other)
@@ -91,3 +92,35 @@ def test_no_form_over_one_with_a_lesser_estimate(planner):
         assert any((rt, splits) == (f[1], f[2]) for f in rows + pieces + forms[:1]), (layers, T, grouped, rt, splits)
         taken["plain" if (rt, splits) == (forms[0][1], forms[0][2]) else "rows" if max(splits) == 1 else "pieces"] += 1
     assert min(taken.values()) > 50, taken
+
+
+def _block(d, f):
+    return [(d, d)] * 4 + [(f, d)] * 2 + [(d, f)]
+
+
+# layers, T, group-wise, us of token tiles beside, measured: {(row tiles per tile, pieces of the longest contraction): us per call}
+MEASURED = [
+    (_block(3072, 7936), 458, False, 0, {(8, 1): 114.1, (8, 2): 117.8, (4, 1): 107.8, (4, 2): 110.7, (6, 1): 101.4, (6, 2): 106.2,
+                                         (7, 1): 111.3, (7, 2): 116.3}),
+    (_block(896, 2816), 607, True, 0, {(8, 1): 51.9, (8, 2): 35.6, (8, 4): 34.4, (8, 5): 33.2, (4, 1): 41.9, (4, 2): 31.0,
+                                       (4, 3): 29.7, (4, 4): 37.8, (6, 2): 34.7, (6, 3): 33.4, (6, 4): 33.4, (7, 3): 34.8}),
+    (_block(384, 1024), 1092, False, 0, {(8, 1): 26.9, (8, 2): 24.8, (7, 1): 25.3, (7, 2): 23.4, (6, 1): 23.2, (6, 2): 22.8, (4, 1): 20.0,
+                                           (4, 2): 21.6}),
+    (_block(1920, 6656), 566, False, 0, {(8, 1): 94.2, (8, 2): 74.5, (8, 3): 85.8, (4, 1): 70.1, (4, 3): 68.9, (6, 1): 80.6,
+                                         (6, 2): 73.3, (6, 3): 73.2, (7, 2): 79.7}),
+    # dX beside token contractions: 11008 x 4096, T = 500 (groups of 64) and 922 (128)
+    ([(4096, 11008)], 500, True, 32 * 43 * 16.8, {(8, 1): 186.4, (8, 2): 114.7, (8, 3): 102.6, (8, 4): 106.4, (4, 1): 151.7, (4, 2): 112.2}),
+    ([(4096, 11008)], 922, True, 32 * 43 * 24.5, {(8, 1): 203.3, (8, 2): 166.3, (8, 3): 171.5, (8, 4): 174.3, (6, 2): 170.9, (7, 2): 169.6}),
+]
+
+
+@pytest.mark.parametrize("layers,T,grouped,other,measured", MEASURED)
+def test_forms_that_were_measured(planner, layers, T, grouped, other, measured):
+    """Launches in which the longest workgroup shares its unit for part of its time only, in which one workgroup more than there
+    are places starts a second round, or which token tiles fill: the plan is within an
+    eighth of the best form measured."""
+    jobs = _forward(layers, T)
+    rt, splits = planner.plan(jobs, T, grouped, False, other=float(other))
+    longest = max(range(len(jobs)), key=lambda j: jobs[j][1])
+    assert (rt, splits[longest]) in measured, (rt, splits)
+    assert measured[rt, splits[longest]] <= 1.125 * min(measured.values()), (rt, splits)
