@@ -58,7 +58,10 @@ struct BlockSpace {
     size_t min_total;
     int split_y[PEQA_MAX_BLOCK], split_dx[PEQA_MAX_BLOCK], split_dds[PEQA_MAX_BLOCK];
     int rt_y[2], rt_dx[2];           // row tiles per tile of the launches of per-channel and of group-wise items
-    bool one_launch;                 // group-wise items: dX and token contractions in one launch (launch_gemm_dw)
+    // Group-wise items: dX and token contractions in one launch (launch_gemm_dw), as split_dx and rt_dx[1] have it; the dX launch of
+    // a call without that one (too many tiles, or no scale gradient asked for) has a plan of its own.
+    bool one_launch;
+    int split_dx_alone[PEQA_MAX_BLOCK], rt_dx_alone;
     size_t acc[PEQA_MAX_BLOCK], acc_dds[PEQA_MAX_BLOCK];
 };
 
@@ -89,7 +92,7 @@ BlockSpace carve_block(int32_t n, const peqa_block_item *items, int32_t T, int32
     w.total = w.min_total = off ? off : 256;
     // splits, planned per launch: the per-channel items' forward, scale-gradient and dX launches, the group-wise items'
     // forward and dX launches (as if every gradient of every item were asked for)
-    for (int j = 0; j < n; ++j) w.split_y[j] = w.split_dx[j] = w.split_dds[j] = 1;
+    for (int j = 0; j < n; ++j) w.split_y[j] = w.split_dx[j] = w.split_dds[j] = w.split_dx_alone[j] = 1;
     auto plan = [&](bool gw, int mode, int *split) {
         peqa::SplitJob job[PEQA_MAX_BLOCK];
         int of[PEQA_MAX_BLOCK], m = 0;
@@ -102,23 +105,25 @@ BlockSpace carve_block(int32_t n, const peqa_block_item *items, int32_t T, int32
             job[m++] = peqa::SplitJob{(C + 255) / 256, KC, out_bytes, 1};
         }
         if (m == 0) return peqa::gemm_row_tiles(T);
-        double beside = 0.0;                                   // the token contractions in the launch of the group-wise dX
-        if (gw && mode == peqa::MODE_DX) {
-            long long dx_tiles = 0, dw_tiles = 0;
-            for (int i = 0; i < m; ++i) {
-                const peqa_layout *L = &items[of[i]].layout;
-                dx_tiles += (long long)tiles_t * job[i].tiles_c;
-                dw_tiles += (long long)(L->k_in / 128) * ((L->n_out + 255) / 256);
-            }
-            w.one_launch = peqa::bwd_one_launch(dx_tiles + dw_tiles, cus);
-            if (w.one_launch) beside = dw_tiles * peqa::dw_tile_us(T);
+        auto take = [&](double beside, int *to) {
+            const int rt = peqa::gemm_plan(m, job, T, gw, false, mode == peqa::MODE_DDS, beside, ~(size_t)0, cus);
+            for (int i = 0; i < m; ++i) to[of[i]] = job[i].split;
+            return rt;
+        };
+        if (!gw || mode != peqa::MODE_DX) return take(0.0, split);
+        long long dx_tiles = 0, dw_tiles = 0;                  // of dX, and of the token contractions beside it
+        for (int i = 0; i < m; ++i) {
+            const peqa_layout *L = &items[of[i]].layout;
+            dx_tiles += (long long)tiles_t * job[i].tiles_c;
+            dw_tiles += (long long)(L->k_in / 128) * ((L->n_out + 255) / 256);
         }
-        int rt = peqa::gemm_plan(m, job, T, gw, false, mode == peqa::MODE_DDS, beside, ~(size_t)0, cus);
-        if (beside > 0.0 && peqa::bwd_dx_chains(m, job, T, cus)) {
-            w.one_launch = false;
-            rt = peqa::gemm_plan(m, job, T, gw, false, false, 0.0, ~(size_t)0, cus);
+        w.rt_dx_alone = take(0.0, w.split_dx_alone);
+        w.one_launch = peqa::bwd_one_launch(dx_tiles + dw_tiles, cus);
+        int rt = w.rt_dx_alone;
+        if (w.one_launch) {
+            rt = take(dw_tiles * peqa::dw_tile_us(T), split);
+            w.one_launch = !peqa::bwd_dx_chains(m, job, T, cus);
         }
-        for (int i = 0; i < m; ++i) split[of[i]] = job[i].split;
         return rt;
     };
     if (op == PEQA_OP_FWD) {
@@ -133,7 +138,8 @@ BlockSpace carve_block(int32_t n, const peqa_block_item *items, int32_t T, int32
         const size_t N = (size_t)items[j].layout.n_out, K = (size_t)items[j].layout.k_in;
         w.acc[j] = w.total;
         if (w.split_y[j] > 1) w.total += round256((size_t)w.split_y[j] * T * N * sizeof(float));
-        if (w.split_dx[j] > 1) w.total += round256((size_t)w.split_dx[j] * T * K * sizeof(float));
+        const int dx = w.split_dx[j] > w.split_dx_alone[j] ? w.split_dx[j] : w.split_dx_alone[j];
+        if (dx > 1) w.total += round256((size_t)dx * T * K * sizeof(float));
         w.acc_dds[j] = w.total;
         if (w.split_dds[j] > 1) w.total += round256((size_t)w.split_dds[j] * tiles_t * N * sizeof(float));
     }
@@ -151,7 +157,7 @@ peqa_status plan_block(BlockSpace &w, int32_t n, const peqa_block_item *items, i
     const int cus = peqa::compute_units();
     if (cus != peqa::PLAN_UNITS) w = carve_block(n, items, T, op, cus);      // (min_total does not hang on the units)
     if (bytes < w.total)
-        for (int j = 0; j < n; ++j) w.split_y[j] = w.split_dx[j] = w.split_dds[j] = 1;
+        for (int j = 0; j < n; ++j) w.split_y[j] = w.split_dx[j] = w.split_dds[j] = w.split_dx_alone[j] = 1;
     return PEQA_OK;
 }
 
@@ -437,9 +443,17 @@ peqa_status peqa_block_bwd(int32_t n, const peqa_block_item *items, int32_t T, v
         if (st != PEQA_OK) return st;
     }
 
-    // ---- group-wise items.  Their (s, b) tables in one launch; every dX contraction in one launch, whose auxiliary
-    // workgroups write the transposed copies of X (once per distinct input) and dY that the scale gradients read;
-    // the token contractions of all scale gradients in one launch; the sums of their chunks in one launch.
+    // ---- group-wise items.  Few tiles and both gradients: the (s, b) tables and the transposed copies of X (once per distinct
+    // input) and dY in one launch, dX and the token contractions of the scale gradients in the next, pieces and chunks added up in
+    // the last.  Otherwise the tables in one launch; every dX contraction in one launch, whose auxiliary workgroups write the copies;
+    // the token contractions in one launch; the sums of their chunks in one launch.
+    bool want_dx = false, want_dds = false;
+    for (int j = 0; j < n; ++j)
+        if (grouped(&items[j].layout)) {
+            want_dx = want_dx || items[j].dX;
+            want_dds = want_dds || items[j].d_ds;
+        }
+    const bool one_launch = want_dx && want_dds && w.one_launch;
     peqa::MultiArgs mg{};
     peqa::DwMultiArgs dw{};
     const uint16_t *xt_of[PEQA_MAX_BLOCK] = {nullptr};
@@ -453,10 +467,12 @@ peqa_status peqa_block_bwd(int32_t n, const peqa_block_item *items, int32_t T, v
             job.mode = peqa::MODE_DX;
             peqa::GemmArgs &a = job.a;
             a.packed = it.packed; a.A = it.dY; a.T = T; a.KC = N; a.C = K; a.K = K;
-            a.rt = w.rt_dx[1]; a.tiles_c = (K + 255) / 256; a.tiles_t = peqa::gemm_tiles_t(T, a.rt);
+            a.rt = one_launch ? w.rt_dx[1] : w.rt_dx_alone;
+            a.tiles_c = (K + 255) / 256; a.tiles_t = peqa::gemm_tiles_t(T, a.rt);
             a.N = N; a.gsz = it.layout.group_size; a.G = G;
             a.sb = reinterpret_cast<const float *>(ws + w.table[j]); a.out = it.dX;
-            a.split = w.split_dx[j]; a.acc_part = reinterpret_cast<float *>(ws + w.acc[j]);
+            a.split = one_launch ? w.split_dx[j] : w.split_dx_alone[j];
+            a.acc_part = reinterpret_cast<float *>(ws + w.acc[j]);
         }
         if (it.d_ds) {
             if (!xt_of[xi[j]]) {
@@ -480,8 +496,7 @@ peqa_status peqa_block_bwd(int32_t n, const peqa_block_item *items, int32_t T, v
             dw.d_ds[dw.n_jobs++] = it.d_ds;
         }
     }
-    if (mg.n_jobs > 0 && dw.n_jobs > 0 && w.one_launch) {
-        // few tiles: tables and copies first, then both kinds of contraction, then what they leave in parts
+    if (one_launch) {
         peqa::GroupPrep p{};
         for (int j = 0; j < n; ++j) {
             const peqa_block_item &it = items[j];

@@ -301,3 +301,39 @@ def test_token_contraction_of_very_many_channels(gpu):
     want = -z0.double() * torch.stack([(dY.double() * sums[:, i:i + 1]).sum(0) for i in range(2)], 1)
     assert ((d_ds.double() - want).norm() / want.norm()).item() <= 1e-5
     assert ((d_ds.double() - want).abs().max() / want.pow(2).mean().sqrt()).item() <= 1e-4
+
+
+@pytest.mark.parametrize("group,bits", [(128, 4), (256, 3)])
+def test_block_dx_alone(gpu, oracle, group, bits):
+    """A block backward that asks for dX only: pieces as a launch by itself has them, in the workspace asked for, and whole in the
+    smallest; rows of dX against the oracle; with the scale gradient beside it the same up to the order of additions."""
+    import torch
+    from paper_2305_14152_amd import peqa
+    N, K, T = 3072, 6912, 260
+    print("dX alone, block, g=%d bits=%d" % (group, bits), flush=True)
+    seed = 76000 + group
+    W = synth.normal_f32(seed, (N, K), 0.02)
+    X, dY = synth.normal_bf16(seed + 1, (T, K), 1.0), synth.normal_bf16(seed + 2, (T, N), 1.0)
+    layer = gpu.GpuLayer(W, bits, group)
+    codes, s0, z0 = oracle.quantize(W, bits, group)
+    rows = [0, 1, 95, 96, 127, 128, 255, 259]
+    dXref = oracle.bwd(codes, s0, None, z0, X[rows], dY[rows], group)[0]
+    d = dict(L=layer.L, packed=layer.packed, s0=layer.s0, z0=layer.z0, X=gpu.to_dev(X), dY=gpu.to_dev(dY),
+             dX=torch.zeros((T, K), dtype=torch.int16, device="cuda"))
+    both = dict(d, dX=torch.zeros_like(d["dX"]), d_ds=torch.zeros_like(layer.s0))
+    alone, pair = peqa.block_items([d]), peqa.block_items([both])
+    nb = peqa.block_workspace_bytes(alone, T, peqa.PEQA_OP_BWD)
+    least = _whole_bytes(peqa, lambda: peqa.block_workspace_bytes(alone, T, peqa.PEQA_OP_BWD))
+    assert nb == peqa.block_workspace_bytes(pair, T, peqa.PEQA_OP_BWD) and nb - least >= 3 * 4 * T * K
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    peqa.block_bwd(pair, T, ws, nb)
+    together = gpu.bf16_dev_to_f64(both["dX"])
+    for size, sums in ((nb, 1), (least, 0)):
+        d["dX"].zero_()
+        peqa.trace_begin(16)
+        peqa.block_bwd(alone, T, ws, size)
+        launches = {k: v[0] for k, v in peqa.trace_end().items()}
+        assert launches["gemm_multi_dx"] == 1 and launches.get("gemm_finish", 0) == sums, launches
+        got = gpu.bf16_dev_to_f64(d["dX"])
+        assert np.abs(got[rows] - dXref).max() <= Y_TOL * np.abs(dXref).max()
+        assert np.abs(got - together).max() <= 2.0 ** -7 * np.abs(together).max()

@@ -124,3 +124,23 @@ def test_forms_that_were_measured(planner, layers, T, grouped, other, measured):
     longest = max(range(len(jobs)), key=lambda j: jobs[j][1])
     assert (rt, splits[longest]) in measured, (rt, splits)
     assert measured[rt, splits[longest]] <= 1.125 * min(measured.values()), (rt, splits)
+
+
+def test_block_workspace_holds_the_plan_of_dx_alone(planner):
+    """A group-wise block backward that asks for dX only launches dX by itself, in the pieces of such a launch, not in those (fewer)
+    that it takes beside the token contractions: the workspace holds either."""
+    from paper_2305_14152_amd import peqa
+    N, K, T = 3072, 6912, 260
+    jobs = [(K, N, 4 * T * K)]
+    alone = planner.plan(jobs, T, True, False)[1]
+    beside = planner.plan(jobs, T, True, False, other=(K // 128) * (N // 256) * (0.55 * 10 + 8))[1]
+    assert beside < alone
+    L = peqa.layout(N, K, 4, 128)
+    items = peqa.block_items([dict(L=L, packed=16, s0=16, z0=16, dY=16, dX=16)])
+    need = peqa.block_workspace_bytes(items, T, peqa.PEQA_OP_BWD)
+    peqa.set_option(peqa.PEQA_OPT_GEMM_WAVES, 4)                   # forced forms are whole contractions
+    try:
+        whole = peqa.block_workspace_bytes(items, T, peqa.PEQA_OP_BWD)
+    finally:
+        peqa.set_option(peqa.PEQA_OPT_GEMM_WAVES, 0)
+    assert need - whole >= alone[0] * 4 * T * K
