@@ -234,6 +234,51 @@ def test_small_batch_form_of_128_channels(gpu, oracle, bits, group):
             assert np.abs(gpu.bf16_dev_to_f64(d["Y"]) - Yref).max() <= Y_TOL * np.abs(Yref).max()
 
 
+@pytest.mark.parametrize("bits,group", [(4, 0), (3, 0), (4, 64), (3, 128)])
+def test_small_batch_form_of_32_channels(gpu, oracle, bits, group):
+    """T <= 8, short layers of few tiles: 32 channels per workgroup of 8 waves (K <= 4544) or 16, rings that are refilled and uneven
+    numbers of rounds per wave; one layer, and several of which some leave most waves without a round.  The result is rounded to
+    bf16 (half of 2^-8 of it); before that its fp32 sums are off by a few 2^-24 of a sum of up to 24-fold magnitudes."""
+    import torch
+    from paper_2305_14152_amd import peqa
+    shapes = [(384, 2176), (256, 4480), (128, 4608), (384, 6016), (128, 128)]
+    seed = 77000 + bits * 1000 + group
+    layers = []
+    for j, (N, K) in enumerate(shapes):
+        W = synth.normal_f32(seed + 10 * j, (N, K), 0.02)
+        codes, s0, z0 = oracle.quantize(W, bits, group)
+        layers.append((gpu.GpuLayer(W, bits, group), codes, s0, z0, synth.normal_f32(seed + 10 * j + 1, s0.shape, 1e-3)))
+
+    def near(got, ref):
+        assert (np.abs(gpu.bf16_dev_to_f64(got) - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-4 * np.abs(ref).max()).all()
+
+    for T in (1, 5, 8, 9):
+        print("32 channels bits=%d g=%d T=%d" % (bits, group, T), flush=True)
+        h = 0 if T <= 8 else 1
+        dicts, refs = [], []
+        for j, ((N, K), (layer, codes, s0, z0, ds)) in enumerate(zip(shapes, layers)):
+            assert _small_batch_form(peqa, [(N, K)], bits, group, T) == (h, 16 if h == 0 and K >= 4608 else 8, [1])
+            X = synth.normal_bf16(seed + 100 + 20 * j + T, (T, K), 1.0)
+            refs.append(oracle.fwd(codes, s0, ds, z0, X, group))
+            near(layer.fwd(X, ds), refs[-1])
+            dicts.append(dict(L=layer.L, packed=layer.packed, s0=layer.s0, z0=layer.z0, ds=gpu.to_dev(ds), X=gpu.to_dev(X),
+                              Y=torch.zeros((T, N), dtype=torch.int16, device="cuda")))
+        for some in ([0, 1, 4], [0, 1, 2, 3, 4]):                      # the longest has 70 rounds (8 waves), or 94 (16)
+            part = [shapes[i] for i in some]
+            assert _small_batch_form(peqa, part, bits, group, T) == (h, 16 if h == 0 and 3 in some else 8, [1] * len(some))
+            items = peqa.block_items([dicts[i] for i in some])
+            nb = peqa.block_workspace_bytes(items, T, peqa.PEQA_OP_FWD)
+            ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+            for i in some:
+                dicts[i]["Y"].zero_()
+            peqa.block_fwd(items, T, ws, nb)
+            torch.cuda.synchronize()
+            for i in some:
+                near(dicts[i]["Y"], refs[i])
+    # a longer layer is sliced instead
+    assert _small_batch_form(peqa, [(384, 6144)], bits, group, 8)[0] == 1
+
+
 @pytest.mark.parametrize("bits,N,K,T", [(4, 128, 512, 33), (4, 384, 512, 65), (3, 256, 640, 300), (3, 128, 8192, 40)])
 def test_zero_point_gradient_beside_the_others(gpu, oracle, bits, N, K, T):
     """One slice of token rows, two, a ragged last one, a split scale gradient: d_ds and d_dz, whose sums share a launch,
