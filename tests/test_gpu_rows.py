@@ -81,16 +81,24 @@ def test_rows_of_a_tile_split_and_paired(gpu, oracle, bits, T):
         gpu.assert_scale_grad_close(gpu.to_host(g), gref)
 
 
-@pytest.mark.parametrize("N,T", [(14336, 530), (16384, 400)])
-@pytest.mark.parametrize("group", [0, 128])
-def test_fewer_rows_where_idle(gpu, N, T, group):
-    """Whole contractions that take tiles of 96 or 112 rows for their number: the bits of 128-row tiles, whose form is asked for."""
+@pytest.mark.parametrize("N,K,T,group,rows", [
+    (14336, 512, 530, 0, 4), (14336, 512, 530, 128, 6), (16384, 512, 400, 0, 4), (16384, 512, 400, 128, 7),
+    (2304, 512, 256, 0, 4), (13184, 512, 640, 0, 6), (17152, 896, 490, 0, 7), (2304, 512, 256, 128, 4), (16640, 512, 1024, 128, 6),
+    (11008, 2048, 490, 64, 7),
+])
+def test_fewer_rows_where_idle(gpu, oracle, N, K, T, group, rows):
+    """Whole contractions planned in tiles of 64, 96 and 112 rows, all but one where gemm_row_tiles gives more (112 at T = 530 and
+    400, else 128): the bits of that height's tiles, which a form that is asked for has, and rows of Y against the oracle."""
     from paper_2305_14152_amd import peqa
-    print("fewer rows, N=%d T=%d group=%d" % (N, T, group), flush=True)
-    K, seed = 512, 83000 + N + T + group
-    layer = gpu.GpuLayer(synth.normal_f32(seed, (N, K), 0.02), 4, group)
+    from test_plan_host import Planner
+    print("fewer rows, N=%d K=%d T=%d group=%d" % (N, K, T, group), flush=True)
+    assert Planner(peqa.lib()).plan([(N, K, 4 * T * N)], T, group > 0, True, most=peqa.STATIC_SCRATCH_BYTES) == (rows, [1])
+    seed = 83000 + N + T + group
+    W = synth.normal_f32(seed, (N, K), 0.02)
+    layer = gpu.GpuLayer(W, 4, group)
     X = synth.normal_bf16(seed + 1, (T, K), 1.0)
-    Y, forms = gpu.to_host(layer.fwd(X)), []
+    Ydev, forms = layer.fwd(X), []
+    Y = gpu.to_host(Ydev)
     for waves in (4, 8):
         peqa.set_option(peqa.PEQA_OPT_GEMM_WAVES, waves)
         try:
@@ -98,6 +106,10 @@ def test_fewer_rows_where_idle(gpu, N, T, group):
         finally:
             peqa.set_option(peqa.PEQA_OPT_GEMM_WAVES, 0)
     assert np.abs(Y).max() > 0 and any((Y == f).all() for f in forms)
+    codes, s0, z0 = oracle.quantize(W, 4, group)
+    some = [0, 63, 64, 95, 96, 111, 112, 127, 128, T - 1]
+    Yref = oracle.fwd(codes, s0, None, z0, X[some], group)
+    assert np.abs(gpu.bf16_dev_to_f64(Ydev)[some] - Yref).max() <= Y_TOL * np.abs(Yref).max()
 
 
 @pytest.mark.parametrize("group", [64, 128, 256])
@@ -107,11 +119,18 @@ def test_few_long_chains_of_the_backward(gpu, N, K, T, group):
     contractions' launch: whole contractions, so the bits of a forced form; the block call agrees."""
     import torch
     from paper_2305_14152_amd import peqa
+    from test_plan_host import Planner
+    planner, beside = Planner(peqa.lib()), (K // 128) * ((N + 255) // 256) * (0.55 * ((T + 63) // 64 * 2) + 8)
+    jobs = [(K, N, 4 * T * K)]
+    assert planner.plan(jobs, T, True, False, other=beside)[1] == [1]
+    assert planner.chains(jobs, [1], T) == (N > 3072)
     print("chains, N=%d K=%d T=%d group=%d" % (N, K, T, group), flush=True)
     seed = 84000 + N + T + group
     layer = gpu.GpuLayer(synth.normal_f32(seed, (N, K), 0.02), 4, group)
     X, dY = synth.normal_bf16(seed + 1, (T, K), 1.0), synth.normal_bf16(seed + 2, (T, N), 1.0)
+    peqa.trace_begin(16)
     dX, g = (gpu.to_host(v) for v in layer.bwd(X, dY))
+    assert ("gemm_dx" in peqa.trace_end()) == (N > 3072)             # a launch of its own, or shared with the token contractions
     forms = []
     for waves in (4, 8):
         peqa.set_option(peqa.PEQA_OPT_GEMM_WAVES, waves)

@@ -20,6 +20,8 @@ class Planner:
         self.plan_fn.argtypes, self.plan_fn.restype = [i, p, i, b, b, b, d, z, i], i
         self.us_fn = lib._ZN4peqa12gemm_form_usEiPKNS_8SplitJobEiibbdi         # peqa::gemm_form_us
         self.us_fn.argtypes, self.us_fn.restype = [i, p, i, i, b, b, d, i], d
+        self.chains_fn = lib._ZN4peqa13bwd_dx_chainsEiPKNS_8SplitJobEii        # peqa::bwd_dx_chains
+        self.chains_fn.argtypes, self.chains_fn.restype = [i, p, i, i], b
         self.rows_fn = lib._ZN4peqa14gemm_row_tilesEi                          # peqa::gemm_row_tiles
 
     def rows(self, T):
@@ -32,6 +34,9 @@ class Planner:
 
     def us(self, jobs, splits, T, rt, grouped, single, other=0.0):
         return self.us_fn(len(jobs), self._jobs(jobs, splits), T, rt, grouped, single, other, CUS)
+
+    def chains(self, jobs, splits, T):
+        return self.chains_fn(len(jobs), self._jobs(jobs, splits), T, CUS)
 
     @staticmethod
     def _jobs(jobs, splits):
