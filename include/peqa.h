@@ -27,12 +27,13 @@
  * Options.  The library reads nothing from the process environment.  Three switches exist for tests and
  * comparisons, set explicitly with peqa_set_option (process-wide, not thread-safe; none is needed):
  * PEQA_OPT_GEMM_WAVES = 4 | 8 forces one of the two forms of the tiled contraction kernel (0, the default:
- * a launch with more than one 128 x 256 tile per compute unit runs four-wave workgroups, two per
- * compute unit, any other launch eight-wave ones); PEQA_OPT_BWD_PAIR = 0 makes a per-channel backward
- * that is asked for both gradients run its two contractions as launches of their own, 1 as one launch of
- * four-wave workgroups (-1, the default: one launch unless PEQA_OPT_GEMM_WAVES is 8);
- * PEQA_OPT_GROUPED_DDS = 1 selects the older of two routes to the scale gradient of group-wise
- * layers (0, the default: the contraction over tokens).  Results agree within rounding.
+ * a launch of one contraction with more tiles, or pieces of tiles, than compute units runs four-wave
+ * workgroups, two per compute unit, one with fewer eight-wave ones; a forced form is never cut into
+ * pieces); PEQA_OPT_BWD_PAIR = 0 makes a per-channel backward that is asked for both gradients run its two
+ * contractions as launches of their own, 1 as one launch of four-wave workgroups (-1, the default: one
+ * launch unless PEQA_OPT_GEMM_WAVES is 8); PEQA_OPT_GROUPED_DDS = 1 selects the older of two routes to the
+ * scale gradient of group-wise layers (0, the default: the contraction over tokens).  Results agree within
+ * rounding.
  *
  * Stacking.  The packed array is stored by rows of 128-channel tiles and the scale-shaped
  * arrays by channel, so layers with equal K, bits and group_size that read the same input
@@ -229,10 +230,13 @@ peqa_status peqa_linear_fwd_fused(int32_t n, const peqa_fwd_item *items, const u
  *     contractions in one launch whose grid also carries the scaling of dY for every item, then all dX
  *     contractions in one launch whose grid also carries the fixed-order sums of the scale-gradient partials.
  *     Group-wise layers: forward = the scale tables of all items in one launch, then all contractions in one
- *     launch.  Backward = the tables, then all dX contractions in one launch whose grid also writes the
- *     transposed copies of X (once per distinct X) and dY, then the token contractions of all scale
- *     gradients in one launch and the sums of their chunks in another.  (Always the token-contraction
- *     route: PEQA_OPT_GROUPED_DDS is not consulted.)
+ *     launch.  Backward of few tiles, both gradients = the tables and the transposed copies of X (once per distinct
+ *     X) and dY in one launch, then all dX contractions and the token contractions of all scale gradients in one
+ *     launch.  Of many tiles, or of one gradient = the tables, then all dX contractions in one launch whose grid
+ *     also writes the copies, then the token contractions in one launch.  (Always the token-contraction route:
+ *     PEQA_OPT_GROUPED_DDS = 1 only keeps the two in launches of their own.)
+ *     Contractions of few tokens are cut into pieces, whose sums, like those of the chunks of groups past 128
+ *     features, are added up by one launch more.
  *   row_sums (optional, [T, 2] fp32 per distinct X, caller-owned): when not NULL, peqa_block_fwd stores the row
  *     sums of the item's X there (see peqa_row_sums) and peqa_block_bwd reads them instead of taking them again;
  *     items that share X may share the array.  Ignored by T <= 16 and by group-wise layers.

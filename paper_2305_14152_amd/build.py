@@ -11,8 +11,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libpeqa_hip.so")
-SOURCES = ["peqa_api.hip", "peqa_quantize.hip", "peqa_small.hip", "peqa_gemm.hip", "peqa_gemm_r4.hip", "peqa_gemm_r6.hip", "peqa_gemm_r7.hip", "peqa_gemm_r8.hip", "peqa_gemv.hip", "peqa_dw.hip",
-           "peqa_block.hip"]
+SOURCES = ["peqa_api.hip", "peqa_quantize.hip", "peqa_small.hip", "peqa_gemm.hip", "peqa_gemm_r4.hip", "peqa_gemm_r6.hip",
+           "peqa_gemm_r7.hip", "peqa_gemm_r8.hip", "peqa_gemv.hip", "peqa_dw.hip", "peqa_block.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument", "-Rpass-analysis=kernel-resource-usage"]

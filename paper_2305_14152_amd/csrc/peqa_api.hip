@@ -619,7 +619,8 @@ static peqa_status bwd_impl(const peqa_layout *L, const uint32_t *packed, const 
         uint16_t *xt = reinterpret_cast<uint16_t *>(ws + w.xt), *dyt = reinterpret_cast<uint16_t *>(ws + w.dyt);
         // When dX is wanted too and its contraction runs two workgroups per compute unit, it goes first and spare
         // workgroups of its launch write the transposed copies that the token contraction needs.
-        const bool tp_in_dx = d_ds && by_tokens && dX && peqa::gemm_four_waves(peqa::gemm_tiles_t(T, w.rt_dx_alone) * ((K + 255) / 256) * w.split_dx_alone);
+        const bool tp_in_dx = d_ds && by_tokens && dX &&
+                              peqa::gemm_four_waves(peqa::gemm_tiles_t(T, w.rt_dx_alone) * ((K + 255) / 256) * w.split_dx_alone);
         float *sb = reinterpret_cast<float *>(ws + w.table), *pc = reinterpret_cast<float *>(ws + w.pc);
         auto dx_args = [&](int rt) {
             peqa::GemmArgs a{};

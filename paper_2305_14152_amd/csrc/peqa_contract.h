@@ -15,7 +15,6 @@ int halves_per_workgroup(int tiles, bool paired);
 
 namespace {
 
-
 template <int BITS, int MODE, bool GROUPED, int KW, int RT>
 __global__ __launch_bounds__(256 * KW, 3 - KW) void gemm_kernel(GemmArgs a)
 {
@@ -37,15 +36,15 @@ __global__ __launch_bounds__(256 * KW, 3 - KW) void gemm_kernel(GemmArgs a)
     gemm_tile<BITS, MODE, GROUPED, KW, RT>(a, (int)blockIdx.x, lds);
 }
 
+// Row tiles of a split scale gradient's tiles, which take their row sums themselves: as many token rows, or more.
+constexpr int piece_rows(int rt) { return rt == 4 ? 4 : 8; }
+
 // Both contractions of a per-channel backward in one launch of four-wave workgroups: the first n_first
 // workgroups are the tiles of one of them (the one with the longer contraction), the rest the tiles of the
 // other.  Neither reads what the other writes.  Two launches of at most one tile per compute unit each -- which
 // would run in the eight-wave form, ring fill and epilogue exposed, or leave most of the machine idle at small T --
 // become one launch with up to two workgroups per compute unit, and the last round of the first contraction is
 // filled with tiles of the second.
-// Row tiles of a split scale gradient's tiles, which take their row sums themselves: as many token rows, or more.
-constexpr int piece_rows(int rt) { return rt == 4 ? 4 : 8; }
-
 template <int BITS, int RT>
 __global__ __launch_bounds__(256, 2) void gemm_bwd_pair_kernel(GemmArgs a_dds, GemmArgs a_dx, int n_first, int dx_first)
 {
@@ -312,8 +311,10 @@ hipError_t GemmRows<RT>::multi(int bits, int gmode, int workgroups, const MultiA
     if (gmode < 0)
         return bits == 4 ? launch_multi<4, -1, RT>(grid, lds_bytes, m, stream) : launch_multi<3, -1, RT>(grid, lds_bytes, m, stream);
     if (gmode == MODE_Y)
-        return bits == 4 ? launch_multi<4, MODE_Y, RT>(grid, lds_bytes, m, stream) : launch_multi<3, MODE_Y, RT>(grid, lds_bytes, m, stream);
-    return bits == 4 ? launch_multi<4, MODE_DX, RT>(grid, lds_bytes, m, stream) : launch_multi<3, MODE_DX, RT>(grid, lds_bytes, m, stream);
+        return bits == 4 ? launch_multi<4, MODE_Y, RT>(grid, lds_bytes, m, stream)
+                         : launch_multi<3, MODE_Y, RT>(grid, lds_bytes, m, stream);
+    return bits == 4 ? launch_multi<4, MODE_DX, RT>(grid, lds_bytes, m, stream)
+                     : launch_multi<3, MODE_DX, RT>(grid, lds_bytes, m, stream);
 }
 
 }  // namespace peqa

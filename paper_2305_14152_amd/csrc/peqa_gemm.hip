@@ -5,8 +5,8 @@
 //                                                   (scale gradient, column-reduced epilogue)
 //   MODE_DX  : dX[t,k]   = sum_i (dY[t,i] s_i) (Q[i,k] - z_i)                (chain rule on Eq. 2)
 //
-// A workgroup owns a 128 (tokens) x 256 (output columns) tile (peqa_tile.h) as four waves of 128 x 64 side by side
-// along the columns: 8 x 4 MFMA 16x16x32 tiles, 128 fp32 AGPRs per wave.  Two forms:
+// A workgroup owns a tile of 64, 96, 112 or 128 tokens x 256 output columns (peqa_tile.h; gemm_plan takes the height) as four
+// waves side by side along the columns: of 128 x 64 in the tallest, 8 x 4 MFMA 16x16x32 tiles, 128 fp32 AGPRs per wave.  Two forms:
 //   KW = 1: four waves run the whole contraction range; two workgroups per compute unit, i.e. two waves per SIMD, so that
 //           the LDS reads, the unpacking and the scalar bookkeeping of one hide behind the matrix instructions of the
 //           other, and one workgroup's ring fill and epilogue behind the other's loop.
@@ -18,7 +18,7 @@
 //
 // Operand paths.  Both operands go global -> LDS by DMA (global_load_lds) into a ring of
 // stages, one 32-deep contraction step per stage: the activation operand (X, or the pre-scaled
-// dY) as 128 x 32 bf16 tiles (16-byte chunks XOR-swizzled by row), the weight operand as
+// dY) as bf16 tiles of the tile's rows x 32 (16-byte chunks XOR-swizzled by row), the weight operand as
 // the packed 8x8 code blocks themselves, half a block per lane.  Each lane reads its words back and
 // unpacks them in registers into bf16 (16 + Q) fragments (peqa_device.h): dequantised weights
 // never exist in memory.  The contraction therefore runs on exact small integers; the offset 16,
@@ -375,16 +375,20 @@ hipError_t launch_gemm_multi(int bits, bool grouped, MultiArgs &m, hipStream_t s
     return e;
 }
 
+// Eight tiles per unit: with more of them the launches are long enough for their starts and ends not to count.  (They still count
+// up to some 30 per unit: backward of blocks, us, one launch for dX and the token contractions against one each, 702 + 2079 tiles
+// 436 / 509, 595 + 5231 tiles 564 / 620, 1308 + 7961 tiles 1444 / 1501.)
 bool bwd_one_launch(long long tiles, int cus)
 {
     return options().gemm_waves == 0 && options().bwd_pair < 0 && options().grouped_dds == 0 && tiles <= 8ll * cus;
 }
 
-// Whole contractions on no more than half of the units: their workgroups share with token tiles for as long as there are any and run
-// on alone, where a launch of their own has twice as many workgroups, in pieces or of 64 rows.  Backward in groups of 128, us, one
-// launch for both against one each: 11008 x 4096, T = 922, 203 against 175; 10880 x 2304, T = 1667, 209 / 185; 6144 x 6144, T = 500,
-// 112 / 98; 4096 x 4096, T = 900, 83 / 77; even at 3072 x 4096, T = 900, 67 / 66.  Short ones gain by the launches saved: 2048 x 2048,
-// T = 1800, 46 / 56.  More tiles, or pieces: 5120 x 5120, T = 1000, 109 / 122; 15872 x 3840, T = 922 (2 pieces), 219 / 229.
+// dX that gemm_plan leaves whole beside the token contractions, of tiles (counted as of gemm_row_tiles rows, whatever it takes) on no
+// more than half of the units: workgroups that share with token tiles for as long as there are any and run on alone, where a launch
+// of their own has pieces or many more of 64 rows.  Backward, us, one launch for both against one each: 9216 x 8192 in groups of
+// 64, T = 400, 163 against 147; 8192 x 3072 in groups of 128, T = 1200, 144 / 129; even at 4096 x 4096, T = 900, 78 / 77.
+// Short ones gain by the launches saved: 3072 x 4096, T = 900, 62 / 66; 2048 x 2048, T = 1800, 46 / 56.  More tiles, or pieces:
+// 5120 x 5120, T = 1000, 109 / 122; 11008 x 4096, T = 922 (2 pieces), 166 / 175; 15872 x 3840, T = 922 (2), 219 / 229.
 bool bwd_dx_chains(int n, const SplitJob *jobs, int T, int cus)
 {
     const int tiles_t = gemm_tiles_t(T, gemm_row_tiles(T));

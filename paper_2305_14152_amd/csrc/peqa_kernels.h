@@ -26,7 +26,7 @@ struct GemmArgs {
     int C;                    // output columns:     N (MODE_Y/DDS) or K (MODE_DX)
     int K;                    // input features of the layer (fixes the block stride of `packed`)
     int tiles_c, tiles_t;     // ceil(C/256), ceil(T/(16 rt))
-    int rt;                   // row tiles (of 16 tokens) per tile: gemm_row_tiles(T), or 4 where gemm_plan asks for it
+    int rt;                   // row tiles (of 16 tokens) per tile: 4, 6, 7 or 8, gemm_row_tiles(T) or what gemm_plan took instead
     // set by the launches: token tiles per L2 patch (at most 4), reciprocals (div_magic) of the numbers of tiles and of tiles
     // in patch_t rows, 128-deep units of a piece (one more in the first unit_rem pieces)
     int patch_t;
@@ -101,7 +101,7 @@ struct FinishMulti {
     int n, n_sums;
 };
 hipError_t launch_split_finish(const FinishMulti &f, hipStream_t stream);
-// whether a per-channel launch of that many 128 x 256 tiles takes the four-wave form (two workgroups per compute unit);
+// whether a launch of one contraction of that many tiles, or pieces of tiles, takes the four-wave form (two workgroups per compute unit);
 // for a huge count: whether the four-wave form is allowed at all (the option gemm_waves = 8 forbids it)
 bool gemm_four_waves(int tiles);
 // Per-channel layers: the MODE_DDS and the MODE_DX contraction of one backward (arguments as for launch_gemm) as one
@@ -233,7 +233,7 @@ inline SumJob chunk_sums(const float *pc, float *d_ds, int N, int K, int gsz)
 // Whether a group-wise backward of both gradients goes that way: `tiles` of dX (of gemm_row_tiles rows) and of the token
 // contractions together.  Launches of many rounds keep the copies in spare workgroups of the dX launch.
 bool bwd_one_launch(long long tiles, int cus);
-// Whether its dX, as planned beside the token contractions, is a few long chains that a launch of its own would cut up.
+// Whether its dX, with the pieces planned beside the token contractions, is a few long chains that a launch of its own would cut up.
 bool bwd_dx_chains(int n, const SplitJob *jobs, int T, int cus);
 // The (s, b) tables of up to GT_MAX layers in one launch.
 constexpr int GT_MAX = 8;

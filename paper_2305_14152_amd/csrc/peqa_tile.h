@@ -18,10 +18,8 @@
 // fp16 codes for the scaling 1129 and 1259 us; 11008 x 4096, 4 bits, groups of 64, T = 500: forward 102 -> 72 -> 67 us;
 // per-channel training steps of the 7B and 65B blocks 2.1 and 2.9 % shorter.
 //
-// Launches that fill the chip for long run at the power limit: their time follows the energy of a step, not its cycles.  Loops of
-// the same mix on random data, two waves per SIMD, us per step: MFMAs alone 0.509, with the unpacking 0.540, with the LDS reads
-// 0.562, with the DMAs 0.548, with all three 0.627 (the kernels: 0.66).  MFMA 32x32x16 with lanes exchanged to its operand
-// order took 5 (per channel) and 11 % (group-wise) fewer cycles in the kernels, at a clock lower by as much: no faster.
+// Launches that fill the chip for long run below the nominal clock of 2.4 GHz, at 1.8 to 1.9 (GRBM_GUI_ACTIVE over their time): what
+// saves cycles there gains less than its share of them.
 #pragma once
 
 #include <type_traits>
@@ -395,15 +393,16 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
     // (Step 0 refills the packed-weight slot of stage 0, which its own wave alone reads and has read; its activation tiles go to
     // stage NSTAGE - 1.  No barrier is needed before it.)
 
-    // ---- main loop.  A step is a 32-deep contraction: 4 RT MFMAs, one per accumulator (the slots below: of 32).  When step `it` starts, its fragments
-    // and the packed weights of step it + 1 are in registers, and stages it + 1 and it + 2 are complete in LDS.  The MFMAs run
-    // back to back from the first instruction after the barrier; everything else sits in their shadow, in fixed slots:
+    // ---- main loop.  A step is a 32-deep contraction: M = 4 RT MFMAs, one per accumulator.  When step `it` starts, its
+    // fragments and the packed weights of step it + 1 are in registers, and stages it + 1 and it + 2 are complete in LDS.  The
+    // MFMAs run back to back from the first instruction after the barrier; everything else sits in their shadow, in fixed slots:
     //   after MFMA 2          LDS read of the packed weights of step it + 2
-    //   from MFMA 4 on        every other MFMA or so, one register of step it + 1's weight fragments (the table entries that
+    //   from MFMA M / 8 on    every other MFMA or so, one register of step it + 1's weight fragments (the table entries that
     //                         scale them are read at the top)
-    //   after MFMA 5, 13, 21  one DMA each: the two activation loads of step it + NSTAGE - 1 (into the stage of step it - 1)
-    //                         and the packed weights of step it + NSTAGE (into this step's own stage: read two steps ago, by
-    //                         this wave alone, and the operand that comes from HBM, so it gets the longer lead).  The tail
+    //   after MFMA M / 8 + 1, 3 M / 8 + 1, 5 M / 8 + 1
+    //                         one DMA each: the activation loads of step it + NSTAGE - 1 (into the stage of step it - 1; one of
+    //                         64 staged rows, two of 128) and the packed weights of step it + NSTAGE (into this step's own
+    //                         stage: read two steps ago, by this wave alone, and the operand that comes from HBM, so it gets the longer lead).  The tail
     //                         re-fetches the last step: harmless, and it keeps the DMA count per step constant so that a
     //                         fixed vmcnt tells when a stage has landed
     //   after each 4 MFMAs    the activation fragment just used up is refilled from LDS for step it + 1
