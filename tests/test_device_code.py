@@ -63,3 +63,25 @@ def test_spills_are_refused_in_every_kernel_that_counts():
     assert len(kernels) >= 20
     remark = "f.hip:1:1: remark: Function Name: %s [-R]\nf.hip:1:1: remark:     ScratchSize [bytes/lane]: 8 [-R]\n"
     assert [k for k in kernels if not build.check_no_scratch(remark % k)] == []
+
+
+def test_token_tiles_wait_for_what_they_use_only():
+    """The loop of the token contraction, in every kernel that has it: operands by global loads, and no wait that empties the
+    memory queue (which the compiler puts where it believes a FLAT operation is pending, and which drains the ring)."""
+    peqa.lib()
+    loops = {}
+    for text in build.device_listings(build.LIB):
+        for part in re.split(r"\n(?=[0-9a-f]+ <)", text):
+            name = re.match(r"[0-9a-f]+ <(.+)>:", part)
+            if not name or "dw_" not in name.group(1):
+                continue
+            code = [line.split("//")[0].strip() for line in part.splitlines()[1:]]
+            barriers = [i for i, op in enumerate(code) if op.startswith("s_barrier")]
+            for a, b in zip(barriers, barriers[1:]):
+                step = code[a:b]
+                if sum(op.startswith("v_mfma") for op in step) == 32 and sum("global_load_lds" in op for op in step) == 2 and \
+                        sum("s_waitcnt vmcnt(18)" in op for op in step) == 1:
+                    assert not [op for op in step if op.startswith("flat_") or "vmcnt(0)" in op], name.group(1)
+                    assert sum(op.startswith("global_load_dwordx4") for op in step) == 4
+                    loops[name.group(1)] = loops.get(name.group(1), 0) + 1
+    assert len(loops) == 12 and set(loops.values()) == {2}, loops   # alone and of several layers, beside dX of four heights; 3, 4 bits
