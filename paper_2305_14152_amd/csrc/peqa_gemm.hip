@@ -209,7 +209,7 @@ double gemm_form_us(int n, const SplitJob *jobs, int T, int rt, bool grouped, bo
         // T = 65, 80 us in 342 workgroups, 85 in 520.
         const double late = third ? c.shared * second + fixed + c.alone * third + fixed : 0.0;
         us = late > us ? late : us;
-        // a token tile by itself: 1664 x 384, T = 3147, training step 75 us with dX in 104 whole tiles of 64 rows, 79 in 200 halves
+        // a token tile by itself: 1664 x 384, T = 3147, backward 45 us with dX in 50 or 100 whole tiles, 48 in halves
         if (other_us > 0.0 && us < dw_tile_alone_us(T)) us = dw_tile_alone_us(T);
     }
     return bytes > 0 ? us + 4.0 + (double)bytes * 2.0 / 5e6 : us;
@@ -240,7 +240,7 @@ static size_t cut_jobs(int n, SplitJob *jobs, int longest, int d)
 // taken is 1.017 times the best in the geometric mean.  With the longest sharing for its mean-length neighbour or not at all, shared
 // steps as with every unit full, sums at 3.5 TB/s, 13 % throughout and no tiles of fewer rows past two per unit it was 1.032:
 // forward of d = 3072, T = 458, 118 us in 536 workgroups, now 106 in 670 of 96 rows; d = 896, groups of 128, T = 607, 35.6 -> 33.5.
-// Of 411 launches of dX beside token contractions 1.018 and 1.041.
+// Of 415 launches of dX beside token contractions 1.021 and 1.044.
 // Whole -> split, us per call:
 //                                     T = 17          T = 128         T = 500
 //   7B block 4-bit, forward           124 ->  56      131 ->  71      whole
@@ -376,8 +376,8 @@ hipError_t launch_gemm_multi(int bits, bool grouped, MultiArgs &m, hipStream_t s
 }
 
 // Eight tiles per unit: with more of them the launches are long enough for their starts and ends not to count.  (They still count
-// up to some 30 per unit: backward of blocks, us, one launch for dX and the token contractions against one each, 702 + 2079 tiles
-// 436 / 509, 595 + 5231 tiles 564 / 620, 1308 + 7961 tiles 1444 / 1501.)
+// wherever measured, up to 66 per unit: backward of blocks, us, one launch for dX and the token contractions against one each, 702 +
+// 2079 tiles 432 / 500, 595 + 5231 tiles 551 / 612, 1308 + 7961 tiles 1415 / 1466.  The bound has not been moved yet.)
 bool bwd_one_launch(long long tiles, int cus)
 {
     return options().gemm_waves == 0 && options().bwd_pair < 0 && options().grouped_dds == 0 && tiles <= 8ll * cus;
@@ -386,9 +386,9 @@ bool bwd_one_launch(long long tiles, int cus)
 // dX that gemm_plan leaves whole beside the token contractions, of tiles (counted as of gemm_row_tiles rows, whatever it takes) on no
 // more than half of the units: workgroups that share with token tiles for as long as there are any and run on alone, where a launch
 // of their own has pieces or many more of 64 rows.  Backward, us, one launch for both against one each: 9216 x 8192 in groups of
-// 64, T = 400, 163 against 147; 8192 x 3072 in groups of 128, T = 1200, 144 / 129; even at 4096 x 4096, T = 900, 78 / 77.
-// Short ones gain by the launches saved: 3072 x 4096, T = 900, 62 / 66; 2048 x 2048, T = 1800, 46 / 56.  More tiles, or pieces:
-// 5120 x 5120, T = 1000, 109 / 122; 11008 x 4096, T = 922 (2 pieces), 166 / 175; 15872 x 3840, T = 922 (2), 219 / 229.
+// 64, T = 400, 167 against 150; 8192 x 3072 in groups of 128, T = 1200, 149 / 132; even at 4096 x 4096, T = 900, 80 / 80.
+// Short ones gain by the launches saved: 3072 x 4096, T = 900, 63 / 69; 2048 x 2048, T = 1800, 44 / 56.  More tiles, or pieces:
+// 5120 x 5120, T = 1000, 113 / 126; 11008 x 4096, T = 922 (2 pieces), 169 / 180; 15872 x 3840, T = 922 (2), 226 / 236.
 bool bwd_dx_chains(int n, const SplitJob *jobs, int T, int cus)
 {
     const int tiles_t = gemm_tiles_t(T, gemm_row_tiles(T));
