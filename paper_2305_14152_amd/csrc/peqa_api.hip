@@ -7,6 +7,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <atomic>
 
 #include "peqa_host.h"
@@ -956,11 +957,19 @@ peqa_status gemv_forward(int n, const GemvItem *items, int32_t T, size_t most, f
     GemvArgs g{};
     int wgs = 0;
     size_t poff = 0;                                           // in floats
-    for (int j = 0; j < GEMV_MAX_LAYERS; ++j) {
-        if (j < n) {
+    // launches of many workgroups: the layers with the longest tiles first (see the kernel)
+    int order[GEMV_MAX_LAYERS];
+    for (int j = 0; j < n; ++j) order[j] = j;
+    auto rounds_of = [&](int j) { return (form.narrow >> j & 1u ? 2 : 1) * (items[j].L->k_in / S[j]); };
+    if (form.waves == 4) std::stable_sort(order, order + n, [&](int x, int y) { return rounds_of(x) > rounds_of(y); });
+    uint32_t narrow = 0;
+    for (int i = 0; i < GEMV_MAX_LAYERS; ++i) {
+        if (i < n) {
+            const int j = order[i];
+            narrow |= (form.narrow >> j & 1u) << i;
             const peqa_layout *L = items[j].L;
             if ((uint64_t)T * (uint64_t)L->n_out >= ((uint64_t)1 << 31)) return PEQA_ERR_SHAPE;   // 32-bit indexing in there
-            GemvLayer &l = g.layer[j];
+            GemvLayer &l = g.layer[i];
             l.packed = items[j].packed; l.s0 = items[j].s0; l.ds = items[j].ds; l.z0 = items[j].z0; l.dz = items[j].dz;
             l.X = items[j].X; l.Y = items[j].Y;
             l.N = L->n_out; l.K = L->k_in; l.G = groups(L);
@@ -968,12 +977,13 @@ peqa_status gemv_forward(int n, const GemvItem *items, int32_t T, size_t most, f
             l.S = S[j];
             l.partial = partial + poff;
             if (S[j] > 1) poff += (size_t)S[j] * (size_t)T * (size_t)L->n_out;
-            wgs += L->n_out / gemv_channels(form) * S[j];
+            wgs += L->n_out / (form.narrow >> j & 1u ? gemv_channels(form) / 2 : gemv_channels(form)) * S[j];
         } else {
-            g.layer[j] = g.layer[n - 1];                       // never selected: its wg_end is the total
+            g.layer[i] = g.layer[n - 1];                       // never selected: its wg_end is the total
         }
-        g.wg_end[j] = wgs;
+        g.wg_end[i] = wgs;
     }
+    form.narrow = narrow;
     g.n_layers = n;
     g.T = T;
     return dev_status(launch_gemv(items[0].L->bits, form, g, s));

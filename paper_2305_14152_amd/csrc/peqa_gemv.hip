@@ -73,49 +73,29 @@ __device__ __forceinline__ void gv_wait_vmcnt()
 // of few channels, which the unpacking bounds on the compute units that they reach.
 // ZBYTE: zero-points are the stored integers (no trained offset dz), kept as bytes in LDS.
 template <int BITS, int H, int WAVES, int NX, bool ZBYTE>
-__global__ __launch_bounds__(WAVES * 64, GV_SIMD_WAVES) void gemv_kernel(GemvArgs a)
+__device__ __forceinline__ void gemv_tile(const GemvArgs &a, const GemvLayer &L, const int bx, const int wg0, uint8_t *stage)
 {
-    // [wave][NBUF rounds][round], reused as [wave][column tile][row in lane][lane] fp32 (4 KB per wave) for the final sum;
-    // then the scale tile: scale s0 + ds and zero-point (16 + z0 + dz as fp32, or z0 as stored) of [group of the slice][channel]
-    // (rows padded: the transposing writes of consecutive groups of one channel then fall into different banks)
-    extern __shared__ __align__(16) uint8_t stage[];
+    // [wave][ring slot][round]; then the scale tile: scale s0 + ds and zero-point (16 + z0 + dz as fp32, or z0 as stored) of
+    // [group of the slice][channel] (rows padded: the transposing writes of consecutive groups of one channel then fall into
+    // different banks); in the end all of it is [wave][column tile][row in lane][lane] fp32 (4 KB per wave) for the final sum
     // (not pinned: the compiler places the unpacking and the matrix instructions, and the wait states between them)
     typedef HalfBlockUnpacker<BITS, false, kFieldBf16, false> Unpacker;
     constexpr int WORDS = Unpacker::WORDS;
     constexpr bool SMALL = H == 0;
-    static_assert(!SMALL || NX == 1, "32 channels: T <= 8");
     constexpr int HH = SMALL ? 1 : H;                             // 16-column accumulators: 4 HH
     constexpr int NBUF = gv_nbuf(H), ROUND = gv_round_bytes(H, NX), NDMA = (SMALL ? 1 : 2 * H) + NX, THREADS = WAVES * 64;
+    const int nbuf = SMALL ? L.form & GEMV_DEPTH : NBUF;                      // slots of the ring
     constexpr int X_AT = ROUND - NX * 1024;                       // token rows behind the packed words
     constexpr int GV_C = gv_channels(H), GV_SROW = gv_srow(H), GV_ZROW = gv_zrow(H);
     static_assert(NBUF == 2 || NBUF == 4, "the waits below");
-    static_assert(NBUF * ROUND >= 4 * HH * (4 * 64 + 16) * 4, "the final sum reuses a wave's ring");
+    static_assert(!SMALL || NX == 1, "32 channels: T <= 8");
     typedef typename std::conditional<ZBYTE, uint8_t, float>::type zp_t;
     constexpr int ZROW = ZBYTE ? GV_ZROW : GV_SROW;
-    float *sS = reinterpret_cast<float *>(stage + WAVES * NBUF * ROUND);
-    zp_t *sZ = reinterpret_cast<zp_t *>(sS + a.groups_cap * GV_SROW);
+    float *sS = reinterpret_cast<float *>(stage + WAVES * nbuf * ROUND);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15, q = lane >> 4;
     const int hb = SMALL ? c & 7 : c;                             // the lane's half block within 64 (32) channels
-    // which layer this workgroup belongs to, and that layer's descriptor: scalar loads from the argument block
-    const int bx = blockIdx.x;
-    // (one word of every cache line of the descriptors, asked for together with the totals that choose among them: the
-    // choice then reads what is on its way already)
-    {
-        int touched[(sizeof(a.layer) + 63) / 64];
-#pragma unroll
-        for (unsigned i = 0; i < sizeof(a.layer) / 64; ++i) touched[i] = kernarg_load<int>(64 * i);
-#pragma unroll
-        for (unsigned i = 0; i < sizeof(a.layer) / 64; ++i) asm volatile("" :: "s"(touched[i]));
-    }
-    int li = 0, wg0 = 0;
-#pragma unroll
-    for (int i = 0; i < GEMV_MAX_LAYERS - 1; ++i) {
-        const int e = a.wg_end[i];
-        if (bx >= e) { li = i + 1; wg0 = e; }
-    }
-    const GemvLayer L = kernarg_load<GemvLayer>((uint32_t)(li * sizeof(GemvLayer)));
     const float *l_s0 = L.s0, *l_ds = L.ds, *l_dz = L.dz;
     const uint8_t *l_z0 = L.z0;
     const int l_N = L.N, l_S = L.S;
@@ -141,7 +121,7 @@ __global__ __launch_bounds__(WAVES * 64, GV_SIMD_WAVES) void gemv_kernel(GemvArg
                           ((size_t)(n0 >> 7) * (K >> 5) + 2 * (size_t)wr0) * TILE +
                           (SMALL ? (size_t)((n0 >> 5) & 3) * (HALF / 2) : (size_t)((n0 >> 6) & 1) * HALF);
     const uint8_t *xsrc = reinterpret_cast<const uint8_t *>(L.X + ((size_t)wr0 << 6));
-    const uint32_t ring = (uint32_t)(uintptr_t)stage + wave * NBUF * ROUND;
+    const uint32_t ring = (uint32_t)(uintptr_t)stage + wave * nbuf * ROUND;
     uint32_t b_voff[2], x_voff[NX];
     if constexpr (SMALL) {
         // one DMA: 4 bits, lane (c, q) its own words, half hb % 2 of block (hb / 2, q) of the tile of its features; 3 bits, the 48
@@ -169,7 +149,7 @@ __global__ __launch_bounds__(WAVES * 64, GV_SIMD_WAVES) void gemv_kernel(GemvArg
         const int t = row < a.T ? row : a.T - 1;                  // rows beyond T repeat the last one (never stored)
         x_voff[i] = (uint32_t)t * (uint32_t)K * 2u + (uint32_t)((x & 7) ^ (row & 7)) * 16u;
     }
-    // round r lives in ring slot r % NBUF; `slot` is the slot of the next round to be issued
+    // round r lives in ring slot r % nbuf; `slot` is the slot of the next round to be issued
     int issued = 0, slot = 0;
     auto issue_round = [&]() {
         const uint32_t dst = ring + slot * ROUND;
@@ -184,15 +164,16 @@ __global__ __launch_bounds__(WAVES * 64, GV_SIMD_WAVES) void gemv_kernel(GemvArg
         bsrc += 2 * TILE;
         xsrc += 128;
         ++issued;
-        slot = slot + 1 == NBUF ? 0 : slot + 1;
+        slot = slot + 1 == nbuf ? 0 : slot + 1;
     };
 #pragma unroll
     for (int i = 0; i < NBUF; ++i)
-        if (i < nrounds) issue_round();
+        if (i < nrounds && (i < 2 || i < nbuf)) issue_round();
 
     // scale / zero-point tile of the slice: [groups touched][64 channels], transposed on the way into LDS (memory has a
     // channel's groups next to each other).  Channels are laid down so that a lane's four are neighbours.
     const int cols = rend > rbeg ? (int)div_magic((uint32_t)(rend - 1), (uint32_t)chunk_rounds, L.chunk_magic).q - g_lo + 1 : 1;
+    zp_t *sZ = reinterpret_cast<zp_t *>(sS + cols * GV_SROW);
     auto store_entry = [&](int jj, int ch, float sv, uint32_t zv, float dzv) {
         const int pos = Unpacker::BY_PARITY ? (ch & ~7) + 4 * (ch & 1) + ((ch & 7) >> 1) : ch;
         sS[jj * GV_SROW + pos] = sv;
@@ -261,36 +242,44 @@ __global__ __launch_bounds__(WAVES * 64, GV_SIMD_WAVES) void gemv_kernel(GemvArg
     }
     __syncthreads();
 
-    f32x4 y[4 * HH], acc[4 * HH], accrs = f32x4{0.f, 0.f, 0.f, 0.f};
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    f32x4 y[4 * HH], acc[4 * HH], accrs = zero;
 #pragma unroll
-    for (int ct = 0; ct < 4 * HH; ++ct) { y[ct] = f32x4{0.f, 0.f, 0.f, 0.f}; acc[ct] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+    for (int ct = 0; ct < 4 * HH; ++ct) { y[ct] = zero; acc[ct] = zero; }
 
     // this lane's words and activation fragment of step 0 within a round (step 1: STEP_B bytes on; chunk 4 + q)
     constexpr int STEP_B = BITS == 4 ? 1024 : 768;
-    const uint8_t *b_lane = stage + wave * NBUF * ROUND +
+    const uint8_t *b_lane = stage + wave * nbuf * ROUND +
                             (BITS == 4 ? lane * 16 : (SMALL ? (c >> 3) * 384 : 0) + ((hb >> 1) * 4 + q) * 24 + 4 * (c & 1));
     // token row of this lane's activation fragment; with 8 rows staged, rows 8..15 (beyond T, never stored) read rows 0..7
-    const uint8_t *x_lane = stage + wave * NBUF * ROUND + X_AT + (NX == 2 ? c : (c & 7)) * 128;
+    const uint8_t *x_lane = stage + wave * nbuf * ROUND + X_AT + (NX == 2 ? c : (c & 7)) * 128;
     const int x_pos[2] = {((SMALL ? 4 * (c >> 3) + q : q) ^ (c & 7)) * 16, ((4 + q) ^ (c & 7)) * 16};
     const Quotient wg = div_magic((uint32_t)wr0, (uint32_t)chunk_rounds, L.chunk_magic);
     int group_left = chunk_rounds - (int)wg.r;                    // rounds to the end of the scale group
     int gj = (int)wg.q - g_lo;                                    // its column of the tile
     uint32_t rd = 0;                                              // ring offset of the round being consumed
-    // A compute unit's arbiter serves the older wave first: of the workgroups that share one, the one dispatched first runs
+    // Workgroups with more rounds than the others start first (gemv_forward lays the layers out so) and go first to their end, at
+    // the highest priority: a wave's rounds follow each other, so that the longest one ends the launch.  us per block at T = 1 / 5 /
+    // 16: 4096 x 11008 4-bit, 2 slices 24.4 / 24.8 / 27.7 -> 24.4 / 24.8 / 27.0; 3072 x 8192 3-bit g64 21.3 / 21.8 / 22.1 -> 19.7 /
+    // 20.2 / 22.1; 6656 x 17920 3-bit 47.8 / 48.5 / 52.1 -> 46.5 / 47.1 / 50.4.
+    // Of the others: a compute unit's arbiter serves the older wave first: of the workgroups that share one, the one dispatched first runs
     // ahead, ends early, and leaves the others to finish with fewer loads in flight.  Where all workgroups of the launch are
     // resident at once, the later ones therefore take a higher priority for the first half of their rounds; the first ones
     // win the ties of the second half, and all end together (13B block, T = 1 and 5: 34.6 -> 33.7 and 35.5 -> 34.3 us).
     // Which came later is a guess from the index (the first prio_step workgroups are dealt one to every compute unit, and so
     // on); a wrong guess costs time only.  Where later workgroups take the places of earlier ones it cost 3 to 6 %.
-    if (a.prio_step && bx >= a.prio_step) {
+    const bool urgent = (L.form & GEMV_URGENT) != 0;
+    if (urgent) {
+        __builtin_amdgcn_s_setprio(3);
+    } else if (a.prio_step && bx >= a.prio_step) {
         if (bx < 2 * a.prio_step) __builtin_amdgcn_s_setprio(1);
         else if (bx < 3 * a.prio_step) __builtin_amdgcn_s_setprio(2);
         else __builtin_amdgcn_s_setprio(3);
     }
 #pragma unroll 1
     for (int r = 0; r < nrounds; ++r) {
-        if (r == nrounds >> 1) __builtin_amdgcn_s_setprio(0);
-        // rounds r .. min(r + NBUF, nrounds) - 1 are in flight, issued in order: wait for r only
+        if (r == nrounds >> 1 && !urgent) __builtin_amdgcn_s_setprio(0);
+        // rounds r .. min(r + nbuf, nrounds) - 1 are in flight, issued in order: wait for r only
         const int after = issued - 1 - r;                         // rounds issued after r
         if (NBUF > 3 && after == 3) gv_wait_vmcnt<3 * NDMA>();
         else if (NBUF > 2 && after == 2) gv_wait_vmcnt<2 * NDMA>();
@@ -329,7 +318,7 @@ __global__ __launch_bounds__(WAVES * 64, GV_SIMD_WAVES) void gemv_kernel(GemvArg
             asm volatile("" ::: "memory");
             issue_round();
         }
-        rd = rd + ROUND == NBUF * ROUND ? 0 : rd + ROUND;
+        rd = rd + ROUND == (uint32_t)(nbuf * ROUND) ? 0 : rd + ROUND;
         if (--group_left == 0 || r + 1 == nrounds) {
             // end of a scale group, or of this wave's share: fold offset, zero-point and scale
             // of the group into y, restart the sums
@@ -348,17 +337,17 @@ __global__ __launch_bounds__(WAVES * 64, GV_SIMD_WAVES) void gemv_kernel(GemvArg
                 for (int ct = 0; ct < 4; ++ct) {
 #pragma unroll
                     for (int jj = 0; jj < 4; ++jj) y[4 * h + ct][jj] += sc[ct] * (acc[4 * h + ct][jj] - zo[ct] * accrs[jj]);
-                    acc[4 * h + ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    acc[4 * h + ct] = zero;
                 }
             }
-            accrs = f32x4{0.f, 0.f, 0.f, 0.f};
+            accrs = zero;
             ++gj;
             group_left = chunk_rounds;
         }
     }
 
     // ---- sum the waves, then write Y (S = 1) or this slice's partial
-    __syncthreads();                                              // everyone is done with the ring
+    __syncthreads();                                              // everyone is done with the ring and the scale tile
     // [wave][column tile][row in lane][lane], column tiles 16 words further apart: those that share a bank otherwise are read together
     float *red = reinterpret_cast<float *>(stage);
     constexpr int CT = 4 * 64 + 16;
@@ -386,6 +375,38 @@ __global__ __launch_bounds__(WAVES * 64, GV_SIMD_WAVES) void gemv_kernel(GemvArg
     }
 }
 
+// NARROW: the launch has layers whose tiles are half as wide (GemvLayer::narrow).
+template <int BITS, int H, int WAVES, int NX, bool ZBYTE, bool NARROW>
+__global__ __launch_bounds__(WAVES * 64, GV_SIMD_WAVES) void gemv_kernel(GemvArgs a)
+{
+    extern __shared__ __align__(16) uint8_t stage[];
+    // which layer this workgroup belongs to, and that layer's descriptor: scalar loads from the argument block
+    const int bx = blockIdx.x;
+    // (one word of every cache line of the descriptors, asked for together with the totals that choose among them: the
+    // choice then reads what is on its way already)
+    {
+        int touched[(sizeof(a.layer) + 63) / 64];
+#pragma unroll
+        for (unsigned i = 0; i < sizeof(a.layer) / 64; ++i) touched[i] = kernarg_load<int>(64 * i);
+#pragma unroll
+        for (unsigned i = 0; i < sizeof(a.layer) / 64; ++i) asm volatile("" :: "s"(touched[i]));
+    }
+    int li = 0, wg0 = 0;
+#pragma unroll
+    for (int i = 0; i < GEMV_MAX_LAYERS - 1; ++i) {
+        const int e = a.wg_end[i];
+        if (bx >= e) { li = i + 1; wg0 = e; }
+    }
+    const GemvLayer L = kernarg_load<GemvLayer>((uint32_t)(li * sizeof(GemvLayer)));
+    if constexpr (NARROW) {
+        if (L.form & GEMV_NARROW) {                                        // (uniform)
+            gemv_tile<BITS, H - 1, WAVES, NX, ZBYTE>(a, L, bx, wg0, stage);
+            return;
+        }
+    }
+    gemv_tile<BITS, H, WAVES, NX, ZBYTE>(a, L, bx, wg0, stage);
+}
+
 // Y[t,n] = bf16( partial[0][t,n] + partial[1][t,n] + ... ), fixed order, for every sliced layer of the launch
 // (blockIdx.y = layer; layers with a single slice wrote their Y themselves).
 __global__ __launch_bounds__(256) void gemv_finish_kernel(GemvArgs a)
@@ -405,9 +426,17 @@ __global__ __launch_bounds__(256) void gemv_finish_kernel(GemvArgs a)
 
 // ---- host side
 
+// LDS of a tile of 64 h channels: ring and scale tile, which the final sums (of 64 column tiles and waves: gemv_tile) take in the end
+static int gv_tile_lds(int h, int waves, int nx, bool zbyte, int groups, int depth)
+{
+    const int loop = waves * depth * gv_round_bytes(h, nx) + groups * gv_group_bytes(h, zbyte);
+    const int sums = waves * 4 * (h > 1 ? h : 1) * (4 * 64 + 16) * 4;
+    return loop > sums ? loop : sums;
+}
+
 static int gv_lds_bytes(const GemvForm &f, int nx, bool zbyte, int groups)
 {
-    return f.waves * gv_nbuf(f.h) * gv_round_bytes(f.h, nx) + groups * gv_group_bytes(f.h, zbyte);
+    return gv_tile_lds(f.h, f.waves, nx, zbyte, groups, gv_nbuf(f.h));
 }
 
 static int gv_per_cu(const GemvForm &f, int lds)                   // workgroups a compute unit holds: LDS, registers
@@ -447,7 +476,14 @@ static int gv_cols(int K, int chunk, int S)                        // most scale
 // slices before, 5120 x 13824 g128 14.8 -> 18.5 / 16.0, and 8064 x 28160 g64 17 us longer, which is why long ones stay.
 //
 // More tiles: four waves.  Every workgroup should be resident at once (the last, partly filled round is otherwise made of
-// few workgroups with a few loads in flight each) and no layer's much longer than the others': layers are sliced to at most
+// few workgroups with a few loads in flight each) and no layer's much longer than the others'.  At most 8 tokens, per-channel layers
+// and more than two workgroups per unit: layers of more than 1.35 times the mean length take tiles of 32 channels beside the
+// others' 64, which need no slices, that is no second launch; such a tile's rounds are as many and follow each other,
+// so they start first and go first (without that the block of d = 5120, 3-bit g128, took 36.5 instead of 32.0 us).  us per block at
+// T = 1 / 5, sliced -> so: d = 4096 4-bit 24.4 / 24.8 -> 22.9 / 23.1, 3-bit 20.5 / 21.1 -> 19.2 / 19.6, d = 5120 3-bit 29.0 / 29.6 -> 27.1 /
+// 27.8, d = 3072 4-bit 17.5 / 18.1 -> 15.7 / 16.4.  Not with scale groups, whose tile and folds cost a tile of 32 channels as much as
+// one of 64 (d = 4096 4-bit g128 27.5 / 28.2 -> 28.4 / 28.9), nor for more tokens, of which a tile of 32 would fetch twice as
+// much per channel, nor at one workgroup per unit (d = 2048 g128 12.1 -> 12.2).  Otherwise layers are sliced to at most
 // 1.35 times the mean length, more while the workgroups' scale tiles keep them from fitting on the chip together; failing
 // that, 128 channels per workgroup (half of the token rows' traffic and LDS per channel).  us per block at T = 1 / 16, 13B
 // 3-bit g128: 3 slices of the long layer 34.6 / 42.3, 2 slices (not resident) 38.9 / 45.6, 128 channels 35.8 / 38.2.
@@ -496,6 +532,23 @@ GemvForm gemv_plan(int n, const int *N, const int *K, const int *chunk, int bits
     int best_len = rmax, best_per_cu = 0;
     for (int w = 0; w < (zbyte ? 2 : 1); ++w) {
         const GemvForm f = w ? wide : small;
+        if (zbyte && T <= 8 && w == 0) {              // long layers in tiles half as wide
+            GemvForm g = f;
+            int wgs = 0, lds = 0;
+            bool fits = true;
+            for (int j = 0; j < n; ++j) {
+                const int r = K[j] / 64, cols = gv_cols(K[j], chunk[j], 1);
+                const bool narrow = r > 1.35 * mean;
+                S[j] = 1;
+                g.narrow |= (narrow ? 1u : 0u) << j;
+                wgs += N[j] / (narrow ? gemv_channels(f) / 2 : gemv_channels(f));
+                const int need = narrow ? gv_tile_lds(f.h - 1, f.waves, nx, true, cols, 2)
+                                        : gv_tile_lds(f.h, f.waves, nx, true, cols, gv_nbuf(f.h));
+                lds = need > lds ? need : lds;
+                fits = fits && (!narrow || (cols == 1 && r <= 2.0 * 1.35 * mean));
+            }
+            if (g.narrow && fits && wgs > 2 * cus && lds <= GV_LDS_MAX / 2 && gv_per_cu(f, lds) * cus >= wgs) return g;
+        }
         for (int s = 1; s <= 8; ++s) {
             const int len = (rmax + s - 1) / s;
             if (len > 1.35 * mean && s < 8) continue;
@@ -525,7 +578,8 @@ hipError_t launch_gemv(int bits, const GemvForm &f, const GemvArgs &a_in, hipStr
     GemvArgs a = a_in;
     bool sliced = false, zbyte = true;
     unsigned max_tn = 0;
-    a.groups_cap = 1;
+    const int nx = a.T > 8 ? 2 : 1;
+    int lds = 0, groups[GEMV_MAX_LAYERS];
     for (int j = 0; j < a.n_layers; ++j) {
         GemvLayer &l = a.layer[j];
         if (l.N % 128 != 0 || l.K % 128 != 0 || l.chunk % 64 != 0 || l.S < 1 || a.T < 1 || a.T > 16) return hipErrorInvalidValue;
@@ -537,11 +591,30 @@ hipError_t launch_gemv(int bits, const GemvForm &f, const GemvArgs &a_in, hipStr
         l.slice_rem = l.K / 64 % l.S;
         l.s_magic = 0xFFFFFFFFu / (uint32_t)l.S;
         l.chunk_magic = 0xFFFFFFFFu / (uint32_t)l.chunk_rounds;
-        const int g = gv_cols(l.K, l.chunk, l.S);
-        a.groups_cap = g > a.groups_cap ? g : a.groups_cap;
+        groups[j] = gv_cols(l.K, l.chunk, l.S);
     }
-    const int wgs = a.wg_end[GEMV_MAX_LAYERS - 1], nx = a.T > 8 ? 2 : 1;
-    const int lds = gv_lds_bytes(f, nx, zbyte, a.groups_cap);
+    for (int j = 0; j < a.n_layers; ++j) {
+        GemvLayer &l = a.layer[j];
+        const bool narrow = (f.narrow >> j & 1u) != 0;
+        const int h = narrow ? f.h - 1 : f.h;
+        if (h < 0 || (narrow && (!zbyte || l.S > 1))) return hipErrorInvalidValue;
+        l.form = narrow ? GEMV_NARROW | 2 : gv_nbuf(h);
+        const int need = gv_tile_lds(h, f.waves, nx, zbyte, groups[j], l.form & GEMV_DEPTH);
+        lds = need > lds ? need : lds;
+    }
+    const int wgs = a.wg_end[GEMV_MAX_LAYERS - 1];
+    double work = 0.0;
+    auto rounds = [](const GemvLayer &l) { return (l.form & GEMV_NARROW ? 0.5 : 1.0) * (l.K / 64) / l.S; };
+    for (int j = 0; j < a.n_layers; ++j) work += rounds(a.layer[j]) * (a.wg_end[j] - (j ? a.wg_end[j - 1] : 0));
+    for (int j = 0; j < a.n_layers; ++j) {
+        GemvLayer &l = a.layer[j];
+        // deeper rings where the LDS is there anyway
+        while ((l.form & GEMV_NARROW) && (l.form & GEMV_DEPTH) < gv_nbuf(f.h - 1) &&
+               gv_tile_lds(f.h - 1, f.waves, nx, zbyte, groups[j], (l.form & GEMV_DEPTH) + 1) <= lds)
+            ++l.form;
+        if (f.waves == 4 && ((l.form & GEMV_NARROW) || rounds(l) * wgs > 1.15 * work)) l.form |= GEMV_URGENT;
+    }
+    for (int j = a.n_layers; j < GEMV_MAX_LAYERS; ++j) a.layer[j] = a.layer[a.n_layers - 1];
     if (lds > GV_LDS_MAX) return hipErrorInvalidValue;
     const int cus = compute_units();
     a.prio_step = wgs <= gv_per_cu(f, lds) * cus ? cus : 0;
@@ -550,10 +623,10 @@ hipError_t launch_gemv(int bits, const GemvForm &f, const GemvArgs &a_in, hipStr
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     // One instantiation: its dynamic LDS (more than the default limit: raised once per device), then the launch.
-    auto go = [&](auto h_c, auto waves_c, auto bits_c, auto nx_c, auto z_c) -> hipError_t {
+    auto go_as = [&](auto h_c, auto waves_c, auto bits_c, auto nx_c, auto z_c, auto narrow_c) -> hipError_t {
         static bool allowed[64];
         const auto kern = gemv_kernel<decltype(bits_c)::value, decltype(h_c)::value, decltype(waves_c)::value,
-                                      decltype(nx_c)::value, decltype(z_c)::value>;
+                                      decltype(nx_c)::value, decltype(z_c)::value, decltype(narrow_c)::value>;
         if (!allowed[dev]) {
             const hipError_t e2 = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                                       hipFuncAttributeMaxDynamicSharedMemorySize, GV_LDS_MAX);
@@ -566,6 +639,14 @@ hipError_t launch_gemv(int bits, const GemvForm &f, const GemvArgs &a_in, hipStr
         return hipGetLastError();
     };
     using std::integral_constant;
+    auto go = [&](auto h_c, auto waves_c, auto bits_c, auto nx_c, auto z_c) -> hipError_t {
+        if (f.narrow) {
+            if constexpr (decltype(h_c)::value == 1 && decltype(waves_c)::value == 4 && decltype(nx_c)::value == 1 && decltype(z_c)::value)
+                return go_as(h_c, waves_c, bits_c, nx_c, z_c, integral_constant<bool, true>{});
+            return hipErrorInvalidValue;
+        }
+        return go_as(h_c, waves_c, bits_c, nx_c, z_c, integral_constant<bool, false>{});
+    };
     const integral_constant<int, 0> none;
     const integral_constant<int, 1> one;
     const integral_constant<int, 2> two;

@@ -259,6 +259,8 @@ hipError_t launch_group_prep(GroupPrep &a, hipStream_t stream);
 // side along the workgroup index.  Every layer has its own shape, input and slicing, so that the linears of a
 // whole decoder block (different K, different X) can share one launch; the bit width is the launch's.
 constexpr int GEMV_MAX_LAYERS = 8;
+// GemvLayer::form: mask of the ring's depth; tiles half as wide as the launch's (GemvForm::narrow); workgroups that go first
+enum { GEMV_DEPTH = 7, GEMV_NARROW = 8, GEMV_URGENT = 16 };
 struct GemvLayer {
     const uint32_t *packed;
     const float *s0, *ds;     // [N, G]; ds may be NULL
@@ -270,8 +272,9 @@ struct GemvLayer {
     int N, K, G;
     int chunk;                // features per scale group (K for per-channel layers)
     int S;                    // feature slices: a channel tile is S workgroups
-    // set by launch_gemv: rounds of 64 features per scale group; rounds of a slice, one more in the first slice_rem slices;
+    // set by launch_gemv: rounds that a wave keeps in flight and flags (GEMV_*); rounds of 64 features per scale group; rounds of a slice, one more in the first slice_rem slices;
     // reciprocals (div_magic) of S and of chunk_rounds
+    int form;
     int chunk_rounds, slice_rounds, slice_rem;
     uint32_t s_magic, chunk_magic;
 };
@@ -281,11 +284,12 @@ struct GemvArgs {
     int n_layers;
     int T;
     int prio_step;                      // workgroups per step of priority, 0: none (set by launch_gemv)
-    int groups_cap;                     // scale groups a workgroup's LDS holds (set by launch_gemv)
 };
-// Form of such a launch: 64 h channels (h = 0: 32) per workgroup of that many waves.
+// Form of such a launch: 64 h channels (h = 0: 32) per workgroup of that many waves; half as many in tiles of layer j where bit j
+// of `narrow` is set.
 struct GemvForm {
     int h, waves;
+    uint32_t narrow = 0;
 };
 inline int gemv_channels(const GemvForm &f) { return f.h == 0 ? 32 : 64 * f.h; }
 // The form, and the slices of every layer (S[0..n)).  zbyte: no layer has a trained zero-point offset, so zero-points are

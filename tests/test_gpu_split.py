@@ -197,6 +197,20 @@ def _small_batch_form(peqa, shapes, bits, group, T):
     return f.h, f.waves, list(S)
 
 
+def _small_batch_narrow(peqa, shapes, bits, group, T):
+    """The layers of that plan whose tiles are half as wide, a bit each."""
+    import ctypes
+
+    class Form(ctypes.Structure):
+        _fields_ = [("h", ctypes.c_int), ("waves", ctypes.c_int), ("narrow", ctypes.c_uint32)]
+
+    plan = peqa.lib()._ZN4peqa9gemv_planEiPKiS1_S1_iibmiPi
+    plan.restype = Form
+    ints = ctypes.c_int * len(shapes)
+    return plan(len(shapes), ints(*[n for n, _ in shapes]), ints(*[k for _, k in shapes]),
+                ints(*[group or k for _, k in shapes]), bits, T, True, ctypes.c_size_t(2 ** 64 - 1), 256, ints()).narrow
+
+
 @pytest.mark.parametrize("bits,group", [(4, 0), (3, 0), (4, 64), (3, 128)])
 def test_small_batch_form_of_128_channels(gpu, oracle, bits, group):
     """T <= 16, more 64-channel tiles than fit on the chip at once: two per workgroup, with both numbers of staged token
@@ -277,6 +291,41 @@ def test_small_batch_form_of_32_channels(gpu, oracle, bits, group):
                 near(dicts[i]["Y"], refs[i])
     # a longer layer is sliced instead
     assert _small_batch_form(peqa, [(384, 6144)], bits, group, 8)[0] == 1
+
+
+@pytest.mark.parametrize("bits", [3, 4])
+def test_small_batch_narrow_tiles(gpu, oracle, bits):
+    """T <= 8, a launch of many per-channel tiles of which two layers are about twice as long: theirs have 32 channels, and are whole;
+    uneven numbers of rounds per wave and rings that are refilled.  With more tokens they are sliced, and laid out
+    first as well.  Tolerance as for 32 channels throughout."""
+    import torch
+    from paper_2305_14152_amd import peqa
+    shapes = [(16512, 768), (16384, 1280), (384, 1664), (256, 2048)]
+    seed = 78000 + bits * 1000
+    dicts, refs, Xs = [], [], []
+    for j, (N, K) in enumerate(shapes):
+        W = synth.normal_f32(seed + 10 * j, (N, K), 0.02)
+        codes, s0, z0 = oracle.quantize(W, bits, 0)
+        ds = synth.normal_f32(seed + 10 * j + 1, s0.shape, 1e-3)
+        layer = gpu.GpuLayer(W, bits, 0)
+        Xs.append(synth.normal_bf16(seed + 10 * j + 2, (16, K), 1.0))
+        refs.append(oracle.fwd(codes, s0, ds, z0, Xs[j], 0))
+        dicts.append(dict(L=layer.L, packed=layer.packed, s0=layer.s0, z0=layer.z0, ds=gpu.to_dev(ds)))
+    for T in (1, 8, 9, 16):
+        print("narrow tiles bits=%d T=%d" % (bits, T), flush=True)
+        h, waves, S = _small_batch_form(peqa, shapes, bits, 0, T)
+        assert (h, waves) == (1, 4) and _small_batch_narrow(peqa, shapes, bits, 0, T) == (0b1100 if T <= 8 else 0)
+        assert S[2] > 1 and S[3] > 1 if T > 8 else S == [1] * 4
+        for j, d in enumerate(dicts):
+            d["X"] = gpu.to_dev(Xs[j][:T])
+            d["Y"] = torch.zeros((T, shapes[j][0]), dtype=torch.int16, device="cuda")
+        items = peqa.block_items(dicts)
+        nb = peqa.block_workspace_bytes(items, T, peqa.PEQA_OP_FWD)
+        ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+        peqa.block_fwd(items, T, ws, nb)
+        torch.cuda.synchronize()
+        for d, ref in zip(dicts, refs):
+            assert (np.abs(gpu.bf16_dev_to_f64(d["Y"]) - ref[:T]) <= 2.0 ** -8 * np.abs(ref[:T]) + 1e-4 * np.abs(ref[:T]).max()).all()
 
 
 @pytest.mark.parametrize("bits,N,K,T", [(4, 128, 512, 33), (4, 384, 512, 65), (3, 256, 640, 300), (3, 128, 8192, 40)])
