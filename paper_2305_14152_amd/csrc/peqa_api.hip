@@ -643,7 +643,7 @@ static peqa_status bwd_impl(const peqa_layout *L, const uint32_t *packed, const 
             if (peqa::launch_group_table(s0, ds, z0, dz, N, G, sb, s) != hipSuccess) return PEQA_ERR_DEVICE;
             peqa::GemmArgs a = dx_args(w.rt_dx_alone);
             if (with_transposes) {
-                a.tp_blocks = (Tp / 64) * (K / 64 + N / 64); a.tp_Tp = Tp; a.tp_X = X; a.tp_Xt = xt; a.tp_dYt = dyt;
+                a.tp_blocks = ((Tp / 64) * (K / 64 + N / 64) + 3) / 4; a.tp_Tp = Tp; a.tp_X = X; a.tp_Xt = xt; a.tp_dYt = dyt;
             }
             return run_contraction(L->bits, peqa::MODE_DX, a, w.split_dx_alone, reinterpret_cast<float *>(ws + w.acc), s);
         };

@@ -25,11 +25,12 @@ __global__ __launch_bounds__(256 * KW, 3 - KW) void gemm_kernel(GemmArgs a)
         // dispatched last and take the places that the last tiles leave free on the compute units, so most of
         // their time is not added to the launch.
         const int spare = (int)blockIdx.x - ((int)gridDim.x - a.tp_blocks);
-        if (spare >= 0) {
-            const int bts = a.tp_Tp >> 6, nx = bts * (a.K >> 6);
-            uint16_t(*tile)[64 + 2] = reinterpret_cast<uint16_t(*)[64 + 2]>(lds);
-            if (spare < nx) transpose_pad_tile(a.tp_X, a.T, a.K, a.tp_Xt, spare % bts, spare / bts, tile);
-            else transpose_pad_tile(a.A, a.T, a.N, a.tp_dYt, (spare - nx) % bts, (spare - nx) / bts, tile);
+        if (spare >= 0) {                                  // a tile per wave, neighbouring columns
+            const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), x = 4 * spare + wave;
+            const int bts = a.tp_Tp >> 6, kb = a.K >> 6, nb = a.N >> 6;
+            u32x4 *piece = reinterpret_cast<u32x4 *>(lds + wave * TRANSPOSE_LDS);
+            if (x < bts * kb) transpose_pad_tile(a.tp_X, a.T, a.K, a.tp_Xt, x / kb, x % kb, piece);
+            else if (x < bts * (kb + nb)) transpose_pad_tile(a.A, a.T, a.N, a.tp_dYt, (x - bts * kb) / nb, (x - bts * kb) % nb, piece);
             return;
         }
     }
@@ -59,7 +60,7 @@ __global__ __launch_bounds__(256, 2) void gemm_bwd_pair_kernel(GemmArgs a_dds, G
 
 // Bandwidth-bound side work inside a multi-contraction launch: auxiliary workgroup `w` of `m.aux_wgs` walks the
 // units w, w + aux_wgs, ... of one index space: first the SDY_ROWS-row blocks of the scale_dy jobs, then the
-// 256-element chunks of the reduce jobs.
+// 256-element chunks of the reduce jobs; before them its waves walk the 64 x 64 tiles of the transpose jobs.
 static_assert(SDY_ROWS == SDY_ROWS_HOST, "row blocks of scale_dy_rows");
 __device__ __forceinline__ void multi_aux(int n_sdy, int n_red, int n_tp, int aux_wgs, int w, uint8_t *lds)
 {
@@ -72,20 +73,46 @@ __device__ __forceinline__ void multi_aux(int n_sdy, int n_red, int n_tp, int au
     const int n_blk = last(SDY0, m.n_sdy, sizeof(ScaleDyJob), offsetof(ScaleDyJob, blk_end));
     const int n_chunk = last(RED0, m.n_red, sizeof(ReduceJob), offsetof(ReduceJob, chunk_end));
     const int n_tile = last(TP0, m.n_tp, sizeof(TransposeJob), offsetof(TransposeJob, tile_end));
-    for (int u = w; u < n_blk + n_chunk + n_tile; u += m.aux_wgs) {
-        if (u >= n_blk + n_chunk) {
-            const int x = u - n_blk - n_chunk;
+    if (n_tile > 0) {
+        // a tile per wave; the wave's next tile is asked for before this one is turned
+        const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        u32x4 *piece = reinterpret_cast<u32x4 *>(lds + wave * TRANSPOSE_LDS);
+        struct Tile { TransposeJob J; int bt, bc; };
+        auto tile_of = [&](int x) __attribute__((always_inline)) {
             int j = 0, x0 = 0;
             for (int i = 0; i + 1 < m.n_tp; ++i) {
                 const int e = kernarg_load<int>(TP0 + (uint32_t)(i * sizeof(TransposeJob) + offsetof(TransposeJob, tile_end)));
                 if (x >= e) { j = i + 1; x0 = e; }
             }
-            const TransposeJob J = kernarg_load<TransposeJob>(TP0 + (uint32_t)(j * sizeof(TransposeJob)));
-            const int bts = J.Tp >> 6;
-            transpose_pad_tile(J.src, J.T, J.C, J.dst, (x - x0) % bts, (x - x0) / bts, reinterpret_cast<uint16_t(*)[64 + 2]>(lds));
-            __syncthreads();                                   // the LDS tile is reused by the next one
-            continue;
+            Tile t;
+            t.J = kernarg_load<TransposeJob>(TP0 + (uint32_t)(j * sizeof(TransposeJob)));
+            const int bcs = t.J.C >> 6;
+            t.bt = (x - x0) / bcs;
+            t.bc = (x - x0) - t.bt * bcs;
+            return t;
+        };
+        int x = 4 * w + wave;
+        if (x < n_tile) {
+            Tile t = tile_of(x);
+            TransposeRows r;
+            transpose_load(t.J.src, t.J.T, t.J.C, t.bt, t.bc, r);
+            for (;;) {
+                x += 4 * m.aux_wgs;
+                Tile next = t;
+                TransposeRows ahead;
+                if (x < n_tile) {
+                    next = tile_of(x);
+                    transpose_load(next.J.src, next.J.T, next.J.C, next.bt, next.bc, ahead);
+                }
+                transpose_store(r, t.J.C, t.J.dst, t.bt, t.bc, piece);
+                if (x >= n_tile) break;
+                t = next;
+                r = ahead;
+            }
         }
+        __syncthreads();                                       // what follows uses the LDS too
+    }
+    for (int u = w; u < n_blk + n_chunk; u += m.aux_wgs) {
         if (u < n_blk) {
             int j = 0, b0 = 0;
             for (int i = 0; i + 1 < m.n_sdy; ++i) {

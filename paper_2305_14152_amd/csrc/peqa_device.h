@@ -245,36 +245,68 @@ __device__ __forceinline__ void reduce_partials_at(const float *__restrict__ par
     if (j < n) out[j] = partials_sum(partial, ntiles, n, j);
 }
 
-// One 64 x 64 tile of the step-major transposed copy that the token contraction of group-wise layers reads:
+// The step-major transposed copy that the token contraction of group-wise layers reads:
 // dst[t / 32][cc / 16][(t % 32) / 8][cc % 16][t % 8] = src[t, cc] for t < T, 0 for T <= t < Tp (the KB of 16 columns and a
-// step is one matrix operand, lane by lane), tile (bt, bc) of 64 tokens x 64 columns, by one workgroup of 256 threads
-// through `tile`, 64 x 66 bf16 of LDS.  C % 64 == 0.
-__device__ __forceinline__ void transpose_pad_tile(const uint16_t *__restrict__ src, int T, int C, uint16_t *__restrict__ dst,
-                                                   int bt, int bc, uint16_t (*tile)[64 + 2])
+// step is one matrix operand, lane by lane), C % 64 == 0, by one wave per 64 x 64 tile (bt, bc) of tokens x columns.
+//
+// Bound by memory where it has the machine to itself; beside matrix work by what it takes of LDS, of the vector units and of a
+// place on a compute unit.  So a lane reads 8 columns of 8 tokens, 16 bytes each (transpose_load), turns them into 8 columns' pieces
+// of 8 tokens in registers (32 byte permutes), and the pieces only change lanes in LDS, 16 bytes at a time, so that the stores are whole
+// KB; nothing but the wave itself waits, and the next tile's loads are on their way meanwhile.
+// By workgroups that moved 2 bytes at a time through LDS between two barriers, the copies of a 13B block (T = 2048, 675 MB read and
+// written) lengthened the dX launch that they ride in by 140 us.
+struct TransposeRows {
+    u32x4 row[8];                                          // tokens 8 (lane / 8) + j, columns 8 (lane % 8) .. + 7 of the tile
+};
+__device__ __forceinline__ void transpose_load(const uint16_t *__restrict__ src, int T, int C, int bt, int bc, TransposeRows &r)
 {
-    const int t0 = bt * 64, c0 = bc * 64;
-    const int ch = threadIdx.x & 7;
+    const int lane = threadIdx.x & 63, t0 = bt * 64 + 8 * (lane >> 3);
+    const uint16_t *from = src + (size_t)bc * 64 + 8 * (lane & 7);
+    if (bt * 64 + 64 <= T) {                               // (uniform)
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int row = (threadIdx.x >> 3) + 32 * h, t = t0 + row;
-        u32x4 v = {0u, 0u, 0u, 0u};
-        if (t < T) v = *reinterpret_cast<const u32x4 *>(src + (size_t)t * C + c0 + 8 * ch);
+        for (int j = 0; j < 8; ++j) r.row[j] = *reinterpret_cast<const u32x4 *>(from + (size_t)(t0 + j) * C);
+    } else {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            tile[row][8 * ch + 2 * e] = (uint16_t)(v[e] & 0xFFFFu);
-            tile[row][8 * ch + 2 * e + 1] = (uint16_t)(v[e] >> 16);
+        for (int j = 0; j < 8; ++j) {
+            r.row[j] = u32x4{0u, 0u, 0u, 0u};
+            if (t0 + j < T) r.row[j] = *reinterpret_cast<const u32x4 *>(from + (size_t)(t0 + j) * C);
         }
     }
-    __syncthreads();
+}
+// `piece`: 8 KB of LDS of this wave's own.  Pieces lie there in the order of the copy, eight of them (128 bytes) permuted by the column
+// block of the lane that wrote them: writes and reads of eight lanes then fall into different banks.
+constexpr int TRANSPOSE_LDS = 8192;                        // per wave
+__device__ __forceinline__ void transpose_store(const TransposeRows &r, int C, uint16_t *__restrict__ dst, int bt, int bc, u32x4 *piece)
+{
+    const int lane = threadIdx.x & 63, cb = lane & 7, tb = lane >> 3;
+    const int at = (((tb >> 2) * 4 + (cb >> 1)) * 4 + (tb & 3)) * 16 + 8 * (cb & 1);   // step, 16 columns, 8 tokens, column
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        // step h, 16-byte pieces in the order of the copy: 4 KB of 64 columns
-        const int cc = 16 * (threadIdx.x >> 6) + (threadIdx.x & 15), t = 32 * h + 8 * ((threadIdx.x >> 4) & 3);
-        u32x4 o;
+    for (int w = 0; w < 4; ++w)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = (uint32_t)tile[t + 2 * e][cc] | ((uint32_t)tile[t + 2 * e + 1][cc] << 16);
-        *reinterpret_cast<u32x4 *>(dst + ((size_t)((t0 >> 5) + h) * C + c0) * 32 + 8 * threadIdx.x) = o;
+        for (int h = 0; h < 2; ++h) {
+            u32x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                o[e] = __builtin_amdgcn_perm(r.row[2 * e + 1][w], r.row[2 * e][w], h ? 0x07060302u : 0x05040100u);
+            piece[at + ((2 * w + h) ^ cb)] = o;
+        }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    uint16_t *to = dst + ((size_t)(2 * bt) * C + (size_t)bc * 64) * 32 + 8 * lane;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int p = 64 * i + lane, writer = ((p >> 3) & 1) | (((p >> 6) & 3) << 1);
+        *reinterpret_cast<u32x4 *>(to + (i >> 2) * (size_t)C * 32 + (i & 3) * 512) = piece[p ^ writer];
     }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();                       // the next tile's pieces overwrite these
+}
+__device__ __forceinline__ void transpose_pad_tile(const uint16_t *__restrict__ src, int T, int C, uint16_t *__restrict__ dst, int bt,
+                                                   int bc, u32x4 *piece)
+{
+    TransposeRows r;
+    transpose_load(src, T, C, bt, bc, r);
+    transpose_store(r, C, dst, bt, bc, piece);
 }
 
 // A piece of the kernel's argument block read at a run-time (wavefront-uniform) byte offset: scalar loads from the

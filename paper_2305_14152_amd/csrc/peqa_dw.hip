@@ -60,17 +60,21 @@ __global__ __launch_bounds__(256, 2) void dw_multi_kernel(DwMultiArgs m)
     dw_tile<BITS>(a, b - wg0, lds);
 }
 
-// transpose_pad_tile (peqa_device.h) for every 64 x 64 tile of both operands, X [T, K] and dY [T, N]: Tp / 64 x (K + N) / 64
-// workgroups, numbered along the tokens first (a grid's second dimension ends at 65536: K + N would too, at 2^22).  One
-// launch, 1.4 us less than two in a step of 193.
+// transpose_pad_tile (peqa_device.h) for every 64 x 64 tile of both operands, X [T, K] and dY [T, N], along the columns first: four
+// to a workgroup, one grid dimension (a second one ends at 65536).  One launch, 1.4 us less than two in a step of 193.
 __global__ __launch_bounds__(256) void transpose_pad_kernel(const uint16_t *__restrict__ X, int K, uint16_t *__restrict__ xt,
                                                              const uint16_t *__restrict__ dY, int N,
                                                              uint16_t *__restrict__ dyt, int T)
 {
-    __shared__ uint16_t tile[64][64 + 2];
-    const int bts = (T + 63) >> 6, bc = (int)blockIdx.x / bts, of_x = K >> 6;
-    const bool x = bc < of_x;
-    transpose_pad_tile(x ? X : dY, T, x ? K : N, x ? xt : dyt, (int)blockIdx.x - bc * bts, x ? bc : bc - of_x, tile);
+    __shared__ u32x4 pieces[4 * TRANSPOSE_LDS / 16];
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int bts = (T + 63) >> 6, of_x = bts * (K >> 6);
+    int b = 4 * (int)blockIdx.x + wave;
+    if (b >= of_x + bts * (N >> 6)) return;
+    const bool x = b < of_x;
+    b -= x ? 0 : of_x;
+    const int bcs = (x ? K : N) >> 6;
+    transpose_pad_tile(x ? X : dY, T, x ? K : N, x ? xt : dyt, b / bcs, b % bcs, pieces + wave * (TRANSPOSE_LDS / 16));
 }
 
 // d_ds[i, g] = sum of pc[i, chunk] over the gsz / 64 chunks of group g, in order.
@@ -112,7 +116,7 @@ hipError_t launch_transpose_pad(const uint16_t *X, int K, uint16_t *xt, const ui
                                 hipStream_t stream)
 {
     trace_before(KID_TRANSPOSE, stream);
-    hipLaunchKernelGGL(transpose_pad_kernel, dim3((T + 63) / 64 * ((K + N) / 64)), dim3(256), 0, stream, X, K, xt, dY, N, dyt, T);
+    hipLaunchKernelGGL(transpose_pad_kernel, dim3(((T + 63) / 64 * ((K + N) / 64) + 3) / 4), dim3(256), 0, stream, X, K, xt, dY, N, dyt, T);
     trace_after(KID_TRANSPOSE, stream);
     return hipGetLastError();
 }

@@ -42,7 +42,7 @@ struct GemmArgs {
     float *partial;           // [tiles_t, N]   (MODE_DDS) per-token-tile column sums
     // MODE_DX, group-wise, four-wave form only: tp_blocks > 0 adds that many workgroups at the end of the grid, which
     // write the step-major transposed copies of X [T, K] and dY [T, N] (transpose_pad_tile) that the token contraction
-    // of the same backward reads afterwards: Tp / 64 x K / 64 tiles of X first, then Tp / 64 x N / 64 of dY
+    // of the same backward reads afterwards: Tp / 64 x K / 64 tiles of X first, then Tp / 64 x N / 64 of dY, four to a workgroup
     int tp_blocks, tp_Tp;
     const uint16_t *tp_X;
     uint16_t *tp_Xt, *tp_dYt;

@@ -158,7 +158,7 @@ __global__ __launch_bounds__(256) void group_table_tile_kernel(const float *__re
     group_table_tile(s0, ds, z0, dz, N, G, sb, (int)blockIdx.x * GT_CH, gt_lds);
 }
 
-// Tables and transposed copies of a group-wise backward (GroupPrep): the tables' workgroups first, then one per 64 x 64 tile of
+// Tables and transposed copies of a group-wise backward (GroupPrep): the tables' workgroups first, then one per four 64 x 64 tiles of
 // the copies.  One launch where there were two, of 3 us and more each.
 __global__ __launch_bounds__(256) void group_prep_kernel(GroupPrep a)
 {
@@ -183,15 +183,17 @@ __global__ __launch_bounds__(256) void group_prep_kernel(GroupPrep a)
         }
         return;
     }
-    b -= a.table_end[GT_MAX - 1];
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    b = 4 * (b - a.table_end[GT_MAX - 1]) + wave;
+    if (b >= kernarg_load<int>((uint32_t)(offsetof(GroupPrep, tp) + (a.n_tp - 1) * sizeof(TransposeJob) + offsetof(TransposeJob, tile_end)))) return;
     int j = 0, b0 = 0;
     for (int i = 0; i + 1 < a.n_tp; ++i) {
         const int e = kernarg_load<int>((uint32_t)(offsetof(GroupPrep, tp) + i * sizeof(TransposeJob) + offsetof(TransposeJob, tile_end)));
         if (b >= e) { j = i + 1; b0 = e; }
     }
     const TransposeJob J = kernarg_load<TransposeJob>((uint32_t)(offsetof(GroupPrep, tp) + j * sizeof(TransposeJob)));
-    const int bts = J.Tp >> 6;
-    transpose_pad_tile(J.src, J.T, J.C, J.dst, (b - b0) % bts, (b - b0) / bts, reinterpret_cast<uint16_t(*)[64 + 2]>(gt_lds));
+    const int bcs = J.C >> 6;
+    transpose_pad_tile(J.src, J.T, J.C, J.dst, (b - b0) / bcs, (b - b0) % bcs, reinterpret_cast<u32x4 *>(gt_lds) + wave * (TRANSPOSE_LDS / 16));
 }
 
 // group_table_tile_kernel for several layers: blockIdx.y = layer.
@@ -503,9 +505,9 @@ hipError_t launch_group_prep(GroupPrep &a, hipStream_t stream)
     }
     const int tp = a.n_tp > 0 ? a.tp[a.n_tp - 1].tile_end : 0;
     if (blocks + tp == 0) return hipSuccess;
-    const int table_lds = a.by_tiles ? 2 * GT_CH * gmax * (int)sizeof(float) : 0, tp_lds = 64 * (64 + 2) * (int)sizeof(uint16_t);
+    const int table_lds = a.by_tiles ? 2 * GT_CH * gmax * (int)sizeof(float) : 0, tp_lds = tp > 0 ? 4 * TRANSPOSE_LDS : 0;
     trace_before(KID_GROUP_TABLE, stream);
-    hipLaunchKernelGGL(group_prep_kernel, dim3(blocks + tp), dim3(256), table_lds > tp_lds ? table_lds : tp_lds, stream, a);
+    hipLaunchKernelGGL(group_prep_kernel, dim3(blocks + (tp + 3) / 4), dim3(256), table_lds > tp_lds ? table_lds : tp_lds, stream, a);
     trace_after(KID_GROUP_TABLE, stream);
     return hipGetLastError();
 }
