@@ -130,7 +130,7 @@ Workspace carve(const peqa_layout *L, int32_t T, int32_t op, int cus)
     if (grouped(L)) {
         w.rt_dx = w.rt_dx_alone;
         const long long dw_tiles = (long long)(K / 128) * ((N + 255) / 256);
-        w.one_launch = peqa::bwd_one_launch((long long)tiles_t * dx.tiles_c + dw_tiles, cus);
+        w.one_launch = peqa::bwd_one_launch((long long)tiles_t * dx.tiles_c + dw_tiles, T, cus);
         if (w.one_launch) {
             peqa::SplitJob beside = dx;
             const int rt = peqa::gemm_plan(1, &beside, T, true, false, false, dw_tiles * peqa::dw_tile_us(T), ~(size_t)0, cus);

@@ -118,7 +118,7 @@ BlockSpace carve_block(int32_t n, const peqa_block_item *items, int32_t T, int32
             dw_tiles += (long long)(L->k_in / 128) * ((L->n_out + 255) / 256);
         }
         w.rt_dx_alone = take(0.0, w.split_dx_alone);
-        w.one_launch = peqa::bwd_one_launch(dx_tiles + dw_tiles, cus);
+        w.one_launch = peqa::bwd_one_launch(dx_tiles + dw_tiles, T, cus);
         int rt = w.rt_dx_alone;
         if (w.one_launch) {
             rt = take(dw_tiles * peqa::dw_tile_us(T), split);

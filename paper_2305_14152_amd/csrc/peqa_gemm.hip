@@ -375,12 +375,16 @@ hipError_t launch_gemm_multi(int bits, bool grouped, MultiArgs &m, hipStream_t s
     return e;
 }
 
-// Eight tiles per unit: with more of them the launches are long enough for their starts and ends not to count.  (They still count
-// wherever measured, up to 66 per unit: backward of blocks, us, one launch for dX and the token contractions against one each, 702 +
-// 2079 tiles 432 / 500, 595 + 5231 tiles 551 / 612, 1308 + 7961 tiles 1415 / 1466.  The bound has not been moved yet.)
-bool bwd_one_launch(long long tiles, int cus)
+// One launch has one start and one end where two have two; it wants the copies made beforehand, where launches of their own hide part
+// of them behind dX.  So up to eight tiles per unit, or 1536 tokens: what the copies take grows with the tokens, and an end
+// is as long as a tile.  Training steps, us, one launch each -> one for both: block of d = 4096, 4 bits, g128, T = 300 497 -> 485,
+// d = 5120, 3 bits, T = 1000 1772 -> 1749, d = 3072, g64, T = 1500 1011 -> 986, 22016 x 8192, T = 1024 1016 -> 997; at
+// T = 2048 and more from 1.00 to 1.01, and 2048 x 12288, T = 3500 (2112 tiles) 525 -> 538.
+constexpr int kOneLaunchTokens = 1536;
+bool bwd_one_launch(long long tiles, int T, int cus)
 {
-    return options().gemm_waves == 0 && options().bwd_pair < 0 && options().grouped_dds == 0 && tiles <= 8ll * cus;
+    return options().gemm_waves == 0 && options().bwd_pair < 0 && options().grouped_dds == 0 &&
+           (tiles <= 8ll * cus || T <= kOneLaunchTokens);
 }
 
 // dX that gemm_plan leaves whole beside the token contractions, of tiles (counted as of gemm_row_tiles rows, whatever it takes) on no
