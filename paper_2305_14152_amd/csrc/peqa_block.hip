@@ -419,7 +419,7 @@ peqa_status peqa_block_bwd(int32_t n, const peqa_block_item *items, int32_t T, v
         if (it.dX) {
             peqa::ScaleDyJob &sd = ma.sdy[ma.n_sdy++];
             sd.dY = it.dY; sd.s0 = it.s0; sd.ds = it.ds; sd.z0 = it.z0; sd.dYs = dys; sd.crow = crow; sd.T = T; sd.N = N;
-            sdy_blocks += (T + peqa::SDY_ROWS_HOST - 1) / peqa::SDY_ROWS_HOST;
+            sdy_blocks += (T + peqa::AUX_SDY_ROWS - 1) / peqa::AUX_SDY_ROWS;
             sd.blk_end = sdy_blocks;
             peqa::MultiJob &job = mb.job[mb.n_jobs++];
             job.mode = peqa::MODE_DX;
@@ -432,7 +432,7 @@ peqa_status peqa_block_bwd(int32_t n, const peqa_block_item *items, int32_t T, v
     }
     if (ma.n_jobs > 0 || ma.n_sdy > 0) {
         sort_jobs(ma);
-        place_aux(ma, 128);
+        place_aux(ma, 64);
         st = launch_multi(bits, false, ma, s);
         if (st != PEQA_OK) return st;
     }

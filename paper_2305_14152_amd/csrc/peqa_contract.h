@@ -59,9 +59,8 @@ __global__ __launch_bounds__(256, 2) void gemm_bwd_pair_kernel(GemmArgs a_dds, G
 }
 
 // Bandwidth-bound side work inside a multi-contraction launch: auxiliary workgroup `w` of `m.aux_wgs` walks the
-// units w, w + aux_wgs, ... of one index space: first the SDY_ROWS-row blocks of the scale_dy jobs, then the
+// units w, w + aux_wgs, ... of one index space: first the AUX_SDY_ROWS-row blocks of the scale_dy jobs, then the
 // 256-element chunks of the reduce jobs; before them its waves walk the 64 x 64 tiles of the transpose jobs.
-static_assert(SDY_ROWS == SDY_ROWS_HOST, "row blocks of scale_dy_rows");
 __device__ __forceinline__ void multi_aux(int n_sdy, int n_red, int n_tp, int aux_wgs, int w, uint8_t *lds)
 {
     struct { int n_sdy, n_red, n_tp, aux_wgs; } m{n_sdy, n_red, n_tp, aux_wgs};
@@ -120,7 +119,7 @@ __device__ __forceinline__ void multi_aux(int n_sdy, int n_red, int n_tp, int au
                 if (u >= e) { j = i + 1; b0 = e; }
             }
             const ScaleDyJob J = kernarg_load<ScaleDyJob>(SDY0 + (uint32_t)(j * sizeof(ScaleDyJob)));
-            scale_dy_rows(J.dY, J.s0, J.ds, J.z0, nullptr, J.T, J.N, J.dYs, J.crow, u - b0, red);
+            scale_dy_rows<AUX_SDY_ROWS>(J.dY, J.s0, J.ds, J.z0, nullptr, J.T, J.N, J.dYs, J.crow, u - b0, red);
             __syncthreads();                                   // `red` is reused by the next block
         } else {
             const int c = u - n_blk;

@@ -123,7 +123,7 @@ struct MultiJob {
     int mode;                 // MODE_Y, MODE_DDS or MODE_DX
     int wg_end;               // tile workgroups of this job and all before it (unused entries: the total)
 };
-constexpr int SDY_ROWS_HOST = 4;      // token rows per row block of scale_dy_rows (checked against the device constant)
+constexpr int AUX_SDY_ROWS = 8;       // token rows per row block of the scaling in auxiliary workgroups
 struct ScaleDyJob {           // dYs = bf16(dY (s0 + ds)), crow[t] = sum_i dYs[t,i] (16 + z0[i])   (scale_dy_rows)
     const uint16_t *dY;
     const float *s0, *ds;
@@ -131,7 +131,7 @@ struct ScaleDyJob {           // dYs = bf16(dY (s0 + ds)), crow[t] = sum_i dYs[t
     uint16_t *dYs;
     float *crow;
     int T, N;
-    int blk_end;              // row blocks (of SDY_ROWS rows) of this job and all before it
+    int blk_end;              // row blocks (of AUX_SDY_ROWS rows) of this job and all before it
 };
 struct ReduceJob {            // out[j] = sum over ntiles of partial[tile][j], fixed order
     const float *partial;

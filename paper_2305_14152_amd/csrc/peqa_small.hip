@@ -233,6 +233,7 @@ __global__ __launch_bounds__(256) void group_table_multi_entry_kernel(GroupTable
 // independent jobs of the same backward: the row sums of X for the scale gradient that follows (rs = NULL: none), or the
 // fixed-order sum of the scale-gradient partials (n_red = 0: none).  A launch saved is 3 us of host time and 1 to 3 us
 // of the GPU's: a 256 x 256 layer's step at T = 64, all of it launches, went from 36.2 to 31.6 us with the row sums here.
+constexpr int SDY_ROWS = 4;
 __global__ __launch_bounds__(256) void scale_dy_kernel(const uint16_t *__restrict__ dY, const float *__restrict__ s0,
                                                         const float *__restrict__ ds, const uint8_t *__restrict__ z0,
                                                         const float *__restrict__ dz, int T, int N,
@@ -249,7 +250,7 @@ __global__ __launch_bounds__(256) void scale_dy_kernel(const uint16_t *__restric
         else reduce_partials_at(partial, ntiles, n_red, (size_t)(past - sum_blocks) * 256 + threadIdx.x, red_out);
         return;
     }
-    scale_dy_rows(dY, s0, ds, z0, dz, T, N, dYs, crow, (int)blockIdx.x, red);
+    scale_dy_rows<SDY_ROWS>(dY, s0, ds, z0, dz, T, N, dYs, crow, (int)blockIdx.x, red);
 }
 
 // Scale gradient from the product P[t,i] = sum_k X[t,k] (Q[i,k] - z0[i]) that the forward kept:
