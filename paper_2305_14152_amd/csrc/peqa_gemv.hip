@@ -407,19 +407,42 @@ __global__ __launch_bounds__(WAVES * 64, GV_SIMD_WAVES) void gemv_kernel(GemvArg
     gemv_tile<BITS, H, WAVES, NX, ZBYTE>(a, L, bx, wg0, stage);
 }
 
-// Y[t,n] = bf16( partial[0][t,n] + partial[1][t,n] + ... ), fixed order, for every sliced layer of the launch
-// (blockIdx.y = layer; layers with a single slice wrote their Y themselves).
-__global__ __launch_bounds__(256) void gemv_finish_kernel(GemvArgs a)
+// Y[t,n] = bf16( partial[0][t,n] + partial[1][t,n] + ... ), fixed order, for the sliced layers of a launch, two neighbouring
+// channels a thread.  Bound by its chain of memory latencies (arguments, partials, store): a short argument block, no division, and
+// the slices asked for eight at a time, all before the first is added.
+struct GemvSums {
+    struct Layer {
+        const float *partial;               // [S, tn]
+        uint16_t *Y;
+        uint32_t tn;                        // T N
+        int S;
+    } layer[GEMV_MAX_LAYERS];
+    int block_end[GEMV_MAX_LAYERS];         // workgroups of layer j and all before it (unused entries: the total)
+};
+__global__ __launch_bounds__(256) void gemv_finish_kernel(GemvSums a)
 {
-    const GemvLayer L = kernarg_load<GemvLayer>((uint32_t)(blockIdx.y * sizeof(GemvLayer)));
-    if (L.S == 1) return;
-    // T <= 16 and at most 2^24 channels: everything fits 32-bit arithmetic
-    const uint32_t tn = (uint32_t)a.T * (uint32_t)L.N;
-    const uint32_t e = blockIdx.x * 256u + threadIdx.x;
-    if (e >= tn) return;
-    float v = 0.f;
-    for (int sl = 0; sl < L.S; ++sl) v += L.partial[(size_t)sl * tn + e];
-    L.Y[e] = (uint16_t)float_to_bf16_bits(v);
+    int j = 0, b0 = 0;
+#pragma unroll
+    for (int i = 0; i < GEMV_MAX_LAYERS - 1; ++i) {
+        const int e = a.block_end[i];
+        if ((int)blockIdx.x >= e) { j = i + 1; b0 = e; }
+    }
+    const GemvSums::Layer L = kernarg_load<GemvSums::Layer>((uint32_t)(j * sizeof(GemvSums::Layer)));
+    const uint32_t e = 2u * ((blockIdx.x - (uint32_t)b0) * 256u + threadIdx.x);
+    if (e >= L.tn) return;                                        // (tn is even: N % 128 == 0)
+    f32x2 v = {0.f, 0.f};
+    for (int s0 = 0; s0 < L.S; s0 += 8) {
+        f32x2 p[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {                             // past the last slice: the last one again, not added
+            const int sl = s0 + u < L.S ? s0 + u : L.S - 1;
+            p[u] = *reinterpret_cast<const f32x2 *>(L.partial + (size_t)sl * L.tn + e);
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (s0 + u < L.S) v += p[u];
+    }
+    *reinterpret_cast<uint32_t *>(L.Y + e) = pack_bf16x2(v[0], v[1]);
 }
 
 }  // namespace
@@ -577,7 +600,6 @@ hipError_t launch_gemv(int bits, const GemvForm &f, const GemvArgs &a_in, hipStr
 {
     GemvArgs a = a_in;
     bool sliced = false, zbyte = true;
-    unsigned max_tn = 0;
     const int nx = a.T > 8 ? 2 : 1;
     int lds = 0, groups[GEMV_MAX_LAYERS];
     for (int j = 0; j < a.n_layers; ++j) {
@@ -585,7 +607,6 @@ hipError_t launch_gemv(int bits, const GemvForm &f, const GemvArgs &a_in, hipStr
         if (l.N % 128 != 0 || l.K % 128 != 0 || l.chunk % 64 != 0 || l.S < 1 || a.T < 1 || a.T > 16) return hipErrorInvalidValue;
         sliced = sliced || l.S > 1;
         zbyte = zbyte && l.dz == nullptr;
-        if (l.S > 1 && (unsigned)a.T * (unsigned)l.N > max_tn) max_tn = (unsigned)a.T * (unsigned)l.N;
         l.chunk_rounds = l.chunk / 64;
         l.slice_rounds = l.K / 64 / l.S;
         l.slice_rem = l.K / 64 % l.S;
@@ -671,8 +692,22 @@ hipError_t launch_gemv(int bits, const GemvForm &f, const GemvArgs &a_in, hipStr
     if (bits == 4) e = nx == 2 ? on_form(four, two) : on_form(four, one);
     else e = nx == 2 ? on_form(three, two) : on_form(three, one);
     if (e != hipSuccess || !sliced) return e;
+    GemvSums sums{};
+    int n = 0, blocks = 0;
+    for (int j = 0; j < a.n_layers; ++j) {
+        const GemvLayer &l = a.layer[j];
+        if (l.S == 1) continue;
+        const uint32_t tn = (uint32_t)a.T * (uint32_t)l.N;        // T <= 16 and at most 2^24 channels: 32-bit arithmetic
+        sums.layer[n] = GemvSums::Layer{l.partial, l.Y, tn, l.S};
+        blocks += (int)((tn + 511) / 512);
+        sums.block_end[n++] = blocks;
+    }
+    for (; n < GEMV_MAX_LAYERS; ++n) {
+        sums.layer[n] = sums.layer[n - 1];
+        sums.block_end[n] = blocks;
+    }
     trace_before(KID_GEMV_FINISH, stream);
-    hipLaunchKernelGGL(gemv_finish_kernel, dim3((max_tn + 255) / 256, a.n_layers), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL(gemv_finish_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, sums);
     trace_after(KID_GEMV_FINISH, stream);
     return hipGetLastError();
 }
