@@ -45,20 +45,26 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
 
 // A pair of fp16 (16 + code), scaled and shifted in fp32 and rounded once (to nearest even) to a bf16 pair:
 // lo -> s_lo * lo + b_lo,  hi -> s_hi * hi + b_hi: two mixed-precision fused multiply-adds that take a half of the register
-// as it stands (as bf16 the halves have to be moved into place first: two instructions more), and a conversion.  The
-// conversion is volatile assembly so that it stays where the caller put it among its matrix instructions: those are
+// as it stands (as bf16 the halves have to be moved into place first: two instructions more), and a conversion.  All of it is
+// volatile assembly, so that every instruction stays where the caller put it among its matrix instructions: those are
 // assembly too, and the wait states that the hardware wants between a vector write and a matrix read of the same register
 // are the distance the caller keeps (the compiler, free to move the conversion, put it right before its use, and the matrix
-// instruction read the old value).
+// instruction read the old value).  In two parts, for other instructions in between.
 typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t scale_pair(uint32_t pair, float s_lo, float b_lo, float s_hi, float b_hi)
+struct ScaledPair {
+    float lo, hi;
+};
+__device__ __forceinline__ ScaledPair scale_pair(uint32_t pair, float s_lo, float b_lo, float s_hi, float b_hi)
 {
-    const f16x2 h = __builtin_bit_cast(f16x2, pair);
-    const float lo = __builtin_fmaf((float)h[0], s_lo, b_lo);
-    const float hi = __builtin_fmaf((float)h[1], s_hi, b_hi);
+    ScaledPair p;
+    asm volatile("v_fma_mix_f32 %0, %1, %2, %3 op_sel_hi:[1,0,0]" : "=v"(p.lo) : "v"(pair), "v"(s_lo), "v"(b_lo));
+    asm volatile("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(p.hi) : "v"(pair), "v"(s_hi), "v"(b_hi));
+    return p;
+}
+__device__ __forceinline__ uint32_t round_pair(const ScaledPair &p)
+{
     uint32_t d;
-    asm volatile("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(d) : "v"(lo), "v"(hi));
+    asm volatile("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(d) : "v"(p.lo), "v"(p.hi));
     return d;
 }
 

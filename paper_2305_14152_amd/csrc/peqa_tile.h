@@ -44,14 +44,16 @@ constexpr int stage_bytes(int kw, int rt) { return kw * (a_half_bytes(rt) + 4 * 
 constexpr int ring_bytes(int kw, int rt) { return NSTAGE * stage_bytes(kw, rt); }
 constexpr int tbl_bytes(int kw) { return kw * 4 * 2 * 1024; }           // group-wise MODE_Y / MODE_DX: 2 x 1 KB of (s, b) per wave
 
-// The MFMA of a step (0 .. 4 rt - 1) after which weight-fragment register r (0..15) of the next step is built: spread over the
-// last seven eighths of them.
-constexpr int frag_reg_slot(int r, int rt) { return rt / 2 + ((4 * rt - 1 - rt / 2) * r) / 15; }
-// The first register of slot m or a later one.
-constexpr int frag_reg_from(int m, int rt)
+// The MFMA of a step (0 .. 4 rt - 1) after which turn r (0 .. turns - 1) of building the next step's weight fragments comes: spread
+// over the last seven eighths of them.  A register is built in one turn, or, where it is scaled, in three (SCALE_TURNS).
+constexpr int SCALE_TURNS = 3;
+constexpr int frag_turns(bool scaled) { return scaled ? 16 + SCALE_TURNS - 1 : 16; }
+constexpr int frag_turn_slot(int r, int rt, int turns) { return rt / 2 + ((4 * rt - 1 - rt / 2) * r) / (turns - 1); }
+// The first turn of slot m or a later one.
+constexpr int frag_turn_from(int m, int rt, int turns)
 {
     int r = 0;
-    while (r < 16 && frag_reg_slot(r, rt) < m) ++r;
+    while (r < turns && frag_turn_slot(r, rt, turns) < m) ++r;
     return r;
 }
 
@@ -286,14 +288,28 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
         const f32x4 v = *reinterpret_cast<const f32x4 *>(tbl_lane + ((m >> 2) & 1) * 1024 + (m & 3) * 256 + 16 * J);
         sc[2 * J] = v[0]; bo[2 * J] = v[1]; sc[2 * J + 1] = v[2]; bo[2 * J + 1] = v[3];
     };
-    // register r (0..15, in the order in which they are built) of the next step's fragments: register J of fragment I
+    // Register r (0..15, in the order in which they are built) of the next step's fragments is register J of fragment I.  Scaled, it
+    // takes three turns, which do not wait for each other: in turn t register t is unpacked, t - 1 scaled and t - 2 rounded.  (One
+    // after the other, each register's five instructions were a chain that a wave waited for between two matrix instructions, with a wait
+    // state of the compiler's own before either use of what assembly had written.)
     constexpr bool J_MAJOR = SCALED && ALONG_CH;
-    auto next_frag_reg = [&](const Unpacker &up, auto i_c, auto j_c) __attribute__((always_inline)) -> uint32_t {
-        constexpr int I = decltype(i_c)::value, J = decltype(j_c)::value;
-        const uint32_t pr = up.template frag_reg<I, J>(magic);
-        if constexpr (!SCALED) return pr;
-        else if constexpr (ALONG_CH) return scale_pair(pr, sc[2 * J], bo[2 * J], sc[2 * J + 1], bo[2 * J + 1]);
-        else return scale_pair(pr, sc[I], bo[I], sc[I], bo[I]);
+    constexpr int TURNS = frag_turns(SCALED);
+    auto reg_i = [](int r) constexpr { return J_MAJOR ? r & 3 : r >> 2; };
+    auto reg_j = [](int r) constexpr { return J_MAJOR ? r >> 2 : r & 3; };
+    uint32_t unpacked = 0;
+    ScaledPair scaled = {0.f, 0.f};
+    auto frag_turn = [&](const Unpacker &up, auto t_c, u32x4 *frag) __attribute__((always_inline)) {
+        constexpr int t = decltype(t_c)::value;
+        if constexpr (!SCALED) {
+            frag[reg_i(t)][reg_j(t)] = up.template frag_reg<reg_i(t), reg_j(t)>(magic);
+        } else {
+            if constexpr (t >= 2) frag[reg_i(t - 2)][reg_j(t - 2)] = round_pair(scaled);
+            if constexpr (t >= 1 && t <= 16) {
+                constexpr int I = reg_i(t - 1), J = reg_j(t - 1), lo = ALONG_CH ? 2 * J : I, hi = ALONG_CH ? 2 * J + 1 : I;
+                scaled = scale_pair(unpacked, sc[lo], bo[lo], sc[hi], bo[hi]);
+            }
+            if constexpr (t < 16) unpacked = up.template frag_reg<reg_i(t), reg_j(t)>(magic);
+        }
     };
 
     f32x4 acc[RT][4];
@@ -386,9 +402,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
         }
         Unpacker up;
         up.prepare(bw[1], perm_sel);
-        static_for<4>([&](auto i) {
-            static_for<4>([&](auto j) { bfrag[0][i.value][j.value] = next_frag_reg(up, i, j); });
-        });
+        static_for<TURNS>([&](auto t) { frag_turn(up, t, bfrag[0]); });
     }
     // (Step 0 refills the packed-weight slot of stage 0, which its own wave alone reads and has read; its activation tiles go to
     // stage NSTAGE - 1.  No barrier is needed before it.)
@@ -440,11 +454,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
             static_for<4>([&](auto ct_c) {
                 constexpr int ct = ct_c.value, m = 4 * rt + ct;
                 mfma16_acc(acc[rt][ct], afrag[rt], bfrag[CUR][ct]);
-                constexpr int r0 = frag_reg_from(m, RT), r1 = frag_reg_from(m + 1, RT);
+                constexpr int r0 = frag_turn_from(m, RT, TURNS), r1 = frag_turn_from(m + 1, RT, TURNS);
                 static_for<r1 - r0>([&](auto r_c) {
-                    constexpr int r = r0 + r_c.value, I = J_MAJOR ? r & 3 : r >> 2, J = J_MAJOR ? r >> 2 : r & 3;
-                    bfrag[NXT][I][J] = next_frag_reg(up, std::integral_constant<int, I>{}, std::integral_constant<int, J>{});
-                    if constexpr (J_MAJOR && I == 3 && J < 2) read_table_pair(m0 + it + 1, J + 2);
+                    constexpr int r = r0 + r_c.value;
+                    frag_turn(up, std::integral_constant<int, r>{}, bfrag[NXT]);
+                    if constexpr (J_MAJOR && r < 8 && reg_i(r) == 3) read_table_pair(m0 + it + 1, reg_j(r) + 2);
                 });
                 if constexpr (ROW_SUMS && rt < 2) rsum[rt] = add_pair(afrag[rt][ct], rsum[rt]);
                 if constexpr (m == 2) read_b(std::integral_constant<int, NNS>{}, bw[NXT]);
