@@ -27,21 +27,18 @@ constexpr uint32_t kMagicF16 = 0x4C004C00u;
 constexpr int kFieldBf16 = 3, kFieldF16 = 6;
 constexpr uint32_t field_mask(int bits, int at) { return ((1u << bits) - 1u) * 0x00010001u << at; }
 
-__device__ __forceinline__ float bf16_bits_to_float(uint32_t h) { return __uint_as_float(h << 16); }
 __device__ __forceinline__ float bf16_lo(uint32_t pair) { return __uint_as_float(pair << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t pair) { return __uint_as_float(pair & 0xFFFF0000u); }
 
-// fp32 -> bf16 bits, round to nearest even (finite inputs).
-__device__ __forceinline__ uint32_t float_to_bf16_bits(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return u >> 16;
-}
+// Two fp32 -> bf16 bits, round to nearest even: one instruction (from integer operations, as before, seven; the epilogue of a
+// 128 x 256 tile rounds 128 numbers a lane).
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
 {
-    return float_to_bf16_bits(lo) | (float_to_bf16_bits(hi) << 16);
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{lo, hi}), bf16x2));
 }
+__device__ __forceinline__ uint32_t float_to_bf16_bits(float f) { return pack_bf16x2(f, 0.f) & 0xFFFFu; }
 
 // A pair of fp16 (16 + code), scaled and shifted in fp32 and rounded once (to nearest even) to a bf16 pair:
 // lo -> s_lo * lo + b_lo,  hi -> s_hi * hi + b_hi: two mixed-precision fused multiply-adds that take a half of the register
@@ -50,7 +47,6 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
 // assembly too, and the wait states that the hardware wants between a vector write and a matrix read of the same register
 // are the distance the caller keeps (the compiler, free to move the conversion, put it right before its use, and the matrix
 // instruction read the old value).  In two parts, for other instructions in between.
-typedef float f32x2 __attribute__((ext_vector_type(2)));
 struct ScaledPair {
     float lo, hi;
 };
@@ -69,7 +65,6 @@ __device__ __forceinline__ uint32_t round_pair(const ScaledPair &p)
 }
 
 // c + a.lo + a.hi of a bf16 pair, in fp32 (one dot instruction against ones).
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ float add_pair(uint32_t a, float c)
 {
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a), __builtin_bit_cast(bf16x2, 0x3F803F80u), c, false);
@@ -229,10 +224,8 @@ __device__ __forceinline__ void scale_dy_rows(const uint16_t *__restrict__ dY, c
             u32x4 o;
 #pragma unroll
             for (int p = 0; p < 4; ++p) {
-                const uint32_t lo = float_to_bf16_bits(bf16_lo(k.v[r][p]) * s[2 * p]);
-                const uint32_t hi = float_to_bf16_bits(bf16_hi(k.v[r][p]) * s[2 * p + 1]);
-                o[p] = lo | (hi << 16);
-                acc[r] += bf16_bits_to_float(lo) * zo[2 * p] + bf16_bits_to_float(hi) * zo[2 * p + 1];
+                o[p] = pack_bf16x2(bf16_lo(k.v[r][p]) * s[2 * p], bf16_hi(k.v[r][p]) * s[2 * p + 1]);
+                acc[r] += bf16_lo(o[p]) * zo[2 * p] + bf16_hi(o[p]) * zo[2 * p + 1];
             }
             if (r < rows) reinterpret_cast<u32x4 *>(dYs + (size_t)(t0 + r) * N)[n8] = o;
         }
