@@ -114,35 +114,40 @@ __device__ __forceinline__ void group_table_entry(const float *__restrict__ s0, 
     o[1] = -s * zoff;
 }
 
-__global__ __launch_bounds__(256) void group_table_kernel(const float *__restrict__ s0, const float *__restrict__ ds,
-                                                           const uint8_t *__restrict__ z0, const float *__restrict__ dz,
-                                                           int N, int G, float *__restrict__ sb)
-{
-    const size_t j = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (j >= (size_t)N * G) return;
-    group_table_entry(s0, ds, z0, dz, N, G, sb, j);
-}
-
 // The same table by workgroups of GT_CH channels x all groups, through LDS: memory has a channel's groups next to each
 // other and the table a group's channels, so entry by entry every 8-byte write is a transaction of its own (25 us for
-// the four tables of a 13B block); here the reads run along the groups and the writes along the channels, 128 bytes
-// per group.  `lds`: 2 x GT_CH x G floats.
+// the four tables of a 13B block); here the reads run along the groups, four entries a thread, and the writes along the channels,
+// 128 bytes per group.  `lds`: 2 x GT_CH x (G | 1) floats: with rows of an odd length a group's channels are in different banks.
+// Bound by the latency of the one load and the one store of a workgroup, and by the workgroups that a launch hands out: with an
+// entry at a time, and a grid as long as the largest layer for every layer (half of its workgroups had nothing to do), the four
+// tables of a 13B block took 17 us.
 constexpr int GT_CH = 16;
+constexpr int gt_tile_bytes(int G) { return 2 * GT_CH * (G | 1) * (int)sizeof(float); }
 __device__ __forceinline__ void group_table_tile(const float *__restrict__ s0, const float *__restrict__ ds,
                                                  const uint8_t *__restrict__ z0, const float *__restrict__ dz, int N, int G,
                                                  float *__restrict__ sb, int n0, float *lds)
 {
-    float *s_l = lds, *z_l = lds + GT_CH * G;
-    const size_t base = (size_t)n0 * G;
-    for (int e = threadIdx.x; e < GT_CH * G; e += 256) {
-        const size_t j = base + e;
-        s_l[e] = ds ? s0[j] + ds[j] : s0[j];
-        z_l[e] = kCodeOffset + (float)z0[j] + (dz ? dz[j] : 0.f);
+    const int row = G | 1;
+    float *s_l = lds, *z_l = lds + GT_CH * row;
+    const size_t base = (size_t)n0 * G;                    // a multiple of GT_CH: the quads are aligned for any G
+    for (int e = 4 * threadIdx.x; e < GT_CH * G; e += 4 * 256) {
+        f32x4 s = *reinterpret_cast<const f32x4 *>(s0 + base + e);
+        const uint32_t z = *reinterpret_cast<const uint32_t *>(z0 + base + e);
+        if (ds) s += *reinterpret_cast<const f32x4 *>(ds + base + e);
+        f32x4 d = {0.f, 0.f, 0.f, 0.f};
+        if (dz) d = *reinterpret_cast<const f32x4 *>(dz + base + e);
+        int nl = e / G, g = e - nl * G;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            s_l[nl * row + g] = s[u];
+            z_l[nl * row + g] = kCodeOffset + (float)((z >> (8 * u)) & 0xFFu) + d[u];
+            if (++g == G) { g = 0; ++nl; }
+        }
     }
     __syncthreads();
     const int nl = threadIdx.x % GT_CH, n = n0 + nl;
     for (int g = threadIdx.x / GT_CH; g < G; g += 256 / GT_CH) {
-        const float s = s_l[nl * G + g], zoff = z_l[nl * G + g];
+        const float s = s_l[nl * row + g], zoff = z_l[nl * row + g];
         f32x2 o;
         o[0] = s;
         o[1] = -s * zoff;
@@ -150,15 +155,7 @@ __device__ __forceinline__ void group_table_tile(const float *__restrict__ s0, c
     }
 }
 
-__global__ __launch_bounds__(256) void group_table_tile_kernel(const float *__restrict__ s0, const float *__restrict__ ds,
-                                                                const uint8_t *__restrict__ z0, const float *__restrict__ dz,
-                                                                int N, int G, float *__restrict__ sb)
-{
-    extern __shared__ __align__(16) float gt_lds[];
-    group_table_tile(s0, ds, z0, dz, N, G, sb, (int)blockIdx.x * GT_CH, gt_lds);
-}
-
-// Tables and transposed copies of a group-wise backward (GroupPrep): the tables' workgroups first, then one per four 64 x 64 tiles of
+// Tables of group-wise layers and, for a backward, transposed copies (GroupPrep): the tables' workgroups first, then one per four 64 x 64 tiles of
 // the copies.  One launch where there were two, of 3 us and more each.
 __global__ __launch_bounds__(256) void group_prep_kernel(GroupPrep a)
 {
@@ -194,39 +191,6 @@ __global__ __launch_bounds__(256) void group_prep_kernel(GroupPrep a)
     const TransposeJob J = kernarg_load<TransposeJob>((uint32_t)(offsetof(GroupPrep, tp) + j * sizeof(TransposeJob)));
     const int bcs = J.C >> 6;
     transpose_pad_tile(J.src, J.T, J.C, J.dst, (b - b0) / bcs, (b - b0) % bcs, reinterpret_cast<u32x4 *>(gt_lds) + wave * (TRANSPOSE_LDS / 16));
-}
-
-// group_table_tile_kernel for several layers: blockIdx.y = layer.
-__global__ __launch_bounds__(256) void group_table_multi_kernel(GroupTableMulti a)
-{
-    extern __shared__ __align__(16) float gt_lds[];
-    const int y = blockIdx.y;
-    const float *s0 = a.s0[0], *ds = a.ds[0];
-    const uint8_t *z0 = a.z0[0];
-    float *sb = a.sb[0];
-    int N = a.N[0], G = a.G[0];
-#pragma unroll
-    for (int i = 1; i < GT_MAX; ++i)
-        if (y == i) { s0 = a.s0[i]; ds = a.ds[i]; z0 = a.z0[i]; sb = a.sb[i]; N = a.N[i]; G = a.G[i]; }
-    const int n0 = (int)blockIdx.x * GT_CH;
-    if (n0 >= N) return;                                   // uniform per workgroup
-    group_table_tile(s0, ds, z0, nullptr, N, G, sb, n0, gt_lds);
-}
-
-// the same entry by entry, for rows of more groups than the tile form's LDS holds
-__global__ __launch_bounds__(256) void group_table_multi_entry_kernel(GroupTableMulti a)
-{
-    const int y = blockIdx.y;
-    const float *s0 = a.s0[0], *ds = a.ds[0];
-    const uint8_t *z0 = a.z0[0];
-    float *sb = a.sb[0];
-    int N = a.N[0], G = a.G[0];
-#pragma unroll
-    for (int i = 1; i < GT_MAX; ++i)
-        if (y == i) { s0 = a.s0[i]; ds = a.ds[i]; z0 = a.z0[i]; sb = a.sb[i]; N = a.N[i]; G = a.G[i]; }
-    const size_t j = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (j >= (size_t)N * G) return;
-    group_table_entry(s0, ds, z0, nullptr, N, G, sb, j);
 }
 
 // scale_dy_rows (peqa_device.h) for every block of SDY_ROWS token rows.  Workgroups past the last row block do
@@ -475,22 +439,17 @@ hipError_t launch_rowsum_groups(const uint16_t *X, int T, int K, int gsz, float 
     return hipGetLastError();
 }
 
-// most groups per channel the tile form takes (48 KB of LDS)
-constexpr int GT_TILE_MAX_G = 48 * 1024 / (2 * GT_CH * (int)sizeof(float));
+// LDS that the tile form takes at most
+constexpr int GT_TILE_MAX_LDS = 49 * 1024;   // 391 groups
 
 hipError_t launch_group_table(const float *s0, const float *ds, const uint8_t *z0, const float *dz, int N, int G,
                               float *sb, hipStream_t stream)
 {
-    trace_before(KID_GROUP_TABLE, stream);
-    if (G <= GT_TILE_MAX_G) {
-        hipLaunchKernelGGL(group_table_tile_kernel, dim3(N / GT_CH), dim3(256), 2 * GT_CH * G * sizeof(float), stream, s0, ds, z0,
-                           dz, N, G, sb);
-    } else {
-        const size_t n = (size_t)N * G;
-        hipLaunchKernelGGL(group_table_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, s0, ds, z0, dz, N, G, sb);
-    }
-    trace_after(KID_GROUP_TABLE, stream);
-    return hipGetLastError();
+    GroupPrep a{};
+    a.table.s0[0] = s0; a.table.ds[0] = ds; a.table.z0[0] = z0; a.table.sb[0] = sb; a.table.N[0] = N; a.table.G[0] = G;
+    a.table.n = 1;
+    a.dz = dz;
+    return launch_group_prep(a, stream);
 }
 
 hipError_t launch_group_prep(GroupPrep &a, hipStream_t stream)
@@ -499,37 +458,25 @@ hipError_t launch_group_prep(GroupPrep &a, hipStream_t stream)
     if (n < 0 || n > GT_MAX || a.n_tp < 0 || a.n_tp > 2 * MULTI_MAX_JOBS || (a.dz && n != 1)) return hipErrorInvalidValue;
     int gmax = 0, blocks = 0;
     for (int i = 0; i < n; ++i) gmax = a.table.G[i] > gmax ? a.table.G[i] : gmax;
-    a.by_tiles = gmax <= GT_TILE_MAX_G;
+    a.by_tiles = gt_tile_bytes(gmax) <= GT_TILE_MAX_LDS;
     for (int i = 0; i < GT_MAX; ++i) {
         if (i < n) blocks += a.by_tiles ? a.table.N[i] / GT_CH : (int)(((size_t)a.table.N[i] * a.table.G[i] + 255) / 256);
         a.table_end[i] = blocks;
     }
     const int tp = a.n_tp > 0 ? a.tp[a.n_tp - 1].tile_end : 0;
     if (blocks + tp == 0) return hipSuccess;
-    const int table_lds = a.by_tiles ? 2 * GT_CH * gmax * (int)sizeof(float) : 0, tp_lds = tp > 0 ? 4 * TRANSPOSE_LDS : 0;
+    const int table_lds = a.by_tiles ? gt_tile_bytes(gmax) : 0, tp_lds = tp > 0 ? 4 * TRANSPOSE_LDS : 0;
     trace_before(KID_GROUP_TABLE, stream);
     hipLaunchKernelGGL(group_prep_kernel, dim3(blocks + (tp + 3) / 4), dim3(256), table_lds > tp_lds ? table_lds : tp_lds, stream, a);
     trace_after(KID_GROUP_TABLE, stream);
     return hipGetLastError();
 }
 
-hipError_t launch_group_table_multi(const GroupTableMulti &a, hipStream_t stream)
+hipError_t launch_group_table_multi(const GroupTableMulti &tables, hipStream_t stream)
 {
-    size_t nmax = 0;
-    int Nmax = 0, Gmax = 0;
-    for (int i = 0; i < a.n; ++i) {
-        const size_t n = (size_t)a.N[i] * a.G[i];
-        nmax = n > nmax ? n : nmax;
-        Nmax = a.N[i] > Nmax ? a.N[i] : Nmax;
-        Gmax = a.G[i] > Gmax ? a.G[i] : Gmax;
-    }
-    trace_before(KID_GROUP_TABLE, stream);
-    if (Gmax <= GT_TILE_MAX_G)
-        hipLaunchKernelGGL(group_table_multi_kernel, dim3(Nmax / GT_CH, a.n), dim3(256), 2 * GT_CH * Gmax * sizeof(float), stream, a);
-    else
-        hipLaunchKernelGGL(group_table_multi_entry_kernel, dim3((unsigned)((nmax + 255) / 256), a.n), dim3(256), 0, stream, a);
-    trace_after(KID_GROUP_TABLE, stream);
-    return hipGetLastError();
+    GroupPrep a{};
+    a.table = tables;
+    return launch_group_prep(a, stream);
 }
 
 hipError_t launch_scale_dy(const uint16_t *dY, const float *s0, const float *ds, const uint8_t *z0, const float *dz,
