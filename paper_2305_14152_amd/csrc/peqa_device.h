@@ -159,6 +159,20 @@ __device__ __forceinline__ float swap_pair_lane(float v)
     return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), 0xB1, 0xF, 0xF, true));
 }
 
+// Loads and stores that are global ones whatever the compiler knows of the pointer.  What comes out of an argument block at a run-time
+// offset is a generic pointer to it and would be used by FLAT instructions, which count as LDS operations too: between two of
+// them, and before the use of what one brings, the compiler waits for every operation in flight, stores included.
+template <class T>
+__device__ __forceinline__ T global_load(const void *p)
+{
+    return *(const __attribute__((address_space(1))) T *)(uintptr_t)p;
+}
+template <class T>
+__device__ __forceinline__ void global_store(void *p, const T &v)
+{
+    *(__attribute__((address_space(1))) T *)(uintptr_t)p = v;
+}
+
 // Per-channel backward, the part of dY the dX contraction reads:  dYs[t,i] = bf16(dY[t,i] (s0 + ds)[i])  and
 // crow[t] = sum_i dYs[t,i] (16 + z0[i] + dz[i])  (from the rounded dYs, so that it cancels the code offset of the
 // contraction exactly), for the ROWS token rows of row block `blk`, by one workgroup of 256 threads
@@ -188,17 +202,17 @@ __device__ __forceinline__ void scale_dy_rows(const uint16_t *__restrict__ dY, c
     auto load = [&](int n8, Columns &k) __attribute__((always_inline)) {
 #pragma unroll
         for (int r = 0; r < ROWS; ++r)
-            k.v[r] = reinterpret_cast<const u32x4 *>(dY + (size_t)(t0 + min(r, rows - 1)) * N)[n8];
-        k.sa = *reinterpret_cast<const f32x4 *>(s0 + 8 * n8);
-        k.sb = *reinterpret_cast<const f32x4 *>(s0 + 8 * n8 + 4);
+            k.v[r] = global_load<u32x4>(dY + (size_t)(t0 + min(r, rows - 1)) * N + 8 * n8);
+        k.sa = global_load<f32x4>(s0 + 8 * n8);
+        k.sb = global_load<f32x4>(s0 + 8 * n8 + 4);
         if (ds) {
-            k.da = *reinterpret_cast<const f32x4 *>(ds + 8 * n8);
-            k.db = *reinterpret_cast<const f32x4 *>(ds + 8 * n8 + 4);
+            k.da = global_load<f32x4>(ds + 8 * n8);
+            k.db = global_load<f32x4>(ds + 8 * n8 + 4);
         }
-        k.zz = *reinterpret_cast<const u32x2 *>(z0 + 8 * n8);
+        k.zz = global_load<u32x2>(z0 + 8 * n8);
         if (dz) {
-            k.za = *reinterpret_cast<const f32x4 *>(dz + 8 * n8);
-            k.zb = *reinterpret_cast<const f32x4 *>(dz + 8 * n8 + 4);
+            k.za = global_load<f32x4>(dz + 8 * n8);
+            k.zb = global_load<f32x4>(dz + 8 * n8 + 4);
         }
     };
     // the next columns (and their parameters: loads arrive in order) are on their way while these are scaled
@@ -227,7 +241,7 @@ __device__ __forceinline__ void scale_dy_rows(const uint16_t *__restrict__ dY, c
                 o[p] = pack_bf16x2(bf16_lo(k.v[r][p]) * s[2 * p], bf16_hi(k.v[r][p]) * s[2 * p + 1]);
                 acc[r] += bf16_lo(o[p]) * zo[2 * p] + bf16_hi(o[p]) * zo[2 * p + 1];
             }
-            if (r < rows) reinterpret_cast<u32x4 *>(dYs + (size_t)(t0 + r) * N)[n8] = o;
+            if (r < rows) global_store(dYs + (size_t)(t0 + r) * N + 8 * n8, o);
         }
     }
 #pragma unroll
@@ -237,7 +251,7 @@ __device__ __forceinline__ void scale_dy_rows(const uint16_t *__restrict__ dY, c
         if ((tid & 63) == 0) red[r * 4 + (tid >> 6)] = acc[r];
     }
     __syncthreads();
-    if (tid < rows) crow[t0 + tid] = (red[tid * 4] + red[tid * 4 + 1]) + (red[tid * 4 + 2] + red[tid * 4 + 3]);
+    if (tid < rows) global_store(crow + t0 + tid, (red[tid * 4] + red[tid * 4 + 1]) + (red[tid * 4 + 2] + red[tid * 4 + 3]));
 }
 
 // partial[0][j] + partial[1][j] + ... in that order (deterministic).
@@ -249,11 +263,11 @@ __device__ __forceinline__ float partials_sum(const float *__restrict__ partial,
     for (; tt + 8 <= ntiles; tt += 8) {
         float p[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) p[u] = partial[(size_t)(tt + u) * n + j];
+        for (int u = 0; u < 8; ++u) p[u] = global_load<float>(partial + (size_t)(tt + u) * n + j);
 #pragma unroll
         for (int u = 0; u < 8; ++u) s += p[u];
     }
-    for (; tt < ntiles; ++tt) s += partial[(size_t)tt * n + j];
+    for (; tt < ntiles; ++tt) s += global_load<float>(partial + (size_t)tt * n + j);
     return s;
 }
 
@@ -261,7 +275,7 @@ __device__ __forceinline__ float partials_sum(const float *__restrict__ partial,
 __device__ __forceinline__ void reduce_partials_at(const float *__restrict__ partial, int ntiles, size_t n, size_t j,
                                                    float *__restrict__ out)
 {
-    if (j < n) out[j] = partials_sum(partial, ntiles, n, j);
+    if (j < n) global_store(out + j, partials_sum(partial, ntiles, n, j));
 }
 
 // The step-major transposed copy that the token contraction of group-wise layers reads:
@@ -283,12 +297,12 @@ __device__ __forceinline__ void transpose_load(const uint16_t *__restrict__ src,
     const uint16_t *from = src + (size_t)bc * 64 + 8 * (lane & 7);
     if (bt * 64 + 64 <= T) {                               // (uniform)
 #pragma unroll
-        for (int j = 0; j < 8; ++j) r.row[j] = *reinterpret_cast<const u32x4 *>(from + (size_t)(t0 + j) * C);
+        for (int j = 0; j < 8; ++j) r.row[j] = global_load<u32x4>(from + (size_t)(t0 + j) * C);
     } else {
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             r.row[j] = u32x4{0u, 0u, 0u, 0u};
-            if (t0 + j < T) r.row[j] = *reinterpret_cast<const u32x4 *>(from + (size_t)(t0 + j) * C);
+            if (t0 + j < T) r.row[j] = global_load<u32x4>(from + (size_t)(t0 + j) * C);
         }
     }
 }
@@ -315,7 +329,7 @@ __device__ __forceinline__ void transpose_store(const TransposeRows &r, int C, u
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const int p = 64 * i + lane, writer = ((p >> 3) & 1) | (((p >> 6) & 3) << 1);
-        *reinterpret_cast<u32x4 *>(to + (i >> 2) * (size_t)C * 32 + (i & 3) * 512) = piece[p ^ writer];
+        global_store(to + (i >> 2) * (size_t)C * 32 + (i & 3) * 512, piece[p ^ writer]);
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();                       // the next tile's pieces overwrite these

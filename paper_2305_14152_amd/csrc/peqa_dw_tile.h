@@ -84,7 +84,7 @@ __device__ __forceinline__ void dw_tile(const DwArgs &a, const int wg, uint8_t *
     // before the use of what a FLAT load brings waits for every memory operation in flight, the ring's DMAs among them
     // (0.51 instead of 0.36 us per step of a tile alone on its unit: the joint launch of 128 x 384, T = 3411, 54 -> 38 us).
     auto load_b = [&](const uint8_t *step_src, int ct) {
-        return *(const __attribute__((address_space(1))) u32x4 *)(step_src + ct * 1024 + lane * 16);
+        return global_load<u32x4>(step_src + ct * 1024 + lane * 16);
     };
     u32x4 bfrag[2][NCT];
 
@@ -203,7 +203,7 @@ __device__ __forceinline__ void dw_tile(const DwArgs &a, const int wg, uint8_t *
 #pragma unroll
         for (int ct = 0; ct < NCT; ++ct) {
             const size_t sg = (size_t)(cb + 16 * ct + c) * a.G + grp;
-            zv[ct] = (float)a.z0[sg] + (a.dz ? a.dz[sg] : 0.f);
+            zv[ct] = (float)global_load<uint8_t>(a.z0 + sg) + (a.dz ? global_load<float>(a.dz + sg) : 0.f);
         }
         static_for<NCT>([&](auto ct_c) {
             constexpr int ct = ct_c.value;
@@ -229,9 +229,9 @@ __device__ __forceinline__ void dw_tile(const DwArgs &a, const int wg, uint8_t *
             const float sum = s1 - zv[ct] * s0;
             if (a.gsz == 128) {                            // (uniform) the tile's two chunks are the group
                 if constexpr (h == 0) below[ct] = sum;
-                else if (q == 0) a.pc[(size_t)i * a.G + grp] = below[ct] + sum;
+                else if (q == 0) global_store(a.pc + (size_t)i * a.G + grp, below[ct] + sum);
             } else if (q == 0) {
-                a.pc[(size_t)i * nchunks + chunk] = sum;
+                global_store(a.pc + (size_t)i * nchunks + chunk, sum);
             }
         });
     });

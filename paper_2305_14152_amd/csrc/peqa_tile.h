@@ -365,6 +365,30 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
     float rsum[2] = {0.f, 0.f};                            // row sums of row tiles 0 and 1 of the registers, this lane's part
     const uint32_t perm_sel = par ? 0x07060302u : 0x05040100u;
 
+    // ---- scale and zero-point of this lane's four columns, for the epilogue: asked for before anything else, as they are (what
+    // comes of them is formed in the epilogue), so that no tile ends with the latency of their loads.
+    constexpr bool EP_SCALE = !SCALED && MODE == MODE_Y, EP_ZERO = !SCALED && !PAIRED && MODE != MODE_DX;
+    f32x4 ep_s0 = {0.f, 0.f, 0.f, 0.f}, ep_ds = ep_s0, ep_dz = ep_s0;
+    uint32_t ep_z0[4] = {0u, 0u, 0u, 0u};                  // MODE_Y: one word of four
+    if (EP_ZERO && wave_on) {
+        const int colc = col0 + 4 * c;
+        if constexpr (MODE == MODE_Y) {
+            ep_z0[0] = global_load<uint32_t>(a.z0 + colc);
+            if (a.dz) ep_dz = global_load<f32x4>(a.dz + colc);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int col = Unpacker::BY_PARITY ? col0 + 4 * (c & ~1) + 2 * e + par : colc + e;
+                ep_z0[e] = global_load<uint8_t>(a.z0 + col);
+                if (a.dz) ep_dz[e] = global_load<float>(a.dz + col);
+            }
+        }
+        if constexpr (EP_SCALE) {
+            ep_s0 = global_load<f32x4>(a.s0 + colc);
+            if (a.ds) ep_ds = global_load<f32x4>(a.ds + colc);
+        }
+    }
+
     // ---- prologue: queue NSTAGE - 1 stages (and the packed weights of one more), wait for the first two, fetch the operands
     // of step 0 and the packed weights of step 1
     u32x4 bfrag[2][4], afrag[RT];
@@ -522,34 +546,44 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
     auto local_row = [&](int rt) __attribute__((always_inline)) { return (ROW_SUMS ? rt ^ (2 * wp) : rt) * 16 + 4 * q; };
     auto row_of = [&](int rt, int j) __attribute__((always_inline)) { return t0 + local_row(rt) + j; };
     auto clamped = [&](int t) __attribute__((always_inline)) { return t < T ? t : T - 1; };
-    // Epilogue parameters are fetched while the last DMAs drain: scale and zero-point of this lane's four columns
     f32x4 ep_sc = {0.f, 0.f, 0.f, 0.f}, ep_zoff = {0.f, 0.f, 0.f, 0.f};
-    if (wave_on && !SCALED) {
-        if constexpr (PAIRED) {
+    if constexpr (PAIRED) {
+        if (wave_on) {
             const int g = half_on ? grp : a.G - 1;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const size_t i = (size_t)own_col(e) * a.G + g;
-                ep_zoff[e] = kCodeOffset + (float)a.z0[i];
-                if (a.dz) ep_zoff[e] += a.dz[i];
+                ep_zoff[e] = kCodeOffset + (float)global_load<uint8_t>(a.z0 + i);
+                if (a.dz) ep_zoff[e] += global_load<float>(a.dz + i);
             }
-        } else if constexpr (MODE == MODE_DDS) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                ep_zoff[e] = kCodeOffset + (float)a.z0[own_col(e)];
-                if (a.dz) ep_zoff[e] += a.dz[own_col(e)];
-            }
-        } else if constexpr (MODE == MODE_Y) {
-            const uint32_t zz = *reinterpret_cast<const uint32_t *>(a.z0 + colc);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) ep_zoff[e] = kCodeOffset + (float)((zz >> (8 * e)) & 0xFFu);
-            if (a.dz) ep_zoff += *reinterpret_cast<const f32x4 *>(a.dz + colc);
         }
-        if constexpr (MODE == MODE_Y) {
-            ep_sc = *reinterpret_cast<const f32x4 *>(a.s0 + colc);
-            if (a.ds) ep_sc += *reinterpret_cast<const f32x4 *>(a.ds + colc);
+    } else if constexpr (EP_ZERO) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t z = MODE == MODE_Y ? (ep_z0[0] >> (8 * e)) & 0xFFu : ep_z0[e];
+            ep_zoff[e] = kCodeOffset + (float)z;
         }
+        if (a.dz) ep_zoff += ep_dz;
+        ep_sc = ep_s0;
+        if (EP_SCALE && a.ds) ep_sc += ep_ds;
     }
+    // Y, dX: correction terms of the rows of a row tile, and of the first one that this wave finishes while the last DMAs drain
+    auto load_terms = [&](int rt, float *r) __attribute__((always_inline)) {
+        if constexpr (!SCALED && MODE != MODE_DDS) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if constexpr (MODE == MODE_Y) {
+                    const f32x2 r2 = global_load<f32x2>(a.rs + 2 * clamped(row_of(rt, j)));
+                    r[j] = r2[0] + r2[1];
+                } else {
+                    r[j] = global_load<float>(a.crow + clamped(row_of(rt, j)));
+                }
+            }
+        }
+    };
+    constexpr int FIRST = (RT + 1) / 2;                    // row tiles that the waves of the first contraction half finish
+    float terms[2][4];                                     // of this row tile and the next
+    load_terms(KW == 2 && wk ? FIRST : 0, terms[0]);
     wait_vmcnt<0>();
     __syncthreads();
     mfma_result_fence();
@@ -586,16 +620,16 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const int tc = clamped(row_of(rt, j));
-                    dst[j] = *reinterpret_cast<const dy_vec *>(dy0 + (size_t)tc * a.C);
+                    dst[j] = global_load<dy_vec>(dy0 + (size_t)tc * a.C);
                     // row sum of X over what this wave contracted
                     if constexpr (ROW_SUMS) {
                         rdst[j] = rs_lds[local_row(rt) + j];
                     } else if constexpr (PAIRED) {
-                        rdst[j] = a.rs[(size_t)tc * a.G + (half_on ? grp : a.G - 1)];
+                        rdst[j] = global_load<float>(a.rs + (size_t)tc * a.G + (half_on ? grp : a.G - 1));
                     } else if constexpr (KW == 2) {
-                        rdst[j] = a.rs[2 * tc + wk];
+                        rdst[j] = global_load<float>(a.rs + 2 * tc + wk);
                     } else {
-                        const f32x2 r2 = *reinterpret_cast<const f32x2 *>(a.rs + 2 * tc);
+                        const f32x2 r2 = global_load<f32x2>(a.rs + 2 * tc);
                         rdst[j] = r2[0] + r2[1];
                     }
                 }
@@ -644,7 +678,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
         }
         if constexpr (KW == 1) {
             if (wave_on && q == 0)
-                *reinterpret_cast<f32x4 *>(a.partial + (size_t)(piece * a.tiles_t + tile_t) * a.C + colc) = colsum;
+                global_store(a.partial + (size_t)(piece * a.tiles_t + tile_t) * a.C + colc, colsum);
         } else {
             float *red = reinterpret_cast<float *>(lds);   // [contraction half][256 columns]
             if (q == 0) *reinterpret_cast<f32x4 *>(red + wk * TILE_C + wn * WAVE_C + 4 * c) = colsum;
@@ -655,10 +689,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
                     // the two contraction halves are two scale groups: one partial each
                     const int g0 = 2 * (int)blockIdx.y;
                     float *dst = a.partial + ((size_t)tile_t * a.C + n) * a.G + g0;
-                    dst[0] = red[tid];
-                    if (g0 + 1 < a.G) dst[1] = red[TILE_C + tid];
+                    global_store(dst, red[tid]);
+                    if (g0 + 1 < a.G) global_store(dst + 1, red[TILE_C + tid]);
                 } else {
-                    a.partial[(size_t)(piece * a.tiles_t + tile_t) * a.C + n] = red[tid] + red[TILE_C + tid];
+                    global_store(a.partial + (size_t)(piece * a.tiles_t + tile_t) * a.C + n, red[tid] + red[TILE_C + tid]);
                 }
             }
         }
@@ -671,12 +705,12 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
                 const int t = row_of(rt, j);
                 f32x4 v = columns_of(sum, j);              // (every lane takes part)
                 if (split > 1) {                           // (uniform)
-                    if (t < T) *reinterpret_cast<f32x4 *>(a.acc_part + ((size_t)piece * T + t) * a.C + colc) = v;
+                    if (t < T) global_store(a.acc_part + ((size_t)piece * T + t) * a.C + colc, v);
                 } else if (t < T) {
                     if constexpr (!SCALED) {
                         if constexpr (MODE == MODE_Y) {
                             v -= ep_zoff * r[j];
-                            if (a.P) *reinterpret_cast<f32x4 *>(a.P + (size_t)t * a.C + colc) = v;   // kept for the backward
+                            if (a.P) global_store(a.P + (size_t)t * a.C + colc, v);   // kept for the backward
                             v *= ep_sc;
                         } else {
                             v -= r[j];
@@ -685,28 +719,13 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
                     u32x2 o;
                     o[0] = pack_bf16x2(v[0], v[1]);
                     o[1] = pack_bf16x2(v[2], v[3]);
-                    *reinterpret_cast<u32x2 *>(a.out + (size_t)t * a.C + colc) = o;
+                    global_store(a.out + (size_t)t * a.C + colc, o);
                 }
             }
         };
-        auto load_terms = [&](int rt, float *r) __attribute__((always_inline)) {
-            if constexpr (!SCALED) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    if constexpr (MODE == MODE_Y) {
-                        const f32x2 r2 = *reinterpret_cast<const f32x2 *>(a.rs + 2 * clamped(row_of(rt, j)));
-                        r[j] = r2[0] + r2[1];
-                    } else {
-                        r[j] = a.crow[clamped(row_of(rt, j))];
-                    }
-                }
-            }
-        };
-        float terms[2][4];                                 // of this row tile and the next
         if constexpr (KW == 1) {
             // one contraction range per workgroup: every wave holds the finished sums of its row tiles
             if (!wave_on) return;
-            load_terms(0, terms[0]);
             static_for<RT>([&](auto rt_c) {
                 constexpr int rt = rt_c.value;
                 if constexpr (rt + 1 < RT) load_terms(rt + 1, terms[(rt + 1) & 1]);
@@ -719,7 +738,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
             // sum the two contraction halves: waves with wk = 0 keep the first half of the row tiles (rounded up) and send the
             // others, waves with wk = 1 the other way round
             f32x4 *xch = reinterpret_cast<f32x4 *>(lds);       // [8 waves][4 FIRST accumulator tiles][64 lanes]
-            constexpr int FIRST = (RT + 1) / 2;
             static_assert(8 * 4 * FIRST * 1024 <= ring_bytes(2, RT), "the exchange reuses the ring");
             auto finish = [&](auto keep_c) __attribute__((always_inline)) {
                 constexpr int KEEP = decltype(keep_c)::value;  // first row tile this wave keeps
@@ -734,7 +752,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a, const int wg, uint8
                 __syncthreads();
                 if (!wave_on) return;
                 const f32x4 *theirs = xch + (size_t)(wave ^ 4) * (4 * FIRST) * 64 + lane;
-                load_terms(KEEP, terms[0]);
                 static_for<KEPT>([&](auto rt_c) {
                     constexpr int rtl = rt_c.value;
                     if constexpr (rtl + 1 < KEPT) load_terms(KEEP + rtl + 1, terms[(rtl + 1) & 1]);
