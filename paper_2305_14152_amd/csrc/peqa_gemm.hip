@@ -73,41 +73,49 @@ __global__ __launch_bounds__(256) void split_finish_kernel(FinishMulti f)
     const uint32_t c4 = (uint32_t)a.C >> 2;
     const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (e >= (size_t)a.T * c4) return;
-    const size_t t = e / c4;
+    // (a 64-bit division is a hundred instructions)
+    const size_t t = e >> 32 ? e / c4 : (size_t)((uint32_t)e / (uint32_t)c4);
     const int col = (int)(e - t * c4) * 4;
+    // what the epilogue needs besides the pieces is asked for before them
+    const bool scale = a.gsz == 0 && J.mode == MODE_Y, shift = a.gsz == 0 && J.mode != MODE_Y;
+    f32x2 r = {0.f, 0.f};
+    f32x4 sc = {0.f, 0.f, 0.f, 0.f}, dz = sc, ds = sc;
+    uint32_t zz = 0;
+    if (scale) {
+        r = global_load<f32x2>(a.rs + 2 * t);
+        zz = global_load<uint32_t>(a.z0 + col);
+        sc = global_load<f32x4>(a.s0 + col);
+        if (a.ds) ds = global_load<f32x4>(a.ds + col);
+        if (a.dz) dz = global_load<f32x4>(a.dz + col);
+    }
+    if (shift) r[0] = global_load<float>(a.crow + t);
     const f32x4 *p = reinterpret_cast<const f32x4 *>(a.acc_part) + e;
     const size_t stride = (size_t)a.T * c4;
-    f32x4 v = p[0];
-    int i = 1;
-    for (; i + 4 <= a.split; i += 4) {                         // four loads in flight, added in order
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < a.split; i += 4) {                     // four loads in flight, added in order
         f32x4 w[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) w[u] = p[(size_t)(i + u) * stride];
+        for (int u = 0; u < 4; ++u) w[u] = global_load<f32x4>(p + (size_t)(i + u < a.split ? i + u : a.split - 1) * stride);
+        v = i == 0 ? w[0] : v + w[0];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v += w[u];
+        for (int u = 1; u < 4; ++u)
+            if (i + u < a.split) v += w[u];
     }
-    for (; i < a.split; ++i) v += p[(size_t)i * stride];
-    if (a.gsz == 0) {
-        if (J.mode == MODE_Y) {
-            const float r = a.rs[2 * t] + a.rs[2 * t + 1];
-            const uint32_t zz = *reinterpret_cast<const uint32_t *>(a.z0 + col);
-            f32x4 zoff;
+    if (scale) {
+        f32x4 zoff;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) zoff[u] = kCodeOffset + (float)((zz >> (8 * u)) & 0xFFu);
-            if (a.dz) zoff += *reinterpret_cast<const f32x4 *>(a.dz + col);
-            f32x4 sc = *reinterpret_cast<const f32x4 *>(a.s0 + col);
-            if (a.ds) sc += *reinterpret_cast<const f32x4 *>(a.ds + col);
-            v -= zoff * r;
-            if (a.P) *reinterpret_cast<f32x4 *>(a.P + t * a.C + col) = v;
-            v *= sc;
-        } else {
-            v -= a.crow[t];
-        }
+        for (int u = 0; u < 4; ++u) zoff[u] = kCodeOffset + (float)((zz >> (8 * u)) & 0xFFu);
+        if (a.dz) zoff += dz;
+        if (a.ds) sc += ds;
+        v -= zoff * (r[0] + r[1]);
+        if (a.P) global_store(a.P + t * a.C + col, v);
+        v *= sc;
     }
+    if (shift) v -= r[0];
     u32x2 o;
     o[0] = pack_bf16x2(v[0], v[1]);
     o[1] = pack_bf16x2(v[2], v[3]);
-    *reinterpret_cast<u32x2 *>(a.out + t * a.C + col) = o;
+    global_store(a.out + t * a.C + col, o);
 }
 
 }  // namespace

@@ -194,10 +194,10 @@ __device__ __forceinline__ void gemv_tile(const GemvArgs &a, const GemvLayer &L,
             for (int i = 0; i < NB; ++i) {
                 int e = e0 + 4 * (tid + i * THREADS);
                 e = e < GV_C * cols ? e : 0;
-                ts[i] = *reinterpret_cast<const f32x4 *>(l_s0 + base + e);
-                tz[i] = *reinterpret_cast<const uint32_t *>(l_z0 + base + e);
-                td[i] = l_ds ? *reinterpret_cast<const f32x4 *>(l_ds + base + e) : f32x4{0.f, 0.f, 0.f, 0.f};
-                if constexpr (!ZBYTE) tdz[i] = l_dz ? *reinterpret_cast<const f32x4 *>(l_dz + base + e) : f32x4{0.f, 0.f, 0.f, 0.f};
+                ts[i] = global_load<f32x4>(l_s0 + base + e);
+                tz[i] = global_load<uint32_t>(l_z0 + base + e);
+                td[i] = l_ds ? global_load<f32x4>(l_ds + base + e) : f32x4{0.f, 0.f, 0.f, 0.f};
+                if constexpr (!ZBYTE) tdz[i] = l_dz ? global_load<f32x4>(l_dz + base + e) : f32x4{0.f, 0.f, 0.f, 0.f};
             }
 #pragma unroll
             for (int i = 0; i < NB; ++i) {
@@ -227,10 +227,10 @@ __device__ __forceinline__ void gemv_tile(const GemvArgs &a, const GemvLayer &L,
                 ch[i] = (int)(((float)e + 0.5f) * inv_cols);
                 jj[i] = e - ch[i] * cols;
                 const size_t si = (size_t)(n0 + ch[i]) * G + g_lo + jj[i];
-                ts[i] = l_s0[si];
-                tz[i] = l_z0[si];
-                td[i] = l_ds ? l_ds[si] : 0.f;
-                if constexpr (!ZBYTE) tdz[i] = l_dz ? l_dz[si] : 0.f;
+                ts[i] = global_load<float>(l_s0 + si);
+                tz[i] = global_load<uint8_t>(l_z0 + si);
+                td[i] = l_ds ? global_load<float>(l_ds + si) : 0.f;
+                if constexpr (!ZBYTE) tdz[i] = l_dz ? global_load<float>(l_dz + si) : 0.f;
             }
 #pragma unroll
             for (int i = 0; i < NB; ++i)
@@ -370,8 +370,8 @@ __device__ __forceinline__ void gemv_tile(const GemvArgs &a, const GemvLayer &L,
             for (int w = 0; w < WAVES; ++w) v += src[w * 4 * HH * CT + 2 * 16 + 8];
         }
         const uint32_t to = (uint32_t)t * (uint32_t)l_N + (uint32_t)(n0 + nn);   // (T N is below 2^31)
-        if (l_S == 1) L.Y[to] = (uint16_t)float_to_bf16_bits(v);
-        else L.partial[(size_t)slice * a.T * l_N + to] = v;
+        if (l_S == 1) global_store(L.Y + to, (uint16_t)float_to_bf16_bits(v));
+        else global_store(L.partial + (size_t)slice * a.T * l_N + to, v);
     }
 }
 
@@ -436,13 +436,13 @@ __global__ __launch_bounds__(256) void gemv_finish_kernel(GemvSums a)
 #pragma unroll
         for (int u = 0; u < 8; ++u) {                             // past the last slice: the last one again, not added
             const int sl = s0 + u < L.S ? s0 + u : L.S - 1;
-            p[u] = *reinterpret_cast<const f32x2 *>(L.partial + (size_t)sl * L.tn + e);
+            p[u] = global_load<f32x2>(L.partial + (size_t)sl * L.tn + e);
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u)
             if (s0 + u < L.S) v += p[u];
     }
-    *reinterpret_cast<uint32_t *>(L.Y + e) = pack_bf16x2(v[0], v[1]);
+    global_store(L.Y + e, pack_bf16x2(v[0], v[1]));
 }
 
 }  // namespace
