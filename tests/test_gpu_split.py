@@ -431,3 +431,62 @@ def test_block_dx_alone(gpu, oracle, group, bits):
         got = gpu.bf16_dev_to_f64(d["dX"])
         assert np.abs(got[rows] - dXref).max() <= Y_TOL * np.abs(dXref).max()
         assert np.abs(got - together).max() <= 2.0 ** -7 * np.abs(together).max()
+
+
+@pytest.mark.parametrize("K,group", [(24576, 64), (25600, 64), (24576, 0)])
+def test_many_groups_and_many_slices(gpu, oracle, K, group):
+    """384 scale groups per channel (tables by tiles, close to the LDS that those may take) and 400 (entry by entry), forward and
+    backward; per channel and T <= 16, 12 slices of one layer, which are added up eight and four at a time."""
+    from paper_2305_14152_amd import peqa
+    N, bits = 128, 4
+    seed = 79000 + K + group
+    W = synth.normal_f32(seed, (N, K), 0.02)
+    layer = gpu.GpuLayer(W, bits, group)
+    codes, s0, z0 = oracle.quantize(W, bits, group)
+    ds = synth.normal_f32(seed + 1, s0.shape, 1e-3)
+    for T in (33,) if group else (1, 16):
+        print("K=%d g=%d T=%d" % (K, group, T), flush=True)
+        X = synth.normal_bf16(seed + 2 + T, (T, K), 1.0)
+        Yref = oracle.fwd(codes, s0, ds, z0, X, group)
+        assert np.abs(gpu.bf16_dev_to_f64(layer.fwd(X, ds)) - Yref).max() <= Y_TOL * np.abs(Yref).max()
+        if group:
+            dY = synth.normal_bf16(seed + 3, (T, N), 1.0)
+            dXref, gref, _ = oracle.bwd(codes, s0, ds, z0, X, dY, group)
+            dX, g = layer.bwd(X, dY, ds)
+            assert np.abs(gpu.bf16_dev_to_f64(dX) - dXref).max() <= Y_TOL * np.abs(dXref).max()
+            gpu.assert_scale_grad_close(gpu.to_host(g), gref)
+        else:
+            assert _small_batch_form(peqa, [(N, K)], bits, group, T)[2] == [12]
+
+
+def test_group_wise_backward_of_many_tiles_and_few_tokens(gpu):
+    """More than eight tiles per unit and at most 1536 tokens: dX and the token contraction in one launch, against a launch each
+    (PEQA_OPT_GEMM_WAVES = 4).  The scale gradients are sums in the same order; a piece of dX may be added in another."""
+    import torch
+    from paper_2305_14152_amd import peqa
+    N, K, group, bits, T = 8192, 8448, 128, 3, 70
+    g = torch.Generator(device="cuda").manual_seed(79900)
+    L = peqa.layout(N, K, bits, group)
+    W = torch.randn((N, K), device="cuda", generator=g) * 0.02
+    packed = torch.empty(peqa.packed_words(L), dtype=torch.int32, device="cuda")
+    s0, z0 = torch.empty((N, L.groups), device="cuda"), torch.empty((N, L.groups), dtype=torch.uint8, device="cuda")
+    peqa.quantize(L, W, packed, s0, z0)
+    X = torch.randn((T, K), device="cuda", generator=g).bfloat16().view(torch.int16)
+    dY = torch.randn((T, N), device="cuda", generator=g).bfloat16().view(torch.int16)
+    got = []
+    for waves, launches in ((0, {"gemm_bwd": 1}), (4, {"gemm_dx": 1, "gemm_dw": 1})):
+        peqa.set_option(peqa.PEQA_OPT_GEMM_WAVES, waves)
+        try:
+            dX, d_ds = torch.zeros_like(X), torch.zeros_like(s0)
+            nb = peqa.workspace_bytes(L, T, peqa.PEQA_OP_BWD)
+            ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+            peqa.trace_begin(16)
+            peqa.linear_bwd(L, packed, s0, None, z0, X, dY, T, dX, d_ds, ws, nb)
+            seen = {k: v[0] for k, v in peqa.trace_end().items()}
+        finally:
+            peqa.set_option(peqa.PEQA_OPT_GEMM_WAVES, 0)
+        print(waves, seen, flush=True)
+        assert all(seen.get(k) == n for k, n in launches.items()), seen
+        got.append((gpu.bf16_dev_to_f64(dX), gpu.to_host(d_ds)))
+    assert np.abs(got[0][0]).max() > 0 and np.abs(got[0][0] - got[1][0]).max() <= 2.0 ** -7 * np.abs(got[1][0]).max()
+    assert (got[0][1] == got[1][1]).all() and np.abs(got[0][1]).max() > 0
