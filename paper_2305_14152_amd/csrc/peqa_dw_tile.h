@@ -24,8 +24,8 @@ __device__ __forceinline__ void dw_tile(const DwArgs &a, const int wg, uint8_t *
     const int wn = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave = quarter of the channels
     const int c = lane & 15, q = lane >> 4;
 
-    // Nothing is in flight here, which the compiler cannot know where this tile shares a kernel with the dX tile, whose FLAT stores
-    // it believes may be pending: it would wait for all of memory in the loop (see load_b).
+    // Nothing is in flight here, which the compiler cannot know where this tile shares a kernel with the dX tile, whose stores
+    // it believes may be pending: it would wait for them in the loop (see load_b).
     __builtin_amdgcn_s_waitcnt(0);
 
     // workgroup -> tile: XCD x gets an eighth of the tiles, in one run of an order in which 64 neighbours (what an XCD

@@ -21,7 +21,9 @@
 // Tiles of 64 channels instead of 128 need no slices where 128 needed two to six, i.e. no second launch, and put twice the
 // workgroups behind a layer.  us per call at T = 5, 128 channels -> this form: 13B 3-bit g128 qkv 18.3 -> 11.9, o 13.7 -> 10.4,
 // gate/up 22.7 -> 18.1, down 18.9 -> 14.5, whole block 36.1 -> 34.6; 7B 4-bit qkv 14.2 -> 9.3, o 11.4 -> 8.1, gate/up 18.4 -> 13.6,
-// down 15.1 -> 11.8, whole block 29.5 -> 26.3.
+// down 15.1 -> 11.8, whole block 29.5 -> 26.3.  What is read and written besides the DMAs goes by global instructions: with FLAT ones
+// (the pointers come out of the argument block) every use of a part of the scale tile waited for all of memory (four 7B blocks, T = 1
+// 91.4 -> 87.9 us, two 13B blocks, T = 16 72.0 -> 70.5).  Three rounds in flight instead of two cost 3 % (places on the unit).
 //
 // A wave moves its operands in rounds of 64 features (two MFMA steps): its packed words and the matching 128 bytes of each
 // token row, by global -> LDS DMA into a private double buffer, from which each lane reads back its own words and

@@ -5,9 +5,11 @@
 // MFMA 16x16x32 tiles in 16 RT AGPRs.  RT is 8 where there are tokens enough (what follows is said of it), 4, 6 or 7 where tiles of
 // 128 rows would be mostly padding or leave the machine idle (gemm_row_tiles, gemm_plan).
 //
-// What bounds it and why this split.  Per 32-deep step and SIMD (two waves) the matrix instructions take 1024 cycles;
-// the vector instructions of two waves take 4 cycles each beside them, and LDS delivers 128 bytes per cycle to the
-// compute unit.  With 128 x 64 per wave every weight of the tile is unpacked (and, group-wise, scaled) by one wave only:
+// What bounds it and why this split.  Per 32-deep step and SIMD (two waves) the matrix instructions take 1024 cycles, and LDS
+// delivers 128 bytes per cycle to the compute unit.  A matrix instruction (16 cycles) holds the SIMD's issue for 8 of them and a vector
+// instruction for 4, whatever it is and whichever wave it is of: loops of 16x16x32 instructions with n others each take
+// max(16, 8 + 4 n) cycles per matrix instruction, with one wave or two (n = 2: 7.6 ns, 3: 9.1, 4: 11.1).  So two are free; per channel there
+// are 1.5, and 2.9 group-wise, which make a step a fifth longer.  With 128 x 64 per wave every weight of the tile is unpacked (and, group-wise, scaled) by one wave only:
 // 2 instructions per weight pair per channel and 5 group-wise (scale_pair) make 256 and 640 cycles per step.  The split this
 // replaced, 64 x 128 per wave, had every weight unpacked by two waves: 512 and, at the 7 instructions per pair it took to
 // scale bf16 codes, 1800 cycles, which made the group-wise contractions vector-bound.  The price is that a wave reads the
@@ -15,7 +17,7 @@
 // compute unit.  Measured, 64 x 128 -> 128 x 64:
 // LLaMA-13B block, 3 bits, groups of 128, T = 2048: forward launch 1537 -> 1239 us, dX 1654 -> 1445 us (with
 // that split dX scaled its activation fragments instead of the weights; here the weights are cheaper to scale), and with
-// fp16 codes for the scaling 1129 and 1259 us; 11008 x 4096, 4 bits, groups of 64, T = 500: forward 102 -> 72 -> 67 us;
+// fp16 codes for the scaling 1129 and 1259 us, with the scaling in three turns and short epilogues 1085 and 1110 (dX alone); 11008 x 4096, 4 bits, groups of 64, T = 500: forward 102 -> 72 -> 67 us;
 // per-channel training steps of the 7B and 65B blocks 2.1 and 2.9 % shorter.
 //
 // Launches that fill the chip for long run below the nominal clock of 2.4 GHz, at 1.8 to 1.9 (GRBM_GUI_ACTIVE over their time): what
