@@ -104,15 +104,34 @@ def early_reads(listing):
     return bad
 
 
-def device_listings(lib):
-    """Disassembly of every code object in a library built here."""
-    objdump = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-objdump")
+def _of_device_objects(lib, tool, *args):
+    """What a tool of the toolchain prints of every code object in a library built here."""
+    tools = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin")
     with tempfile.TemporaryDirectory() as tmp:
         name = os.path.basename(lib)
         shutil.copy(lib, tmp)
-        subprocess.run([objdump, "--offloading", name], cwd=tmp, check=True, stdout=subprocess.DEVNULL)
+        subprocess.run([os.path.join(tools, "llvm-objdump"), "--offloading", name], cwd=tmp, check=True, stdout=subprocess.DEVNULL)
         objects = [f for f in sorted(os.listdir(tmp)) if "amdgcn" in f]
-        return [subprocess.run([objdump, "-d", f], cwd=tmp, check=True, stdout=subprocess.PIPE, text=True).stdout for f in objects]
+        return [subprocess.run([os.path.join(tools, tool), *args, f], cwd=tmp, check=True, stdout=subprocess.PIPE, text=True).stdout
+                for f in objects]
+
+
+def device_listings(lib):
+    """Disassembly of every code object in a library built here."""
+    return _of_device_objects(lib, "llvm-objdump", "-d")
+
+
+def kernel_registers(lib):
+    """Vector registers of a lane, accumulators among them, of every kernel in a library built here: {mangled name: number}."""
+    found, name = {}, None
+    for text in _of_device_objects(lib, "llvm-readelf", "--notes"):
+        for line in text.splitlines():
+            key, _, value = line.strip().partition(":")
+            if key == ".name" and value.strip().startswith("_Z"):
+                name = value.strip()
+            elif key == ".vgpr_count":
+                found[name] = int(value)
+    return found
 
 
 def _quiet(text):

@@ -58,73 +58,78 @@ __global__ __launch_bounds__(256, 2) void gemm_bwd_pair_kernel(GemmArgs a_dds, G
     else gemm_tile<BITS, MODE_DDS, false, 1, RT>(a_dds, wg, lds);
 }
 
-// Bandwidth-bound side work inside a multi-contraction launch: auxiliary workgroup `w` of `m.aux_wgs` walks the
-// units w, w + aux_wgs, ... of one index space: first the AUX_SDY_ROWS-row blocks of the scale_dy jobs, then the
-// 256-element chunks of the reduce jobs; before them its waves walk the 64 x 64 tiles of the transpose jobs.
-__device__ __forceinline__ void multi_aux(int n_sdy, int n_red, int n_tp, int aux_wgs, int w, uint8_t *lds)
+// Bandwidth-bound side work inside a multi-contraction launch: auxiliary workgroup `w` of `aux_wgs` walks units w, w + aux_wgs, ...
+// Registers are a kernel's, not a workgroup's: what one of these takes, the tiles have taken too.  So a kernel has the side work of
+// its own launches only, and that of 64-row tiles stays within what three workgroups per unit leave (see gemm_multi_kernel).
+//
+// Group-wise dX: the 64 x 64 tiles of the transpose jobs, one per wave.
+__device__ __forceinline__ void multi_aux_copies(int n_tp, int aux_wgs, int w, uint8_t *lds)
 {
-    struct { int n_sdy, n_red, n_tp, aux_wgs; } m{n_sdy, n_red, n_tp, aux_wgs};
+    constexpr uint32_t TP0 = offsetof(MultiArgs, tp);
+    auto end_of = [](int i) { return kernarg_load<int>(TP0 + (uint32_t)(i * sizeof(TransposeJob) + offsetof(TransposeJob, tile_end))); };
+    const int n_tile = n_tp > 0 ? end_of(n_tp - 1) : 0;
+    // a tile per wave; the wave's next tile is asked for before this one is turned
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    u32x4 *piece = reinterpret_cast<u32x4 *>(lds + wave * TRANSPOSE_LDS);
+    struct Tile { TransposeJob J; int bt, bc; };
+    auto tile_of = [&](int x) __attribute__((always_inline)) {
+        int j = 0, x0 = 0;
+        for (int i = 0; i + 1 < n_tp; ++i) {
+            const int e = end_of(i);
+            if (x >= e) { j = i + 1; x0 = e; }
+        }
+        Tile t;
+        t.J = kernarg_load<TransposeJob>(TP0 + (uint32_t)(j * sizeof(TransposeJob)));
+        const int bcs = t.J.C >> 6;
+        t.bt = (x - x0) / bcs;
+        t.bc = (x - x0) - t.bt * bcs;
+        return t;
+    };
+    int x = 4 * w + wave;
+    if (x >= n_tile) return;
+    Tile t = tile_of(x);
+    TransposeRows r;
+    transpose_load(t.J.src, t.J.T, t.J.C, t.bt, t.bc, r);
+    for (;;) {
+        x += 4 * aux_wgs;
+        Tile next = t;
+        TransposeRows ahead;
+        if (x < n_tile) {
+            next = tile_of(x);
+            transpose_load(next.J.src, next.J.T, next.J.C, next.bt, next.bc, ahead);
+        }
+        transpose_store(r, t.J.C, t.J.dst, t.bt, t.bc, piece);
+        if (x >= n_tile) break;
+        t = next;
+        r = ahead;
+    }
+}
+
+// Per channel: one index space, first the AUX_SDY_ROWS-row blocks of the scale_dy jobs, then the 256-element chunks of the reduce jobs.
+template <bool AHEAD>
+__device__ __forceinline__ void multi_aux(int n_sdy, int n_red, int aux_wgs, int w, uint8_t *lds)
+{
     float *red = reinterpret_cast<float *>(lds);
-    constexpr uint32_t SDY0 = offsetof(MultiArgs, sdy), RED0 = offsetof(MultiArgs, red), TP0 = offsetof(MultiArgs, tp);
+    constexpr uint32_t SDY0 = offsetof(MultiArgs, sdy), RED0 = offsetof(MultiArgs, red);
     auto last = [](uint32_t table, int n, size_t size, size_t member) {   // a running total's value behind the last of n jobs
         return n > 0 ? kernarg_load<int>(table + (uint32_t)((n - 1) * size + member)) : 0;
     };
-    const int n_blk = last(SDY0, m.n_sdy, sizeof(ScaleDyJob), offsetof(ScaleDyJob, blk_end));
-    const int n_chunk = last(RED0, m.n_red, sizeof(ReduceJob), offsetof(ReduceJob, chunk_end));
-    const int n_tile = last(TP0, m.n_tp, sizeof(TransposeJob), offsetof(TransposeJob, tile_end));
-    if (n_tile > 0) {
-        // a tile per wave; the wave's next tile is asked for before this one is turned
-        const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-        u32x4 *piece = reinterpret_cast<u32x4 *>(lds + wave * TRANSPOSE_LDS);
-        struct Tile { TransposeJob J; int bt, bc; };
-        auto tile_of = [&](int x) __attribute__((always_inline)) {
-            int j = 0, x0 = 0;
-            for (int i = 0; i + 1 < m.n_tp; ++i) {
-                const int e = kernarg_load<int>(TP0 + (uint32_t)(i * sizeof(TransposeJob) + offsetof(TransposeJob, tile_end)));
-                if (x >= e) { j = i + 1; x0 = e; }
-            }
-            Tile t;
-            t.J = kernarg_load<TransposeJob>(TP0 + (uint32_t)(j * sizeof(TransposeJob)));
-            const int bcs = t.J.C >> 6;
-            t.bt = (x - x0) / bcs;
-            t.bc = (x - x0) - t.bt * bcs;
-            return t;
-        };
-        int x = 4 * w + wave;
-        if (x < n_tile) {
-            Tile t = tile_of(x);
-            TransposeRows r;
-            transpose_load(t.J.src, t.J.T, t.J.C, t.bt, t.bc, r);
-            for (;;) {
-                x += 4 * m.aux_wgs;
-                Tile next = t;
-                TransposeRows ahead;
-                if (x < n_tile) {
-                    next = tile_of(x);
-                    transpose_load(next.J.src, next.J.T, next.J.C, next.bt, next.bc, ahead);
-                }
-                transpose_store(r, t.J.C, t.J.dst, t.bt, t.bc, piece);
-                if (x >= n_tile) break;
-                t = next;
-                r = ahead;
-            }
-        }
-        __syncthreads();                                       // what follows uses the LDS too
-    }
-    for (int u = w; u < n_blk + n_chunk; u += m.aux_wgs) {
+    const int n_blk = last(SDY0, n_sdy, sizeof(ScaleDyJob), offsetof(ScaleDyJob, blk_end));
+    const int n_chunk = last(RED0, n_red, sizeof(ReduceJob), offsetof(ReduceJob, chunk_end));
+    for (int u = w; u < n_blk + n_chunk; u += aux_wgs) {
         if (u < n_blk) {
             int j = 0, b0 = 0;
-            for (int i = 0; i + 1 < m.n_sdy; ++i) {
+            for (int i = 0; i + 1 < n_sdy; ++i) {
                 const int e = kernarg_load<int>(SDY0 + (uint32_t)(i * sizeof(ScaleDyJob) + offsetof(ScaleDyJob, blk_end)));
                 if (u >= e) { j = i + 1; b0 = e; }
             }
             const ScaleDyJob J = kernarg_load<ScaleDyJob>(SDY0 + (uint32_t)(j * sizeof(ScaleDyJob)));
-            scale_dy_rows<AUX_SDY_ROWS>(J.dY, J.s0, J.ds, J.z0, nullptr, J.T, J.N, J.dYs, J.crow, u - b0, red);
+            scale_dy_rows<AUX_SDY_ROWS, AHEAD>(J.dY, J.s0, J.ds, J.z0, nullptr, J.T, J.N, J.dYs, J.crow, u - b0, red);
             __syncthreads();                                   // `red` is reused by the next block
         } else {
             const int c = u - n_blk;
             int j = 0, c0 = 0;
-            for (int i = 0; i + 1 < m.n_red; ++i) {
+            for (int i = 0; i + 1 < n_red; ++i) {
                 const int e = kernarg_load<int>(RED0 + (uint32_t)(i * sizeof(ReduceJob) + offsetof(ReduceJob, chunk_end)));
                 if (c >= e) { j = i + 1; c0 = e; }
             }
@@ -138,6 +143,12 @@ __device__ __forceinline__ void multi_aux(int n_sdy, int n_red, int n_tp, int au
 // jobs' running totals; the job's arguments come out of the argument block with scalar loads.
 // GMODE < 0: per-channel jobs of any mode; GMODE = MODE_Y or MODE_DX: group-wise jobs, all of that mode (their
 // scale gradient is the token contraction of peqa_dw.hip).
+//
+// Per-channel tiles of 64 rows have 48 KB of LDS and 64 accumulators: three workgroups fit a unit as long as the kernel takes no
+// more than 104 registers besides.  With the copies' two tiles in flight and the scaling's two sets of columns compiled in it took 127
+// (82 and 92 without), and blocks of 513 to 768 workgroups a second round.  Blocks of d = 8192, f = 22016 (752 and 760 workgroups), us,
+// two on a unit -> three: forward at T = 17 / 32 107.9 / 116.5 -> 104.2 / 111.9, training step 337 / 351 -> 308 / 330; d = 6656, 3 bits,
+// T = 17 216 -> 210.  At T = 64, where a tile has as much to compute as to wait for, 394 -> 393 and, d = 6656, 289 -> 296.
 template <int BITS, int GMODE, int RT>
 __global__ __launch_bounds__(256, 2) void gemm_multi_kernel(MultiArgs m)
 {
@@ -146,7 +157,8 @@ __global__ __launch_bounds__(256, 2) void gemm_multi_kernel(MultiArgs m)
     if constexpr (GMODE != MODE_Y) {                           // a group-wise forward has no side work
         if (b >= m.aux_begin) {
             if (b < m.aux_begin + m.aux_wgs) {
-                multi_aux(m.n_sdy, m.n_red, m.n_tp, m.aux_wgs, b - m.aux_begin, lds);
+                if constexpr (GMODE < 0) multi_aux<RT != 4>(m.n_sdy, m.n_red, m.aux_wgs, b - m.aux_begin, lds);
+                else multi_aux_copies(m.n_tp, m.aux_wgs, b - m.aux_begin, lds);
                 return;
             }
             b -= m.aux_wgs;

@@ -181,8 +181,9 @@ __device__ __forceinline__ void global_store(void *p, const T &v)
 // Bound by latency: what a workgroup has in flight is ROWS x 4 KB.  Four rows where there are workgroups enough to fill the machine (a launch
 // of its own), eight beside matrix work, where every place that the scaling holds for longer is one less for tiles, and half as
 // many workgroups: backward of a 7B block 1218 -> 1190 us; dX alone with the scaling before it 649 -> 636.  (The next columns asked for
-// early, with four rows: the same.  Sixteen rows: the registers do not hold them.)
-template <int ROWS>
+// early, with four rows: the same.  Sixteen rows: the registers do not hold them.)  AHEAD: with two sets of columns in registers; not
+// beside tiles of 64 rows, whose third workgroup on a unit they would cost (gemm_multi_kernel).
+template <int ROWS, bool AHEAD>
 __device__ __forceinline__ void scale_dy_rows(const uint16_t *__restrict__ dY, const float *__restrict__ s0,
                                               const float *__restrict__ ds, const uint8_t *__restrict__ z0,
                                               const float *__restrict__ dz, int T, int N, uint16_t *__restrict__ dYs,
@@ -215,12 +216,17 @@ __device__ __forceinline__ void scale_dy_rows(const uint16_t *__restrict__ dY, c
             k.zb = global_load<f32x4>(dz + 8 * n8 + 4);
         }
     };
-    // the next columns (and their parameters: loads arrive in order) are on their way while these are scaled
+    // AHEAD: the next columns (and their parameters: loads arrive in order) are on their way while these are scaled
     Columns ahead;
-    if (tid < n8s) load(tid, ahead);
+    if (AHEAD && tid < n8s) load(tid, ahead);
     for (int n8 = tid; n8 < n8s; n8 += 256) {
-        const Columns k = ahead;
-        if (n8 + 256 < n8s) load(n8 + 256, ahead);
+        Columns k;
+        if constexpr (AHEAD) {
+            k = ahead;
+            if (n8 + 256 < n8s) load(n8 + 256, ahead);
+        } else {
+            load(n8, k);
+        }
         float s[8] = {k.sa[0], k.sa[1], k.sa[2], k.sa[3], k.sb[0], k.sb[1], k.sb[2], k.sb[3]};
         float zo[8];
 #pragma unroll

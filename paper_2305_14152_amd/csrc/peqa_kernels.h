@@ -154,7 +154,8 @@ struct MultiArgs {
     int n_jobs, n_sdy, n_red, n_tp;
     int aux_begin, aux_wgs;
 };
-// Per-channel jobs (any mode), or, with `grouped`, group-wise MODE_Y / MODE_DX jobs (their tables in a.sb).
+// Per-channel jobs (any mode), with scale_dy and reduce jobs beside them, or, with `grouped`, group-wise MODE_Y / MODE_DX jobs
+// (their tables in a.sb), with transpose jobs beside dX.
 static_assert(sizeof(MultiArgs) <= 4096, "kernel argument block");
 hipError_t launch_gemm_multi(int bits, bool grouped, MultiArgs &m, hipStream_t stream);
 // The launches themselves, of tiles of RT row tiles: a contraction, a backward pair, or `workgroups` of a multi-contraction

@@ -65,6 +65,16 @@ def test_spills_are_refused_in_every_kernel_that_counts():
     assert [k for k in kernels if not build.check_no_scratch(remark % k)] == []
 
 
+def test_three_workgroups_of_64_row_tiles_fit_a_unit():
+    """Per-channel tiles of 64 rows have 48 KB of LDS, so that three four-wave workgroups fit a unit if their kernel, with whatever
+    side work is compiled into it, takes no more than a third of a SIMD's 512 registers (in steps of eight)."""
+    peqa.lib()
+    found = {name: regs for name, regs in build.kernel_registers(build.LIB).items()
+             if re.search(r"gemm_multi_kernelILi[34]ELin1ELi4E|gemm_bwd_pair_kernelILi[34]ELi4E|gemm_kernelILi[34]ELi[012]ELb0ELi1ELi4E", name)}
+    assert len(found) == 10, found
+    assert {name: regs for name, regs in found.items() if regs > 512 // 3 // 8 * 8} == {}
+
+
 def test_token_tiles_wait_for_what_they_use_only():
     """The loop of the token contraction, in every kernel that has it: operands by global loads, and no wait that empties the
     memory queue (which the compiler puts where it believes a FLAT operation is pending, and which drains the ring)."""
