@@ -102,8 +102,8 @@ __global__ __launch_bounds__(256) void chunk_reduce_multi_kernel(DwMultiArgs m)
     const size_t j = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (j >= n) return;
     float s = 0.f;
-    for (int e = 0; e < per; ++e) s += a.pc[j * per + e];
-    d_ds[j] = s;
+    for (int e = 0; e < per; ++e) s += global_load<float>(a.pc + j * per + e);
+    global_store(d_ds + j, s);
 }
 
 constexpr int kMaxDev = 64;

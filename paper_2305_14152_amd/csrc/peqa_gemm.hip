@@ -59,12 +59,12 @@ __global__ __launch_bounds__(256) void split_finish_kernel(FinishMulti f)
         for (; i + 8 <= S.count; i += 8) {                     // eight loads in flight, added in order
             float p[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) p[u] = src[(size_t)(i + u) * S.step];
+            for (int u = 0; u < 8; ++u) p[u] = global_load<float>(src + (size_t)(i + u) * S.step);
 #pragma unroll
             for (int u = 0; u < 8; ++u) v += p[u];
         }
-        for (; i < S.count; ++i) v += src[(size_t)i * S.step];
-        S.dst[j] = v;
+        for (; i < S.count; ++i) v += global_load<float>(src + (size_t)i * S.step);
+        global_store(S.dst + j, v);
         return;
     }
     const FinishJob J = kernarg_load<FinishJob>((uint32_t)(blockIdx.y * sizeof(FinishJob)));

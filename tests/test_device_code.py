@@ -75,6 +75,14 @@ def test_three_workgroups_of_64_row_tiles_fit_a_unit():
     assert {name: regs for name, regs in found.items() if regs > 512 // 3 // 8 * 8} == {}
 
 
+def test_memory_is_read_and_written_by_global_instructions():
+    """FLAT loads and stores, which the compiler takes for pointers whose memory it cannot tell, count as LDS operations too: it waits
+    for every operation in flight before the use of what one brings."""
+    peqa.lib()
+    assert [line for text in build.device_listings(build.LIB) for line in text.splitlines()
+            if re.match(r"\s+flat_(load|store|atomic)", line)] == []
+
+
 def test_token_tiles_wait_for_what_they_use_only():
     """The loop of the token contraction, in every kernel that has it: operands by global loads, and no wait that empties the
     memory queue (which the compiler puts where it believes a FLAT operation is pending, and which drains the ring)."""
