@@ -341,6 +341,67 @@ def test_block_groupwise_skips_and_shared_inputs(gpu, oracle, bits, group):
                 assert (gpu.to_host(d["d_ds"]).view(np.uint32) == gpu.to_host(d2["d_ds"]).view(np.uint32)).all()
 
 
+def _traced(run):
+    """What `run` returns, and how often it launched each kernel."""
+    from paper_2305_14152_amd import peqa
+    peqa.trace_begin(256)
+    try:
+        out = run()
+    finally:
+        seen = {k: v[0] for k, v in peqa.trace_end().items()}
+    return out, seen
+
+
+@pytest.mark.parametrize("bits,T", [(4, 650), (3, 330)])
+def test_block_groupwise_copies_beside_dx(gpu, oracle, bits, T):
+    """The transposed copies in the auxiliary workgroups of the dX launch: tiles for two or four turns of every wave, so that a wave goes on
+    to another item's and from X to dY; the last 64 tokens are ten, the rest zeros."""
+    from paper_2305_14152_amd import peqa
+    print("copies beside dX bits=%d T=%d" % (bits, T), flush=True)
+    seed = 39500 + 100 * bits + T
+    X = synth.normal_bf16(seed, (T, 1024), 1.0)
+    members = [Member(gpu, oracle, seed + 50 * j, bits, N, K, group, T, X=x, with_ds=j != 1)
+               for j, (N, K, group, x) in enumerate([(2304, 1024, 128, X), (1280, 2176, 64, None), (256, 1024, 256, X), (1152, 1408, 128, None)])]
+    assert ((T + 63) // 64) * sum(c // 64 for c in (1024, 2176, 1408, 2304, 1280, 256, 1152)) > 512   # 128 workgroups of four waves
+    peqa.set_option(peqa.PEQA_OPT_GEMM_WAVES, 4)                   # dX and the token contractions in launches of their own
+    try:
+        dicts, seen = _traced(lambda: _run_block(gpu, members, T, backward=True))
+    finally:
+        peqa.set_option(peqa.PEQA_OPT_GEMM_WAVES, 0)
+    assert seen.get("gemm_multi_dx") == 1 and "gemm_bwd" not in seen and "transpose_pad" not in seen, seen
+    for m, d in zip(members, dicts):
+        dXref, gref, _ = oracle.bwd(m.codes, m.s0, m.ds, m.z0, m.X, m.dY, m.group)
+        assert np.abs(gpu.bf16_dev_to_f64(d["dX"]) - dXref).max() <= Y_TOL * np.abs(dXref).max(), (m.N, m.K)
+        gpu.assert_scale_grad_close(gpu.to_host(d["d_ds"]), gref)
+
+
+@pytest.mark.parametrize("bits,T", [(3, 70), (4, 333)])
+def test_block_groupwise_one_launch_of_many_tiles(gpu, oracle, bits, T):
+    """More than eight tiles per unit and at most 1536 tokens: dX and the token contractions of all items in one launch, two of them on
+    one input, one with groups whose chunks are added up afterwards.  dX on sampled rows, the gradients on a channel of every 128."""
+    print("one launch of many tiles bits=%d T=%d" % (bits, T), flush=True)
+    seed = 39700 + 100 * bits + T
+    X = synth.normal_bf16(seed, (T, 4096), 1.0)
+    members = [Member(gpu, oracle, seed + 50 * j, bits, N, K, group, T, X=x, with_ds=j != 1)
+               for j, (N, K, group, x) in enumerate([(11008, 4096, 128, X), (4096, 4096, 64, X), (4096, 2048, 256, None)])]
+    assert sum(m.K // 128 * (m.N // 256) for m in members) > 8 * 256
+    dicts, seen = _traced(lambda: _run_block(gpu, members, T, backward=True))
+    assert seen.get("gemm_bwd") == 1 and "gemm_multi_dx" not in seen and "gemm_dw" not in seen, seen
+    rng = np.random.default_rng(seed)
+    ts = np.unique(np.r_[0, T - 1, 63, 64, T // 128 * 128, rng.integers(0, T, 6)])
+    for m, d in zip(members, dicts):
+        dX = gpu.bf16_dev_to_f64(d["dX"])
+        dXref, _, _ = oracle.bwd(m.codes, m.s0, m.ds, m.z0, m.X[ts], m.dY[ts], m.group, want_P=False)
+        assert np.abs(dX[ts] - dXref).max() <= Y_TOL * np.abs(dXref).max(), (m.N, m.K)
+        assert (np.abs(dX).reshape(T, m.K // 128, 128).max(axis=2) > 0).all()
+        ns = np.arange(0, m.N, 128) + rng.integers(0, 128, m.N // 128)
+        _, gref, _ = oracle.bwd(m.codes[ns], m.s0[ns], None if m.ds is None else m.ds[ns], m.z0[ns], m.X,
+                                np.ascontiguousarray(m.dY[:, ns]), m.group, want_dX=False)
+        g = gpu.to_host(d["d_ds"]).astype(np.float64)
+        gpu.assert_scale_grad_close(g[ns], gref)
+        assert np.isfinite(g).all() and (np.abs(g).reshape(m.N // 128, -1).max(axis=1) > 0).all()
+
+
 def test_block_groupwise_graph_capture(gpu, oracle):
     """The block calls on group-wise layers captured in a HIP graph: replays equal the eager results bit for bit."""
     import torch

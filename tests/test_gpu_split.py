@@ -198,7 +198,7 @@ def _small_batch_form(peqa, shapes, bits, group, T):
 
 
 def _small_batch_narrow(peqa, shapes, bits, group, T):
-    """The layers of that plan whose tiles are half as wide, a bit each."""
+    """The layers of that plan whose tiles are half as wide, a bit each.  group: of every layer, or a list."""
     import ctypes
 
     class Form(ctypes.Structure):
@@ -207,8 +207,9 @@ def _small_batch_narrow(peqa, shapes, bits, group, T):
     plan = peqa.lib()._ZN4peqa9gemv_planEiPKiS1_S1_iibmiPi
     plan.restype = Form
     ints = ctypes.c_int * len(shapes)
+    groups = group if isinstance(group, list) else [group] * len(shapes)
     return plan(len(shapes), ints(*[n for n, _ in shapes]), ints(*[k for _, k in shapes]),
-                ints(*[group or k for _, k in shapes]), bits, T, True, ctypes.c_size_t(2 ** 64 - 1), 256, ints()).narrow
+                ints(*[g or k for g, (_, k) in zip(groups, shapes)]), bits, T, True, ctypes.c_size_t(2 ** 64 - 1), 256, ints()).narrow
 
 
 @pytest.mark.parametrize("bits,group", [(4, 0), (3, 0), (4, 64), (3, 128)])
@@ -316,6 +317,38 @@ def test_small_batch_narrow_tiles(gpu, oracle, bits):
         h, waves, S = _small_batch_form(peqa, shapes, bits, 0, T)
         assert (h, waves) == (1, 4) and _small_batch_narrow(peqa, shapes, bits, 0, T) == (0b1100 if T <= 8 else 0)
         assert S[2] > 1 and S[3] > 1 if T > 8 else S == [1] * 4
+        for j, d in enumerate(dicts):
+            d["X"] = gpu.to_dev(Xs[j][:T])
+            d["Y"] = torch.zeros((T, shapes[j][0]), dtype=torch.int16, device="cuda")
+        items = peqa.block_items(dicts)
+        nb = peqa.block_workspace_bytes(items, T, peqa.PEQA_OP_FWD)
+        ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+        peqa.block_fwd(items, T, ws, nb)
+        torch.cuda.synchronize()
+        for d, ref in zip(dicts, refs):
+            assert (np.abs(gpu.bf16_dev_to_f64(d["Y"]) - ref[:T]) <= 2.0 ** -8 * np.abs(ref[:T]) + 1e-4 * np.abs(ref[:T]).max()).all()
+
+
+@pytest.mark.parametrize("bits,K,long_K", [(4, 1024, 2816), (3, 1664, 4224)])
+def test_small_batch_narrow_tiles_beside_groups(gpu, oracle, bits, K, long_K):
+    """Group-wise layers set the LDS of a launch that also has a long per-channel layer in narrow tiles, whose rings take what room
+    there is: with 16 groups of 64 three rounds, with 26 four.  Tolerance as above."""
+    import torch
+    from paper_2305_14152_amd import peqa
+    shapes, groups = [(32768, K), (2048, long_K), (256, K)], [64, 0, 128]
+    dicts, refs, Xs = [], [], []
+    for j, ((N, k), group) in enumerate(zip(shapes, groups)):
+        seed = 78500 + bits * 1000 + 10 * j
+        W = synth.normal_f32(seed, (N, k), 0.02)
+        codes, s0, z0 = oracle.quantize(W, bits, group)
+        ds = synth.normal_f32(seed + 1, s0.shape, 1e-3)
+        layer = gpu.GpuLayer(W, bits, group)
+        Xs.append(synth.normal_bf16(seed + 2, (8, k), 1.0))
+        refs.append(oracle.fwd(codes, s0, ds, z0, Xs[j], group))
+        dicts.append(dict(L=layer.L, packed=layer.packed, s0=layer.s0, z0=layer.z0, ds=gpu.to_dev(ds)))
+    for T in (1, 5, 8):
+        print("narrow tiles beside groups bits=%d K=%d T=%d" % (bits, K, T), flush=True)
+        assert _small_batch_narrow(peqa, shapes, bits, groups, T) == 0b010
         for j, d in enumerate(dicts):
             d["X"] = gpu.to_dev(Xs[j][:T])
             d["Y"] = torch.zeros((T, shapes[j][0]), dtype=torch.int16, device="cuda")
