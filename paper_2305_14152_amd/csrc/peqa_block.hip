@@ -391,7 +391,7 @@ peqa_status peqa_block_bwd(int32_t n, const peqa_block_item *items, int32_t T, v
     // First launch: every scale-gradient contraction, and in its auxiliary workgroups the scaling of dY for every
     // dX contraction.  Second launch: every dX contraction, and the fixed-order sums of the first launch's partials.
     peqa::MultiArgs ma{}, mb{};
-    int sdy_blocks = 0, red_chunks = 0;
+    int red_chunks = 0;
     for (int j = 0; j < n; ++j) {
         const peqa_block_item &it = items[j];
         if (grouped(&it.layout)) continue;
@@ -419,8 +419,6 @@ peqa_status peqa_block_bwd(int32_t n, const peqa_block_item *items, int32_t T, v
         if (it.dX) {
             peqa::ScaleDyJob &sd = ma.sdy[ma.n_sdy++];
             sd.dY = it.dY; sd.s0 = it.s0; sd.ds = it.ds; sd.z0 = it.z0; sd.dYs = dys; sd.crow = crow; sd.T = T; sd.N = N;
-            sdy_blocks += (T + peqa::AUX_SDY_ROWS - 1) / peqa::AUX_SDY_ROWS;
-            sd.blk_end = sdy_blocks;
             peqa::MultiJob &job = mb.job[mb.n_jobs++];
             job.mode = peqa::MODE_DX;
             peqa::GemmArgs &a = job.a;

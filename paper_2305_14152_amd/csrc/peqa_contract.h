@@ -105,8 +105,8 @@ __device__ __forceinline__ void multi_aux_copies(int n_tp, int aux_wgs, int w, u
     }
 }
 
-// Per channel: one index space, first the AUX_SDY_ROWS-row blocks of the scale_dy jobs, then the 256-element chunks of the reduce jobs.
-template <bool AHEAD>
+// Per channel: one index space, first the SDY_ROWS-row blocks of the scale_dy jobs, then the 256-element chunks of the reduce jobs.
+template <int SDY_ROWS>
 __device__ __forceinline__ void multi_aux(int n_sdy, int n_red, int aux_wgs, int w, uint8_t *lds)
 {
     float *red = reinterpret_cast<float *>(lds);
@@ -124,7 +124,7 @@ __device__ __forceinline__ void multi_aux(int n_sdy, int n_red, int aux_wgs, int
                 if (u >= e) { j = i + 1; b0 = e; }
             }
             const ScaleDyJob J = kernarg_load<ScaleDyJob>(SDY0 + (uint32_t)(j * sizeof(ScaleDyJob)));
-            scale_dy_rows<AUX_SDY_ROWS, AHEAD>(J.dY, J.s0, J.ds, J.z0, nullptr, J.T, J.N, J.dYs, J.crow, u - b0, red);
+            scale_dy_rows<SDY_ROWS>(J.dY, J.s0, J.ds, J.z0, nullptr, J.T, J.N, J.dYs, J.crow, u - b0, red);
             __syncthreads();                                   // `red` is reused by the next block
         } else {
             const int c = u - n_blk;
@@ -145,10 +145,10 @@ __device__ __forceinline__ void multi_aux(int n_sdy, int n_red, int aux_wgs, int
 // scale gradient is the token contraction of peqa_dw.hip).
 //
 // Per-channel tiles of 64 rows have 48 KB of LDS and 64 accumulators: three workgroups fit a unit as long as the kernel takes no
-// more than 104 registers besides.  With the copies' two tiles in flight and the scaling's two sets of columns compiled in it took 127
-// (82 and 92 without), and blocks of 513 to 768 workgroups a second round.  Blocks of d = 8192, f = 22016 (752 and 760 workgroups), us,
-// two on a unit -> three: forward at T = 17 / 32 107.9 / 116.5 -> 104.2 / 111.9, training step 337 / 351 -> 308 / 330; d = 6656, 3 bits,
-// T = 17 216 -> 210.  At T = 64, where a tile has as much to compute as to wait for, 394 -> 393 and, d = 6656, 289 -> 296.
+// more than 104 registers besides.  With the copies' two tiles in flight and the scaling of eight rows compiled in it took 127 (92
+// without), and blocks of 513 to 768 workgroups a second round.  Blocks of d = 8192, f = 22016 (752 and 760 workgroups), us, two on a
+// unit -> three: forward at T = 17 / 32 107.9 / 116.5 -> 104.2 / 111.9, training step 329 / 346 -> 302 / 322; d = 6656, f = 17920, T = 32
+// 237 -> 230.
 template <int BITS, int GMODE, int RT>
 __global__ __launch_bounds__(256, 2) void gemm_multi_kernel(MultiArgs m)
 {
@@ -157,7 +157,7 @@ __global__ __launch_bounds__(256, 2) void gemm_multi_kernel(MultiArgs m)
     if constexpr (GMODE != MODE_Y) {                           // a group-wise forward has no side work
         if (b >= m.aux_begin) {
             if (b < m.aux_begin + m.aux_wgs) {
-                if constexpr (GMODE < 0) multi_aux<RT != 4>(m.n_sdy, m.n_red, m.aux_wgs, b - m.aux_begin, lds);
+                if constexpr (GMODE < 0) multi_aux<aux_sdy_rows(RT)>(m.n_sdy, m.n_red, m.aux_wgs, b - m.aux_begin, lds);
                 else multi_aux_copies(m.n_tp, m.aux_wgs, b - m.aux_begin, lds);
                 return;
             }

@@ -178,12 +178,16 @@ __device__ __forceinline__ void global_store(void *p, const T &v)
 // contraction exactly), for the ROWS token rows of row block `blk`, by one workgroup of 256 threads
 // (the per-channel parameters are read once per ROWS rows).  `red` is 4 ROWS floats of LDS.  Rows do not mix.
 //
-// Bound by latency: what a workgroup has in flight is ROWS x 4 KB.  Four rows where there are workgroups enough to fill the machine (a launch
-// of its own), eight beside matrix work, where every place that the scaling holds for longer is one less for tiles, and half as
-// many workgroups: backward of a 7B block 1218 -> 1190 us; dX alone with the scaling before it 649 -> 636.  (The next columns asked for
-// early, with four rows: the same.  Sixteen rows: the registers do not hold them.)  AHEAD: with two sets of columns in registers; not
-// beside tiles of 64 rows, whose third workgroup on a unit they would cost (gemm_multi_kernel).
-template <int ROWS, bool AHEAD>
+// Bound by latency: what a workgroup has in flight is ROWS x 4 KB, and the next columns are asked for before these are scaled (a launch
+// of its own: 104 registers instead of 70, 2048 x 11008 19.4 -> 18.4 us, 500 x 11008 11.2 -> 10.9, 4096 x 22016 and 1000 x 16384 the same).
+// Four rows where there are workgroups enough to fill the machine (a launch of its own), eight beside matrix work, where every
+// place that the scaling holds for longer is one less for tiles, and half as many workgroups: backward of a 7B block 1218 -> 1190 us;
+// dX alone with the scaling before it 649 -> 636.  (Sixteen rows: the registers do not hold them.)  Two beside tiles of 64 rows, where
+// there are no more than 64 tokens, which four or eight rows deal to few workgroups, and where two sets of columns of eight rows take the
+// registers of a third workgroup on the unit (gemm_multi_kernel).  Training steps, us, eight rows and one set / four / two: d = 2048,
+// f = 7040, T = 47 67.0 / 62.4 / 62.8, d = 2432, f = 7552, T = 18 70.6 / 66.1 / 64.4, d = 6656, f = 17920, T = 64 288 / 282 / 276,
+// d = 8192, f = 22016, T = 64 388 / 386 / 383.
+template <int ROWS>
 __device__ __forceinline__ void scale_dy_rows(const uint16_t *__restrict__ dY, const float *__restrict__ s0,
                                               const float *__restrict__ ds, const uint8_t *__restrict__ z0,
                                               const float *__restrict__ dz, int T, int N, uint16_t *__restrict__ dYs,
@@ -216,17 +220,12 @@ __device__ __forceinline__ void scale_dy_rows(const uint16_t *__restrict__ dY, c
             k.zb = global_load<f32x4>(dz + 8 * n8 + 4);
         }
     };
-    // AHEAD: the next columns (and their parameters: loads arrive in order) are on their way while these are scaled
+    // the next columns (and their parameters: loads arrive in order) are on their way while these are scaled
     Columns ahead;
-    if (AHEAD && tid < n8s) load(tid, ahead);
+    if (tid < n8s) load(tid, ahead);
     for (int n8 = tid; n8 < n8s; n8 += 256) {
-        Columns k;
-        if constexpr (AHEAD) {
-            k = ahead;
-            if (n8 + 256 < n8s) load(n8 + 256, ahead);
-        } else {
-            load(n8, k);
-        }
+        const Columns k = ahead;
+        if (n8 + 256 < n8s) load(n8 + 256, ahead);
         float s[8] = {k.sa[0], k.sa[1], k.sa[2], k.sa[3], k.sb[0], k.sb[1], k.sb[2], k.sb[3]};
         float zo[8];
 #pragma unroll

@@ -367,6 +367,7 @@ hipError_t launch_gemm_multi(int bits, bool grouped, MultiArgs &m, hipStream_t s
         m.job[j].wg_end = total;
     }
     if (grouped ? m.n_sdy + m.n_red > 0 : m.n_tp > 0) return hipErrorInvalidValue;   // (multi_aux)
+    for (int j = 0, blocks = 0; j < m.n_sdy; ++j) m.sdy[j].blk_end = blocks += (m.sdy[j].T + aux_sdy_rows(rt) - 1) / aux_sdy_rows(rt);
     if ((m.aux_begin & 7) || (m.aux_wgs & 7) || m.aux_begin < 0 || m.aux_begin > total) return hipErrorInvalidValue;
     if (total + m.aux_wgs == 0) return hipSuccess;
     const int mode0 = m.n_jobs > 0 ? m.job[0].mode : MODE_DX;

@@ -123,7 +123,8 @@ struct MultiJob {
     int mode;                 // MODE_Y, MODE_DDS or MODE_DX
     int wg_end;               // tile workgroups of this job and all before it (unused entries: the total)
 };
-constexpr int AUX_SDY_ROWS = 8;       // token rows per row block of the scaling in auxiliary workgroups
+// Token rows per row block of the scaling in the auxiliary workgroups of a launch whose tiles have rt row tiles (see scale_dy_rows).
+constexpr int aux_sdy_rows(int rt) { return rt == 4 ? 2 : 8; }
 struct ScaleDyJob {           // dYs = bf16(dY (s0 + ds)), crow[t] = sum_i dYs[t,i] (16 + z0[i])   (scale_dy_rows)
     const uint16_t *dY;
     const float *s0, *ds;
@@ -131,7 +132,7 @@ struct ScaleDyJob {           // dYs = bf16(dY (s0 + ds)), crow[t] = sum_i dYs[t
     uint16_t *dYs;
     float *crow;
     int T, N;
-    int blk_end;              // row blocks (of AUX_SDY_ROWS rows) of this job and all before it
+    int blk_end;              // row blocks (of aux_sdy_rows rows) of this job and all before it (set by the launch)
 };
 struct ReduceJob {            // out[j] = sum over ntiles of partial[tile][j], fixed order
     const float *partial;

@@ -220,7 +220,7 @@ __global__ __launch_bounds__(256) void scale_dy_kernel(const uint16_t *__restric
         else reduce_partials_at(partial, ntiles, n_red, (size_t)(past - sum_blocks) * 256 + threadIdx.x, red_out);
         return;
     }
-    scale_dy_rows<SDY_ROWS, true>(dY, s0, ds, z0, dz, T, N, dYs, crow, (int)blockIdx.x, red);
+    scale_dy_rows<SDY_ROWS>(dY, s0, ds, z0, dz, T, N, dYs, crow, (int)blockIdx.x, red);
 }
 
 // Scale gradient from the product P[t,i] = sum_k X[t,k] (Q[i,k] - z0[i]) that the forward kept:

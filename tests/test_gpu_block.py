@@ -114,6 +114,31 @@ def test_block_backward_parity(gpu, oracle, bits, group, shapes, T):
             gpu.assert_scale_grad_close(gpu.to_host(d["d_ds"]), gref)
 
 
+@pytest.mark.parametrize("bits,T", [(4, 17), (3, 63), (4, 64), (3, 65), (4, 71)])
+def test_block_scaling_of_dY(gpu, oracle, bits, T):
+    """The scaling of dY in the auxiliary workgroups: two token rows at a time beside scale-gradient tiles of 64 rows, eight beside others
+    and where no scale gradient is asked for; the last rows of an odd T, layers of one and of several turns over the channels.  dX
+    has the same bits either way."""
+    import torch
+    from paper_2305_14152_amd import peqa
+    print("block scaling bits=%d T=%d" % (bits, T), flush=True)
+    seed = 34200 + 100 * bits + T
+    members = [Member(gpu, oracle, seed + 50 * j, bits, N, K, 0, T, with_ds=j % 2 == 0)
+               for j, (N, K) in enumerate([(4224, 256), (128, 384), (2048, 128)])]
+    full = _run_block(gpu, members, T, backward=True)
+    dicts = [dict(L=m.layer.L, packed=m.layer.packed, s0=m.layer.s0, z0=m.layer.z0, ds=m.dsd, dY=gpu.to_dev(m.dY),
+                  dX=torch.zeros((T, m.K), dtype=torch.int16, device="cuda")) for m in members]
+    items = peqa.block_items(dicts)
+    nb = peqa.block_workspace_bytes(items, T, peqa.PEQA_OP_BWD)
+    peqa.block_bwd(items, T, torch.empty(nb, dtype=torch.uint8, device="cuda"), nb)
+    torch.cuda.synchronize()
+    for m, d, only in zip(members, full, dicts):
+        dXref, gref, _ = oracle.bwd(m.codes, m.s0, m.ds, m.z0, m.X, m.dY, 0)
+        assert np.abs(gpu.bf16_dev_to_f64(d["dX"]) - dXref).max() <= Y_TOL * np.abs(dXref).max(), (m.N, m.K)
+        gpu.assert_scale_grad_close(gpu.to_host(d["d_ds"]), gref)
+        assert (gpu.to_host(only["dX"]) == gpu.to_host(d["dX"])).all()
+
+
 @pytest.mark.parametrize("bits", [4, 3])
 @pytest.mark.parametrize("T", [1, 7, 16])
 def test_block_step_of_few_tokens_with_row_sums(gpu, oracle, bits, T):
