@@ -253,7 +253,7 @@ struct GroupPrep {
     TransposeJob tp[2 * MULTI_MAX_JOBS];   // tile_end: running totals
     const float *dz;                       // of the only table, or NULL
     int table_end[GT_MAX];                 // set by the launch
-    int n_tp, by_tiles;
+    int n_tp, whole_rows;
 };
 hipError_t launch_group_prep(GroupPrep &a, hipStream_t stream);
 

@@ -105,22 +105,9 @@ __global__ __launch_bounds__(256) void rowsum_groups_kernel(const uint16_t *__re
     }
 }
 
-// Entry j = n * G + g of the per-group table from which the grouped contractions take their scales, with
-// s = (s0 + ds)[n, g] and z = (z0 + dz)[n, g].
+// The per-group table from which the grouped contractions take their scales, with s = (s0 + ds)[n, g] and z = (z0 + dz)[n, g]:
 //   sb[g][n] = (s, -s (16 + z)): the weights are scaled in the loop (forward, dX)
-__device__ __forceinline__ void group_table_entry(const float *__restrict__ s0, const float *__restrict__ ds,
-                                                  const uint8_t *__restrict__ z0, const float *__restrict__ dz, int N,
-                                                  int G, float *__restrict__ sb, size_t j)
-{
-    const size_t n = j / G, g = j - n * G;
-    const float s = ds ? s0[j] + ds[j] : s0[j];
-    const float zoff = kCodeOffset + (float)z0[j] + (dz ? dz[j] : 0.f);
-    float *o = sb + (g * N + n) * 2;
-    o[0] = s;
-    o[1] = -s * zoff;
-}
-
-// The same table by workgroups of GT_CH channels x all groups, through LDS: memory has a channel's groups next to each
+// by workgroups of GT_CH channels x all groups, through LDS: memory has a channel's groups next to each
 // other and the table a group's channels, so entry by entry every 8-byte write is a transaction of its own (25 us for
 // the four tables of a 13B block); here the reads run along the groups, four entries a thread, and the writes along the channels,
 // 128 bytes per group.  `lds`: 2 x GT_CH x (G | 1) floats: with rows of an odd length a group's channels are in different banks.
@@ -161,6 +148,35 @@ __device__ __forceinline__ void group_table_tile(const float *__restrict__ s0, c
     }
 }
 
+// The same by workgroups of GT_CH channels x GT_PART groups, numbered along the groups first: where all groups do not fit in LDS.  (Entry
+// by entry, as before, 161 us for the seven tables of a block of d = 8064, f = 25600 in groups of 64, 57 so; forward at T = 52 332 -> 230.)
+constexpr int GT_PART = 128;
+__device__ __forceinline__ void group_table_part(const float *__restrict__ s0, const float *__restrict__ ds,
+                                                 const uint8_t *__restrict__ z0, const float *__restrict__ dz, int N, int G,
+                                                 float *__restrict__ sb, int wg, float *lds)
+{
+    const int parts = (G + GT_PART - 1) / GT_PART, n0 = wg / parts * GT_CH, g0 = wg % parts * GT_PART;
+    const int gn = min(GT_PART, G - g0);
+    constexpr int row = GT_PART | 1;
+    float *s_l = lds, *z_l = lds + GT_CH * row;
+#pragma unroll
+    for (int e = threadIdx.x; e < GT_CH * GT_PART; e += 256) {
+        const int nl = e / GT_PART, g = e % GT_PART;
+        const size_t at = (size_t)(n0 + nl) * G + g0 + min(g, gn - 1);     // past the end: the last one again, not written
+        s_l[nl * row + g] = ds ? s0[at] + ds[at] : s0[at];
+        z_l[nl * row + g] = kCodeOffset + (float)z0[at] + (dz ? dz[at] : 0.f);
+    }
+    __syncthreads();
+    const int nl = threadIdx.x % GT_CH, n = n0 + nl;
+    for (int g = threadIdx.x / GT_CH; g < gn; g += 256 / GT_CH) {
+        const float s = s_l[nl * row + g], zoff = z_l[nl * row + g];
+        f32x2 o;
+        o[0] = s;
+        o[1] = -s * zoff;
+        *reinterpret_cast<f32x2 *>(sb + ((size_t)(g0 + g) * N + n) * 2) = o;
+    }
+}
+
 // Tables of group-wise layers and, for a backward, transposed copies (GroupPrep): the tables' workgroups first, then one per four 64 x 64 tiles of
 // the copies.  One launch where there were two, of 3 us and more each.
 __global__ __launch_bounds__(256) void group_prep_kernel(GroupPrep a)
@@ -178,12 +194,8 @@ __global__ __launch_bounds__(256) void group_prep_kernel(GroupPrep a)
                 s0 = a.table.s0[i]; ds = a.table.ds[i]; z0 = a.table.z0[i]; sb = a.table.sb[i]; N = a.table.N[i]; G = a.table.G[i];
                 b0 = a.table_end[i - 1];
             }
-        if (a.by_tiles) {
-            group_table_tile(s0, ds, z0, a.dz, N, G, sb, (b - b0) * GT_CH, gt_lds);
-        } else {
-            const size_t j = (size_t)(b - b0) * 256 + threadIdx.x;
-            if (j < (size_t)N * G) group_table_entry(s0, ds, z0, a.dz, N, G, sb, j);
-        }
+        if (a.whole_rows) group_table_tile(s0, ds, z0, a.dz, N, G, sb, (b - b0) * GT_CH, gt_lds);
+        else group_table_part(s0, ds, z0, a.dz, N, G, sb, b - b0, gt_lds);
         return;
     }
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -445,8 +457,9 @@ hipError_t launch_rowsum_groups(const uint16_t *X, int T, int K, int gsz, float 
     return hipGetLastError();
 }
 
-// LDS that the tile form takes at most
-constexpr int GT_TILE_MAX_LDS = 49 * 1024;   // 391 groups
+// Groups of a layer up to which workgroups take whole rows of them (49 KB of LDS)
+constexpr int GT_TILE_MAX_G = 391;
+static_assert(gt_tile_bytes(GT_TILE_MAX_G) <= 49 * 1024, "what a launch may ask for without an attribute");
 
 hipError_t launch_group_table(const float *s0, const float *ds, const uint8_t *z0, const float *dz, int N, int G,
                               float *sb, hipStream_t stream)
@@ -464,14 +477,14 @@ hipError_t launch_group_prep(GroupPrep &a, hipStream_t stream)
     if (n < 0 || n > GT_MAX || a.n_tp < 0 || a.n_tp > 2 * MULTI_MAX_JOBS || (a.dz && n != 1)) return hipErrorInvalidValue;
     int gmax = 0, blocks = 0;
     for (int i = 0; i < n; ++i) gmax = a.table.G[i] > gmax ? a.table.G[i] : gmax;
-    a.by_tiles = gt_tile_bytes(gmax) <= GT_TILE_MAX_LDS;
+    a.whole_rows = gmax <= GT_TILE_MAX_G;
     for (int i = 0; i < GT_MAX; ++i) {
-        if (i < n) blocks += a.by_tiles ? a.table.N[i] / GT_CH : (int)(((size_t)a.table.N[i] * a.table.G[i] + 255) / 256);
+        if (i < n) blocks += a.table.N[i] / GT_CH * (a.whole_rows ? 1 : (a.table.G[i] + GT_PART - 1) / GT_PART);
         a.table_end[i] = blocks;
     }
     const int tp = a.n_tp > 0 ? a.tp[a.n_tp - 1].tile_end : 0;
     if (blocks + tp == 0) return hipSuccess;
-    const int table_lds = a.by_tiles ? gt_tile_bytes(gmax) : 0, tp_lds = tp > 0 ? 4 * TRANSPOSE_LDS : 0;
+    const int table_lds = gt_tile_bytes(a.whole_rows ? gmax : GT_PART), tp_lds = tp > 0 ? 4 * TRANSPOSE_LDS : 0;
     trace_before(KID_GROUP_TABLE, stream);
     hipLaunchKernelGGL(group_prep_kernel, dim3(blocks + (tp + 3) / 4), dim3(256), table_lds > tp_lds ? table_lds : tp_lds, stream, a);
     trace_after(KID_GROUP_TABLE, stream);

@@ -492,6 +492,44 @@ def test_many_groups_and_many_slices(gpu, oracle, K, group):
             assert _small_batch_form(peqa, [(N, K)], bits, group, T)[2] == [12]
 
 
+@pytest.mark.parametrize("bits,T", [(3, 17), (4, 40)])
+def test_tables_of_many_groups(gpu, oracle, bits, T):
+    """A layer of more groups than a workgroup's LDS holds (400 of 64: three runs of 128 and 16 more), beside one of few and odd (29): the tables of
+    both in one launch, with a trained zero-point in a launch of its own; forward and backward against the oracle."""
+    import torch
+    from paper_2305_14152_amd import peqa
+    print("tables of many groups bits=%d T=%d" % (bits, T), flush=True)
+    dicts, refs = [], []
+    for j, (N, K, group) in enumerate([(256, 25600, 64), (128, 7424, 256)]):
+        seed = 79300 + 1000 * bits + T + 10 * j
+        W = synth.normal_f32(seed, (N, K), 0.02)
+        X, dY = synth.normal_bf16(seed + 1, (T, K), 1.0), synth.normal_bf16(seed + 2, (T, N), 1.0)
+        layer = gpu.GpuLayer(W, bits, group)
+        codes, s0, z0 = oracle.quantize(W, bits, group)
+        ds, dz = synth.normal_f32(seed + 3, s0.shape, 1e-3), synth.normal_f32(seed + 4, s0.shape, 0.5)
+        refs.append((oracle.fwd(codes, s0, ds, z0, X, group),) + tuple(oracle.bwd(codes, s0, ds, z0, X, dY, group)[:2]))
+        dicts.append(dict(L=layer.L, packed=layer.packed, s0=layer.s0, z0=layer.z0, ds=gpu.to_dev(ds), X=gpu.to_dev(X), dY=gpu.to_dev(dY),
+                          Y=torch.zeros((T, N), dtype=torch.int16, device="cuda"), dX=torch.zeros((T, K), dtype=torch.int16, device="cuda"),
+                          d_ds=torch.zeros(s0.shape, dtype=torch.float32, device="cuda")))
+        Yz = oracle.fwd_z(codes, s0, ds, z0, dz, X, group)
+        assert np.abs(gpu.bf16_dev_to_f64(layer.fwd_z(X, ds, dz)) - Yz).max() <= Y_TOL * np.abs(Yz).max()
+        dXz, gz, ddz = layer.bwd_z(X, dY, ds, dz)
+        dXzref, gzref, ddzref = oracle.bwd_z(codes, s0, ds, z0, dz, X, dY, group)
+        assert np.abs(gpu.bf16_dev_to_f64(dXz) - dXzref).max() <= Y_TOL * np.abs(dXzref).max()
+        gpu.assert_scale_grad_close(gpu.to_host(gz), gzref)
+        gpu.assert_scale_grad_close(gpu.to_host(ddz), ddzref, "d_dz")
+    items = peqa.block_items(dicts)
+    nb = max(peqa.block_workspace_bytes(items, T, op) for op in (peqa.PEQA_OP_FWD, peqa.PEQA_OP_BWD))
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    peqa.block_fwd(items, T, ws, nb)
+    peqa.block_bwd(items, T, ws, nb)
+    torch.cuda.synchronize()
+    for d, (Yref, dXref, gref) in zip(dicts, refs):
+        assert np.abs(gpu.bf16_dev_to_f64(d["Y"]) - Yref).max() <= Y_TOL * np.abs(Yref).max()
+        assert np.abs(gpu.bf16_dev_to_f64(d["dX"]) - dXref).max() <= Y_TOL * np.abs(dXref).max()
+        gpu.assert_scale_grad_close(gpu.to_host(d["d_ds"]), gref)
+
+
 def test_group_wise_backward_of_many_tiles_and_few_tokens(gpu):
     """More than eight tiles per unit and at most 1536 tokens: dX and the token contraction in one launch, against a launch each
     (PEQA_OPT_GEMM_WAVES = 4).  The scale gradients are sums in the same order; a piece of dX may be added in another."""
