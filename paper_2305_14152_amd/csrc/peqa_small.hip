@@ -177,6 +177,25 @@ __device__ __forceinline__ void group_table_part(const float *__restrict__ s0, c
     }
 }
 
+// A workgroup's share of a layer's table: whole rows of groups, or runs of GT_PART.
+__device__ __forceinline__ void group_table_share(const float *__restrict__ s0, const float *__restrict__ ds,
+                                                  const uint8_t *__restrict__ z0, const float *__restrict__ dz, int N, int G,
+                                                  float *__restrict__ sb, int wg, bool whole_rows, float *lds)
+{
+    if (whole_rows) group_table_tile(s0, ds, z0, dz, N, G, sb, wg * GT_CH, lds);
+    else group_table_part(s0, ds, z0, dz, N, G, sb, wg, lds);
+}
+
+// The table of one layer.  (As group_prep_kernel's only table it waits for the descriptors of eight: 512 x 256 in groups of 128 3.4 us,
+// 2.7 so, of a training step of 27.)
+__global__ __launch_bounds__(256) void group_table_kernel(const float *__restrict__ s0, const float *__restrict__ ds,
+                                                           const uint8_t *__restrict__ z0, const float *__restrict__ dz, int N, int G,
+                                                           float *__restrict__ sb, int whole_rows)
+{
+    extern __shared__ __align__(16) float gt_lds[];
+    group_table_share(s0, ds, z0, dz, N, G, sb, (int)blockIdx.x, whole_rows != 0, gt_lds);
+}
+
 // Tables of group-wise layers and, for a backward, transposed copies (GroupPrep): the tables' workgroups first, then one per four 64 x 64 tiles of
 // the copies.  One launch where there were two, of 3 us and more each.
 __global__ __launch_bounds__(256) void group_prep_kernel(GroupPrep a)
@@ -194,8 +213,7 @@ __global__ __launch_bounds__(256) void group_prep_kernel(GroupPrep a)
                 s0 = a.table.s0[i]; ds = a.table.ds[i]; z0 = a.table.z0[i]; sb = a.table.sb[i]; N = a.table.N[i]; G = a.table.G[i];
                 b0 = a.table_end[i - 1];
             }
-        if (a.whole_rows) group_table_tile(s0, ds, z0, a.dz, N, G, sb, (b - b0) * GT_CH, gt_lds);
-        else group_table_part(s0, ds, z0, a.dz, N, G, sb, b - b0, gt_lds);
+        group_table_share(s0, ds, z0, a.dz, N, G, sb, b - b0, a.whole_rows != 0, gt_lds);
         return;
     }
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -461,14 +479,19 @@ hipError_t launch_rowsum_groups(const uint16_t *X, int T, int K, int gsz, float 
 constexpr int GT_TILE_MAX_G = 391;
 static_assert(gt_tile_bytes(GT_TILE_MAX_G) <= 49 * 1024, "what a launch may ask for without an attribute");
 
+// workgroups of a layer's table, and their LDS
+static int table_wgs(int N, int G, bool whole_rows) { return N / GT_CH * (whole_rows ? 1 : (G + GT_PART - 1) / GT_PART); }
+static int table_lds(int G, bool whole_rows) { return gt_tile_bytes(whole_rows ? G : GT_PART); }
+
 hipError_t launch_group_table(const float *s0, const float *ds, const uint8_t *z0, const float *dz, int N, int G,
                               float *sb, hipStream_t stream)
 {
-    GroupPrep a{};
-    a.table.s0[0] = s0; a.table.ds[0] = ds; a.table.z0[0] = z0; a.table.sb[0] = sb; a.table.N[0] = N; a.table.G[0] = G;
-    a.table.n = 1;
-    a.dz = dz;
-    return launch_group_prep(a, stream);
+    const bool whole_rows = G <= GT_TILE_MAX_G;
+    trace_before(KID_GROUP_TABLE, stream);
+    hipLaunchKernelGGL(group_table_kernel, dim3(table_wgs(N, G, whole_rows)), dim3(256), table_lds(G, whole_rows), stream, s0, ds, z0, dz,
+                       N, G, sb, whole_rows ? 1 : 0);
+    trace_after(KID_GROUP_TABLE, stream);
+    return hipGetLastError();
 }
 
 hipError_t launch_group_prep(GroupPrep &a, hipStream_t stream)
@@ -479,14 +502,14 @@ hipError_t launch_group_prep(GroupPrep &a, hipStream_t stream)
     for (int i = 0; i < n; ++i) gmax = a.table.G[i] > gmax ? a.table.G[i] : gmax;
     a.whole_rows = gmax <= GT_TILE_MAX_G;
     for (int i = 0; i < GT_MAX; ++i) {
-        if (i < n) blocks += a.table.N[i] / GT_CH * (a.whole_rows ? 1 : (a.table.G[i] + GT_PART - 1) / GT_PART);
+        if (i < n) blocks += table_wgs(a.table.N[i], a.table.G[i], a.whole_rows);
         a.table_end[i] = blocks;
     }
     const int tp = a.n_tp > 0 ? a.tp[a.n_tp - 1].tile_end : 0;
     if (blocks + tp == 0) return hipSuccess;
-    const int table_lds = gt_tile_bytes(a.whole_rows ? gmax : GT_PART), tp_lds = tp > 0 ? 4 * TRANSPOSE_LDS : 0;
+    const int tables = table_lds(gmax, a.whole_rows), copies = tp > 0 ? 4 * TRANSPOSE_LDS : 0;
     trace_before(KID_GROUP_TABLE, stream);
-    hipLaunchKernelGGL(group_prep_kernel, dim3(blocks + (tp + 3) / 4), dim3(256), table_lds > tp_lds ? table_lds : tp_lds, stream, a);
+    hipLaunchKernelGGL(group_prep_kernel, dim3(blocks + (tp + 3) / 4), dim3(256), tables > copies ? tables : copies, stream, a);
     trace_after(KID_GROUP_TABLE, stream);
     return hipGetLastError();
 }
