@@ -252,8 +252,8 @@ struct GroupPrep {
     GroupTableMulti table;
     TransposeJob tp[2 * MULTI_MAX_JOBS];   // tile_end: running totals
     const float *dz;                       // of the only table, or NULL
-    int table_end[GT_MAX];                 // set by the launch
-    int n_tp, whole_rows;
+    int table_end[GT_MAX];                 // set by the launch, as are whole_rows and copies_per_wg
+    int n_tp, whole_rows, copies_per_wg;
 };
 hipError_t launch_group_prep(GroupPrep &a, hipStream_t stream);
 

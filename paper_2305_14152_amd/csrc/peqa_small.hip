@@ -196,8 +196,8 @@ __global__ __launch_bounds__(256) void group_table_kernel(const float *__restric
     group_table_share(s0, ds, z0, dz, N, G, sb, (int)blockIdx.x, whole_rows != 0, gt_lds);
 }
 
-// Tables of group-wise layers and, for a backward, transposed copies (GroupPrep): the tables' workgroups first, then one per four 64 x 64 tiles of
-// the copies.  One launch where there were two, of 3 us and more each.
+// Tables of group-wise layers and, for a backward, transposed copies (GroupPrep): the tables' workgroups first, then those of the copies, which
+// take a 64 x 64 tile in each of one wave or four.  One launch where there were two, of 3 us and more each.
 __global__ __launch_bounds__(256) void group_prep_kernel(GroupPrep a)
 {
     extern __shared__ __align__(16) float gt_lds[];
@@ -217,7 +217,8 @@ __global__ __launch_bounds__(256) void group_prep_kernel(GroupPrep a)
         return;
     }
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    b = 4 * (b - a.table_end[GT_MAX - 1]) + wave;
+    if (wave >= a.copies_per_wg) return;
+    b = a.copies_per_wg * (b - a.table_end[GT_MAX - 1]) + wave;
     if (b >= kernarg_load<int>((uint32_t)(offsetof(GroupPrep, tp) + (a.n_tp - 1) * sizeof(TransposeJob) + offsetof(TransposeJob, tile_end)))) return;
     int j = 0, b0 = 0;
     for (int i = 0; i + 1 < a.n_tp; ++i) {
@@ -507,9 +508,16 @@ hipError_t launch_group_prep(GroupPrep &a, hipStream_t stream)
     }
     const int tp = a.n_tp > 0 ? a.tp[a.n_tp - 1].tile_end : 0;
     if (blocks + tp == 0) return hipSuccess;
-    const int tables = table_lds(gmax, a.whole_rows), copies = tp > 0 ? 4 * TRANSPOSE_LDS : 0;
+    // Every workgroup of the launch, the tables' among them, has the LDS of the copies': with four tiles five fit a unit, with one as
+    // many as there are waves for, which is what counts until the copies outlast the tables.  The launch, us, four tiles / one: blocks of
+    // d = 2048 in groups of 256, T = 64 (520 tiles) 7.0 / 5.2, T = 128 (1040) 9.0 / 6.6, T = 333 (3120) 11.3 / 10.1, T = 700 (5720) 17.9 / 16.5,
+    // T = 1400 (11440) 33.8 / 35.7; d = 4096 in groups of 128, T = 128 (2056) 13.8 / 12.5, T = 333 (6168) 24.9 / 24.8, T = 1400 (22616)
+    // 63.1 / 65.3.
+    a.copies_per_wg = tp <= 24 * compute_units() ? 1 : 4;
+    const int tables = table_lds(gmax, a.whole_rows), copies = tp > 0 ? a.copies_per_wg * TRANSPOSE_LDS : 0;
     trace_before(KID_GROUP_TABLE, stream);
-    hipLaunchKernelGGL(group_prep_kernel, dim3(blocks + (tp + 3) / 4), dim3(256), tables > copies ? tables : copies, stream, a);
+    hipLaunchKernelGGL(group_prep_kernel, dim3(blocks + (tp + a.copies_per_wg - 1) / a.copies_per_wg), dim3(256),
+                       tables > copies ? tables : copies, stream, a);
     trace_after(KID_GROUP_TABLE, stream);
     return hipGetLastError();
 }
