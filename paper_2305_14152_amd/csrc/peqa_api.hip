@@ -21,12 +21,13 @@ constexpr int PEQA_GEMV_MAX_T = GEMV_MAX_T;
 struct Workspace {
     size_t rs, dys, crow, partial, table, zpartial, xt, dyt, pc, total;
     // Pieces of the contractions (1 = whole) and the regions of their partial results.  `total` includes these regions; a
-    // workspace of at least `min_total` but less than `total` bytes is served too, with whole contractions.
+    // workspace of at least `min_total` but less than `total` bytes is served too (fit_workspace).
     size_t min_total;
+    size_t alone_total;                    // what dX in a launch of its own wants
     int split_y, split_dx, split_dds;      // split_dx, split_dds: of the backward that computes both gradients
     int split_dx_alone;
     int rt_y, rt_dx, rt_dx_alone;          // row tiles per tile of those launches
-    bool one_launch;                       // group-wise backward of both gradients: launch_gemm_dw
+    bool one_launch, many_tiles;           // group-wise backward of both gradients: launch_gemm_dw; not by bwd_few_tiles
     size_t acc, acc_dds;
     size_t gemv_most;                      // T <= 16: the most bytes that the plan's partial sums may take
 };
@@ -130,6 +131,7 @@ Workspace carve(const peqa_layout *L, int32_t T, int32_t op, int cus)
     if (grouped(L)) {
         w.rt_dx = w.rt_dx_alone;
         const long long dw_tiles = (long long)(K / 128) * ((N + 255) / 256);
+        w.many_tiles = !peqa::bwd_few_tiles((long long)tiles_t * dx.tiles_c + dw_tiles, cus);
         w.one_launch = peqa::bwd_one_launch((long long)tiles_t * dx.tiles_c + dw_tiles, T, cus);
         if (w.one_launch) {
             peqa::SplitJob beside = dx;
@@ -150,16 +152,26 @@ Workspace carve(const peqa_layout *L, int32_t T, int32_t op, int cus)
     }
     const int most_dx = w.split_dx > w.split_dx_alone ? w.split_dx : w.split_dx_alone;
     w.acc = w.total;
+    w.alone_total = w.acc + (w.split_dx_alone > 1 ? round256((size_t)w.split_dx_alone * dx_bytes) : 0);
     if (most_dx > 1) w.total += round256((size_t)most_dx * dx_bytes);
     w.acc_dds = w.total;
     if (w.split_dds > 1) w.total += round256((size_t)w.split_dds * tiles_t * N * sizeof(float));
     return w;
 }
 
-// Takes the splits back where the caller's workspace only holds the whole contractions' needs.
+// Takes the splits back where the caller's workspace only holds the whole contractions' needs.  A group-wise backward of many tiles
+// gets its launches of their own instead, with their pieces where there is room for those: whole dX chains in the shared launch outlast
+// the token tiles.  us, T = 162, shared and whole / launches of their own, whole / in pieces: 26112 x 3584 in groups of 256 340 / 294 / 131,
+// 21120 x 3584 in groups of 64 277 / 242 / 104.  (Of few tiles they mostly end sooner in the shared one, whole in either:
+// 11008 x 4096 in groups of 64, T = 922, 212 / 231.)
 void fit_workspace(Workspace &w, size_t bytes)
 {
-    if (bytes < w.total) w.split_y = w.split_dx = w.split_dds = w.split_dx_alone = 1;
+    if (bytes >= w.total) return;
+    if (w.one_launch && w.many_tiles) {
+        w.one_launch = false;
+        if (bytes >= w.alone_total) return;
+    }
+    w.split_y = w.split_dx = w.split_dds = w.split_dx_alone = 1;
 }
 
 // The regions of a call with a workspace of `bytes`, checked before the device is touched.

@@ -54,16 +54,32 @@ struct BlockSpace {
     size_t pc[PEQA_MAX_BLOCK];       //   scale gradient per 64-feature chunk [N, K / 64], groups past 128 only
     size_t total;
     // Pieces of the contractions (1 = whole) and the regions of their partial results, behind the others: `total` includes
-    // them, and a workspace of at least `min_total` bytes is served with whole contractions.
+    // them, and a workspace of at least `min_total` bytes is served too (plan_block).
     size_t min_total;
     int split_y[PEQA_MAX_BLOCK], split_dx[PEQA_MAX_BLOCK], split_dds[PEQA_MAX_BLOCK];
     int rt_y[2], rt_dx[2];           // row tiles per tile of the launches of per-channel and of group-wise items
     // Group-wise items: dX and token contractions in one launch (launch_gemm_dw), as split_dx and rt_dx[1] have it; the dX launch of
-    // a call without that one (too many tiles, or no scale gradient asked for) has a plan of its own.
-    bool one_launch;
+    // a call without that one (too many tiles and tokens, or no scale gradient asked for) has a plan of its own.
+    bool one_launch, many_tiles;     // many_tiles: not by bwd_few_tiles
     int split_dx_alone[PEQA_MAX_BLOCK], rt_dx_alone;
     size_t acc[PEQA_MAX_BLOCK], acc_dds[PEQA_MAX_BLOCK];
 };
+
+// The regions of the pieces.
+void lay_out_pieces(BlockSpace &w, int32_t n, const peqa_block_item *items, int32_t T)
+{
+    const size_t tiles_t = ((size_t)T + 127) / 128;
+    w.total = w.min_total;
+    for (int j = 0; j < n; ++j) {
+        const size_t N = (size_t)items[j].layout.n_out, K = (size_t)items[j].layout.k_in;
+        w.acc[j] = w.total;
+        if (w.split_y[j] > 1) w.total += round256((size_t)w.split_y[j] * T * N * sizeof(float));
+        const int dx = w.split_dx[j] > w.split_dx_alone[j] ? w.split_dx[j] : w.split_dx_alone[j];
+        if (dx > 1) w.total += round256((size_t)dx * T * K * sizeof(float));
+        w.acc_dds[j] = w.total;
+        if (w.split_dds[j] > 1) w.total += round256((size_t)w.split_dds[j] * tiles_t * N * sizeof(float));
+    }
+}
 
 BlockSpace carve_block(int32_t n, const peqa_block_item *items, int32_t T, int32_t op, int cus)
 {
@@ -118,6 +134,7 @@ BlockSpace carve_block(int32_t n, const peqa_block_item *items, int32_t T, int32
             dw_tiles += (long long)(L->k_in / 128) * ((L->n_out + 255) / 256);
         }
         w.rt_dx_alone = take(0.0, w.split_dx_alone);
+        w.many_tiles = !peqa::bwd_few_tiles(dx_tiles + dw_tiles, cus);
         w.one_launch = peqa::bwd_one_launch(dx_tiles + dw_tiles, T, cus);
         int rt = w.rt_dx_alone;
         if (w.one_launch) {
@@ -134,20 +151,13 @@ BlockSpace carve_block(int32_t n, const peqa_block_item *items, int32_t T, int32
         w.rt_dx[0] = plan(false, peqa::MODE_DX, w.split_dx);
         w.rt_dx[1] = plan(true, peqa::MODE_DX, w.split_dx);
     }
-    for (int j = 0; j < n; ++j) {
-        const size_t N = (size_t)items[j].layout.n_out, K = (size_t)items[j].layout.k_in;
-        w.acc[j] = w.total;
-        if (w.split_y[j] > 1) w.total += round256((size_t)w.split_y[j] * T * N * sizeof(float));
-        const int dx = w.split_dx[j] > w.split_dx_alone[j] ? w.split_dx[j] : w.split_dx_alone[j];
-        if (dx > 1) w.total += round256((size_t)dx * T * K * sizeof(float));
-        w.acc_dds[j] = w.total;
-        if (w.split_dds[j] > 1) w.total += round256((size_t)w.split_dds[j] * tiles_t * N * sizeof(float));
-    }
+    lay_out_pieces(w, n, items, T);
     return w;
 }
 
-// The regions of a call with a workspace of `bytes`, checked before the device is touched: whole contractions where it is
-// too small for the split ones.
+// The regions of a call with a workspace of `bytes`, checked before the device is touched.  Where it is too small for the split
+// contractions: whole ones, and group-wise items of many tiles as fit_workspace has it (block of d = 4736, f = 15744 in groups of 128, T = 138,
+// shared and whole / launches of their own in pieces 455 / 325 us).
 peqa_status plan_block(BlockSpace &w, int32_t n, const peqa_block_item *items, int32_t T, int32_t op, const void *workspace,
                        size_t bytes)
 {
@@ -156,6 +166,12 @@ peqa_status plan_block(BlockSpace &w, int32_t n, const peqa_block_item *items, i
     if (!aligned16(workspace)) return PEQA_ERR_ALIGN;
     const int cus = peqa::compute_units();
     if (cus != peqa::PLAN_UNITS) w = carve_block(n, items, T, op, cus);      // (min_total does not hang on the units)
+    if (bytes < w.total && w.one_launch && w.many_tiles) {
+        w.one_launch = false;
+        for (int j = 0; j < n; ++j)
+            if (grouped(&items[j].layout)) w.split_dx[j] = w.split_dx_alone[j];
+        lay_out_pieces(w, n, items, T);
+    }
     if (bytes < w.total)
         for (int j = 0; j < n; ++j) w.split_y[j] = w.split_dx[j] = w.split_dds[j] = w.split_dx_alone[j] = 1;
     return PEQA_OK;

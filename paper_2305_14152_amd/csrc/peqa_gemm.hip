@@ -394,7 +394,7 @@ constexpr int kOneLaunchTokens = 1536;
 bool bwd_one_launch(long long tiles, int T, int cus)
 {
     return options().gemm_waves == 0 && options().bwd_pair < 0 && options().grouped_dds == 0 &&
-           (tiles <= 8ll * cus || T <= kOneLaunchTokens);
+           (bwd_few_tiles(tiles, cus) || T <= kOneLaunchTokens);
 }
 
 // dX that gemm_plan leaves whole beside the token contractions, of tiles (counted as of gemm_row_tiles rows, whatever it takes) on no

@@ -233,8 +233,9 @@ inline SumJob chunk_sums(const float *pc, float *d_ds, int N, int K, int gsz)
     return SumJob{pc, d_ds, (size_t)N * (size_t)(K / gsz), (size_t)(gsz / 64), 1, gsz / 64};
 }
 // Whether a group-wise backward of both gradients goes that way: `tiles` of dX (of gemm_row_tiles rows) and of the token
-// contractions together.  Launches of many rounds keep the copies in spare workgroups of the dX launch.
+// contractions together.  The others keep the copies in spare workgroups of the dX launch.
 bool bwd_one_launch(long long tiles, int T, int cus);
+inline bool bwd_few_tiles(long long tiles, int cus) { return tiles <= 8ll * cus; }
 // Whether its dX, with the pieces planned beside the token contractions, is a few long chains that a launch of its own would cut up.
 bool bwd_dx_chains(int n, const SplitJob *jobs, int T, int cus);
 // The (s, b) tables of up to GT_MAX layers in one launch.

@@ -561,3 +561,54 @@ def test_group_wise_backward_of_many_tiles_and_few_tokens(gpu):
         got.append((gpu.bf16_dev_to_f64(dX), gpu.to_host(d_ds)))
     assert np.abs(got[0][0]).max() > 0 and np.abs(got[0][0] - got[1][0]).max() <= 2.0 ** -7 * np.abs(got[1][0]).max()
     assert (got[0][1] == got[1][1]).all() and np.abs(got[0][1]).max() > 0
+
+
+@pytest.mark.parametrize("shapes,group,bits,T,block", [
+    ([(17152, 4864)], 256, 3, 118, False),
+    ([(10368, 3456), (3456, 3456), (18176, 3456), (3456, 9088)], 128, 4, 459, True)])
+def test_group_wise_backward_of_many_tiles_with_less_workspace(gpu, shapes, group, bits, T, block):
+    """The shared launch of many tiles wants room for more pieces of dX than launches of their own: with less, those, in pieces, and with
+    the least, whole.  Scale gradients are sums in the same order throughout; pieces of dX are added in another."""
+    import torch
+    from paper_2305_14152_amd import peqa
+    g = torch.Generator(device="cuda").manual_seed(79950 + T)
+    items = []
+    for N, K in shapes:
+        L = peqa.layout(N, K, bits, group)
+        d = dict(L=L, packed=torch.empty(peqa.packed_words(L), dtype=torch.int32, device="cuda"),
+                 s0=torch.empty((N, L.groups), device="cuda"), z0=torch.empty((N, L.groups), dtype=torch.uint8, device="cuda"))
+        peqa.quantize(L, torch.randn((N, K), device="cuda", generator=g) * 0.02, d["packed"], d["s0"], d["z0"])
+        d["X"] = torch.randn((T, K), device="cuda", generator=g).bfloat16().view(torch.int16)
+        d["dY"] = torch.randn((T, N), device="cuda", generator=g).bfloat16().view(torch.int16)
+        items.append(d)
+
+    def size():
+        if block:
+            return peqa.block_workspace_bytes(peqa.block_items(items), T, peqa.PEQA_OP_BWD)
+        return peqa.workspace_bytes(items[0]["L"], T, peqa.PEQA_OP_BWD)
+
+    full = size()
+    peqa.set_option(peqa.PEQA_OPT_GEMM_WAVES, 4)               # whole contractions
+    try:
+        least = size()
+    finally:
+        peqa.set_option(peqa.PEQA_OPT_GEMM_WAVES, 0)
+    dx = "gemm_multi_dx" if block else "gemm_dx"
+    ws, got = torch.empty(full, dtype=torch.uint8, device="cuda"), []
+    for nb, launches, pieces in ((full, {"gemm_bwd": 1}, True), (full - 256, {dx: 1, "gemm_dw": 1}, True), (least, {dx: 1, "gemm_dw": 1}, False)):
+        for d in items:
+            d["dX"], d["d_ds"] = torch.zeros_like(d["X"]), torch.zeros_like(d["s0"])
+        peqa.trace_begin(16)
+        if block:
+            peqa.block_bwd(peqa.block_items(items), T, ws, nb)
+        else:
+            d = items[0]
+            peqa.linear_bwd(d["L"], d["packed"], d["s0"], None, d["z0"], d["X"], d["dY"], T, d["dX"], d["d_ds"], ws, nb)
+        seen = {k: v[0] for k, v in peqa.trace_end().items()}
+        print(nb, seen, flush=True)
+        assert all(seen.get(k) == n for k, n in launches.items()) and ("gemm_finish" in seen) == pieces, seen
+        got.append([(gpu.bf16_dev_to_f64(d["dX"]), gpu.to_host(d["d_ds"])) for d in items])
+    for other in got[1:]:
+        for (dX, d_ds), (dXo, d_dso) in zip(got[0], other):
+            assert np.abs(dX).max() > 0 and np.abs(dX - dXo).max() <= 2.0 ** -7 * np.abs(dX).max()
+            assert np.abs(d_ds).max() > 0 and (d_ds == d_dso).all()
