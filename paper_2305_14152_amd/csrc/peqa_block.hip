@@ -216,6 +216,27 @@ void place_aux(peqa::MultiArgs &m, int aux_wgs)
     m.aux_wgs = (m.n_sdy > 0 || m.n_red > 0 || m.n_tp > 0) ? aux_wgs : 0;
 }
 
+// The auxiliary workgroups of a launch whose side work is the scaling of dY.
+int launch_scaling_wgs(const peqa::MultiArgs &m)
+{
+    const int rows = peqa::aux_sdy_rows(m.n_jobs > 0 ? m.job[0].a.rt : 8), places = 2 * peqa::compute_units();
+    int blocks = 0, tiles = 0;
+    double scaling = 0.0, sum = 0.0, longest = 0.0;
+    for (int j = 0; j < m.n_sdy; ++j) {
+        const int b = (m.sdy[j].T + rows - 1) / rows;
+        blocks += b;
+        scaling += b * (2.0 + 1.4 * ((m.sdy[j].N + 2047) / 2048));
+    }
+    for (int j = 0; j < m.n_jobs; ++j) {
+        const int n = peqa::gemm_multi_wgs(m.job[j].a);
+        const double us = 8.0 + 0.55 * (piece_length(m.job[j]) / 32);
+        tiles += n;
+        sum += us * n;
+        longest = us > longest ? us : longest;
+    }
+    return peqa::scaling_wgs(blocks, scaling, tiles, sum / places > longest ? sum / places : longest, places);
+}
+
 // Tables of every group-wise item (of those whose dX is wanted, if only_dx): one launch.
 peqa_status group_tables(int32_t n, const peqa_block_item *items, uint8_t *ws, const BlockSpace &w, bool only_dx,
                          hipStream_t s)
@@ -446,7 +467,7 @@ peqa_status peqa_block_bwd(int32_t n, const peqa_block_item *items, int32_t T, v
     }
     if (ma.n_jobs > 0 || ma.n_sdy > 0) {
         sort_jobs(ma);
-        place_aux(ma, 64);
+        place_aux(ma, launch_scaling_wgs(ma));
         st = launch_multi(bits, false, ma, s);
         if (st != PEQA_OK) return st;
     }

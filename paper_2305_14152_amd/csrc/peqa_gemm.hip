@@ -345,6 +345,21 @@ hipError_t launch_gemm(int bits, int mode, const GemmArgs &a_in, hipStream_t str
     return e;
 }
 
+// A workgroup of the scaling costs a place for as long as it lasts, so launches of many rounds get few; but no launch is over before the
+// scaling is.  So it takes a quarter of the launch by the estimates, in no fewer than 192 workgroups where there are less than four
+// rounds of tiles (those end early in a round that is not full), and in no more than 512.  Backward, us, with 64 / 128 / 192 / 256 / 512:
+// blocks of d = 256, f = 640, T = 3727 130 / 80 / 63 / 60 / 51, d = 640, f = 1792, T = 1795 124 / 90 / 82 / 79 / 75, d = 1152, f = 3456, T = 2928
+// 255 / 207 / 206 / 208 / 206, d = 3072, f = 8192, T = 1024 399 / 388 / 388 / 391 / 390, d = 4096, f = 11008, T = 512 369 / 354 / 348 / 349 / 350,
+// and with five rounds, T = 2048, 1222 / 1227 / 1231 / 1230 / 1232.
+int scaling_wgs(int blocks, double scaling_us, int tiles, double launch_us, int places)
+{
+    const double quarter = scaling_us / (0.25 * launch_us);
+    int wgs = quarter < 512.0 ? 64 * (int)(quarter / 64 + 0.5) : 512;
+    const int least = tiles < 4 * places ? 192 : 64;
+    wgs = wgs < least ? least : wgs;
+    return wgs < blocks ? wgs : (blocks + 7) / 8 * 8;
+}
+
 hipError_t launch_gemm_multi(int bits, bool grouped, MultiArgs &m, hipStream_t stream)
 {
     if (m.n_jobs < 0 || m.n_jobs > MULTI_MAX_JOBS || m.n_sdy < 0 || m.n_sdy > MULTI_MAX_JOBS || m.n_red < 0 ||

@@ -125,6 +125,9 @@ struct MultiJob {
 };
 // Token rows per row block of the scaling in the auxiliary workgroups of a launch whose tiles have rt row tiles (see scale_dy_rows).
 constexpr int aux_sdy_rows(int rt) { return rt == 4 ? 2 : 8; }
+// Auxiliary workgroups for `blocks` row blocks of the scaling, `scaling_us` of work for one, beside `tiles` workgroups that take launch_us by
+// themselves with so many places on the machine.
+int scaling_wgs(int blocks, double scaling_us, int tiles, double launch_us, int places);
 struct ScaleDyJob {           // dYs = bf16(dY (s0 + ds)), crow[t] = sum_i dYs[t,i] (16 + z0[i])   (scale_dy_rows)
     const uint16_t *dY;
     const float *s0, *ds;

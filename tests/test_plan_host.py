@@ -149,3 +149,23 @@ def test_block_workspace_holds_the_plan_of_dx_alone(planner):
     finally:
         peqa.set_option(peqa.PEQA_OPT_GEMM_WAVES, 0)
     assert need - whole >= alone[0] * 4 * T * K
+
+
+def test_workgroups_that_scale_dY():
+    """Multiples of 8, no more than there are row blocks, 64 to 512: many beside tiles that last no longer than the scaling, few in
+    launches of many rounds.  By measurement (backward, us): d = 256, f = 640, T = 3727 130 with 64 workgroups and 51 with 512, d = 3072,
+    f = 8192, T = 1024 399 and 388 with 192, d = 4096, f = 11008, T = 2048 1222 and 1231 with 192."""
+    from paper_2305_14152_amd import peqa
+    i, d = ctypes.c_int, ctypes.c_double
+    fn = peqa.lib()._ZN4peqa11scaling_wgsEididi                    # peqa::scaling_wgs
+    fn.argtypes, fn.restype = [i, d, i, d, i], i
+    assert fn(1864, 6340.0, 304, 19.0, 2 * CUS) == 512
+    assert fn(512, 4150.0, 992, 150.0, 2 * CUS) == 192
+    assert fn(1024, 9574.0, 2656, 466.0, 2 * CUS) == 64
+    assert fn(0, 0.0, 8, 20.0, 2 * CUS) == 0 and fn(3, 11.0, 8, 20.0, 2 * CUS) == 8 and fn(81, 300.0, 24, 20.0, 2 * CUS) == 88
+    rng = random.Random(0)
+    for _ in range(500):
+        blocks, tiles, launch = rng.randint(1, 5000), rng.randint(8, 8000), rng.uniform(10, 3000)
+        n = fn(blocks, rng.uniform(3, 30) * blocks, tiles, launch, 2 * CUS)
+        assert n % 8 == 0 and min(64, blocks) <= n <= min(512, blocks + 7)
+        assert tiles >= 8 * CUS or n >= min(192, blocks)
