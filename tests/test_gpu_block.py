@@ -116,8 +116,8 @@ def test_block_backward_parity(gpu, oracle, bits, group, shapes, T):
 
 @pytest.mark.parametrize("bits,T", [(4, 17), (3, 63), (4, 64), (3, 65), (4, 71), (4, 333), (3, 2053)])
 def test_block_scaling_of_dY(gpu, oracle, bits, T):
-    """The scaling of dY in the auxiliary workgroups: two token rows at a time beside scale-gradient tiles of 64 rows, eight beside others
-    and where no scale gradient is asked for; the last rows of an odd T, layers of one and of several turns over the channels; fewer row blocks
+    """The scaling of dY in the auxiliary workgroups: two token rows at a time beside scale-gradient tiles of 64 rows, eight beside others;
+    without a scale gradient two up to 255 blocks of eight (here T = 679), eight from there on; the last rows of an odd T, layers of one and of several turns over the channels; fewer row blocks
     than workgroups and (T = 2053) more than there are at most.  dX has the same bits either way."""
     import torch
     from paper_2305_14152_amd import peqa
