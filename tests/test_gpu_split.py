@@ -612,3 +612,39 @@ def test_group_wise_backward_of_many_tiles_with_less_workspace(gpu, shapes, grou
         for (dX, d_ds), (dXo, d_dso) in zip(got[0], other):
             assert np.abs(dX).max() > 0 and np.abs(dX - dXo).max() <= 2.0 ** -7 * np.abs(dX).max()
             assert np.abs(d_ds).max() > 0 and (d_ds == d_dso).all()
+
+
+def test_group_wise_backward_of_many_tiles_and_some_gradients(gpu):
+    """The shared launch is planned for every gradient of every item.  Where a call asks for the dX of the wide items and the scale gradients of
+    the others, its long dX workgroups would run on alone: launches of their own; with the dX of the narrow ones, the shared one."""
+    import torch
+    from paper_2305_14152_amd import peqa
+    d, f, group, bits, T = 2560, 7680, 128, 4, 1200
+    g = torch.Generator(device="cuda").manual_seed(79980)
+    items = []
+    for N, K in ((3 * d, d), (d, d), (2 * f, d), (d, f)):
+        L = peqa.layout(N, K, bits, group)
+        it = dict(L=L, packed=torch.empty(peqa.packed_words(L), dtype=torch.int32, device="cuda"),
+                  s0=torch.empty((N, L.groups), device="cuda"), z0=torch.empty((N, L.groups), dtype=torch.uint8, device="cuda"))
+        peqa.quantize(L, torch.randn((N, K), device="cuda", generator=g) * 0.02, it["packed"], it["s0"], it["z0"])
+        it["X"] = torch.randn((T, K), device="cuda", generator=g).bfloat16().view(torch.int16)
+        it["dY"] = torch.randn((T, N), device="cuda", generator=g).bfloat16().view(torch.int16)
+        items.append(it)
+    everything = None
+    for dx_of, dds_of, shared in (((0, 1, 2, 3), (0, 1, 2, 3), True), ((0, 2), (1, 3), False), ((1, 3), (0, 2), True)):
+        for i, it in enumerate(items):
+            it["dX"] = torch.zeros_like(it["X"]) if i in dx_of else None
+            it["d_ds"] = torch.zeros_like(it["s0"]) if i in dds_of else None
+        nb = peqa.block_workspace_bytes(peqa.block_items(items), T, peqa.PEQA_OP_BWD)
+        ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+        peqa.trace_begin(16)
+        peqa.block_bwd(peqa.block_items(items), T, ws, nb)
+        seen = peqa.trace_end()
+        print(dx_of, dds_of, {k: v[0] for k, v in seen.items()}, flush=True)
+        assert ("gemm_bwd" in seen) == shared and ("gemm_multi_dx" in seen) == (not shared)
+        got = [(gpu.bf16_dev_to_f64(it["dX"]) if i in dx_of else None, gpu.to_host(it["d_ds"]) if i in dds_of else None)
+               for i, it in enumerate(items)]
+        everything = everything or got
+        for (dX, d_ds), (dXo, d_dso) in zip(everything, got):
+            assert dXo is None or np.abs(dX).max() > 0 and np.abs(dX - dXo).max() <= 2.0 ** -7 * np.abs(dX).max()
+            assert d_dso is None or np.abs(d_ds).max() > 0 and (d_ds == d_dso).all()
