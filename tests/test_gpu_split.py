@@ -648,3 +648,27 @@ def test_group_wise_backward_of_many_tiles_and_some_gradients(gpu):
         for (dX, d_ds), (dXo, d_dso) in zip(everything, got):
             assert dXo is None or np.abs(dX).max() > 0 and np.abs(dX - dXo).max() <= 2.0 ** -7 * np.abs(dX).max()
             assert d_dso is None or np.abs(d_ds).max() > 0 and (d_ds == d_dso).all()
+
+
+@pytest.mark.parametrize("pieces,K", [(3, 1536), (4, 2048), (5, 2560), (6, 3072), (8, 4096), (10, 5120), (12, 6144), (24, 12288)])
+def test_sums_of_any_number_of_pieces(gpu, oracle, pieces, K):
+    """The pieces after the first are added eight, four, two and one at a time: every remainder of eight, below eight and above."""
+    from paper_2305_14152_amd import peqa
+    N, T = 128, 32
+    for group in (0, 64):
+        print("pieces=%d K=%d g=%d" % (pieces, K, group), flush=True)
+        L = peqa.layout(N, K, 4, group)
+        full = peqa.workspace_bytes(L, T, peqa.PEQA_OP_FWD)
+        peqa.set_option(peqa.PEQA_OPT_GEMM_WAVES, 4)               # whole contractions
+        try:
+            least = peqa.workspace_bytes(L, T, peqa.PEQA_OP_FWD)
+        finally:
+            peqa.set_option(peqa.PEQA_OPT_GEMM_WAVES, 0)
+        assert full - least == pieces * T * N * 4
+        W = synth.normal_f32(80100 + K, (N, K), 0.02)
+        codes, s0, z0 = oracle.quantize(W, 4, group)
+        ds = synth.normal_f32(80101 + K, s0.shape, 1e-3)
+        X = synth.normal_bf16(80102 + K, (T, K), 1.0)
+        Yref = oracle.fwd(codes, s0, ds, z0, X, group)
+        Y = gpu.bf16_dev_to_f64(gpu.GpuLayer(W, 4, group).fwd(X, ds))
+        assert np.abs(Y - Yref).max() <= Y_TOL * np.abs(Yref).max()
