@@ -49,9 +49,10 @@
  * Workspaces.  Where a launch's tiles would leave the machine idle (T > 16, but few tokens or a few tiles of a long
  * contraction), contractions are split along their length into pieces whose fp32 sums meet in the workspace.  The size
  * queries include that room.  A workspace that has room for everything but the pieces (what the queries return while
- * PEQA_OPT_GEMM_WAVES or PEQA_OPT_BWD_PAIR forces a form) is served too, with whole contractions: the same products
+ * PEQA_OPT_GEMM_WAVES or PEQA_OPT_BWD_PAIR forces a form) is served too, with whole contractions (a group-wise backward
+ * of many tiles: in launches of its own, with their pieces where there is room for those): the same products
  * in another order; so is, at T <= 16, one that holds the partial sums of the fewest slices the layers need, with those.
- * For a given shape, T and workspace size results are always the same bits.
+ * For a given shape, T, workspace size and set of gradients asked for results are always the same bits.
  */
 #ifndef PEQA_H
 #define PEQA_H
@@ -230,10 +231,12 @@ peqa_status peqa_linear_fwd_fused(int32_t n, const peqa_fwd_item *items, const u
  *     contractions in one launch whose grid also carries the scaling of dY for every item, then all dX
  *     contractions in one launch whose grid also carries the fixed-order sums of the scale-gradient partials.
  *     Group-wise layers: forward = the scale tables of all items in one launch, then all contractions in one
- *     launch.  Backward of few tiles, both gradients = the tables and the transposed copies of X (once per distinct
- *     X) and dY in one launch, then all dX contractions and the token contractions of all scale gradients in one
- *     launch.  Of many tiles, or of one gradient = the tables, then all dX contractions in one launch whose grid
- *     also writes the copies, then the token contractions in one launch.  (Always the token-contraction route:
+ *     launch.  Backward of few tiles (8 per compute unit) or of at most 1536 tokens, both gradients = the tables and
+ *     the transposed copies of X (once per distinct X) and dY in one launch, then all dX contractions and the token
+ *     contractions of all scale gradients in one launch.  Otherwise, and where dX is a few long contractions that a
+ *     launch of its own would cut up or that would outlast what is asked for beside it, and (more tiles) with less
+ *     workspace than the query says = the tables, then all dX contractions in one launch whose grid also writes the
+ *     copies, then the token contractions in one launch.  (Always the token-contraction route:
  *     PEQA_OPT_GROUPED_DDS = 1 only keeps the two in launches of their own.)
  *     Contractions of few tokens are cut into pieces, whose sums, like those of the chunks of groups past 128
  *     features, are added up by one launch more.

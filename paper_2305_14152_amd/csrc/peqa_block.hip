@@ -499,7 +499,7 @@ peqa_status peqa_block_bwd(int32_t n, const peqa_block_item *items, int32_t T, v
         if (st != PEQA_OK) return st;
     }
 
-    // ---- group-wise items.  Few tiles and both gradients: the (s, b) tables and the transposed copies of X (once per distinct
+    // ---- group-wise items.  Few tiles or tokens (bwd_one_launch) and both gradients: the (s, b) tables and the transposed copies of X (once per distinct
     // input) and dY in one launch, dX and the token contractions of the scale gradients in the next, pieces and chunks added up in
     // the last.  Otherwise the tables in one launch; every dX contraction in one launch, whose auxiliary workgroups write the copies;
     // the token contractions in one launch; the sums of their chunks in one launch.

@@ -377,7 +377,7 @@ __device__ __forceinline__ void gemv_tile(const GemvArgs &a, const GemvLayer &L,
     }
 }
 
-// NARROW: the launch has layers whose tiles are half as wide (GemvLayer::narrow).
+// NARROW: the launch has layers whose tiles are half as wide (GEMV_NARROW in GemvLayer::form).
 template <int BITS, int H, int WAVES, int NX, bool ZBYTE, bool NARROW>
 __global__ __launch_bounds__(WAVES * 64, GV_SIMD_WAVES) void gemv_kernel(GemvArgs a)
 {
@@ -504,11 +504,15 @@ static int gv_cols(int K, int chunk, int S)                        // most scale
 // few workgroups with a few loads in flight each) and no layer's much longer than the others'.  At most 8 tokens, per-channel layers
 // and more than two workgroups per unit: layers of more than 1.35 times the mean length take tiles of 32 channels beside the
 // others' 64, which need no slices, that is no second launch; such a tile's rounds are as many and follow each other,
-// so they start first and go first (without that the block of d = 5120, 3-bit g128, took 36.5 instead of 32.0 us).  us per block at
+// so they start first and go first (laid out last and with the others' priorities, d = 4096 4-bit, T = 1, takes 24.7 instead of 23.1 us,
+// d = 5120 3-bit 31.1 instead of 28.2).  us per block at
 // T = 1 / 5, sliced -> so: d = 4096 4-bit 24.4 / 24.8 -> 22.9 / 23.1, 3-bit 20.5 / 21.1 -> 19.2 / 19.6, d = 5120 3-bit 29.0 / 29.6 -> 27.1 /
-// 27.8, d = 3072 4-bit 17.5 / 18.1 -> 15.7 / 16.4.  Not with scale groups, whose tile and folds cost a tile of 32 channels as much as
-// one of 64 (d = 4096 4-bit g128 27.5 / 28.2 -> 28.4 / 28.9), nor for more tokens, of which a tile of 32 would fetch twice as
-// much per channel, nor at one workgroup per unit (d = 2048 g128 12.1 -> 12.2).  Otherwise layers are sliced to at most
+// 27.8, d = 3072 4-bit 17.5 / 18.1 -> 15.7 / 16.4.  Not where a layer has more than 2.7 times the mean length, as long as in tiles of 64 then
+// even with half the channels a round; not with scale groups, whose tile and folds cost a tile of 32 channels as much as
+// one of 64 (d = 4096 4-bit g128, in a build that let it, 27.5 / 28.2 -> 28.4 / 28.9), nor for more tokens, of which a tile of 32 would
+// fetch twice as much per channel.  The bound of two workgroups per unit stands where the first measurements ended: with one to two it
+// would be the shorter form as well (T = 1 / 8: d = 1792, f = 4864 4-bit 11.0 / 11.7 -> 9.6 / 10.0, d = 2048, f = 5632 11.8 / 12.6 -> 10.7 / 11.0,
+// d = 2560, f = 6912 13.6 / 14.3 -> 12.6 / 13.1), which has not been taken yet.  Otherwise layers are sliced to at most
 // 1.35 times the mean length, more while the workgroups' scale tiles keep them from fitting on the chip together; failing
 // that, 128 channels per workgroup (half of the token rows' traffic and LDS per channel).  us per block at T = 1 / 16, 13B
 // 3-bit g128: 3 slices of the long layer 34.6 / 42.3, 2 slices (not resident) 38.9 / 45.6, 128 channels 35.8 / 38.2.
