@@ -238,24 +238,27 @@ int launch_scaling_wgs(const peqa::MultiArgs &m)
 }
 
 // Whether dX, in the pieces planned beside the token contractions of every group-wise item, is far from over when the work of those that a call
-// asks for is.  Of calls of many tiles that ask for some gradients only (backward, us, launches of their own / shared; its longest
-// workgroup over the work by the estimates below): d = 3328, f = 9728 in groups of 64, T = 859, dX of the wide items and scale gradients of the others 303 / 343
-// (2.2), all dX and the scale gradient of q, k, v 353 / 376 (1.9), of q, k, v and o 370 / 388 (1.7); the first of d = 3072, f = 8192, T = 1500
-// 399 / 355 (1.5), of d = 4096, f = 11008 in groups of 128, T = 1400 558 / 504 (1.2 or less); close to the line d = 5120, f = 13824, T = 700 539 / 505.
+// asks for is, and a launch of its own has shorter pieces.  Of calls of many tiles that ask for some gradients only (backward, us, launches
+// of their own / shared; the longest workgroup over the work by the estimates below): d = 3328, f = 9728 in groups of 64, T = 859, dX
+// of the wide items and scale gradients of the others 303 / 343 (2.2), all dX and the scale gradient of q, k, v 353 / 376 (1.9), of q, k, v
+// and o 370 / 388 (1.7); the first of d = 3584, f = 12544 in groups of 256, T = 1193 463 / 498 (1.6), of d = 3200, f = 9728 in groups of 128,
+// T = 33 66 / 59 (1.4).  Where the pieces are the same, shared: d = 2176, f = 6272, T = 1532 263 / 246 (2.0), d = 5120, f = 13824, T = 700 539 / 505 (1.7).
 bool dx_outlasts(int32_t n, const peqa_block_item *items, const BlockSpace &w, int32_t T)
 {
-    double sum = 0.0, longest = 0.0;
+    double sum = 0.0, longest = 0.0, alone = 0.0;
+    auto us = [](int steps, int rt) { return 8.0 + 0.55 * rt / 8 * steps; };
     for (int j = 0; j < n; ++j) {
         const int N = items[j].layout.n_out, K = items[j].layout.k_in;
         if (!grouped(&items[j].layout)) continue;
         if (items[j].dX) {
-            const double us = 8.0 + 0.55 * (N / 32 / w.split_dx[j]);
-            sum += us * peqa::gemm_tiles_t(T, w.rt_dx[1]) * ((K + 255) / 256) * w.split_dx[j];
-            longest = us > longest ? us : longest;
+            const double piece = us(N / 32 / w.split_dx[j], w.rt_dx[1]), own = us(N / 32 / w.split_dx_alone[j], w.rt_dx_alone);
+            sum += piece * peqa::gemm_tiles_t(T, w.rt_dx[1]) * ((K + 255) / 256) * w.split_dx[j];
+            longest = piece > longest ? piece : longest;
+            alone = own > alone ? own : alone;
         }
         if (items[j].d_ds) sum += peqa::dw_tile_us(T) * (K / 128) * ((N + 255) / 256);
     }
-    return longest > 1.6 * sum / (2 * peqa::compute_units());
+    return longest > 1.6 * sum / (2 * peqa::compute_units()) && alone < 0.6 * longest;
 }
 
 // Tables of every group-wise item (of those whose dX is wanted, if only_dx): one launch.
