@@ -182,7 +182,7 @@ __device__ __forceinline__ void global_store(void *p, const T &v)
 // of its own: 104 registers instead of 70, 2048 x 11008 19.4 -> 18.4 us, 500 x 11008 11.2 -> 10.9, 4096 x 22016 and 1000 x 16384 the same).
 // Four rows where there are workgroups enough to fill the machine (a launch of its own), eight beside matrix work, where every
 // place that the scaling holds for longer is one less for tiles, and half as many workgroups: backward of a 7B block 1218 -> 1190 us;
-// dX alone with the scaling before it 649 -> 636.  (Sixteen rows: the registers do not hold them.)  Two beside tiles of 64 rows, where
+// dX alone with the scaling before it 649 -> 636.  (Sixteen rows: the registers do not hold them.)  Two in launches without tiles and with few blocks (launch_gemm_multi), and beside tiles of 64 rows, where
 // there are no more than 64 tokens, which four or eight rows deal to few workgroups, and where two sets of columns of eight rows take the
 // registers of a third workgroup on the unit (gemm_multi_kernel).  Training steps, us, eight rows and one set / four / two: d = 2048,
 // f = 7040, T = 47 67.0 / 62.4 / 62.8, d = 2432, f = 7552, T = 18 70.6 / 66.1 / 64.4, d = 6656, f = 17920, T = 64 288 / 282 / 276,

@@ -123,7 +123,8 @@ struct MultiJob {
     int mode;                 // MODE_Y, MODE_DDS or MODE_DX
     int wg_end;               // tile workgroups of this job and all before it (unused entries: the total)
 };
-// Token rows per row block of the scaling in the auxiliary workgroups of a launch whose tiles have rt row tiles (see scale_dy_rows).
+// Token rows per row block of the scaling in the auxiliary workgroups of a launch whose tiles have rt row tiles (see scale_dy_rows); without tiles
+// launch_gemm_multi takes the kernel of the rows that it wants.
 constexpr int aux_sdy_rows(int rt) { return rt == 4 ? 2 : 8; }
 // Auxiliary workgroups for `blocks` row blocks of the scaling, `scaling_us` of work for one, beside `tiles` workgroups that take launch_us by
 // themselves with so many places on the machine.
