@@ -347,6 +347,39 @@ __device__ __forceinline__ void transpose_pad_tile(const uint16_t *__restrict__ 
     transpose_store(r, C, dst, bt, bc, piece);
 }
 
+// 16 columns of such a tile by one wave, the quarter'th, without LDS: a lane has 2 columns of 8 tokens, which is two neighbouring pieces.
+// For launches of few tiles, which the chain of a wave's own instructions bounds (a quarter of them here).  Scale gradient alone of one layer, us,
+// a tile per wave / four waves per tile: 256 x 384, T = 125 (20 tiles) 9.06 / 8.83, 640 x 7552, T = 32 (128) 9.34 / 8.97, 2048 x 1536,
+// T = 845 (784) 25.1 / 25.2, 1664 x 4096, T = 2352 (3330) 42.3 / 42.4.
+__device__ __forceinline__ void transpose_pad_quarter(const uint16_t *__restrict__ src, int T, int C, uint16_t *__restrict__ dst, int bt,
+                                                      int bc, int quarter)
+{
+    const int lane = threadIdx.x & 63, c2 = lane & 7, tb = lane >> 3, t0 = bt * 64 + 8 * tb, col = bc * 64 + quarter * 16;
+    uint32_t row[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) row[j] = global_load<uint32_t>(src + (size_t)min(t0 + j, T - 1) * C + col + 2 * c2);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) row[j] = t0 + j < T ? row[j] : 0u;
+    uint16_t *to = dst + ((size_t)(2 * bt + (tb >> 2)) * C + col) * 32 + ((tb & 3) * 16 + 2 * c2) * 8;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        u32x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = __builtin_amdgcn_perm(row[2 * e + 1], row[2 * e], h ? 0x07060302u : 0x05040100u);
+        global_store(to + 8 * h, o);
+    }
+}
+
+// Tile b of a launch of copies: along the columns first where workgroups take four (neighbours share rows of the source), else along the
+// tokens (1664 x 4096, T = 2352, scale gradient alone 42.3 us along the columns, 41.4 so; 22016 x 8192, T = 700 214 and 216).
+struct CopyTile {
+    int bt, bc;
+};
+__device__ __forceinline__ CopyTile copy_tile(int b, int bts, int bcs, int per_wg)
+{
+    return per_wg == 4 ? CopyTile{b / bcs, b % bcs} : CopyTile{b % bts, b / bts};
+}
+
 // A piece of the kernel's argument block read at a run-time (wavefront-uniform) byte offset: scalar loads from the
 // kernarg segment.  Indexing an array inside a by-value kernel argument with a run-time index would make the
 // compiler keep a private copy of the whole argument in scratch memory; this reads the segment itself.

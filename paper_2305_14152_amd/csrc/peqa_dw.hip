@@ -60,24 +60,27 @@ __global__ __launch_bounds__(256, 2) void dw_multi_kernel(DwMultiArgs m)
     dw_tile<BITS>(a, b - wg0, lds);
 }
 
-// transpose_pad_tile (peqa_device.h) for every 64 x 64 tile of both operands, X [T, K] and dY [T, N], along the columns first: one to a
-// wave, one grid dimension (a second one ends at 65536).  One launch, 1.4 us less than two in a step of 193.  Workgroups of one wave
-// up to 24 tiles per unit, of four past that (as group_prep_kernel); us, four / one: 256 x 384, T = 125 (20 tiles) 3.1 / 2.8,
-// 1664 x 4096, T = 2352 (3330) 10.8 / 10.6, 11008 x 4096, T = 2048 (7552) 20.5 / 20.4, 8192 x 22016 (15104) 38.7 / 41.7.
+// The step-major transposed copies (peqa_device.h) of both operands, X [T, K] and dY [T, N], in 64 x 64 tiles and one grid dimension (a
+// second one ends at 65536).  One launch, 1.4 us less than two in a step of 193.  Bound by a wave's chain of instructions up to
+// two tiles per unit, where four waves share one (transpose_pad_quarter); then workgroups of one wave up to 24 tiles per unit, of four
+// past that (as group_prep_kernel); us, four / one: 1664 x 4096, T = 2352 (3330 tiles) 10.8 / 10.6, 11008 x 4096, T = 2048 (7552) 20.5 / 20.4,
+// 8192 x 22016 (15104) 38.7 / 41.7.
 __global__ __launch_bounds__(256) void transpose_pad_kernel(const uint16_t *__restrict__ X, int K, uint16_t *__restrict__ xt,
                                                              const uint16_t *__restrict__ dY, int N,
-                                                             uint16_t *__restrict__ dyt, int T)
+                                                             uint16_t *__restrict__ dyt, int T, int per_wg)
 {
     extern __shared__ __align__(16) uint8_t lds[];
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int bts = (T + 63) >> 6, of_x = bts * (K >> 6);
-    int b = (int)(blockDim.x >> 6) * (int)blockIdx.x + wave;
+    int b = per_wg == 4 ? 4 * (int)blockIdx.x + wave : (int)blockIdx.x;
     if (b >= of_x + bts * (N >> 6)) return;
     const bool x = b < of_x;
     b -= x ? 0 : of_x;
-    const int bcs = (x ? K : N) >> 6;
-    transpose_pad_tile(x ? X : dY, T, x ? K : N, x ? xt : dyt, b / bcs, b % bcs,
-                       reinterpret_cast<u32x4 *>(lds + wave * TRANSPOSE_LDS));
+    const CopyTile c = copy_tile(b, bts, (x ? K : N) >> 6, per_wg);
+    if (per_wg)
+        transpose_pad_tile(x ? X : dY, T, x ? K : N, x ? xt : dyt, c.bt, c.bc, reinterpret_cast<u32x4 *>(lds + wave * TRANSPOSE_LDS));
+    else
+        transpose_pad_quarter(x ? X : dY, T, x ? K : N, x ? xt : dyt, c.bt, c.bc, wave);
 }
 
 // d_ds[i, g] = sum of pc[i, chunk] over the gsz / 64 chunks of group g, in order.
@@ -115,13 +118,15 @@ bool g_attr_done_multi[2][kMaxDev];
 
 }  // namespace
 
+int copies_per_wg(int tiles) { return tiles <= 2 * compute_units() ? 0 : tiles <= 24 * compute_units() ? 1 : 4; }
+
 hipError_t launch_transpose_pad(const uint16_t *X, int K, uint16_t *xt, const uint16_t *dY, int N, uint16_t *dyt, int T,
                                 hipStream_t stream)
 {
-    const int tiles = (T + 63) / 64 * ((K + N) / 64), waves = tiles <= 24 * compute_units() ? 1 : 4;
+    const int tiles = (T + 63) / 64 * ((K + N) / 64), per_wg = copies_per_wg(tiles);
     trace_before(KID_TRANSPOSE, stream);
-    hipLaunchKernelGGL(transpose_pad_kernel, dim3((tiles + waves - 1) / waves), dim3(64 * waves), waves * TRANSPOSE_LDS, stream, X, K, xt, dY, N,
-                       dyt, T);
+    hipLaunchKernelGGL(transpose_pad_kernel, dim3(copies_wgs(tiles)), dim3(per_wg == 1 ? 64 : 256), per_wg * TRANSPOSE_LDS, stream, X, K, xt, dY, N,
+                       dyt, T, per_wg);
     trace_after(KID_TRANSPOSE, stream);
     return hipGetLastError();
 }

@@ -194,6 +194,10 @@ struct DwArgs {
 // workgroups of a layer: its tiles, rounded up to a whole number per XCD
 inline int dw_wgs(const DwArgs &a) { return (a.tiles_f * a.tiles_c + 7) / 8 * 8; }
 bool dw_args_ok(const DwArgs &a);          // what the kernel's indexing assumes
+// 64 x 64 tiles of the copies that a workgroup of a launch of so many takes: four or one, one per wave (transpose_pad_tile), or 0: one by
+// all its waves (transpose_pad_quarter).
+int copies_per_wg(int tiles);
+inline int copies_wgs(int tiles) { return copies_per_wg(tiles) == 4 ? (tiles + 3) / 4 : tiles; }
 // X [T, K] -> xt, dY [T, N] -> dyt
 hipError_t launch_transpose_pad(const uint16_t *X, int K, uint16_t *xt, const uint16_t *dY, int N, uint16_t *dyt, int T,
                                 hipStream_t stream);

@@ -197,7 +197,7 @@ __global__ __launch_bounds__(256) void group_table_kernel(const float *__restric
 }
 
 // Tables of group-wise layers and, for a backward, transposed copies (GroupPrep): the tables' workgroups first, then those of the copies, which
-// take a 64 x 64 tile in each of one wave or four.  One launch where there were two, of 3 us and more each.
+// take a 64 x 64 tile together, or one in each of one wave or four.  One launch where there were two, of 3 us and more each.
 __global__ __launch_bounds__(256) void group_prep_kernel(GroupPrep a)
 {
     extern __shared__ __align__(16) float gt_lds[];
@@ -217,8 +217,9 @@ __global__ __launch_bounds__(256) void group_prep_kernel(GroupPrep a)
         return;
     }
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    if (wave >= a.copies_per_wg) return;
-    b = a.copies_per_wg * (b - a.table_end[GT_MAX - 1]) + wave;
+    b -= a.table_end[GT_MAX - 1];
+    if (a.copies_per_wg == 1 && wave > 0) return;
+    if (a.copies_per_wg == 4) b = 4 * b + wave;
     if (b >= kernarg_load<int>((uint32_t)(offsetof(GroupPrep, tp) + (a.n_tp - 1) * sizeof(TransposeJob) + offsetof(TransposeJob, tile_end)))) return;
     int j = 0, b0 = 0;
     for (int i = 0; i + 1 < a.n_tp; ++i) {
@@ -226,8 +227,9 @@ __global__ __launch_bounds__(256) void group_prep_kernel(GroupPrep a)
         if (b >= e) { j = i + 1; b0 = e; }
     }
     const TransposeJob J = kernarg_load<TransposeJob>((uint32_t)(offsetof(GroupPrep, tp) + j * sizeof(TransposeJob)));
-    const int bcs = J.C >> 6;
-    transpose_pad_tile(J.src, J.T, J.C, J.dst, (b - b0) / bcs, (b - b0) % bcs, reinterpret_cast<u32x4 *>(gt_lds) + wave * (TRANSPOSE_LDS / 16));
+    const CopyTile c = copy_tile(b - b0, J.Tp >> 6, J.C >> 6, a.copies_per_wg);
+    if (a.copies_per_wg) transpose_pad_tile(J.src, J.T, J.C, J.dst, c.bt, c.bc, reinterpret_cast<u32x4 *>(gt_lds) + wave * (TRANSPOSE_LDS / 16));
+    else transpose_pad_quarter(J.src, J.T, J.C, J.dst, c.bt, c.bc, wave);
 }
 
 // scale_dy_rows (peqa_device.h) for every block of SDY_ROWS token rows.  Workgroups past the last row block do
@@ -508,15 +510,15 @@ hipError_t launch_group_prep(GroupPrep &a, hipStream_t stream)
     }
     const int tp = a.n_tp > 0 ? a.tp[a.n_tp - 1].tile_end : 0;
     if (blocks + tp == 0) return hipSuccess;
-    // Every workgroup of the launch, the tables' among them, has the LDS of the copies': with four tiles five fit a unit, with one as
+    // Every workgroup of the launch, the tables' among them, has the LDS of the copies' (copies_per_wg): with four tiles five fit a unit, with one as
     // many as there are waves for, which is what counts until the copies outlast the tables.  The launch, us, four tiles / one: blocks of
     // d = 2048 in groups of 256, T = 64 (520 tiles) 7.0 / 5.2, T = 128 (1040) 9.0 / 6.6, T = 333 (3120) 11.3 / 10.1, T = 700 (5720) 17.9 / 16.5,
     // T = 1400 (11440) 33.8 / 35.7; d = 4096 in groups of 128, T = 128 (2056) 13.8 / 12.5, T = 333 (6168) 24.9 / 24.8, T = 1400 (22616)
     // 63.1 / 65.3.
-    a.copies_per_wg = tp <= 24 * compute_units() ? 1 : 4;
-    const int tables = table_lds(gmax, a.whole_rows), copies = tp > 0 ? a.copies_per_wg * TRANSPOSE_LDS : 0;
+    a.copies_per_wg = copies_per_wg(tp);
+    const int tables = n > 0 ? table_lds(gmax, a.whole_rows) : 0, copies = a.copies_per_wg * TRANSPOSE_LDS;
     trace_before(KID_GROUP_TABLE, stream);
-    hipLaunchKernelGGL(group_prep_kernel, dim3(blocks + (tp + a.copies_per_wg - 1) / a.copies_per_wg), dim3(256),
+    hipLaunchKernelGGL(group_prep_kernel, dim3(blocks + copies_wgs(tp)), dim3(256),
                        tables > copies ? tables : copies, stream, a);
     trace_after(KID_GROUP_TABLE, stream);
     return hipGetLastError();

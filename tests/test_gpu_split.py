@@ -672,3 +672,31 @@ def test_sums_of_any_number_of_pieces(gpu, oracle, pieces, K):
         Yref = oracle.fwd(codes, s0, ds, z0, X, group)
         Y = gpu.bf16_dev_to_f64(gpu.GpuLayer(W, 4, group).fwd(X, ds))
         assert np.abs(Y - Yref).max() <= Y_TOL * np.abs(Yref).max()
+
+
+@pytest.mark.parametrize("T", [63, 125, 6001, 66049])
+def test_copies_of_few_and_many_tiles(gpu, oracle, T):
+    """The transposed copies by four waves per tile, a tile per workgroup of one wave and four per workgroup, by the number of tiles (6, 12,
+    564, 6198; ragged last tokens), in the launch of their own (scale gradient alone) and beside the tables (both gradients), whose
+    scale gradients are the same bits.  Against fp64: T additions in fp32, rounded
+    at random, are 2^-24 sqrt(T) = 1.6e-5 of the sum off at most; six times that."""
+    import torch
+    from paper_2305_14152_amd import peqa
+    N, K, group, bits = 128, 256, 128, 4
+    W = synth.normal_f32(80200, (N, K), 0.02)
+    layer = gpu.GpuLayer(W, bits, group)
+    codes, s0, z0 = oracle.quantize(W, bits, group)
+    g = torch.Generator(device="cuda").manual_seed(80200 + T)
+    X = torch.randn((T, K), device="cuda", generator=g).bfloat16()
+    dY = torch.randn((T, N), device="cuda", generator=g).bfloat16()
+    got = []
+    for dX in (None, torch.zeros((T, K), dtype=torch.int16, device="cuda")):
+        d_ds = torch.zeros((N, K // group), device="cuda")
+        nb = peqa.workspace_bytes(layer.L, T, peqa.PEQA_OP_BWD)
+        ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+        peqa.linear_bwd(layer.L, layer.packed, layer.s0, None, layer.z0, X.view(torch.int16), dY.view(torch.int16), T, dX, d_ds, ws, nb)
+        got.append(d_ds)
+    assert (got[0] == got[1]).all()
+    q = torch.from_numpy(codes.astype(np.float64)).cuda().view(N, K // group, group) - torch.from_numpy(z0.astype(np.float64)).cuda().view(N, -1, 1)
+    want = ((dY.double().T.contiguous() @ X.double()).view(N, K // group, group) * q).sum(-1)
+    assert ((got[0].double() - want).norm() / want.norm()).item() <= 1e-4
